@@ -1286,12 +1286,27 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tn_bf(GemmTnArgs g) {
         }
 }
 
-// C[i] = sum over the slabs, in slab order
-__global__ void k_sum_splits(const double *__restrict__ part, int splits, long long mn, int n, float *__restrict__ C, long long ldc) {
-    const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= mn) return;
+// C[i] = sum over the slabs.  What bounds it is latency: with one thread per element walking all slabs (768 of them for a small product)
+// a 100 x 47 result kept 19 workgroups busy for 188 us.  A workgroup takes 16 elements (one 128-byte line of a slab) and deals the slabs
+// to 16 lanes each, which keep eight loads in flight; the 16 partial sums are added in lane order through LDS, so the order of the
+// additions is fixed.  100 x 47, 768 slabs: 188 -> 10 us; 602 x 256, 77 slabs: 66 -> under 22 us.
+constexpr int kSumElems = 16, kSumLanes = 16;
+__global__ __launch_bounds__(kSumElems * kSumLanes) void k_sum_splits(const double *__restrict__ part, int splits, long long mn, int n,
+                                                                       float *__restrict__ C, long long ldc) {
+    __shared__ double red[kSumLanes][kSumElems];
+    const int q = threadIdx.x % kSumElems, y = threadIdx.x / kSumElems;
+    const long long e = (long long)blockIdx.x * kSumElems + q;
     double s = 0.0;
-    for (int p = 0; p < splits; ++p) s += part[(size_t)p * (size_t)mn + e];
+    if (e < mn) {
+        const double *src = part + e;
+#pragma unroll 8
+        for (int p = y; p < splits; p += kSumLanes) s += src[(size_t)p * (size_t)mn];
+    }
+    red[y][q] = s;
+    __syncthreads();
+    if (y != 0 || e >= mn) return;
+#pragma unroll
+    for (int u = 1; u < kSumLanes; ++u) s += red[u][q];
     C[(e / n) * ldc + (e % n)] = (float)s;
 }
 
@@ -1570,7 +1585,8 @@ hipError_t launch_gemm_tn(const float *A, int64_t lda, const float *B, int64_t l
     else if (vb) hipLaunchKernelGGL((k_gemm_tn<1, 4>), grid, dim3(kThreads), 0, s, g);
     else hipLaunchKernelGGL((k_gemm_tn<1, 1>), grid, dim3(kThreads), 0, s, g);
     const long long mn = (long long)m * n;
-    hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((mn + 255) / 256)), dim3(256), 0, s, part, splits, mn, n, C, (long long)ldc);
+    hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((mn + kSumElems - 1) / kSumElems)), dim3(kSumElems * kSumLanes), 0, s, part, splits, mn, n, C,
+                       (long long)ldc);
     return hipGetLastError();
 }
 
