@@ -1,0 +1,72 @@
+"""The per-entry kernels that walk the entries of a chunk instead of its rows: row lengths around the chunk length, rows that start and
+end exactly on chunk boundaries, runs of empty and of one-entry rows, a row over more chunks than one lane joins, and a ragged last
+chunk, for each of the four chunk lengths, against fp64 on the host."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from paper_2306_15155_amd import Context
+from paper_2306_15155_amd.binding import chunk_nnz
+
+from gpu_util import DeviceCSR, assert_close, dev
+
+pytestmark = pytest.mark.gpu
+
+N_COLS = 12_000
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = Context(0)
+    yield c
+    torch.cuda.synchronize()
+    c.close()
+
+
+def pattern(t, least):
+    """Row lengths that meet the chunk boundaries of length t in every way, then random short rows up to `least` entries and a ragged end."""
+    rng = np.random.default_rng(t)
+    head = [t, t, 1, 0, t - 1, 0, 0, 2 * t, t + 1, 9 * t + 3, 63, 64, 65] + [1] * 130 + [0] * 70 + [17 * t + 5 if 17 * t + 5 <= N_COLS else N_COLS, 0, 1]
+    rest = max(least - sum(head), 0) + 7
+    tail = rng.integers(0, 90, rest // 30 + 2)
+    cut = int(np.searchsorted(np.cumsum(tail), rest))
+    lens = np.concatenate([head, tail[:cut + 1], [0, 0, 5, 0]]).astype(np.int64)
+    row_ptr = np.concatenate([[0], np.cumsum(lens)])
+    row = np.repeat(np.arange(lens.size), lens)
+    k = np.arange(row_ptr[-1]) - row_ptr[row]
+    step = N_COLS // lens[row]
+    col = k * step + (rng.random(k.size) * step).astype(np.int64)   # ascending and distinct: one column per `step`
+    return synth.CSR(lens.size, max(N_COLS, lens.size), row_ptr.astype(np.int32), col.astype(np.int32))
+
+
+@pytest.mark.parametrize("t,least", [(64, 3_000), (128, 140_000), (256, 270_000), (512, 530_000)])
+def test_flat_walk_at_chunk_boundaries(ctx, t, least):
+    g = pattern(t, least)
+    assert chunk_nnz(g.nnz) == t
+    n, A = g.n_rows, DeviceCSR(g)
+    row = np.repeat(np.arange(n), np.diff(g.row_ptr))
+    s_l, s_r = synth.normal(t, 1, (n,)), synth.normal(t, 2, (g.n_cols,))
+    e = s_l[row].astype(np.float64) + s_r[g.col_idx]
+    e = np.where(e > 0, e, 0.2 * e)
+    got = ctx.sddmm_score(A.s, dev(s_l), dev(s_r))
+    assert_close(got, e, tol=2.0 ** -22, what="logits")   # one fp32 addition and one product
+    m = np.full(n, -np.inf)
+    np.maximum.at(m, row, e)
+    p = np.exp(e - m[row])
+    z = np.zeros(n)
+    np.add.at(z, row, p)
+    # exponents up to 16 (rounded at 2^-24 relative: 1e-6) and about twenty additions per value in the sum (1.2e-6)
+    assert_close(ctx.edge_softmax(A.s, got), p / z[row], tol=4e-6, what="softmax")
+    # two 32-column slices of per-entry dot products, their row sums and the sums of dt over rows of the pattern and of its transpose
+    # (slope 1: the derivative of the score does not jump)
+    gt = synth.transpose(g)
+    f_in, f_out = 24, 40
+    X, W, dY = synth.uniform(t, 3, (g.n_cols, f_in)), synth.glorot(t, 4, f_in, f_out), synth.normal(t, 5, (n, f_out))
+    a_l, a_r = synth.normal(t, 6, (f_out,), 0.0, 0.3), synth.normal(t, 7, (f_out,), 0.0, 0.3)
+    At = DeviceCSR(gt)
+    pos = ctx.transpose_positions(A.s, At.s)
+    want = oracle.gat_backward(n, g.n_cols, g.row_ptr, g.col_idx, X, W, a_l, a_r, dY, slope=1.0)
+    for gpu, ref, what in zip(ctx.gat_backward(A.s, At.s, pos, dev(X), dev(W), dev(a_l), dev(a_r), dev(dY), neg_slope=1.0), want, ("dX", "dW", "da_l", "da_r")):
+        assert_close(gpu, ref, what=what)
