@@ -316,14 +316,11 @@ int run_gcn(const sensei_csr &A, const float *r, const float *c, const sensei_ma
         // rows are gathered often enough to pay for writing it.
         const float *src = X.ptr;
         int64_t ld_src = X.ld;
-        const bool sliced = relayout_pays(A);
-        if (sliced || id == SENSEI_GCN_DYN_AGG) {
+        const bool sliced = id == SENSEI_GCN_DYN_AGG || relayout_pays(A);   // DYN_AGG writes its copy anyway
+        if (sliced) {
             float *T = cv.take<float>((size_t)A.n_cols * pad32(f_in));
-            const float *scale = (id == SENSEI_GCN_DYN_AGG) ? c : nullptr;
-            if (sliced) SENSEI_TRY(launch_to_slices(scale, X.ptr, X.ld, A.n_cols, f_in, T, s));
-            else SENSEI_TRY(launch_row_broadcast(scale, X.ptr, X.ld, A.n_cols, f_in, T, fs, SENSEI_ACT_NONE, s));
+            SENSEI_TRY(launch_to_slices(id == SENSEI_GCN_DYN_AGG ? c : nullptr, X.ptr, X.ld, A.n_cols, f_in, T, s));
             src = T;
-            ld_src = fs;
         }
         const bool scaled = (mode == SENSEI_SPMM_SCALED);
         SENSEI_TRY(spmm_any(A, mode, scaled ? r : nullptr, scaled ? c : nullptr, src, ld_src, f_in, U, fs, f_in, SENSEI_ACT_NONE, plan, carry, s, kt,
@@ -497,10 +494,8 @@ int run_gcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r, 
         float *T = cv.take<float>((size_t)A.n_rows * pad32(f_out));
         float *G = cv.take<float>((size_t)A.n_cols * fo4);
         double *part = cv.take<double>(gemm_tn_bytes(A.n_cols, f_in, f_out) / sizeof(double));
-        // T = r (x) (dY (.) mask), slice-major when the transposed SpMM gathers each row often enough (always between hops)
-        const bool sliced = relayout_pays(At) || k_hops > 1;
-        if (sliced) SENSEI_TRY(launch_to_slices(r, dY.ptr, dY.ld, A.n_rows, f_out, T, s, mask, ldy));
-        else SENSEI_TRY(launch_row_broadcast(r, dY.ptr, dY.ld, A.n_rows, f_out, T, fo4, SENSEI_ACT_NONE, s, mask, ldy));
+        // T = r (x) (dY (.) mask), slice-major: what the transposed SpMM gathers from
+        SENSEI_TRY(launch_to_slices(r, dY.ptr, dY.ld, A.n_rows, f_out, T, s, mask, ldy));
         const float *last = T;
         if (k_hops > 1) {  // inner hops: T <- (r (.) c) (x) (A~^T T)
             float *T2 = cv.take<float>((size_t)A.n_cols * pad32(f_out));
@@ -512,7 +507,7 @@ int run_gcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r, 
         }
         // G = c (x) (A~^T T)
         SENSEI_TRY(spmm_any(At, SENSEI_SPMM_PATTERN, c, nullptr, last, fo4, f_out, G, fo4, f_out, SENSEI_ACT_NONE, plan_t, carry, s, nullptr, false,
-                            nullptr, sliced));
+                            nullptr, true));
         SENSEI_TRY(launch_gemm_tn(X.ptr, X.ld, G, fo4, A.n_cols, f_in, f_out, dW, lddw, part, s));
         if (dX) {
             float *Wt = cv.take<float>((size_t)f_out * pad4(f_in));
@@ -532,9 +527,7 @@ int run_gcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r, 
             SENSEI_TRY(launch_chunk_rows(A, plan, s));
             float *T = cv.take<float>((size_t)A.n_cols * fi32);
             float *Uw = cv.take<float>((size_t)A.n_rows * fi4);
-            const bool sliced = relayout_pays(A) || k_hops > 1;
-            if (sliced) SENSEI_TRY(launch_to_slices(c, X.ptr, X.ld, A.n_cols, f_in, T, s));
-            else SENSEI_TRY(launch_row_broadcast(c, X.ptr, X.ld, A.n_cols, f_in, T, fi4, SENSEI_ACT_NONE, s));
+            SENSEI_TRY(launch_to_slices(c, X.ptr, X.ld, A.n_cols, f_in, T, s));
             const float *last = T;
             if (k_hops > 1) {  // the inner hops of the forward: T <- (r (.) c) (x) (A~ T)
                 float *T2 = cv.take<float>((size_t)A.n_cols * fi32);
@@ -545,7 +538,7 @@ int run_gcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r, 
                 last = buf[(k_hops - 1) & 1];
             }
             SENSEI_TRY(spmm_any(A, SENSEI_SPMM_PATTERN, r, nullptr, last, fi4, f_in, Uw, fi4, f_in, SENSEI_ACT_NONE, plan, carry, s, nullptr, false,
-                                nullptr, sliced));
+                                nullptr, true));
             U = Uw;
             ld_u = fi4;
         }
@@ -555,9 +548,7 @@ int run_gcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r, 
             float *V = cv.take<float>((size_t)A.n_rows * fi32);
             SENSEI_TRY(launch_transpose(W.ptr, W.ld, f_in, f_out, Wt, fi4, s));
             // V = r (x) (dP W^T), written slice-major by the GEMM epilogue; dX = c (x) (A~^T V)
-            const bool sliced = relayout_pays(At) || k_hops > 1;
-            SENSEI_TRY(launch_gemm(dP, fo4, Wt, fi4, V, sliced ? fi32 : fi4, A.n_rows, f_out, f_in, sliced ? fi32 : f_in, SENSEI_ACT_NONE, s, r,
-                                   nullptr, sliced));
+            SENSEI_TRY(launch_gemm(dP, fo4, Wt, fi4, V, fi32, A.n_rows, f_out, f_in, fi32, SENSEI_ACT_NONE, s, r, nullptr, true));
             const float *last = V;
             if (k_hops > 1) {  // inner hops of the transposed chain
                 float *V2 = cv.take<float>((size_t)A.n_cols * fi32);
@@ -568,7 +559,7 @@ int run_gcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r, 
                 last = buf[(k_hops - 1) & 1];
             }
             SENSEI_TRY(spmm_any(At, SENSEI_SPMM_PATTERN, c, nullptr, last, fi4, f_in, dX, lddx, f_in, SENSEI_ACT_NONE, plan_t, carry, s, nullptr, false,
-                                nullptr, sliced));
+                                nullptr, true));
         }
     }
     return SENSEI_OK;

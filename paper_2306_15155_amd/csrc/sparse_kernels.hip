@@ -64,7 +64,7 @@ struct SpmmArgs {
     const float2 *mz;  // softmax mode: per-row (max logit, sum of exp(logit - max))
     int val_stride;    // floats from the value of one entry to the next (1, or 2 when the values sit in (value, other) pairs)
     long long c_tile;  // floats from feature tile t of C to tile t + 1: VEC*LPG for a row-major C, n_rows * 32 for a slice-major one (ldc = 32)
-    int c_tf;          // columns per feature tile (VEC * LPG)
+    int c_tf, c_shift; // columns per feature tile (VEC * LPG, a power of two) and their logarithm
     float *C, *carry;
     long long ldb, ldc;
     long long tile_stride_b;  // bytes from feature tile t of B to tile t + 1: 4*VEC*LPG when rows are contiguous, a whole slice otherwise
@@ -72,6 +72,8 @@ struct SpmmArgs {
     int f, f_store, f_carry, n_tiles, act, store_vec_ok;
     int tiles_live, n_groups;  // feature tiles worked on at the same time; chunk groups (blocks per tile)
     int accumulate, finalize;  // column panels: add to what C holds; apply row scale and activation (last panel only)
+    int fix_quads;      // k_spmm_fixup: groups of four columns per workgroup
+    int scale_weights;  // k_spmm_flat: the row factor (or 1 / z) is applied to the weights of the entries, by every panel pass
     // fused attention mode: the two score vectors, the LeakyReLU slope, and where the (max, sum) pairs of row pieces go
     const float *s_l, *s_r;
     float slope;
@@ -91,9 +93,161 @@ __device__ __forceinline__ float uni_f(float x) { return __int_as_float(__builti
 // 1/z of a softmax row; a row without entries (z = 0) gives 0, never inf
 __device__ __forceinline__ float inv_z(float z) { return z > 0.f ? 1.f / z : 0.f; }
 
-// One wavefront = one (chunk, feature tile).  The 64 lanes form G = 64/LPG
+struct NnzArgs {
+    const int32_t *row_ptr, *col_idx, *chunk_row;
+    int n_rows, nnz, chunk_nnz, n_chunks;
+};
+
+// ---- flat walk: the same chunk ownership, but the lanes walk the entries of the chunk and not its rows
+//
+// Walking a chunk row by row costs one chain of memory round trips per row: on a pattern with 20 entries per row a chunk of 512 entries
+// has 25 rows and more, and the per-entry kernels ran at a tenth of the memory rate (row sum of 2.1 M values: 173 us).  Here a wavefront
+// first marks in LDS where the rows of its chunk start (row pointers read 64 at a time) and spreads the marks by a running maximum, which
+// gives every entry its row; everything after that is independent of where the rows end.  (PAD: words left free after each of PARTS equal parts
+// of the chunk's entries, for a kernel whose lane groups read the same place of their parts at the same time.)  Entries are read in striped order (entry
+// 64 u + lane: coalesced); sums over rows are segmented sums in blocked order (a lane owns PER consecutive entries: they are added in the
+// lane, one scan over the lanes joins the pieces), the values change order through LDS.  PER = chunk_nnz / 64.
+template <int PER, int PAD = 0, int PARTS = 8> __device__ __forceinline__ int flat_at(int p) { return PAD ? p + (p / (64 * PER / PARTS)) * PAD : p; }
+
+template <int PER> struct FlatLds {
+    __attribute__((aligned(16))) int row[kWavesPerBlock][64 * PER];     // row of every entry of the wavefront's chunk
+    __attribute__((aligned(16))) float val[kWavesPerBlock][64 * PER];   // values on their way from striped to blocked order
+};
+
+// LDS written by other lanes of the wavefront is read after this point (the hardware keeps a wavefront's LDS operations in order; the
+// compiler has to be told)
+__device__ __forceinline__ void lds_exchange() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+template <int PER> struct FlatChunk {
+    int lo, hi, i_first, i1;
+    bool cont;              // the first row began in an earlier chunk: its sum goes to the chunk's carry slot
+    int rid[PER];           // rows of this lane's entries in blocked order
+    unsigned starts;        // bit e: blocked entry e of this lane is the first of its row in the chunk
+    int prev_row;           // row of the entry before this lane's first one
+};
+
+// empty(r0, none) is called for every 64 rows of the chunk, by all lanes: `none` says that row r0 + lane is owned and has no entries
+template <int PER, int PAD = 0, int PARTS = 8, class Empty>
+__device__ __forceinline__ FlatChunk<PER> flat_rows(const NnzArgs &a, int chunk, int lane, int *rows, Empty empty) {
+    FlatChunk<PER> c;
+    c.lo = chunk * (64 * PER);
+    c.hi = (a.nnz - c.lo > 64 * PER) ? c.lo + 64 * PER : a.nnz;
+    const int i0 = __builtin_amdgcn_readfirstlane(a.chunk_row[chunk]);
+    c.i1 = __builtin_amdgcn_readfirstlane(a.chunk_row[chunk + 1]);
+    c.cont = (a.nnz > 0) && (__builtin_amdgcn_readfirstlane(a.row_ptr[i0]) > c.lo);
+    c.i_first = c.cont ? i0 - 1 : i0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) rows[flat_at<PER, PAD, PARTS>(u * 64 + lane)] = -1;
+    lds_exchange();
+    for (int r0 = c.i_first; r0 < c.i1; r0 += 64) {
+        const int r = r0 + lane;
+        bool none = false;
+        if (r < c.i1) {
+            const int s = a.row_ptr[r], e = a.row_ptr[r + 1];
+            none = e <= s;
+            if (!none) rows[flat_at<PER, PAD, PARTS>(s > c.lo ? s - c.lo : 0)] = r;   // the rows of a chunk that have entries start at different places
+        }
+        empty(r0, none);
+    }
+    lds_exchange();
+    c.starts = 0u;
+    int top = -1;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+        const int r = rows[flat_at<PER, PAD, PARTS>(lane * PER + e)];
+        c.starts |= (r >= 0 ? 1u : 0u) << e;
+        top = r > top ? r : top;
+        c.rid[e] = top;
+    }
+    int run = top;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(run, off, 64);
+        if (lane >= off) run = o > run ? o : run;
+    }
+    c.prev_row = __shfl_up(run, 1, 64);
+    if (lane == 0) c.prev_row = -1;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+        c.rid[e] = c.rid[e] > c.prev_row ? c.rid[e] : c.prev_row;
+        rows[flat_at<PER, PAD, PARTS>(lane * PER + e)] = c.rid[e];
+    }
+    lds_exchange();
+    return c;
+}
+
+// Segmented sum of v (blocked order; entries past the end of the chunk hold 0): write(row, sum, place of the piece's last entry) once per
+// row piece of the chunk.
+// A lane's entries fall into a head (up to its first row start), whole rows, and a tail; the heads are completed by the scan.
+template <int PER, class Write>
+__device__ __forceinline__ void flat_sum(const FlatChunk<PER> &c, int lane, const float (&v)[PER], Write write) {
+    float head = 0.f, run = 0.f;
+    int head_end = 0;
+    bool started = false;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+        if ((c.starts >> e) & 1u) {
+            if (started) write(c.rid[e > 0 ? e - 1 : 0], run, lane * PER + e - 1);
+            else { head = run; head_end = lane * PER + e - 1; }
+            started = true;
+            run = 0.f;
+        }
+        run += v[e];
+    }
+    float tail = run;
+    int f = started;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const float o = __shfl_up(tail, off, 64);
+        const int of = __shfl_up(f, off, 64);
+        if (lane >= off) {
+            if (!f) tail += o;
+            f |= of;
+        }
+    }
+    const float before = __shfl_up(tail, 1, 64);   // the open row piece of the lanes before this one
+    const int head_row = (c.starts & 1u) ? c.prev_row : c.rid[0];
+    if (started && head_row >= 0 && lane > 0) write(head_row, before + head, head_end);
+    if (lane == 63) write(c.rid[PER - 1], tail, c.hi - c.lo - 1);
+}
+
+// A value per row for entries in striped order.  Chunks of at most 64 rows keep the values of their rows in the lanes' registers and hand
+// them out by cross-lane reads; the others gather them (a gather costs the vector cache path what the entry's own gather costs:
+// statistics pass on 98,000 rows of 1,021 entries 0.73 ms with it, 0.48 without).
+struct RowVals {
+    bool in_lanes;
+    int i_first;
+    float x;
+    const float *src;
+};
+template <int PER>
+__device__ __forceinline__ RowVals row_vals(const FlatChunk<PER> &c, int lane, const float *__restrict__ src) {
+    RowVals v;
+    v.in_lanes = c.i1 - c.i_first <= 64;
+    v.i_first = c.i_first;
+    v.src = src;
+    v.x = (v.in_lanes && c.i_first + lane < c.i1) ? src[c.i_first + lane] : 0.f;
+    return v;
+}
+__device__ __forceinline__ float row_val(const RowVals &v, int row) { return v.in_lanes ? lane_read((row - v.i_first) * 4, v.x) : v.src[row]; }
+
+// values from striped to blocked order (val[] of the wavefront)
+template <int PER>
+__device__ __forceinline__ void to_blocked(float *val, int lane, const float (&striped)[PER], float (&blocked)[PER]) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) val[u * 64 + lane] = striped[u];
+    lds_exchange();
+#pragma unroll
+    for (int e = 0; e < PER; ++e) blocked[e] = val[lane * PER + e];
+}
+
+// SpMM on a row-major operand whose rows allow only 8- or 4-byte loads (odd leading dimension or width); everything else takes
+// k_spmm_flat below.  One wavefront = one (chunk, feature tile).  The 64 lanes form G = 64/LPG
 // neighbour groups of LPG lanes; a group reads VEC*LPG consecutive floats of
-// one neighbour row per step (one 128-byte line at the default shape), so G
+// one neighbour row per step, so G
 // neighbours are in flight per step and 4 steps are issued back to back.
 // Column indices (and weights) are fetched 64 at a time, one per lane, and
 // handed to the groups by cross-lane reads.  The inner loop carries no
@@ -103,12 +257,9 @@ __device__ __forceinline__ float inv_z(float z) { return z > 0.f ? 1.f / z : 0.f
 // 4 GiB with fewer than 2^24 rows of fewer than 2^24 bytes, and addresses are
 // a uniform base plus a 32-bit byte offset formed by one 24-bit multiply-add.
 // Consecutive workgroups go to consecutive XCDs and take consecutive tiles of
-// the live tile set, so each XCD's L2 keeps seeing the same 128-byte slice of
+// the live tile set, so each XCD's L2 keeps seeing the same slice of
 // the gathered matrix; the number of live tiles bounds how much of that matrix
-// is in use at one time.  B is either row-major (a row holds all its tiles) or
-// slice-major (all rows of tile 0, then all rows of tile 1, ...: what an XCD
-// gathers from is then one contiguous range, which spreads evenly over the
-// memory channels whatever the row pitch).
+// is in use at one time.
 // MODE kSpmmSoftmax: `val` holds attention logits; the weight of an entry is exp(logit - m_i) and the row is
 // scaled by 1/z_i when it is complete, so the normalised attention weights are never stored (Eq. 6).
 // MODE kSpmmAttnFused: score, softmax and weighted sum in one walk (Eq. 5-6 with nothing stored per entry): the logit
@@ -116,9 +267,6 @@ __device__ __forceinline__ float inv_z(float z) { return z > 0.f ? 1.f / z : 0.f
 // maximum m, the sum z of exp(logit - m) and its partial row relative to m, rescaling both when the maximum grows; the
 // lanes' (m, z, row) triples are merged when the row (piece) ends.  A piece of a row that spans chunks leaves its pair
 // beside its partial row (mz_out / carry_mz) and k_spmm_fixup_attn merges the pieces in chunk order.
-// MODES kSpmmSignSum, kSpmmLreluSum (slice-major operands, 32-column tiles): the gathered row meets a vector of the output row itself,
-// u = self[i, :] + B[j, :], and what is summed is val_ij LeakyReLU'(u) or val_ij LeakyReLU(u), column by column: the reductions
-// of the backward pass of a score with a vector per entry.
 template <int VEC, int LPG, int MODE, bool OFF32>
 __global__ __launch_bounds__(kBlock) void k_spmm(SpmmArgs a) {
     constexpr int G = 64 / LPG;
@@ -163,15 +311,6 @@ __global__ __launch_bounds__(kBlock) void k_spmm(SpmmArgs a) {
     if (MODE == kSpmmSoftmax) m_row = uni_f((i < a.n_rows) ? a.mz[i].x : 0.f);
     if (MODE == kSpmmAttnFused) m_row = uni_f((i < a.n_rows) ? a.s_l[i] : 0.f);
     float m_run = -INFINITY, z_run = 0.f;  // fused attention mode: this lane's running maximum and sum of exp(logit - maximum)
-    constexpr bool kSelfMode = (MODE == kSpmmSignSum || MODE == kSpmmLreluSum);
-    const float *self_lane = nullptr;   // this lane's columns of row 0 of the per-row vector
-    Vec<VEC> self_v;
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) self_v.v[e] = 0.f;
-    if (kSelfMode) {
-        self_lane = a.self + (size_t)tile * a.self_tile + (fok ? (lane % LPG) * VEC : 0);
-        if (i < a.n_rows) self_v = Vec<VEC>::load(self_lane + (size_t)i * 32);
-    }
 
     Vec<VEC> acc;
 #pragma unroll
@@ -188,15 +327,6 @@ __global__ __launch_bounds__(kBlock) void k_spmm(SpmmArgs a) {
 #pragma unroll
             for (int e = 0; e < VEC; ++e) acc.v[e] = fmaf(acc.v[e], keep, p * b.v[e]);
             m_run = mn;
-            return;
-        }
-        if (kSelfMode) {
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-                const float u = self_v.v[e] + b.v[e];
-                const float d = u > 0.f ? 1.f : a.slope;
-                acc.v[e] = fmaf(ww, MODE == kSpmmSignSum ? d : d * u, acc.v[e]);
-            }
             return;
         }
 #pragma unroll
@@ -292,10 +422,6 @@ __global__ __launch_bounds__(kBlock) void k_spmm(SpmmArgs a) {
             for (int e = 0; e < VEC; ++e) racc.v[e] = 0.f;
             float rm = -INFINITY, rz = 0.f;  // fused attention mode: running maximum and sum of the group's row
             const float sl_g = (MODE == kSpmmAttnFused && rok) ? a.s_l[row] : 0.f;
-            Vec<VEC> self_g;
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) self_g.v[e] = 0.f;
-            if (kSelfMode && rok) self_g = Vec<VEC>::load(self_lane + (size_t)row * 32);
             for (int k = rs; k < rend; k += U) {
                 Vec<VEC> b[U];
                 float ww[U];
@@ -305,7 +431,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm(SpmmArgs a) {
                     const int kq = valid ? k + q : k;
                     const int j = a.col_idx[kq];
                     float wq = 1.f;
-                    if (MODE == SENSEI_SPMM_WEIGHTED || kSelfMode) wq = a.val[(size_t)kq * a.val_stride];
+                    if (MODE == SENSEI_SPMM_WEIGHTED) wq = a.val[(size_t)kq * a.val_stride];
                     if (MODE == SENSEI_SPMM_SCALED) wq = a.c[j];
                     if (MODE == kSpmmSoftmax) wq = __expf(a.val[(size_t)kq * a.val_stride] - mz_g.x);
                     if (MODE == kSpmmAttnFused) {
@@ -335,15 +461,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm(SpmmArgs a) {
 #pragma unroll
                 for (int q = 0; q < U; ++q) {
 #pragma unroll
-                    for (int e = 0; e < VEC; ++e) {
-                        if (kSelfMode) {
-                            const float u = self_g.v[e] + b[q].v[e];
-                            const float d = u > 0.f ? 1.f : a.slope;
-                            racc.v[e] = fmaf(ww[q], MODE == kSpmmSignSum ? d : d * u, racc.v[e]);
-                        } else {
-                            racc.v[e] = fmaf(ww[q], b[q].v[e], racc.v[e]);
-                        }
-                    }
+                    for (int e = 0; e < VEC; ++e) racc.v[e] = fmaf(ww[q], b[q].v[e], racc.v[e]);
                 }
             }
             if (MODE == kSpmmAttnFused && rok && tile == 0 && (lane % LPG) == 0) {
@@ -394,7 +512,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm(SpmmArgs a) {
         float w = 0.f;
         if (k < hi) {
             col = a.col_idx[k];
-            if (MODE == SENSEI_SPMM_WEIGHTED || MODE == kSpmmSoftmax || kSelfMode) w = a.val[(size_t)k * a.val_stride];
+            if (MODE == SENSEI_SPMM_WEIGHTED || MODE == kSpmmSoftmax) w = a.val[(size_t)k * a.val_stride];
             if (MODE == SENSEI_SPMM_SCALED) w = a.c[col];
             if (MODE == kSpmmAttnFused) w = a.s_r[col];
         }
@@ -407,7 +525,6 @@ __global__ __launch_bounds__(kBlock) void k_spmm(SpmmArgs a) {
                 re = uni(a.row_ptr[i + 1]);
                 if (MODE == kSpmmSoftmax) m_row = uni_f(a.mz[i].x);
                 if (MODE == kSpmmAttnFused) m_row = uni_f(a.s_l[i]);
-                if (kSelfMode) self_v = Vec<VEC>::load(self_lane + (size_t)i * 32);
             }
             const int seg_hi = uni(re < bhi ? re : bhi);
             const int u0 = uni(pos - base), n = uni(seg_hi - pos);
@@ -461,74 +578,450 @@ __global__ __launch_bounds__(kBlock) void k_spmm(SpmmArgs a) {
     }
 }
 
-// Adds the carry slots of a row that spans several chunks to its output row, in chunk order,
-// then applies the row scale and the activation.  One wavefront per chunk; only the chunk that
-// holds the first continuation of a row does the work for that row.
-__global__ __launch_bounds__(kBlock) void k_spmm_fixup(SpmmArgs a) {
-    const int c = 1 + blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-    if (c >= a.n_chunks) return;
-    const int lane = threadIdx.x & 63;
+// SpMM as a flat walk.  k_spmm walks the rows of its chunk one after the other, two or three dependent memory round trips each: with 20
+// entries per row a chunk of 512 entries is a chain of 75 round trips (2.1 M entries x 32 columns: 67 us).  Here the chunk's entries are cut
+// into eight equal parts, one per group of eight lanes, whatever rows they belong to; a group gathers its entries in order, eight in
+// flight, and closes a row where the entry's flag (the sign bit of its column in LDS) says that it is the row's last one in the chunk.
+// The first row a group closes and what it has left at the end are joined over the groups by a scan; rows in between are written
+// directly.  Rows (by the marks of flat_rows), columns, weights and row factors are in LDS before the loop, so that the loop waits for
+// gathers only.  Tiles, chunk ownership, carry slots and fix-up are those of k_spmm.
+// kSpmmAttnFused: the logits of the chunk are formed before the loop, and with them the maximum and the sum of every row piece
+// (segmented scans), so that the loop is a plain weighted sum.
+// kSpmmSignSum, kSpmmLreluSum (slice-major operands): the gathered row meets a vector of the output row itself, u = self[i, :] + B[j, :],
+// and what is summed is val_ij LeakyReLU'(u) or val_ij LeakyReLU(u), column by column: the reductions of the backward pass of a score
+// with a vector per entry.  The own vectors are gathered per entry while rows change and kept in registers where none does.
+// B is row-major (a row holds all its 32-column tiles) or slice-major (all rows of tile 0, then all rows of tile 1, ...: what an XCD
+// gathers from is then one contiguous range, which spreads evenly over the memory channels whatever the row pitch).
+template <int MODE, int PER, int LPG, bool OFF32>
+__global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
+    constexpr bool kSelf = MODE == kSpmmSignSum || MODE == kSpmmLreluSum;
+    constexpr int G = 64 / LPG, T = 64 * PER, PART = T / G, PAD = 4, U = kSelf ? 4 : 8;
+    constexpr bool kWeights = MODE != SENSEI_SPMM_PATTERN;
+    // where entries have weights the row factor goes into them (launch_spmm tells the fix-up so); a third array in LDS would cost a
+    // third of the wavefronts
+    constexpr bool kScaleRows = MODE == SENSEI_SPMM_PATTERN || MODE == kSpmmAttnFused;
+    __shared__ __attribute__((aligned(16))) int s_col[kWavesPerBlock][T + G * PAD];
+    __shared__ __attribute__((aligned(16))) int s_row[kWavesPerBlock][T + G * PAD];
+    __shared__ __attribute__((aligned(16))) float s_scale[kScaleRows ? kWavesPerBlock : 1][kScaleRows ? T + G * PAD : 4];
+    __shared__ __attribute__((aligned(16))) float s_w[kWeights ? kWavesPerBlock : 1][kWeights ? T + G * PAD : 4];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane / LPG, li = lane % LPG;
+    const int per_set = a.n_groups * a.tiles_live;
+    const int set = blockIdx.x / per_set, in_set = blockIdx.x % per_set;
+    const int tile = set * a.tiles_live + in_set % a.tiles_live;
+    if (tile >= a.n_tiles) return;
+    const int chunk = (in_set / a.tiles_live) * kWavesPerBlock + __builtin_amdgcn_readfirstlane(wave);
+    if (chunk >= a.n_chunks) return;
+    const int f0 = tile * (4 * LPG) + li * 4;
+    const bool fok = f0 < a.f;
+    const char *Bb = reinterpret_cast<const char *>(a.B) + (long long)tile * a.tile_stride_b;
+    const unsigned f0_b = fok ? (unsigned)li * 16u : 0u;
+    float *c_lane = a.C + (size_t)tile * a.c_tile + li * 4;   // this lane's columns of row 0 of C
+    const unsigned ldb_b32 = (unsigned)(a.ldb * 4);
+    const size_t ldb_b64 = (size_t)a.ldb * 4;
+    auto gather = [&](int j) -> float4 {
+        if (OFF32) return *reinterpret_cast<const float4 *>(Bb + (__umul24((unsigned)j, ldb_b32) + f0_b));
+        return *reinterpret_cast<const float4 *>(Bb + ((size_t)j * ldb_b64 + f0_b));
+    };
+    int *rows = s_row[wave], *cols = s_col[wave];
+    float *scale = s_scale[kScaleRows ? wave : 0], *wgt = s_w[kWeights ? wave : 0];
+
+    int cont_row = -1, open_row = -1;   // the row continued from the chunk before; the row that goes on in the next chunk
+    auto write_row = [&](int row, float sc, float4 v) {
+        if (row == cont_row) {
+            if (fok) *reinterpret_cast<float4 *>(a.carry + (size_t)chunk * a.f_carry + f0) = v;
+            return;
+        }
+        float *dst = c_lane + (size_t)row * a.ldc;
+        const bool vec = a.store_vec_ok && f0 + 4 <= a.f_store;
+        if (a.accumulate) {   // later column panel: add to what the earlier panels left in C
+            if (vec) {
+                const float4 o = *reinterpret_cast<const float4 *>(dst);
+                v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+            } else {
+                if (f0 < a.f_store) v.x += dst[0];
+                if (f0 + 1 < a.f_store) v.y += dst[1];
+                if (f0 + 2 < a.f_store) v.z += dst[2];
+                if (f0 + 3 < a.f_store) v.w += dst[3];
+            }
+        }
+        if (a.finalize && row != open_row) {
+            v.x *= sc; v.y *= sc; v.z *= sc; v.w *= sc;
+            if (a.act == SENSEI_ACT_RELU) {
+                v.x = v.x > 0.f ? v.x : 0.f; v.y = v.y > 0.f ? v.y : 0.f; v.z = v.z > 0.f ? v.z : 0.f; v.w = v.w > 0.f ? v.w : 0.f;
+            }
+        }
+        if (vec) {
+            *reinterpret_cast<float4 *>(dst) = v;
+        } else {
+            if (f0 < a.f_store) dst[0] = v.x;
+            if (f0 + 1 < a.f_store) dst[1] = v.y;
+            if (f0 + 2 < a.f_store) dst[2] = v.z;
+            if (f0 + 3 < a.f_store) dst[3] = v.w;
+        }
+    };
+    const NnzArgs nz = {a.row_ptr, a.col_idx, a.chunk_row, a.n_rows, a.nnz, a.chunk_nnz, a.n_chunks};
+    const FlatChunk<PER> c = flat_rows<PER, PAD, G>(nz, chunk, lane, rows, [&](int r0, bool none) {
+        unsigned long long m = __ballot(none);
+        for (int b = 0; m; ++b, m >>= G) {   // rows without entries: one per group at a time
+            if (!((m >> g) & 1ull)) continue;
+            const int row = r0 + b * G + g;
+            write_row(row, MODE == SENSEI_SPMM_PATTERN && a.r ? a.r[row] : 1.f, make_float4(0.f, 0.f, 0.f, 0.f));
+        }
+    });
+    if (c.lo >= c.hi) return;
+    const int n = c.hi - c.lo;
+    if (c.cont) cont_row = c.i_first;
+    {   // the last entry of every row piece is flagged (sign bit of its row for now)
+        const int next_start = __shfl_down((int)(c.starts & 1u), 1, 64);
+        unsigned ends = (c.starts >> 1) | ((lane < 63 ? (unsigned)next_start : 0u) << (PER - 1));
+        const int e_last = n - 1 - lane * PER;
+        if (e_last >= 0 && e_last < PER) ends |= 1u << e_last;
+#pragma unroll
+        for (int e = 0; e < PER; ++e) rows[flat_at<PER, PAD, G>(lane * PER + e)] = (int)((unsigned)c.rid[e] | (((ends >> e) & 1u) << 31));
+        const int last_row = __shfl(c.rid[PER - 1], 63, 64);
+        if (__builtin_amdgcn_readfirstlane(a.row_ptr[last_row + 1]) > c.hi) open_row = __builtin_amdgcn_readfirstlane(last_row);
+    }
+    lds_exchange();
+    const bool use_scale = MODE == kSpmmSoftmax ? a.scale_weights != 0 : MODE != kSpmmAttnFused && a.r && (kWeights ? a.scale_weights != 0 : a.finalize != 0);
+    {
+        float es[PER];
+        int col[PER], rw[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int k = c.lo + u * 64 + lane;
+            const size_t kc = k < c.hi ? k : c.lo;
+            col[u] = a.col_idx[kc];
+            if (MODE == SENSEI_SPMM_WEIGHTED || MODE == kSpmmSoftmax || kSelf) es[u] = a.val[kc * a.val_stride];
+        }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int at = flat_at<PER, PAD, G>(u * 64 + lane);
+            rw[u] = rows[at];
+            cols[at] = (int)((unsigned)col[u] | ((unsigned)rw[u] & 0x80000000u));
+            rw[u] &= 0x7fffffff;
+            if (MODE == SENSEI_SPMM_SCALED) es[u] = a.c[col[u]];
+            if (MODE == kSpmmAttnFused) es[u] = a.s_r[col[u]];
+        }
+        if (MODE == kSpmmSoftmax) {
+            // (max, sum) pairs of the rows; gathered per entry where the chunk has more rows than lanes
+            const bool in_lanes = c.i1 - c.i_first <= 64;
+            float2 st = make_float2(0.f, 0.f);
+            if (in_lanes && c.i_first + lane < c.i1) st = a.mz[c.i_first + lane];
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                float2 p;
+                if (in_lanes) p = make_float2(lane_read((rw[u] - c.i_first) * 4, st.x), lane_read((rw[u] - c.i_first) * 4, st.y));
+                else p = a.mz[rw[u]];
+                es[u] = __expf(es[u] - p.x);
+                if (use_scale) es[u] *= inv_z(p.y);
+            }
+        } else if (use_scale) {
+            const RowVals rv = row_vals<PER>(c, lane, a.r);
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const float x = row_val(rv, rw[u]);
+                if (kWeights) es[u] *= x;
+                else scale[flat_at<PER, PAD, G>(u * 64 + lane)] = x;
+            }
+        }
+        if (MODE == kSpmmAttnFused) {
+            const RowVals rv = row_vals<PER>(c, lane, a.s_l);
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const float t = row_val(rv, rw[u]) + es[u];
+                es[u] = t > 0.f ? t : a.slope * t;
+            }
+        }
+        if (kWeights) {
+#pragma unroll
+            for (int u = 0; u < PER; ++u) wgt[flat_at<PER, PAD, G>(u * 64 + lane)] = es[u];
+        }
+    }
+    lds_exchange();
+    if (MODE == kSpmmAttnFused) {
+        // the maximum over every row piece, for each of its entries: inside the lane, then what lies before the lane (forward scan of the
+        // tails) and behind it (backward scan of the heads)
+        float e[PER], mx[PER], p[PER];
+        const int n_mine = n - lane * PER;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            e[q] = q < n_mine ? wgt[flat_at<PER, PAD, G>(lane * PER + q)] : -INFINITY;
+            mx[q] = (q > 0 && !((c.starts >> q) & 1u)) ? fmaxf(mx[q > 0 ? q - 1 : 0], e[q]) : e[q];
+        }
+#pragma unroll
+        for (int q = PER - 2; q >= 0; --q)
+            if (!((c.starts >> (q + 1)) & 1u)) mx[q] = mx[q + 1];
+        float fwd = mx[PER - 1], bwd = (c.starts & 1u) ? -INFINITY : mx[0];
+        int ff = c.starts != 0u, fb = ff;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const float of = __shfl_up(fwd, off, 64), ob = __shfl_down(bwd, off, 64);
+            const int gf = __shfl_up(ff, off, 64), gb = __shfl_down(fb, off, 64);
+            if (lane >= off) {
+                if (!ff) fwd = fmaxf(fwd, of);
+                ff |= gf;
+            }
+            if (lane + off < 64) {
+                if (!fb) bwd = fmaxf(bwd, ob);
+                fb |= gb;
+            }
+        }
+        float before = __shfl_up(fwd, 1, 64), behind = __shfl_down(bwd, 1, 64);
+        if (lane == 0) before = -INFINITY;
+        if (lane == 63) behind = -INFINITY;
+        bool open = true;   // entries up to the lane's first row start belong to a piece that began before the lane
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            if ((c.starts >> q) & 1u) open = false;
+            if (open) mx[q] = fmaxf(mx[q], before);
+            if ((c.starts >> q) < 2u) mx[q] = fmaxf(mx[q], behind);   // no row starts after entry q: its piece goes on behind the lane
+            p[q] = q < n_mine ? __expf(e[q] - mx[q]) : 0.f;
+            wgt[flat_at<PER, PAD, G>(lane * PER + q)] = p[q];
+            scale[flat_at<PER, PAD, G>(lane * PER + q)] = mx[q];
+        }
+        lds_exchange();
+        flat_sum<PER>(c, lane, p, [&](int i, float z, int end) {
+            const int at = flat_at<PER, PAD, G>(end);
+            if (tile == 0) {   // every feature tile of the chunk forms the same pairs: one writes them
+                if (i == cont_row) a.carry_mz[chunk] = make_float2(scale[at], z);
+                else if (i == open_row) a.mz_out[i] = make_float2(scale[at], z);
+            }
+            scale[at] = inv_z(z);
+        });
+        lds_exchange();
+    }
+
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), head = acc;
+    int head_at = -1;
+    const int part0 = g * (PART + PAD);
+    const float *self_lane = kSelf ? a.self + (size_t)tile * a.self_tile + (fok ? li * 4 : 0) : nullptr;
+    float4 self_cur = acc;   // the output row's own vector, for the row of the last entry seen
+    int self_row = -1;
+    for (int s = 0; s < PART && s < n; s += U) {
+        float4 sv[kSelf ? U : 1];
+        if (kSelf) {
+            const int4 r4 = *reinterpret_cast<const int4 *>(&rows[part0 + s]);
+            if (__all((r4.w & 0x7fffffff) == self_row)) {   // (rows ascend) every group stays in its row
+#pragma unroll
+                for (int q = 0; q < (kSelf ? U : 1); ++q) sv[q] = self_cur;
+            } else {
+                const int r[4] = {r4.x, r4.y, r4.z, r4.w};
+#pragma unroll
+                for (int q = 0; q < (kSelf ? U : 1); ++q) sv[q] = *reinterpret_cast<const float4 *>(self_lane + (size_t)(r[q] & 0x7fffffff) * 32);
+                self_row = r4.w & 0x7fffffff;
+                self_cur = sv[kSelf ? U - 1 : 0];
+            }
+        }
+        int cf[U];
+        float w[U];
+        float4 b[U];
+#pragma unroll
+        for (int q = 0; q < U; q += 4) {
+            const int4 t = *reinterpret_cast<const int4 *>(&cols[part0 + s + q]);
+            cf[q] = t.x; cf[q + 1] = t.y; cf[q + 2] = t.z; cf[q + 3] = t.w;
+            if (kWeights) {
+                const float4 v = *reinterpret_cast<const float4 *>(&wgt[part0 + s + q]);
+                w[q] = v.x; w[q + 1] = v.y; w[q + 2] = v.z; w[q + 3] = v.w;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) b[q] = gather(cf[q] & 0x7fffffff);
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            if (kSelf) {
+                auto term = [&](float own, float x) {
+                    const float t = own + x, d = t > 0.f ? 1.f : a.slope;
+                    return MODE == kSpmmSignSum ? d : d * t;
+                };
+                const float4 o = sv[kSelf ? q : 0];
+                acc.x = fmaf(w[q], term(o.x, b[q].x), acc.x); acc.y = fmaf(w[q], term(o.y, b[q].y), acc.y);
+                acc.z = fmaf(w[q], term(o.z, b[q].z), acc.z); acc.w = fmaf(w[q], term(o.w, b[q].w), acc.w);
+            } else if (kWeights) {
+                acc.x = fmaf(w[q], b[q].x, acc.x); acc.y = fmaf(w[q], b[q].y, acc.y); acc.z = fmaf(w[q], b[q].z, acc.z); acc.w = fmaf(w[q], b[q].w, acc.w);
+            } else {
+                acc.x += b[q].x; acc.y += b[q].y; acc.z += b[q].z; acc.w += b[q].w;
+            }
+            if (cf[q] < 0) {
+                const int at = part0 + s + q;
+                if (head_at < 0) {
+                    head = acc;
+                    head_at = at;
+                } else {
+                    write_row(rows[at] & 0x7fffffff, kScaleRows && (use_scale || MODE == kSpmmAttnFused) ? scale[at] : 1.f, acc);
+                }
+                acc = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+        }
+    }
+    int f = head_at >= 0;
+    float4 in = acc;
+#pragma unroll
+    for (int off = LPG; off < 64; off <<= 1) {
+        const float x = __shfl_up(in.x, off, 64), y = __shfl_up(in.y, off, 64), z = __shfl_up(in.z, off, 64), w = __shfl_up(in.w, off, 64);
+        const int of = __shfl_up(f, off, 64);
+        if (lane >= off) {
+            if (!f) { in.x += x; in.y += y; in.z += z; in.w += w; }
+            f |= of;
+        }
+    }
+    in = make_float4(__shfl_up(in.x, LPG, 64), __shfl_up(in.y, LPG, 64), __shfl_up(in.z, LPG, 64), __shfl_up(in.w, LPG, 64));
+    if (head_at >= 0) {
+        if (g > 0) { head.x += in.x; head.y += in.y; head.z += in.z; head.w += in.w; }
+        write_row(rows[head_at] & 0x7fffffff, kScaleRows && (use_scale || MODE == kSpmmAttnFused) ? scale[head_at] : 1.f, head);
+    }
+}
+
+// First chunk of a row that spans several chunks, seen from the chunk c that holds its first continuation: returns the row, or -1 where
+// chunk c starts with a row of its own or continues a row that an earlier chunk already continued; c_last: last chunk of the row.
+__device__ __forceinline__ int continued_row(const NnzArgs &a, int c, int &c_last) {
     const long long lo = (long long)c * a.chunk_nnz;
     const int i0 = a.chunk_row[c];
-    if ((long long)a.row_ptr[i0] <= lo) return;  // a row starts exactly at the boundary
+    if ((long long)a.row_ptr[i0] <= lo) return -1;
     const int i = i0 - 1;
-    const long long rs = a.row_ptr[i];
-    if (rs < lo - a.chunk_nnz) return;  // the row began before the previous chunk: not its first continuation
-    const int re = a.row_ptr[i + 1];
-    const int c_last = (re - 1) / a.chunk_nnz;
-    const float sc = a.mz ? inv_z(a.mz[i].y) : (a.r ? a.r[i] : 1.f);
-    const int tf = a.c_tf;
-    // four columns per lane at a time: a hub row spans a hundred chunks, and one chain of dependent adds per column would
-    // leave the wavefront waiting for one load after the other; every column still adds its slots in chunk order
-    for (int f0 = lane; f0 < a.f_store; f0 += 4 * 64) {
-        float acc[4];
-        float *dst[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int f = f0 + 64 * q;
-            dst[q] = a.C + (size_t)(f / tf) * a.c_tile + (size_t)i * a.ldc + (f % tf);
-            acc[q] = f < a.f_store ? *dst[q] : 0.f;
+    if ((long long)a.row_ptr[i] < lo - a.chunk_nnz) return -1;
+    c_last = (a.row_ptr[i + 1] - 1) / a.chunk_nnz;
+    return i;
+}
+
+// Rows that span several chunks, one lane per chunk: a row of up to kFixupSerial pieces is finished by the lane of its first continuation
+// (serial(i, c, c_last)), a longer one by the whole wavefront (wide(i, c, c_last), uniform arguments; a hub row of 109,000 entries has 213
+// pieces).  One wavefront per chunk instead costs three dependent loads per wavefront: 58 us against 12 on 195,000 chunks.
+constexpr int kFixupSerial = 8;
+template <class Serial, class Wide>
+__device__ __forceinline__ void fixup_rows(const NnzArgs &a, Serial serial, Wide wide) {
+    const int c = 1 + blockIdx.x * blockDim.x + threadIdx.x;
+    int c_last = 0, i = -1;
+    if (c < a.n_chunks) i = continued_row(a, c, c_last);
+    const bool is_long = i >= 0 && c_last - c >= kFixupSerial;
+    if (i >= 0 && !is_long) serial(i, c, c_last);
+    unsigned long long todo = __ballot(is_long);
+    while (todo) {
+        const int l = __ffsll((long long)todo) - 1;
+        todo &= todo - 1;
+        wide(__builtin_amdgcn_readlane(i, l), __builtin_amdgcn_readlane(c, l), __builtin_amdgcn_readlane(c_last, l));
+    }
+}
+
+// Adds the carry slots of the rows that span several chunks to their output rows, then applies the row scale and the activation.  A
+// wavefront looks for such rows in kFixupChunks chunks (one per lane) and then spreads (row, four columns) pairs over its lanes; rows of
+// more than kFixupSerial pieces are summed by eight groups of lanes that take the pieces in turn and are added in group order.
+// blockIdx.y: the columns are dealt out 128 at a time, 32 where there are few chunks.  Bound by the traffic of the rows and slots: with one wavefront per chunk, each
+// waiting for four dependent loads, 248,000 chunks x 512 columns took 0.85 ms, now 0.2 ms; with 64 chunks a wavefront a graph of 4,100
+// chunks keeps too few wavefronts busy (20 us instead of 7).
+constexpr int kFixupChunks = 8;
+struct FixupRows {
+    int i, c, c_last;            // this lane's chunk: the row it continues first (-1: none) and that row's last chunk
+    unsigned long long serial, wide;
+    int n_serial;
+};
+struct FixupLds { int row[kWavesPerBlock][kFixupChunks], first[kWavesPerBlock][kFixupChunks], last[kWavesPerBlock][kFixupChunks]; };
+__device__ __forceinline__ FixupRows fixup_find(const SpmmArgs &a, FixupLds &lds, int wave, int lane) {
+    const NnzArgs nz = {a.row_ptr, a.col_idx, a.chunk_row, a.n_rows, a.nnz, a.chunk_nnz, a.n_chunks};
+    FixupRows r;
+    r.c = 1 + (blockIdx.x * kWavesPerBlock + wave) * kFixupChunks + lane;
+    r.c_last = 0;
+    r.i = -1;
+    if (lane < kFixupChunks && r.c < a.n_chunks) r.i = continued_row(nz, r.c, r.c_last);
+    const bool is_long = r.i >= 0 && r.c_last - r.c >= kFixupSerial;
+    r.serial = __ballot(r.i >= 0 && !is_long);
+    r.wide = __ballot(is_long);
+    r.n_serial = __popcll(r.serial);
+    if (r.i >= 0 && !is_long) {
+        const int at = __popcll(r.serial & ((1ull << lane) - 1));
+        lds.row[wave][at] = r.i;
+        lds.first[wave][at] = r.c;
+        lds.last[wave][at] = r.c_last;
+    }
+    lds_exchange();
+    return r;
+}
+
+__global__ __launch_bounds__(kBlock) void k_spmm_fixup(SpmmArgs a) {
+    __shared__ FixupLds lds;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const FixupRows fr = fixup_find(a, lds, wave, lane);
+    unsigned long long wide = fr.wide;
+    const int q0 = blockIdx.y * a.fix_quads, n_q = min((a.f_store + 3) / 4 - q0, a.fix_quads);   // quads of columns of this workgroup
+    auto add4 = [](float4 &x, const float4 &y) { x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w; };
+    const bool vec_ok = a.store_vec_ok && a.ldc % 4 == 0 && (reinterpret_cast<uintptr_t>(a.C) & 15) == 0;
+    // a quad of columns never straddles feature tiles (c_tf is a power of two, 32 or more)
+    auto place = [&](int row, int f) { return a.C + (size_t)(f >> a.c_shift) * a.c_tile + (size_t)row * a.ldc + (f & (a.c_tf - 1)); };
+    auto fetch = [&](const float *dst, int f) {
+        if (vec_ok && f + 4 <= a.f_store) return *reinterpret_cast<const float4 *>(dst);
+        float4 o = make_float4(dst[0], 0.f, 0.f, 0.f);
+        if (f + 1 < a.f_store) o.y = dst[1];
+        if (f + 2 < a.f_store) o.z = dst[2];
+        if (f + 3 < a.f_store) o.w = dst[3];
+        return o;
+    };
+    auto factor = [&](int row) { return !a.finalize ? 1.f : a.mz ? inv_z(a.mz[row].y) : (a.r ? a.r[row] : 1.f); };
+    auto finish = [&](float *dst, int f, float sc, float4 v) {
+        v.x *= sc; v.y *= sc; v.z *= sc; v.w *= sc;
+        if (a.finalize && a.act == SENSEI_ACT_RELU) {
+            v.x = v.x > 0.f ? v.x : 0.f; v.y = v.y > 0.f ? v.y : 0.f; v.z = v.z > 0.f ? v.z : 0.f; v.w = v.w > 0.f ? v.w : 0.f;
         }
+        if (vec_ok && f + 4 <= a.f_store) {
+            *reinterpret_cast<float4 *>(dst) = v;
+        } else {
+            dst[0] = v.x;
+            if (f + 1 < a.f_store) dst[1] = v.y;
+            if (f + 2 < a.f_store) dst[2] = v.z;
+            if (f + 3 < a.f_store) dst[3] = v.w;
+        }
+    };
+    const int items = fr.n_serial * n_q;
+    for (int item = lane; item < items; item += 64) {
+        const int r = item / n_q, f = (q0 + item % n_q) * 4;
+        const int first = lds.first[wave][r], last = lds.last[wave][r], row = lds.row[wave][r];
+        float *dst = place(row, f);
+        float4 v = fetch(dst, f);
+        const float sc = factor(row);
+        for (int cc = first; cc <= last; ++cc) add4(v, *reinterpret_cast<const float4 *>(a.carry + (size_t)cc * a.f_carry + f));
+        finish(dst, f, sc, v);
+    }
+    const int g = lane >> 3;
+    while (wide) {
+        const int l = __ffsll((long long)wide) - 1;
+        wide &= wide - 1;
+        const int row = __builtin_amdgcn_readlane(fr.i, l), first = __builtin_amdgcn_readlane(fr.c, l), last = __builtin_amdgcn_readlane(fr.c_last, l);
+        for (int q = lane & 7; q < n_q; q += 8) {
+            const int f = (q0 + q) * 4;
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 4
-        for (int cc = c; cc <= c_last; ++cc) {
-            const float *slot = a.carry + (size_t)cc * a.f_carry + f0;
+            for (int cc = first + g; cc <= last; cc += 8) add4(v, *reinterpret_cast<const float4 *>(a.carry + (size_t)cc * a.f_carry + f));
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (f0 + 64 * q < a.f_store) acc[q] += slot[64 * q];
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (f0 + 64 * q >= a.f_store) continue;
-            float y = acc[q];
-            if (a.finalize) {
-                y *= sc;
-                if (a.act == SENSEI_ACT_RELU) y = y > 0.f ? y : 0.f;
+            for (int off = 8; off < 64; off <<= 1)
+                add4(v, make_float4(__shfl_xor(v.x, off, 64), __shfl_xor(v.y, off, 64), __shfl_xor(v.z, off, 64), __shfl_xor(v.w, off, 64)));
+            if (g == 0) {
+                float *dst = place(row, f);
+                float4 o = fetch(dst, f);
+                add4(o, v);
+                finish(dst, f, factor(row), o);
             }
-            *dst[q] = y;
         }
     }
 }
 
 // The same for the fused attention mode: the pieces of a row come with their (maximum, sum) pairs and are merged like the
-// lanes of a wavefront are - everything rescaled to the larger maximum - in chunk order; then 1 / sum and the activation.
+// lanes of a wavefront are - everything rescaled to the largest maximum; then 1 / sum and the activation.
 __global__ __launch_bounds__(kBlock) void k_spmm_fixup_attn(SpmmArgs a) {
-    const int c = 1 + blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-    if (c >= a.n_chunks) return;
-    const int lane = threadIdx.x & 63;
-    const long long lo = (long long)c * a.chunk_nnz;
-    const int i0 = a.chunk_row[c];
-    if ((long long)a.row_ptr[i0] <= lo) return;
-    const int i = i0 - 1;
-    const long long rs = a.row_ptr[i];
-    if (rs < lo - a.chunk_nnz) return;
-    const int re = a.row_ptr[i + 1];
-    const int c_last = (re - 1) / a.chunk_nnz;
-    const int tf = a.c_tf;
-    const float2 first = a.mz_out[i];
-    for (int f = lane; f < a.f_store; f += 64) {
-        float *dst = a.C + (size_t)(f / tf) * a.c_tile + (size_t)i * a.ldc + (f % tf);
-        float m = first.x, z = first.y, acc = *dst;
-        for (int cc = c; cc <= c_last; ++cc) {
+    __shared__ FixupLds lds;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const FixupRows fr = fixup_find(a, lds, wave, lane);
+    unsigned long long wide = fr.wide;
+    auto finish = [&](float *dst, float acc, float iz) {
+        float y = acc * iz;
+        if (a.act == SENSEI_ACT_RELU) y = y > 0.f ? y : 0.f;
+        *dst = y;
+    };
+    const int items = fr.n_serial * a.f_store;
+    for (int item = lane; item < items; item += 64) {
+        const int r = item / a.f_store, f = item % a.f_store;
+        const int row = lds.row[wave][r], first = lds.first[wave][r], last = lds.last[wave][r];
+        float *dst = a.C + (size_t)(f / a.c_tf) * a.c_tile + (size_t)row * a.ldc + (f % a.c_tf);
+        float2 own = a.mz_out[row];
+        float m = own.x, z = own.y, acc = *dst;
+        for (int cc = first; cc <= last; ++cc) {
             const float2 p = a.carry_mz[cc];
             const float mn = p.x > m ? p.x : m;
             const float k0 = __expf(m - mn), k1 = __expf(p.x - mn);
@@ -536,9 +1029,28 @@ __global__ __launch_bounds__(kBlock) void k_spmm_fixup_attn(SpmmArgs a) {
             z = z * k0 + p.y * k1;
             m = mn;
         }
-        float y = acc * inv_z(z);
-        if (a.act == SENSEI_ACT_RELU) y = y > 0.f ? y : 0.f;
-        *dst = y;
+        finish(dst, acc, inv_z(z));
+    }
+    while (wide) {   // one long row at a time: the maximum over its pieces, then lanes over columns
+        const int l = __ffsll((long long)wide) - 1;
+        wide &= wide - 1;
+        const int row = __builtin_amdgcn_readlane(fr.i, l), first = __builtin_amdgcn_readlane(fr.c, l), last = __builtin_amdgcn_readlane(fr.c_last, l);
+        const float2 own = a.mz_out[row];
+        float m = own.x, z = 0.f;
+        for (int cc = first + lane; cc <= last; cc += 64) m = fmaxf(m, a.carry_mz[cc].x);
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+        for (int cc = first + lane; cc <= last; cc += 64) z += a.carry_mz[cc].y * __expf(a.carry_mz[cc].x - m);
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) z += __shfl_xor(z, off, 64);
+        const float k_own = __expf(own.x - m), iz = inv_z(z + own.y * k_own);
+        for (int f = lane; f < a.f_store; f += 64) {
+            float *dst = a.C + (size_t)(f / a.c_tf) * a.c_tile + (size_t)row * a.ldc + (f % a.c_tf);
+            float acc = *dst * k_own;
+#pragma unroll 8
+            for (int cc = first; cc <= last; ++cc) acc = fmaf(a.carry[(size_t)cc * a.f_carry + f], __expf(a.carry_mz[cc].x - m), acc);
+            finish(dst, acc, iz);
+        }
     }
 }
 
@@ -550,23 +1062,45 @@ hipError_t spmm_dispatch_mode(const SpmmArgs &a, int mode, dim3 grid, hipStream_
         case kSpmmSoftmax: hipLaunchKernelGGL((k_spmm<VEC, LPG, kSpmmSoftmax, OFF32>), grid, dim3(kBlock), 0, s, a); break;
         case kSpmmAttnFused: hipLaunchKernelGGL((k_spmm<VEC, LPG, kSpmmAttnFused, OFF32>), grid, dim3(kBlock), 0, s, a); break;
         case kSpmmSignSum:
-        case kSpmmLreluSum:
-            if constexpr (VEC == 4 && LPG == 8) {   // slice-major operands only
-                if (mode == kSpmmSignSum) hipLaunchKernelGGL((k_spmm<4, 8, kSpmmSignSum, OFF32>), grid, dim3(kBlock), 0, s, a);
-                else hipLaunchKernelGGL((k_spmm<4, 8, kSpmmLreluSum, OFF32>), grid, dim3(kBlock), 0, s, a);
-                break;
-            } else {
-                return hipErrorInvalidValue;
-            }
+        case kSpmmLreluSum: return hipErrorInvalidValue;   // slice-major operands only
         default: hipLaunchKernelGGL((k_spmm<VEC, LPG, SENSEI_SPMM_SCALED, OFF32>), grid, dim3(kBlock), 0, s, a); break;
     }
     return hipGetLastError();
 }
 
+template <int MODE, int LPG, bool OFF32>
+hipError_t spmm_flat_per(const SpmmArgs &a, dim3 grid, hipStream_t s) {
+    switch (a.chunk_nnz) {
+        case 64: hipLaunchKernelGGL((k_spmm_flat<MODE, 1, LPG, OFF32>), grid, dim3(kBlock), 0, s, a); break;
+        case 128: hipLaunchKernelGGL((k_spmm_flat<MODE, 2, LPG, OFF32>), grid, dim3(kBlock), 0, s, a); break;
+        case 256: hipLaunchKernelGGL((k_spmm_flat<MODE, 4, LPG, OFF32>), grid, dim3(kBlock), 0, s, a); break;
+        case 512: hipLaunchKernelGGL((k_spmm_flat<MODE, 8, LPG, OFF32>), grid, dim3(kBlock), 0, s, a); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+// operands with 16-byte loads: 32-column tiles, or wider ones on a row-major operand (spmm_shape)
+template <int LPG, bool OFF32>
+hipError_t spmm_flat_mode(const SpmmArgs &a, int mode, dim3 grid, hipStream_t s) {
+    switch (mode) {
+        case SENSEI_SPMM_PATTERN: return spmm_flat_per<SENSEI_SPMM_PATTERN, LPG, OFF32>(a, grid, s);
+        case SENSEI_SPMM_WEIGHTED: return spmm_flat_per<SENSEI_SPMM_WEIGHTED, LPG, OFF32>(a, grid, s);
+        case SENSEI_SPMM_SCALED: return spmm_flat_per<SENSEI_SPMM_SCALED, LPG, OFF32>(a, grid, s);
+        case kSpmmSoftmax: return spmm_flat_per<kSpmmSoftmax, LPG, OFF32>(a, grid, s);
+        case kSpmmAttnFused: return spmm_flat_per<kSpmmAttnFused, LPG, OFF32>(a, grid, s);
+        default: break;
+    }
+    if constexpr (LPG == 8) {
+        if (mode == kSpmmSignSum) return spmm_flat_per<kSpmmSignSum, LPG, OFF32>(a, grid, s);
+        if (mode == kSpmmLreluSum) return spmm_flat_per<kSpmmLreluSum, LPG, OFF32>(a, grid, s);
+    }
+    return hipErrorInvalidValue;
+}
+
 template <int VEC>
 hipError_t spmm_dispatch_lpg(const SpmmArgs &a, int mode, int lpg, bool off32, dim3 grid, hipStream_t s) {
     switch (lpg) {
-        case 8: return off32 ? spmm_dispatch_mode<VEC, 8, true>(a, mode, grid, s) : spmm_dispatch_mode<VEC, 8, false>(a, mode, grid, s);
         case 16: return off32 ? spmm_dispatch_mode<VEC, 16, true>(a, mode, grid, s) : spmm_dispatch_mode<VEC, 16, false>(a, mode, grid, s);
         case 32: return off32 ? spmm_dispatch_mode<VEC, 32, true>(a, mode, grid, s) : spmm_dispatch_mode<VEC, 32, false>(a, mode, grid, s);
         default: return off32 ? spmm_dispatch_mode<VEC, 64, true>(a, mode, grid, s) : spmm_dispatch_mode<VEC, 64, false>(a, mode, grid, s);
@@ -636,10 +1170,6 @@ __global__ void k_norm_vec(const int32_t *__restrict__ deg, long long n, float *
     }
 }
 
-struct NnzArgs {
-    const int32_t *row_ptr, *col_idx, *chunk_row;
-    int n_rows, nnz, chunk_nnz, n_chunks;
-};
 
 constexpr int kShortRowElem = 16;  // element-wise kernels: chunks whose rows average fewer non-zeros use one lane per row
 
@@ -686,142 +1216,6 @@ __device__ __forceinline__ void walk_chunk(const NnzArgs &a, int chunk, int lane
     }
 }
 
-// ---- flat walk: the same chunk ownership, but the lanes walk the entries of the chunk and not its rows
-//
-// Walking a chunk row by row costs one chain of memory round trips per row: on a pattern with 20 entries per row a chunk of 512 entries
-// has 25 rows and more, and the per-entry kernels ran at a tenth of the memory rate (row sum of 2.1 M values: 173 us).  Here a wavefront
-// first marks in LDS where the rows of its chunk start (row pointers read 64 at a time) and spreads the marks by a running maximum, which
-// gives every entry its row; everything after that is independent of where the rows end.  Entries are read in striped order (entry
-// 64 u + lane: coalesced); sums over rows are segmented sums in blocked order (a lane owns PER consecutive entries: they are added in the
-// lane, one scan over the lanes joins the pieces), the values change order through LDS.  PER = chunk_nnz / 64.
-template <int PER> struct FlatLds {
-    __attribute__((aligned(16))) int row[kWavesPerBlock][64 * PER];     // row of every entry of the wavefront's chunk
-    __attribute__((aligned(16))) float val[kWavesPerBlock][64 * PER];   // values on their way from striped to blocked order
-};
-
-// LDS written by other lanes of the wavefront is read after this point (the hardware keeps a wavefront's LDS operations in order; the
-// compiler has to be told)
-__device__ __forceinline__ void lds_exchange() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
-template <int PER> struct FlatChunk {
-    int lo, hi, i_first, i1;
-    bool cont;              // the first row began in an earlier chunk: its sum goes to the chunk's carry slot
-    int rid[PER];           // rows of this lane's entries in blocked order
-    unsigned starts;        // bit e: blocked entry e of this lane is the first of its row in the chunk
-    int prev_row;           // row of the entry before this lane's first one
-};
-
-// empty(i) is called once for every row without entries that the chunk owns
-template <int PER, class Empty>
-__device__ __forceinline__ FlatChunk<PER> flat_rows(const NnzArgs &a, int chunk, int lane, int *rows, Empty empty) {
-    FlatChunk<PER> c;
-    c.lo = chunk * (64 * PER);
-    c.hi = (a.nnz - c.lo > 64 * PER) ? c.lo + 64 * PER : a.nnz;
-    const int i0 = __builtin_amdgcn_readfirstlane(a.chunk_row[chunk]);
-    c.i1 = __builtin_amdgcn_readfirstlane(a.chunk_row[chunk + 1]);
-    c.cont = (a.nnz > 0) && (__builtin_amdgcn_readfirstlane(a.row_ptr[i0]) > c.lo);
-    c.i_first = c.cont ? i0 - 1 : i0;
-#pragma unroll
-    for (int u = 0; u < PER; ++u) rows[u * 64 + lane] = -1;
-    lds_exchange();
-    for (int r = c.i_first + lane; r < c.i1; r += 64) {
-        const int s = a.row_ptr[r], e = a.row_ptr[r + 1];
-        if (e > s) rows[s > c.lo ? s - c.lo : 0] = r;   // the rows of a chunk that have entries start at different places
-        else empty(r);
-    }
-    lds_exchange();
-    c.starts = 0u;
-    int top = -1;
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-        const int r = rows[lane * PER + e];
-        c.starts |= (r >= 0 ? 1u : 0u) << e;
-        top = r > top ? r : top;
-        c.rid[e] = top;
-    }
-    int run = top;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int o = __shfl_up(run, off, 64);
-        if (lane >= off) run = o > run ? o : run;
-    }
-    c.prev_row = __shfl_up(run, 1, 64);
-    if (lane == 0) c.prev_row = -1;
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-        c.rid[e] = c.rid[e] > c.prev_row ? c.rid[e] : c.prev_row;
-        rows[lane * PER + e] = c.rid[e];
-    }
-    lds_exchange();
-    return c;
-}
-
-// Segmented sum of v (blocked order; entries past the end of the chunk hold 0): write(row, sum) once per row piece of the chunk.
-// A lane's entries fall into a head (up to its first row start), whole rows, and a tail; the heads are completed by the scan.
-template <int PER, class Write>
-__device__ __forceinline__ void flat_sum(const FlatChunk<PER> &c, int lane, const float (&v)[PER], Write write) {
-    float head = 0.f, run = 0.f;
-    bool started = false;
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-        if ((c.starts >> e) & 1u) {
-            if (started) write(c.rid[e > 0 ? e - 1 : 0], run);
-            else head = run;
-            started = true;
-            run = 0.f;
-        }
-        run += v[e];
-    }
-    float tail = run;
-    int f = started;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const float o = __shfl_up(tail, off, 64);
-        const int of = __shfl_up(f, off, 64);
-        if (lane >= off) {
-            if (!f) tail += o;
-            f |= of;
-        }
-    }
-    const float before = __shfl_up(tail, 1, 64);   // the open row piece of the lanes before this one
-    const int head_row = (c.starts & 1u) ? c.prev_row : c.rid[0];
-    if (started && head_row >= 0 && lane > 0) write(head_row, before + head);
-    if (lane == 63) write(c.rid[PER - 1], tail);
-}
-
-// A value per row for entries in striped order.  Chunks of at most 64 rows keep the values of their rows in the lanes' registers and hand
-// them out by cross-lane reads; the others gather them (a gather costs the vector cache path what the entry's own gather costs:
-// statistics pass on 98,000 rows of 1,021 entries 0.73 ms with it, 0.48 without).
-struct RowVals {
-    bool in_lanes;
-    int i_first;
-    float x;
-    const float *src;
-};
-template <int PER>
-__device__ __forceinline__ RowVals row_vals(const FlatChunk<PER> &c, int lane, const float *__restrict__ src) {
-    RowVals v;
-    v.in_lanes = c.i1 - c.i_first <= 64;
-    v.i_first = c.i_first;
-    v.src = src;
-    v.x = (v.in_lanes && c.i_first + lane < c.i1) ? src[c.i_first + lane] : 0.f;
-    return v;
-}
-__device__ __forceinline__ float row_val(const RowVals &v, int row) { return v.in_lanes ? lane_read((row - v.i_first) * 4, v.x) : v.src[row]; }
-
-// values from striped to blocked order (val[] of the wavefront)
-template <int PER>
-__device__ __forceinline__ void to_blocked(float *val, int lane, const float (&striped)[PER], float (&blocked)[PER]) {
-#pragma unroll
-    for (int u = 0; u < PER; ++u) val[u * 64 + lane] = striped[u];
-    lds_exchange();
-#pragma unroll
-    for (int e = 0; e < PER; ++e) blocked[e] = val[lane * PER + e];
-}
-
 __device__ __forceinline__ int wave_chunk() {
     return blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 }
@@ -834,7 +1228,7 @@ __device__ __forceinline__ void flat_edge_op(const NnzArgs &a, const float *__re
     const int chunk = wave_chunk(), lane = threadIdx.x & 63;
     if (chunk >= a.n_chunks) return;
     int *rows = lds.row[threadIdx.x >> 6];
-    const FlatChunk<PER> c = flat_rows<PER>(a, chunk, lane, rows, [](int) {});
+    const FlatChunk<PER> c = flat_rows<PER>(a, chunk, lane, rows, [](int, bool) {});
     if (c.lo >= c.hi) return;
     const RowVals rv = row_vals<PER>(c, lane, row_vec);
     float x[PER], y[PER];
@@ -968,7 +1362,7 @@ __global__ __launch_bounds__(kBlock) void k_softmax_stats(SoftmaxArgs a) {
     const int chunk = wave_chunk(), lane = threadIdx.x & 63;
     if (chunk >= a.n.n_chunks) return;
     int *rows = lds.row[threadIdx.x >> 6];
-    const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [&](int i) { a.stats[i] = make_float2(-INFINITY, 0.f); });
+    const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [&](int r0, bool none) { if (none) a.stats[r0 + lane] = make_float2(-INFINITY, 0.f); });
     if (c.lo >= c.hi) return;
     float es[PER], e[PER];
     if (FROM_E) {
@@ -1047,37 +1441,6 @@ __global__ __launch_bounds__(kBlock) void k_softmax_stats(SoftmaxArgs a) {
     if (lane == 63) write(c.rid[PER - 1], m, z);
 }
 
-// First chunk of a row that spans several chunks, seen from the chunk c that holds its first continuation: returns the row, or -1 where
-// chunk c starts with a row of its own or continues a row that an earlier chunk already continued; c_last: last chunk of the row.
-__device__ __forceinline__ int continued_row(const NnzArgs &a, int c, int &c_last) {
-    const long long lo = (long long)c * a.chunk_nnz;
-    const int i0 = a.chunk_row[c];
-    if ((long long)a.row_ptr[i0] <= lo) return -1;
-    const int i = i0 - 1;
-    if ((long long)a.row_ptr[i] < lo - a.chunk_nnz) return -1;
-    c_last = (a.row_ptr[i + 1] - 1) / a.chunk_nnz;
-    return i;
-}
-
-// Rows that span several chunks, one lane per chunk: a row of up to kFixupSerial pieces is finished by the lane of its first continuation
-// (serial(i, c, c_last)), a longer one by the whole wavefront (wide(i, c, c_last), uniform arguments; a hub row of 109,000 entries has 213
-// pieces).  One wavefront per chunk instead costs three dependent loads per wavefront: 58 us against 12 on 195,000 chunks.
-constexpr int kFixupSerial = 8;
-template <class Serial, class Wide>
-__device__ __forceinline__ void fixup_rows(const NnzArgs &a, Serial serial, Wide wide) {
-    const int c = 1 + blockIdx.x * blockDim.x + threadIdx.x;
-    int c_last = 0, i = -1;
-    if (c < a.n_chunks) i = continued_row(a, c, c_last);
-    const bool is_long = i >= 0 && c_last - c >= kFixupSerial;
-    if (i >= 0 && !is_long) serial(i, c, c_last);
-    unsigned long long todo = __ballot(is_long);
-    while (todo) {
-        const int l = __ffsll((long long)todo) - 1;
-        todo &= todo - 1;
-        wide(__builtin_amdgcn_readlane(i, l), __builtin_amdgcn_readlane(c, l), __builtin_amdgcn_readlane(c_last, l));
-    }
-}
-
 // merges the carried (m, z) pieces of rows that span several chunks, in chunk order or (long rows) lane by lane and then over the lanes
 __global__ __launch_bounds__(kBlock) void k_softmax_fixup(SoftmaxArgs a) {
     const int lane = threadIdx.x & 63;
@@ -1116,7 +1479,7 @@ __global__ __launch_bounds__(kBlock) void k_softmax_alpha(SoftmaxArgs a) {
     const int chunk = wave_chunk(), lane = threadIdx.x & 63;
     if (chunk >= a.n.n_chunks) return;
     int *rows = lds.row[threadIdx.x >> 6];
-    const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [](int) {});
+    const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [](int, bool) {});
     if (c.lo >= c.hi) return;
     float e[PER];
     float2 st[PER];
@@ -1399,7 +1762,7 @@ __global__ __launch_bounds__(kBlock) void k_row_sum(NnzArgs a, const float *__re
     __shared__ FlatLds<PER> lds;
     const int chunk = wave_chunk(), lane = threadIdx.x & 63;
     if (chunk >= a.n_chunks) return;
-    const FlatChunk<PER> c = flat_rows<PER>(a, chunk, lane, lds.row[threadIdx.x >> 6], [&](int i) { out[i] = 0.f; });
+    const FlatChunk<PER> c = flat_rows<PER>(a, chunk, lane, lds.row[threadIdx.x >> 6], [&](int r0, bool none) { if (none) out[r0 + lane] = 0.f; });
     if (c.lo >= c.hi) return;
     float vs[PER], v[PER];
 #pragma unroll
@@ -1408,7 +1771,7 @@ __global__ __launch_bounds__(kBlock) void k_row_sum(NnzArgs a, const float *__re
         vs[u] = k < c.hi ? val[(size_t)k * stride] : 0.f;
     }
     to_blocked<PER>(lds.val[threadIdx.x >> 6], lane, vs, v);
-    flat_sum<PER>(c, lane, v, [&](int i, float t) {
+    flat_sum<PER>(c, lane, v, [&](int i, float t, int) {
         if (c.cont && i == c.i_first) carry[chunk] = t;
         else out[i] = t;
     });
@@ -1510,7 +1873,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_dalpha(GatBwdArgs a, int tile, i
     const int sub = lane & 3;
     int *rows = lds.row[threadIdx.x >> 6];
     float *val = lds.val[threadIdx.x >> 6];
-    const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [&](int i) { if (LAST) a.rowdot[i] = 0.f; });
+    const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [&](int r0, bool none) { if (LAST && none) a.rowdot[r0 + lane] = 0.f; });
     if (c.lo >= c.hi) return;
     const float *theta = a.theta + (size_t)tile * a.theta_tile + sub * 4;
     const float *dP = a.dP + (size_t)tile * a.dp_tile + sub * 4;
@@ -1545,7 +1908,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_dalpha(GatBwdArgs a, int tile, i
         lds_exchange();
 #pragma unroll
         for (int e = 0; e < PER; ++e) v[e] = val[lane * PER + e];
-        flat_sum<PER>(c, lane, v, [&](int i, float t) {
+        flat_sum<PER>(c, lane, v, [&](int i, float t, int) {
             if (c.cont && i == c.i_first) a.carry[chunk] = t;
             else a.rowdot[i] = t;
         });
@@ -1564,7 +1927,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_dalpha_merge(NnzArgs a, const in
     const int chunk = wave_chunk(), lane = threadIdx.x & 63;
     if (chunk >= a.n_chunks) return;
     int *rows = lds.row[threadIdx.x >> 6];
-    const FlatChunk<PER> c = flat_rows<PER>(a, chunk, lane, rows, [&](int i) { rowdot[i] = 0.f; });
+    const FlatChunk<PER> c = flat_rows<PER>(a, chunk, lane, rows, [&](int r0, bool none) { if (none) rowdot[r0 + lane] = 0.f; });
     if (c.lo >= c.hi) return;
     int w[PER];
     float e[PER], v[PER], s[PER];
@@ -1588,7 +1951,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_dalpha_merge(NnzArgs a, const in
     }
     float b[PER];
     to_blocked<PER>(lds.val[threadIdx.x >> 6], lane, s, b);
-    flat_sum<PER>(c, lane, b, [&](int i, float t) {
+    flat_sum<PER>(c, lane, b, [&](int i, float t, int) {
         if (c.cont && i == c.i_first) carry[chunk] = t;
         else rowdot[i] = t;
     });
@@ -1613,7 +1976,7 @@ __global__ __launch_bounds__(kBlock) void k_score_v2(ScoreV2Args a, int tile, in
     const int lane = threadIdx.x & 63;
     const int sub = lane & 3;
     int *rows = lds.row[threadIdx.x >> 6];
-    const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [](int) {});
+    const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [](int, bool) {});
     if (c.lo >= c.hi) return;
     const float *theta_r = a.theta_r + (size_t)tile * a.tr_tile + sub * 4;
     const float *theta_l = a.theta_l + (size_t)tile * a.tl_tile + sub * 4;
@@ -1656,7 +2019,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_dt(GatDtArgs a) {
     const int chunk = wave_chunk(), lane = threadIdx.x & 63;
     if (chunk >= a.n.n_chunks) return;
     int *rows = lds.row[threadIdx.x >> 6];
-    const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [](int) {});
+    const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [](int, bool) {});
     if (c.lo >= c.hi) return;
     float e[PER], da[PER];
     int p[PER];
@@ -1872,13 +2235,11 @@ SpmmShape spmm_shape(const float *B, int64_t ldb, int f) {
     const int fv = (f + sh.vec - 1) / sh.vec;  // vector columns
     // A neighbour group reads one 128-byte line per neighbour (32 floats) and the feature tiles are spread
     // over the XCDs.  Rows that do not fill whole groups use one wider group instead when that covers the
-    // row in a single tile (measured faster than leaving a nearly empty last tile); very wide rows use
+    // row in a single tile (measured faster than leaving a nearly empty last tile); very wide rows that allow only narrow loads use
     // wider groups so the number of tiles stays moderate.
-    const int base = 32 / sh.vec;
-    int lpg = base;
-    while (lpg > 8 && lpg / 2 >= fv) lpg >>= 1;
+    int lpg = 32 / sh.vec;
     if (fv > lpg && fv <= 32 && fv % lpg != 0) while (lpg < fv) lpg <<= 1;
-    while (lpg < 64 && (fv + lpg - 1) / lpg > 32) lpg <<= 1;
+    if (sh.vec < 4) while (lpg < 64 && (fv + lpg - 1) / lpg > 32) lpg <<= 1;
     sh.lpg = lpg;
     sh.n_tiles = (fv + lpg - 1) / lpg;
     sh.f_carry = sh.n_tiles * lpg * sh.vec;
@@ -1907,6 +2268,7 @@ hipError_t launch_spmm(const sensei_csr &A, int mode, const float *r, const floa
     a.val_stride = val_stride;
     if (c_sliced) ldc = 32;  // requires b_sliced (tiles of 32 columns) and f_store == pad32(f): checked by the callers
     a.c_tf = sh.vec * sh.lpg;
+    a.c_shift = __builtin_ctz((unsigned)a.c_tf);
     a.c_tile = c_sliced ? (long long)(A.n_rows > 0 ? A.n_rows : 1) * 32 : (long long)a.c_tf;
     a.row_ptr = A.row_ptr; a.col_idx = A.col_idx; a.chunk_row = p.chunk_row;
     a.val = A.val; a.r = r; a.c = c; a.B = B; a.C = C; a.carry = carry;
@@ -1915,6 +2277,7 @@ hipError_t launch_spmm(const sensei_csr &A, int mode, const float *r, const floa
     a.f = f; a.f_store = f_store; a.f_carry = sh.f_carry; a.n_tiles = sh.n_tiles; a.act = act;
     a.store_vec_ok = (ldc % sh.vec == 0) && (reinterpret_cast<uintptr_t>(C) % (4 * sh.vec) == 0);
     a.accumulate = accumulate ? 1 : 0; a.finalize = finalize ? 1 : 0;
+    a.scale_weights = defer_fixup ? 0 : 1;   // deferred fix-up: the caller wants raw sums
     a.s_l = nullptr; a.s_r = nullptr; a.slope = 0.f; a.mz_out = nullptr; a.carry_mz = nullptr;
     if (mode == kSpmmAttnFused) {
         if (!fused || accumulate || !finalize || defer_fixup) return hipErrorInvalidValue;
@@ -1942,17 +2305,23 @@ hipError_t launch_spmm(const sensei_csr &A, int mode, const float *r, const floa
     hipError_t err;
     hipEvent_t t0 = timer ? timer->next() : nullptr, t1 = t0 ? timer->next() : nullptr;
     if (t1 && hipEventRecord(t0, s) != hipSuccess) return hipErrorUnknown;
-    switch (sh.vec) {
-        case 4: err = spmm_dispatch_lpg<4>(a, mode, sh.lpg, off32, grid, s); break;
+    const bool flat = sh.vec == 4;
+    if (flat && sh.lpg == 8) err = off32 ? spmm_flat_mode<8, true>(a, mode, grid, s) : spmm_flat_mode<8, false>(a, mode, grid, s);
+    else if (flat) err = sh.lpg == 16 ? spmm_flat_mode<16, false>(a, mode, grid, s) : spmm_flat_mode<32, false>(a, mode, grid, s);
+    else switch (sh.vec) {
         case 2: err = spmm_dispatch_lpg<2>(a, mode, sh.lpg, off32, grid, s); break;
         default: err = spmm_dispatch_lpg<1>(a, mode, sh.lpg, off32, grid, s); break;
     }
     if (err != hipSuccess) return err;
     if (t1 && hipEventRecord(t1, s) != hipSuccess) return hipErrorUnknown;
     if (p.n_chunks > 1 && !(defer_fixup && b_sliced && !finalize)) {
-        dim3 fg(blocks_for(p.n_chunks - 1, kWavesPerBlock));
-        if (mode == kSpmmAttnFused) hipLaunchKernelGGL(k_spmm_fixup_attn, fg, dim3(kBlock), 0, s, a);
-        else hipLaunchKernelGGL(k_spmm_fixup, fg, dim3(kBlock), 0, s, a);
+        const unsigned fg = blocks_for(p.n_chunks - 1, kWavesPerBlock * kFixupChunks);
+        if (mode == kSpmmAttnFused) hipLaunchKernelGGL(k_spmm_fixup_attn, dim3(fg), dim3(kBlock), 0, s, a);
+        else {
+            a.fix_quads = p.n_chunks < 8192 ? 8 : 32;
+            if (flat && a.scale_weights && mode != SENSEI_SPMM_PATTERN) { a.r = nullptr; a.mz = nullptr; }   // the pieces are scaled already
+            hipLaunchKernelGGL(k_spmm_fixup, dim3(fg, blocks_for(f_store, 4 * a.fix_quads)), dim3(kBlock), 0, s, a);
+        }
         err = hipGetLastError();
     }
     return err;

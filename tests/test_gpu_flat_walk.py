@@ -7,7 +7,7 @@ import torch
 
 import oracle
 import synth
-from paper_2306_15155_amd import Context
+from paper_2306_15155_amd import ACT_NONE, ACT_RELU, SPMM_PATTERN, SPMM_SCALED, SPMM_WEIGHTED, Context
 from paper_2306_15155_amd.binding import chunk_nnz
 
 from gpu_util import DeviceCSR, assert_close, dev
@@ -69,4 +69,37 @@ def test_flat_walk_at_chunk_boundaries(ctx, t, least):
     pos = ctx.transpose_positions(A.s, At.s)
     want = oracle.gat_backward(n, g.n_cols, g.row_ptr, g.col_idx, X, W, a_l, a_r, dY, slope=1.0)
     for gpu, ref, what in zip(ctx.gat_backward(A.s, At.s, pos, dev(X), dev(W), dev(a_l), dev(a_r), dev(dY), neg_slope=1.0), want, ("dX", "dW", "da_l", "da_r")):
+        assert_close(gpu, ref, what=what)
+
+
+@pytest.mark.parametrize("t,least", [(64, 3_000), (128, 140_000), (256, 270_000), (512, 530_000)])
+def test_flat_spmm_at_chunk_boundaries(ctx, t, least):
+    """Every mode of the SpMM on the same patterns, operands of one and two 32-column tiles (the second partly filled) and of an odd width."""
+    g = pattern(t, least)
+    n, row = g.n_rows, np.repeat(np.arange(g.n_rows), np.diff(g.row_ptr))
+    val = synth.uniform(t, 8, (g.nnz,))
+    r, c = synth.uniform(t, 9, (n,), 0.5, 1.5), synth.uniform(t, 10, (g.n_cols,), 0.5, 1.5)
+    A, Av = DeviceCSR(g), DeviceCSR(g, val)
+    for f in (32, 40, 41):
+        B = synth.uniform(t, 11, (g.n_cols, f))
+        for mode, a, w in ((SPMM_PATTERN, A, np.ones(g.nnz)), (SPMM_WEIGHTED, Av, val.astype(np.float64)),
+                           (SPMM_SCALED, A, r[row].astype(np.float64) * c[g.col_idx])):
+            ref = np.zeros((n, f))
+            for lo in range(0, g.nnz, 1 << 18):
+                np.add.at(ref, row[lo:lo + (1 << 18)], w[lo:lo + (1 << 18), None] * B[g.col_idx[lo:lo + (1 << 18)]].astype(np.float64))
+            scaled = mode == SPMM_SCALED
+            for act in (ACT_NONE, ACT_RELU):
+                got = ctx.spmm(a.s, mode, dev(B), dev(r) if scaled else None, dev(c) if scaled else None, act)
+                assert_close(got, np.maximum(ref, 0) if act else ref, what=f"mode {mode}, {f} columns, activation {act}")
+    # attention aggregations: one walk or two passes by the mean row, and the sums with a vector per entry of the GATv2 backward
+    X, W, Wl = synth.uniform(t, 12, (g.n_cols, 24)), synth.glorot(t, 13, 24, 32), synth.glorot(t, 14, 24, 32)
+    a_l, a_r = synth.normal(t, 15, (32,), 0.0, 0.5), synth.normal(t, 16, (32,), 0.0, 0.5)
+    for f in (32, 20):
+        ref = oracle.gat_layer(n, g.n_cols, g.row_ptr, g.col_idx, X, W[:, :f].copy(), a_l[:f], a_r[:f], 0.2, 1)
+        assert_close(ctx.gat_layer(A.s, dev(X), dev(W[:, :f].copy()), dev(a_l[:f]), dev(a_r[:f]), 0, 0.2, ACT_RELU), ref, what=f"attention, {f} columns")
+    gt = synth.transpose(g)
+    At, dY = DeviceCSR(gt), synth.normal(t, 17, (n, 32))
+    want = oracle.gatv2_backward(n, g.n_cols, g.row_ptr, g.col_idx, X, Wl, W, a_l, dY, slope=1.0)
+    got = ctx.gatv2_backward(A.s, At.s, ctx.transpose_positions(A.s, At.s), dev(X), dev(Wl), dev(W), dev(a_l), dev(dY), neg_slope=1.0)
+    for gpu, ref, what in zip(got, want, ("dX", "dW_l", "dW_r", "datt")):
         assert_close(gpu, ref, what=what)
