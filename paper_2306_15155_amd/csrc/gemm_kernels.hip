@@ -169,6 +169,92 @@ hipError_t gemm_launch_vec(const GemmArgs &g, int avec, int bvec, hipStream_t s)
     return hipGetLastError();
 }
 
+// Products too small to give every compute unit a block of k_gemm (64 x 64 there: 16 k a step, one barrier and one exposed memory round
+// trip each, so the time is the number of steps, whatever the size).  A workgroup owns 32 rows x 32 columns and its four wavefronts split
+// k; operands go from memory to the matrix instruction's registers without LDS (a lane takes four consecutive k of its row of A in one load
+// and the same four rows of W: the instruction only wants both operands to agree on which k a lane holds), all loads of four steps of 16 k
+// in flight together, and the four partial sums are added in wavefront order through LDS.  fp32 instructions: infinities and NaN pass as
+// in k_gemm.  Bound by two or three memory round trips: 1,024 x 256 x 47 12.7 -> 6.6 us, 4,900 x 256 x 47 12.9 -> 8.2, 600 x 100 x 256
+// 7.3 -> 5.0, 10,000 x 64 x 32 5.4 -> 4.6.
+template <int AVEC>
+__global__ __launch_bounds__(kThreads) void k_gemm_small(GemmArgs g) {
+    constexpr int GS = 4;   // steps of 16 k loaded together
+    constexpr int kWaves = kThreads / 64;
+    __shared__ float red[kWaves][16][64];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, kh = lane >> 5, ll = lane & 31;
+    const long long m0 = (long long)(blockIdx.x / g.n_bn) * 32;
+    const int col = (int)(blockIdx.x % g.n_bn) * 32 + ll;
+    const int steps = (g.k + 15) / 16;
+    const int s0 = steps * wave / kWaves, s1 = steps * (wave + 1) / kWaves;
+
+    floatx16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+
+    // rows past the end read the last row and are not stored; columns past m read the last column and are cleared; k past the end of this
+    // wavefront's range reads k = 0 and is cleared in both operands (masks, not branches around the loads)
+    const float *a_row = g.A + (m0 + ll < g.n ? m0 + ll : g.n - 1) * g.lda;
+    const unsigned w_mask = col < g.m ? ~0u : 0u;
+    const float *w_col = g.W + (col < g.m ? col : g.m - 1);
+    auto masked = [](float v, unsigned m) { return __uint_as_float(__float_as_uint(v) & m); };
+    const int k_end = s1 * 16 < g.k ? s1 * 16 : g.k;
+    for (int st = s0; st < s1; st += GS) {
+        float a[GS][2][4], w[GS][2][4];
+#pragma unroll
+        for (int q = 0; q < GS; ++q)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int k0 = (st + q) * 16 + h * 8 + kh * 4;
+                if (AVEC == 4) {   // k is a multiple of 4: four k are all there or all past the end
+                    const int kc = k0 < k_end ? k0 : 0;
+                    const float4 v = *reinterpret_cast<const float4 *>(a_row + (long long)(kc >> 5) * g.a_slice + (kc & 31));
+                    const unsigned live = k0 < k_end ? ~0u : 0u;
+                    a[q][h][0] = masked(v.x, live); a[q][h][1] = masked(v.y, live); a[q][h][2] = masked(v.z, live); a[q][h][3] = masked(v.w, live);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int k = k0 + e, kc = k < k_end ? k : 0;
+                        a[q][h][e] = masked(a_row[(long long)(kc >> 5) * g.a_slice + (kc & 31)], k < k_end ? ~0u : 0u);
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int k = k0 + e, kc = k < k_end ? k : 0;
+                    w[q][h][e] = masked(w_col[(long long)kc * g.ldw], k < k_end ? w_mask : 0u);
+                }
+            }
+#pragma unroll
+        for (int q = 0; q < GS; ++q) {
+            if (st + q >= s1) break;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q][h][e], w[q][h][e], acc, 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) red[wave][r][lane] = acc[r];
+    __syncthreads();
+    // register r of lane l holds row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32; a wavefront finishes four of the sixteen
+    if (col >= g.m_store) return;
+    const long long y_col = g.y_sliced ? (long long)(col >> 5) * g.n * 32 + (col & 31) : (long long)col;
+    const long long y_ld = g.y_sliced ? 32 : g.ldy;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int r = wave * 4 + q;
+        const long long row = m0 + 8 * wave + 4 * kh + q;
+        if (row < g.n) {
+            float y = red[0][r][lane];
+#pragma unroll
+            for (int v = 1; v < kWaves; ++v) y += red[v][r][lane];
+            if (g.add) y += g.add[(long long)(col >> 5) * g.n * 32 + row * 32 + (col & 31)];
+            if (g.row_scale) y *= g.row_scale[row];
+            if (g.act == SENSEI_ACT_RELU) y = y > 0.f ? y : 0.f;
+            g.Y[row * y_ld + y_col] = y;
+        }
+    }
+}
+
 // ---- the same GEMM on the bf16 matrix cores, which run 16 times the fp32 rate, at fp32 accuracy.  Every fp32 operand element
 // is cut into three bf16 pieces of eight significand bits (truncate, subtract, truncate, subtract: the pieces add up to the
 // element exactly); of the nine piece products of a term the six of weight 2^-16 and above are formed (a1 b1, a1 b2, a2 b1, a1 b3,
@@ -1409,6 +1495,16 @@ hipError_t launch_gemm(const float *A, int64_t lda, const float *W, int64_t ldw,
             if (tn == 2) return done(gemm_bf_launch<2>(g, av, s));
             return done(gemm_bf_launch<4>(g, av, s));
         }
+    }
+    // Few enough 64 x 64 blocks to leave compute units idle: 32 x 32 blocks with k split over the wavefronts.  The line: at 77 blocks
+    // (4,900 x 256 x 47) 8.2 against 12.9 us and at 157 (10,000 x 64 x 32) 4.6 against 5.4, but at 250 (16,000 x 300 x 64) 16.8 against 13.5
+    // and at 308 (4,900 x 47 x 256) 7.8 against 7.0: a block reads its operands for a quarter of the output.
+    if (((n + 63) / 64) * ((m_store + 63) / 64) <= 160) {
+        g.n_bn = (m_store + 31) / 32;
+        const dim3 grid((unsigned)(((n + 31) / 32) * g.n_bn));
+        if (avec == 4) hipLaunchKernelGGL(k_gemm_small<4>, grid, dim3(kThreads), 0, s, g);
+        else hipLaunchKernelGGL(k_gemm_small<1>, grid, dim3(kThreads), 0, s, g);
+        return done(hipGetLastError());
     }
     // tile choice: widest column tile that the output needs; small tiles when the big ones
     // would leave most of the 256 compute units without a workgroup
