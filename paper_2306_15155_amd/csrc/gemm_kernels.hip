@@ -1242,9 +1242,14 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tn(GemmTnArgs g) {
 // of 16 k, fetches one step ahead.  The fp32 accumulators are emptied into fp64 registers after every second step.
 constexpr int kFlushStepsBf = 2;
 
+// TN = 1 (blocks of 128 x 64) where the product has at most 64 columns: half of the matrix work, of the pieces of B and of the fp64
+// accumulators of a 128-column block would be for columns that are not there (100,000 rows, 100 x 47: 45 -> 26.5 us; 233,000 rows,
+// 256 x 41: 150 -> 97; 50,000 rows, 100 x 64: 33 -> 19.6).
+template <int TN>
 __global__ __launch_bounds__(kThreads) void k_gemm_tn_bf(GemmTnArgs g) {
-    constexpr int BM = 128, BN = 128, TM = 2, TN = 2;
-    __shared__ __attribute__((aligned(16))) unsigned short Ps[2][2][3][4][2][32][8];   // [buffer][operand][piece][32-column block][k half][column][8 k]
+    constexpr int BM = 128, BN = 64 * TN, TM = 2;
+    // [buffer][piece][32-column block: four of A, then 2 TN of B][k half][column][8 k]
+    __shared__ __attribute__((aligned(16))) unsigned short Ps[2][3][4 + 2 * TN][2][32][8];
     const int t = threadIdx.x;
     const int wave = t >> 6, lane = t & 63;
     const int wm = wave >> 1, wn = wave & 1;
@@ -1279,11 +1284,13 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tn_bf(GemmTnArgs g) {
     // staging: thread -> (column of the 128, k half); columns past the edge read the last column and are cleared, rows past the slab
     // read its last row and are cleared (masks, not branches around the fetches)
     const int col = t & 127, skh = t >> 7;
-    const bool a_ok = m0 + col < g.m, b_ok = n0 + col < g.n;
+    const int b_col = t % BN, b_skh = (t / BN) & 1;   // TN = 1: the second 128 threads fetch the same words again and leave them
+    const bool b_on = t < 2 * BN;
+    const bool a_ok = m0 + col < g.m, b_ok = n0 + b_col < g.n;
     const unsigned a_mask = a_ok ? ~0u : 0u, b_mask = b_ok ? ~0u : 0u;
     // addresses: a uniform row pointer per k plus one 32-bit byte offset per lane (its k half and column), fixed before the loop
     const unsigned a_off = (unsigned)(((long long)skh * 8 * g.lda + (a_ok ? m0 + col : g.m - 1)) * 4);
-    const unsigned b_off = (unsigned)(((long long)skh * 8 * g.ldb + (b_ok ? n0 + col : g.n - 1)) * 4);
+    const unsigned b_off = (unsigned)(((long long)b_skh * 8 * g.ldb + (b_ok ? n0 + b_col : g.n - 1)) * 4);
     float ra[8], rb[8];
     auto fetch = [&](long long k0, auto whole) {
 #pragma unroll
@@ -1293,16 +1300,16 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tn_bf(GemmTnArgs g) {
                 ra[e] = __uint_as_float(__float_as_uint(*reinterpret_cast<const float *>(ar + a_off)) & a_mask);
                 rb[e] = __uint_as_float(__float_as_uint(*reinterpret_cast<const float *>(br + b_off)) & b_mask);
             } else {
-                const long long k = k0 + skh * 8 + e;
-                const long long kc = (k < k_hi ? k : k_hi - 1) - skh * 8;
+                const long long k = k0 + skh * 8 + e, kb = k0 + b_skh * 8 + e;
+                const long long kc = (k < k_hi ? k : k_hi - 1) - skh * 8, kbc = (kb < k_hi ? kb : k_hi - 1) - b_skh * 8;
                 const unsigned live = k < k_hi ? ~0u : 0u;
-                const char *ar = reinterpret_cast<const char *>(g.A + kc * g.lda), *br = reinterpret_cast<const char *>(g.B + kc * g.ldb);
+                const char *ar = reinterpret_cast<const char *>(g.A + kc * g.lda), *br = reinterpret_cast<const char *>(g.B + kbc * g.ldb);
                 ra[e] = __uint_as_float(__float_as_uint(*reinterpret_cast<const float *>(ar + a_off)) & a_mask & live);
                 rb[e] = __uint_as_float(__float_as_uint(*reinterpret_cast<const float *>(br + b_off)) & b_mask);
             }
         }
     };
-    auto stash_one = [&](const float (&src)[8], int buf, int operand) {
+    auto stash_one = [&](const float (&src)[8], int buf, int operand, int c, int half) {
         unsigned pc[8][3];
 #pragma unroll
         for (int e = 0; e < 8; ++e) split_bf16x3(src[e], pc[e][0], pc[e][1], pc[e][2]);
@@ -1312,13 +1319,13 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tn_bf(GemmTnArgs g) {
             uintx4 w;
 #pragma unroll
             for (int d = 0; d < 4; ++d) w[d] = pack_bf16(pc[2 * d][p], pc[2 * d + 1][p]) ^ flip;
-            *reinterpret_cast<uintx4 *>(&Ps[buf][operand][p][col >> 5][skh][col & 31][0]) = w;
+            if (operand == 0 || b_on) *reinterpret_cast<uintx4 *>(&Ps[buf][p][operand * 4 + (c >> 5)][half][c & 31][0]) = w;
         }
     };
     auto stash = [&](int buf) {
-        stash_one(ra, buf, 0);
+        stash_one(ra, buf, 0, col, skh);
         __builtin_amdgcn_sched_barrier(0);   // one operand's pieces at a time in registers
-        stash_one(rb, buf, 1);
+        stash_one(rb, buf, 1, b_col, b_skh);
     };
 
     if (k_lo < k_hi) {
@@ -1333,12 +1340,12 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tn_bf(GemmTnArgs g) {
             for (int pa = 2; pa >= 0; --pa) {
                 uintx4 af[TM];
 #pragma unroll
-                for (int i = 0; i < TM; ++i) af[i] = *reinterpret_cast<const uintx4 *>(&Ps[buf][0][pa][wm * TM + i][kh][ll][0]);
+                for (int i = 0; i < TM; ++i) af[i] = *reinterpret_cast<const uintx4 *>(&Ps[buf][pa][wm * TM + i][kh][ll][0]);
 #pragma unroll
                 for (int pb = 2 - pa; pb >= 0; --pb)   // smallest products first
 #pragma unroll
                     for (int j = 0; j < TN; ++j) {
-                        const uintx4 bf = *reinterpret_cast<const uintx4 *>(&Ps[buf][1][pb][wn * TN + j][kh][ll][0]);
+                        const uintx4 bf = *reinterpret_cast<const uintx4 *>(&Ps[buf][pb][4 + wn * TN + j][kh][ll][0]);
 #pragma unroll
                         for (int i = 0; i < TM; ++i)
                             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[i]), __builtin_bit_cast(bf16x8, bf), acc[i][j], 0, 0, 0);
@@ -1684,7 +1691,10 @@ hipError_t launch_gemm_tn(const float *A, int64_t lda, const float *B, int64_t l
     const bool vb = (n % 4 == 0 && ldb % 4 == 0 && reinterpret_cast<uintptr_t>(B) % 16 == 0);
     dim3 grid((unsigned)(g.n_tiles * splits));
     // long reductions (the weight gradients of a layer) take the bf16-piece kernel
-    if (g.k >= 4096 && g.k_per_split >= 64) hipLaunchKernelGGL(k_gemm_tn_bf, grid, dim3(kThreads), 0, s, g);
+    if (g.k >= 4096 && g.k_per_split >= 64) {
+        if (n <= 64) hipLaunchKernelGGL(k_gemm_tn_bf<1>, grid, dim3(kThreads), 0, s, g);   // one block of columns either way
+        else hipLaunchKernelGGL(k_gemm_tn_bf<2>, grid, dim3(kThreads), 0, s, g);
+    }
     else if (va && vb) hipLaunchKernelGGL((k_gemm_tn<4, 4>), grid, dim3(kThreads), 0, s, g);
     else if (va) hipLaunchKernelGGL((k_gemm_tn<4, 1>), grid, dim3(kThreads), 0, s, g);
     else if (vb) hipLaunchKernelGGL((k_gemm_tn<1, 4>), grid, dim3(kThreads), 0, s, g);

@@ -35,3 +35,21 @@ def test_small_gemm(n, k, m, pad):
         keep = [i for i in range(n) if i not in (1, 2)]
         assert torch.equal(z[keep], y[keep])
     ctx.close()
+
+
+# the weight gradient of a layer on the identity pattern is X^T dY: around the 64 columns that choose the narrow block, the 128 x 64 block's
+# edges, odd leading dimensions and row counts that leave a ragged last slab.  Slabs of 32 rows are summed in fp32 (six products a term),
+# everything after that in fp64.
+@pytest.mark.parametrize("n,f_in,f_out", [(4096, 1, 1), (4097, 100, 47), (5003, 128, 64), (4999, 129, 63), (6000, 130, 65), (20_001, 33, 32)])
+def test_weight_gradient_columns(n, f_in, f_out):
+    from paper_2306_15155_amd import Context, csr_struct
+    ctx = Context(0)
+    g = torch.Generator(device="cuda").manual_seed(n + f_in)
+    ptr, col = torch.arange(n + 1, dtype=torch.int32, device="cuda"), torch.arange(n, dtype=torch.int32, device="cuda")
+    A, one = csr_struct(n, n, ptr, col), torch.ones(n, device="cuda")
+    x, dy = torch.randn(n, f_in, generator=g, device="cuda"), torch.randn(n, f_out, generator=g, device="cuda")
+    w = torch.randn(f_in, f_out, generator=g, device="cuda")
+    _, dw = ctx.gcn_backward(A, A, one, one, x, w, dy, 0, want_dx=False)
+    ref, mag = x.double().t() @ dy.double(), x.double().abs().t() @ dy.double().abs()
+    assert bool(((dw.double() - ref).abs() <= (32 * 6 + 1) * 2.0 ** -24 * mag).all())
+    ctx.close()
