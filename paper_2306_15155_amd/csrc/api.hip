@@ -304,7 +304,8 @@ int run_gcn(const sensei_csr &A, const float *r, const float *c, const sensei_ma
     const int f_in = (int)X.cols, f_out = (int)W.cols;
     Carver cv(ws, ws_bytes);
     ChunkPlan plan = make_plan(A, cv);
-    SENSEI_TRY(launch_chunk_rows(A, plan, s));
+    SideWork side;
+    side.add_plan(A, plan);
     const int mode = (id == SENSEI_GCN_DYN_AGG || id == SENSEI_GCN_DYN_UPD) ? SENSEI_SPMM_PATTERN
                      : (id == SENSEI_GCN_DYNF_AGG || id == SENSEI_GCN_DYNF_UPD) ? SENSEI_SPMM_SCALED
                                                                                  : SENSEI_SPMM_WEIGHTED;
@@ -319,9 +320,10 @@ int run_gcn(const sensei_csr &A, const float *r, const float *c, const sensei_ma
         const bool sliced = id == SENSEI_GCN_DYN_AGG || relayout_pays(A);   // DYN_AGG writes its copy anyway
         if (sliced) {
             float *T = cv.take<float>((size_t)A.n_cols * pad32(f_in));
-            SENSEI_TRY(launch_to_slices(id == SENSEI_GCN_DYN_AGG ? c : nullptr, X.ptr, X.ld, A.n_cols, f_in, T, s));
+            SENSEI_TRY(launch_to_slices(id == SENSEI_GCN_DYN_AGG ? c : nullptr, X.ptr, X.ld, A.n_cols, f_in, T, s, nullptr, 0, &side));
             src = T;
         }
+        SENSEI_TRY(launch_side(&side, s));
         const bool scaled = (mode == SENSEI_SPMM_SCALED);
         SENSEI_TRY(spmm_any(A, mode, scaled ? r : nullptr, scaled ? c : nullptr, src, ld_src, f_in, U, fs, f_in, SENSEI_ACT_NONE, plan, carry, s, kt,
                             false, nullptr, sliced));
@@ -337,7 +339,7 @@ int run_gcn(const sensei_csr &A, const float *r, const float *c, const sensei_ma
         // Z is only ever gathered by the SpMM, so the GEMM writes it slice-major (the in-place row broadcast of
         // DYN_UPD keeps the row-major form)
         const bool sliced = (id != SENSEI_GCN_DYN_UPD);
-        SENSEI_TRY(launch_gemm(X.ptr, X.ld, W.ptr, W.ld, Z, fs, A.n_cols, f_in, f_out, fs, SENSEI_ACT_NONE, s, z_scale, gt, sliced));
+        SENSEI_TRY(launch_gemm(X.ptr, X.ld, W.ptr, W.ld, Z, fs, A.n_cols, f_in, f_out, fs, SENSEI_ACT_NONE, s, z_scale, gt, sliced, false, nullptr, &side));
         if (id == SENSEI_GCN_DYN_UPD) {
             SENSEI_TRY(launch_row_broadcast(c, Z, fs, A.n_cols, fs, Z, fs, SENSEI_ACT_NONE, s));
             SENSEI_TRY(spmm_any(A, mode, nullptr, nullptr, Z, fs, fs, Y, ldy, f_out, SENSEI_ACT_NONE, plan, carry, s, kt));
@@ -371,9 +373,10 @@ int run_sgc(const sensei_csr &A, const float *r, const float *c, const sensei_ma
     float *carry = cv.take<float>(spmm_carry_bytes(A.nnz, fp) / sizeof(float));
     float *buf[2] = {cv.take<float>((size_t)A.n_cols * fp), cv.take<float>((size_t)A.n_cols * fp)};
     float *rc = cv.take<float>((size_t)A.n_rows);
-    SENSEI_TRY(launch_chunk_rows(A, plan, s));
+    SideWork side;
+    side.add_plan(A, plan);
     // between two hops the row scaling of one and the column scaling of the next meet: one factor r_i c_i per node
-    SENSEI_TRY(launch_row_broadcast(r, c, 1, A.n_rows, 1, rc, 1, SENSEI_ACT_NONE, s));
+    SENSEI_TRY(launch_row_broadcast(r, c, 1, A.n_rows, 1, rc, 1, SENSEI_ACT_NONE, s, nullptr, 0, &side));
     // hop input 0, slice-major with the column scaling applied: c (x) X, or c (x) (X.W) straight from the GEMM epilogue
     if (id == 0) SENSEI_TRY(launch_to_slices(c, X.ptr, X.ld, A.n_cols, f_in, buf[0], s));
     else SENSEI_TRY(launch_gemm(X.ptr, X.ld, W.ptr, W.ld, buf[0], fp, A.n_cols, f_in, f_out, fp, SENSEI_ACT_NONE, s, c, gt, true));
@@ -417,7 +420,8 @@ int run_tagcn(const sensei_csr &A, const float *r, const float *c, const sensei_
     ChunkPlan plan = make_plan(A, cv);
     float *carry = cv.take<float>(spmm_carry_bytes(A.nnz, fp) / sizeof(float));
     float *rc = cv.take<float>((size_t)n);
-    SENSEI_TRY(launch_chunk_rows(A, plan, s));
+    SideWork side;
+    side.add_plan(A, plan);
     if (id == 0) {
         // hops at width f_in, kept as G_k = c (x) H_k (what the next SpMM gathers); the one GEMM over all hops undoes the
         // scaling per row: sum_k H_k W_k = diag(1/c) [G_0 .. G_K] [W_0; ..; W_K]
@@ -426,7 +430,7 @@ int run_tagcn(const sensei_csr &A, const float *r, const float *c, const sensei_
         float *inv_c = cv.take<float>((size_t)n);
         const int ldws = pad4(f_out);
         float *Wst = cv.take<float>((size_t)(k_hops + 1) * fp * ldws);
-        SENSEI_TRY(launch_row_broadcast(r, c, 1, n, 1, rc, 1, SENSEI_ACT_NONE, s));
+        SENSEI_TRY(launch_row_broadcast(r, c, 1, n, 1, rc, 1, SENSEI_ACT_NONE, s, nullptr, 0, &side));
         SENSEI_TRY(launch_reciprocal(c, n, inv_c, s));
         SENSEI_TRY(launch_stack_weights(W.ptr, W.ld, k_hops + 1, f_in, f_out, Wst, ldws, s));
         SENSEI_TRY(launch_to_slices(c, X.ptr, X.ld, n, f_in, G, s));
@@ -439,7 +443,7 @@ int run_tagcn(const sensei_csr &A, const float *r, const float *c, const sensei_
     // Horner form at width f_out: T_K = X W_K, T_k = X W_k + A^ T_{k+1}; T is kept as c (x) T_k, slice-major
     float *T = cv.take<float>((size_t)n * fp), *P = cv.take<float>((size_t)n * fp);
     auto w_block = [&](int k) { return W.ptr + (size_t)k * f_in * W.ld; };
-    SENSEI_TRY(launch_gemm(X.ptr, X.ld, w_block(k_hops), W.ld, T, fp, n, f_in, f_out, fp, SENSEI_ACT_NONE, s, c, gt, true));
+    SENSEI_TRY(launch_gemm(X.ptr, X.ld, w_block(k_hops), W.ld, T, fp, n, f_in, f_out, fp, SENSEI_ACT_NONE, s, c, gt, true, false, nullptr, &side));
     for (int k = k_hops - 1; k >= 0; --k) {
         SENSEI_TRY(spmm_any(A, SENSEI_SPMM_PATTERN, r, nullptr, T, fp, fp, P, fp, fp, SENSEI_ACT_NONE, plan, carry, s, kt, false, nullptr, true, true));
         if (k > 0) SENSEI_TRY(launch_gemm(X.ptr, X.ld, w_block(k), W.ld, T, fp, n, f_in, f_out, fp, SENSEI_ACT_NONE, s, c, gt, true, false, P));
@@ -480,7 +484,8 @@ int run_gcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r, 
     const float *mask = (act == SENSEI_ACT_RELU) ? Y : nullptr;
     Carver cv(ws, ws_bytes);
     ChunkPlan plan_t = make_plan(At, cv);
-    SENSEI_TRY(launch_chunk_rows(At, plan_t, s));
+    SideWork side;
+    side.add_plan(At, plan_t);
     // K-hop layer (square pattern): every chain of hops keeps its intermediate results slice-major, one buffer written while the
     // other is gathered from, with the adjacent scalings of two hops merged into r (.) c, as in the forward
     float *rc = nullptr;
@@ -494,8 +499,10 @@ int run_gcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r, 
         float *T = cv.take<float>((size_t)A.n_rows * pad32(f_out));
         float *G = cv.take<float>((size_t)A.n_cols * fo4);
         double *part = cv.take<double>(gemm_tn_bytes(A.n_cols, f_in, f_out) / sizeof(double));
+        float *Wt = dX ? cv.take<float>((size_t)f_out * pad4(f_in)) : nullptr;
+        if (dX) side.add_transpose(W.ptr, W.ld, f_in, f_out, Wt, pad4(f_in));
         // T = r (x) (dY (.) mask), slice-major: what the transposed SpMM gathers from
-        SENSEI_TRY(launch_to_slices(r, dY.ptr, dY.ld, A.n_rows, f_out, T, s, mask, ldy));
+        SENSEI_TRY(launch_to_slices(r, dY.ptr, dY.ld, A.n_rows, f_out, T, s, mask, ldy, &side));
         const float *last = T;
         if (k_hops > 1) {  // inner hops: T <- (r (.) c) (x) (A~^T T)
             float *T2 = cv.take<float>((size_t)A.n_cols * pad32(f_out));
@@ -510,8 +517,6 @@ int run_gcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r, 
                             nullptr, true));
         SENSEI_TRY(launch_gemm_tn(X.ptr, X.ld, G, fo4, A.n_cols, f_in, f_out, dW, lddw, part, s));
         if (dX) {
-            float *Wt = cv.take<float>((size_t)f_out * pad4(f_in));
-            SENSEI_TRY(launch_transpose(W.ptr, W.ld, f_in, f_out, Wt, pad4(f_in), s));
             SENSEI_TRY(launch_gemm(G, fo4, Wt, pad4(f_in), dX, lddx, A.n_cols, f_out, f_in, f_in, SENSEI_ACT_NONE, s));
         }
     } else {
@@ -519,12 +524,17 @@ int run_gcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r, 
         float *carry = cv.take<float>(spmm_carry_bytes(A.nnz, fi32) / sizeof(float));
         float *dP = cv.take<float>((size_t)A.n_rows * fo4);
         double *part = cv.take<double>(gemm_tn_bytes(A.n_rows, f_in, f_out) / sizeof(double));
-        SENSEI_TRY(launch_row_broadcast(nullptr, dY.ptr, dY.ld, A.n_rows, f_out, dP, fo4, SENSEI_ACT_NONE, s, mask, ldy));
+        ChunkPlan plan;
+        if (!U_saved) {
+            plan = make_plan(A, cv);
+            side.add_plan(A, plan);
+        }
+        float *Wt = dX ? cv.take<float>((size_t)f_out * fi4) : nullptr;
+        if (dX) side.add_transpose(W.ptr, W.ld, f_in, f_out, Wt, fi4);
+        SENSEI_TRY(launch_row_broadcast(nullptr, dY.ptr, dY.ld, A.n_rows, f_out, dP, fo4, SENSEI_ACT_NONE, s, mask, ldy, &side));
         const float *U = U_saved;
         int64_t ld_u = ldu;
         if (!U) {  // recompute U = r (x) (A~ (c (x) X)), the aggregate-first half of the forward
-            ChunkPlan plan = make_plan(A, cv);
-            SENSEI_TRY(launch_chunk_rows(A, plan, s));
             float *T = cv.take<float>((size_t)A.n_cols * fi32);
             float *Uw = cv.take<float>((size_t)A.n_rows * fi4);
             SENSEI_TRY(launch_to_slices(c, X.ptr, X.ld, A.n_cols, f_in, T, s));
@@ -544,9 +554,7 @@ int run_gcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r, 
         }
         SENSEI_TRY(launch_gemm_tn(U, ld_u, dP, fo4, A.n_rows, f_in, f_out, dW, lddw, part, s));
         if (dX) {
-            float *Wt = cv.take<float>((size_t)f_out * fi4);
             float *V = cv.take<float>((size_t)A.n_rows * fi32);
-            SENSEI_TRY(launch_transpose(W.ptr, W.ld, f_in, f_out, Wt, fi4, s));
             // V = r (x) (dP W^T), written slice-major by the GEMM epilogue; dX = c (x) (A~^T V)
             SENSEI_TRY(launch_gemm(dP, fo4, Wt, fi4, V, fi32, A.n_rows, f_out, f_in, fi32, SENSEI_ACT_NONE, s, r, nullptr, true));
             const float *last = V;
@@ -602,7 +610,8 @@ int run_tagcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r
     const float *mask = (act == SENSEI_ACT_RELU) ? Y : nullptr;
     Carver cv(ws, ws_bytes);
     ChunkPlan plan_t = make_plan(At, cv);
-    SENSEI_TRY(launch_chunk_rows(At, plan_t, s));
+    SideWork side;
+    side.add_plan(At, plan_t);
     auto w_block = [&](int k) { return W.ptr + (size_t)k * f_in * W.ld; };
     auto dw_block = [&](int k) { return dW + (size_t)k * f_in * lddw; };
     if (id == SENSEI_GCN_BWD_AGG) {
@@ -612,11 +621,12 @@ int run_tagcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r
         float *S = cv.take<float>((size_t)n * fo32);
         float *Wst = cv.take<float>((size_t)ldq * fi4);
         double *part = cv.take<double>(gemm_tn_bytes(n, f_in, f_out) / sizeof(double));
-        if (fo4 != f_out) SENSEI_TRY(launch_zero_matrix(Q, n, (int)ldq, ldq, false, s));   // the pad columns enter the GEMM below
-        SENSEI_TRY(launch_row_broadcast(nullptr, dY.ptr, dY.ld, n, f_out, Q, ldq, SENSEI_ACT_NONE, s, mask, ldy));
+        // the pad columns enter the GEMM below: those of Q_0 are cleared here, the propagations write the others (S has zeros there)
+        if (fo4 != f_out) SENSEI_TRY(launch_zero_matrix(Q + f_out, n, fo4 - f_out, ldq, false, s));
+        SENSEI_TRY(launch_row_broadcast(nullptr, dY.ptr, dY.ld, n, f_out, Q, ldq, SENSEI_ACT_NONE, s, mask, ldy, &side));
         for (int k = 1; k <= k_hops; ++k) {   // Q_k = c (x) (A~^T (r (x) Q_(k-1)))
             SENSEI_TRY(launch_to_slices(r, Q + (size_t)(k - 1) * fo4, ldq, n, f_out, S, s));
-            SENSEI_TRY(spmm_any(At, SENSEI_SPMM_PATTERN, c, nullptr, S, fo32, f_out, Q + (size_t)k * fo4, ldq, f_out, SENSEI_ACT_NONE, plan_t, carry, s,
+            SENSEI_TRY(spmm_any(At, SENSEI_SPMM_PATTERN, c, nullptr, S, fo32, fo4, Q + (size_t)k * fo4, ldq, fo4, SENSEI_ACT_NONE, plan_t, carry, s,
                                 nullptr, false, nullptr, true));
         }
         for (int k = 0; k <= k_hops; ++k)
@@ -629,14 +639,14 @@ int run_tagcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r
         return SENSEI_OK;
     }
     ChunkPlan plan = make_plan(A, cv);
-    SENSEI_TRY(launch_chunk_rows(A, plan, s));
+    side.add_plan(A, plan);
     float *carry = cv.take<float>(spmm_carry_bytes(A.nnz, fi32) / sizeof(float));
     float *dP = cv.take<float>((size_t)n * fo4);
     float *H = cv.take<float>((size_t)n * fi4);
     float *T = cv.take<float>((size_t)n * fi32), *P = cv.take<float>((size_t)n * fi32);
     float *Wt = cv.take<float>((size_t)(k_hops + 1) * fo4 * fi4);
     double *part = cv.take<double>(gemm_tn_bytes(n, f_in, f_out) / sizeof(double));
-    SENSEI_TRY(launch_row_broadcast(nullptr, dY.ptr, dY.ld, n, f_out, dP, fo4, SENSEI_ACT_NONE, s, mask, ldy));
+    SENSEI_TRY(launch_row_broadcast(nullptr, dY.ptr, dY.ld, n, f_out, dP, fo4, SENSEI_ACT_NONE, s, mask, ldy, &side));
     // weight gradients, hop after hop: H_k = r (x) (A~ (c (x) H_(k-1)))
     SENSEI_TRY(launch_gemm_tn(X.ptr, X.ld, dP, fo4, n, f_in, f_out, dw_block(0), lddw, part, s));
     for (int k = 1; k <= k_hops; ++k) {
@@ -704,13 +714,16 @@ int run_gat(const sensei_csr &A, const sensei_mat &X, const sensei_mat &W, const
     float *theta = nullptr;
     if (id != SENSEI_GAT_RECOMP_FOLD) theta = cv.take<float>((size_t)A.n_cols * fo);
 
-    SENSEI_TRY(launch_chunk_rows(A, plan, s));
+    SideWork side;
+    side.add_plan(A, plan);
     const bool fold = (id == SENSEI_GAT_RECOMP_FOLD || id == SENSEI_GAT_REUSE_FOLD);
     const bool reuse = gat_is_reuse(id);
     // Theta is slice-major when the SpMM gathers from it (reuse) and a head's columns are whole 32-column slices; the
     // recompute id only projects it
     const bool theta_sliced = reuse && (n_heads == 1 || d % 32 == 0);
-    if (theta) SENSEI_TRY(launch_gemm(X.ptr, X.ld, W.ptr, W.ld, theta, fo, A.n_cols, f_in, f_out, fo, SENSEI_ACT_NONE, s, nullptr, gt, theta_sliced));
+    if (theta)
+        SENSEI_TRY(launch_gemm(X.ptr, X.ld, W.ptr, W.ld, theta, fo, A.n_cols, f_in, f_out, fo, SENSEI_ACT_NONE, s, nullptr, gt, theta_sliced, false, nullptr,
+                               &side));
     // recompute ids gather from X: slice-major copy once for all heads when its rows are gathered often enough
     float *carry = cv.take<float>(spmm_carry_bytes(A.nnz, reuse ? fo : fi) / sizeof(float));
     float *U = nullptr;
@@ -721,10 +734,11 @@ int run_gat(const sensei_csr &A, const sensei_mat &X, const sensei_mat &W, const
         x_sliced = relayout_pays(A);
         if (x_sliced) {
             float *T = cv.take<float>((size_t)A.n_cols * pad32(f_in));
-            SENSEI_TRY(launch_to_slices(nullptr, X.ptr, X.ld, A.n_cols, f_in, T, s));
+            SENSEI_TRY(launch_to_slices(nullptr, X.ptr, X.ld, A.n_cols, f_in, T, s, nullptr, 0, &side));
             x_src = T;
         }
     }
+    SENSEI_TRY(launch_side(&side, s));
     const int f_gather = reuse ? (n_heads == 1 ? fo : d) : f_in;  // width of the aggregation of one head
     // dense-tile split (the gathered operand, Theta or X, must be slice-major): the tiles form their weights from s_l, s_r
     // themselves, only the remainder's logits are stored
@@ -831,8 +845,9 @@ int run_gatv2(const sensei_csr &A, const sensei_mat &X, const sensei_mat &Wl, co
     // the destinations are the first n_rows sources: with one shared weight matrix their projections are rows of Theta_r,
     // but a slice of Theta_r holds n_cols rows and a slice of Theta_l n_rows, so the slices coincide only on a square pattern
     float *theta_l = (shared && A.n_rows == A.n_cols) ? theta_r : cv.take<float>((size_t)A.n_rows * fo);
-    SENSEI_TRY(launch_chunk_rows(A, plan, s));
-    SENSEI_TRY(launch_to_slices(nullptr, att, f_out, 1, f_out, att_pad, s));
+    SideWork side;
+    side.add_plan(A, plan);
+    SENSEI_TRY(launch_to_slices(nullptr, att, f_out, 1, f_out, att_pad, s, nullptr, 0, &side));
     SENSEI_TRY(launch_gemm(X.ptr, X.ld, Wr.ptr, Wr.ld, theta_r, fo, A.n_cols, f_in, f_out, fo, SENSEI_ACT_NONE, s, nullptr, gt, true));
     if (theta_l != theta_r)
         SENSEI_TRY(launch_gemm(X.ptr, X.ld, Wl.ptr, Wl.ld, theta_l, fo, A.n_rows, f_in, f_out, fo, SENSEI_ACT_NONE, s, nullptr, gt, true));
@@ -919,10 +934,11 @@ int run_gatv2_backward(const sensei_csr &A_in, const sensei_csr &At_in, const in
     double *part_a = cv.take<double>(theta_t_vec_bytes(A.n_rows, f_out) / sizeof(double));
     float *dThR = Dcat, *dThL = Dcat + fo4;
 
-    SENSEI_TRY(launch_chunk_rows(A, plan, s));
-    SENSEI_TRY(launch_chunk_rows(At, plan_t, s));
+    SideWork side;
+    side.add_plan(A, plan);
+    side.add_plan(At, plan_t);
     // forward quantities: both projections (slice-major), the logits and the row statistics
-    SENSEI_TRY(launch_to_slices(nullptr, att, f_out, 1, f_out, att_pad, s));
+    SENSEI_TRY(launch_to_slices(nullptr, att, f_out, 1, f_out, att_pad, s, nullptr, 0, &side));
     SENSEI_TRY(launch_gemm(X.ptr, X.ld, Wr.ptr, Wr.ld, theta_r, fo, A.n_cols, f_in, f_out, fo, SENSEI_ACT_NONE, s, nullptr, nullptr, true));
     SENSEI_TRY(launch_gemm(X.ptr, X.ld, Wl.ptr, Wl.ld, theta_l, fo, A.n_rows, f_in, f_out, fo, SENSEI_ACT_NONE, s, nullptr, nullptr, true));
     SENSEI_TRY(launch_score_v2(A, theta_l, theta_r, f_out, att_pad, slope, logits, plan, s));
@@ -993,9 +1009,10 @@ int run_dotgat(const sensei_csr &A, const sensei_mat &X, const sensei_mat &Wq, c
     float *logits = cv.take<float>((size_t)(A.nnz > 0 ? A.nnz : 1));
     float *Q = cv.take<float>((size_t)A.n_rows * dk);
     float *K = cv.take<float>((size_t)A.n_cols * dk);
-    SENSEI_TRY(launch_chunk_rows(A, plan, s));
+    SideWork side;
+    side.add_plan(A, plan);
     // both projections slice-major with zero pad columns, the layout the per-entry dot product walks (one launch per 32-column slice)
-    SENSEI_TRY(launch_gemm(X.ptr, X.ld, Wq.ptr, Wq.ld, Q, dk, A.n_rows, f_in, d_k, dk, SENSEI_ACT_NONE, s, nullptr, gt, true));
+    SENSEI_TRY(launch_gemm(X.ptr, X.ld, Wq.ptr, Wq.ld, Q, dk, A.n_rows, f_in, d_k, dk, SENSEI_ACT_NONE, s, nullptr, gt, true, false, nullptr, &side));
     SENSEI_TRY(launch_gemm(X.ptr, X.ld, Wk.ptr, Wk.ld, K, dk, A.n_cols, f_in, d_k, dk, SENSEI_ACT_NONE, s, nullptr, gt, true));
     SENSEI_TRY(launch_gat_dalpha(A, K, Q, d_k, nullptr, nullptr, logits, nullptr, plan, nullptr, s, scale));
     SENSEI_TRY(launch_softmax(A, logits, logits, plan, stats, carry_stats, s));
@@ -1077,10 +1094,11 @@ int run_dotgat_backward(const sensei_csr &A_in, const sensei_csr &At_in, const i
     double *part = cv.take<double>(gemm_tn_bytes(A.n_cols, f_in, f_out > d_k ? f_out : d_k) / sizeof(double));
     float *dK = Dcat, *dV = Dcat + dk4, *dQ = Dcat + dk4 + fo4;
 
-    SENSEI_TRY(launch_chunk_rows(A, plan, s));
-    SENSEI_TRY(launch_chunk_rows(At, plan_t, s));
+    SideWork side;
+    side.add_plan(A, plan);
+    side.add_plan(At, plan_t);
     // forward quantities
-    SENSEI_TRY(launch_gemm(X.ptr, X.ld, Wq.ptr, Wq.ld, Q, dk, A.n_rows, f_in, d_k, dk, SENSEI_ACT_NONE, s, nullptr, nullptr, true));
+    SENSEI_TRY(launch_gemm(X.ptr, X.ld, Wq.ptr, Wq.ld, Q, dk, A.n_rows, f_in, d_k, dk, SENSEI_ACT_NONE, s, nullptr, nullptr, true, false, nullptr, &side));
     SENSEI_TRY(launch_gemm(X.ptr, X.ld, Wk.ptr, Wk.ld, K, dk, A.n_cols, f_in, d_k, dk, SENSEI_ACT_NONE, s, nullptr, nullptr, true));
     SENSEI_TRY(launch_gemm(X.ptr, X.ld, Wv.ptr, Wv.ld, V, fo, A.n_cols, f_in, f_out, fo, SENSEI_ACT_NONE, s, nullptr, nullptr, true));
     SENSEI_TRY(launch_gat_dalpha(A, K, Q, d_k, nullptr, nullptr, logits, nullptr, plan, nullptr, s, scale));
@@ -1194,10 +1212,13 @@ int run_gat_backward(const sensei_csr &A, const sensei_csr &At, const int32_t *t
     double *part = cv.take<double>(gemm_tn_bytes(A.n_cols, f_in, f_out) / sizeof(double));
     double *part_a = cv.take<double>(theta_t_vec_bytes(A.n_cols, f_out) / sizeof(double));
 
-    SENSEI_TRY(launch_chunk_rows(A, plan, s));
-    SENSEI_TRY(launch_chunk_rows(At, plan_t, s));
+    SideWork side;
+    side.add_plan(A, plan);
+    side.add_plan(At, plan_t);
+    if (dX && !dtheta_out) side.add_transpose(W.ptr, W.ld, f_in, f_out, Wt, fi4);
     // forward quantities: Theta (slice-major: the edge kernel gathers its rows), projections, logits, row statistics
-    SENSEI_TRY(launch_gemm(X.ptr, X.ld, W.ptr, W.ld, theta, fo32, A.n_cols, f_in, f_out, fo32, SENSEI_ACT_NONE, s, nullptr, nullptr, true));
+    SENSEI_TRY(launch_gemm(X.ptr, X.ld, W.ptr, W.ld, theta, fo32, A.n_cols, f_in, f_out, fo32, SENSEI_ACT_NONE, s, nullptr, nullptr, true, false, nullptr,
+                           &side));
     SENSEI_TRY(launch_gemv2(theta, fo32, A.n_cols, f_out, a_l, a_r, s_l, s_r, s, true));
     SENSEI_TRY(launch_attention_stats(A, s_l, s_r, slope, logits, nullptr, plan, stats, carry_stats, s));
     // dP = dY (.) [Y > 0], slice-major
@@ -1275,7 +1296,6 @@ int run_gat_backward(const sensei_csr &A, const sensei_csr &At, const int32_t *t
     if (dtheta_out) return SENSEI_OK;
     SENSEI_TRY(launch_gemm_tn(X.ptr, X.ld, dTheta, ldt, A.n_cols, f_in, f_out, dW, lddw, part, s));
     if (dX) {
-        SENSEI_TRY(launch_transpose(W.ptr, W.ld, f_in, f_out, Wt, fi4, s));
         SENSEI_TRY(launch_gemm(dTheta, ldt, Wt, fi4, dX, lddx, A.n_cols, f_out, f_in, f_in, SENSEI_ACT_NONE, s));
     }
     return SENSEI_OK;

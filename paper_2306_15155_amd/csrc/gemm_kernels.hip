@@ -12,7 +12,7 @@ namespace {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-constexpr int kThreads = 256;
+constexpr int kThreads = kSideThreads;
 constexpr int KT = 16;  // k extent of one LDS tile
 
 struct GemmArgs {
@@ -23,6 +23,7 @@ struct GemmArgs {
     int y_sliced;  // Y stored slice-major in tiles of 32 columns: (row, col) at Y[(col / 32) * n * 32 + row * 32 + col % 32]
     long long a_slice;   // floats from columns 32 s .. 32 s + 31 of A to the next 32: 32 for a row-major A, n * 32 (with lda = 32) for a slice-major one
     const float *add;    // optional n x pad32(m) slice-major matrix added to the product before scaling and activation
+    SideWork side;       // small work of the call this product belongs to, done by the first workgroups
 };
 
 // Block tile BM x BN, 4 wavefronts laid out WGM x WGN, each computing TM x TN tiles of 32 x 32
@@ -31,6 +32,8 @@ struct GemmArgs {
 // fetched from HBM into registers while the current one is multiplied.
 template <int BM, int BN, int WGM, int WGN, int AVEC, int BVEC>
 __global__ __launch_bounds__(kThreads) void k_gemm(GemmArgs g) {
+    if ((int)blockIdx.x < g.side.blocks) return side_block(g.side, (int)blockIdx.x);
+    const unsigned block = blockIdx.x - g.side.blocks;
     constexpr int TM = BM / WGM / 32, TN = BN / WGN / 32;
     constexpr int APAD = 36, BPAD = 36;  // row stride = 36 mod 64 words: the two k-rows an MFMA operand read touches fall on (nearly) disjoint LDS banks, and the four k-rows a stash writes are 16 banks apart
     constexpr int A_TPR = KT / AVEC;             // threads per A row
@@ -45,8 +48,8 @@ __global__ __launch_bounds__(kThreads) void k_gemm(GemmArgs g) {
     const int t = threadIdx.x;
     const int wave = t >> 6, lane = t & 63;
     const int wm = wave / WGN, wn = wave % WGN;
-    const long long m0 = (long long)(blockIdx.x / g.n_bn) * BM;
-    const int n0 = (int)(blockIdx.x % g.n_bn) * BN;
+    const long long m0 = (long long)(block / g.n_bn) * BM;
+    const int n0 = (int)(block % g.n_bn) * BN;
 
     floatx16 acc[TM][TN];
 #pragma unroll
@@ -157,7 +160,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm(GemmArgs g) {
 template <int BM, int BN, int WGM, int WGN>
 hipError_t gemm_launch_vec(const GemmArgs &g, int avec, int bvec, hipStream_t s) {
     const long long n_bm = (g.n + BM - 1) / BM;
-    dim3 grid((unsigned)(n_bm * g.n_bn));
+    dim3 grid((unsigned)(n_bm * g.n_bn + g.side.blocks));
 #define SENSEI_GEMM_CASE(AV, BV) \
     hipLaunchKernelGGL((k_gemm<BM, BN, WGM, WGN, AV, BV>), grid, dim3(kThreads), 0, s, g)
     if (bvec == 4) {
@@ -178,12 +181,14 @@ hipError_t gemm_launch_vec(const GemmArgs &g, int avec, int bvec, hipStream_t s)
 // 7.3 -> 5.0, 10,000 x 64 x 32 5.4 -> 4.6.
 template <int AVEC>
 __global__ __launch_bounds__(kThreads) void k_gemm_small(GemmArgs g) {
+    if ((int)blockIdx.x < g.side.blocks) return side_block(g.side, (int)blockIdx.x);
+    const unsigned block = blockIdx.x - g.side.blocks;
     constexpr int GS = 4;   // steps of 16 k loaded together
     constexpr int kWaves = kThreads / 64;
     __shared__ float red[kWaves][16][64];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, kh = lane >> 5, ll = lane & 31;
-    const long long m0 = (long long)(blockIdx.x / g.n_bn) * 32;
-    const int col = (int)(blockIdx.x % g.n_bn) * 32 + ll;
+    const long long m0 = (long long)(block / g.n_bn) * 32;
+    const int col = (int)(block % g.n_bn) * 32 + ll;
     const int steps = (g.k + 15) / 16;
     const int s0 = steps * wave / kWaves, s1 = steps * (wave + 1) / kWaves;
 
@@ -280,14 +285,16 @@ __device__ __forceinline__ unsigned pack_bf16(unsigned first, unsigned second) {
 // barrier per step.  Rows past the end are computed from the last row and dropped.
 template <int TN, int AVEC>
 __global__ __launch_bounds__(kThreads, 2) void k_gemm_bf(GemmArgs g) {
+    if ((int)blockIdx.x < g.side.blocks) return side_block(g.side, (int)blockIdx.x);
+    const unsigned block = blockIdx.x - g.side.blocks;
     constexpr int BM = 256, BN = 32 * TN;
     constexpr int A_TPR = 16 / AVEC, A_RPP = kThreads / A_TPR, A_PASSES = BM / A_RPP;   // threads per row, rows per pass
     constexpr int ALD = 20;   // floats per row of A in LDS: 16 k and 16 bytes of padding (conflict-free 16-byte reads of 16 rows)
     __shared__ __attribute__((aligned(16))) float As[2][BM][ALD];
     __shared__ __attribute__((aligned(16))) unsigned short Bs[2][3][TN][2][32][8];
     const int t = threadIdx.x, wave = t >> 6, lane = t & 63, kh = lane >> 5, ll = lane & 31;
-    const long long m0 = (long long)(blockIdx.x / g.n_bn) * BM;
-    const int n0 = (int)(blockIdx.x % g.n_bn) * BN;
+    const long long m0 = (long long)(block / g.n_bn) * BM;
+    const int n0 = (int)(block % g.n_bn) * BN;
 
     floatx16 acc[2][TN];
 #pragma unroll
@@ -445,7 +452,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_gemm_bf(GemmArgs g) {
 
 template <int TN>
 hipError_t gemm_bf_launch(const GemmArgs &g, int avec, hipStream_t s) {
-    const dim3 grid((unsigned)(((g.n + 255) / 256) * g.n_bn));
+    const dim3 grid((unsigned)(((g.n + 255) / 256) * g.n_bn + g.side.blocks));
     if (avec == 4) hipLaunchKernelGGL((k_gemm_bf<TN, 4>), grid, dim3(kThreads), 0, s, g);
     else if (avec == 2) hipLaunchKernelGGL((k_gemm_bf<TN, 2>), grid, dim3(kThreads), 0, s, g);
     else hipLaunchKernelGGL((k_gemm_bf<TN, 1>), grid, dim3(kThreads), 0, s, g);
@@ -1470,8 +1477,8 @@ bool gemm_uses_pieces(int64_t n, int k, int m_store) {
 
 hipError_t launch_gemm(const float *A, int64_t lda, const float *W, int64_t ldw, float *Y, int64_t ldy, int64_t n,
                        int k, int m, int m_store, int act, hipStream_t s, const float *row_scale, KernelTimer *timer, bool y_sliced,
-                       bool a_sliced, const float *add_sliced) {
-    if (n <= 0 || m_store <= 0) return hipSuccess;
+                       bool a_sliced, const float *add_sliced, SideWork *side) {
+    if (n <= 0 || m_store <= 0) return launch_side(side, s);
     if (a_sliced) lda = 32;
     hipEvent_t t0 = timer ? timer->next() : nullptr, t1 = t0 ? timer->next() : nullptr;
     if (t1 && hipEventRecord(t0, s) != hipSuccess) return hipErrorUnknown;
@@ -1480,6 +1487,7 @@ hipError_t launch_gemm(const float *A, int64_t lda, const float *W, int64_t ldw,
         return e;
     };
     GemmArgs g;
+    g.side = take_side(side);
     g.row_scale = row_scale;
     g.A = A; g.W = W; g.Y = Y; g.lda = lda; g.ldw = ldw; g.ldy = ldy; g.n = n;
     g.k = k; g.m = m; g.m_store = m_store; g.act = act; g.y_sliced = y_sliced ? 1 : 0;
@@ -1508,7 +1516,7 @@ hipError_t launch_gemm(const float *A, int64_t lda, const float *W, int64_t ldw,
     // and at 308 (4,900 x 47 x 256) 7.8 against 7.0: a block reads its operands for a quarter of the output.
     if (((n + 63) / 64) * ((m_store + 63) / 64) <= 160) {
         g.n_bn = (m_store + 31) / 32;
-        const dim3 grid((unsigned)(((n + 31) / 32) * g.n_bn));
+        const dim3 grid((unsigned)(((n + 31) / 32) * g.n_bn + g.side.blocks));
         if (avec == 4) hipLaunchKernelGGL(k_gemm_small<4>, grid, dim3(kThreads), 0, s, g);
         else hipLaunchKernelGGL(k_gemm_small<1>, grid, dim3(kThreads), 0, s, g);
         return done(hipGetLastError());

@@ -21,9 +21,60 @@ struct ChunkPlan {
     int32_t *chunk_row;   // device, n_chunks + 1: first row starting at or after c*T; [n_chunks] = n_rows
 };
 
+// Small work that nothing before it on the stream produces and the next kernels need: the chunk boundaries of up to two patterns (a
+// binary search per chunk) and a transposed weight matrix.  As kernels of their own these cost 4 to 6 us each, whatever they do; the first
+// launch of a call takes them along instead, in workgroups (of kSideThreads) ahead of its own.  A launcher that was handed a SideWork
+// empties it; launch_side runs what nobody took.
+constexpr int kSideThreads = 256;
+struct SideWork {
+    int blocks = 0;            // workgroups in all
+    int n_plans = 0;
+    struct Plan { const int32_t *row_ptr; int32_t *chunk_row; int n_rows, chunk_nnz, n_chunks, block0; } plan[2] = {};
+    const float *w = nullptr;  // wt[c * ldt + r] = w[r * ldw + c]
+    float *wt = nullptr;
+    long long ldw = 0, ldt = 0;
+    int w_rows = 0, w_cols = 0, w_block0 = 0;
+    void add_plan(const sensei_csr &A, const ChunkPlan &p) {
+        plan[n_plans++] = {A.row_ptr, p.chunk_row, A.n_rows, p.chunk_nnz, p.n_chunks, blocks};
+        blocks += (p.n_chunks + 1 + kSideThreads - 1) / kSideThreads;
+    }
+    void add_transpose(const float *W, int64_t ld, int rows, int cols, float *Wt, int64_t ld_t) {
+        if (rows <= 0 || cols <= 0) return;
+        w = W; wt = Wt; ldw = ld; ldt = ld_t; w_rows = rows; w_cols = cols; w_block0 = blocks;
+        blocks += (int)(((long long)rows * cols + kSideThreads - 1) / kSideThreads);
+    }
+    SideWork take() { SideWork t = *this; *this = SideWork(); return t; }
+};
+inline SideWork take_side(SideWork *s) { return s ? s->take() : SideWork(); }
+
+#ifdef __HIPCC__
+// what workgroup `block` (< w.blocks) of the side work does
+__device__ __forceinline__ void side_block(const SideWork &w, int block) {
+    if (w.w && block >= w.w_block0) {
+        const long long e = (long long)(block - w.w_block0) * kSideThreads + threadIdx.x;
+        if (e >= (long long)w.w_rows * w.w_cols) return;
+        const int c = (int)(e / w.w_rows), r = (int)(e % w.w_rows);   // neighbouring threads write neighbouring words
+        w.wt[c * w.ldt + r] = w.w[r * w.ldw + c];
+        return;
+    }
+    const SideWork::Plan &p = (w.n_plans > 1 && block >= w.plan[1].block0) ? w.plan[1] : w.plan[0];
+    const int chunk = (block - p.block0) * kSideThreads + threadIdx.x;
+    if (chunk > p.n_chunks) return;
+    if (chunk == p.n_chunks) { p.chunk_row[chunk] = p.n_rows; return; }
+    const long long target = (long long)chunk * p.chunk_nnz;
+    int lo = 0, hi = p.n_rows + 1;  // first index in [0, n_rows] with row_ptr[idx] >= target
+    while (lo < hi) {
+        const int mid = (int)(((long long)lo + hi) >> 1);
+        if ((long long)p.row_ptr[mid] < target) lo = mid + 1; else hi = mid;
+    }
+    p.chunk_row[chunk] = lo < p.n_rows ? lo : p.n_rows;
+}
+#endif
+
 int choose_chunk_nnz(int64_t nnz);
 size_t plan_bytes(int64_t nnz);  // upper bound over all chunk sizes
 hipError_t launch_chunk_rows(const sensei_csr &A, const ChunkPlan &p, hipStream_t s);
+hipError_t launch_side(SideWork *side, hipStream_t s);   // nothing if it is empty
 
 // ---- optional timing of a kernel's launches with HIP events on the launch stream
 struct KernelTimer {
@@ -116,11 +167,11 @@ hipError_t launch_sddmm_norm(const sensei_csr &A, const float *r, const float *c
                              hipStream_t s);
 // mask (optional, n x f, ldm): elements whose mask value is not > 0 are written as 0 (backward of ReLU)
 hipError_t launch_row_broadcast(const float *s_vec, const float *X, int64_t ldx, int64_t n, int f, float *Y,
-                                int64_t ldy, int act, hipStream_t s, const float *mask = nullptr, int64_t ldm = 0);
+                                int64_t ldy, int act, hipStream_t s, const float *mask = nullptr, int64_t ldm = 0, SideWork *side = nullptr);
 
 // Y (slice-major, pad32(f) columns, 128-byte aligned, n * pad32(f) floats) = s_vec (x) X, s_vec optional; pad columns = 0
 hipError_t launch_to_slices(const float *s_vec, const float *X, int64_t ldx, int64_t n, int f, float *Y, hipStream_t s,
-                            const float *mask = nullptr, int64_t ldm = 0);
+                            const float *mask = nullptr, int64_t ldm = 0, SideWork *side = nullptr);
 
 // ---- attention: logits, per-row softmax statistics, normalised weights
 hipError_t launch_score(const sensei_csr &A, const float *s_l, const float *s_r, float slope, float *e,
@@ -250,7 +301,8 @@ hipError_t launch_tiles_combine_pm(const TileSplit &T, float *C, int64_t n_rows,
 bool gemm_uses_pieces(int64_t n, int k, int m_store);   // whether launch_gemm takes the bf16-piece kernel for this shape (ordinary leading dimensions)
 hipError_t launch_gemm(const float *A, int64_t lda, const float *W, int64_t ldw, float *Y, int64_t ldy, int64_t n,
                        int k, int m, int m_store, int act, hipStream_t s, const float *row_scale = nullptr,
-                       KernelTimer *timer = nullptr, bool y_sliced = false, bool a_sliced = false, const float *add_sliced = nullptr);
+                       KernelTimer *timer = nullptr, bool y_sliced = false, bool a_sliced = false, const float *add_sliced = nullptr,
+                       SideWork *side = nullptr);
 // y_sliced / a_sliced: that matrix is stored slice-major in tiles of 32 floats (see launch_spmm); its leading dimension is ignored
 // (a slice-major A has k padded to a multiple of 32 in memory; columns k .. are not read).  add_sliced: optional n x pad32(m)
 // slice-major matrix added to the product before the row scaling and the activation.

@@ -18,26 +18,14 @@ namespace sensei {
 
 namespace {
 
-constexpr int kBlock = 256;
+constexpr int kBlock = kSideThreads;
 constexpr int kWavesPerBlock = kBlock / 64;
 constexpr int kMaxPanels = SENSEI_MAX_PANELS;
 constexpr int kShortRowNnz = 12;  // chunks whose rows average fewer non-zeros than this use one neighbour group per row
 
 // ------------------------------------------------------------------ chunk plan
 
-__global__ void k_chunk_rows(const int32_t *__restrict__ row_ptr, int n_rows, int chunk_nnz, int n_chunks,
-                             int32_t *__restrict__ chunk_row) {
-    int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c > n_chunks) return;
-    if (c == n_chunks) { chunk_row[c] = n_rows; return; }
-    const long long target = (long long)c * chunk_nnz;
-    int lo = 0, hi = n_rows + 1;  // first index in [0, n_rows] with row_ptr[idx] >= target
-    while (lo < hi) {
-        int mid = (int)(((long long)lo + hi) >> 1);
-        if ((long long)row_ptr[mid] < target) lo = mid + 1; else hi = mid;
-    }
-    chunk_row[c] = lo < n_rows ? lo : n_rows;
-}
+__global__ __launch_bounds__(kSideThreads) void k_side(SideWork w) { side_block(w, (int)blockIdx.x); }
 
 // ------------------------------------------------------------------------ SpMM
 
@@ -1261,9 +1249,10 @@ __global__ __launch_bounds__(kBlock) void k_score(NnzArgs a, const float *__rest
 
 template <int VEC>
 __global__ void k_row_broadcast(const float *__restrict__ s, const float *X, long long ldx, long long n, int f, float *Y,
-                                long long ldy, int act, const float *__restrict__ mask, long long ldm) {  // Y may be X (in place)
+                                long long ldy, int act, const float *__restrict__ mask, long long ldm, SideWork side) {  // Y may be X (in place)
+    if ((int)blockIdx.x < side.blocks) return side_block(side, (int)blockIdx.x);
     const int fv = f / VEC;
-    long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    long long t = (long long)(blockIdx.x - side.blocks) * blockDim.x + threadIdx.x;
     if (t >= n * fv) return;
     const long long i = t / fv;
     const int q = (int)(t % fv) * VEC;
@@ -1297,9 +1286,10 @@ __global__ void k_stack_weights(const float *__restrict__ W, long long ldw, int 
 // Copy of X (n x f, row-major) into slice-major tiles of 32 columns, optionally scaled per row; the pad columns
 // up to the next multiple of 32 are written as zeros.  One thread per (row, 4 columns).
 __global__ void k_to_slices(const float *__restrict__ s, const float *__restrict__ X, long long ldx, long long n, int f,
-                            float *__restrict__ Y, int x_vec_ok, const float *__restrict__ mask, long long ldm) {
+                            float *__restrict__ Y, int x_vec_ok, const float *__restrict__ mask, long long ldm, SideWork side) {
+    if ((int)blockIdx.x < side.blocks) return side_block(side, (int)blockIdx.x);
     const int fp4 = ((f + 31) & ~31) / 4;
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long t = (long long)(blockIdx.x - side.blocks) * blockDim.x + threadIdx.x;
     if (t >= n * fp4) return;
     // consecutive threads walk the rows of one tile: reads are 16-byte pieces 8 to a row, writes are contiguous
     const long long per_tile = n * 8;
@@ -2220,10 +2210,17 @@ size_t plan_bytes(int64_t nnz) {
     return align_up(((size_t)n_chunks_for(nnz, choose_chunk_nnz(nnz)) + 1) * sizeof(int32_t), 256);
 }
 
-hipError_t launch_chunk_rows(const sensei_csr &A, const ChunkPlan &p, hipStream_t s) {
-    hipLaunchKernelGGL(k_chunk_rows, dim3(blocks_for(p.n_chunks + 1, kBlock)), dim3(kBlock), 0, s, A.row_ptr, A.n_rows,
-                       p.chunk_nnz, p.n_chunks, p.chunk_row);
+hipError_t launch_side(SideWork *side, hipStream_t s) {
+    if (!side || side->blocks <= 0) return hipSuccess;
+    const SideWork w = side->take();
+    hipLaunchKernelGGL(k_side, dim3((unsigned)w.blocks), dim3(kSideThreads), 0, s, w);
     return hipGetLastError();
+}
+
+hipError_t launch_chunk_rows(const sensei_csr &A, const ChunkPlan &p, hipStream_t s) {
+    SideWork w;
+    w.add_plan(A, p);
+    return launch_side(&w, s);
 }
 
 SpmmShape spmm_shape(const float *B, int64_t ldb, int f) {
@@ -2363,13 +2360,14 @@ hipError_t launch_score(const sensei_csr &A, const float *s_l, const float *s_r,
 }
 
 hipError_t launch_row_broadcast(const float *s_vec, const float *X, int64_t ldx, int64_t n, int f, float *Y, int64_t ldy, int act, hipStream_t s,
-                                const float *mask, int64_t ldm) {
-    if (n <= 0 || f <= 0) return hipSuccess;
+                                const float *mask, int64_t ldm, SideWork *side) {
+    if (n <= 0 || f <= 0) return launch_side(side, s);
+    const SideWork sw = take_side(side);
     const bool a16 = reinterpret_cast<uintptr_t>(X) % 16 == 0 && reinterpret_cast<uintptr_t>(Y) % 16 == 0;
     if (f % 4 == 0 && ldx % 4 == 0 && ldy % 4 == 0 && a16)
-        hipLaunchKernelGGL((k_row_broadcast<4>), dim3(blocks_for(n * (f / 4), kBlock)), dim3(kBlock), 0, s, s_vec, X, (long long)ldx, (long long)n, f, Y, (long long)ldy, act, mask, (long long)ldm);
+        hipLaunchKernelGGL((k_row_broadcast<4>), dim3(blocks_for(n * (f / 4), kBlock) + sw.blocks), dim3(kBlock), 0, s, s_vec, X, (long long)ldx, (long long)n, f, Y, (long long)ldy, act, mask, (long long)ldm, sw);
     else
-        hipLaunchKernelGGL((k_row_broadcast<1>), dim3(blocks_for(n * f, kBlock)), dim3(kBlock), 0, s, s_vec, X, (long long)ldx, (long long)n, f, Y, (long long)ldy, act, mask, (long long)ldm);
+        hipLaunchKernelGGL((k_row_broadcast<1>), dim3(blocks_for(n * f, kBlock) + sw.blocks), dim3(kBlock), 0, s, s_vec, X, (long long)ldx, (long long)n, f, Y, (long long)ldy, act, mask, (long long)ldm, sw);
     return hipGetLastError();
 }
 
@@ -2387,11 +2385,12 @@ hipError_t launch_stack_weights(const float *W, int64_t ldw, int hops, int f_in,
 }
 
 hipError_t launch_to_slices(const float *s_vec, const float *X, int64_t ldx, int64_t n, int f, float *Y, hipStream_t s, const float *mask,
-                            int64_t ldm) {
-    if (n <= 0 || f <= 0) return hipSuccess;
+                            int64_t ldm, SideWork *side) {
+    if (n <= 0 || f <= 0) return launch_side(side, s);
+    const SideWork sw = take_side(side);
     const int x_vec_ok = (ldx % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0) ? 1 : 0;
     const long long threads = n * (long long)(pad32(f) / 4);
-    hipLaunchKernelGGL(k_to_slices, dim3(blocks_for(threads, kBlock)), dim3(kBlock), 0, s, s_vec, X, (long long)ldx, (long long)n, f, Y, x_vec_ok, mask, (long long)ldm);
+    hipLaunchKernelGGL(k_to_slices, dim3(blocks_for(threads, kBlock) + sw.blocks), dim3(kBlock), 0, s, s_vec, X, (long long)ldx, (long long)n, f, Y, x_vec_ok, mask, (long long)ldm, sw);
     return hipGetLastError();
 }
 
