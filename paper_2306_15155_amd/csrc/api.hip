@@ -1258,8 +1258,7 @@ int run_gat_backward(const sensei_csr &A, const sensei_csr &At, const int32_t *t
         if (split_t) SENSEI_TRY(fork_transposed_tiles());
         SENSEI_TRY(launch_gat_dalpha(A, theta, T, f_out, logits, stats, dt, rowdot, plan, sum_carry, s));
     }
-    SENSEI_TRY(launch_gat_dt(A, logits, dt, rowdot, stats, t_pos, slope, dt, adt_t, plan, s));
-    SENSEI_TRY(launch_row_sum(A, dt, 1, ds_l, plan, sum_carry, s));
+    SENSEI_TRY(launch_gat_dt(A, logits, dt, rowdot, stats, t_pos, slope, nullptr, adt_t, plan, s, ds_l, sum_carry));
     SENSEI_TRY(launch_row_sum(At, reinterpret_cast<const float *>(adt_t) + 1, 2, ds_r, plan_t, sum_carry, s));
     // dTheta = alpha^T.dP + ds_l a_l^T + ds_r a_r^T
     if (split_t) {

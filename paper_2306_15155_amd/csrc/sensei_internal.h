@@ -196,9 +196,11 @@ hipError_t launch_gat_dalpha(const sensei_csr &A, const float *theta, const floa
 // dense-tile split: dalpha[k] from the remainder's values (where[k] >= 0) or the cells of the tiles' product Dt (where[k] < 0), and rowdot
 hipError_t launch_gat_dalpha_merge(const sensei_csr &A, const int32_t *where, const float *dalpha_rem, const float *Dt, const float *logits,
                                    const float2 *mz, float *dalpha, float *rowdot, const ChunkPlan &p, float *carry, hipStream_t s);
-// dt[k] = alpha (dalpha - rowdot_i) LeakyReLU'(e); dt may be dalpha; adt_t[t_pos[k]] = (alpha, dt)
+// dt[k] = alpha (dalpha - rowdot_i) LeakyReLU'(e); dt may be dalpha; adt_t[t_pos[k]] = (alpha, dt).  With rowsum (and carry, n_chunks
+// floats): dt is not written, rowsum[i] is its sum over row i.
 hipError_t launch_gat_dt(const sensei_csr &A, const float *logits, const float *dalpha, const float *rowdot, const float2 *mz,
-                         const int32_t *t_pos, float slope, float *dt, float2 *adt_t, const ChunkPlan &p, hipStream_t s);
+                         const int32_t *t_pos, float slope, float *dt, float2 *adt_t, const ChunkPlan &p, hipStream_t s, float *rowsum = nullptr,
+                         float *carry = nullptr);
 // logits[k] = sum_m att[m] LeakyReLU(theta_l[i, m] + theta_r[j, m]) per stored entry (i, j); both matrices slice-major
 // (n_rows x pad32(f), n_cols x pad32(f)), att padded with zeros to pad32(f)
 hipError_t launch_score_v2(const sensei_csr &A, const float *theta_l, const float *theta_r, int f, const float *att_padded, float slope,

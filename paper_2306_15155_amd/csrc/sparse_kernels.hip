@@ -20,6 +20,7 @@ namespace {
 
 constexpr int kBlock = kSideThreads;
 constexpr int kWavesPerBlock = kBlock / 64;
+constexpr int kXcds = 8;               // accelerator dies; workgroups go to them round robin
 constexpr int kMaxPanels = SENSEI_MAX_PANELS;
 constexpr int kShortRowNnz = 12;  // chunks whose rows average fewer non-zeros than this use one neighbour group per row
 
@@ -1208,6 +1209,12 @@ __device__ __forceinline__ int wave_chunk() {
     return blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 }
 
+// The same with the chunks in one contiguous range per XCD (workgroups go round robin to the eight XCDs): for grids of blocks_by_xcd().
+__device__ __forceinline__ int wave_chunk_by_xcd() {
+    const int block = (blockIdx.x & (kXcds - 1)) * (gridDim.x / kXcds) + blockIdx.x / kXcds;
+    return block * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+}
+
 // out[k] = op(row value of entry k, column value of entry k): the SDDMM instances with a vector on either side
 template <int PER, class Op>
 __device__ __forceinline__ void flat_edge_op(const NnzArgs &a, const float *__restrict__ row_vec, const float *__restrict__ col_vec,
@@ -1723,6 +1730,7 @@ __global__ void k_zero_rows(float *__restrict__ C, long long n, int f, long long
     if (t < n * f) C[(t / f) * ldc + (t % f)] = 0.f;
 }
 
+inline unsigned blocks_by_xcd(long long n_chunks) { return (unsigned)((n_chunks + kXcds * kWavesPerBlock - 1) / (kXcds * kWavesPerBlock)) * kXcds; }
 inline unsigned blocks_for(long long n, int per_block) { return (unsigned)((n + per_block - 1) / per_block); }
 
 // ------------------------------------------------------- backward of the attention layer
@@ -1995,23 +2003,27 @@ struct GatDtArgs {
     const float *logits, *dalpha, *rowdot;
     const float2 *mz;
     const int32_t *t_pos;   // place of entry k in the transposed pattern
-    float *dt;
+    float *dt;              // SUMS: not written, may be null
     float2 *adt_t;          // (alpha, dt) at the entry's place in the transposed pattern: one 8-byte scattered store
+    float *rowsum, *carry;  // SUMS: row sums of dt (+ per-chunk carry slots)
     float slope;
 };
 
 // Softmax and LeakyReLU backward per stored entry: alpha = exp(e - m_i) / z_i, de = alpha (dalpha - rowdot_i),
-// dt = de * (e > 0 ? 1 : slope) (e > 0 exactly when the pre-activation is).  dt is kept in row order (for the row
-// sums ds_l) and, together with alpha, written at its place in the transposed pattern (for ds_r and alpha^T dP).
-template <int PER>
+// dt = de * (e > 0 ? 1 : slope) (e > 0 exactly when the pre-activation is).  (alpha, dt) is written at the entry's place in the transposed
+// pattern (for ds_r and alpha^T dP); in row order dt is either kept, or summed over the rows at once (SUMS: ds_l).
+// The scattered stores bound it: entries of consecutive rows go to consecutive places of a transposed row, so a line fills up over many
+// rows, and with neighbouring chunks on different XCDs every L2 holds a piece of it and writes it out by itself.  Chunks are therefore
+// given out so that an XCD has one range of them (2.1 M entries with the row sums 32 + 7 -> 27 us, 3 M entries without 53 -> 47).
+template <bool SUMS, int PER>
 __global__ __launch_bounds__(kBlock) void k_gat_dt(GatDtArgs a) {
     __shared__ FlatLds<PER> lds;
-    const int chunk = wave_chunk(), lane = threadIdx.x & 63;
+    const int chunk = wave_chunk_by_xcd(), lane = threadIdx.x & 63;
     if (chunk >= a.n.n_chunks) return;
     int *rows = lds.row[threadIdx.x >> 6];
-    const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [](int, bool) {});
+    const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [&](int r0, bool none) { if (SUMS && none) a.rowsum[r0 + lane] = 0.f; });
     if (c.lo >= c.hi) return;
-    float e[PER], da[PER];
+    float e[PER], da[PER], t[PER];
     int p[PER];
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
@@ -2026,10 +2038,20 @@ __global__ __launch_bounds__(kBlock) void k_gat_dt(GatDtArgs a) {
         const float2 st = a.mz[i];
         const float al = expf(e[u] - st.x) * inv_z(st.y);
         const float dt = al * (da[u] - a.rowdot[i]) * (e[u] > 0.f ? 1.f : a.slope);
+        t[u] = 0.f;
         if (k < c.hi) {
-            a.dt[k] = dt;
+            if (SUMS) t[u] = dt;
+            else a.dt[k] = dt;
             a.adt_t[p[u]] = make_float2(al, dt);
         }
+    }
+    if (SUMS) {
+        float v[PER];
+        to_blocked<PER>(lds.val[threadIdx.x >> 6], lane, t, v);
+        flat_sum<PER>(c, lane, v, [&](int i, float sum, int) {
+            if (c.cont && i == c.i_first) a.carry[chunk] = sum;
+            else a.rowsum[i] = sum;
+        });
     }
 }
 
@@ -2483,14 +2505,19 @@ hipError_t launch_score_v2(const sensei_csr &A, const float *theta_l, const floa
 }
 
 hipError_t launch_gat_dt(const sensei_csr &A, const float *logits, const float *dalpha, const float *rowdot, const float2 *mz,
-                         const int32_t *t_pos, float slope, float *dt, float2 *adt_t, const ChunkPlan &p, hipStream_t s) {
-    if (A.nnz <= 0) return hipSuccess;
+                         const int32_t *t_pos, float slope, float *dt, float2 *adt_t, const ChunkPlan &p, hipStream_t s, float *rowsum, float *carry) {
+    if (A.nnz <= 0 && !rowsum) return hipSuccess;
     GatDtArgs a;
     a.n = nnz_args(A, p);
     a.logits = logits; a.dalpha = dalpha; a.rowdot = rowdot; a.mz = mz; a.t_pos = t_pos; a.dt = dt; a.adt_t = adt_t;
+    a.rowsum = rowsum; a.carry = carry;
     a.slope = slope;
+    const dim3 grid(blocks_by_xcd(p.n_chunks));
     return with_per(p.chunk_nnz, [&](auto per) {
-        hipLaunchKernelGGL(k_gat_dt<per()>, dim3(blocks_for(p.n_chunks, kWavesPerBlock)), dim3(kBlock), 0, s, a);
+        if (rowsum) hipLaunchKernelGGL((k_gat_dt<true, per()>), grid, dim3(kBlock), 0, s, a);
+        else hipLaunchKernelGGL((k_gat_dt<false, per()>), grid, dim3(kBlock), 0, s, a);
+        if (rowsum && p.n_chunks > 1)
+            hipLaunchKernelGGL(k_sum_fixup, dim3(blocks_for(p.n_chunks - 1, kBlock)), dim3(kBlock), 0, s, a.n, rowsum, carry);
     });
 }
 
