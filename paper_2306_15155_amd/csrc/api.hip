@@ -1250,10 +1250,13 @@ int run_gat_backward(const sensei_csr &A, const sensei_csr &At, const int32_t *t
         SENSEI_TRY(hipEventRecord(D.ev_join, D.side));
         sensei_csr Ar = A;
         Ar.nnz = D.nnz_rem; Ar.row_ptr = D.row_ptr_rem; Ar.col_idx = D.col_rem; Ar.panels = nullptr; Ar.tiles = nullptr;
-        SENSEI_TRY(launch_gat_dalpha(Ar, theta, T, f_out, nullptr, nullptr, dalpha_rem, nullptr, D.plan_rem, sum_carry, s));
+        // panel-major where the split has that copy: the part of a slice that is gathered from at a time is one panel's
+        const bool pm = remainder_panels_usable(D, f_out);
+        if (pm) { Ar.n_rows = D.rem_panels * A.n_rows; Ar.row_ptr = D.seg_ptr; Ar.col_idx = D.col_pm; }
+        SENSEI_TRY(launch_gat_dalpha(Ar, theta, T, f_out, nullptr, nullptr, dalpha_rem, nullptr, pm ? D.plan_pm : D.plan_rem, sum_carry, s, 1.f, A.n_rows));
         SENSEI_TRY(hipStreamWaitEvent(s, D.ev_join, 0));
         if (split_t) SENSEI_TRY(fork_transposed_tiles());  // the side stream goes on while this one merges
-        SENSEI_TRY(launch_gat_dalpha_merge(A, D.dst_rem, dalpha_rem, Dt, logits, stats, dt, rowdot, plan, sum_carry, s));
+        SENSEI_TRY(launch_gat_dalpha_merge(A, D.dst_rem, dalpha_rem, Dt, logits, stats, dt, rowdot, plan, sum_carry, s, pm ? D.pos_pm : nullptr));
     } else {
         if (split_t) SENSEI_TRY(fork_transposed_tiles());
         SENSEI_TRY(launch_gat_dalpha(A, theta, T, f_out, logits, stats, dt, rowdot, plan, sum_carry, s));

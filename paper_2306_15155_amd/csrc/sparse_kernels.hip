@@ -1854,6 +1854,7 @@ struct GatBwdArgs {
     float *rowdot, *carry;    // out, per row: sum_j alpha_ij dalpha_ij (+ per-chunk carry slots)
     long long theta_tile, dp_tile;  // floats from one tile to the next
     int n_tiles;
+    int dp_rows;  // rows of dP; row r of the pattern is row r mod dp_rows (r >= dp_rows: a segment of a panel-major pattern)
     float scale;  // factor on every dot product (1 in the attention backward; the 1 / sqrt(d) of a key-query score)
 };
 
@@ -1881,8 +1882,11 @@ __global__ __launch_bounds__(kBlock) void k_gat_dalpha(GatBwdArgs a, int tile, i
         lds_exchange();
     }
     struct Got { float sum, e; float2 st; };
+    const int panel_row = c.i_first / a.dp_rows * a.dp_rows;   // first row of the panel the chunk begins in
     flat_dots<PER>(c, rows, lane, a.n.col_idx, theta,
                    [&](int i, float4 &p, float4 &q) {
+                       i -= panel_row;
+                       while (i >= a.dp_rows) i -= a.dp_rows;   // only where a chunk runs over the end of its panel
                        p = *reinterpret_cast<const float4 *>(dP + (size_t)i * 32);
                        q = *reinterpret_cast<const float4 *>(dP + (size_t)i * 32 + 16);
                    },
@@ -1914,10 +1918,10 @@ __global__ __launch_bounds__(kBlock) void k_gat_dalpha(GatBwdArgs a, int tile, i
 }
 
 // dalpha of every stored entry from its two sources when the pattern carries a dense-tile split: where[k] >= 0 is the place of
-// entry k in the remainder (dalpha_rem), a negative value -(cell + 1) the cell of the dense product Dt that holds it.  Writes
+// entry k in the remainder (dalpha_rem, or with `place` dalpha_rem[place[.]]: the remainder's panel-major order), a negative value -(cell + 1) the cell of the dense product Dt that holds it.  Writes
 // dalpha in the order of the pattern and forms the row sums sum_j alpha_ij dalpha_ij.
 template <int PER>
-__global__ __launch_bounds__(kBlock) void k_gat_dalpha_merge(NnzArgs a, const int32_t *__restrict__ where, const float *__restrict__ dalpha_rem,
+__global__ __launch_bounds__(kBlock) void k_gat_dalpha_merge(NnzArgs a, const int32_t *__restrict__ where, const int32_t *__restrict__ place, const float *__restrict__ dalpha_rem,
                                                               const float *__restrict__ Dt, const float *__restrict__ logits,
                                                               const float2 *__restrict__ mz, float *__restrict__ dalpha,
                                                               float *__restrict__ rowdot, float *__restrict__ carry) {
@@ -1934,6 +1938,10 @@ __global__ __launch_bounds__(kBlock) void k_gat_dalpha_merge(NnzArgs a, const in
         const int k = c.lo + u * 64 + lane, kc = k < c.hi ? k : c.lo;
         w[u] = where[kc];
         e[u] = logits[kc];
+    }
+    if (place) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) w[u] = w[u] >= 0 ? place[w[u]] : w[u];
     }
 #pragma unroll
     for (int u = 0; u < PER; ++u) v[u] = w[u] >= 0 ? dalpha_rem[w[u]] : Dt[-(long long)w[u] - 1];
@@ -2459,14 +2467,15 @@ hipError_t launch_row_sum(const sensei_csr &A, const float *val, int stride, flo
 }
 
 hipError_t launch_gat_dalpha(const sensei_csr &A, const float *theta, const float *dP, int f, const float *logits, const float2 *mz,
-                             float *dalpha, float *rowdot, const ChunkPlan &p, float *carry, hipStream_t s, float scale) {
+                             float *dalpha, float *rowdot, const ChunkPlan &p, float *carry, hipStream_t s, float scale, int dp_rows) {
     GatBwdArgs a;
     a.scale = scale;
     a.n = nnz_args(A, p);
     a.theta = theta; a.dP = dP; a.logits = logits; a.mz = mz; a.dalpha = dalpha; a.rowdot = rowdot; a.carry = carry;
     a.theta_tile = (long long)(A.n_cols > 0 ? A.n_cols : 1) * 32;
-    a.dp_tile = (long long)(A.n_rows > 0 ? A.n_rows : 1) * 32;
+    a.dp_tile = (long long)(dp_rows > 0 ? dp_rows : A.n_rows > 0 ? A.n_rows : 1) * 32;
     a.n_tiles = (f + 31) / 32;
+    a.dp_rows = dp_rows > 0 ? dp_rows : A.n_rows > 0 ? A.n_rows : 1;
     const dim3 grid(blocks_for(p.n_chunks, kWavesPerBlock));
     if (A.nnz <= 0 && !rowdot) return hipSuccess;
     return with_per(p.chunk_nnz, [&](auto per) {
@@ -2480,10 +2489,10 @@ hipError_t launch_gat_dalpha(const sensei_csr &A, const float *theta, const floa
 }
 
 hipError_t launch_gat_dalpha_merge(const sensei_csr &A, const int32_t *where, const float *dalpha_rem, const float *Dt, const float *logits,
-                                   const float2 *mz, float *dalpha, float *rowdot, const ChunkPlan &p, float *carry, hipStream_t s) {
+                                   const float2 *mz, float *dalpha, float *rowdot, const ChunkPlan &p, float *carry, hipStream_t s, const int32_t *place) {
     const NnzArgs n = nnz_args(A, p);
     return with_per(p.chunk_nnz, [&](auto per) {
-        hipLaunchKernelGGL(k_gat_dalpha_merge<per()>, dim3(blocks_for(p.n_chunks, kWavesPerBlock)), dim3(kBlock), 0, s, n, where, dalpha_rem, Dt, logits,
+        hipLaunchKernelGGL(k_gat_dalpha_merge<per()>, dim3(blocks_for(p.n_chunks, kWavesPerBlock)), dim3(kBlock), 0, s, n, where, place, dalpha_rem, Dt, logits,
                            mz, dalpha, rowdot, carry);
         if (p.n_chunks > 1) hipLaunchKernelGGL(k_sum_fixup, dim3(blocks_for(p.n_chunks - 1, kBlock)), dim3(kBlock), 0, s, n, rowdot, carry);
     });
