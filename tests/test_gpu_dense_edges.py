@@ -53,3 +53,30 @@ def test_weight_gradient_columns(n, f_in, f_out):
     ref, mag = x.double().t() @ dy.double(), x.double().abs().t() @ dy.double().abs()
     assert bool(((dw.double() - ref).abs() <= (32 * 6 + 1) * 2.0 ** -24 * mag).all())
     ctx.close()
+
+
+# the per-entry products of kept tiles: a full pattern (whole tiles, and a last row and column of tiles that are partly empty) with zero
+# attention vectors, where alpha = 1 / n, every logit sits on the LeakyReLU's lower branch, and da_r = Theta^T ds_r is what the products
+# <dP_i, Theta_j> reach; Theta = W exactly (X is the identity).  Bound: f + 8 roundings per product, n + 8 in each of the two sums over
+# nodes it passes through.
+@pytest.mark.parametrize("n,f", [(128, 96), (128, 128), (300, 160), (300, 256)])
+def test_tile_products_of_the_attention_backward(n, f):
+    from paper_2306_15155_amd import Context, Tiles, csr_struct
+    ctx, slope = Context(0), 0.2
+    g = torch.Generator(device="cuda").manual_seed(n * 31 + f)
+    row_ptr = (torch.arange(n + 1, device="cuda") * n).to(torch.int32)
+    col_idx = torch.arange(n, device="cuda", dtype=torch.int32).repeat(n)
+    W, dY = torch.randn(n, f, generator=g, device="cuda"), torch.randn(n, f, generator=g, device="cuda")
+    X, zero = torch.eye(n, device="cuda"), torch.zeros(f, device="cuda")
+    A = csr_struct(n, n, row_ptr, col_idx)
+    T = Tiles(ctx, A, 0.05, 256, min_width=32)
+    assert T.n_tiles == ((n + 127) // 128) ** 2
+    Ah = csr_struct(n, n, row_ptr, col_idx, tiles=T)
+    got = ctx.gat_backward(Ah, Ah, ctx.transpose_positions(A, A), X, W, zero, zero, dY, neg_slope=slope)[3].double()
+    D = dY.double() @ W.double().t()
+    ref = W.double().t() @ ((D - D.mean(1, keepdim=True)) * (slope / n)).sum(0)
+    M = dY.double().abs() @ W.double().abs().t()
+    bound = W.double().abs().t() @ ((M + M.mean(1, keepdim=True)) * (slope / n)).sum(0) * (f + 2 * n + 24) * 2.0 ** -24
+    assert bool(((got - ref).abs() <= bound).all()), float(((got - ref).abs() / bound).max())
+    T.close()
+    ctx.close()
