@@ -55,10 +55,11 @@ def test_weight_gradient_columns(n, f_in, f_out):
     ctx.close()
 
 
-# the per-entry products of kept tiles: a full pattern (whole tiles, and a last row and column of tiles that are partly empty) with zero
-# attention vectors, where alpha = 1 / n, every logit sits on the LeakyReLU's lower branch, and da_r = Theta^T ds_r is what the products
-# <dP_i, Theta_j> reach; Theta = W exactly (X is the identity).  Bound: f + 8 roundings per product, n + 8 in each of the two sums over
-# nodes it passes through.
+# the per-entry products of kept tiles, their places: a full pattern (whole tiles, and a last row and column of tiles that are partly empty)
+# with zero attention vectors, where alpha = 1 / n, every logit sits on the LeakyReLU's lower branch, and da_r = Theta^T ds_r is what the
+# products <dP_i, Theta_j> reach; Theta = W exactly (X is the identity).  96 columns are below the width from which tiles serve these products
+# and take the per-entry kernel.  Bound: f + 8 roundings per product, n + 8 in each of the two sums over nodes it passes through: wide enough
+# to pass products of fewer bits, which the test after this one measures.
 @pytest.mark.parametrize("n,f", [(128, 96), (128, 128), (300, 160), (300, 256)])
 def test_tile_products_of_the_attention_backward(n, f):
     from paper_2306_15155_amd import Context, Tiles, csr_struct
@@ -78,5 +79,44 @@ def test_tile_products_of_the_attention_backward(n, f):
     M = dY.double().abs() @ W.double().abs().t()
     bound = W.double().abs().t() @ ((M + M.mean(1, keepdim=True)) * (slope / n)).sum(0) * (f + 2 * n + 24) * 2.0 ** -24
     assert bool(((got - ref).abs() <= bound).all()), float(((got - ref).abs() / bound).max())
+    T.close()
+    ctx.close()
+
+
+# their accuracy: one row of dY with one element, so that every product of that row is a single term d Theta_jq and reaches dW unsummed.  X is
+# the identity, all logits are 1 (columns 1 and 2 of Theta are 1 and the attention vectors select them), alpha = 2^-8 exactly, and column 1 of
+# dW is dt of that row: 2^-8 (d Theta_jq - m), m the row's mean.  The difference of neighbours is free of m.  Each product may be one fp32
+# rounding off, the subtraction of m another, and m itself is 0 but for one node's term; the rest is exact, so 3 units of 2^-24 hold any
+# fp32 product.  Theta holds full 24-bit significands and, every fourth pair, 1 + 2^-7 - 2^-23, whose pieces of eight bits are as large as they get.
+@pytest.mark.parametrize("f", [128, 160, 256])
+def test_tile_products_keep_all_bits(f):
+    from paper_2306_15155_amd import Context, Tiles, csr_struct
+    ctx, n = Context(0), 256
+    g = torch.Generator(device="cuda").manual_seed(f)
+    row_ptr = (torch.arange(n + 1, device="cuda") * n).to(torch.int32)
+    col_idx = torch.arange(n, device="cuda", dtype=torch.int32).repeat(n)
+    A = csr_struct(n, n, row_ptr, col_idx)
+    T = Tiles(ctx, A, 0.05, 256, min_width=32)
+    assert T.n_tiles == 4
+    Ah, pos = csr_struct(n, n, row_ptr, col_idx, tiles=T), ctx.transpose_positions(A, A)
+    half = 1.0 + torch.rand(n // 2, f, generator=g, device="cuda")
+    half[::4] = 1.0 + 2.0 ** -7 - 2.0 ** -23
+    theta = torch.stack([half, -half], 1).reshape(n, f).contiguous()   # neighbours cancel in the mean
+    theta[:, 1:3] = 1.0
+    a_l, a_r = torch.zeros(f, device="cuda"), torch.zeros(f, device="cuda")
+    a_l[2] = a_r[1] = 0.5
+    X, worst = torch.eye(n, device="cuda"), 0.0
+    for q, i in ((0, 0), (3, 127), (17, 128), (f // 2 + 5, 200), (f - 1, 255)):
+        for d in (1.0 + 2.0 ** -7 - 2.0 ** -23, 1.7320508):
+            dY = torch.zeros(n, f, device="cuda")
+            dY[i, q] = d
+            dW = ctx.gat_backward(Ah, Ah, pos, X, theta, a_l, a_r, dY, neg_slope=0.2)[1]
+            ds_r = 2.0 * dW[:, 1].double()   # a_r[1] = 1 / 2
+            term = theta[:, q].double() * float(dY[i, q])
+            got, want = ds_r[0::2] - ds_r[1::2], (term[0::2] - term[1::2]) * 2.0 ** -8
+            mag = (term[0::2].abs() + term[1::2].abs()) * 2.0 ** -8
+            worst = max(worst, float(((got - want).abs() / mag).max()) * 2.0 ** 24)
+    print(f"{f} columns: {worst:.2f} units of 2^-24")
+    assert worst <= 3.0, worst
     T.close()
     ctx.close()
