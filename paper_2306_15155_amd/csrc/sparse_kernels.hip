@@ -933,7 +933,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_fixup(SpmmArgs a) {
     const int q0 = blockIdx.y * a.fix_quads, n_q = min((a.f_store + 3) / 4 - q0, a.fix_quads);   // quads of columns of this workgroup
     auto add4 = [](float4 &x, const float4 &y) { x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w; };
     const bool vec_ok = a.store_vec_ok && a.ldc % 4 == 0 && (reinterpret_cast<uintptr_t>(a.C) & 15) == 0;
-    // a quad of columns never straddles feature tiles (c_tf is a power of two, 32 or more)
+    // a quad of columns never straddles feature tiles (c_tf is a power of two, 8 or more)
     auto place = [&](int row, int f) { return a.C + (size_t)(f >> a.c_shift) * a.c_tile + (size_t)row * a.ldc + (f & (a.c_tf - 1)); };
     auto fetch = [&](const float *dst, int f) {
         if (vec_ok && f + 4 <= a.f_store) return *reinterpret_cast<const float4 *>(dst);
@@ -1090,6 +1090,7 @@ hipError_t spmm_flat_mode(const SpmmArgs &a, int mode, dim3 grid, hipStream_t s)
 template <int VEC>
 hipError_t spmm_dispatch_lpg(const SpmmArgs &a, int mode, int lpg, bool off32, dim3 grid, hipStream_t s) {
     switch (lpg) {
+        case 8: return off32 ? spmm_dispatch_mode<VEC, 8, true>(a, mode, grid, s) : spmm_dispatch_mode<VEC, 8, false>(a, mode, grid, s);
         case 16: return off32 ? spmm_dispatch_mode<VEC, 16, true>(a, mode, grid, s) : spmm_dispatch_mode<VEC, 16, false>(a, mode, grid, s);
         case 32: return off32 ? spmm_dispatch_mode<VEC, 32, true>(a, mode, grid, s) : spmm_dispatch_mode<VEC, 32, false>(a, mode, grid, s);
         default: return off32 ? spmm_dispatch_mode<VEC, 64, true>(a, mode, grid, s) : spmm_dispatch_mode<VEC, 64, false>(a, mode, grid, s);
@@ -2263,8 +2264,10 @@ SpmmShape spmm_shape(const float *B, int64_t ldb, int f) {
     // A neighbour group reads one 128-byte line per neighbour (32 floats) and the feature tiles are spread
     // over the XCDs.  Rows that do not fill whole groups use one wider group instead when that covers the
     // row in a single tile (measured faster than leaving a nearly empty last tile); very wide rows that allow only narrow loads use
-    // wider groups so the number of tiles stays moderate.
+    // wider groups so the number of tiles stays moderate.  Rows of a few 8- or 4-byte words take the narrowest group that covers them:
+    // more neighbours per step (1 M nodes of a grid, one column: 156 us with 32 lanes a neighbour, 59 with 8).
     int lpg = 32 / sh.vec;
+    while (lpg > 8 && lpg / 2 >= fv) lpg >>= 1;
     if (fv > lpg && fv <= 32 && fv % lpg != 0) while (lpg < fv) lpg <<= 1;
     if (sh.vec < 4) while (lpg < 64 && (fv + lpg - 1) / lpg > 32) lpg <<= 1;
     sh.lpg = lpg;

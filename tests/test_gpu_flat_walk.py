@@ -103,3 +103,18 @@ def test_flat_spmm_at_chunk_boundaries(ctx, t, least):
     got = ctx.gatv2_backward(A.s, At.s, ctx.transpose_positions(A.s, At.s), dev(X), dev(Wl), dev(W), dev(a_l), dev(dY), neg_slope=1.0)
     for gpu, ref, what in zip(got, want, ("dX", "dW_l", "dW_r", "datt")):
         assert_close(gpu, ref, what=what)
+
+
+# operands of 8- and 4-byte words: widths on both sides of every lane group (8, 16, 32 lanes) and of two tiles
+@pytest.mark.parametrize("t,least", [(64, 3_000), (512, 530_000)])
+def test_spmm_on_narrow_words(ctx, t, least):
+    g = pattern(t, least)
+    row = np.repeat(np.arange(g.n_rows), np.diff(g.row_ptr))
+    A, r, c = DeviceCSR(g), synth.uniform(t, 9, (g.n_rows,), 0.5, 1.5), synth.uniform(t, 10, (g.n_cols,), 0.5, 1.5)
+    for f, ld in ((1, 1), (1, 3), (2, 2), (3, 3), (7, 7), (8, 9), (9, 9), (10, 10), (16, 17), (16, 18), (18, 18), (31, 31), (33, 33), (62, 62)):
+        B = synth.uniform(t, f, (g.n_cols, ld))
+        ref = np.zeros((g.n_rows, f))
+        w = r[row].astype(np.float64) * c[g.col_idx]
+        for lo in range(0, g.nnz, 1 << 18):
+            np.add.at(ref, row[lo:lo + (1 << 18)], w[lo:lo + (1 << 18), None] * B[g.col_idx[lo:lo + (1 << 18)], :f].astype(np.float64))
+        assert_close(ctx.spmm(A.s, SPMM_SCALED, dev(B)[:, :f], dev(r), dev(c), ACT_NONE), ref, what=f"{f} of {ld} columns")
