@@ -2261,15 +2261,16 @@ SpmmShape spmm_shape(const float *B, int64_t ldb, int f) {
     else if (f % 2 == 0 && ldb % 2 == 0 && addr % 8 == 0) sh.vec = 2;
     else sh.vec = 1;
     const int fv = (f + sh.vec - 1) / sh.vec;  // vector columns
-    // A neighbour group reads one 128-byte line per neighbour (32 floats) and the feature tiles are spread
-    // over the XCDs.  Rows that do not fill whole groups use one wider group instead when that covers the
-    // row in a single tile (measured faster than leaving a nearly empty last tile); very wide rows that allow only narrow loads use
-    // wider groups so the number of tiles stays moderate.  Rows of a few 8- or 4-byte words take the narrowest group that covers them:
-    // more neighbours per step (1 M nodes of a grid, one column: 156 us with 32 lanes a neighbour, 59 with 8).
+    // A neighbour group reads one 128-byte line per neighbour (32 floats) and the feature tiles are spread over the XCDs.  Rows that do not
+    // fill whole groups use one wider group instead when that covers the row in a single tile (measured faster than leaving a nearly empty
+    // last tile).  Very wide rows use wider groups so that the number of tiles stays moderate: every tile of a chunk finds the rows and reads
+    // the columns again (50,000 rows of 12 entries, 4,096 columns: 1,635 us in 128 tiles of 8 lanes, 1,378 in 32 of 32), and the grid, tiles
+    // times chunks, has to stay below 2^32 threads.  Rows of a few 8- or 4-byte words take the narrowest group that covers them: more
+    // neighbours per step (1 M nodes of a grid, one column: 156 us with 32 lanes a neighbour, 57 with 8).
     int lpg = 32 / sh.vec;
     while (lpg > 8 && lpg / 2 >= fv) lpg >>= 1;
     if (fv > lpg && fv <= 32 && fv % lpg != 0) while (lpg < fv) lpg <<= 1;
-    if (sh.vec < 4) while (lpg < 64 && (fv + lpg - 1) / lpg > 32) lpg <<= 1;
+    while (lpg < 64 && (fv + lpg - 1) / lpg > 32) lpg <<= 1;
     sh.lpg = lpg;
     sh.n_tiles = (fv + lpg - 1) / lpg;
     sh.f_carry = sh.n_tiles * lpg * sh.vec;
@@ -2337,7 +2338,8 @@ hipError_t launch_spmm(const sensei_csr &A, int mode, const float *r, const floa
     if (t1 && hipEventRecord(t0, s) != hipSuccess) return hipErrorUnknown;
     const bool flat = sh.vec == 4;
     if (flat && sh.lpg == 8) err = off32 ? spmm_flat_mode<8, true>(a, mode, grid, s) : spmm_flat_mode<8, false>(a, mode, grid, s);
-    else if (flat) err = sh.lpg == 16 ? spmm_flat_mode<16, false>(a, mode, grid, s) : spmm_flat_mode<32, false>(a, mode, grid, s);
+    else if (flat) err = sh.lpg == 16 ? spmm_flat_mode<16, false>(a, mode, grid, s) : sh.lpg == 32 ? spmm_flat_mode<32, false>(a, mode, grid, s)
+                                                                                         : spmm_flat_mode<64, false>(a, mode, grid, s);
     else switch (sh.vec) {
         case 2: err = spmm_dispatch_lpg<2>(a, mode, sh.lpg, off32, grid, s); break;
         default: err = spmm_dispatch_lpg<1>(a, mode, sh.lpg, off32, grid, s); break;

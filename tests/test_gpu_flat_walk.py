@@ -118,3 +118,21 @@ def test_spmm_on_narrow_words(ctx, t, least):
         for lo in range(0, g.nnz, 1 << 18):
             np.add.at(ref, row[lo:lo + (1 << 18)], w[lo:lo + (1 << 18), None] * B[g.col_idx[lo:lo + (1 << 18)], :f].astype(np.float64))
         assert_close(ctx.spmm(A.s, SPMM_SCALED, dev(B)[:, :f], dev(r), dev(c), ACT_NONE), ref, what=f"{f} of {ld} columns")
+
+
+# wide row-major operands: groups of 16, 32 and 64 lanes, widths that fill their last tile and widths that do not (the pattern has too few
+# entries per column for the slice-major copy)
+@pytest.mark.parametrize("f", [1_028, 2_048, 2_052, 4_096, 4_100, 8_192, 8_196])
+def test_spmm_on_wide_rows(ctx, f):
+    g = pattern(64, 3_000)
+    row = np.repeat(np.arange(g.n_rows), np.diff(g.row_ptr))
+    val = synth.uniform(f, 8, (g.nnz,))
+    gen = torch.Generator(device="cuda").manual_seed(f)
+    B = torch.randn(g.n_cols, f, generator=gen, device="cuda")
+    col, rows = torch.from_numpy(g.col_idx).long().cuda(), torch.from_numpy(row).cuda()
+    for mode, A, w in ((SPMM_PATTERN, DeviceCSR(g), None), (SPMM_WEIGHTED, DeviceCSR(g, val), dev(val).double()[:, None])):
+        ref = torch.zeros(g.n_rows, f, dtype=torch.float64, device="cuda")
+        for lo in range(0, g.nnz, 4096):
+            x = B[col[lo:lo + 4096]].double()
+            ref.index_add_(0, rows[lo:lo + 4096], x if w is None else w[lo:lo + 4096] * x)
+        assert_close(ctx.spmm(A.s, mode, B), ref.cpu().numpy(), what=f"mode {mode}, {f} columns")

@@ -32,3 +32,11 @@ def shape():
 def test_narrow_rows_take_narrow_groups(shape, f, ld, vec, lpg):
     s = shape(f, ld)
     assert (s.vec, s.lpg, s.n_tiles) == (vec, lpg, 1)
+
+
+# every tile walks the pattern again: at most 32 of them until a group is a whole wavefront
+@pytest.mark.parametrize("f,vec,lpg,tiles", [(1024, 4, 8, 32), (1028, 4, 16, 17), (2048, 4, 16, 32), (4096, 4, 32, 32), (8192, 4, 64, 32), (16384, 4, 64, 64),
+                                             (4098, 2, 64, 33), (4097, 1, 64, 65)])
+def test_wide_rows_take_wide_groups(shape, f, vec, lpg, tiles):
+    s = shape(f)
+    assert (s.vec, s.lpg, s.n_tiles) == (vec, lpg, tiles)
