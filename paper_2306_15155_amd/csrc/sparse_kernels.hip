@@ -1330,14 +1330,9 @@ __global__ void k_to_slices(const float *__restrict__ s, const float *__restrict
 // ------------------------------------------------------------- edge softmax
 
 // (m, z) pairs: z = sum of exp(e - m).  Merge keeps m the larger maximum.
-__device__ __forceinline__ void mz_add(float &m, float &z, float e) {  // e finite; branch-free: lanes of a wavefront disagree on e > m
-    const float mm = e > m ? e : m;
-    z = z * __expf(m - mm) + __expf(e - mm);  // m = -inf at the start: exp(-inf) = 0 and z = 0
-    m = mm;
-}
 __device__ __forceinline__ void mz_merge(float &m, float &z, float m2, float z2) {
     const float mm = m > m2 ? m : m2;
-    if (mm == -INFINITY) { m = mm; z = 0.f; return; }
+    if (mm == -INFINITY) { m = mm; z += z2; return; }   // nothing but -inf so far: both sums are 0, or NaN
     z = z * expf(m - mm) + z2 * expf(m2 - mm);
     m = mm;
 }
@@ -1417,7 +1412,8 @@ __global__ __launch_bounds__(kBlock) void k_softmax_stats(SoftmaxArgs a) {
             started = true;
             rz = 0.f;
         }
-        if (q < n_mine) rz += __expf(e[q] - mx[q]);
+        // entries of -inf (masked out) weigh 0, also where the lane holds no others of their row
+        if (q < n_mine) rz += __expf(e[q] - (mx[q] == -INFINITY ? 0.f : mx[q]));
     }
     float m = mx[PER - 1], z = rz;
     int f = started;

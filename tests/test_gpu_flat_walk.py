@@ -105,6 +105,30 @@ def test_flat_spmm_at_chunk_boundaries(ctx, t, least):
         assert_close(gpu, ref, what=what)
 
 
+# logits of -inf (masked entries) weigh 0 wherever they stand in their row; a row of nothing else is NaN, as 0 / 0 is; the lowest finite
+# value is an ordinary logit
+@pytest.mark.parametrize("mask", [-np.inf, np.finfo(np.float32).min])
+@pytest.mark.parametrize("t,least", [(64, 3_000), (128, 140_000), (256, 270_000), (512, 530_000)])
+def test_softmax_of_masked_logits(ctx, t, least, mask):
+    g = pattern(t, least)
+    n, A, row = g.n_rows, DeviceCSR(g), np.repeat(np.arange(g.n_rows), np.diff(g.row_ptr))
+    pos = np.arange(g.nnz) - g.row_ptr[row]
+    rng = np.random.default_rng(t + 1)
+    for what, hit in (("one in 500", rng.random(g.nnz) < 0.002), ("a third", rng.random(g.nnz) < 0.33), ("the first of a row", pos == 0),
+                      ("the first 600 of a row", pos < 600), ("all", np.ones(g.nnz, bool))):
+        e = np.where(hit, np.float32(mask), synth.normal(t, 1, (g.nnz,)))
+        m = np.full(n, -np.inf)
+        np.maximum.at(m, row, e)
+        with np.errstate(invalid="ignore"):
+            p = np.exp(e.astype(np.float64) - m[row])
+            z = np.zeros(n)
+            np.add.at(z, row, p)
+            want = p / z[row]
+        got = ctx.edge_softmax(A.s, dev(e)).cpu().numpy()
+        assert np.array_equal(np.isnan(got), np.isnan(want)), f"{what}: {np.isnan(got).sum()} NaN, {np.isnan(want).sum()} wanted"
+        assert_close(np.nan_to_num(got), np.nan_to_num(want), tol=4e-6, what=what)   # as above
+
+
 # operands of 8- and 4-byte words: widths on both sides of every lane group (8, 16, 32 lanes) and of two tiles
 @pytest.mark.parametrize("t,least", [(64, 3_000), (512, 530_000)])
 def test_spmm_on_narrow_words(ctx, t, least):
