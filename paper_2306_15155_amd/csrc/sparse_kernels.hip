@@ -233,8 +233,8 @@ __device__ __forceinline__ void to_blocked(float *val, int lane, const float (&s
     for (int e = 0; e < PER; ++e) blocked[e] = val[lane * PER + e];
 }
 
-// SpMM on a row-major operand whose rows allow only 8- or 4-byte loads (odd leading dimension or width); everything else takes
-// k_spmm_flat below.  One wavefront = one (chunk, feature tile).  The 64 lanes form G = 64/LPG
+// SpMM on a row-major operand whose rows allow only 8- or 4-byte loads (odd leading dimension or width), and value-less on patterns of
+// very short rows (spmm_by_rows); everything else takes k_spmm_flat below.  One wavefront = one (chunk, feature tile).  The 64 lanes form G = 64/LPG
 // neighbour groups of LPG lanes; a group reads VEC*LPG consecutive floats of
 // one neighbour row per step, so G
 // neighbours are in flight per step and 4 steps are issued back to back.
@@ -414,6 +414,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm(SpmmArgs a) {
             for (int k = rs; k < rend; k += U) {
                 Vec<VEC> b[U];
                 float ww[U];
+                unsigned live[U];   // a weight of 0 alone would make NaN of an infinity (masks, not branches around the gathers)
 #pragma unroll
                 for (int q = 0; q < U; ++q) {
                     const bool valid = k + q < rend;
@@ -431,6 +432,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm(SpmmArgs a) {
                         ww[q] = valid ? wq : 0.f;
                     }
                     b[q] = gather(j);
+                    live[q] = valid ? ~0u : 0u;
                 }
                 if (MODE == kSpmmAttnFused) {  // one rescale for the four neighbours of the step
                     float mn = rm;
@@ -450,7 +452,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm(SpmmArgs a) {
 #pragma unroll
                 for (int q = 0; q < U; ++q) {
 #pragma unroll
-                    for (int e = 0; e < VEC; ++e) racc.v[e] = fmaf(ww[q], b[q].v[e], racc.v[e]);
+                    for (int e = 0; e < VEC; ++e) racc.v[e] = fmaf(ww[q], __uint_as_float(__float_as_uint(b[q].v[e]) & live[q]), racc.v[e]);
                 }
             }
             if (MODE == kSpmmAttnFused && rok && tile == 0 && (lane % LPG) == 0) {
@@ -1053,6 +1055,17 @@ hipError_t spmm_dispatch_mode(const SpmmArgs &a, int mode, dim3 grid, hipStream_
         case kSpmmSignSum:
         case kSpmmLreluSum: return hipErrorInvalidValue;   // slice-major operands only
         default: hipLaunchKernelGGL((k_spmm<VEC, LPG, SENSEI_SPMM_SCALED, OFF32>), grid, dim3(kBlock), 0, s, a); break;
+    }
+    return hipGetLastError();
+}
+
+template <bool OFF32>
+hipError_t spmm_rows_pattern(const SpmmArgs &a, int lpg, dim3 grid, hipStream_t s) {
+    switch (lpg) {
+        case 8: hipLaunchKernelGGL((k_spmm<4, 8, SENSEI_SPMM_PATTERN, OFF32>), grid, dim3(kBlock), 0, s, a); break;
+        case 16: hipLaunchKernelGGL((k_spmm<4, 16, SENSEI_SPMM_PATTERN, OFF32>), grid, dim3(kBlock), 0, s, a); break;
+        case 32: hipLaunchKernelGGL((k_spmm<4, 32, SENSEI_SPMM_PATTERN, OFF32>), grid, dim3(kBlock), 0, s, a); break;
+        default: hipLaunchKernelGGL((k_spmm<4, 64, SENSEI_SPMM_PATTERN, OFF32>), grid, dim3(kBlock), 0, s, a); break;
     }
     return hipGetLastError();
 }
@@ -2273,6 +2286,19 @@ SpmmShape spmm_shape(const float *B, int64_t ldb, int f) {
     return sh;
 }
 
+// Value-less SpMM on rows of two and a half to five entries on average: a row to every lane group of k_spmm, so that the groups of a wavefront
+// read and write neighbouring rows, where the flat walk has them an eighth of a chunk apart and its 26 KB of LDS a workgroup cost a quarter
+// of the wavefronts.  Times flat / by rows, us: 4 M nodes of a grid, 4 columns 245 / 192, 20 columns 448 / 315, 64 columns 807 / 702, 128
+// columns 1,737 / 1,405; 2 M rows of three random entries, 4 / 20 / 128 columns 146 / 132, 233 / 218, 870 / 809.  Where a tile is all of the row
+// and fills its line, only if the operand exceeds the 256 MB of the last-level cache (32 columns, 4 M nodes 407 / 362; a GCN layer on 1 M nodes
+// 249 / 259).  Not where most rows are empty or nearly so (300,000 rows of 2, 4 columns 52 / 59; training on sampled blocks, 103,000 rows of
+// 0.6, 151 / 156), not from five entries on (300,000 rows of 5, 8 columns 44 / 47; of 16, 58 / 116), nor with weights, where the rows of hubs
+// cost the most (power-law pattern of 300,000 rows, 64 columns: 238 / 370, value-less 296 / 355).
+static bool spmm_by_rows(const sensei_csr &A, int mode, int f, bool b_sliced, int n_tiles) {
+    if (mode != SENSEI_SPMM_PATTERN || A.nnz >= 5 * (int64_t)A.n_rows || 2 * A.nnz < 5 * (int64_t)A.n_rows) return false;
+    return n_tiles > 1 || !(b_sliced || f == 32) || (int64_t)A.n_cols * 128 > (256LL << 20);
+}
+
 size_t spmm_carry_bytes(int64_t nnz, int f) {
     const int t = choose_chunk_nnz(nnz);
     // tiles are at most 256 floats wide, so the padded width stays below f + 256
@@ -2332,8 +2358,9 @@ hipError_t launch_spmm(const sensei_csr &A, int mode, const float *r, const floa
     hipError_t err;
     hipEvent_t t0 = timer ? timer->next() : nullptr, t1 = t0 ? timer->next() : nullptr;
     if (t1 && hipEventRecord(t0, s) != hipSuccess) return hipErrorUnknown;
-    const bool flat = sh.vec == 4;
-    if (flat && sh.lpg == 8) err = off32 ? spmm_flat_mode<8, true>(a, mode, grid, s) : spmm_flat_mode<8, false>(a, mode, grid, s);
+    const bool by_rows = sh.vec == 4 && spmm_by_rows(A, mode, f, b_sliced, sh.n_tiles), flat = sh.vec == 4 && !by_rows;
+    if (by_rows) err = off32 ? spmm_rows_pattern<true>(a, sh.lpg, grid, s) : spmm_rows_pattern<false>(a, sh.lpg, grid, s);
+    else if (flat && sh.lpg == 8) err = off32 ? spmm_flat_mode<8, true>(a, mode, grid, s) : spmm_flat_mode<8, false>(a, mode, grid, s);
     else if (flat) err = sh.lpg == 16 ? spmm_flat_mode<16, false>(a, mode, grid, s) : sh.lpg == 32 ? spmm_flat_mode<32, false>(a, mode, grid, s)
                                                                                          : spmm_flat_mode<64, false>(a, mode, grid, s);
     else switch (sh.vec) {

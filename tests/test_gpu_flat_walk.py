@@ -129,6 +129,35 @@ def test_softmax_of_masked_logits(ctx, t, least, mask):
         assert_close(np.nan_to_num(got), np.nan_to_num(want), tol=4e-6, what=what)   # as above
 
 
+# value-less SpMM on both sides of the mean rows between which it goes by rows (2.5 and 5 entries): empty rows, a row over many chunks, row-major operands of
+# every lane group and slice-major ones of several tiles (a layer that aggregates first), infinities where they belong
+@pytest.mark.parametrize("n", [2_000, 60_000, 150_000])
+@pytest.mark.parametrize("mean", [2.4, 2.6, 4.9, 5.1])
+def test_spmm_on_short_rows(ctx, n, mean):
+    rng = np.random.default_rng(n)
+    lens = np.bincount(rng.integers(0, n, int(n * mean) - 1_500), minlength=n)
+    lens[7] += 1_500
+    row_ptr = np.concatenate([[0], np.cumsum(lens)])
+    row = np.repeat(np.arange(n), lens)
+    step = n // lens[row]
+    col = (np.arange(row.size) - row_ptr[row]) * step + (rng.random(row.size) * step).astype(np.int64)
+    g = synth.CSR(n, n, row_ptr.astype(np.int32), col.astype(np.int32))
+    A = DeviceCSR(g)
+    r, c = (ctx.norm_vectors(d) for d in ctx.degrees(A.s))
+    for f in (4, 20, 32, 64, 100) if n < 100_000 else (8, 64):
+        B = synth.uniform(n, f, (n, f))
+        ref = np.zeros((n, f))
+        np.add.at(ref, row, B[g.col_idx].astype(np.float64))
+        assert_close(ctx.spmm(A.s, SPMM_PATTERN, dev(B)), ref, what=f"{f} columns")
+        W = synth.glorot(n, 10, f, 16)
+        assert_close(ctx.gcn_layer(A.s, r, c, dev(B), dev(W), 0, ACT_RELU), oracle.gcn_layer(n, n, g.row_ptr, g.col_idx, B, W, 1), what=f"layer, {f} columns")
+    B[3] = np.inf
+    hit = np.zeros(n, bool)
+    hit[row[g.col_idx == 3]] = True
+    got = ctx.spmm(A.s, SPMM_PATTERN, dev(B)).cpu().numpy()
+    assert np.isposinf(got[hit]).all() and np.isfinite(got[~hit]).all()
+
+
 # operands of 8- and 4-byte words: widths on both sides of every lane group (8, 16, 32 lanes) and of two tiles
 @pytest.mark.parametrize("t,least", [(64, 3_000), (512, 530_000)])
 def test_spmm_on_narrow_words(ctx, t, least):
