@@ -314,14 +314,21 @@ int run_gcn(const sensei_csr &A, const float *r, const float *c, const sensei_ma
         float *carry = cv.take<float>(spmm_carry_bytes(A.nnz, fs) / sizeof(float));
         float *U = cv.take<float>((size_t)A.n_rows * fs);
         // The SpMM gathers from c (x) X (DYN_AGG, Eq. 3) or from X itself; either way from a slice-major copy when the
-        // rows are gathered often enough to pay for writing it.
+        // rows are gathered often enough to pay for writing it.  DYN_AGG writes a copy anyway: a row-major one where slices are wider than
+        // the rows and either two rows or more fit a line (4 M nodes of a grid, layer of 4 / 8 / 16 -> 32 columns, slices / row-major: 612 /
+        // 416, 640 / 491, 705 / 638 us; 2 M nodes of ten entries, 568 / 424 at 4 columns) or a row is gathered fewer than five times (20
+        // columns: the grid 786 / 730; but 2 M nodes of six entries 514 / 579, rows that straddle lines).
         const float *src = X.ptr;
         int64_t ld_src = X.ld;
-        const bool sliced = id == SENSEI_GCN_DYN_AGG || relayout_pays(A);   // DYN_AGG writes its copy anyway
-        if (sliced) {
+        const bool narrow = fs < pad32(f_in) && (fs <= 16 || A.nnz < 5 * (int64_t)A.n_cols);
+        const bool sliced = (id == SENSEI_GCN_DYN_AGG && !narrow) || relayout_pays(A);
+        if (sliced || id == SENSEI_GCN_DYN_AGG) {
             float *T = cv.take<float>((size_t)A.n_cols * pad32(f_in));
-            SENSEI_TRY(launch_to_slices(id == SENSEI_GCN_DYN_AGG ? c : nullptr, X.ptr, X.ld, A.n_cols, f_in, T, s, nullptr, 0, &side));
+            const float *scale = id == SENSEI_GCN_DYN_AGG ? c : nullptr;
+            if (sliced) SENSEI_TRY(launch_to_slices(scale, X.ptr, X.ld, A.n_cols, f_in, T, s, nullptr, 0, &side));
+            else SENSEI_TRY(launch_row_broadcast(scale, X.ptr, X.ld, A.n_cols, f_in, T, fs, SENSEI_ACT_NONE, s, nullptr, 0, &side));
             src = T;
+            if (!sliced) ld_src = fs;
         }
         SENSEI_TRY(launch_side(&side, s));
         const bool scaled = (mode == SENSEI_SPMM_SCALED);

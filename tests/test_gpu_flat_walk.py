@@ -144,7 +144,7 @@ def test_spmm_on_short_rows(ctx, n, mean):
     g = synth.CSR(n, n, row_ptr.astype(np.int32), col.astype(np.int32))
     A = DeviceCSR(g)
     r, c = (ctx.norm_vectors(d) for d in ctx.degrees(A.s))
-    for f in (4, 20, 32, 64, 100) if n < 100_000 else (8, 64):
+    for f in (4, 13, 16, 20, 32, 64, 100) if n < 100_000 else (8, 64):
         B = synth.uniform(n, f, (n, f))
         ref = np.zeros((n, f))
         np.add.at(ref, row, B[g.col_idx].astype(np.float64))
