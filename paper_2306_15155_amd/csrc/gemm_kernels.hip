@@ -1511,10 +1511,17 @@ hipError_t launch_gemm(const float *A, int64_t lda, const float *W, int64_t ldw,
             return done(gemm_bf_launch<4>(g, av, s));
         }
     }
-    // Few enough 64 x 64 blocks to leave compute units idle: 32 x 32 blocks with k split over the wavefronts.  The line: at 77 blocks
-    // (4,900 x 256 x 47) 8.2 against 12.9 us and at 157 (10,000 x 64 x 32) 4.6 against 5.4, but at 250 (16,000 x 300 x 64) 16.8 against 13.5
-    // and at 308 (4,900 x 47 x 256) 7.8 against 7.0: a block reads its operands for a quarter of the output.
-    if (((n + 63) / 64) * ((m_store + 63) / 64) <= 160) {
+    // Few enough 64 x 64 blocks to leave compute units idle: 32 x 32 blocks with k split over the wavefronts.  A small block reads its operands
+    // for a quarter of the output and without LDS, so the line lies lower the more blocks there are and the longer k is.  Small / 64 x 64, us
+    // with one call's launch in them (9.8), A in 16-byte loads: 308 small blocks (4,900 x 47) k = 256 10.0 / 13.5, 2,048 60 / 78; 504 (2,000 x
+    // 256) k = 512 16.3 / 19.0, 8,192 226 / 248; 626 (10,000 x 64) k = 256 10.4 / 11.9, 384 16.6 / 15.7, 2,048 71 / 66.  A in 4-byte loads:
+    // 40 blocks of 64 (600 x 256) k = 1,024 23 / 36, 4,096 131 / 137; 77 (4,900 x 47) k = 512 17.5 / 24.2, 1,024 42 / 44, 1,536 68 / 64; 128
+    // (2,000 x 256) k = 384 16.1 / 16.6, 512 22.9 / 20.7; 157 (10,000 x 16) k = 384 15.2 / 16.0, 1,024 44 / 37; 157, but 626 small (10,000 x
+    // 64) k = 128 10.2 / 9.9, 256 14.6 / 12.6, 1,024 58 / 37.
+    const long long small_blocks = ((n + 31) / 32) * ((m_store + 31) / 32), blocks_64 = ((n + 63) / 64) * ((m_store + 63) / 64);
+    const int small_k = avec == 4 ? (small_blocks <= 512 ? INT32_MAX : 256)
+                                  : blocks_64 <= 64 ? INT32_MAX : blocks_64 <= 96 ? 1024 : small_blocks <= 512 ? 384 : 128;
+    if (blocks_64 <= 160 && k <= small_k) {
         g.n_bn = (m_store + 31) / 32;
         const dim3 grid((unsigned)(((n + 31) / 32) * g.n_bn + g.side.blocks));
         if (avec == 4) hipLaunchKernelGGL(k_gemm_small<4>, grid, dim3(kThreads), 0, s, g);

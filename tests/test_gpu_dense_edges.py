@@ -37,6 +37,20 @@ def test_small_gemm(n, k, m, pad):
     ctx.close()
 
 
+# both sides of the lines where that kernel ends: by k for each alignment and each number of blocks
+@pytest.mark.parametrize("n,k,m", [(10_240, 128, 64), (10_240, 129, 64), (10_240, 256, 64), (10_240, 260, 64), (10_240, 384, 32), (10_240, 388, 32),
+                                   (10_240, 2_052, 16), (8_192, 2_052, 32), (2_048, 512, 256), (2_049, 512, 256), (4_096, 1_030, 40), (4_097, 1_024, 40), (4_097, 1_030, 40)])
+@pytest.mark.parametrize("pad", [0, 1])
+def test_gemm_beside_the_small_kernel(n, k, m, pad):
+    from paper_2306_15155_amd import Context
+    ctx = Context(0)
+    g = torch.Generator(device="cuda").manual_seed(n + k * 31 + m)
+    a = torch.randn(n, k + pad, generator=g, device="cuda")[:, :k]
+    w = torch.randn(k, m, generator=g, device="cuda")
+    _bound_check(ctx.gemm(a, w), a, w)
+    ctx.close()
+
+
 # the weight gradient of a layer on the identity pattern is X^T dY: around the 64 columns that choose the narrow block, the 128 x 64 block's
 # edges, odd leading dimensions and row counts that leave a ragged last slab.  Slabs of 32 rows are summed in fp32 (six products a term),
 # everything after that in fp64.
