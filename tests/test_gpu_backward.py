@@ -475,6 +475,34 @@ def test_gat_backward_with_a_split_of_a_rectangular_transposed_pattern(ctx):
     Tt.close()
 
 
+@pytest.mark.parametrize("panels", [1, 3, 8])
+@pytest.mark.parametrize("shape,f_out", [("square", 130), ("square", 256), ("rect", 160), ("gap", 160)])
+def test_gat_backward_walks_the_remainder_panel_by_panel(ctx, shape, f_out, panels):
+    """The per-entry products of a split's remainder in panel-major order (and alpha^T . dP of the transposed pattern's): segments (panel, row)
+    without entries, chunks that run over the end of one panel or of several, a rectangular pattern, and one whose last third of the
+    columns holds nothing, so that whole panels are empty."""
+    from paper_2306_15155_amd import Tiles, csr_struct
+    g = synth.rmat(90, 4500, 200_000)
+    if shape != "square":   # the first 3000 destinations, all sources (gap: half as many again)
+        rp = g.row_ptr[:3001].copy()
+        g = synth.CSR(3000, g.n_cols if shape == "rect" else g.n_cols * 3 // 2, rp, g.col_idx[:rp[-1]].copy())
+    gt = synth.transpose(g)
+    X, W, dY = _inputs(g, 40, f_out, 91)
+    a_l, a_r = synth.normal(91, 20, (f_out,), 0.0, 0.3), synth.normal(91, 21, (f_out,), 0.0, 0.3)
+    want = oracle.gat_backward(g.n_rows, g.n_cols, g.row_ptr, g.col_idx, X, W, a_l, a_r, dY, slope=0.2)
+    A, At = DeviceCSR(g), DeviceCSR(gt)
+    T, Tt = (Tiles(ctx, M.s, 0.05, 256, min_width=32, remainder_panels=panels) for M in (A, At))
+    assert T.n_tiles > 0 and T.nnz_sparse > 0 and Tt.n_tiles > 0 and Tt.nnz_sparse > 0
+    Ah, Ath = (csr_struct(M.g.n_rows, M.g.n_cols, M.row_ptr, M.col_idx, tiles=S) for M, S in ((A, T), (At, Tt)))
+    pos = ctx.transpose_positions(A.s, At.s)
+    for how, first, second in (("A", Ah, At.s), ("both", Ah, Ath), ("both again", Ah, Ath)):
+        got = ctx.gat_backward(first, second, pos, dev(X), dev(W), dev(a_l), dev(a_r), dev(dY))
+        for gpu, ref, what in zip(got, want, ("dX", "dW", "da_l", "da_r")):
+            assert_close(gpu, ref, what=f"{what}, split on {how}")
+    T.close()
+    Tt.close()
+
+
 def test_transpose_positions_rejects_a_pattern_that_is_not_the_transpose(ctx):
     from paper_2306_15155_amd import SenseiError
     g = hub_and_empty_graph(74, 500, 3000, 200, 5)   # not symmetric
