@@ -10,6 +10,7 @@
 // fix-up kernel adds the carry slots to the row in chunk order.  No float
 // atomics: the summation order is fixed, results are reproducible, and a hub
 // row of a power-law graph is spread over as many wavefronts as it needs.
+#include <cfloat>
 #include <type_traits>
 
 #include "sensei_internal.h"
@@ -1345,7 +1346,7 @@ __global__ void k_to_slices(const float *__restrict__ s, const float *__restrict
 // (m, z) pairs: z = sum of exp(e - m).  Merge keeps m the larger maximum.
 __device__ __forceinline__ void mz_merge(float &m, float &z, float m2, float z2) {
     const float mm = m > m2 ? m : m2;
-    if (mm == -INFINITY) { m = mm; z += z2; return; }   // nothing but -inf so far: both sums are 0, or NaN
+    if (mm == -INFINITY) { m = mm; z = 0.f; return; }
     z = z * expf(m - mm) + z2 * expf(m2 - mm);
     m = mm;
 }
@@ -1401,16 +1402,17 @@ __global__ __launch_bounds__(kBlock) void k_softmax_stats(SoftmaxArgs a) {
     // head, whole rows and tail of this lane as in flat_sum, with (max, sum of exp) pairs: the maximum over the part of a row that
     // lies in this lane first (forwards, then handed back), then one exp per entry
     const int n_mine = c.hi - c.lo - lane * PER;   // entries of this lane inside the chunk (may be more than PER, or negative)
-    float mx[PER];
+    float mx[PER];   // never below the lowest finite value: entries of -inf (masked out) then weigh exp(-inf) = 0, also where the lane holds no others
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
         if (q >= n_mine) e[q] = -INFINITY;
-        mx[q] = (q > 0 && !((c.starts >> q) & 1u)) ? fmaxf(mx[q > 0 ? q - 1 : 0], e[q]) : e[q];
+        mx[q] = fmaxf((q > 0 && !((c.starts >> q) & 1u)) ? mx[q > 0 ? q - 1 : 0] : -FLT_MAX, e[q]);
     }
 #pragma unroll
     for (int q = PER - 2; q >= 0; --q)
         if (!((c.starts >> (q + 1)) & 1u)) mx[q] = mx[q + 1];
     auto write = [&](int i, float m, float z) {
+        if (z == 0.f) m = -INFINITY;
         if (c.cont && i == c.i_first) a.carry[chunk] = make_float2(m, z);
         else a.stats[i] = make_float2(m, z);
     };
@@ -1425,8 +1427,7 @@ __global__ __launch_bounds__(kBlock) void k_softmax_stats(SoftmaxArgs a) {
             started = true;
             rz = 0.f;
         }
-        // entries of -inf (masked out) weigh 0, also where the lane holds no others of their row
-        if (q < n_mine) rz += __expf(e[q] - (mx[q] == -INFINITY ? 0.f : mx[q]));
+        if (q < n_mine) rz += __expf(e[q] - mx[q]);
     }
     float m = mx[PER - 1], z = rz;
     int f = started;
