@@ -229,8 +229,8 @@ int sensei_chunk_nnz(int64_t nnz);
 
 /* Which matrix-core kernel sensei_gemm (and the GEMM inside the layers) takes for an n x k by k x m product: the fp32 instruction,
  * or, for large products, the bf16 instruction on three exact bf16 pieces per fp32 operand element with six piece products per
- * term (what is left out is below 2^-23 of a term: the result is as accurate as the fp32 instruction's, at several times its
- * rate).  Host arithmetic; for reports that price the kernel against the right matrix-core peak. */
+ * term (what is left out is below 2^-21 of a term, 2^-24.7 on average: over many terms the result is as accurate as the fp32
+ * instruction's, at several times its rate).  Host arithmetic; for reports that price the kernel against the right matrix-core peak. */
 enum { SENSEI_GEMM_FP32 = 0, SENSEI_GEMM_BF16_PIECES = 1 };
 int sensei_gemm_kernel(int64_t n, int k, int m);
 
@@ -327,7 +327,7 @@ int sensei_dotgat_layer(sensei_ctx *ctx, const sensei_csr *A, sensei_mat X, sens
  * evaluated as a block-sparse GEMM), the SpMM runs over the CSR remainder of the entries outside such tiles, and a last
  * pass joins the two sums and applies the row scaling and the activation.  The tiles use the bf16 matrix instruction at
  * fp32 accuracy: a mask entry is 0 or 1, and every fp32 operand element is cut exactly into three bf16 pieces (the attention
- * weights as well: six piece products per term, what is left out is below 2^-23 of a term).  Where a step uses the object's
+ * weights as well: six piece products per term, what is left out is below 2^-21 of a term).  Where a step uses the object's
  * own stream (the GAT layer's tile statistics, the backward), the fork and join are event dependencies between the two
  * streams, so the call stays asynchronous and can be captured into a graph.  These steps use the split when `tiles` is set
  * in the sensei_csr:

@@ -136,7 +136,10 @@ ChunkPlan make_plan(const sensei_csr &A, Carver &cv) {
 bool gcn_is_agg(int id) { return id == SENSEI_GCN_DYN_AGG || id == SENSEI_GCN_DYNF_AGG || id == SENSEI_GCN_PRE_AGG; }
 
 // A slice-major copy of a user matrix the SpMM gathers from costs one pass over it (8 bytes per element); it pays
-// once every row is gathered many times.
+// once every row is gathered many times.  SpMM with / without the copy, us: 2.45 M nodes of 52 entries, 32 / 128 columns 1,784 / 2,314 and 7,159 /
+// 9,129; 300,000 nodes, power law, of 131, 128 columns 1,096 / 1,426; 98,000 random of 1,021, 128 columns 4,882 / 5,212; the line is low for
+// operands that fit the caches (300,000 random of 17 / 25 / 61, 128 columns 432 / 400, 583 / 560, 1,278 / 1,302) and 12 M nodes of 3 entries
+// are far below it (1,379 / 882).
 bool relayout_pays(const sensei_csr &A) { return A.nnz >= 16 * (int64_t)A.n_cols; }  // declared above
 
 size_t gcn_ws(const sensei_csr &A, int f_in, int f_out, int id) {
@@ -688,9 +691,10 @@ int run_tagcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r
 //   tiles: statistics and aggregation split into dense tiles and remainder; panels: two passes, the logits stored in panel order;
 //   one walk: score, running-maximum softmax and weighted sum fused in the aggregation kernel (no stored logits, no statistics
 //   pass) - where the aggregation is one 32-column slice wide and rows average at least 16 entries, or two slices and 128
-//   entries (measured, 32 / 64 columns, layer time against the two-pass form: 233,000-node power-law graph -19 % / -7 %,
-//   98,000 nodes with 1,021 entries per row -26 % / -17 %, 2.45 M nodes with 52 per row -12 % / +6 %, road-shaped graph with 3
-//   per row +6 % / +13 %: each further slice repeats the score work, and short rows pay the per-row merge);
+//   entries (32 / 64 columns, layer time against the two-pass form: 233,000-node power-law graph of 494 entries per row -14 % / -1 %,
+//   98,000 nodes of 1,021 -22 % / -13 %, 300,000 random nodes of 131 -16 % / -7 %, of 17 -11 % / -5 %, power-law of 131 -11 % / +3 %, of
+//   41 -5 % / +6 %, 2.45 M nodes of 52 -3 % / +12 %: each further slice repeats the score work, which power-law graphs hide least;
+//   below 16 entries there is little left to save: 9 -6 % / -4 %, a grid of 5 -5 % / -1 %);
 //   two passes otherwise.
 enum { kAttnTwoPass = SENSEI_GAT_PATH_TWO_PASS, kAttnOneWalk = SENSEI_GAT_PATH_ONE_WALK, kAttnTiles = SENSEI_GAT_PATH_TILES,
        kAttnPanels = SENSEI_GAT_PATH_PANELS };
@@ -1144,8 +1148,9 @@ int run_dotgat_backward(const sensei_csr &A_in, const sensei_csr &At_in, const i
 
 // ---- backward of the GAT layer
 // The per-entry dot products of the attention backward can use the dense-tile split of A: same pattern, wide enough, and
-// every tile cell addressable by the (negative) codes in dst_rem.  Below 128 columns the extra pass that merges the two
-// sources costs more than the matrix cores save.
+// every tile cell addressable by the (negative) codes in dst_rem.  Narrow products leave little for the matrix cores to save over the
+// extra pass that merges the two sources: GAT backward on 115 M entries, ms with / without, 64 columns 6.60 / 6.64, 96 8.47 / 9.04, 128 8.85 / 9.82,
+// 192 11.97 / 13.92.
 constexpr int kDalphaTilesMinWidth = 128;
 bool tiles_serve_dalpha(const sensei_csr &A, int f_out) {
     const sensei_tiles *D = A.tiles;
@@ -1871,9 +1876,9 @@ struct TilesLayout {
 // Column panels of the remainder's panel-major copy, from the features known before the split: two where a 128-byte slice of the
 // gathered matrix exceeds the L2s several times over (12 MB) and rows are long enough that a part of a row is still a run of
 // gathers, three from 24 MB on; none otherwise.  Measured on the 233,000-node power-law graph (slice 29.8 MB, 494 entries per
-// row, 41.8 M of 115 M entries in the remainder), whole three-layer step with 2 / 3 / 4 panels: 10.00 / 9.90 / 10.59 ms - the L2
-// hit rate of the remainder keeps rising with the panel count (44 % -> 82 % at eight), but every (panel, row) segment costs a
-// row end in the kernel and a partial row written and read back.
+// row, 41.8 M of 115 M entries in the remainder) with 1 / 2 / 3 / 4 / 6 / 8 panels, ms: GCN layer 602 -> 256 4.52 / 3.60 / 3.40 / 3.42 / 3.64 /
+// 3.93, GAT layer over 602 columns 13.1 / 10.9 / 10.5 / 10.6 / 11.1 / 11.9, GAT backward 15.1 / 13.8 / 13.5 / 13.5 / 13.8 / 14.0 - the L2 hit
+// rate of the remainder keeps rising with the panel count, but every (panel, row) segment costs a partial row written and read back.
 int g_remainder_panels_override = 0;  // sensei_tiles_remainder_panels: 0 = the rule below
 int remainder_panels_for(const sensei_csr &A) {
     if (g_remainder_panels_override > 0) return (int64_t)A.n_rows * g_remainder_panels_override < (1LL << 30) ? g_remainder_panels_override : 1;

@@ -263,8 +263,9 @@ __global__ __launch_bounds__(kThreads) void k_gemm_small(GemmArgs g) {
 // ---- the same GEMM on the bf16 matrix cores, which run 16 times the fp32 rate, at fp32 accuracy.  Every fp32 operand element
 // is cut into three bf16 pieces of eight significand bits (truncate, subtract, truncate, subtract: the pieces add up to the
 // element exactly); of the nine piece products of a term the six of weight 2^-16 and above are formed (a1 b1, a1 b2, a2 b1, a1 b3,
-// a2 b2, a3 b1), each exact, and accumulated in fp32 by the matrix core: what is left out is below 2^-23 of the term, the
-// rounding of the fp32 instruction.
+// a2 b2, a3 b1), each exact, and accumulated in fp32 by the matrix core.  What is left out (a2 b3, a3 b2, a3 b3) has the sign of the term:
+// below 2^-21 of it, 2^-24.7 on average over random significands, above 2^-23 for one term in twenty.  In a sum of many terms that is below
+// the rounding of the accumulation; a sum that one term dominates can be 6.6 units of 2^-24 off instead of 1.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
@@ -602,8 +603,8 @@ __global__ __launch_bounds__(kThreads) void k_dense_tiles_bf(DenseTilesBfArgs g)
 
 // The attention modes on the bf16 matrix cores.  Entry (i, k) of a tile weighs w = exp(LeakyReLU(u[i] + v[k]) - shift), an fp32
 // number, which is cut into three bf16 pieces like the right-hand operand; of the nine piece products the six of weight
-// 2^-16 and above are formed (w1 b1, w1 b2, w2 b1, w1 b3, w2 b2, w3 b1: what is left out is below 2^-23 of a term, the rounding
-// of the fp32 instruction).  kTilesAttn: u = s_l, v = s_r, shift = the maximum of row i (tiles of the pattern itself).
+// 2^-16 and above are formed (w1 b1, w1 b2, w2 b1, w1 b3, w2 b2, w3 b1: what is left out is below 2^-21 of a term, 2^-24.7 on
+// average).  kTilesAttn: u = s_l, v = s_r, shift = the maximum of row i (tiles of the pattern itself).
 // kTilesAttnT: the tiles are those of the transposed pattern, so the softmax row is the tile's column: u = s_r, v = s_l,
 // shift = the maximum of column k.
 // The weights of one step (128 rows x 16 k) are computed once per workgroup, every thread a few of them, and shared through

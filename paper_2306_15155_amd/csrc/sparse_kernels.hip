@@ -1764,7 +1764,7 @@ __global__ __launch_bounds__(kBlock) void k_sum_fixup(NnzArgs a, float *__restri
                });
 }
 
-// out[i] = sum of val over the stored entries of row i.  2.1 M values at stride 2, 100,000 rows: 173 -> 10 us.
+// out[i] = sum of val over the stored entries of row i.  2.1 M values at stride 2, 100,000 rows: 173 -> 7 us.
 template <int PER>
 __global__ __launch_bounds__(kBlock) void k_row_sum(NnzArgs a, const float *__restrict__ val, int stride, float *__restrict__ out,
                                                      float *__restrict__ carry) {
@@ -2234,10 +2234,10 @@ NnzArgs nnz_args(const sensei_csr &A, const ChunkPlan &p) {
 
 // ----------------------------------------------------------------- host side
 
-// Non-zeros per chunk (= per wavefront).  Large graphs: 512 - with 2048 the same kernels left the GPU short of
-// wavefronts: the attention statistics pass took 0.92 ms instead of 0.59 on 115 M non-zeros, an SpMM 64 columns wide
-// 1.46 ms instead of 1.34, one 256 wide 4.70 against 4.72 (1024: 4.66; 256: 4.92), the whole three-layer step 13.9 ms
-// instead of 13.3 (sweep of 128 .. 2048); only SpMMs 512 or more columns wide lose 1-2 %.
+// Non-zeros per chunk (= per wavefront): 64 times the entries a lane of the flat walks owns, at most eight (more would not fit its registers
+// and LDS).  Large graphs: 512.  With 512 / 256 / 128 on 115 M non-zeros, ms: GCN layer 602 -> 256 on the tile split 3.40 / 3.47 / 3.86, unsplit
+// 6.32 / 6.56 / 7.59, 256 -> 41 0.90 / 0.92 / 1.07, GAT backward 13.5 / 13.9 / 14.9; 62 M non-zeros, GAT layer 4.65 / 4.72 / 4.95; on 2 to 4 M
+// non-zeros the three are within 3 %.
 int choose_chunk_nnz(int64_t nnz) {
     if (nnz >= (1LL << 19)) return 512;
     if (nnz >= (1LL << 18)) return 256;
@@ -2345,8 +2345,9 @@ hipError_t launch_spmm(const sensei_csr &A, int mode, const float *r, const floa
     }
     const unsigned groups = blocks_for(p.n_chunks, kWavesPerBlock);
     // Feature tiles worked on at the same time (consecutive XCDs take consecutive tiles of the live set): all eight
-    // while a 128-byte slice of the gathered matrix is small, four beyond that (measured on the 233 k-node R-MAT graph
-    // at F = 256: 6.5 / 6.1 / 5.9 / 6.0 ms with 1 / 2 / 4 / 8 live tiles; 2.45 M nodes at F = 1024: 52.2 / 51.5 / 50.7 / 51.6).
+    // while a 128-byte slice of the gathered matrix is small, four beyond that (233 k-node R-MAT graph at F = 256, ms with 1 / 2 / 4 / 8 live
+    // tiles: 6.13 / 5.91 / 5.85 / 6.04; GAT layer that aggregates 602 columns of it over a panel-major remainder, 2 / 4 / 8: 10.8 / 10.5 / 11.6;
+    // 2.45 M nodes at F = 512: 27.9 / 27.9 / 27.4 / 27.6; 98 k nodes of 1,021 random entries at F = 512: 19.5 / 19.0 / 19.0 / 18.9).
     const double slice_bytes = (double)(A.n_cols > 0 ? A.n_cols : 1) * sh.lpg * sh.vec * 4.0;
     a.tiles_live = slice_bytes > 8e6 ? 4 : 8;
     if (a.tiles_live > sh.n_tiles) a.tiles_live = sh.n_tiles;
