@@ -20,6 +20,7 @@ struct GemmArgs {
     float *Y;
     long long lda, ldw, ldy, n;
     int k, m, m_store, act, n_bn;
+    int n_parts, by_xcd, a_lds;   // k_gemm_bf: shares of the rows; whether the blocks of columns of a share run on one XCD; where in LDS the rows of A are
     int y_sliced;  // Y stored slice-major in tiles of 32 columns: (row, col) at Y[(col / 32) * n * 32 + row * 32 + col % 32]
     long long a_slice;   // floats from columns 32 s .. 32 s + 31 of A to the next 32: 32 for a row-major A, n * 32 (with lda = 32) for a slice-major one
     const float *add;    // optional n x pad32(m) slice-major matrix added to the product before scaling and activation
@@ -261,13 +262,28 @@ __global__ __launch_bounds__(kThreads) void k_gemm_small(GemmArgs g) {
 }
 
 // ---- the same GEMM on the bf16 matrix cores, which run 16 times the fp32 rate, at fp32 accuracy.  Every fp32 operand element
-// is cut into three bf16 pieces of eight significand bits (truncate, subtract, truncate, subtract: the pieces add up to the
-// element exactly); of the nine piece products of a term the six of weight 2^-16 and above are formed (a1 b1, a1 b2, a2 b1, a1 b3,
-// a2 b2, a3 b1), each exact, and accumulated in fp32 by the matrix core.  What is left out (a2 b3, a3 b2, a3 b3) has the sign of the term:
-// below 2^-21 of it, 2^-24.7 on average over random significands, above 2^-23 for one term in twenty.  In a sum of many terms that is below
-// the rounding of the accumulation; a sum that one term dominates can be 6.6 units of 2^-24 off instead of 1.
+// is cut into three bf16 pieces (round to nearest, subtract, round, subtract: both subtractions are exact and the pieces add up to the
+// element exactly); of the nine piece products of a term the six largest are formed (a1 b1, a1 b2, a2 b1, a1 b3, a2 b2, a3 b1), each exact,
+// and accumulated in fp32 by the matrix core.  A rounded piece is at most 2^-9 of what it was cut from, so what is left out (a2 b3, a3 b2,
+// a3 b3) is below 2^-26 of the term, either sign: less than the rounding of the product itself.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));   // 16-byte load at any word: the vector memory unit needs no more alignment
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+
+// Two elements -> their three pieces, packed as pairs (first in the low half).  The largest finite values round up to infinity, so the first
+// piece is cut from the value clamped to the largest finite bf16; what is left over still fits the other two.  The second is clamped for the sake
+// of infinities, which then end up in the third piece alone (inf - inf nowhere): a product with one is infinite or NaN as in fp32.
+__device__ __forceinline__ void cut_pair(float x, float y, unsigned &hi, unsigned &mid, unsigned &lo) {
+    constexpr float kMaxBf = 3.3895313892515355e38f;
+    auto pack = [](float a, float b) { const floatx2 v = {a, b}; return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2)); };
+    hi = pack(__builtin_amdgcn_fmed3f(x, -kMaxBf, kMaxBf), __builtin_amdgcn_fmed3f(y, -kMaxBf, kMaxBf));
+    x -= __uint_as_float(hi << 16);
+    y -= __uint_as_float(hi & 0xFFFF0000u);
+    mid = pack(__builtin_amdgcn_fmed3f(x, -kMaxBf, kMaxBf), __builtin_amdgcn_fmed3f(y, -kMaxBf, kMaxBf));
+    lo = pack(x - __uint_as_float(mid << 16), y - __uint_as_float(mid & 0xFFFF0000u));
+}
 
 __device__ __forceinline__ void split_bf16x3(float v, unsigned &hi, unsigned &mid, unsigned &lo) {
     hi = __float_as_uint(v) & 0xFFFF0000u;
@@ -278,185 +294,302 @@ __device__ __forceinline__ void split_bf16x3(float v, unsigned &hi, unsigned &mi
 // two fp32 bit patterns whose low halves do not matter -> their high halves as a pair of bf16 (first in the low half)
 __device__ __forceinline__ unsigned pack_bf16(unsigned first, unsigned second) { return __builtin_amdgcn_perm(second, first, 0x07060302u); }
 
-// Block tile 256 x 32 TN: four wavefronts stacked over the rows, each 64 rows x 32 TN columns (2 x TN accumulators).  The
-// 256 x 16 block of A of a step goes through LDS as fp32 (fetched with neighbouring lanes on one row, so that a row's 64 bytes
-// are one request); a lane of the 32 x 32 x 16 instruction holds eight consecutive k of one row, reads them back as two 16-byte
-// words and cuts them into pieces in registers.  The 16 x 32 TN block of W of a step is cut once per workgroup (a thread:
-// eight k of one column) and left in LDS in lane order.  Two buffers each, filled for step s + 1 while step s multiplies: one
-// barrier per step.  Rows past the end are computed from the last row and dropped.
-template <int TN, int AVEC>
-__global__ __launch_bounds__(kThreads, 2) void k_gemm_bf(GemmArgs g) {
-    if ((int)blockIdx.x < g.side.blocks) return side_block(g.side, (int)blockIdx.x);
-    const unsigned block = blockIdx.x - g.side.blocks;
-    constexpr int BM = 256, BN = 32 * TN;
-    constexpr int A_TPR = 16 / AVEC, A_RPP = kThreads / A_TPR, A_PASSES = BM / A_RPP;   // threads per row, rows per pass
-    constexpr int ALD = 20;   // floats per row of A in LDS: 16 k and 16 bytes of padding (conflict-free 16-byte reads of 16 rows)
-    __shared__ __attribute__((aligned(16))) float As[2][BM][ALD];
-    __shared__ __attribute__((aligned(16))) unsigned short Bs[2][3][TN][2][32][8];
-    const int t = threadIdx.x, wave = t >> 6, lane = t & 63, kh = lane >> 5, ll = lane & 31;
-    const long long m0 = (long long)(block / g.n_bn) * BM;
-    const int n0 = (int)(block % g.n_bn) * BN;
+// A wavefront owns 32 rows x 32 TN columns (TN accumulators of the 32 x 32 x 16 instruction) and brings its own rows of A: groups of 32 rows x
+// 32 k, eight lanes to a row's 128 bytes, DEPTH groups ahead of the multiply (four: all of a row up to 128 k, so that a tile costs one memory
+// round trip and the next tile's is under way); a group changes places through 4 KB of LDS that no other wavefront touches (16-byte pieces,
+// exchanged within a row by the row's number so that neither side meets bank conflicts) into the order the instruction reads, lane (row, k
+// half) eight consecutive k, and is cut there.  A is thus read once and cut once per block of columns, and never waits for a barrier.  W is cut
+// once per workgroup (512 threads) and left in LDS in lane order, every fragment one contiguous kilobyte:
+//   CHUNKED = false: all of W's k fits beside the rows of A in 160 KB; it is cut once, after which the wavefronts walk their rows
+//     independently of each other;
+//   CHUNKED = true: chunks of gemm_kc k in two buffers, the next chunk fetched and cut while this one is multiplied, one barrier per chunk.
+// The grid is what the chip holds at a time; every workgroup takes an equal share of the 32-row tiles, and the blocks of columns of one
+// share run on one XCD, so that A comes from its L2 for all but the first of them.
+// Rows past the end read the last row and are not stored; k past the end are cleared in both operands.
+// Up to about 128 k and 128 columns it is bound by memory (1 M rows, 64 -> 32 columns 82 us, 4.7 TB/s); beyond, by the matrix pipe and the vector
+// instructions of the cuts, which hardly overlap on a SIMD, at a clock that the matrix load brings down to about 1.9 GHz.  Before (a block of 256
+// rows a workgroup, A through LDS uncut behind a barrier per 16 k) / now, us: 100,000 x 64 x 256 50 / 33, 233,000 x 41 x 256 89 / 63, 233,000 x 602
+// x 64 204 / 169, 2.45 M x 100 x 512 2,660 / 2,150, 12 M x 32 x 128 1,800 / 1,600, 150,000 x 333 x 160 180 / 153, 233,000 x 602 x 256 493 / 467, 2.45 M
+// x 512 x 512 7,560 / 7,640; and against the fp32 kernel 30,000 x 602 x 256 97 / 63, 50,000 x 128 x 128 30 / 23.
+constexpr int kGemmThreads = 512, kGemmWaves = kGemmThreads / 64, kGemmCusPerXcd = 32;
+constexpr size_t kGemmLds = 160 * 1024;
+constexpr int gemm_kc(int tn) { return tn <= 2 ? 128 : 64; }     // k per chunk: 24 to 48 KB of pieces a buffer
+constexpr int gemm_depth(int tn) { return tn == 1 ? 1 : 4; }
+constexpr int gemm_held(int tn) { return tn == 1 ? 2 : 1; }      // workgroups a compute unit holds at a time, by registers
+constexpr int gemm_a_bufs(int tn) { return tn == 1 ? 1 : 2; }
 
-    floatx16 acc[2][TN];
+template <int TN, bool CHUNKED>
+__global__ __launch_bounds__(kGemmThreads, 2 * gemm_held(TN)) void k_gemm_bf(GemmArgs g) {
+    if ((int)blockIdx.x < g.side.blocks) {
+        if (threadIdx.x < kSideThreads) side_block(g.side, (int)blockIdx.x);
+        return;
+    }
+    constexpr int BN = 32 * TN, KC = gemm_kc(TN), DEPTH = CHUNKED && TN > 1 ? KC / 32 : gemm_depth(TN), ABUF = gemm_a_bufs(TN);
+    constexpr int STEP_BYTES = 3 * TN * 1024;                                    // pieces of 16 k x BN columns
+    constexpr int WI = (KC / 16 * 2 * BN + kGemmThreads - 1) / kGemmThreads;     // (column, k half, step) items a thread cuts per chunk
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const unsigned block = blockIdx.x - g.side.blocks;
+    const int bn = g.by_xcd ? (int)(block >> 3) % g.n_bn : (int)block % g.n_bn;
+    const int part = g.by_xcd ? (int)((block >> 3) / g.n_bn) * 8 + (int)(block & 7) : (int)block / g.n_bn;
+    const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63, kh = lane >> 5, ll = lane & 31;
+    const int n0 = bn * BN;
+    const long long tiles = (g.n + 31) / 32;
+    const long long t0 = tiles * part / g.n_parts, t1 = tiles * (part + 1) / g.n_parts;
+    if (t0 >= t1) return;
+    const int groups = (g.k + 31) / 32, steps = 2 * groups;
+
+    // W: element e of item (column, k half, step) is row 16 step + 8 half + e
+    auto item_of = [&](int item, int &c, int &row0, unsigned &at) {
+        c = item % BN;
+        const int rest = item / BN;
+        row0 = rest * 8;
+        at = (unsigned)((rest >> 1) * STEP_BYTES + (c >> 5) * 1024 + (rest & 1) * 512 + (c & 31) * 16);
+    };
+    auto fetch_w = [&](int k0, int c, int row0, float (&w)[8]) {
+        const unsigned col_off = (unsigned)((n0 + c < g.m ? n0 + c : g.m - 1) * 4);
+        const unsigned off = (unsigned)(row0 * (unsigned)g.ldw * 4u) + col_off;
+        const bool col_ok = n0 + c < g.m;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int e = 0; e < 8; ++e) {   // uniform base, lane offset; rows past k read a row that exists and are cleared (masks, not branches)
+            const int kb = k0 + e < g.k ? k0 + e : g.k - 1;
+            const bool ok = k0 + row0 + e < g.k;
+            const char *base = reinterpret_cast<const char *>(g.W + (long long)kb * g.ldw);
+            const float v = *reinterpret_cast<const float *>(base + (ok ? off : col_off));
+            w[e] = __uint_as_float(__float_as_uint(v) & (ok && col_ok ? ~0u : 0u));
+        }
+    };
+    auto stash_w = [&](unsigned char *dst, const float (&w)[8]) {
+        uintx4 p[3];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            unsigned a, b, c;
+            cut_pair(w[2 * d], w[2 * d + 1], a, b, c);
+            p[0][d] = a; p[1][d] = b; p[2][d] = c;
+        }
+#pragma unroll
+        for (int q = 0; q < 3; ++q) *reinterpret_cast<uintx4 *>(dst + q * TN * 1024) = p[q];
+    };
+
+    // A: 32 k from k0 on of the rows of a tile; this lane takes piece lane % 8 (four k) of rows lane / 8 + 8 i.  A piece that would run past
+    // the row's last element is read from four before it and put in order before it is stashed.  Slice-major rows are padded to whole groups
+    // in memory: nothing to clamp.
+    const int k_last = (g.a_slice != 32 ? (g.k + 31) / 32 * 32 : g.k) - 4;
+    const int piece = lane & 7, prow = lane >> 3;
+    unsigned char *const a_lds = lds + g.a_lds + wave * (4096 * ABUF);
+    float raw[DEPTH][4][4];
+    auto fetch_a = [&](long long tile, int k0, float (&v)[4][4]) {
+        const long long m0 = tile * 32;
+        const float *base = g.A + m0 * g.lda + (long long)(k0 >> 5) * g.a_slice - 4;   // uniform; lanes add 1 or more
+        const int rows = g.n - m0 < 32 ? (int)(g.n - m0) : 32;
+        const int lim = k_last - k0, o = (piece * 4 < lim ? piece * 4 : lim) + 4;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int row = i * 8 + prow, rc = row < rows ? row : rows - 1;
+            const floatx4u x = *reinterpret_cast<const floatx4u *>(reinterpret_cast<const char *>(base) + (__umul24((unsigned)rc, (unsigned)g.lda) + (unsigned)o) * 4u);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[i][e] = x[e];
+        }
+    };
+    auto stash_a = [&](int k0, float (&v)[4][4], int buf) {
+        if (k0 + 32 > g.k) {   // the last group of a row: clamped pieces shifted into place, elements past k cleared
+            const int lim = k_last - k0, d = piece * 4 > lim ? piece * 4 - lim : 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float w[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = (d & 1) ? v[i][e + 1 < 4 ? e + 1 : 3] : v[i][e];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[i][e] = (d & 2) ? w[e + 2 < 4 ? e + 2 : 3] : w[e];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[i][e] = k0 + piece * 4 + e < g.k ? v[i][e] : 0.f;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            *reinterpret_cast<float4 *>(a_lds + buf * 4096 + (i * 8 + prow) * 128 + (piece ^ prow) * 16) = make_float4(v[i][0], v[i][1], v[i][2], v[i][3]);
+    };
+    auto wave_lds = [&]() {   // LDS is in order within a wavefront; the compiler has to be told
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+
+    floatx16 acc[TN];
+    auto clear = [&]() {
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    const int a_row = t / A_TPR, a_kk = (t % A_TPR) * AVEC;
-    float ra[A_PASSES][AVEC];
-    // Addresses: a uniform base that moves with k, plus a 32-bit byte offset per lane and pass that never changes (the row within
-    // the block, clamped to the last row of A, and the lane's k): nothing per step is left for the vector ALU.
-    const float *a_blk = g.A + m0 * g.lda;
-    unsigned a_off[A_PASSES];
-#pragma unroll
-    for (int p = 0; p < A_PASSES; ++p) {
-        long long row = m0 + p * A_RPP + a_row;
-        if (row > g.n - 1) row = g.n - 1;
-        a_off[p] = (unsigned)(((row - m0) * g.lda + a_kk) * 4);
-    }
-    // a step whose 16 k all exist: vector fetches; the last step of a k that is no multiple of 16 (and the idle fetch past the
-    // last step): element by element from a clamped k, zeros past k
-    auto fetch_a = [&](int k0, auto whole) {
-        const char *src = reinterpret_cast<const char *>(a_blk + (long long)(k0 >> 5) * g.a_slice + (k0 & 31));
-#pragma unroll
-        for (int p = 0; p < A_PASSES; ++p) {
-            if constexpr (decltype(whole)::value) {
-                if (AVEC == 4) { const float4 v = *reinterpret_cast<const float4 *>(src + a_off[p]); ra[p][0] = v.x; ra[p][1 % AVEC] = v.y; ra[p][2 % AVEC] = v.z; ra[p][3 % AVEC] = v.w; }
-                else if (AVEC == 2) { const float2 v = *reinterpret_cast<const float2 *>(src + a_off[p]); ra[p][0] = v.x; ra[p][1 % AVEC] = v.y; }
-                else ra[p][0] = *reinterpret_cast<const float *>(src + a_off[p]);
-            } else {
-                const float *base = reinterpret_cast<const float *>(reinterpret_cast<const char *>(a_blk) + a_off[p]) - a_kk;   // the row's first element
-#pragma unroll
-                for (int e = 0; e < AVEC; ++e) {
-                    const int k = k0 + a_kk + e, kc = k < g.k ? k : g.k - 1;
-                    const float v = base[(long long)(kc >> 5) * g.a_slice + (kc & 31)];
-                    ra[p][e] = __uint_as_float(__float_as_uint(v) & (k < g.k ? ~0u : 0u));   // a mask, not a branch around the fetch
-                }
-            }
-        }
+            for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
     };
-    auto stash_a = [&](int buf) {
-#pragma unroll
-        for (int p = 0; p < A_PASSES; ++p) {
-            float *dst = &As[buf][p * A_RPP + a_row][a_kk];
-            if (AVEC == 4) *reinterpret_cast<float4 *>(dst) = make_float4(ra[p][0], ra[p][1 % AVEC], ra[p][2 % AVEC], ra[p][3 % AVEC]);
-            else if (AVEC == 2) *reinterpret_cast<float2 *>(dst) = make_float2(ra[p][0], ra[p][1 % AVEC]);
-            else *dst = ra[p][0];
-        }
-    };
-    const bool w_on = t < 2 * BN;
-    const int wcol = t % BN, wkh = (t / BN) & 1;
-    const bool wcol_ok = n0 + wcol < g.m;
-    const unsigned wmask = wcol_ok ? ~0u : 0u;   // columns past m read the last column and are cleared: a mask, not a branch around the fetch
-    const unsigned w_off = (unsigned)(((long long)wkh * 8 * g.ldw + (wcol_ok ? n0 + wcol : g.m - 1)) * 4);
-    float w_raw[8];
-    auto fetch_w = [&](int k0, auto whole) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            if constexpr (decltype(whole)::value) {
-                const char *row = reinterpret_cast<const char *>(g.W + (long long)(k0 + e) * g.ldw);   // uniform
-                w_raw[e] = __uint_as_float(__float_as_uint(*reinterpret_cast<const float *>(row + w_off)) & wmask);
-            } else {   // rows past k read the last row: their factors in A are zero
-                const int k = k0 + wkh * 8 + e;
-                const char *row = reinterpret_cast<const char *>(g.W + (long long)(k < g.k ? k : g.k - 1) * g.ldw - (long long)wkh * 8 * g.ldw);
-                w_raw[e] = __uint_as_float(__float_as_uint(*reinterpret_cast<const float *>(row + w_off)) & wmask);
-            }
-        }
-    };
-    auto stash_w = [&](int buf) {
-        unsigned pc[8][3];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) split_bf16x3(w_raw[e], pc[e][0], pc[e][1], pc[e][2]);
-        if (w_on) {
-#pragma unroll
-            for (int p = 0; p < 3; ++p) {
-                uintx4 w;
-#pragma unroll
-                for (int d = 0; d < 4; ++d) w[d] = pack_bf16(pc[2 * d][p], pc[2 * d + 1][p]);
-                *reinterpret_cast<uintx4 *>(&Bs[buf][p][wcol >> 5][wkh][wcol & 31][0]) = w;
-            }
-        }
-    };
-
-    // one step: fetch what step st + 1 needs, multiply step st out of the buffers st & 1, then fill the other buffers
-    auto step = [&](int st, auto next_whole) {
-        const int k1 = (st + 1) * 16;
-        fetch_a(k1, next_whole);   // past the last step: zeros, not used
-        fetch_w(k1, next_whole);
-        __builtin_amdgcn_sched_barrier(0);   // the fetches stay here and their use stays below the multiply: the scheduler would join them
-        __syncthreads();   // this step's blocks are in As[st & 1], Bs[st & 1]; nobody reads the other buffers any more
+    auto multiply = [&](int buf, const unsigned char *w) {   // the group in `buf` (two steps), fragments of W at w
         uintx4 af[2][3];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const float *src = &As[st & 1][wave * 64 + i * 32 + ll][kh * 8];
-            const float4 lo4 = *reinterpret_cast<const float4 *>(src), hi4 = *reinterpret_cast<const float4 *>(src + 4);
-            const float av[8] = {lo4.x, lo4.y, lo4.z, lo4.w, hi4.x, hi4.y, hi4.z, hi4.w};
-            unsigned pc[8][3];
+        for (int step = 0; step < 2; ++step)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) split_bf16x3(av[e], pc[e][0], pc[e][1], pc[e][2]);
+            for (int q = 0; q < 2; ++q) {
+                const float4 v = *reinterpret_cast<const float4 *>(a_lds + buf * 4096 + ll * 128 + (((step * 4 + kh * 2 + q) ^ (ll & 7)) * 16));
+                unsigned x, y, z;
+                cut_pair(v.x, v.y, x, y, z);
+                af[step][0][2 * q] = x; af[step][1][2 * q] = y; af[step][2][2 * q] = z;
+                cut_pair(v.z, v.w, x, y, z);
+                af[step][0][2 * q + 1] = x; af[step][1][2 * q + 1] = y; af[step][2][2 * q + 1] = z;
+            }
+        constexpr int J = TN % 2 == 0 ? 2 : 1;   // accumulators in turn, so that consecutive instructions do not wait for each other
 #pragma unroll
-            for (int p = 0; p < 3; ++p)
+        for (int step = 0; step < 2; ++step)
 #pragma unroll
-                for (int d = 0; d < 4; ++d) af[i][p][d] = pack_bf16(pc[2 * d][p], pc[2 * d + 1][p]);
-        }
+            for (int j = 0; j < TN; j += J) {
+                uintx4 bf[J][3];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            uintx4 bf[3];
+                for (int i = 0; i < J; ++i)
 #pragma unroll
-            for (int p = 0; p < 3; ++p) bf[p] = *reinterpret_cast<const uintx4 *>(&Bs[st & 1][p][j][kh][ll][0]);
+                    for (int p = 0; p < 3; ++p) bf[i][p] = *reinterpret_cast<const uintx4 *>(w + step * STEP_BYTES + (p * TN + j + i) * 1024 + lane * 16);
 #pragma unroll
-            for (int pa = 2; pa >= 0; --pa)
+                for (int pa = 2; pa >= 0; --pa)
 #pragma unroll
-                for (int pb = 2 - pa; pb >= 0; --pb)   // smallest products first
+                    for (int pb = 2 - pa; pb >= 0; --pb)   // smallest products first
 #pragma unroll
-                    for (int i = 0; i < 2; ++i)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[i][pa]), __builtin_bit_cast(bf16x8, bf[pb]),
-                                                                             acc[i][j], 0, 0, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        stash_a((st + 1) & 1);
-        stash_w((st + 1) & 1);
+                        for (int i = 0; i < J; ++i)
+                            acc[j + i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[step][pa]), __builtin_bit_cast(bf16x8, bf[i][pb]),
+                                                                                 acc[j + i], 0, 0, 0);
+            }
     };
-    const int n_full = g.k / 16, n_steps = (g.k + 15) / 16;
-    if (n_full > 0) { fetch_a(0, std::true_type()); fetch_w(0, std::true_type()); }
-    else { fetch_a(0, std::false_type()); fetch_w(0, std::false_type()); }
-    stash_a(0);
-    stash_w(0);
-    int st = 0;
-    for (; st + 1 < n_full; ++st) step(st, std::true_type());
-    for (; st < n_steps; ++st) step(st, std::false_type());
-
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int col = n0 + j * 32 + ll;
-            if (col >= g.m_store) continue;
-            const long long y_col = g.y_sliced ? (long long)(col >> 5) * g.n * 32 + (col & 31) : (long long)col;
-            const long long y_ld = g.y_sliced ? 32 : g.ldy;
+    // register r of lane l holds row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32; in a tile whose rows all exist the loads of `add` and
+    // `row_scale` are not behind branches and are in flight together
+    auto store_rows = [&](long long tile, auto whole) {
+        constexpr bool kWhole = decltype(whole)::value;
+        const long long row0 = tile * 32 + 4 * kh;
+        {
+            float sc[16];
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const long long row = m0 + wave * 64 + i * 32 + 8 * (r / 4) + 4 * kh + (r % 4);
-                if (row < g.n) {
-                    float y = acc[i][j][r];
-                    if (g.add) y += g.add[(long long)(col >> 5) * g.n * 32 + row * 32 + (col & 31)];
-                    if (g.row_scale) y *= g.row_scale[row];
-                    if (g.act == SENSEI_ACT_RELU) y = y > 0.f ? y : 0.f;
-                    g.Y[row * y_ld + y_col] = y;
+                const long long row = row0 + 8 * (r / 4) + (r % 4);
+                sc[r] = g.row_scale ? g.row_scale[kWhole || row < g.n ? row : g.n - 1] : 1.f;
+            }
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int col = n0 + j * 32 + ll;
+                if (col >= g.m_store) continue;
+                const long long y_col = g.y_sliced ? (long long)(col >> 5) * g.n * 32 + (col & 31) : (long long)col;
+                const long long y_ld = g.y_sliced ? 32 : g.ldy;
+                float y[16];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) y[r] = acc[j][r];
+                if (g.add) {
+                    const float *add = g.add + (long long)(col >> 5) * g.n * 32 + (col & 31);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const long long row = row0 + 8 * (r / 4) + (r % 4);
+                        y[r] += add[(kWhole || row < g.n ? row : g.n - 1) * 32];
+                    }
+                }
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const long long row = row0 + 8 * (r / 4) + (r % 4);
+                    float v = y[r] * sc[r];
+                    if (g.act == SENSEI_ACT_RELU) v = v > 0.f ? v : 0.f;
+                    if (kWhole || row < g.n) g.Y[row * y_ld + y_col] = v;
                 }
             }
         }
+    };
+    auto store = [&](long long tile) {
+        if ((tile + 1) * 32 <= g.n) store_rows(tile, std::true_type());
+        else store_rows(tile, std::false_type());
+    };
+
+    // DEPTH groups of this wavefront's tile from group g0 on, out of the fragments at w; every group's registers are refilled with the group
+    // DEPTH later (of the next tile where the row ends)
+    long long tile = t0 + wave;
+    auto run = [&](int g0, const unsigned char *w) {
+        const bool ends = g0 + DEPTH >= groups;
+        const long long tile_n = ends ? (tile + kGemmWaves < t1 ? tile + kGemmWaves : tile) : tile;
+        const int next0 = ends ? 0 : g0 + DEPTH;
+#pragma unroll
+        for (int i = 0; i < DEPTH; ++i) {
+            if (ABUF == 1) wave_lds();
+            if (g0 + i < groups) stash_a((g0 + i) * 32, raw[i], i % ABUF);
+            if (next0 + i < groups) fetch_a(tile_n, (next0 + i) * 32, raw[i]);
+            __builtin_amdgcn_sched_barrier(0);   // the fetches stay here: the scheduler would sink them to their use
+            wave_lds();
+            if (g0 + i < groups) {
+                multiply(i % ABUF, w + i * 2 * STEP_BYTES);
+            }
+        }
+        if (ends) {
+            store(tile);
+            clear();
+            tile += kGemmWaves;
+        }
+    };
+    {
+        const long long first = tile < t1 ? tile : t1 - 1;
+#pragma unroll
+        for (int i = 0; i < DEPTH; ++i)
+            if (i < groups) fetch_a(first, i * 32, raw[i]);
+    }
+    clear();
+    if constexpr (!CHUNKED) {
+        for (int item = t; item < steps * 2 * BN; item += kGemmThreads) {
+            int c, row0;
+            unsigned at;
+            float w[8];
+            item_of(item, c, row0, at);
+            fetch_w(0, c, row0, w);
+            stash_w(lds + at, w);
+        }
+        __syncthreads();
+        while (tile < t1)
+            for (int g0 = 0; g0 < groups; g0 += DEPTH) run(g0, lds + g0 * 2 * STEP_BYTES);
+    } else {
+        const int chunks = (g.k + KC - 1) / KC, rounds = (int)((t1 - t0 + kGemmWaves - 1) / kGemmWaves);
+        float w[WI][8];
+        int wc[WI], wrow[WI];
+        unsigned wat[WI];
+#pragma unroll
+        for (int i = 0; i < WI; ++i) item_of(t + i * kGemmThreads, wc[i], wrow[i], wat[i]);
+        auto fetch_chunk = [&](int k0) {
+#pragma unroll
+            for (int i = 0; i < WI; ++i) fetch_w(k0, wc[i], wrow[i], w[i]);
+        };
+        auto stash_chunk = [&](unsigned char *dst) {
+#pragma unroll
+            for (int i = 0; i < WI; ++i)
+                if (t + i * kGemmThreads < KC / 16 * 2 * BN) stash_w(dst + wat[i], w[i]);
+        };
+        fetch_chunk(0);
+        stash_chunk(lds);
+        int which = 0;
+        for (int round = 0; round < rounds; ++round)
+            for (int ch = 0; ch < chunks; ++ch) {
+                __syncthreads();   // this chunk's pieces are in its buffer; nobody reads the other one any more
+                const bool more = ch + 1 < chunks || round + 1 < rounds;
+                if (more) fetch_chunk(ch + 1 < chunks ? (ch + 1) * KC : 0);
+                if (tile < t1)
+                    for (int g0 = ch * (KC / 32), g1 = g0 + KC / 32; g0 < g1 && g0 < groups; g0 += DEPTH)
+                        run(g0, lds + which * (KC / 16 * STEP_BYTES) + (g0 - ch * (KC / 32)) * 2 * STEP_BYTES);
+                __builtin_amdgcn_sched_barrier(0);
+                which ^= 1;
+                if (more) stash_chunk(lds + which * (KC / 16 * STEP_BYTES));
+            }
+    }
 }
 
 template <int TN>
-hipError_t gemm_bf_launch(const GemmArgs &g, int avec, hipStream_t s) {
-    const dim3 grid((unsigned)(((g.n + 255) / 256) * g.n_bn + g.side.blocks));
-    if (avec == 4) hipLaunchKernelGGL((k_gemm_bf<TN, 4>), grid, dim3(kThreads), 0, s, g);
-    else if (avec == 2) hipLaunchKernelGGL((k_gemm_bf<TN, 2>), grid, dim3(kThreads), 0, s, g);
-    else hipLaunchKernelGGL((k_gemm_bf<TN, 1>), grid, dim3(kThreads), 0, s, g);
+hipError_t gemm_bf_launch(GemmArgs g, hipStream_t s) {
+    const int steps = (g.k + 31) / 32 * 2;
+    const size_t a_bytes = (size_t)kGemmWaves * 4096 * gemm_a_bufs(TN);
+    const bool chunked = steps * 3 * TN * 1024 + a_bytes > kGemmLds;
+    g.a_lds = (chunked ? 2 * (gemm_kc(TN) / 16) : steps) * 3 * TN * 1024;
+    const long long tiles = (g.n + 31) / 32;
+    // one workgroup too many on an XCD (32 compute units) would run a whole share after all the others: shares are dealt out XCD by XCD where
+    // the blocks of columns divide what an XCD holds, and one after the other where they do not
+    const int held = kGemmCusPerXcd * (g.a_lds + a_bytes <= kGemmLds / 2 ? gemm_held(TN) : 1);
+    g.by_xcd = held % g.n_bn == 0 && tiles >= 8 * (held / g.n_bn);
+    const long long parts = g.by_xcd ? 8 * (held / g.n_bn) : 8 * held > g.n_bn ? 8 * held / g.n_bn : 1;
+    g.n_parts = (int)(parts < tiles ? parts : tiles);
+    const dim3 grid((unsigned)(g.n_parts * g.n_bn + g.side.blocks));
+    if (chunked) hipLaunchKernelGGL((k_gemm_bf<TN, true>), grid, dim3(kGemmThreads), g.a_lds + a_bytes, s, g);
+    else hipLaunchKernelGGL((k_gemm_bf<TN, false>), grid, dim3(kGemmThreads), g.a_lds + a_bytes, s, g);
     return hipGetLastError();
 }
 
@@ -1469,11 +1602,25 @@ void gemv2_launch(const float *A, long long lda, long long n, int k, const float
 
 }  // namespace
 
-// from one 256-row block per compute unit on, and at least one whole step of 16 k
+// blocks of 32 columns a wavefront of k_gemm_bf takes: as many as split the columns evenly in up to four, fewer where that leaves less
+// than half of the chip's 2,048 wavefronts a tile of rows
+static int gemm_bf_blocks(int64_t n, int m_store) {
+    const int blocks = (m_store + 31) / 32;
+    const long long tiles = (n + 31) / 32;
+    int tn = (blocks + (blocks + 3) / 4 - 1) / ((blocks + 3) / 4);
+    while (tn > 1 && tiles * ((blocks + tn - 1) / tn) < 1024) tn = tn > 2 ? 2 : 1;
+    return tn;
+}
+
+// Where the fixed costs of k_gemm_bf (about 6 us: W is fetched and cut before the first multiply) are earned back, by k and rows; outputs wider
+// than 192 columns count more.  fp32 kernels / k_gemm_bf, us: k = 602, 256 columns, 6,000 rows 34 / 25, 18,000 94 / 57; k = 300, 96 columns, 6,000
+// rows 13.3 / 12.3; k = 256, 41 columns, 10,000 rows 10.8 / 12.9, 18,000 18.5 / 13.4; k = 100, 47 columns, 14,000 rows 8.8 / 9.9, 18,000 10.7 /
+// 10.0, 256 columns, 10,000 rows 12.8 / 13.8, 14,000 16.3 / 14.4; k = 32, 128 columns, 22,000 rows 7.7 / 8.9, 28,000 9.2 / 8.4; k = 16, 32 columns,
+// 50,000 rows 6.2 / 7.2, 100,000 8.7 / 8.3.
 bool gemm_uses_pieces(int64_t n, int k, int m_store) {
-    const int tn = m_store <= 32 ? 1 : m_store <= 64 ? 2 : 4;
-    const int n_bn = (m_store + 32 * tn - 1) / (32 * tn);
-    return k >= 16 && m_store > 0 && ((n + 255) / 256) * n_bn >= 256;
+    if (k < 16 || m_store <= 0) return false;
+    const int64_t blocks = (m_store + 31) / 32;
+    return n * (blocks > 6 ? blocks : 6) / 6 >= (k >= 300 ? 6000 : k >= 64 ? 16000 : k >= 32 ? 28000 : 65536);
 }
 
 hipError_t launch_gemm(const float *A, int64_t lda, const float *W, int64_t ldw, float *Y, int64_t ldy, int64_t n,
@@ -1498,18 +1645,17 @@ hipError_t launch_gemm(const float *A, int64_t lda, const float *W, int64_t ldw,
     if (k % 4 == 0 && lda % 4 == 0 && aa % 16 == 0) avec = 4;
     else if (k % 2 == 0 && lda % 2 == 0 && aa % 8 == 0) avec = 2;
     if (m % 4 == 0 && ldw % 4 == 0 && wa % 16 == 0) bvec = 4;
-    // Large products go to the bf16-piece kernel (256-row blocks)
+    // Large products go to the bf16-piece kernel
     {
-        const int tn = m_store <= 32 ? 1 : m_store <= 64 ? 2 : 4;
-        const int n_bn = (m_store + 32 * tn - 1) / (32 * tn);
-        if (gemm_uses_pieces(n, k, m_store) && lda < (1 << 21) && ldw < (1 << 21)) {   // leading dimensions: 32-bit byte offsets within a block
-            g.n_bn = n_bn;
-            int av = 1;
-            if (lda % 4 == 0 && aa % 16 == 0) av = 4;
-            else if (lda % 2 == 0 && aa % 8 == 0) av = 2;
-            if (tn == 1) return done(gemm_bf_launch<1>(g, av, s));
-            if (tn == 2) return done(gemm_bf_launch<2>(g, av, s));
-            return done(gemm_bf_launch<4>(g, av, s));
+        const int tn = gemm_bf_blocks(n, m_store), blocks = (m_store + 31) / 32;
+        g.n_bn = (blocks + tn - 1) / tn;
+        if (gemm_uses_pieces(n, k, m_store) && lda < (1 << 20) && ldw < (1 << 20)) {   // leading dimensions: 32-bit byte offsets within a block
+            switch (tn) {
+                case 1: return done(gemm_bf_launch<1>(g, s));
+                case 2: return done(gemm_bf_launch<2>(g, s));
+                case 3: return done(gemm_bf_launch<3>(g, s));
+                default: return done(gemm_bf_launch<4>(g, s));
+            }
         }
     }
     // Few enough 64 x 64 blocks to leave compute units idle: 32 x 32 blocks with k split over the wavefronts.  A small block reads its operands

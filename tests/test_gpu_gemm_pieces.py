@@ -1,0 +1,72 @@
+"""The dense product on bf16 pieces where it can go wrong: k around the 16- and 32-wide steps and the chunk lengths, columns around blocks of 32,
+the last tile of rows, operands whose rows are longer than the product and start at odd words, infinities; and the epilogue that adds a
+slice-major matrix.  The bound on a product is that of fp32 accumulation: one rounding of the running sum per instruction (six a step of 16 k)
+and the roundings inside one, all relative to the sum of the terms' magnitudes."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from paper_2306_15155_amd import ACT_NONE, ACT_RELU, Context, binding
+
+from gpu_util import DeviceCSR, assert_close, dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = Context(0)
+    yield c
+    c.close()
+
+
+# resident and chunked W, every number of column blocks a wavefront takes, ragged last tiles
+SHAPES = [(65_537, 16, 5), (65_540, 17, 33), (65_567, 31, 64), (30_001, 32, 100), (28_001, 33, 128), (16_031, 64, 65), (16_001, 65, 130), (17_000, 100, 47),
+          (16_005, 127, 160), (20_001, 129, 256), (16_033, 255, 31), (40_001, 256, 96), (70_000, 257, 47), (6_001, 300, 600), (33_000, 602, 24),
+          (36_001, 602, 41), (6_033, 601, 300), (7_001, 700, 224), (50_000, 340, 384)]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("extra", [0, 3])   # floats by which the rows of both operands are longer (and start late)
+def test_product_against_fp64(ctx, shape, extra):
+    n, k, m = shape
+    assert binding.gemm_kernel(n, k, m) == binding.GEMM_BF16_PIECES
+    g = torch.Generator(device="cuda:0").manual_seed(n + k + m)
+    A = torch.randn(n, k + extra, device="cuda:0", generator=g)[:, extra // 2 : extra // 2 + k]
+    W = torch.randn(k, m + extra, device="cuda:0", generator=g)[:, extra - extra // 2 : extra - extra // 2 + m]
+    for act in (ACT_NONE, ACT_RELU):
+        Y = ctx.gemm(A, W, act).double()
+        ref, terms = A.double() @ W.double(), A.double().abs() @ W.double().abs()
+        if act == ACT_RELU:
+            ref = ref.clamp(min=0)
+        bound = 2.0 ** -24 * (6 * ((k + 15) // 16) + 16)
+        worst = ((Y - ref).abs() / terms).max().item()
+        assert worst <= bound, (worst, bound)
+
+
+def test_infinities_and_the_largest_values(ctx):
+    n, k, m = 20_000, 70, 40
+    A, W = synth.uniform(5, 1, (n, k), 0.5, 1.0), synth.uniform(5, 2, (k, m), 0.5, 1.0)
+    big = float(np.finfo(np.float32).max)
+    A[7, 3], A[9, 5], A[11, 0] = np.inf, -np.inf, np.nan
+    A[13, :], A[13, 2] = 0.0, -big
+    Y = ctx.gemm(dev(A), dev(W), ACT_NONE).cpu().numpy()
+    assert np.all(Y[7] == np.inf) and np.all(Y[9] == -np.inf) and np.all(np.isnan(Y[11]))
+    ref = -big * W[2].astype(np.float64)
+    assert np.all(np.abs(Y[13] - ref) <= 2.0 ** -22 * np.abs(ref))
+    rest = np.setdiff1d(np.arange(n), [7, 9, 11, 13])
+    assert np.all(np.isfinite(Y[rest]))
+
+
+@pytest.mark.parametrize("f_in,f_out", [(64, 41), (101, 96)])
+def test_epilogue_adds_a_sliced_matrix(ctx, f_in, f_out):
+    """TAGCN, update first: every product but the first adds the running sum of the hops."""
+    g = synth.rmat(17, 20_011, 60_000)
+    A = DeviceCSR(g)
+    dr, dc = ctx.degrees(A.s)
+    r, c = ctx.norm_vectors(dr), ctx.norm_vectors(dc)
+    X, W = synth.uniform(17, 1, (g.n_cols, f_in)), synth.glorot(17, 2, 3 * f_in, f_out)
+    Y = ctx.tagcn_layer(A.s, r, c, dev(X), dev(W), 2, 1, ACT_RELU)
+    assert_close(Y, oracle.tagcn_layer(g.n_rows, g.row_ptr, g.col_idx, X, W, 2, ACT_RELU), what="tagcn update first")
