@@ -156,10 +156,24 @@ size_t gcn_ws(const sensei_csr &A, int f_in, int f_out, int id) {
 
 bool gat_is_reuse(int id) { return id == SENSEI_GAT_REUSE || id == SENSEI_GAT_REUSE_FOLD; }
 
+// Heads of 32 columns whose Theta is slice-major are aggregated in one launch where the one-walk form is taken; at most kHeadsPerLaunch (the
+// workspace query does not know the number of heads: it makes room for as many as f_out allows).
+constexpr int kHeadsPerLaunch = 16;
+int fused_heads_max(int f_out, int id) {
+    const int heads = f_out % 32 == 0 && id == SENSEI_GAT_REUSE ? f_out / 32 : 1;
+    return heads < kHeadsPerLaunch ? heads : kHeadsPerLaunch;
+}
+
 size_t gat_ws(const sensei_csr &A, int f_in, int f_out, int id) {
     const int fo = pad32(f_out), fi = pad4(f_in);
     size_t b = plan_bytes(A.nnz) + softmax_ws_bytes(A);
     b += 2 * align_up((size_t)A.n_cols * sizeof(float), 256);                  // s_l, s_r
+    if (fused_heads_max(f_out, id) > 1) {                                      // the same for every head of one slice, and (max, sum) pairs
+        const size_t h = fused_heads_max(f_out, id);
+        const int t = choose_chunk_nnz(A.nnz);
+        b += 2 * align_up(h * A.n_cols * sizeof(float), 256) + align_up(h * ((size_t)A.n_rows + 1) * sizeof(float2), 256) +
+             align_up(h * (size_t)(A.nnz > 0 ? (A.nnz + t - 1) / t : 1) * sizeof(float2), 256);
+    }
     b += align_up((size_t)(A.nnz > 0 ? A.nnz : 1) * sizeof(float), 256);       // attention logits
     b += 2 * align_up((size_t)fi * sizeof(float), 256);                        // W.a_l, W.a_r
     if (id != SENSEI_GAT_RECOMP_FOLD) b += align_up((size_t)A.n_cols * fo * sizeof(float), 256);  // Theta
@@ -755,6 +769,24 @@ int run_gat(const sensei_csr &A, const sensei_mat &X, const sensei_mat &W, const
     // themselves, only the remainder's logits are stored
     const int path = attention_path(A, f_gather, reuse ? theta_sliced : x_sliced);
     const bool by_tiles = path == kAttnTiles, by_panel = path == kAttnPanels, fused = path == kAttnOneWalk;
+    if (fused && theta_sliced && n_heads > 1 && d == 32 && id == SENSEI_GAT_REUSE) {
+        // every head is a slice of Theta: projections, walk and fix-up of up to kHeadsPerLaunch heads in a launch each
+        const int most = fused_heads_max(f_out, id);
+        float *hs_l = cv.take<float>((size_t)most * A.n_cols), *hs_r = cv.take<float>((size_t)most * A.n_cols);
+        float2 *h_mz = cv.take<float2>((size_t)most * (A.n_rows + 1)), *h_carry = cv.take<float2>((size_t)most * plan.n_chunks);
+        for (int h = 0; h < n_heads; h += most) {
+            const int hb = n_heads - h < most ? n_heads - h : most;
+            const float *theta_h = theta + (size_t)h * (size_t)A.n_cols * 32;
+            SENSEI_TRY(launch_head_scores(theta_h, A.n_cols, hb, d, a_l + (size_t)h * d, a_r + (size_t)h * d, hs_l, hs_r, s));
+            const AttnFusedArgs fa = {hs_l, hs_r, slope, h_mz, h_carry, hb};
+            hipEvent_t t0 = kt ? kt->next() : nullptr, t1 = t0 ? kt->next() : nullptr;
+            if (t1) SENSEI_TRY(hipEventRecord(t0, s));
+            SENSEI_TRY(launch_spmm(A, kSpmmAttnFused, nullptr, nullptr, theta_h, fo, hb * d, Y + (size_t)h * d, ldy, hb * d, act, plan, carry, s, nullptr, false,
+                                   true, nullptr, true, 1, false, false, &fa));
+            if (t1) SENSEI_TRY(hipEventRecord(t1, s));
+        }
+        return SENSEI_OK;
+    }
     for (int h = 0; h < n_heads; ++h) {
         const float *al = a_l + (size_t)h * d, *ar = a_r + (size_t)h * d;
         const float *theta_h = !theta ? nullptr : theta_sliced ? theta + (size_t)h * (d / 32) * (size_t)A.n_cols * 32 : theta + (size_t)h * d;
@@ -1166,6 +1198,8 @@ bool tiles_serve_transposed(const sensei_csr &At, int f_out) {
     return D->n_rows == At.n_rows && D->n_cols == At.n_cols && D->nnz == At.nnz && D->src_row_ptr == At.row_ptr && D->src_col_idx == At.col_idx;
 }
 
+size_t narrow_bwd_ws(const sensei_csr &A, int f_in, int n_heads);
+
 size_t gat_bwd_ws(const sensei_csr &A, const sensei_csr *At, int f_in, int f_out) {
     const size_t nz = (size_t)(A.nnz > 0 ? A.nnz : 1), fo32 = pad32(f_out), fo4 = pad4(f_out), fi4 = pad4(f_in);
     const int t = choose_chunk_nnz(A.nnz);
@@ -1189,7 +1223,71 @@ size_t gat_bwd_ws(const sensei_csr &A, const sensei_csr *At, int f_in, int f_out
         b += align_up((size_t)(D.nnz_rem > 0 ? D.nnz_rem : 1) * sizeof(float), 256);
     }
     if (At && tiles_serve_transposed(*At, f_out)) b += align_up((size_t)(At->tiles->nnz_rem > 0 ? At->tiles->nnz_rem : 1) * sizeof(float), 256);
+    if (f_out <= 32) {   // the walks of narrow heads, behind dTheta, W^T and the slabs of dW
+        const size_t narrow = narrow_bwd_ws(A, f_in, 1) + align_up((size_t)A.n_cols * fo4 * sizeof(float), 256) + align_up(fo4 * fi4 * sizeof(float), 256) +
+                              gemm_tn_bytes(A.n_cols, f_in, f_out);
+        b = b > narrow ? b : narrow;
+    }
     return b;
+}
+
+// Heads of one slice (at most 32 columns) without tile splits: both walks of all heads in one launch each, nothing stored per entry.
+bool heads_narrow(const sensei_csr &A, const sensei_csr &At, int d) { return d <= 32 && !tiles_serve_dalpha(A, d) && !tiles_serve_transposed(At, d); }
+
+size_t narrow_bwd_ws(const sensei_csr &A, int f_in, int n_heads) {
+    const size_t h = n_heads < kHeadsPerLaunch ? n_heads : kHeadsPerLaunch;
+    const int t = choose_chunk_nnz(A.nnz);
+    const size_t n_chunks = A.nnz <= 0 ? 1 : (size_t)((A.nnz + t - 1) / t);
+    size_t b = 2 * plan_bytes(A.nnz) + 512;
+    b += 4 * align_up(h * A.n_cols * sizeof(float), 256);                                            // s_l, s_r, ds_l, ds_r
+    b += align_up(h * A.n_cols * 32 * sizeof(float), 256) + align_up(h * A.n_rows * 32 * sizeof(float), 256);   // Theta, dP
+    b += align_up(h * ((size_t)A.n_rows + 1) * sizeof(float4), 256);                                 // rows
+    b += align_up(h * n_chunks * 16 * sizeof(float), 256) + align_up(h * n_chunks * 32 * sizeof(float), 256) + align_up(h * n_chunks * sizeof(float), 256);
+    b += align_up((size_t)f_in * h * 32 * sizeof(float), 256);                                       // W with a slice per head
+    return b + theta_t_vec_bytes(A.n_cols, (int)(h * 32));
+}
+
+// dTheta (row-major, ldt, head h's columns from h * d on), da_l and da_r of all heads; Wt (optional, leading dimension ldwt): W transposed
+int run_narrow_backward(const sensei_csr &A, const sensei_csr &At, const sensei_mat &X, const sensei_mat &W, const float *a_l, const float *a_r, int n_heads,
+                        float slope, const float *Y, int64_t ldy, const sensei_mat &dY, int act, float *dTheta, int64_t ldt, float *da_l, float *da_r,
+                        float *Wt, int64_t ldwt, Carver cv, hipStream_t s) {
+    const int f_in = (int)X.cols, d = (int)W.cols / n_heads, most = n_heads < kHeadsPerLaunch ? n_heads : kHeadsPerLaunch;
+    const size_t nc = A.n_cols, nr = A.n_rows;
+    ChunkPlan plan = make_plan(A, cv), plan_t = make_plan(At, cv);
+    SideWork side;
+    side.add_plan(A, plan);
+    side.add_plan(At, plan_t);
+    if (Wt) side.add_transpose(W.ptr, W.ld, f_in, (int)W.cols, Wt, ldwt);
+    float *s_l = cv.take<float>(most * nc), *s_r = cv.take<float>(most * nc), *ds_l = cv.take<float>(most * nc), *ds_r = cv.take<float>(most * nc);
+    float *theta = cv.take<float>(most * nc * 32), *T = cv.take<float>(most * nr * 32);
+    float4 *row = cv.take<float4>(most * (nr + 1));
+    float *piece = cv.take<float>((size_t)most * plan.n_chunks * 16);
+    float *carry = cv.take<float>((size_t)most * plan_t.n_chunks * 32), *ds_carry = cv.take<float>((size_t)most * plan_t.n_chunks);
+    float *Wp = cv.take<float>((size_t)f_in * most * 32);
+    double *part_a = cv.take<double>(theta_t_vec_bytes(A.n_cols, most * 32) / sizeof(double));
+    for (int h = 0; h < n_heads; h += most) {
+        const int hb = n_heads - h < most ? n_heads - h : most;
+        const size_t at = (size_t)h * d;
+        const float *Wh = W.ptr + at;
+        int64_t ldw = W.ld;
+        if (d < 32 && hb > 1) {
+            SENSEI_TRY(launch_pad_heads(Wh, ldw, f_in, hb, d, Wp, hb * 32, s));
+            Wh = Wp;
+            ldw = hb * 32;
+        }
+        SENSEI_TRY(launch_gemm(X.ptr, X.ld, Wh, ldw, theta, hb * 32, A.n_cols, f_in, hb > 1 ? hb * 32 : d, hb * 32, SENSEI_ACT_NONE, s, nullptr, nullptr, true,
+                               false, nullptr, &side));
+        SENSEI_TRY(launch_side(&side, s));   // a pattern without columns launches no product
+        SENSEI_TRY(launch_head_scores(theta, A.n_cols, hb, d, a_l + at, a_r + at, s_l, s_r, s));
+        SENSEI_TRY(launch_to_slices(nullptr, dY.ptr + at, dY.ld, A.n_rows, hb * d, T, s, act == SENSEI_ACT_RELU ? Y + at : nullptr, ldy, nullptr, hb));
+        GatHeadsBackward b;
+        b.theta = theta; b.dP = T; b.s_l = s_l; b.s_r = s_r; b.row = row; b.ds_l = ds_l; b.ds_r = ds_r; b.piece = piece;
+        b.dtheta = dTheta + at; b.carry = carry; b.ds_carry = ds_carry; b.ldd = ldt; b.d = d; b.heads = hb; b.slope = slope;
+        SENSEI_TRY(launch_gat_heads_backward(A, plan, At, plan_t, b, s));
+        SENSEI_TRY(launch_rank1_add(dTheta + at, ldt, A.n_cols, hb * d, ds_l, A.n_rows, ds_r, a_l + at, a_r + at, s, hb));
+        SENSEI_TRY(launch_theta_t_vec(theta, A.n_cols, hb * d, ds_l, A.n_rows, ds_r, da_l + at, da_r + at, part_a, s, hb));
+    }
+    return SENSEI_OK;
 }
 
 int run_gat_backward(const sensei_csr &A, const sensei_csr &At, const int32_t *t_pos, const sensei_mat &X, const sensei_mat &W,
@@ -1202,6 +1300,16 @@ int run_gat_backward(const sensei_csr &A, const sensei_csr &At, const int32_t *t
     const int fo32 = pad32(f_out), fo4 = pad4(f_out), fi4 = pad4(f_in);
     const size_t nz = (size_t)(A.nnz > 0 ? A.nnz : 1);
     Carver cv(ws, ws_bytes);
+    if (!dtheta_out && heads_narrow(A, At, f_out)) {
+        float *dTheta = cv.take<float>((size_t)A.n_cols * fo4), *Wt = cv.take<float>((size_t)fo4 * fi4);
+        double *part = cv.take<double>(gemm_tn_bytes(A.n_cols, f_in, f_out) / sizeof(double));
+        const int rc = run_narrow_backward(A, At, X, W, a_l, a_r, 1, slope, Y, ldy, dY, act, dTheta, fo4, da_l, da_r, dX ? Wt : nullptr, fi4,
+                                           cv, s);
+        if (rc != SENSEI_OK) return rc;
+        SENSEI_TRY(launch_gemm_tn(X.ptr, X.ld, dTheta, fo4, A.n_cols, f_in, f_out, dW, lddw, part, s));
+        if (dX) SENSEI_TRY(launch_gemm(dTheta, fo4, Wt, fi4, dX, lddx, A.n_cols, f_out, f_in, f_in, SENSEI_ACT_NONE, s));
+        return SENSEI_OK;
+    }
     ChunkPlan plan = make_plan(A, cv), plan_t = make_plan(At, cv);
     float2 *stats = cv.take<float2>((size_t)A.n_rows + 1);
     float2 *carry_stats = cv.take<float2>((size_t)plan.n_chunks);
@@ -1319,7 +1427,8 @@ int run_gat_backward(const sensei_csr &A, const sensei_csr &At, const int32_t *t
 // beside the others'; dW = X^T [dTheta_0 .. dTheta_(H-1)] and dX = [dTheta_0 ..] W^T are then one product each for all heads.
 size_t gat_bwd_heads_ws(const sensei_csr &A, const sensei_csr *At, int f_in, int f_out, int n_heads) {
     const size_t fo4 = pad4(f_out), fi4 = pad4(f_in);
-    return gat_bwd_ws(A, At, f_in, f_out / n_heads) + align_up((size_t)A.n_cols * fo4 * sizeof(float), 256) + align_up(fo4 * fi4 * sizeof(float), 256) +
+    const size_t one = gat_bwd_ws(A, At, f_in, f_out / n_heads), narrow = f_out / n_heads <= 32 ? narrow_bwd_ws(A, f_in, n_heads) : 0;
+    return (one > narrow ? one : narrow) + align_up((size_t)A.n_cols * fo4 * sizeof(float), 256) + align_up(fo4 * fi4 * sizeof(float), 256) +
            gemm_tn_bytes(A.n_cols, f_in, f_out) + 256;
 }
 
@@ -1332,6 +1441,14 @@ int run_gat_backward_heads(const sensei_csr &A, const sensei_csr &At, const int3
     float *dTh = cv.take<float>((size_t)A.n_cols * fo4);
     float *Wt = cv.take<float>((size_t)fo4 * fi4);
     double *part = cv.take<double>(gemm_tn_bytes(A.n_cols, f_in, f_out) / sizeof(double));
+    if (heads_narrow(A, At, d)) {
+        const int rc = run_narrow_backward(A, At, X, W, a_l, a_r, n_heads, slope, Y, ldy, dY, act, dTh, fo4, da_l, da_r, dX ? Wt : nullptr,
+                                           fi4, cv, s);
+        if (rc != SENSEI_OK) return rc;
+        SENSEI_TRY(launch_gemm_tn(X.ptr, X.ld, dTh, fo4, A.n_cols, f_in, f_out, dW, lddw, part, s));
+        if (dX) SENSEI_TRY(launch_gemm(dTh, fo4, Wt, fi4, dX, lddx, A.n_cols, f_out, f_in, f_in, SENSEI_ACT_NONE, s));
+        return SENSEI_OK;
+    }
     void *ws_head = cv.base + cv.used;
     const size_t ws_head_bytes = ws_bytes - cv.used;
     for (int h = 0; h < n_heads; ++h) {

@@ -1098,6 +1098,39 @@ __global__ __launch_bounds__(kThreads) void k_tiles_sddmm(const float *__restric
         }
 }
 
+// the projections of every head (blockIdx.y) of one slice: eight lanes a row
+__global__ __launch_bounds__(kThreads) void k_head_scores(const float *__restrict__ theta, long long n, int d, const float *__restrict__ a_l,
+                                                          const float *__restrict__ a_r, float *__restrict__ s_l, float *__restrict__ s_r) {
+    const int head = blockIdx.y, li = threadIdx.x & 7;
+    const long long row = (long long)blockIdx.x * (kThreads / 8) + threadIdx.x / 8, rc = row < n ? row : n - 1;
+    const float4 x = *reinterpret_cast<const float4 *>(theta + ((size_t)head * n + rc) * 32 + li * 4);
+    const float xe[4] = {x.x, x.y, x.z, x.w};
+    float l = 0.f, r = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int q = li * 4 + e;
+        if (q < d) {
+            l = fmaf(xe[e], a_l[head * d + q], l);
+            r = fmaf(xe[e], a_r[head * d + q], r);
+        }
+    }
+#pragma unroll
+    for (int off = 4; off > 0; off >>= 1) {
+        l += __shfl_xor(l, off, 64);
+        r += __shfl_xor(r, off, 64);
+    }
+    if (li == 0 && row < n) { s_l[head * n + row] = l; s_r[head * n + row] = r; }
+}
+
+__global__ void k_pad_heads(const float *__restrict__ W, long long ldw, int f_in, int heads, int d, float *__restrict__ out, long long ldo) {
+    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const int cols = heads * 32;
+    if (t >= (long long)f_in * cols) return;
+    const int q = (int)(t % cols), c = q & 31;
+    const long long k = t / cols;
+    out[k * ldo + q] = c < d ? W[k * ldw + (q >> 5) * d + c] : 0.f;
+}
+
 // the attention vectors in rank order (zeros where a rank has no node)
 __global__ void k_gather_ranked_vecs(const float *__restrict__ s_l, const float *__restrict__ s_r, const float2 *__restrict__ mz,
                                      const int32_t *__restrict__ order_r, int n_r, const int32_t *__restrict__ order_c, int n_c,
@@ -1814,6 +1847,20 @@ hipError_t launch_tiles_combine_pm(const TileSplit &T, float *C, int64_t n_rows,
     hipLaunchKernelGGL(k_tiles_combine_pm, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, C, (long long)n_rows, f_store,
                        c_sliced ? 32LL : (long long)ldc, c_sliced ? (long long)n_rows * 32 : 32LL, (const float *)T.dh, f, T.rank_r, T.nt_r * 128, r, mz,
                        act, vec4, part, n_panels, seg_ptr, chunk_nnz, carry, f_carry, mz ? tile_shift : nullptr);
+    return hipGetLastError();
+}
+
+hipError_t launch_head_scores(const float *theta, int64_t n, int heads, int d, const float *a_l, const float *a_r, float *s_l, float *s_r, hipStream_t s) {
+    if (n <= 0 || heads <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_head_scores, dim3((unsigned)((n + kThreads / 8 - 1) / (kThreads / 8)), (unsigned)heads), dim3(kThreads), 0, s, theta, (long long)n,
+                       d, a_l, a_r, s_l, s_r);
+    return hipGetLastError();
+}
+
+hipError_t launch_pad_heads(const float *W, int64_t ldw, int f_in, int heads, int d, float *out, int64_t ldo, hipStream_t s) {
+    const long long total = (long long)f_in * heads * 32;
+    if (total <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_pad_heads, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, W, (long long)ldw, f_in, heads, d, out, (long long)ldo);
     return hipGetLastError();
 }
 

@@ -134,6 +134,7 @@ struct AttnFusedArgs {
     const float *s_l, *s_r;
     float slope;
     float2 *row_mz, *chunk_mz;
+    int heads = 1;   // > 1 (slice-major B of heads * 32 columns, all stored): slice h is head h's; s_l, s_r, row_mz and chunk_mz one after the other per head
 };
 // Internal SpMM modes for the backward pass of a score with a vector per entry, e_ij = att . LeakyReLU(U_ij), U_ij = self[i, :] + B[j, :]
 // (slice-major self over the rows and B over the columns): C[i, m] = sum_j val_ij LeakyReLU'(U_ij[m]) (kSpmmSignSum: 1 where
@@ -171,7 +172,8 @@ hipError_t launch_row_broadcast(const float *s_vec, const float *X, int64_t ldx,
 
 // Y (slice-major, pad32(f) columns, 128-byte aligned, n * pad32(f) floats) = s_vec (x) X, s_vec optional; pad columns = 0
 hipError_t launch_to_slices(const float *s_vec, const float *X, int64_t ldx, int64_t n, int f, float *Y, hipStream_t s,
-                            const float *mask = nullptr, int64_t ldm = 0, SideWork *side = nullptr);
+                            const float *mask = nullptr, int64_t ldm = 0, SideWork *side = nullptr, int n_heads = 1);
+// n_heads > 1: every head's f / n_heads (at most 32) columns get a slice of their own
 
 // ---- attention: logits, per-row softmax statistics, normalised weights
 hipError_t launch_score(const sensei_csr &A, const float *s_l, const float *s_r, float slope, float *e,
@@ -208,14 +210,32 @@ hipError_t launch_gat_dt(const sensei_csr &A, const float *logits, const float *
 hipError_t launch_score_v2(const sensei_csr &A, const float *theta_l, const float *theta_r, int f, const float *att_padded, float slope,
                            float *logits, const ChunkPlan &p, hipStream_t s);
 hipError_t launch_rank1_add(float *D, int64_t ldd, int64_t n, int f, const float *ds_l, int64_t n_l, const float *ds_r, const float *a_l,
-                            const float *a_r, hipStream_t s);
+                            const float *a_r, hipStream_t s, int n_heads = 1);
 // out_l = Theta^T v_l (v_l counted for the first n_l rows), out_r = Theta^T v_r; Theta slice-major n x pad32(f); sums in fp64
 // D[i, m] = (accumulate ? D[i, m] : 0) + v[m] G[i, m] over n rows and f columns (G may be D)
 hipError_t launch_scale_cols(float *D, int64_t ldd, const float *G, int64_t ldg, const float *v, int64_t n, int f, bool accumulate, hipStream_t s);
 hipError_t launch_fill_f32(float *p, int64_t n, float v, hipStream_t s);
 size_t theta_t_vec_bytes(int64_t n, int f);
 hipError_t launch_theta_t_vec(const float *theta_sliced, int64_t n, int f, const float *v_l, int64_t n_l, const float *v_r, float *out_l,
-                              float *out_r, double *part, hipStream_t s);
+                              float *out_r, double *part, hipStream_t s, int n_heads = 1);
+// n_heads > 1 (here and in launch_rank1_add): heads of f / n_heads columns, a pair of vectors each, n floats apart; Theta holds one slice a head
+// Backward of attention heads of d <= 32 columns, slice h of theta (n_cols rows) and dP (n_rows rows) being head h's: ds_l, ds_r (n_cols floats a head)
+// and dtheta (row-major, head h's columns from h * d on) without the rank-1 terms.  Scratch: row n_rows float4 a head, piece 16 floats a head and chunk
+// of A, carry 32 floats and ds_carry one a head and chunk of At.
+struct GatHeadsBackward {
+    const float *theta, *dP, *s_l, *s_r;   // s_l, s_r: n_cols floats a head
+    float4 *row;
+    float *ds_l, *ds_r, *piece, *dtheta, *carry, *ds_carry;
+    int64_t ldd;
+    int d, heads;
+    float slope;
+};
+hipError_t launch_gat_heads_backward(const sensei_csr &A, const ChunkPlan &p, const sensei_csr &At, const ChunkPlan &pt, const GatHeadsBackward &b,
+                                     hipStream_t s);
+// s_l[h][j] = Theta_h[j, :] . a_l[h], s_r likewise, for heads of d <= 32 columns; theta holds one slice a head (n rows)
+hipError_t launch_head_scores(const float *theta, int64_t n, int heads, int d, const float *a_l, const float *a_r, float *s_l, float *s_r, hipStream_t s);
+// out (f_in x heads * 32, ldo): head h's d columns of W followed by zero columns up to 32
+hipError_t launch_pad_heads(const float *W, int64_t ldw, int f_in, int heads, int d, float *out, int64_t ldo, hipStream_t s);
 // pos[k] = place of entry k of A in At (binary search in the ascending columns of At); *miss (cleared first) counts entries not found
 hipError_t launch_transpose_pos(const sensei_csr &A, const sensei_csr &At, const ChunkPlan &p, int32_t *pos, int32_t *miss, hipStream_t s);
 

@@ -67,6 +67,7 @@ struct SpmmArgs {
     // fused attention mode: the two score vectors, the LeakyReLU slope, and where the (max, sum) pairs of row pieces go
     const float *s_l, *s_r;
     float slope;
+    long long head_vec, head_mz;  // several heads of one tile each: floats from one head's score vectors to the next, pairs from one head's mz_out to the next (0: one head)
     float2 *mz_out, *carry_mz;  // per row: pair of a first piece whose row goes on in the next chunk; per chunk: pair of its continued row
     // modes kSpmmSignSum / kSpmmLreluSum: a vector per row, slice-major like C (tile t of row i at self + t * self_tile + i * 32)
     const float *self;
@@ -172,36 +173,93 @@ __device__ __forceinline__ FlatChunk<PER> flat_rows(const NnzArgs &a, int chunk,
 // Segmented sum of v (blocked order; entries past the end of the chunk hold 0): write(row, sum, place of the piece's last entry) once per
 // row piece of the chunk.
 // A lane's entries fall into a head (up to its first row start), whole rows, and a tail; the heads are completed by the scan.
-template <int PER, class Write>
-__device__ __forceinline__ void flat_sum(const FlatChunk<PER> &c, int lane, const float (&v)[PER], Write write) {
-    float head = 0.f, run = 0.f;
+template <int PER, int N, class Write>
+__device__ __forceinline__ void flat_sums(const FlatChunk<PER> &c, int lane, const float (&v)[N][PER], Write write) {
+    float head[N], run[N], before[N];
+#pragma unroll
+    for (int n = 0; n < N; ++n) head[n] = run[n] = 0.f;
     int head_end = 0;
     bool started = false;
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
         if ((c.starts >> e) & 1u) {
             if (started) write(c.rid[e > 0 ? e - 1 : 0], run, lane * PER + e - 1);
-            else { head = run; head_end = lane * PER + e - 1; }
+            else head_end = lane * PER + e - 1;
+#pragma unroll
+            for (int n = 0; n < N; ++n) {
+                if (!started) head[n] = run[n];
+                run[n] = 0.f;
+            }
             started = true;
-            run = 0.f;
         }
-        run += v[e];
+#pragma unroll
+        for (int n = 0; n < N; ++n) run[n] += v[n][e];
     }
-    float tail = run;
-    int f = started;
+    int f = started;   // run: the tail from here on
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
-        const float o = __shfl_up(tail, off, 64);
+        float o[N];
+#pragma unroll
+        for (int n = 0; n < N; ++n) o[n] = __shfl_up(run[n], off, 64);
         const int of = __shfl_up(f, off, 64);
         if (lane >= off) {
-            if (!f) tail += o;
+#pragma unroll
+            for (int n = 0; n < N; ++n) if (!f) run[n] += o[n];
             f |= of;
         }
     }
-    const float before = __shfl_up(tail, 1, 64);   // the open row piece of the lanes before this one
+#pragma unroll
+    for (int n = 0; n < N; ++n) before[n] = __shfl_up(run[n], 1, 64);   // the open row piece of the lanes before this one
     const int head_row = (c.starts & 1u) ? c.prev_row : c.rid[0];
-    if (started && head_row >= 0 && lane > 0) write(head_row, before + head, head_end);
-    if (lane == 63) write(c.rid[PER - 1], tail, c.hi - c.lo - 1);
+    if (started && head_row >= 0 && lane > 0) {
+#pragma unroll
+        for (int n = 0; n < N; ++n) head[n] = before[n] + head[n];
+        write(head_row, head, head_end);
+    }
+    if (lane == 63) write(c.rid[PER - 1], run, c.hi - c.lo - 1);
+}
+template <int PER, class Write>
+__device__ __forceinline__ void flat_sum(const FlatChunk<PER> &c, int lane, const float (&v)[PER], Write write) {
+    float one[1][PER];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) one[0][e] = v[e];
+    flat_sums<PER, 1>(c, lane, one, [&](int row, const float (&sum)[1], int end) { write(row, sum[0], end); });
+}
+
+// The maximum over every row piece, for each of its entries (blocked order; entries past the end of the chunk hold -inf): inside the lane,
+// then what lies before the lane (forward scan of the tails) and behind it (backward scan of the heads).
+template <int PER>
+__device__ __forceinline__ void flat_piece_max(const FlatChunk<PER> &c, int lane, const float (&e)[PER], float (&mx)[PER]) {
+#pragma unroll
+    for (int q = 0; q < PER; ++q) mx[q] = (q > 0 && !((c.starts >> q) & 1u)) ? fmaxf(mx[q > 0 ? q - 1 : 0], e[q]) : e[q];
+#pragma unroll
+    for (int q = PER - 2; q >= 0; --q)
+        if (!((c.starts >> (q + 1)) & 1u)) mx[q] = mx[q + 1];
+    float fwd = mx[PER - 1], bwd = (c.starts & 1u) ? -INFINITY : mx[0];
+    int ff = c.starts != 0u, fb = ff;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const float of = __shfl_up(fwd, off, 64), ob = __shfl_down(bwd, off, 64);
+        const int gf = __shfl_up(ff, off, 64), gb = __shfl_down(fb, off, 64);
+        if (lane >= off) {
+            if (!ff) fwd = fmaxf(fwd, of);
+            ff |= gf;
+        }
+        if (lane + off < 64) {
+            if (!fb) bwd = fmaxf(bwd, ob);
+            fb |= gb;
+        }
+    }
+    float before = __shfl_up(fwd, 1, 64), behind = __shfl_down(bwd, 1, 64);
+    if (lane == 0) before = -INFINITY;
+    if (lane == 63) behind = -INFINITY;
+    bool open = true;   // entries up to the lane's first row start belong to a piece that began before the lane
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        if ((c.starts >> q) & 1u) open = false;
+        if (open) mx[q] = fmaxf(mx[q], before);
+        if ((c.starts >> q) < 2u) mx[q] = fmaxf(mx[q], behind);   // no row starts after entry q: its piece goes on behind the lane
+    }
 }
 
 // A value per row for entries in striped order.  Chunks of at most 64 rows keep the values of their rows in the lanes' registers and hand
@@ -692,7 +750,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
             cols[at] = (int)((unsigned)col[u] | ((unsigned)rw[u] & 0x80000000u));
             rw[u] &= 0x7fffffff;
             if (MODE == SENSEI_SPMM_SCALED) es[u] = a.c[col[u]];
-            if (MODE == kSpmmAttnFused) es[u] = a.s_r[col[u]];
+            if (MODE == kSpmmAttnFused) es[u] = a.s_r[tile * a.head_vec + col[u]];
         }
         if (MODE == kSpmmSoftmax) {
             // (max, sum) pairs of the rows; gathered per entry where the chunk has more rows than lanes
@@ -717,7 +775,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
             }
         }
         if (MODE == kSpmmAttnFused) {
-            const RowVals rv = row_vals<PER>(c, lane, a.s_l);
+            const RowVals rv = row_vals<PER>(c, lane, a.s_l + tile * a.head_vec);
 #pragma unroll
             for (int u = 0; u < PER; ++u) {
                 const float t = row_val(rv, rw[u]) + es[u];
@@ -731,42 +789,13 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
     }
     lds_exchange();
     if (MODE == kSpmmAttnFused) {
-        // the maximum over every row piece, for each of its entries: inside the lane, then what lies before the lane (forward scan of the
-        // tails) and behind it (backward scan of the heads)
         float e[PER], mx[PER], p[PER];
         const int n_mine = n - lane * PER;
 #pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            e[q] = q < n_mine ? wgt[flat_at<PER, PAD, G>(lane * PER + q)] : -INFINITY;
-            mx[q] = (q > 0 && !((c.starts >> q) & 1u)) ? fmaxf(mx[q > 0 ? q - 1 : 0], e[q]) : e[q];
-        }
-#pragma unroll
-        for (int q = PER - 2; q >= 0; --q)
-            if (!((c.starts >> (q + 1)) & 1u)) mx[q] = mx[q + 1];
-        float fwd = mx[PER - 1], bwd = (c.starts & 1u) ? -INFINITY : mx[0];
-        int ff = c.starts != 0u, fb = ff;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const float of = __shfl_up(fwd, off, 64), ob = __shfl_down(bwd, off, 64);
-            const int gf = __shfl_up(ff, off, 64), gb = __shfl_down(fb, off, 64);
-            if (lane >= off) {
-                if (!ff) fwd = fmaxf(fwd, of);
-                ff |= gf;
-            }
-            if (lane + off < 64) {
-                if (!fb) bwd = fmaxf(bwd, ob);
-                fb |= gb;
-            }
-        }
-        float before = __shfl_up(fwd, 1, 64), behind = __shfl_down(bwd, 1, 64);
-        if (lane == 0) before = -INFINITY;
-        if (lane == 63) behind = -INFINITY;
-        bool open = true;   // entries up to the lane's first row start belong to a piece that began before the lane
+        for (int q = 0; q < PER; ++q) e[q] = q < n_mine ? wgt[flat_at<PER, PAD, G>(lane * PER + q)] : -INFINITY;
+        flat_piece_max<PER>(c, lane, e, mx);
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
-            if ((c.starts >> q) & 1u) open = false;
-            if (open) mx[q] = fmaxf(mx[q], before);
-            if ((c.starts >> q) < 2u) mx[q] = fmaxf(mx[q], behind);   // no row starts after entry q: its piece goes on behind the lane
             p[q] = q < n_mine ? __expf(e[q] - mx[q]) : 0.f;
             wgt[flat_at<PER, PAD, G>(lane * PER + q)] = p[q];
             scale[flat_at<PER, PAD, G>(lane * PER + q)] = mx[q];
@@ -774,9 +803,9 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
         lds_exchange();
         flat_sum<PER>(c, lane, p, [&](int i, float z, int end) {
             const int at = flat_at<PER, PAD, G>(end);
-            if (tile == 0) {   // every feature tile of the chunk forms the same pairs: one writes them
-                if (i == cont_row) a.carry_mz[chunk] = make_float2(scale[at], z);
-                else if (i == open_row) a.mz_out[i] = make_float2(scale[at], z);
+            if (tile == 0 || a.head_vec) {   // every feature tile of the chunk forms the same pairs: one writes them (a tile is a head: each its own)
+                if (i == cont_row) a.carry_mz[(a.head_vec ? (size_t)tile * a.n_chunks : 0) + chunk] = make_float2(scale[at], z);
+                else if (i == open_row) a.mz_out[tile * a.head_mz + i] = make_float2(scale[at], z);
             }
             scale[at] = inv_z(z);
         });
@@ -999,6 +1028,14 @@ __global__ __launch_bounds__(kBlock) void k_spmm_fixup(SpmmArgs a) {
 __global__ __launch_bounds__(kBlock) void k_spmm_fixup_attn(SpmmArgs a) {
     __shared__ FixupLds lds;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (a.head_vec) {   // one head (32 columns) per blockIdx.y
+        const int head = blockIdx.y;
+        a.f_store = min(a.f_store - head * 32, 32);
+        a.C += (size_t)head * a.c_tile;
+        a.carry += (size_t)head * 32;
+        a.mz_out += head * a.head_mz;
+        a.carry_mz += (size_t)head * a.n_chunks;
+    }
     const FixupRows fr = fixup_find(a, lds, wave, lane);
     unsigned long long wide = fr.wide;
     auto finish = [&](float *dst, float acc, float iz) {
@@ -1307,10 +1344,11 @@ __global__ void k_stack_weights(const float *__restrict__ W, long long ldw, int 
 
 // Copy of X (n x f, row-major) into slice-major tiles of 32 columns, optionally scaled per row; the pad columns
 // up to the next multiple of 32 are written as zeros.  One thread per (row, 4 columns).
-__global__ void k_to_slices(const float *__restrict__ s, const float *__restrict__ X, long long ldx, long long n, int f,
+// d < f: heads of d columns (at most 32) that get a slice each
+__global__ void k_to_slices(const float *__restrict__ s, const float *__restrict__ X, long long ldx, long long n, int f, int d,
                             float *__restrict__ Y, int x_vec_ok, const float *__restrict__ mask, long long ldm, SideWork side) {
     if ((int)blockIdx.x < side.blocks) return side_block(side, (int)blockIdx.x);
-    const int fp4 = ((f + 31) & ~31) / 4;
+    const int fp4 = d < f ? f / d * 8 : ((f + 31) & ~31) / 4;
     const long long t = (long long)(blockIdx.x - side.blocks) * blockDim.x + threadIdx.x;
     if (t >= n * fp4) return;
     // consecutive threads walk the rows of one tile: reads are 16-byte pieces 8 to a row, writes are contiguous
@@ -1318,7 +1356,8 @@ __global__ void k_to_slices(const float *__restrict__ s, const float *__restrict
     const int tile = (int)(t / per_tile);
     const long long in_tile = t % per_tile;
     const long long i = in_tile >> 3;
-    const int q = tile * 32 + (int)(in_tile & 7) * 4;
+    const int q = (d < f ? tile * d : tile * 32) + (int)(in_tile & 7) * 4;
+    if (d < f) f = tile * d + d;   // where this slice's columns end
     const float sc = s ? s[i] : 1.f;
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
     const float *x = X + i * ldx + q;
@@ -2074,15 +2113,324 @@ __global__ __launch_bounds__(kBlock) void k_gat_dt(GatDtArgs a) {
     }
 }
 
-// dTheta[j, :] += ds_l[j] a_l + ds_r[j] a_r (ds_l counts only for j < n_l)
-__global__ void k_rank1_add(float *__restrict__ D, long long ldd, long long n, int f, const float *__restrict__ ds_l, long long n_l,
+// ---- backward of attention heads that are one slice wide (at most 32 columns), every head in one launch (blockIdx.y)
+//
+// Two walks and nothing stored per entry.  Over the rows of the pattern (k_gat_head_rows): logits and softmax statistics of the row, the dot
+// products dalpha_ij = <dP_i, Theta_j>, and from them rowdot_i = sum_j alpha_ij dalpha_ij and ds_l[i] = sum_j dt_ij.  Over the rows of the
+// transposed pattern (k_gat_head_cols): the coefficients again from the scores and the row's statistics, the dot product of the gathered row of
+// dP with the row's own Theta_j, dt_ij = alpha_ij (dalpha_ij - rowdot_i) LeakyReLU'(e_ij), and with them dTheta_j = sum_i alpha_ij dP_i and ds_r[j]
+// = sum_i dt_ij.  Before, dalpha was stored, and a pass over the rows left (alpha, dt) at its place in the transposed pattern for another two
+// passes over that: the scattered stores, and 24 bytes per entry and head written and read.
+//
+// ds_l needs rowdot, a sum over the same row, before it can weigh an entry.  With P and N the entries of the row with a positive logit and the
+// others, LeakyReLU' is 1 on P and `slope` on N, and since alpha sums to 1, sum_j alpha (dalpha - rowdot) = 0, so
+//   ds_l = (1 - slope) (A_P - rowdot Z_P) = -(1 - slope) (A_N - rowdot Z_N),   A = sum of alpha dalpha, Z = sum of alpha over the set:
+// four sums in one walk, and the set that weighs less is used (a row of one sign only gives exactly 0, as it should).
+struct GatHeadArgs {
+    NnzArgs n;                      // the pattern, or its transpose (k_gat_head_cols)
+    const float *theta, *dP;        // slice h belongs to head h: Theta over the sources, dP over the destinations, padded with zeros to 32 columns
+    const float *s_l, *s_r;         // per head, n_src floats apart
+    float4 *row;                    // per head, n_dst apart: (s_l, maximum, 1 / sum of exp, rowdot) of every destination
+    float *ds_l, *ds_r;             // per head, n_src apart
+    float *piece;                   // per head, chunk and kind (continued, open): (m, Z_P, Z_N, A_P, A_N) of a piece of a row that spans chunks, 8 floats
+    float *dtheta;                  // k_gat_head_cols: head h's columns start at h * d
+    float *carry, *ds_carry;        // per head and chunk: the piece of the continued row (32 floats; one float)
+    long long n_src, n_dst, ldd;
+    int d, store_vec_ok;
+    float slope;
+};
+
+struct HeadPiece { float m, zp, zn, ap, an; };
+__device__ __forceinline__ void merge_piece(HeadPiece &a, const HeadPiece &b) {
+    const float m = a.m > b.m ? a.m : b.m;
+    if (m == -INFINITY) { a.m = m; return; }   // neither has entries that weigh anything
+    const float ka = expf(a.m - m), kb = expf(b.m - m);
+    a.zp = a.zp * ka + b.zp * kb;
+    a.zn = a.zn * ka + b.zn * kb;
+    a.ap = a.ap * ka + b.ap * kb;
+    a.an = a.an * ka + b.an * kb;
+    a.m = m;
+}
+__device__ __forceinline__ void finish_head_row(const GatHeadArgs &a, int head, int i, const HeadPiece &p) {
+    const float z = p.zp + p.zn, iz = inv_z(z), rowdot = (p.ap + p.an) * iz;
+    a.row[head * a.n_dst + i] = make_float4(a.s_l[head * a.n_src + i], z == 0.f ? -INFINITY : p.m, iz, rowdot);
+    const float t = p.zn < p.zp ? rowdot * p.zn - p.an : p.ap - rowdot * p.zp;
+    a.ds_l[head * a.n_src + i] = (1.f - a.slope) * iz * t;
+}
+
+template <int PER>
+__global__ __launch_bounds__(kBlock) void k_gat_head_rows(GatHeadArgs a) {
+    __shared__ FlatLds<PER> lds;
+    __shared__ float s_max[kWavesPerBlock][64 * PER];
+    const int chunk = wave_chunk(), head = blockIdx.y, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, sub = lane & 3;
+    if (chunk >= a.n.n_chunks) return;
+    int *rows = lds.row[wave];
+    float *val = lds.val[wave], *top = s_max[wave];
+    const float *s_l = a.s_l + head * a.n_src, *s_r = a.s_r + head * a.n_src;
+    const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [&](int r0, bool none) { if (none) a.ds_l[head * a.n_src + r0 + lane] = 0.f; });
+    if (c.lo >= c.hi) return;
+    float es[PER], p[PER];
+    unsigned neg = 0u;   // bit q: entry q of this lane (blocked order) has a logit of 0 or below
+    {
+        const RowVals sl = row_vals<PER>(c, lane, s_l);
+        float mx[PER], e[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int k = c.lo + u * 64 + lane;
+            es[u] = s_r[a.n.col_idx[k < c.hi ? k : c.lo]];
+        }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) es[u] = leaky(row_val(sl, rows[u * 64 + lane]) + es[u], a.slope);
+        to_blocked<PER>(val, lane, es, e);
+        const int n_mine = c.hi - c.lo - lane * PER;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) if (q >= n_mine) e[q] = -INFINITY;
+        flat_piece_max<PER>(c, lane, e, mx);
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            mx[q] = fmaxf(mx[q], -FLT_MAX);   // entries of -inf weigh 0 also where a piece holds no others
+            p[q] = q < n_mine ? __expf(e[q] - mx[q]) : 0.f;
+            neg |= (e[q] > 0.f ? 0u : 1u) << q;
+            top[lane * PER + q] = mx[q];
+        }
+    }
+    lds_exchange();
+#pragma unroll
+    for (int u = 0; u < PER; ++u) val[u * 64 + lane] = 0.f;
+    const float *theta = a.theta + (size_t)head * a.n_src * 32 + sub * 4, *dP = a.dP + (size_t)head * a.n_dst * 32 + sub * 4;
+    flat_dots<PER>(c, rows, lane, a.n.col_idx, theta,
+                   [&](int i, float4 &x, float4 &y) {
+                       x = *reinterpret_cast<const float4 *>(dP + (size_t)i * 32);
+                       y = *reinterpret_cast<const float4 *>(dP + (size_t)i * 32 + 16);
+                   },
+                   [&](const float4 &x, const float4 &y, const float4 &b, const float4 &d) {
+                       return fmaf(b.x, x.x, fmaf(b.y, x.y, fmaf(b.z, x.z, fmaf(b.w, x.w, fmaf(d.x, y.x, fmaf(d.y, y.y, fmaf(d.z, y.z, d.w * y.w)))))));
+                   },
+                   [](int, int) { return 0; }, [&](int local, int, float total, int) { val[local] = total; });
+    lds_exchange();
+    float v[4][PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const float t = p[q] * val[lane * PER + q];
+        const bool n = (neg >> q) & 1u;
+        v[0][q] = n ? 0.f : p[q];
+        v[1][q] = n ? p[q] : 0.f;
+        v[2][q] = n ? 0.f : t;
+        v[3][q] = n ? t : 0.f;
+    }
+    const int last_row = __builtin_amdgcn_readfirstlane(__shfl(c.rid[PER - 1], 63, 64));
+    const bool open = __builtin_amdgcn_readfirstlane(a.n.row_ptr[last_row + 1]) > c.hi;
+    flat_sums<PER, 4>(c, lane, v, [&](int i, const float (&sum)[4], int end) {
+        const HeadPiece piece = {top[end], sum[0], sum[1], sum[2], sum[3]};
+        const bool cont = c.cont && i == c.i_first;
+        if (cont || (open && i == last_row)) {
+            float *dst = a.piece + (((size_t)head * a.n.n_chunks + chunk) * 2 + (cont ? 0 : 1)) * 8;
+            *reinterpret_cast<float4 *>(dst) = make_float4(piece.m, piece.zp, piece.zn, piece.ap);
+            dst[4] = piece.an;
+        } else {
+            finish_head_row(a, head, i, piece);
+        }
+    });
+}
+
+// merges the pieces of rows that span several chunks, in chunk order or (long rows) lane by lane and then over the lanes
+__global__ __launch_bounds__(kBlock) void k_gat_head_fixup(GatHeadArgs a) {
+    const int head = blockIdx.y, lane = threadIdx.x & 63;
+    auto load = [&](int chunk, int kind) {
+        const float *src = a.piece + (((size_t)head * a.n.n_chunks + chunk) * 2 + kind) * 8;
+        const float4 t = *reinterpret_cast<const float4 *>(src);
+        return HeadPiece{t.x, t.y, t.z, t.w, src[4]};
+    };
+    fixup_rows(a.n,
+               [&](int i, int c, int c_last) {
+                   HeadPiece p = load(c - 1, 1);
+                   for (int cc = c; cc <= c_last; ++cc) merge_piece(p, load(cc, 0));
+                   finish_head_row(a, head, i, p);
+               },
+               [&](int i, int c, int c_last) {
+                   HeadPiece p = {-INFINITY, 0.f, 0.f, 0.f, 0.f};
+                   for (int cc = c + lane; cc <= c_last; cc += 64) merge_piece(p, load(cc, 0));
+#pragma unroll
+                   for (int off = 1; off < 64; off <<= 1)
+                       merge_piece(p, HeadPiece{__shfl_xor(p.m, off, 64), __shfl_xor(p.zp, off, 64), __shfl_xor(p.zn, off, 64), __shfl_xor(p.ap, off, 64),
+                                                __shfl_xor(p.an, off, 64)});
+                   if (lane == 0) {
+                       HeadPiece q = load(c - 1, 1);
+                       merge_piece(q, p);
+                       finish_head_row(a, head, i, q);
+                   }
+               });
+}
+
+// The walk over the transposed pattern: k_spmm_flat's, with the own row's Theta gathered per entry while rows change (as in kSpmmSignSum) and
+// the dot product reduced over the eight lanes of a group by DPP moves.
+template <int PER>
+__global__ __launch_bounds__(kBlock) void k_gat_head_cols(GatHeadArgs a) {
+    constexpr int LPG = 8, G = 64 / LPG, T = 64 * PER, PART = T / G, PAD = 4, U = 4;
+    __shared__ __attribute__((aligned(16))) int s_col[kWavesPerBlock][T + G * PAD];
+    __shared__ __attribute__((aligned(16))) int s_row[kWavesPerBlock][T + G * PAD];
+    __shared__ __attribute__((aligned(16))) float s_alpha[kWavesPerBlock][T + G * PAD];   // negative: the logit is 0 or below
+    __shared__ __attribute__((aligned(16))) float s_dot[kWavesPerBlock][T + G * PAD];     // rowdot of the entry's destination
+    const int chunk = wave_chunk(), head = blockIdx.y, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane / LPG, li = lane % LPG;
+    if (chunk >= a.n.n_chunks) return;
+    int *rows = s_row[wave], *cols = s_col[wave];
+    float *alpha = s_alpha[wave], *rdot = s_dot[wave];
+    const float *theta = a.theta + (size_t)head * a.n_src * 32 + li * 4, *dP = a.dP + (size_t)head * a.n_dst * 32 + li * 4;
+    float *out = a.dtheta + (size_t)head * a.d + li * 4, *ds_out = a.ds_r + head * a.n_src;
+    int cont_row = -1;
+    auto write_row = [&](int row, float4 v, float ds) {
+        if (row == cont_row) {
+            *reinterpret_cast<float4 *>(a.carry + ((size_t)head * a.n.n_chunks + chunk) * 32 + li * 4) = v;
+            if (li == 0) a.ds_carry[(size_t)head * a.n.n_chunks + chunk] = ds;
+            return;
+        }
+        float *dst = out + (size_t)row * a.ldd;
+        if (a.store_vec_ok && li * 4 + 4 <= a.d) {
+            *reinterpret_cast<float4 *>(dst) = v;
+        } else {
+            if (li * 4 < a.d) dst[0] = v.x;
+            if (li * 4 + 1 < a.d) dst[1] = v.y;
+            if (li * 4 + 2 < a.d) dst[2] = v.z;
+            if (li * 4 + 3 < a.d) dst[3] = v.w;
+        }
+        if (li == 0) ds_out[row] = ds;
+    };
+    const FlatChunk<PER> c = flat_rows<PER, PAD, G>(a.n, chunk, lane, rows, [&](int r0, bool none) {
+        unsigned long long m = __ballot(none);
+        for (int b = 0; m; ++b, m >>= G) {   // rows without entries: one per group at a time
+            if (!((m >> g) & 1ull)) continue;
+            write_row(r0 + b * G + g, make_float4(0.f, 0.f, 0.f, 0.f), 0.f);
+        }
+    });
+    if (c.lo >= c.hi) return;
+    const int n = c.hi - c.lo;
+    if (c.cont) cont_row = c.i_first;
+    {   // the last entry of every row piece is flagged (sign bit of its row for now)
+        const int next_start = __shfl_down((int)(c.starts & 1u), 1, 64);
+        unsigned ends = (c.starts >> 1) | ((lane < 63 ? (unsigned)next_start : 0u) << (PER - 1));
+        const int e_last = n - 1 - lane * PER;
+        if (e_last >= 0 && e_last < PER) ends |= 1u << e_last;
+#pragma unroll
+        for (int e = 0; e < PER; ++e) rows[flat_at<PER, PAD, G>(lane * PER + e)] = (int)((unsigned)c.rid[e] | (((ends >> e) & 1u) << 31));
+    }
+    lds_exchange();
+    {
+        const RowVals sr = row_vals<PER>(c, lane, a.s_r + head * a.n_src);
+        int col[PER];
+        float4 st[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int k = c.lo + u * 64 + lane;
+            col[u] = a.n.col_idx[k < c.hi ? k : c.lo];
+        }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) st[u] = a.row[head * a.n_dst + col[u]];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int at = flat_at<PER, PAD, G>(u * 64 + lane), rw = rows[at];
+            cols[at] = (int)((unsigned)col[u] | ((unsigned)rw & 0x80000000u));
+            const float t = st[u].x + row_val(sr, rw & 0x7fffffff);
+            float w = __expf(leaky(t, a.slope) - st[u].y) * st[u].z;
+            if (c.lo + u * 64 + lane >= c.hi) w = 0.f;
+            alpha[at] = t > 0.f ? w : __uint_as_float(__float_as_uint(w) | 0x80000000u);
+            rdot[at] = st[u].w;
+        }
+    }
+    lds_exchange();
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), head_acc = acc, own = acc;
+    float ds = 0.f, head_ds = 0.f;
+    int head_at = -1, own_row = -1;
+    const int part0 = g * (PART + PAD);
+    for (int s = 0; s < PART && s < n; s += U) {
+        const int4 c4 = *reinterpret_cast<const int4 *>(&cols[part0 + s]), r4 = *reinterpret_cast<const int4 *>(&rows[part0 + s]);
+        const float4 w4 = *reinterpret_cast<const float4 *>(&alpha[part0 + s]), d4 = *reinterpret_cast<const float4 *>(&rdot[part0 + s]);
+        const int cf[U] = {c4.x, c4.y, c4.z, c4.w}, rf[U] = {r4.x, r4.y, r4.z, r4.w};
+        const float w[U] = {w4.x, w4.y, w4.z, w4.w}, rd[U] = {d4.x, d4.y, d4.z, d4.w};
+        float4 b[U], o[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) b[q] = *reinterpret_cast<const float4 *>(dP + (size_t)(cf[q] & 0x7fffffff) * 32);
+        if (__all((rf[U - 1] & 0x7fffffff) == own_row)) {   // (rows ascend) every group stays in its row
+#pragma unroll
+            for (int q = 0; q < U; ++q) o[q] = own;
+        } else {
+#pragma unroll
+            for (int q = 0; q < U; ++q) o[q] = *reinterpret_cast<const float4 *>(theta + (size_t)(rf[q] & 0x7fffffff) * 32);
+            own_row = rf[U - 1] & 0x7fffffff;
+            own = o[U - 1];
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            float x = fmaf(b[q].x, o[q].x, fmaf(b[q].y, o[q].y, fmaf(b[q].z, o[q].z, b[q].w * o[q].w)));
+            x += dpp_f32<0xB1>(x);    // lane ^ 1
+            x += dpp_f32<0x4E>(x);    // lane ^ 2
+            x += dpp_f32<0x141>(x);   // the other four of the eight (mirrored)
+            const float al = fabsf(w[q]);
+            ds = fmaf(__float_as_uint(w[q]) >> 31 ? a.slope * al : al, x - rd[q], ds);
+            acc.x = fmaf(al, b[q].x, acc.x); acc.y = fmaf(al, b[q].y, acc.y); acc.z = fmaf(al, b[q].z, acc.z); acc.w = fmaf(al, b[q].w, acc.w);
+            if (cf[q] < 0) {
+                if (head_at < 0) {
+                    head_acc = acc;
+                    head_ds = ds;
+                    head_at = part0 + s + q;
+                } else {
+                    write_row(rf[q] & 0x7fffffff, acc, ds);
+                }
+                acc = make_float4(0.f, 0.f, 0.f, 0.f);
+                ds = 0.f;
+            }
+        }
+    }
+    int f = head_at >= 0;
+#pragma unroll
+    for (int off = LPG; off < 64; off <<= 1) {
+        const float x = __shfl_up(acc.x, off, 64), y = __shfl_up(acc.y, off, 64), z = __shfl_up(acc.z, off, 64), w = __shfl_up(acc.w, off, 64);
+        const float t = __shfl_up(ds, off, 64);
+        const int of = __shfl_up(f, off, 64);
+        if (lane >= off) {
+            if (!f) { acc.x += x; acc.y += y; acc.z += z; acc.w += w; ds += t; }
+            f |= of;
+        }
+    }
+    acc = make_float4(__shfl_up(acc.x, LPG, 64), __shfl_up(acc.y, LPG, 64), __shfl_up(acc.z, LPG, 64), __shfl_up(acc.w, LPG, 64));
+    ds = __shfl_up(ds, LPG, 64);
+    if (head_at >= 0) {
+        if (g > 0) { head_acc.x += acc.x; head_acc.y += acc.y; head_acc.z += acc.z; head_acc.w += acc.w; head_ds += ds; }
+        write_row(rows[head_at] & 0x7fffffff, head_acc, head_ds);
+    }
+}
+
+// the rows of dTheta and ds_r that span several chunks, in chunk order or (long rows) eight pieces at a time: a wavefront takes 8 chunks' rows,
+// lanes over the columns (lane 32: ds_r)
+__global__ __launch_bounds__(kBlock) void k_gat_head_cols_fixup(GatHeadArgs a) {
+    const int head = blockIdx.y, lane = threadIdx.x & 63;
+    const int c0 = 1 + (blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6)) * 8;
+    int c_last = 0, i = -1;
+    if (lane < 8 && c0 + lane < a.n.n_chunks) i = continued_row(a.n, c0 + lane, c_last);
+    unsigned long long todo = __ballot(i >= 0);
+    const float *carry = a.carry + (size_t)head * a.n.n_chunks * 32, *ds_carry = a.ds_carry + (size_t)head * a.n.n_chunks;
+    while (todo) {
+        const int l = __ffsll((long long)todo) - 1;
+        todo &= todo - 1;
+        const int row = __builtin_amdgcn_readlane(i, l), first = c0 + l, last = __builtin_amdgcn_readlane(c_last, l);
+        float *dst = lane < a.d ? a.dtheta + (size_t)row * a.ldd + (size_t)head * a.d + lane : lane == 32 ? a.ds_r + head * a.n_src + row : nullptr;
+        if (!dst) continue;
+        float s = 0.f;
+#pragma unroll 8
+        for (int cc = first; cc <= last; ++cc) s += lane == 32 ? ds_carry[cc] : carry[(size_t)cc * 32 + lane];
+        *dst += s;
+    }
+}
+
+// dTheta[j, q] += ds_l[j] a_l[q] + ds_r[j] a_r[q] (ds_l counts only for j < n_l); with several heads of d columns, head q / d's vectors, n apart
+__global__ void k_rank1_add(float *__restrict__ D, long long ldd, long long n, int f, int d, const float *__restrict__ ds_l, long long n_l,
                             const float *__restrict__ ds_r, const float *__restrict__ a_l, const float *__restrict__ a_r) {
     const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n * f) return;
     const long long j = t / f;
     const int q = (int)(t % f);
-    const float l = j < n_l ? ds_l[j] : 0.f;
-    D[j * ldd + q] += l * a_l[q] + ds_r[j] * a_r[q];
+    const long long at = (d == f ? 0 : (q / d) * n) + j;
+    const float l = j < n_l ? ds_l[at] : 0.f;
+    D[j * ldd + q] += l * a_l[q] + ds_r[at] * a_r[q];
 }
 
 // D[i, m] = (accumulate ? D[i, m] : 0) + v[m] G[i, m]: a column scaling, on its own or added to what D holds (G may be D itself)
@@ -2107,9 +2455,11 @@ __global__ void k_set_f32(float *p, long long n, float v) {
 // slabs a 100,000 x 32 slice took 234 us at 55 GB/s; now 7 us (both kernels: 11).
 __global__ __launch_bounds__(256) void k_theta_t_vec(const float *__restrict__ theta, long long n, int f_pad, const float *__restrict__ v_l,
                                                      long long n_l, const float *__restrict__ v_r, int rows_per_slab,
-                                                     double *__restrict__ part) {
+                                                     double *__restrict__ part, long long head_stride) {
     __shared__ double red[2][4][32];   // per wavefront
     const int tile = blockIdx.x, slab = blockIdx.y;
+    v_l += tile * head_stride;   // heads of one slice: a pair of vectors per tile
+    v_r += tile * head_stride;
     const int q = threadIdx.x & 7, rr = threadIdx.x >> 3;
     const long long j_lo = (long long)slab * rows_per_slab;
     const long long j_hi = (j_lo + rows_per_slab < n) ? j_lo + rows_per_slab : n;
@@ -2143,10 +2493,12 @@ __global__ __launch_bounds__(256) void k_theta_t_vec(const float *__restrict__ t
 
 // adds the slabs: 16 columns a workgroup, the slabs dealt to 16 lanes each whose partial sums are added in lane order
 __global__ __launch_bounds__(256) void k_sum_slabs(const double *__restrict__ part, int slabs, int f_pad, int f, float *__restrict__ out_l,
-                                                   float *__restrict__ out_r) {
+                                                   float *__restrict__ out_r, int d) {
     __shared__ double red[2][16][16];
     const int c = threadIdx.x & 15, y = threadIdx.x >> 4;
     const int q = blockIdx.x * 16 + c;
+    const int out = d < f ? q / 32 * d + q % 32 : q;            // heads of d columns in slices of 32
+    const bool on = q < f && (d >= f || q % 32 < d);
     double l = 0.0, r = 0.0;
     if (q < f) {
 #pragma unroll 8
@@ -2158,11 +2510,11 @@ __global__ __launch_bounds__(256) void k_sum_slabs(const double *__restrict__ pa
     red[0][y][c] = l;
     red[1][y][c] = r;
     __syncthreads();
-    if (y > 1 || q >= f) return;
+    if (y > 1 || !on) return;
     double t = 0.0;
 #pragma unroll
     for (int u = 0; u < 16; ++u) t += red[y][u][c];
-    (y == 0 ? out_l : out_r)[q] = (float)t;
+    (y == 0 ? out_l : out_r)[out] = (float)t;
 }
 
 // pos[k] = index in the transposed pattern of the entry (i, j) stored at k: the place of i among the ascending
@@ -2332,10 +2684,14 @@ hipError_t launch_spmm(const sensei_csr &A, int mode, const float *r, const floa
     a.store_vec_ok = (ldc % sh.vec == 0) && (reinterpret_cast<uintptr_t>(C) % (4 * sh.vec) == 0);
     a.accumulate = accumulate ? 1 : 0; a.finalize = finalize ? 1 : 0;
     a.scale_weights = defer_fixup ? 0 : 1;   // deferred fix-up: the caller wants raw sums
-    a.s_l = nullptr; a.s_r = nullptr; a.slope = 0.f; a.mz_out = nullptr; a.carry_mz = nullptr;
+    a.s_l = nullptr; a.s_r = nullptr; a.slope = 0.f; a.mz_out = nullptr; a.carry_mz = nullptr; a.head_vec = 0; a.head_mz = 0;
     if (mode == kSpmmAttnFused) {
         if (!fused || accumulate || !finalize || defer_fixup) return hipErrorInvalidValue;
         a.s_l = fused->s_l; a.s_r = fused->s_r; a.slope = fused->slope; a.mz_out = fused->row_mz; a.carry_mz = fused->chunk_mz;
+        if (fused->heads > 1) {
+            if (!b_sliced || f != fused->heads * 32 || f_store != f) return hipErrorInvalidValue;
+            a.head_vec = A.n_cols; a.head_mz = A.n_rows + 1;
+        }
     }
     a.self = nullptr; a.self_tile = 0;
     if (mode == kSpmmSignSum || mode == kSpmmLreluSum) {
@@ -2373,7 +2729,7 @@ hipError_t launch_spmm(const sensei_csr &A, int mode, const float *r, const floa
     if (t1 && hipEventRecord(t1, s) != hipSuccess) return hipErrorUnknown;
     if (p.n_chunks > 1 && !(defer_fixup && b_sliced && !finalize)) {
         const unsigned fg = blocks_for(p.n_chunks - 1, kWavesPerBlock * kFixupChunks);
-        if (mode == kSpmmAttnFused) hipLaunchKernelGGL(k_spmm_fixup_attn, dim3(fg), dim3(kBlock), 0, s, a);
+        if (mode == kSpmmAttnFused) hipLaunchKernelGGL(k_spmm_fixup_attn, dim3(fg, a.head_vec ? sh.n_tiles : 1), dim3(kBlock), 0, s, a);
         else {
             a.fix_quads = p.n_chunks < 8192 ? 8 : 32;
             if (flat && a.scale_weights && mode != SENSEI_SPMM_PATTERN) { a.r = nullptr; a.mz = nullptr; }   // the pieces are scaled already
@@ -2445,12 +2801,13 @@ hipError_t launch_stack_weights(const float *W, int64_t ldw, int hops, int f_in,
 }
 
 hipError_t launch_to_slices(const float *s_vec, const float *X, int64_t ldx, int64_t n, int f, float *Y, hipStream_t s, const float *mask,
-                            int64_t ldm, SideWork *side) {
+                            int64_t ldm, SideWork *side, int n_heads) {
     if (n <= 0 || f <= 0) return launch_side(side, s);
     const SideWork sw = take_side(side);
-    const int x_vec_ok = (ldx % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0) ? 1 : 0;
-    const long long threads = n * (long long)(pad32(f) / 4);
-    hipLaunchKernelGGL(k_to_slices, dim3(blocks_for(threads, kBlock) + sw.blocks), dim3(kBlock), 0, s, s_vec, X, (long long)ldx, (long long)n, f, Y, x_vec_ok, mask, (long long)ldm, sw);
+    const int d = f / n_heads;
+    const int x_vec_ok = (ldx % 4 == 0 && (n_heads == 1 || d % 4 == 0) && reinterpret_cast<uintptr_t>(X) % 16 == 0) ? 1 : 0;
+    const long long threads = n * (long long)(n_heads > 1 ? n_heads * 8 : pad32(f) / 4);
+    hipLaunchKernelGGL(k_to_slices, dim3(blocks_for(threads, kBlock) + sw.blocks), dim3(kBlock), 0, s, s_vec, X, (long long)ldx, (long long)n, f, d, Y, x_vec_ok, mask, (long long)ldm, sw);
     return hipGetLastError();
 }
 
@@ -2561,10 +2918,10 @@ hipError_t launch_gat_dt(const sensei_csr &A, const float *logits, const float *
 }
 
 hipError_t launch_rank1_add(float *D, int64_t ldd, int64_t n, int f, const float *ds_l, int64_t n_l, const float *ds_r, const float *a_l,
-                            const float *a_r, hipStream_t s) {
+                            const float *a_r, hipStream_t s, int n_heads) {
     if (n <= 0 || f <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_rank1_add, dim3(blocks_for(n * f, kBlock)), dim3(kBlock), 0, s, D, (long long)ldd, (long long)n, f, ds_l, (long long)n_l,
-                       ds_r, a_l, a_r);
+    hipLaunchKernelGGL(k_rank1_add, dim3(blocks_for(n * f, kBlock)), dim3(kBlock), 0, s, D, (long long)ldd, (long long)n, f, f / n_heads, ds_l,
+                       (long long)n_l, ds_r, a_l, a_r);
     return hipGetLastError();
 }
 
@@ -2589,14 +2946,38 @@ static int theta_t_slabs(int64_t n) {   // at least 128 rows (four passes of a w
 size_t theta_t_vec_bytes(int64_t n, int f) { return align_up((size_t)theta_t_slabs(n) * 2 * (size_t)pad32(f) * sizeof(double), 256); }
 
 hipError_t launch_theta_t_vec(const float *theta_sliced, int64_t n, int f, const float *v_l, int64_t n_l, const float *v_r, float *out_l,
-                              float *out_r, double *part, hipStream_t s) {
+                              float *out_r, double *part, hipStream_t s, int n_heads) {
     if (f <= 0) return hipSuccess;
-    const int slabs = theta_t_slabs(n), f_pad = pad32(f);
+    const int d = f / n_heads, width = n_heads > 1 ? n_heads * 32 : f;   // several heads: one slice each
+    const int slabs = theta_t_slabs(n), f_pad = pad32(width);
     const int rows_per_slab = (int)((((n > 0 ? n : 1) + slabs - 1) / slabs + 31) / 32 * 32);
     hipLaunchKernelGGL(k_theta_t_vec, dim3((unsigned)(f_pad / 32), (unsigned)slabs), dim3(256), 0, s, theta_sliced, (long long)n, f_pad, v_l,
-                       (long long)n_l, v_r, rows_per_slab, part);
-    hipLaunchKernelGGL(k_sum_slabs, dim3(blocks_for(f, 16)), dim3(256), 0, s, part, slabs, f_pad, f, out_l, out_r);
+                       (long long)n_l, v_r, rows_per_slab, part, n_heads > 1 ? (long long)n : 0LL);
+    hipLaunchKernelGGL(k_sum_slabs, dim3(blocks_for(width, 16)), dim3(256), 0, s, part, slabs, f_pad, width, out_l, out_r, n_heads > 1 ? d : width);
     return hipGetLastError();
+}
+
+// The two walks of the heads' backward (see k_gat_head_rows); `row` is scratch, written by the first and read by the second.
+hipError_t launch_gat_heads_backward(const sensei_csr &A, const ChunkPlan &p, const sensei_csr &At, const ChunkPlan &pt, const GatHeadsBackward &b,
+                                     hipStream_t s) {
+    GatHeadArgs a;
+    a.n = nnz_args(A, p);
+    a.theta = b.theta; a.dP = b.dP; a.s_l = b.s_l; a.s_r = b.s_r; a.row = b.row; a.ds_l = b.ds_l; a.ds_r = b.ds_r; a.piece = b.piece;
+    a.dtheta = b.dtheta; a.carry = b.carry; a.ds_carry = b.ds_carry;
+    a.n_src = A.n_cols; a.n_dst = A.n_rows; a.ldd = b.ldd; a.d = b.d; a.slope = b.slope;
+    a.store_vec_ok = b.ldd % 4 == 0 && b.d % 4 == 0 && reinterpret_cast<uintptr_t>(b.dtheta) % 16 == 0;
+    const unsigned heads = (unsigned)b.heads;
+    hipError_t e = with_per(p.chunk_nnz, [&](auto per) {
+        hipLaunchKernelGGL(k_gat_head_rows<per()>, dim3(blocks_for(p.n_chunks, kWavesPerBlock), heads), dim3(kBlock), 0, s, a);
+        if (p.n_chunks > 1) hipLaunchKernelGGL(k_gat_head_fixup, dim3(blocks_for(p.n_chunks - 1, kBlock), heads), dim3(kBlock), 0, s, a);
+    });
+    if (e != hipSuccess) return e;
+    a.n = nnz_args(At, pt);
+    return with_per(pt.chunk_nnz, [&](auto per) {
+        hipLaunchKernelGGL(k_gat_head_cols<per()>, dim3(blocks_for(pt.n_chunks, kWavesPerBlock), heads), dim3(kBlock), 0, s, a);
+        if (pt.n_chunks > 1)
+            hipLaunchKernelGGL(k_gat_head_cols_fixup, dim3(blocks_for(pt.n_chunks - 1, kWavesPerBlock * 8), heads), dim3(kBlock), 0, s, a);
+    });
 }
 
 hipError_t launch_transpose_pos(const sensei_csr &A, const sensei_csr &At, const ChunkPlan &p, int32_t *pos, int32_t *miss, hipStream_t s) {
