@@ -1282,9 +1282,9 @@ int run_narrow_backward(const sensei_csr &A, const sensei_csr &At, const sensei_
         SENSEI_TRY(launch_to_slices(nullptr, dY.ptr + at, dY.ld, A.n_rows, hb * d, T, s, act == SENSEI_ACT_RELU ? Y + at : nullptr, ldy, nullptr, hb));
         GatHeadsBackward b;
         b.theta = theta; b.dP = T; b.s_l = s_l; b.s_r = s_r; b.row = row; b.ds_l = ds_l; b.ds_r = ds_r; b.piece = piece;
+        b.a_l = a_l + at; b.a_r = a_r + at;
         b.dtheta = dTheta + at; b.carry = carry; b.ds_carry = ds_carry; b.ldd = ldt; b.d = d; b.heads = hb; b.slope = slope;
         SENSEI_TRY(launch_gat_heads_backward(A, plan, At, plan_t, b, s));
-        SENSEI_TRY(launch_rank1_add(dTheta + at, ldt, A.n_cols, hb * d, ds_l, A.n_rows, ds_r, a_l + at, a_r + at, s, hb));
         SENSEI_TRY(launch_theta_t_vec(theta, A.n_cols, hb * d, ds_l, A.n_rows, ds_r, da_l + at, da_r + at, part_a, s, hb));
     }
     return SENSEI_OK;

@@ -1098,28 +1098,37 @@ __global__ __launch_bounds__(kThreads) void k_tiles_sddmm(const float *__restric
         }
 }
 
-// the projections of every head (blockIdx.y) of one slice: eight lanes a row
+// the projections of every head (blockIdx.y) of one slice: eight lanes a row, four rows of a lane in flight
+constexpr int kScoreRows = 4;
 __global__ __launch_bounds__(kThreads) void k_head_scores(const float *__restrict__ theta, long long n, int d, const float *__restrict__ a_l,
                                                           const float *__restrict__ a_r, float *__restrict__ s_l, float *__restrict__ s_r) {
     const int head = blockIdx.y, li = threadIdx.x & 7;
-    const long long row = (long long)blockIdx.x * (kThreads / 8) + threadIdx.x / 8, rc = row < n ? row : n - 1;
-    const float4 x = *reinterpret_cast<const float4 *>(theta + ((size_t)head * n + rc) * 32 + li * 4);
-    const float xe[4] = {x.x, x.y, x.z, x.w};
-    float l = 0.f, r = 0.f;
+    const long long row0 = (long long)blockIdx.x * (kThreads / 8 * kScoreRows) + threadIdx.x / 8;
+    float4 x[kScoreRows];
+#pragma unroll
+    for (int u = 0; u < kScoreRows; ++u) {
+        const long long row = row0 + u * (kThreads / 8), rc = row < n ? row : n - 1;
+        x[u] = *reinterpret_cast<const float4 *>(theta + ((size_t)head * n + rc) * 32 + li * 4);
+    }
+    float al[4], ar[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int q = li * 4 + e;
-        if (q < d) {
-            l = fmaf(xe[e], a_l[head * d + q], l);
-            r = fmaf(xe[e], a_r[head * d + q], r);
-        }
+        al[e] = q < d ? a_l[head * d + q] : 0.f;
+        ar[e] = q < d ? a_r[head * d + q] : 0.f;
     }
 #pragma unroll
-    for (int off = 4; off > 0; off >>= 1) {
-        l += __shfl_xor(l, off, 64);
-        r += __shfl_xor(r, off, 64);
+    for (int u = 0; u < kScoreRows; ++u) {
+        float l = fmaf(x[u].x, al[0], fmaf(x[u].y, al[1], fmaf(x[u].z, al[2], x[u].w * al[3])));
+        float r = fmaf(x[u].x, ar[0], fmaf(x[u].y, ar[1], fmaf(x[u].z, ar[2], x[u].w * ar[3])));
+#pragma unroll
+        for (int off = 4; off > 0; off >>= 1) {
+            l += __shfl_xor(l, off, 64);
+            r += __shfl_xor(r, off, 64);
+        }
+        const long long row = row0 + u * (kThreads / 8);
+        if (li == 0 && row < n) { s_l[head * n + row] = l; s_r[head * n + row] = r; }
     }
-    if (li == 0 && row < n) { s_l[head * n + row] = l; s_r[head * n + row] = r; }
 }
 
 __global__ void k_pad_heads(const float *__restrict__ W, long long ldw, int f_in, int heads, int d, float *__restrict__ out, long long ldo) {
@@ -1852,8 +1861,8 @@ hipError_t launch_tiles_combine_pm(const TileSplit &T, float *C, int64_t n_rows,
 
 hipError_t launch_head_scores(const float *theta, int64_t n, int heads, int d, const float *a_l, const float *a_r, float *s_l, float *s_r, hipStream_t s) {
     if (n <= 0 || heads <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_head_scores, dim3((unsigned)((n + kThreads / 8 - 1) / (kThreads / 8)), (unsigned)heads), dim3(kThreads), 0, s, theta, (long long)n,
-                       d, a_l, a_r, s_l, s_r);
+    hipLaunchKernelGGL(k_head_scores, dim3((unsigned)((n + kThreads / 8 * kScoreRows - 1) / (kThreads / 8 * kScoreRows)), (unsigned)heads), dim3(kThreads), 0,
+                       s, theta, (long long)n, d, a_l, a_r, s_l, s_r);
     return hipGetLastError();
 }
 

@@ -210,7 +210,7 @@ hipError_t launch_gat_dt(const sensei_csr &A, const float *logits, const float *
 hipError_t launch_score_v2(const sensei_csr &A, const float *theta_l, const float *theta_r, int f, const float *att_padded, float slope,
                            float *logits, const ChunkPlan &p, hipStream_t s);
 hipError_t launch_rank1_add(float *D, int64_t ldd, int64_t n, int f, const float *ds_l, int64_t n_l, const float *ds_r, const float *a_l,
-                            const float *a_r, hipStream_t s, int n_heads = 1);
+                            const float *a_r, hipStream_t s);
 // out_l = Theta^T v_l (v_l counted for the first n_l rows), out_r = Theta^T v_r; Theta slice-major n x pad32(f); sums in fp64
 // D[i, m] = (accumulate ? D[i, m] : 0) + v[m] G[i, m] over n rows and f columns (G may be D)
 hipError_t launch_scale_cols(float *D, int64_t ldd, const float *G, int64_t ldg, const float *v, int64_t n, int f, bool accumulate, hipStream_t s);
@@ -218,12 +218,13 @@ hipError_t launch_fill_f32(float *p, int64_t n, float v, hipStream_t s);
 size_t theta_t_vec_bytes(int64_t n, int f);
 hipError_t launch_theta_t_vec(const float *theta_sliced, int64_t n, int f, const float *v_l, int64_t n_l, const float *v_r, float *out_l,
                               float *out_r, double *part, hipStream_t s, int n_heads = 1);
-// n_heads > 1 (here and in launch_rank1_add): heads of f / n_heads columns, a pair of vectors each, n floats apart; Theta holds one slice a head
+// n_heads > 1: heads of f / n_heads columns, a pair of vectors each, n floats apart; Theta holds one slice a head
 // Backward of attention heads of d <= 32 columns, slice h of theta (n_cols rows) and dP (n_rows rows) being head h's: ds_l, ds_r (n_cols floats a head)
-// and dtheta (row-major, head h's columns from h * d on) without the rank-1 terms.  Scratch: row n_rows float4 a head, piece 16 floats a head and chunk
+// and dtheta (row-major, head h's columns from h * d on).  Scratch: row n_rows float4 a head, piece 16 floats a head and chunk
 // of A, carry 32 floats and ds_carry one a head and chunk of At.
 struct GatHeadsBackward {
     const float *theta, *dP, *s_l, *s_r;   // s_l, s_r: n_cols floats a head
+    const float *a_l, *a_r;                // d floats a head
     float4 *row;
     float *ds_l, *ds_r, *piece, *dtheta, *carry, *ds_carry;
     int64_t ldd;

@@ -2118,8 +2118,8 @@ __global__ __launch_bounds__(kBlock) void k_gat_dt(GatDtArgs a) {
 // Two walks and nothing stored per entry.  Over the rows of the pattern (k_gat_head_rows): logits and softmax statistics of the row, the dot
 // products dalpha_ij = <dP_i, Theta_j>, and from them rowdot_i = sum_j alpha_ij dalpha_ij and ds_l[i] = sum_j dt_ij.  Over the rows of the
 // transposed pattern (k_gat_head_cols): the coefficients again from the scores and the row's statistics, the dot product of the gathered row of
-// dP with the row's own Theta_j, dt_ij = alpha_ij (dalpha_ij - rowdot_i) LeakyReLU'(e_ij), and with them dTheta_j = sum_i alpha_ij dP_i and ds_r[j]
-// = sum_i dt_ij.  Before, dalpha was stored, and a pass over the rows left (alpha, dt) at its place in the transposed pattern for another two
+// dP with the row's own Theta_j, dt_ij = alpha_ij (dalpha_ij - rowdot_i) LeakyReLU'(e_ij), and with them ds_r[j] = sum_i dt_ij and dTheta_j =
+// sum_i alpha_ij dP_i + ds_l[j] a_l + ds_r[j] a_r.  Before, dalpha was stored, and a pass over the rows left (alpha, dt) at its place in the transposed pattern for another two
 // passes over that: the scattered stores, and 24 bytes per entry and head written and read.
 //
 // ds_l needs rowdot, a sum over the same row, before it can weigh an entry.  With P and N the entries of the row with a positive logit and the
@@ -2131,6 +2131,7 @@ struct GatHeadArgs {
     const float *theta, *dP;        // slice h belongs to head h: Theta over the sources, dP over the destinations, padded with zeros to 32 columns
     const float *s_l, *s_r;         // per head, n_src floats apart
     float4 *row;                    // per head, n_dst apart: (s_l, maximum, 1 / sum of exp, rowdot) of every destination
+    const float *a_l, *a_r;         // d floats a head
     float *ds_l, *ds_r;             // per head, n_src apart
     float *piece;                   // per head, chunk and kind (continued, open): (m, Z_P, Z_N, A_P, A_N) of a piece of a row that spans chunks, 8 floats
     float *dtheta;                  // k_gat_head_cols: head h's columns start at h * d
@@ -2277,8 +2278,22 @@ __global__ __launch_bounds__(kBlock) void k_gat_head_cols(GatHeadArgs a) {
     float *alpha = s_alpha[wave], *rdot = s_dot[wave];
     const float *theta = a.theta + (size_t)head * a.n_src * 32 + li * 4, *dP = a.dP + (size_t)head * a.n_dst * 32 + li * 4;
     float *out = a.dtheta + (size_t)head * a.d + li * 4, *ds_out = a.ds_r + head * a.n_src;
+    float4 al = make_float4(0.f, 0.f, 0.f, 0.f), ar = al;   // this lane's columns of the attention vectors
+    {
+        const float *pl = a.a_l + head * a.d, *pr = a.a_r + head * a.d;
+        const int q = li * 4;
+        if (q < a.d) { al.x = pl[q]; ar.x = pr[q]; }
+        if (q + 1 < a.d) { al.y = pl[q + 1]; ar.y = pr[q + 1]; }
+        if (q + 2 < a.d) { al.z = pl[q + 2]; ar.z = pr[q + 2]; }
+        if (q + 3 < a.d) { al.w = pl[q + 3]; ar.w = pr[q + 3]; }
+    }
+    const float *ds_l = a.ds_l + head * a.n_src;
+    auto own_ds = [&](int row) { return row < a.n_dst ? ds_l[row] : 0.f; };   // sources that are no destination have none
     int cont_row = -1;
-    auto write_row = [&](int row, float4 v, float ds) {
+    // the rank-1 terms ds_l a_l + ds_r a_r: every piece of a row adds its share of ds_r, the first one ds_l
+    auto write_row = [&](int row, float4 v, float ds, float dl) {
+        v.x = fmaf(ds, ar.x, v.x); v.y = fmaf(ds, ar.y, v.y); v.z = fmaf(ds, ar.z, v.z); v.w = fmaf(ds, ar.w, v.w);
+        if (row != cont_row) { v.x = fmaf(dl, al.x, v.x); v.y = fmaf(dl, al.y, v.y); v.z = fmaf(dl, al.z, v.z); v.w = fmaf(dl, al.w, v.w); }
         if (row == cont_row) {
             *reinterpret_cast<float4 *>(a.carry + ((size_t)head * a.n.n_chunks + chunk) * 32 + li * 4) = v;
             if (li == 0) a.ds_carry[(size_t)head * a.n.n_chunks + chunk] = ds;
@@ -2299,7 +2314,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_head_cols(GatHeadArgs a) {
         unsigned long long m = __ballot(none);
         for (int b = 0; m; ++b, m >>= G) {   // rows without entries: one per group at a time
             if (!((m >> g) & 1ull)) continue;
-            write_row(r0 + b * G + g, make_float4(0.f, 0.f, 0.f, 0.f), 0.f);
+            write_row(r0 + b * G + g, make_float4(0.f, 0.f, 0.f, 0.f), 0.f, own_ds(r0 + b * G + g));
         }
     });
     if (c.lo >= c.hi) return;
@@ -2338,7 +2353,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_head_cols(GatHeadArgs a) {
     }
     lds_exchange();
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), head_acc = acc, own = acc;
-    float ds = 0.f, head_ds = 0.f;
+    float ds = 0.f, head_ds = 0.f, head_dl = 0.f, own_dl = 0.f;
     int head_at = -1, own_row = -1;
     const int part0 = g * (PART + PAD);
     for (int s = 0; s < PART && s < n; s += U) {
@@ -2347,16 +2362,21 @@ __global__ __launch_bounds__(kBlock) void k_gat_head_cols(GatHeadArgs a) {
         const int cf[U] = {c4.x, c4.y, c4.z, c4.w}, rf[U] = {r4.x, r4.y, r4.z, r4.w};
         const float w[U] = {w4.x, w4.y, w4.z, w4.w}, rd[U] = {d4.x, d4.y, d4.z, d4.w};
         float4 b[U], o[U];
+        float dl[U];
 #pragma unroll
         for (int q = 0; q < U; ++q) b[q] = *reinterpret_cast<const float4 *>(dP + (size_t)(cf[q] & 0x7fffffff) * 32);
         if (__all((rf[U - 1] & 0x7fffffff) == own_row)) {   // (rows ascend) every group stays in its row
 #pragma unroll
-            for (int q = 0; q < U; ++q) o[q] = own;
+            for (int q = 0; q < U; ++q) { o[q] = own; dl[q] = own_dl; }
         } else {
 #pragma unroll
-            for (int q = 0; q < U; ++q) o[q] = *reinterpret_cast<const float4 *>(theta + (size_t)(rf[q] & 0x7fffffff) * 32);
+            for (int q = 0; q < U; ++q) {
+                o[q] = *reinterpret_cast<const float4 *>(theta + (size_t)(rf[q] & 0x7fffffff) * 32);
+                dl[q] = own_ds(rf[q] & 0x7fffffff);
+            }
             own_row = rf[U - 1] & 0x7fffffff;
             own = o[U - 1];
+            own_dl = dl[U - 1];
         }
 #pragma unroll
         for (int q = 0; q < U; ++q) {
@@ -2371,9 +2391,10 @@ __global__ __launch_bounds__(kBlock) void k_gat_head_cols(GatHeadArgs a) {
                 if (head_at < 0) {
                     head_acc = acc;
                     head_ds = ds;
+                    head_dl = dl[q];
                     head_at = part0 + s + q;
                 } else {
-                    write_row(rf[q] & 0x7fffffff, acc, ds);
+                    write_row(rf[q] & 0x7fffffff, acc, ds, dl[q]);
                 }
                 acc = make_float4(0.f, 0.f, 0.f, 0.f);
                 ds = 0.f;
@@ -2395,7 +2416,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_head_cols(GatHeadArgs a) {
     ds = __shfl_up(ds, LPG, 64);
     if (head_at >= 0) {
         if (g > 0) { head_acc.x += acc.x; head_acc.y += acc.y; head_acc.z += acc.z; head_acc.w += acc.w; head_ds += ds; }
-        write_row(rows[head_at] & 0x7fffffff, head_acc, head_ds);
+        write_row(rows[head_at] & 0x7fffffff, head_acc, head_ds, head_dl);
     }
 }
 
@@ -2421,16 +2442,15 @@ __global__ __launch_bounds__(kBlock) void k_gat_head_cols_fixup(GatHeadArgs a) {
     }
 }
 
-// dTheta[j, q] += ds_l[j] a_l[q] + ds_r[j] a_r[q] (ds_l counts only for j < n_l); with several heads of d columns, head q / d's vectors, n apart
-__global__ void k_rank1_add(float *__restrict__ D, long long ldd, long long n, int f, int d, const float *__restrict__ ds_l, long long n_l,
+// dTheta[j, :] += ds_l[j] a_l + ds_r[j] a_r (ds_l counts only for j < n_l)
+__global__ void k_rank1_add(float *__restrict__ D, long long ldd, long long n, int f, const float *__restrict__ ds_l, long long n_l,
                             const float *__restrict__ ds_r, const float *__restrict__ a_l, const float *__restrict__ a_r) {
     const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n * f) return;
     const long long j = t / f;
     const int q = (int)(t % f);
-    const long long at = (d == f ? 0 : (q / d) * n) + j;
-    const float l = j < n_l ? ds_l[at] : 0.f;
-    D[j * ldd + q] += l * a_l[q] + ds_r[at] * a_r[q];
+    const float l = j < n_l ? ds_l[j] : 0.f;
+    D[j * ldd + q] += l * a_l[q] + ds_r[j] * a_r[q];
 }
 
 // D[i, m] = (accumulate ? D[i, m] : 0) + v[m] G[i, m]: a column scaling, on its own or added to what D holds (G may be D itself)
@@ -2918,10 +2938,10 @@ hipError_t launch_gat_dt(const sensei_csr &A, const float *logits, const float *
 }
 
 hipError_t launch_rank1_add(float *D, int64_t ldd, int64_t n, int f, const float *ds_l, int64_t n_l, const float *ds_r, const float *a_l,
-                            const float *a_r, hipStream_t s, int n_heads) {
+                            const float *a_r, hipStream_t s) {
     if (n <= 0 || f <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_rank1_add, dim3(blocks_for(n * f, kBlock)), dim3(kBlock), 0, s, D, (long long)ldd, (long long)n, f, f / n_heads, ds_l,
-                       (long long)n_l, ds_r, a_l, a_r);
+    hipLaunchKernelGGL(k_rank1_add, dim3(blocks_for(n * f, kBlock)), dim3(kBlock), 0, s, D, (long long)ldd, (long long)n, f, ds_l, (long long)n_l,
+                       ds_r, a_l, a_r);
     return hipGetLastError();
 }
 
@@ -2963,6 +2983,7 @@ hipError_t launch_gat_heads_backward(const sensei_csr &A, const ChunkPlan &p, co
     GatHeadArgs a;
     a.n = nnz_args(A, p);
     a.theta = b.theta; a.dP = b.dP; a.s_l = b.s_l; a.s_r = b.s_r; a.row = b.row; a.ds_l = b.ds_l; a.ds_r = b.ds_r; a.piece = b.piece;
+    a.a_l = b.a_l; a.a_r = b.a_r;
     a.dtheta = b.dtheta; a.carry = b.carry; a.ds_carry = b.ds_carry;
     a.n_src = A.n_cols; a.n_dst = A.n_rows; a.ldd = b.ldd; a.d = b.d; a.slope = b.slope;
     a.store_vec_ok = b.ldd % 4 == 0 && b.d % 4 == 0 && reinterpret_cast<uintptr_t>(b.dtheta) % 16 == 0;
