@@ -164,6 +164,13 @@ int fused_heads_max(int f_out, int id) {
     return heads < kHeadsPerLaunch ? heads : kHeadsPerLaunch;
 }
 
+// scratch of the statistics pass over a column-panel copy (launch_panel_stats)
+size_t panel_stats_pairs(const sensei_panels &P) {
+    size_t chunks = 0;
+    for (int q = 0; q < P.n_panels; ++q) chunks += (size_t)P.n_chunks_q[q];
+    return (size_t)P.n_panels * P.n_rows + chunks;
+}
+
 size_t gat_ws(const sensei_csr &A, int f_in, int f_out, int id) {
     const int fo = pad32(f_out), fi = pad4(f_in);
     size_t b = plan_bytes(A.nnz) + softmax_ws_bytes(A);
@@ -177,6 +184,7 @@ size_t gat_ws(const sensei_csr &A, int f_in, int f_out, int id) {
     b += align_up((size_t)(A.nnz > 0 ? A.nnz : 1) * sizeof(float), 256);       // attention logits
     b += 2 * align_up((size_t)fi * sizeof(float), 256);                        // W.a_l, W.a_r
     if (id != SENSEI_GAT_RECOMP_FOLD) b += align_up((size_t)A.n_cols * fo * sizeof(float), 256);  // Theta
+    if (A.panels) b += align_up(panel_stats_pairs(*A.panels) * sizeof(float2), 256);
     if (gat_is_reuse(id)) {
         b += spmm_carry_bytes(A.nnz, fo);
     } else {
@@ -787,6 +795,7 @@ int run_gat(const sensei_csr &A, const sensei_mat &X, const sensei_mat &W, const
         }
         return SENSEI_OK;
     }
+    float2 *panel_pairs = by_panel ? cv.take<float2>(panel_stats_pairs(*A.panels)) : nullptr;
     for (int h = 0; h < n_heads; ++h) {
         const float *al = a_l + (size_t)h * d, *ar = a_r + (size_t)h * d;
         const float *theta_h = !theta ? nullptr : theta_sliced ? theta + (size_t)h * (d / 32) * (size_t)A.n_cols * 32 : theta + (size_t)h * d;
@@ -821,6 +830,16 @@ int run_gat(const sensei_csr &A, const sensei_mat &X, const sensei_mat &W, const
                                               carry_stats, s));
             SENSEI_TRY(hipStreamWaitEvent(s, D.ev_join, 0));
             SENSEI_TRY(launch_tile_stats_merge(D.T, stats, A.n_rows, s));
+        } else if (by_panel && panel_stats_usable(A.panels->width, A.panels->chunk_nnz)) {
+            const sensei_panels &P = *A.panels;
+            PanelWalk walk[SENSEI_MAX_PANELS];
+            for (int q = 0; q < P.n_panels; ++q) {
+                walk[q].A = A;
+                walk[q].A.nnz = P.nnz_q[q]; walk[q].A.row_ptr = P.row_ptr_q[q]; walk[q].A.col_idx = P.col_q[q]; walk[q].A.val = logits + P.off_q[q];
+                walk[q].plan.chunk_nnz = P.chunk_nnz; walk[q].plan.n_chunks = P.n_chunks_q[q]; walk[q].plan.chunk_row = P.chunk_row_q[q];
+            }
+            SENSEI_TRY(launch_panel_stats(walk, P.n_panels, P.width, A.n_rows, A.n_cols, s_l, s_r, slope, panel_pairs, panel_pairs + (size_t)P.n_panels * A.n_rows,
+                                          stats, s));
         } else if (!fused) {
             SENSEI_TRY(launch_attention_stats(A, s_l, s_r, slope, logits, by_panel ? A.panels->position : nullptr, plan, stats, carry_stats, s));
         }

@@ -187,6 +187,12 @@ hipError_t launch_softmax(const sensei_csr &A, const float *e, float *alpha, con
 hipError_t launch_attention_stats(const sensei_csr &A, const float *s_l, const float *s_r, float slope, float *logits,
                                   const int32_t *dst_index, const ChunkPlan &p, float2 *stats, float2 *carry_stats, hipStream_t s);
 size_t softmax_ws_bytes(const sensei_csr &A);
+// The same over a column-panel copy: logits of panel q to its A.val (the copy's order); seg_stats: n_rows pairs a panel, seg_carry: a pair per chunk
+// of all panels (scratch).  For panels of a width whose share of s_r fits LDS and chunks of 512 entries.
+struct PanelWalk { sensei_csr A; ChunkPlan plan; };
+bool panel_stats_usable(int width, int chunk_nnz);
+hipError_t launch_panel_stats(const PanelWalk *panels, int n_panels, int width, int n_rows, int n_cols, const float *s_l, const float *s_r, float slope,
+                              float2 *seg_stats, float2 *seg_carry, float2 *stats, hipStream_t s);
 
 // ---- backward of the attention layer
 // out[i] = sum of val[k * stride] over the entries k of row i; carry: n_chunks floats

@@ -1402,12 +1402,8 @@ struct SoftmaxArgs {
 
 // Row statistics of the logits (read, or formed from the two score vectors and stored on the way): a flat walk whose segmented
 // reduction merges (max, sum) pairs.
-template <bool FROM_E, int PER>
-__global__ __launch_bounds__(kBlock) void k_softmax_stats(SoftmaxArgs a) {
-    __shared__ FlatLds<PER> lds;
-    const int chunk = wave_chunk(), lane = threadIdx.x & 63;
-    if (chunk >= a.n.n_chunks) return;
-    int *rows = lds.row[threadIdx.x >> 6];
+template <bool FROM_E, int PER, class SrOf>
+__device__ __forceinline__ void softmax_stats_chunk(const SoftmaxArgs &a, int chunk, int lane, int *rows, float *val, SrOf s_r_of) {
     const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [&](int r0, bool none) { if (none) a.stats[r0 + lane] = make_float2(-INFINITY, 0.f); });
     if (c.lo >= c.hi) return;
     float es[PER], e[PER];
@@ -1428,7 +1424,7 @@ __global__ __launch_bounds__(kBlock) void k_softmax_stats(SoftmaxArgs a) {
         const RowVals sl = row_vals<PER>(c, lane, a.s_l);
         float sr[PER];
 #pragma unroll
-        for (int u = 0; u < PER; ++u) sr[u] = a.s_r[col[u]];
+        for (int u = 0; u < PER; ++u) sr[u] = s_r_of(col[u]);
 #pragma unroll
         for (int u = 0; u < PER; ++u) es[u] = row_val(sl, rows[u * 64 + lane]);
 #pragma unroll
@@ -1437,7 +1433,7 @@ __global__ __launch_bounds__(kBlock) void k_softmax_stats(SoftmaxArgs a) {
             if (c.lo + u * 64 + lane < c.hi && dst[u] >= 0) a.logits[dst[u]] = es[u];   // kept for the second pass (negative: the entry lies in a dense tile)
         }
     }
-    to_blocked<PER>(lds.val[threadIdx.x >> 6], lane, es, e);
+    to_blocked<PER>(val, lane, es, e);
     // head, whole rows and tail of this lane as in flat_sum, with (max, sum of exp) pairs: the maximum over the part of a row that
     // lies in this lane first (forwards, then handed back), then one exp per entry
     const int n_mine = c.hi - c.lo - lane * PER;   // entries of this lane inside the chunk (may be more than PER, or negative)
@@ -1486,6 +1482,61 @@ __global__ __launch_bounds__(kBlock) void k_softmax_stats(SoftmaxArgs a) {
         write(head_row, hm, hz);
     }
     if (lane == 63) write(c.rid[PER - 1], m, z);
+}
+
+template <bool FROM_E, int PER>
+__global__ __launch_bounds__(kBlock) void k_softmax_stats(SoftmaxArgs a) {
+    __shared__ FlatLds<PER> lds;
+    const int chunk = wave_chunk(), wave = threadIdx.x >> 6;
+    if (chunk >= a.n.n_chunks) return;
+    softmax_stats_chunk<FROM_E, PER>(a, chunk, threadIdx.x & 63, lds.row[wave], lds.val[wave], [&](int col) { return a.s_r[col]; });
+}
+
+// The same over a column-panel copy of the pattern, the logits left in the copy's order.  Over the pattern itself the pass is bound by its 4-byte
+// gathers of s_r, which move a 128-byte line from L2 each (100 M entries on 98,000 columns: 12.8 GB, 490 us) and by the places of the entries in
+// the copy, read and scattered to.  A panel's share of s_r fits LDS: a workgroup of 16 wavefronts fills it once (up to kPanelStatsCols floats) and
+// walks its share of the panel's chunks, one workgroup a compute unit.  A row's statistics come in one pair per panel and chunk and are put
+// together by k_panel_stats_join: 490 -> 340 us in all (then bound by the instructions of the segmented scans: fetching the next chunk ahead gains nothing).
+constexpr int kPanelStatsWaves = 16, kPanelStatsCols = 20480;
+struct PanelStatsArgs {
+    SoftmaxArgs s[kMaxPanels];   // stats, carry: the panel's own
+    int n_panels, per_panel, width, n_cols;
+};
+template <int PER>
+__global__ __launch_bounds__(64 * kPanelStatsWaves) void k_panel_stats(PanelStatsArgs a) {
+    extern __shared__ __attribute__((aligned(16))) float panel_lds[];
+    const int q = blockIdx.x / a.per_panel, part = blockIdx.x % a.per_panel, wave = threadIdx.x >> 6;
+    const SoftmaxArgs &s = a.s[q];
+    int *rows = reinterpret_cast<int *>(panel_lds) + wave * (128 * PER);
+    float *val = panel_lds + wave * (128 * PER) + 64 * PER, *sr = panel_lds + kPanelStatsWaves * (128 * PER);
+    const int col0 = q * a.width, cols = a.n_cols - col0 < a.width ? a.n_cols - col0 : a.width;
+    for (int j = threadIdx.x; j < cols; j += 64 * kPanelStatsWaves) sr[j] = s.s_r[col0 + j];
+    __syncthreads();
+    const int c0 = (int)((long long)s.n.n_chunks * part / a.per_panel), c1 = (int)((long long)s.n.n_chunks * (part + 1) / a.per_panel);
+    for (int chunk = c0 + wave; chunk < c1; chunk += kPanelStatsWaves) {
+        softmax_stats_chunk<false, PER>(s, chunk, threadIdx.x & 63, rows, val, [&](int col) { return sr[col - col0]; });
+        lds_exchange();   // the next chunk writes where this one read
+    }
+}
+
+// stats[i] = the pairs of row i over all panels and the chunks it goes on in, in that order
+__global__ void k_panel_stats_join(PanelStatsArgs a, float2 *__restrict__ stats, int n_rows) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n_rows) return;
+    float m = -INFINITY, z = 0.f;
+    for (int q = 0; q < a.n_panels; ++q) {
+        const SoftmaxArgs &s = a.s[q];
+        const int rs = s.n.row_ptr[i], re = s.n.row_ptr[i + 1];
+        const float2 own = s.stats[i];
+        mz_merge(m, z, own.x, own.y);
+        if (re <= rs) continue;
+#pragma unroll 4
+        for (int c = rs / s.n.chunk_nnz + 1; c <= (re - 1) / s.n.chunk_nnz; ++c) {
+            const float2 p = s.carry[c];
+            mz_merge(m, z, p.x, p.y);
+        }
+    }
+    stats[i] = make_float2(m, z);
 }
 
 // merges the carried (m, z) pieces of rows that span several chunks, in chunk order or (long rows) lane by lane and then over the lanes
@@ -2862,6 +2913,31 @@ hipError_t launch_attention_stats(const sensei_csr &A, const float *s_l, const f
     });
 }
 
+
+bool panel_stats_usable(int width, int chunk_nnz) { return width <= kPanelStatsCols && chunk_nnz == 512; }
+
+hipError_t launch_panel_stats(const PanelWalk *panels, int n_panels, int width, int n_rows, int n_cols, const float *s_l, const float *s_r, float slope,
+                              float2 *seg_stats, float2 *seg_carry, float2 *stats, hipStream_t s) {
+    PanelStatsArgs a;
+    a.n_panels = n_panels; a.width = width; a.n_cols = n_cols;
+    a.per_panel = 256 / n_panels;   // one workgroup a compute unit
+    int chunk_nnz = 0;
+    for (int q = 0; q < n_panels; ++q) {
+        SoftmaxArgs &p = a.s[q];
+        p.n = nnz_args(panels[q].A, panels[q].plan);
+        p.e = nullptr; p.s_l = s_l; p.s_r = s_r; p.slope = slope; p.alpha = nullptr; p.dst_index = nullptr;
+        p.logits = const_cast<float *>(panels[q].A.val);
+        p.stats = seg_stats + (size_t)q * n_rows;
+        p.carry = seg_carry;
+        seg_carry += panels[q].plan.n_chunks;
+        chunk_nnz = panels[q].plan.chunk_nnz;
+    }
+    if (chunk_nnz != 512 || width > kPanelStatsCols) return hipErrorInvalidValue;
+    const size_t lds = (size_t)kPanelStatsWaves * 1024 * sizeof(float) + (size_t)width * sizeof(float);
+    hipLaunchKernelGGL(k_panel_stats<8>, dim3((unsigned)(a.per_panel * n_panels)), dim3(64 * kPanelStatsWaves), lds, s, a);
+    if (n_rows > 0) hipLaunchKernelGGL(k_panel_stats_join, dim3(blocks_for(n_rows, kBlock)), dim3(kBlock), 0, s, a, stats, n_rows);
+    return hipGetLastError();
+}
 
 // ------------------------------------------------------------ backward of the attention layer (host side)
 
