@@ -120,6 +120,15 @@ template <int PER> struct FlatChunk {
     int prev_row;           // row of the entry before this lane's first one
 };
 
+// The entries of a chunk, which depend on its number alone: what a kernel loads per entry is issued before flat_rows, whose row pointers are
+// two dependent round trips.
+template <int PER> struct ChunkSpan {
+    int lo, hi;
+    __device__ __forceinline__ ChunkSpan(const NnzArgs &a, int chunk) : lo(chunk * (64 * PER)), hi(a.nnz - lo > 64 * PER ? lo + 64 * PER : a.nnz) {}
+    // place of the lane's u-th entry in striped order; past the end of the chunk, its first (last of the pattern if it has none)
+    __device__ __forceinline__ int at(int u, int lane) const { const int k = lo + u * 64 + lane; return k < hi ? k : lo < hi ? lo : hi - 1; }
+};
+
 // empty(r0, none) is called for every 64 rows of the chunk, by all lanes: `none` says that row r0 + lane is owned and has no entries
 template <int PER, int PAD = 0, int PARTS = 8, class Empty>
 __device__ __forceinline__ FlatChunk<PER> flat_rows(const NnzArgs &a, int chunk, int lane, int *rows, Empty empty) {
@@ -128,16 +137,23 @@ __device__ __forceinline__ FlatChunk<PER> flat_rows(const NnzArgs &a, int chunk,
     c.hi = (a.nnz - c.lo > 64 * PER) ? c.lo + 64 * PER : a.nnz;
     const int i0 = __builtin_amdgcn_readfirstlane(a.chunk_row[chunk]);
     c.i1 = __builtin_amdgcn_readfirstlane(a.chunk_row[chunk + 1]);
-    c.cont = (a.nnz > 0) && (__builtin_amdgcn_readfirstlane(a.row_ptr[i0]) > c.lo);
-    c.i_first = c.cont ? i0 - 1 : i0;
+    // rows from i0 - 1 on, the one that may go on from the chunk before: whether it does is in the first lane's own row pointers
+    const int r_first = i0 > 0 ? i0 - 1 : 0;
+    int s = 0, e = 0;
+    if (r_first + lane < c.i1 || lane == 0) {
+        const int r = r_first + lane;
+        if (r < a.n_rows) { s = a.row_ptr[r]; e = a.row_ptr[r + 1]; }
+    }
 #pragma unroll
     for (int u = 0; u < PER; ++u) rows[flat_at<PER, PAD, PARTS>(u * 64 + lane)] = -1;
     lds_exchange();
-    for (int r0 = c.i_first; r0 < c.i1; r0 += 64) {
+    c.cont = i0 > 0 && __builtin_amdgcn_readfirstlane(e) > c.lo && a.nnz > 0;
+    c.i_first = c.cont ? i0 - 1 : i0;
+    for (int r0 = r_first; r0 < c.i1; r0 += 64) {
         const int r = r0 + lane;
         bool none = false;
-        if (r < c.i1) {
-            const int s = a.row_ptr[r], e = a.row_ptr[r + 1];
+        if (r0 != r_first && r < c.i1) { s = a.row_ptr[r]; e = a.row_ptr[r + 1]; }
+        if (r < c.i1 && r >= c.i_first) {
             none = e <= s;
             if (!none) rows[flat_at<PER, PAD, PARTS>(s > c.lo ? s - c.lo : 0)] = r;   // the rows of a chunk that have entries start at different places
         }
@@ -710,6 +726,17 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
         }
     };
     const NnzArgs nz = {a.row_ptr, a.col_idx, a.chunk_row, a.n_rows, a.nnz, a.chunk_nnz, a.n_chunks};
+    float es[PER];
+    int col[PER];
+    if (a.nnz > 0) {
+        const ChunkSpan<PER> span(nz, chunk);
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const size_t k = span.at(u, lane);
+            col[u] = a.col_idx[k];
+            if (MODE == SENSEI_SPMM_WEIGHTED || MODE == kSpmmSoftmax || kSelf) es[u] = a.val[k * a.val_stride];
+        }
+    }
     const FlatChunk<PER> c = flat_rows<PER, PAD, G>(nz, chunk, lane, rows, [&](int r0, bool none) {
         unsigned long long m = __ballot(none);
         for (int b = 0; m; ++b, m >>= G) {   // rows without entries: one per group at a time
@@ -734,15 +761,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
     lds_exchange();
     const bool use_scale = MODE == kSpmmSoftmax ? a.scale_weights != 0 : MODE != kSpmmAttnFused && a.r && (kWeights ? a.scale_weights != 0 : a.finalize != 0);
     {
-        float es[PER];
-        int col[PER], rw[PER];
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int k = c.lo + u * 64 + lane;
-            const size_t kc = k < c.hi ? k : c.lo;
-            col[u] = a.col_idx[kc];
-            if (MODE == SENSEI_SPMM_WEIGHTED || MODE == kSpmmSoftmax || kSelf) es[u] = a.val[kc * a.val_stride];
-        }
+        int rw[PER];
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
             const int at = flat_at<PER, PAD, G>(u * 64 + lane);
@@ -1275,15 +1294,13 @@ __device__ __forceinline__ void flat_edge_op(const NnzArgs &a, const float *__re
     const int chunk = wave_chunk(), lane = threadIdx.x & 63;
     if (chunk >= a.n_chunks) return;
     int *rows = lds.row[threadIdx.x >> 6];
+    const ChunkSpan<PER> span(a, chunk);
+    float x[PER], y[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) y[u] = col_vec[a.col_idx[span.at(u, lane)]];
     const FlatChunk<PER> c = flat_rows<PER>(a, chunk, lane, rows, [](int, bool) {});
     if (c.lo >= c.hi) return;
     const RowVals rv = row_vals<PER>(c, lane, row_vec);
-    float x[PER], y[PER];
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        const int k = c.lo + u * 64 + lane;
-        y[u] = col_vec[a.col_idx[k < c.hi ? k : c.lo]];
-    }
 #pragma unroll
     for (int u = 0; u < PER; ++u) x[u] = row_val(rv, rows[u * 64 + lane]);
 #pragma unroll
@@ -1404,27 +1421,29 @@ struct SoftmaxArgs {
 // reduction merges (max, sum) pairs.
 template <bool FROM_E, int PER, class SrOf>
 __device__ __forceinline__ void softmax_stats_chunk(const SoftmaxArgs &a, int chunk, int lane, int *rows, float *val, SrOf s_r_of) {
+    float es[PER], e[PER], sr[PER];
+    int dst[PER];
+    if (a.n.nnz > 0) {
+        const ChunkSpan<PER> span(a.n, chunk);
+        if (FROM_E) {
+#pragma unroll
+            for (int u = 0; u < PER; ++u) es[u] = a.e[span.at(u, lane)];
+        } else {
+            int col[PER];
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const int k = span.at(u, lane);
+                col[u] = a.n.col_idx[k];
+                dst[u] = a.dst_index ? a.dst_index[k] : k;
+            }
+#pragma unroll
+            for (int u = 0; u < PER; ++u) sr[u] = s_r_of(col[u]);
+        }
+    }
     const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [&](int r0, bool none) { if (none) a.stats[r0 + lane] = make_float2(-INFINITY, 0.f); });
     if (c.lo >= c.hi) return;
-    float es[PER], e[PER];
-    if (FROM_E) {
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int k = c.lo + u * 64 + lane;
-            es[u] = a.e[k < c.hi ? k : c.lo];
-        }
-    } else {
-        int col[PER], dst[PER];
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int k = c.lo + u * 64 + lane, kc = k < c.hi ? k : c.lo;
-            col[u] = a.n.col_idx[kc];
-            dst[u] = a.dst_index ? a.dst_index[kc] : kc;
-        }
+    if (!FROM_E) {
         const RowVals sl = row_vals<PER>(c, lane, a.s_l);
-        float sr[PER];
-#pragma unroll
-        for (int u = 0; u < PER; ++u) sr[u] = s_r_of(col[u]);
 #pragma unroll
         for (int u = 0; u < PER; ++u) es[u] = row_val(sl, rows[u * 64 + lane]);
 #pragma unroll
@@ -1577,16 +1596,15 @@ __global__ __launch_bounds__(kBlock) void k_softmax_alpha(SoftmaxArgs a) {
     const int chunk = wave_chunk(), lane = threadIdx.x & 63;
     if (chunk >= a.n.n_chunks) return;
     int *rows = lds.row[threadIdx.x >> 6];
-    const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [](int, bool) {});
-    if (c.lo >= c.hi) return;
+    const ChunkSpan<PER> span(a.n, chunk);
     float e[PER];
     float2 st[PER];
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        const int k = c.lo + u * 64 + lane;
-        e[u] = a.e[k < c.hi ? k : c.lo];
-        st[u] = a.stats[rows[u * 64 + lane]];
-    }
+    for (int u = 0; u < PER; ++u) e[u] = a.e[span.at(u, lane)];
+    const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [](int, bool) {});
+    if (c.lo >= c.hi) return;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) st[u] = a.stats[rows[u * 64 + lane]];
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
         const int k = c.lo + u * 64 + lane;
@@ -1861,14 +1879,17 @@ __global__ __launch_bounds__(kBlock) void k_row_sum(NnzArgs a, const float *__re
     __shared__ FlatLds<PER> lds;
     const int chunk = wave_chunk(), lane = threadIdx.x & 63;
     if (chunk >= a.n_chunks) return;
+    float vs[PER], v[PER];
+    if (a.nnz > 0) {
+        const ChunkSpan<PER> span(a, chunk);
+#pragma unroll
+        for (int u = 0; u < PER; ++u) vs[u] = val[(size_t)span.at(u, lane) * stride];
+    }
     const FlatChunk<PER> c = flat_rows<PER>(a, chunk, lane, lds.row[threadIdx.x >> 6], [&](int r0, bool none) { if (none) out[r0 + lane] = 0.f; });
     if (c.lo >= c.hi) return;
-    float vs[PER], v[PER];
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        const int k = c.lo + u * 64 + lane;
-        vs[u] = k < c.hi ? val[(size_t)k * stride] : 0.f;
-    }
+    for (int u = 0; u < PER; ++u)
+        if (c.lo + u * 64 + lane >= c.hi) vs[u] = 0.f;
     to_blocked<PER>(lds.val[threadIdx.x >> 6], lane, vs, v);
     flat_sum<PER>(c, lane, v, [&](int i, float t, int) {
         if (c.cont && i == c.i_first) carry[chunk] = t;
@@ -2030,22 +2051,25 @@ __global__ __launch_bounds__(kBlock) void k_gat_dalpha_merge(NnzArgs a, const in
     const int chunk = wave_chunk(), lane = threadIdx.x & 63;
     if (chunk >= a.n_chunks) return;
     int *rows = lds.row[threadIdx.x >> 6];
-    const FlatChunk<PER> c = flat_rows<PER>(a, chunk, lane, rows, [&](int r0, bool none) { if (none) rowdot[r0 + lane] = 0.f; });
-    if (c.lo >= c.hi) return;
     int w[PER];
     float e[PER], v[PER], s[PER];
+    if (a.nnz > 0) {
+        const ChunkSpan<PER> span(a, chunk);
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        const int k = c.lo + u * 64 + lane, kc = k < c.hi ? k : c.lo;
-        w[u] = where[kc];
-        e[u] = logits[kc];
+        for (int u = 0; u < PER; ++u) {
+            const int k = span.at(u, lane);
+            w[u] = where[k];
+            e[u] = logits[k];
+        }
+        if (place) {
+#pragma unroll
+            for (int u = 0; u < PER; ++u) w[u] = w[u] >= 0 ? place[w[u]] : w[u];
+        }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) v[u] = w[u] >= 0 ? dalpha_rem[w[u]] : Dt[-(long long)w[u] - 1];
     }
-    if (place) {
-#pragma unroll
-        for (int u = 0; u < PER; ++u) w[u] = w[u] >= 0 ? place[w[u]] : w[u];
-    }
-#pragma unroll
-    for (int u = 0; u < PER; ++u) v[u] = w[u] >= 0 ? dalpha_rem[w[u]] : Dt[-(long long)w[u] - 1];
+    const FlatChunk<PER> c = flat_rows<PER>(a, chunk, lane, rows, [&](int r0, bool none) { if (none) rowdot[r0 + lane] = 0.f; });
+    if (c.lo >= c.hi) return;
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
         const int k = c.lo + u * 64 + lane;
@@ -2130,17 +2154,20 @@ __global__ __launch_bounds__(kBlock) void k_gat_dt(GatDtArgs a) {
     const int chunk = wave_chunk_by_xcd(), lane = threadIdx.x & 63;
     if (chunk >= a.n.n_chunks) return;
     int *rows = lds.row[threadIdx.x >> 6];
-    const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [&](int r0, bool none) { if (SUMS && none) a.rowsum[r0 + lane] = 0.f; });
-    if (c.lo >= c.hi) return;
     float e[PER], da[PER], t[PER];
     int p[PER];
+    if (a.n.nnz > 0) {
+        const ChunkSpan<PER> span(a.n, chunk);
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        const int k = c.lo + u * 64 + lane, kc = k < c.hi ? k : c.lo;
-        e[u] = a.logits[kc];
-        da[u] = a.dalpha[kc];
-        p[u] = a.t_pos[kc];
+        for (int u = 0; u < PER; ++u) {
+            const int k = span.at(u, lane);
+            e[u] = a.logits[k];
+            da[u] = a.dalpha[k];
+            p[u] = a.t_pos[k];
+        }
     }
+    const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [&](int r0, bool none) { if (SUMS && none) a.rowsum[r0 + lane] = 0.f; });
+    if (c.lo >= c.hi) return;
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
         const int k = c.lo + u * 64 + lane, i = rows[u * 64 + lane];
@@ -2219,18 +2246,18 @@ __global__ __launch_bounds__(kBlock) void k_gat_head_rows(GatHeadArgs a) {
     int *rows = lds.row[wave];
     float *val = lds.val[wave], *top = s_max[wave];
     const float *s_l = a.s_l + head * a.n_src, *s_r = a.s_r + head * a.n_src;
+    float es[PER], p[PER];
+    if (a.n.nnz > 0) {
+        const ChunkSpan<PER> span(a.n, chunk);
+#pragma unroll
+        for (int u = 0; u < PER; ++u) es[u] = s_r[a.n.col_idx[span.at(u, lane)]];
+    }
     const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [&](int r0, bool none) { if (none) a.ds_l[head * a.n_src + r0 + lane] = 0.f; });
     if (c.lo >= c.hi) return;
-    float es[PER], p[PER];
     unsigned neg = 0u;   // bit q: entry q of this lane (blocked order) has a logit of 0 or below
     {
         const RowVals sl = row_vals<PER>(c, lane, s_l);
         float mx[PER], e[PER];
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int k = c.lo + u * 64 + lane;
-            es[u] = s_r[a.n.col_idx[k < c.hi ? k : c.lo]];
-        }
 #pragma unroll
         for (int u = 0; u < PER; ++u) es[u] = leaky(row_val(sl, rows[u * 64 + lane]) + es[u], a.slope);
         to_blocked<PER>(val, lane, es, e);
@@ -2361,6 +2388,15 @@ __global__ __launch_bounds__(kBlock) void k_gat_head_cols(GatHeadArgs a) {
         }
         if (li == 0) ds_out[row] = ds;
     };
+    int col[PER];
+    float4 st[PER];
+    if (a.n.nnz > 0) {
+        const ChunkSpan<PER> span(a.n, chunk);
+#pragma unroll
+        for (int u = 0; u < PER; ++u) col[u] = a.n.col_idx[span.at(u, lane)];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) st[u] = a.row[head * a.n_dst + col[u]];
+    }
     const FlatChunk<PER> c = flat_rows<PER, PAD, G>(a.n, chunk, lane, rows, [&](int r0, bool none) {
         unsigned long long m = __ballot(none);
         for (int b = 0; m; ++b, m >>= G) {   // rows without entries: one per group at a time
@@ -2382,15 +2418,6 @@ __global__ __launch_bounds__(kBlock) void k_gat_head_cols(GatHeadArgs a) {
     lds_exchange();
     {
         const RowVals sr = row_vals<PER>(c, lane, a.s_r + head * a.n_src);
-        int col[PER];
-        float4 st[PER];
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int k = c.lo + u * 64 + lane;
-            col[u] = a.n.col_idx[k < c.hi ? k : c.lo];
-        }
-#pragma unroll
-        for (int u = 0; u < PER; ++u) st[u] = a.row[head * a.n_dst + col[u]];
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
             const int at = flat_at<PER, PAD, G>(u * 64 + lane), rw = rows[at];
