@@ -621,7 +621,7 @@ size_t tagcn_bwd_ws(const sensei_csr &A, int f_in, int f_out, int k_hops, int id
         b += align_up(n * (size_t)(k_hops + 1) * fo4 * sizeof(float), 256);          // Q_0 .. Q_K side by side, row-major
         b += align_up(n * pad32(f_out) * sizeof(float), 256);                        // r (x) Q_k, slice-major
         b += align_up((size_t)(k_hops + 1) * fo4 * fi4 * sizeof(float), 256);        // W_k^T stacked
-        b += gemm_tn_bytes(A.n_rows, f_in, f_out);
+        b += gemm_tn_bytes(A.n_rows, f_in, f_out, k_hops + 1);
     } else {
         b += spmm_carry_bytes(A.nnz, pad32(f_in));
         b += align_up(n * fo4 * sizeof(float), 256);                                 // dP
@@ -644,7 +644,6 @@ int run_tagcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r
     ChunkPlan plan_t = make_plan(At, cv);
     SideWork side;
     side.add_plan(At, plan_t);
-    auto w_block = [&](int k) { return W.ptr + (size_t)k * f_in * W.ld; };
     auto dw_block = [&](int k) { return dW + (size_t)k * f_in * lddw; };
     if (id == SENSEI_GCN_BWD_AGG) {
         const int64_t ldq = (int64_t)(k_hops + 1) * fo4;
@@ -652,7 +651,7 @@ int run_tagcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r
         float *Q = cv.take<float>((size_t)n * ldq);
         float *S = cv.take<float>((size_t)n * fo32);
         float *Wst = cv.take<float>((size_t)ldq * fi4);
-        double *part = cv.take<double>(gemm_tn_bytes(n, f_in, f_out) / sizeof(double));
+        double *part = cv.take<double>(gemm_tn_bytes(n, f_in, f_out, k_hops + 1) / sizeof(double));
         // the pad columns enter the GEMM below: those of Q_0 are cleared here, the propagations write the others (S has zeros there)
         if (fo4 != f_out) SENSEI_TRY(launch_zero_matrix(Q + f_out, n, fo4 - f_out, ldq, false, s));
         SENSEI_TRY(launch_row_broadcast(nullptr, dY.ptr, dY.ld, n, f_out, Q, ldq, SENSEI_ACT_NONE, s, mask, ldy, &side));
@@ -661,11 +660,11 @@ int run_tagcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r
             SENSEI_TRY(spmm_any(At, SENSEI_SPMM_PATTERN, c, nullptr, S, fo32, fo4, Q + (size_t)k * fo4, ldq, fo4, SENSEI_ACT_NONE, plan_t, carry, s,
                                 nullptr, false, nullptr, true));
         }
-        for (int k = 0; k <= k_hops; ++k)
-            SENSEI_TRY(launch_gemm_tn(X.ptr, X.ld, Q + (size_t)k * fo4, ldq, n, f_in, f_out, dw_block(k), lddw, part, s));
+        // dW_k = X^T Q_k, all hops in one launch
+        SENSEI_TRY(launch_gemm_tn(X.ptr, X.ld, Q, ldq, n, f_in, f_out, dW, lddw, part, s, k_hops + 1, fo4, (int64_t)f_in * lddw));
         if (dX) {
-            SENSEI_TRY(launch_zero_matrix(Wst, ldq, fi4, fi4, false, s));
-            for (int k = 0; k <= k_hops; ++k) SENSEI_TRY(launch_transpose(w_block(k), W.ld, f_in, f_out, Wst + (size_t)k * fo4 * fi4, fi4, s));
+            if (fo4 != f_out) SENSEI_TRY(launch_zero_matrix(Wst, ldq, fi4, fi4, false, s));   // the rows that meet the pad columns of Q
+            SENSEI_TRY(launch_transpose(W.ptr, W.ld, f_in, f_out, Wst, fi4, s, k_hops + 1, (int64_t)f_in * W.ld, (int64_t)fo4 * fi4));
             SENSEI_TRY(launch_gemm(Q, ldq, Wst, fi4, dX, lddx, n, (int)ldq, f_in, f_in, SENSEI_ACT_NONE, s));
         }
         return SENSEI_OK;
@@ -688,7 +687,7 @@ int run_tagcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r
         SENSEI_TRY(launch_gemm_tn(H, fi4, dP, fo4, n, f_in, f_out, dw_block(k), lddw, part, s));
     }
     if (dX) {
-        for (int k = 0; k <= k_hops; ++k) SENSEI_TRY(launch_transpose(w_block(k), W.ld, f_in, f_out, Wt + (size_t)k * fo4 * fi4, fi4, s));
+        SENSEI_TRY(launch_transpose(W.ptr, W.ld, f_in, f_out, Wt, fi4, s, k_hops + 1, (int64_t)f_in * W.ld, (int64_t)fo4 * fi4));
         auto wt_block = [&](int k) { return Wt + (size_t)k * fo4 * fi4; };
         if (k_hops == 0) {
             SENSEI_TRY(launch_gemm(dP, fo4, wt_block(0), fi4, dX, lddx, n, f_out, f_in, f_in, SENSEI_ACT_NONE, s));

@@ -1288,6 +1288,8 @@ struct GemmTnArgs {
     double *part;     // splits x M x N
     long long lda, ldb, k;
     int m, n, n_bn, n_tiles, k_per_split;
+    int segs;           // several products with the same A in one launch: B's columns h * b_seg .. + n belong to product h, n_bn blocks of columns each
+    long long b_seg;
 };
 
 constexpr int kFlushTiles = 1;  // k-tiles (of KT = 16) summed in fp32 before the accumulators move to fp64
@@ -1301,7 +1303,9 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tn(GemmTnArgs g) {
     const int wave = t >> 6, lane = t & 63;
     const int wm = wave >> 1, wn = wave & 1;
     const int tile = (int)(blockIdx.x % g.n_tiles), split = (int)(blockIdx.x / g.n_tiles);
-    const int m0 = (tile / g.n_bn) * BM, n0 = (tile % g.n_bn) * BN;
+    const int jn = tile % (g.n_bn * g.segs), seg = jn / g.n_bn;
+    const int m0 = tile / (g.n_bn * g.segs) * BM, n0 = jn % g.n_bn * BN;
+    const float *const B = g.B + seg * g.b_seg;
     const long long k_lo = (long long)split * g.k_per_split;
     const long long k_hi = (k_lo + g.k_per_split < g.k) ? k_lo + g.k_per_split : g.k;
 
@@ -1350,7 +1354,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tn(GemmTnArgs g) {
             const long long kk = k0 + kr;
             const int col = n0 + b_cc;
             if (kr < KT && kk < k_hi && col < g.n) {
-                const float *src = g.B + kk * g.ldb + col;
+                const float *src = B + kk * g.ldb + col;
                 if (VB == 4) { float4 v = *reinterpret_cast<const float4 *>(src); rb[p][0] = v.x; rb[p][1 % VB] = v.y; rb[p][2 % VB] = v.z; rb[p][3 % VB] = v.w; }
                 else rb[p][0] = *src;
             } else {
@@ -1403,7 +1407,8 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tn(GemmTnArgs g) {
     }
     flush();
 
-    double *out = g.part + (size_t)split * (size_t)g.m * (size_t)g.n;
+    const size_t width = (size_t)g.n * g.segs;
+    double *out = g.part + (size_t)split * (size_t)g.m * width + (size_t)seg * g.n;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -1413,7 +1418,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tn(GemmTnArgs g) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int row = m0 + (wm * TM + i) * 32 + 8 * (r / 4) + 4 * kh + (r % 4);
-                if (row < g.m) out[(size_t)row * g.n + col] = dacc[i][j][r];
+                if (row < g.m) out[(size_t)row * width + col] = dacc[i][j][r];
             }
         }
 }
@@ -1438,7 +1443,9 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tn_bf(GemmTnArgs g) {
     const int wm = wave >> 1, wn = wave & 1;
     const int kh = lane >> 5, ll = lane & 31;
     const int tile = (int)(blockIdx.x % g.n_tiles), split = (int)(blockIdx.x / g.n_tiles);
-    const int m0 = (tile / g.n_bn) * BM, n0 = (tile % g.n_bn) * BN;
+    const int jn = tile % (g.n_bn * g.segs), seg = jn / g.n_bn;
+    const int m0 = tile / (g.n_bn * g.segs) * BM, n0 = jn % g.n_bn * BN;
+    const float *const B = g.B + seg * g.b_seg;
     const long long k_lo = (long long)split * g.k_per_split;
     const long long k_hi = (k_lo + g.k_per_split < g.k) ? k_lo + g.k_per_split : g.k;
 
@@ -1479,14 +1486,14 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tn_bf(GemmTnArgs g) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             if constexpr (decltype(whole)::value) {   // all 16 rows of the step lie inside the slab
-                const char *ar = reinterpret_cast<const char *>(g.A + (k0 + e) * g.lda), *br = reinterpret_cast<const char *>(g.B + (k0 + e) * g.ldb);
+                const char *ar = reinterpret_cast<const char *>(g.A + (k0 + e) * g.lda), *br = reinterpret_cast<const char *>(B + (k0 + e) * g.ldb);
                 ra[e] = __uint_as_float(__float_as_uint(*reinterpret_cast<const float *>(ar + a_off)) & a_mask);
                 rb[e] = __uint_as_float(__float_as_uint(*reinterpret_cast<const float *>(br + b_off)) & b_mask);
             } else {
                 const long long k = k0 + skh * 8 + e, kb = k0 + b_skh * 8 + e;
                 const long long kc = (k < k_hi ? k : k_hi - 1) - skh * 8, kbc = (kb < k_hi ? kb : k_hi - 1) - b_skh * 8;
                 const unsigned live = k < k_hi ? ~0u : 0u;
-                const char *ar = reinterpret_cast<const char *>(g.A + kc * g.lda), *br = reinterpret_cast<const char *>(g.B + kbc * g.ldb);
+                const char *ar = reinterpret_cast<const char *>(g.A + kc * g.lda), *br = reinterpret_cast<const char *>(B + kbc * g.ldb);
                 ra[e] = __uint_as_float(__float_as_uint(*reinterpret_cast<const float *>(ar + a_off)) & a_mask & live);
                 rb[e] = __uint_as_float(__float_as_uint(*reinterpret_cast<const float *>(br + b_off)) & b_mask);
             }
@@ -1547,7 +1554,8 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tn_bf(GemmTnArgs g) {
     }
     flush();
 
-    double *out = g.part + (size_t)split * (size_t)g.m * (size_t)g.n;
+    const size_t width = (size_t)g.n * g.segs;
+    double *out = g.part + (size_t)split * (size_t)g.m * width + (size_t)seg * g.n;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -1557,7 +1565,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tn_bf(GemmTnArgs g) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int row = m0 + (wm * TM + i) * 32 + 8 * (r / 4) + 4 * kh + (r % 4);
-                if (row < g.m) out[(size_t)row * g.n + c] = dacc[i][j][r];
+                if (row < g.m) out[(size_t)row * width + c] = dacc[i][j][r];
             }
         }
 }
@@ -1567,8 +1575,8 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tn_bf(GemmTnArgs g) {
 // to 16 lanes each, which keep eight loads in flight; the 16 partial sums are added in lane order through LDS, so the order of the
 // additions is fixed.  100 x 47, 768 slabs: 188 -> 10 us; 602 x 256, 77 slabs: 66 -> under 22 us.
 constexpr int kSumElems = 16, kSumLanes = 16;
-__global__ __launch_bounds__(kSumElems * kSumLanes) void k_sum_splits(const double *__restrict__ part, int splits, long long mn, int n,
-                                                                       float *__restrict__ C, long long ldc) {
+__global__ __launch_bounds__(kSumElems * kSumLanes) void k_sum_splits(const double *__restrict__ part, int splits, long long mn, int n, int segs,
+                                                                       float *__restrict__ C, long long ldc, long long c_seg) {
     __shared__ double red[kSumLanes][kSumElems];
     const int q = threadIdx.x % kSumElems, y = threadIdx.x / kSumElems;
     const long long e = (long long)blockIdx.x * kSumElems + q;
@@ -1583,11 +1591,15 @@ __global__ __launch_bounds__(kSumElems * kSumLanes) void k_sum_splits(const doub
     if (y != 0 || e >= mn) return;
 #pragma unroll
     for (int u = 1; u < kSumLanes; ++u) s += red[u][q];
-    C[(e / n) * ldc + (e % n)] = (float)s;
+    const int q_all = (int)(e % ((long long)n * segs));
+    C[q_all / n * c_seg + (e / ((long long)n * segs)) * ldc + q_all % n] = (float)s;
 }
 
-// Wt[c][r] = W[r][c] for a small matrix (the layer weights)
-__global__ void k_transpose(const float *__restrict__ W, long long ldw, int rows, int cols, float *__restrict__ Wt, long long ldt) {
+// Wt[c][r] = W[r][c] for small matrices (the layer weights; blockIdx.z: several, w_step and wt_step floats apart)
+__global__ void k_transpose(const float *__restrict__ W, long long ldw, int rows, int cols, float *__restrict__ Wt, long long ldt, long long w_step,
+                            long long wt_step) {
+    W += blockIdx.z * w_step;
+    Wt += blockIdx.z * wt_step;
     __shared__ float tile[32][33];
     const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
@@ -1885,28 +1897,31 @@ hipError_t launch_gemv2(const float *A, int64_t lda, int64_t n, int k, const flo
     return hipGetLastError();
 }
 
-int gemm_tn_splits(int64_t k, int m, int n) {
-    const long long tiles = (long long)((m + 127) / 128) * ((n + 127) / 128);
+int gemm_tn_splits(int64_t k, int m, int n, int segs) {
+    const long long tiles = (long long)((m + 127) / 128) * ((n + 127) / 128) * segs;
     long long s = (768 + tiles - 1) / tiles;              // about three workgroups per compute unit
     const long long max_s = (k + 4 * KT - 1) / (4 * KT);  // at least four k-tiles per slab
     if (s > max_s) s = max_s;
     return (int)(s < 1 ? 1 : s);
 }
 
-size_t gemm_tn_bytes(int64_t k, int m, int n) { return align_up((size_t)gemm_tn_splits(k, m, n) * (size_t)m * (size_t)n * sizeof(double), 256); }
+size_t gemm_tn_bytes(int64_t k, int m, int n, int segs) {
+    return align_up((size_t)gemm_tn_splits(k, m, n, segs) * (size_t)m * (size_t)n * segs * sizeof(double), 256);
+}
 
 hipError_t launch_gemm_tn(const float *A, int64_t lda, const float *B, int64_t ldb, int64_t k, int m, int n, float *C, int64_t ldc,
-                          double *part, hipStream_t s) {
+                          double *part, hipStream_t s, int segs, int64_t b_seg, int64_t c_seg) {
     if (m <= 0 || n <= 0) return hipSuccess;
     GemmTnArgs g;
     g.A = A; g.B = B; g.part = part; g.lda = lda; g.ldb = ldb; g.k = k > 0 ? k : 0; g.m = m; g.n = n;
+    g.segs = segs; g.b_seg = b_seg;
     g.n_bn = (n + 127) / 128;
-    g.n_tiles = ((m + 127) / 128) * g.n_bn;
-    const int splits = gemm_tn_splits(k, m, n);
+    g.n_tiles = ((m + 127) / 128) * g.n_bn * segs;
+    const int splits = gemm_tn_splits(k, m, n, segs);
     g.k_per_split = (int)(((g.k + splits - 1) / splits + KT - 1) / KT * KT);
     if (g.k_per_split < KT) g.k_per_split = KT;
     const bool va = (m % 4 == 0 && lda % 4 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0);
-    const bool vb = (n % 4 == 0 && ldb % 4 == 0 && reinterpret_cast<uintptr_t>(B) % 16 == 0);
+    const bool vb = (n % 4 == 0 && ldb % 4 == 0 && (segs == 1 || b_seg % 4 == 0) && reinterpret_cast<uintptr_t>(B) % 16 == 0);
     dim3 grid((unsigned)(g.n_tiles * splits));
     // long reductions (the weight gradients of a layer) take the bf16-piece kernel
     if (g.k >= 4096 && g.k_per_split >= 64) {
@@ -1917,16 +1932,17 @@ hipError_t launch_gemm_tn(const float *A, int64_t lda, const float *B, int64_t l
     else if (va) hipLaunchKernelGGL((k_gemm_tn<4, 1>), grid, dim3(kThreads), 0, s, g);
     else if (vb) hipLaunchKernelGGL((k_gemm_tn<1, 4>), grid, dim3(kThreads), 0, s, g);
     else hipLaunchKernelGGL((k_gemm_tn<1, 1>), grid, dim3(kThreads), 0, s, g);
-    const long long mn = (long long)m * n;
-    hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((mn + kSumElems - 1) / kSumElems)), dim3(kSumElems * kSumLanes), 0, s, part, splits, mn, n, C,
-                       (long long)ldc);
+    const long long mn = (long long)m * n * segs;
+    hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((mn + kSumElems - 1) / kSumElems)), dim3(kSumElems * kSumLanes), 0, s, part, splits, mn, n,
+                       segs, C, (long long)ldc, (long long)c_seg);
     return hipGetLastError();
 }
 
-hipError_t launch_transpose(const float *W, int64_t ldw, int rows, int cols, float *Wt, int64_t ldt, hipStream_t s) {
-    if (rows <= 0 || cols <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_transpose, dim3((unsigned)((cols + 31) / 32), (unsigned)((rows + 31) / 32)), dim3(256), 0, s, W, (long long)ldw, rows, cols,
-                       Wt, (long long)ldt);
+hipError_t launch_transpose(const float *W, int64_t ldw, int rows, int cols, float *Wt, int64_t ldt, hipStream_t s, int count, int64_t w_step,
+                            int64_t wt_step) {
+    if (rows <= 0 || cols <= 0 || count <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_transpose, dim3((unsigned)((cols + 31) / 32), (unsigned)((rows + 31) / 32), (unsigned)count), dim3(256), 0, s, W, (long long)ldw,
+                       rows, cols, Wt, (long long)ldt, (long long)w_step, (long long)wt_step);
     return hipGetLastError();
 }
 
