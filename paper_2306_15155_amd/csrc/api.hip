@@ -942,7 +942,13 @@ int run_gatv2(const sensei_csr &A, const sensei_mat &X, const sensei_mat &Wl, co
 //   dTheta_r[j] = sum_i alpha_ij dP_i + att (.) sum_i de_ij LeakyReLU'(U_ij)                           (row sums over the transposed pattern)
 //   datt        = sum_i sum_j de_ij LeakyReLU(U_ij)
 //   dW_l = X_dst^T dTheta_l,  dW_r = X^T dTheta_r,  dX = dTheta_r W_r^T + [dTheta_l W_l^T on the first n_rows rows]
-// The three sums with a vector per entry are SpMM walks whose gathered row meets a vector of the output row (kSpmmSignSum / kSpmmLreluSum).
+// The three sums with a vector per entry are SpMM walks whose gathered row meets a vector of the output row (launch_v2_walk).
+// both weight gradients are one launch where both are sums over the same rows
+size_t v2_tn_bytes(const sensei_csr &A, int f_in, int f_out) {
+    const size_t one = gemm_tn_bytes(A.n_cols, f_in, f_out), both = gemm_tn_bytes(A.n_cols, f_in, f_out, 2);
+    return one > both ? one : both;
+}
+
 size_t gatv2_bwd_ws(const sensei_csr &A, int f_in, int f_out) {
     const size_t nz = (size_t)(A.nnz > 0 ? A.nnz : 1), fo = pad32(f_out), fo4 = pad4(f_out), fi4 = pad4(f_in);
     const int t = choose_chunk_nnz(A.nnz);
@@ -950,15 +956,13 @@ size_t gatv2_bwd_ws(const sensei_csr &A, int f_in, int f_out) {
     size_t b = 2 * plan_bytes(A.nnz) + softmax_ws_bytes(A) + 1024;
     b += 2 * align_up(nz * sizeof(float), 256) + align_up(nz * sizeof(float2), 256);   // logits, dalpha / de, (alpha, de) transposed
     b += align_up((size_t)(A.n_rows + 1) * sizeof(float), 256) + align_up(n_chunks * sizeof(float), 256);   // row dots and their carry
-    b += 2 * align_up(fo * sizeof(float), 256);                                        // att padded, a scratch vector
+    b += align_up(fo * sizeof(float), 256);                                            // att padded
     b += align_up((size_t)A.n_cols * fo * sizeof(float), 256);                         // Theta_r (slice-major)
     b += 3 * align_up((size_t)A.n_rows * fo * sizeof(float), 256);                     // Theta_l, dP, the LeakyReLU sums (slice-major)
     b += align_up((size_t)A.n_cols * 2 * fo4 * sizeof(float), 256);                    // [dTheta_r | dTheta_l]
-    b += align_up((size_t)A.n_cols * fo4 * sizeof(float), 256);                        // the sign sums over the transposed pattern
-    b += align_up((size_t)A.n_rows * sizeof(float), 256);                              // ones
-    b += spmm_carry_bytes(A.nnz, (int)fo);
+    b += 2 * spmm_carry_bytes(A.nnz, (int)fo);
     b += align_up(2 * fo4 * fi4 * sizeof(float), 256);                                 // [W_r^T; W_l^T]
-    b += gemm_tn_bytes(A.n_cols, f_in, f_out) + theta_t_vec_bytes(A.n_rows, f_out);
+    b += v2_tn_bytes(A, f_in, f_out) + theta_t_vec_bytes(A.n_rows, f_out);
     return b;
 }
 
@@ -981,17 +985,14 @@ int run_gatv2_backward(const sensei_csr &A_in, const sensei_csr &At_in, const in
     float *rowdot = cv.take<float>((size_t)A.n_rows + 1);
     float *sum_carry = cv.take<float>((size_t)plan.n_chunks);
     float *att_pad = cv.take<float>((size_t)fo);
-    float *vec_scratch = cv.take<float>((size_t)fo);
     float *theta_r = cv.take<float>((size_t)A.n_cols * fo);
     float *theta_l = cv.take<float>((size_t)A.n_rows * fo);
     float *dPs = cv.take<float>((size_t)A.n_rows * fo);
     float *Rs = cv.take<float>((size_t)A.n_rows * fo);
     float *Dcat = cv.take<float>((size_t)A.n_cols * ldd);
-    float *GR = cv.take<float>((size_t)A.n_cols * fo4);
-    float *ones = cv.take<float>((size_t)A.n_rows);
-    float *carry = cv.take<float>(spmm_carry_bytes(A.nnz, fo) / sizeof(float));
+    float *carry = cv.take<float>(spmm_carry_bytes(A.nnz, fo) / sizeof(float)), *carry_r = cv.take<float>(spmm_carry_bytes(A.nnz, fo) / sizeof(float));
     float *Wcat = cv.take<float>((size_t)ldd * fi4);
-    double *part = cv.take<double>(gemm_tn_bytes(A.n_cols, f_in, f_out) / sizeof(double));
+    double *part = cv.take<double>(v2_tn_bytes(A, f_in, f_out) / sizeof(double));
     double *part_a = cv.take<double>(theta_t_vec_bytes(A.n_rows, f_out) / sizeof(double));
     float *dThR = Dcat, *dThL = Dcat + fo4;
 
@@ -1003,35 +1004,27 @@ int run_gatv2_backward(const sensei_csr &A_in, const sensei_csr &At_in, const in
     SENSEI_TRY(launch_gemm(X.ptr, X.ld, Wr.ptr, Wr.ld, theta_r, fo, A.n_cols, f_in, f_out, fo, SENSEI_ACT_NONE, s, nullptr, nullptr, true));
     SENSEI_TRY(launch_gemm(X.ptr, X.ld, Wl.ptr, Wl.ld, theta_l, fo, A.n_rows, f_in, f_out, fo, SENSEI_ACT_NONE, s, nullptr, nullptr, true));
     SENSEI_TRY(launch_score_v2(A, theta_l, theta_r, f_out, att_pad, slope, logits, plan, s));
-    SENSEI_TRY(launch_softmax(A, logits, de, plan, stats, carry_stats, s));   // the weights it writes are not kept: de is overwritten below
+    SENSEI_TRY(launch_softmax(A, logits, nullptr, plan, stats, carry_stats, s));
     SENSEI_TRY(launch_to_slices(nullptr, dY.ptr, dY.ld, A.n_rows, f_out, dPs, s, act == SENSEI_ACT_RELU ? Y : nullptr, ldy));
     // per stored entry: dalpha and its weighted row sums, then the softmax backward; alpha and de also in transposed order
     SENSEI_TRY(launch_gat_dalpha(A, theta_r, dPs, f_out, logits, stats, de, rowdot, plan, sum_carry, s));
     SENSEI_TRY(launch_gat_dt(A, logits, de, rowdot, stats, t_pos, 1.f, de, ade_t, plan, s));
     // [dTheta_r | dTheta_l], zero where nothing is written (pad columns; the rows of dTheta_l past the destinations)
-    SENSEI_TRY(launch_zero_matrix(Dcat, A.n_cols, (int)ldd, ldd, false, s));
-    SENSEI_TRY(launch_zero_matrix(Wcat, ldd, fi4, fi4, false, s));
-    sensei_csr Aw = At;
-    Aw.val = reinterpret_cast<const float *>(ade_t);
-    SENSEI_TRY(launch_spmm(Aw, SENSEI_SPMM_WEIGHTED, nullptr, nullptr, dPs, fo, f_out, dThR, ldd, f_out, SENSEI_ACT_NONE, plan_t, carry, s, nullptr, false,
-                           true, nullptr, true, 2));
-    SelfSumArgs self_l = {theta_l, slope}, self_r = {theta_r, slope};
-    sensei_csr Ae = A;
-    Ae.val = de;
-    SENSEI_TRY(launch_spmm(Ae, kSpmmSignSum, nullptr, nullptr, theta_r, fo, f_out, dThL, ldd, f_out, SENSEI_ACT_NONE, plan, carry, s, nullptr, false, true,
-                           nullptr, true, 1, false, false, nullptr, &self_l));
-    SENSEI_TRY(launch_spmm(Ae, kSpmmLreluSum, nullptr, nullptr, theta_r, fo, fo, Rs, fo, fo, SENSEI_ACT_NONE, plan, carry, s, nullptr, false, true, nullptr,
-                           true, 1, true, false, nullptr, &self_l));
-    Aw.val = reinterpret_cast<const float *>(ade_t) + 1;
-    SENSEI_TRY(launch_spmm(Aw, kSpmmSignSum, nullptr, nullptr, theta_l, fo, f_out, GR, fo4, f_out, SENSEI_ACT_NONE, plan_t, carry, s, nullptr, false, true,
-                           nullptr, true, 2, false, false, nullptr, &self_r));
-    SENSEI_TRY(launch_scale_cols(dThL, ldd, dThL, ldd, att, A.n_rows, f_out, false, s));
-    SENSEI_TRY(launch_scale_cols(dThR, ldd, GR, fo4, att, A.n_cols, f_out, true, s));
+    const bool padded = fo4 != f_out;
+    if (padded || A.n_rows != A.n_cols) SENSEI_TRY(launch_zero_matrix(Dcat, A.n_cols, (int)ldd, ldd, false, s));
+    if (padded) SENSEI_TRY(launch_zero_matrix(Wcat, ldd, fi4, fi4, false, s));
+    SENSEI_TRY(launch_v2_walk(At, plan_t, true, theta_r, theta_l, dPs, reinterpret_cast<const float *>(ade_t), att_pad, slope, f_out, dThR, ldd, nullptr, carry,
+                              nullptr, s));
+    SENSEI_TRY(launch_v2_walk(A, plan, false, theta_l, theta_r, nullptr, de, att_pad, slope, f_out, dThL, ldd, Rs, carry, carry_r, s));
     // datt: column sums of the LeakyReLU sums
-    SENSEI_TRY(launch_fill_f32(ones, A.n_rows, 1.f, s));
-    SENSEI_TRY(launch_theta_t_vec(Rs, A.n_rows, f_out, ones, A.n_rows, ones, datt, vec_scratch, part_a, s));
-    SENSEI_TRY(launch_gemm_tn(X.ptr, X.ld, dThL, ldd, A.n_rows, f_in, f_out, dWl, lddwl, part, s));
-    SENSEI_TRY(launch_gemm_tn(X.ptr, X.ld, dThR, ldd, A.n_cols, f_in, f_out, dWr, lddwr, part, s));
+    SENSEI_TRY(launch_theta_t_vec(Rs, A.n_rows, f_out, nullptr, A.n_rows, nullptr, datt, nullptr, part_a, s));
+    const intptr_t apart = reinterpret_cast<intptr_t>(dWl) - reinterpret_cast<intptr_t>(dWr);
+    if (A.n_rows == A.n_cols && lddwl == lddwr && apart % (intptr_t)sizeof(float) == 0) {
+        SENSEI_TRY(launch_gemm_tn(X.ptr, X.ld, Dcat, ldd, A.n_cols, f_in, f_out, dWr, lddwr, part, s, 2, fo4, apart / (intptr_t)sizeof(float)));
+    } else {
+        SENSEI_TRY(launch_gemm_tn(X.ptr, X.ld, dThL, ldd, A.n_rows, f_in, f_out, dWl, lddwl, part, s));
+        SENSEI_TRY(launch_gemm_tn(X.ptr, X.ld, dThR, ldd, A.n_cols, f_in, f_out, dWr, lddwr, part, s));
+    }
     if (dX) {
         SENSEI_TRY(launch_transpose(Wr.ptr, Wr.ld, f_in, f_out, Wcat, fi4, s));
         SENSEI_TRY(launch_transpose(Wl.ptr, Wl.ld, f_in, f_out, Wcat + (size_t)fo4 * fi4, fi4, s));
@@ -1163,7 +1156,7 @@ int run_dotgat_backward(const sensei_csr &A_in, const sensei_csr &At_in, const i
     SENSEI_TRY(launch_gemm(X.ptr, X.ld, Wk.ptr, Wk.ld, K, dk, A.n_cols, f_in, d_k, dk, SENSEI_ACT_NONE, s, nullptr, nullptr, true));
     SENSEI_TRY(launch_gemm(X.ptr, X.ld, Wv.ptr, Wv.ld, V, fo, A.n_cols, f_in, f_out, fo, SENSEI_ACT_NONE, s, nullptr, nullptr, true));
     SENSEI_TRY(launch_gat_dalpha(A, K, Q, d_k, nullptr, nullptr, logits, nullptr, plan, nullptr, s, scale));
-    SENSEI_TRY(launch_softmax(A, logits, de, plan, stats, carry_stats, s));   // the weights it writes are not kept: de is overwritten below
+    SENSEI_TRY(launch_softmax(A, logits, nullptr, plan, stats, carry_stats, s));
     SENSEI_TRY(launch_to_slices(nullptr, dY.ptr, dY.ld, A.n_rows, f_out, dPs, s, act == SENSEI_ACT_RELU ? Y : nullptr, ldy));
     // per stored entry: dalpha and its weighted row sums, then the softmax backward; alpha and de also in transposed order
     SENSEI_TRY(launch_gat_dalpha(A, V, dPs, f_out, logits, stats, de, rowdot, plan, sum_carry, s));

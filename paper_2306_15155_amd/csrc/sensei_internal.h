@@ -114,7 +114,7 @@ hipError_t launch_spmm(const sensei_csr &A, int mode, const float *r, const floa
                        int f, float *C, int64_t ldc, int f_store, int act, const ChunkPlan &p, float *carry,
                        hipStream_t s, KernelTimer *timer = nullptr, bool accumulate = false, bool finalize = true,
                        const float2 *mz = nullptr, bool b_sliced = false, int val_stride = 1, bool c_sliced = false, bool defer_fixup = false,
-                       const struct AttnFusedArgs *fused = nullptr, const struct SelfSumArgs *self = nullptr);
+                       const struct AttnFusedArgs *fused = nullptr);
 // b_sliced: B is stored slice-major in tiles of 32 floats, element (j, col) at B[(col / 32) * n_cols * 32 + j * 32 + col % 32]
 // (f padded to a multiple of 32, B 128-byte aligned); `ldb` is ignored.  val_stride: floats between consecutive values of A.val.
 // c_sliced (needs b_sliced, f a multiple of 32, f_store == f): C is written slice-major too (n_rows x f), `ldc` is ignored.
@@ -136,15 +136,11 @@ struct AttnFusedArgs {
     float2 *row_mz, *chunk_mz;
     int heads = 1;   // > 1 (slice-major B of heads * 32 columns, all stored): slice h is head h's; s_l, s_r, row_mz and chunk_mz one after the other per head
 };
-// Internal SpMM modes for the backward pass of a score with a vector per entry, e_ij = att . LeakyReLU(U_ij), U_ij = self[i, :] + B[j, :]
-// (slice-major self over the rows and B over the columns): C[i, m] = sum_j val_ij LeakyReLU'(U_ij[m]) (kSpmmSignSum: 1 where
-// U > 0, else the slope) or sum_j val_ij LeakyReLU(U_ij[m]) (kSpmmLreluSum).  Single pass, slice-major B only.
-constexpr int kSpmmSignSum = 5;
-constexpr int kSpmmLreluSum = 6;
-struct SelfSumArgs {
-    const float *self_sliced;
-    float slope;
-};
+// Backward of the GATv2 score (slice-major own over the rows of A, other and dP over its columns): cols = false: C = att (x) sum_j w LeakyReLU'(own + other)
+// and R (slice-major) = sum_j w LeakyReLU(own + other); cols = true, w holding (alpha, de) pairs: C = sum_j alpha dP_j + att (x) sum_j de LeakyReLU'(own +
+// other).  C row-major, f columns.
+hipError_t launch_v2_walk(const sensei_csr &A, const ChunkPlan &p, bool cols, const float *own, const float *other, const float *dP, const float *w,
+                          const float *att_padded, float slope, int f, float *C, int64_t ldc, float *R, float *carry, float *carry_r, hipStream_t s);
 
 // ---- column panels: a copy of the pattern with the columns of each panel contiguous
 #define SENSEI_MAX_PANELS SENSEI_PANELS_MAX
@@ -178,7 +174,7 @@ hipError_t launch_to_slices(const float *s_vec, const float *X, int64_t ldx, int
 // ---- attention: logits, per-row softmax statistics, normalised weights
 hipError_t launch_score(const sensei_csr &A, const float *s_l, const float *s_r, float slope, float *e,
                         const ChunkPlan &p, hipStream_t s);
-// alpha = row-wise softmax of the logits e (in place allowed); stats[i] = (row max, sum of exp(e - max)) as a by-product.
+// alpha = row-wise softmax of the logits e (in place allowed; null: statistics only); stats[i] = (row max, sum of exp(e - max)) as a by-product.
 hipError_t launch_softmax(const sensei_csr &A, const float *e, float *alpha, const ChunkPlan &p, float2 *stats, float2 *carry_stats,
                           hipStream_t s);
 // Logits e_ij = LeakyReLU(s_l[i] + s_r[j]) of every stored entry, written to logits[k] (or logits[dst_index[k]]), and the
@@ -224,7 +220,7 @@ hipError_t launch_fill_f32(float *p, int64_t n, float v, hipStream_t s);
 size_t theta_t_vec_bytes(int64_t n, int f);
 hipError_t launch_theta_t_vec(const float *theta_sliced, int64_t n, int f, const float *v_l, int64_t n_l, const float *v_r, float *out_l,
                               float *out_r, double *part, hipStream_t s, int n_heads = 1);
-// n_heads > 1: heads of f / n_heads columns, a pair of vectors each, n floats apart; Theta holds one slice a head
+// null v_l: column sums; null v_r: out_r is not written.  n_heads > 1: heads of f / n_heads columns, a pair of vectors each, n floats apart; Theta holds one slice a head
 // Backward of attention heads of d <= 32 columns, slice h of theta (n_cols rows) and dP (n_rows rows) being head h's: ds_l, ds_r (n_cols floats a head)
 // and dtheta (row-major, head h's columns from h * d on).  Scratch: row n_rows float4 a head, piece 16 floats a head and chunk
 // of A, carry 32 floats and ds_carry one a head and chunk of At.

@@ -69,9 +69,6 @@ struct SpmmArgs {
     float slope;
     long long head_vec, head_mz;  // several heads of one tile each: floats from one head's score vectors to the next, pairs from one head's mz_out to the next (0: one head)
     float2 *mz_out, *carry_mz;  // per row: pair of a first piece whose row goes on in the next chunk; per chunk: pair of its continued row
-    // modes kSpmmSignSum / kSpmmLreluSum: a vector per row, slice-major like C (tile t of row i at self + t * self_tile + i * 32)
-    const float *self;
-    long long self_tile;
 };
 
 // value of `x` held by the lane whose number is byte_lane / 4 (all lanes must be active)
@@ -653,15 +650,11 @@ __global__ __launch_bounds__(kBlock) void k_spmm(SpmmArgs a) {
 // gathers only.  Tiles, chunk ownership, carry slots and fix-up are those of k_spmm.
 // kSpmmAttnFused: the logits of the chunk are formed before the loop, and with them the maximum and the sum of every row piece
 // (segmented scans), so that the loop is a plain weighted sum.
-// kSpmmSignSum, kSpmmLreluSum (slice-major operands): the gathered row meets a vector of the output row itself, u = self[i, :] + B[j, :],
-// and what is summed is val_ij LeakyReLU'(u) or val_ij LeakyReLU(u), column by column: the reductions of the backward pass of a score
-// with a vector per entry.  The own vectors are gathered per entry while rows change and kept in registers where none does.
 // B is row-major (a row holds all its 32-column tiles) or slice-major (all rows of tile 0, then all rows of tile 1, ...: what an XCD
 // gathers from is then one contiguous range, which spreads evenly over the memory channels whatever the row pitch).
 template <int MODE, int PER, int LPG, bool OFF32>
 __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
-    constexpr bool kSelf = MODE == kSpmmSignSum || MODE == kSpmmLreluSum;
-    constexpr int G = 64 / LPG, T = 64 * PER, PART = T / G, PAD = 4, U = kSelf ? 4 : 8;
+    constexpr int G = 64 / LPG, T = 64 * PER, PART = T / G, PAD = 4, U = 8;
     constexpr bool kWeights = MODE != SENSEI_SPMM_PATTERN;
     // where entries have weights the row factor goes into them (launch_spmm tells the fix-up so); a third array in LDS would cost a
     // third of the wavefronts
@@ -734,7 +727,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
         for (int u = 0; u < PER; ++u) {
             const size_t k = span.at(u, lane);
             col[u] = a.col_idx[k];
-            if (MODE == SENSEI_SPMM_WEIGHTED || MODE == kSpmmSoftmax || kSelf) es[u] = a.val[k * a.val_stride];
+            if (MODE == SENSEI_SPMM_WEIGHTED || MODE == kSpmmSoftmax) es[u] = a.val[k * a.val_stride];
         }
     }
     const FlatChunk<PER> c = flat_rows<PER, PAD, G>(nz, chunk, lane, rows, [&](int r0, bool none) {
@@ -834,24 +827,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), head = acc;
     int head_at = -1;
     const int part0 = g * (PART + PAD);
-    const float *self_lane = kSelf ? a.self + (size_t)tile * a.self_tile + (fok ? li * 4 : 0) : nullptr;
-    float4 self_cur = acc;   // the output row's own vector, for the row of the last entry seen
-    int self_row = -1;
     for (int s = 0; s < PART && s < n; s += U) {
-        float4 sv[kSelf ? U : 1];
-        if (kSelf) {
-            const int4 r4 = *reinterpret_cast<const int4 *>(&rows[part0 + s]);
-            if (__all((r4.w & 0x7fffffff) == self_row)) {   // (rows ascend) every group stays in its row
-#pragma unroll
-                for (int q = 0; q < (kSelf ? U : 1); ++q) sv[q] = self_cur;
-            } else {
-                const int r[4] = {r4.x, r4.y, r4.z, r4.w};
-#pragma unroll
-                for (int q = 0; q < (kSelf ? U : 1); ++q) sv[q] = *reinterpret_cast<const float4 *>(self_lane + (size_t)(r[q] & 0x7fffffff) * 32);
-                self_row = r4.w & 0x7fffffff;
-                self_cur = sv[kSelf ? U - 1 : 0];
-            }
-        }
         int cf[U];
         float w[U];
         float4 b[U];
@@ -868,15 +844,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
         for (int q = 0; q < U; ++q) b[q] = gather(cf[q] & 0x7fffffff);
 #pragma unroll
         for (int q = 0; q < U; ++q) {
-            if (kSelf) {
-                auto term = [&](float own, float x) {
-                    const float t = own + x, d = t > 0.f ? 1.f : a.slope;
-                    return MODE == kSpmmSignSum ? d : d * t;
-                };
-                const float4 o = sv[kSelf ? q : 0];
-                acc.x = fmaf(w[q], term(o.x, b[q].x), acc.x); acc.y = fmaf(w[q], term(o.y, b[q].y), acc.y);
-                acc.z = fmaf(w[q], term(o.z, b[q].z), acc.z); acc.w = fmaf(w[q], term(o.w, b[q].w), acc.w);
-            } else if (kWeights) {
+            if (kWeights) {
                 acc.x = fmaf(w[q], b[q].x, acc.x); acc.y = fmaf(w[q], b[q].y, acc.y); acc.z = fmaf(w[q], b[q].z, acc.z); acc.w = fmaf(w[q], b[q].w, acc.w);
             } else {
                 acc.x += b[q].x; acc.y += b[q].y; acc.z += b[q].z; acc.w += b[q].w;
@@ -1109,8 +1077,6 @@ hipError_t spmm_dispatch_mode(const SpmmArgs &a, int mode, dim3 grid, hipStream_
         case SENSEI_SPMM_WEIGHTED: hipLaunchKernelGGL((k_spmm<VEC, LPG, SENSEI_SPMM_WEIGHTED, OFF32>), grid, dim3(kBlock), 0, s, a); break;
         case kSpmmSoftmax: hipLaunchKernelGGL((k_spmm<VEC, LPG, kSpmmSoftmax, OFF32>), grid, dim3(kBlock), 0, s, a); break;
         case kSpmmAttnFused: hipLaunchKernelGGL((k_spmm<VEC, LPG, kSpmmAttnFused, OFF32>), grid, dim3(kBlock), 0, s, a); break;
-        case kSpmmSignSum:
-        case kSpmmLreluSum: return hipErrorInvalidValue;   // slice-major operands only
         default: hipLaunchKernelGGL((k_spmm<VEC, LPG, SENSEI_SPMM_SCALED, OFF32>), grid, dim3(kBlock), 0, s, a); break;
     }
     return hipGetLastError();
@@ -1149,10 +1115,6 @@ hipError_t spmm_flat_mode(const SpmmArgs &a, int mode, dim3 grid, hipStream_t s)
         case kSpmmSoftmax: return spmm_flat_per<kSpmmSoftmax, LPG, OFF32>(a, grid, s);
         case kSpmmAttnFused: return spmm_flat_per<kSpmmAttnFused, LPG, OFF32>(a, grid, s);
         default: break;
-    }
-    if constexpr (LPG == 8) {
-        if (mode == kSpmmSignSum) return spmm_flat_per<kSpmmSignSum, LPG, OFF32>(a, grid, s);
-        if (mode == kSpmmLreluSum) return spmm_flat_per<kSpmmLreluSum, LPG, OFF32>(a, grid, s);
     }
     return hipErrorInvalidValue;
 }
@@ -2341,7 +2303,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_head_fixup(GatHeadArgs a) {
                });
 }
 
-// The walk over the transposed pattern: k_spmm_flat's, with the own row's Theta gathered per entry while rows change (as in kSpmmSignSum) and
+// The walk over the transposed pattern: k_spmm_flat's, with the own row's Theta gathered per entry while rows change and
 // the dot product reduced over the eight lanes of a group by DPP moves.
 template <int PER>
 __global__ __launch_bounds__(kBlock) void k_gat_head_cols(GatHeadArgs a) {
@@ -2520,6 +2482,183 @@ __global__ __launch_bounds__(kBlock) void k_gat_head_cols_fixup(GatHeadArgs a) {
     }
 }
 
+// ---- backward of the GATv2 score e_ij = a . LeakyReLU(U_ij), U_ij = Theta_l[i, :] + Theta_r[j, :]: the sums with a vector per entry, one slice of 32
+// columns per wavefront, k_spmm_flat's walk with the row's own vector gathered per entry while rows change.
+//   COLS = false, over the pattern (own: Theta_l, gathered: Theta_r, weights de): dTheta_l[i] = a (x) sum_j de_ij LeakyReLU'(U_ij) and the sums
+//     R[i] = sum_j de_ij LeakyReLU(U_ij), whose column sums are da;
+//   COLS = true, over its transpose (own: Theta_r, gathered: Theta_l and dP, weights (alpha, de) pairs): dTheta_r[j] = sum_i alpha_ij dP_i +
+//     a (x) sum_i de_ij LeakyReLU'(U_ij).
+// a multiplies the finished pieces.  Bound by the gathers of both vectors; as four walks of one sum each with a pass to multiply by a they took
+// 297 us on 3 M entries x 64 columns, as two 179.
+struct V2WalkArgs {
+    NnzArgs n;
+    const float *own, *other, *dP;   // slice-major: over the rows of n, over its columns, over its columns
+    const float *w, *att;            // per entry; padded with zeros to whole slices
+    float *C, *R;                    // row-major (ldc); slice-major over the rows
+    float *carry, *carry_r;          // f_carry floats a chunk
+    long long own_tile, other_tile, ldc;
+    int f, f_carry, n_tiles, tiles_live, n_groups, store_vec_ok;
+    float slope;
+};
+
+template <bool COLS, int PER>
+__global__ __launch_bounds__(kBlock) void k_v2_walk(V2WalkArgs a) {
+    constexpr int LPG = 8, G = 64 / LPG, T = 64 * PER, PART = T / G, PAD = 4, U = 4;
+    __shared__ __attribute__((aligned(16))) int s_col[kWavesPerBlock][T + G * PAD];
+    __shared__ __attribute__((aligned(16))) int s_row[kWavesPerBlock][T + G * PAD];
+    __shared__ __attribute__((aligned(16))) float s_de[kWavesPerBlock][T + G * PAD];
+    __shared__ __attribute__((aligned(16))) float s_al[COLS ? kWavesPerBlock : 1][COLS ? T + G * PAD : 4];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane / LPG, li = lane % LPG;
+    const int per_set = a.n_groups * a.tiles_live, in_set = blockIdx.x % per_set;
+    const int tile = blockIdx.x / per_set * a.tiles_live + in_set % a.tiles_live;
+    if (tile >= a.n_tiles) return;
+    const int chunk = in_set / a.tiles_live * kWavesPerBlock + __builtin_amdgcn_readfirstlane(wave);
+    if (chunk >= a.n.n_chunks) return;
+    const int f0 = tile * 32 + li * 4;
+    int *rows = s_row[wave], *cols = s_col[wave];
+    float *de = s_de[wave], *al = s_al[COLS ? wave : 0];
+    const float *own = a.own + (size_t)tile * a.own_tile + li * 4, *other = a.other + (size_t)tile * a.other_tile + li * 4;
+    const float *dP = COLS ? a.dP + (size_t)tile * a.other_tile + li * 4 : nullptr;
+    const float4 at4 = *reinterpret_cast<const float4 *>(a.att + f0);
+    int cont_row = -1;
+    auto write_row = [&](int row, float4 v, float4 r) {   // v: the sums that a multiplies; r: the others
+        v.x *= at4.x; v.y *= at4.y; v.z *= at4.z; v.w *= at4.w;
+        if (COLS) { v.x += r.x; v.y += r.y; v.z += r.z; v.w += r.w; }
+        if (row == cont_row) {
+            *reinterpret_cast<float4 *>(a.carry + (size_t)chunk * a.f_carry + f0) = v;
+            if (!COLS) *reinterpret_cast<float4 *>(a.carry_r + (size_t)chunk * a.f_carry + f0) = r;
+            return;
+        }
+        float *dst = a.C + (size_t)row * a.ldc + f0;
+        if (a.store_vec_ok && f0 + 4 <= a.f) {
+            *reinterpret_cast<float4 *>(dst) = v;
+        } else {
+            if (f0 < a.f) dst[0] = v.x;
+            if (f0 + 1 < a.f) dst[1] = v.y;
+            if (f0 + 2 < a.f) dst[2] = v.z;
+            if (f0 + 3 < a.f) dst[3] = v.w;
+        }
+        if (!COLS) *reinterpret_cast<float4 *>(a.R + (size_t)tile * a.own_tile + (size_t)row * 32 + li * 4) = r;
+    };
+    float we[PER], wa[COLS ? PER : 1];
+    int col[PER];
+    if (a.n.nnz > 0) {
+        const ChunkSpan<PER> span(a.n, chunk);
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const size_t k = span.at(u, lane);
+            col[u] = a.n.col_idx[k];
+            if (COLS) {
+                const float2 p = reinterpret_cast<const float2 *>(a.w)[k];
+                wa[COLS ? u : 0] = p.x;
+                we[u] = p.y;
+            } else {
+                we[u] = a.w[k];
+            }
+        }
+    }
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    const FlatChunk<PER> c = flat_rows<PER, PAD, G>(a.n, chunk, lane, rows, [&](int r0, bool none) {
+        unsigned long long m = __ballot(none);
+        for (int b = 0; m; ++b, m >>= G)   // rows without entries: one per group at a time
+            if ((m >> g) & 1ull) write_row(r0 + b * G + g, zero, zero);
+    });
+    if (c.lo >= c.hi) return;
+    const int n = c.hi - c.lo;
+    if (c.cont) cont_row = c.i_first;
+    {   // the last entry of every row piece is flagged (sign bit of its column)
+        const int next_start = __shfl_down((int)(c.starts & 1u), 1, 64);
+        unsigned ends = (c.starts >> 1) | ((lane < 63 ? (unsigned)next_start : 0u) << (PER - 1));
+        const int e_last = n - 1 - lane * PER;
+        if (e_last >= 0 && e_last < PER) ends |= 1u << e_last;
+#pragma unroll
+        for (int e = 0; e < PER; ++e) cols[flat_at<PER, PAD, G>(lane * PER + e)] = (int)(((ends >> e) & 1u) << 31);
+    }
+    lds_exchange();
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int at = flat_at<PER, PAD, G>(u * 64 + lane);
+        const bool live = c.lo + u * 64 + lane < c.hi;
+        cols[at] |= col[u];
+        de[at] = live ? we[u] : 0.f;
+        if (COLS) al[at] = live ? wa[COLS ? u : 0] : 0.f;
+    }
+    lds_exchange();
+    float4 acc = zero, accr = zero, head = zero, headr = zero, mine = zero;
+    int head_at = -1, mine_row = -1;
+    const int part0 = g * (PART + PAD);
+    for (int s = 0; s < PART && s < n; s += U) {
+        const int4 c4 = *reinterpret_cast<const int4 *>(&cols[part0 + s]), r4 = *reinterpret_cast<const int4 *>(&rows[part0 + s]);
+        const float4 e4 = *reinterpret_cast<const float4 *>(&de[part0 + s]);
+        float4 a4 = zero;
+        if (COLS) a4 = *reinterpret_cast<const float4 *>(&al[part0 + s]);
+        const int cf[U] = {c4.x, c4.y, c4.z, c4.w}, rf[U] = {r4.x, r4.y, r4.z, r4.w};
+        const float e[U] = {e4.x, e4.y, e4.z, e4.w}, w[U] = {a4.x, a4.y, a4.z, a4.w};
+        float4 b[U], d[COLS ? U : 1], o[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const size_t j = (size_t)(cf[q] & 0x7fffffff) * 32;
+            b[q] = *reinterpret_cast<const float4 *>(other + j);
+            if (COLS) d[COLS ? q : 0] = *reinterpret_cast<const float4 *>(dP + j);
+        }
+        if (__all(rf[U - 1] == mine_row)) {   // (rows ascend) every group stays in its row
+#pragma unroll
+            for (int q = 0; q < U; ++q) o[q] = mine;
+        } else {
+#pragma unroll
+            for (int q = 0; q < U; ++q) o[q] = *reinterpret_cast<const float4 *>(own + (size_t)rf[q] * 32);
+            mine_row = rf[U - 1];
+            mine = o[U - 1];
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            auto add = [&](float &s1, float &s2, float x, float y, float p) {
+                const float t = x + y, dt = t > 0.f ? 1.f : a.slope;
+                s1 = fmaf(e[q], dt, s1);
+                s2 = COLS ? fmaf(w[q], p, s2) : fmaf(e[q], dt * t, s2);
+            };
+            const float4 p = d[COLS ? q : 0];
+            add(acc.x, accr.x, o[q].x, b[q].x, p.x);
+            add(acc.y, accr.y, o[q].y, b[q].y, p.y);
+            add(acc.z, accr.z, o[q].z, b[q].z, p.z);
+            add(acc.w, accr.w, o[q].w, b[q].w, p.w);
+            if (cf[q] < 0) {
+                if (head_at < 0) {
+                    head = acc;
+                    headr = accr;
+                    head_at = part0 + s + q;
+                } else {
+                    write_row(rf[q], acc, accr);
+                }
+                acc = accr = zero;
+            }
+        }
+    }
+    int f = head_at >= 0;
+    auto up = [&](const float4 &v, int off) { return make_float4(__shfl_up(v.x, off, 64), __shfl_up(v.y, off, 64), __shfl_up(v.z, off, 64), __shfl_up(v.w, off, 64)); };
+#pragma unroll
+    for (int off = LPG; off < 64; off <<= 1) {
+        const float4 x = up(acc, off), y = up(accr, off);
+        const int of = __shfl_up(f, off, 64);
+        if (lane >= off) {
+            if (!f) {
+                acc.x += x.x; acc.y += x.y; acc.z += x.z; acc.w += x.w;
+                accr.x += y.x; accr.y += y.y; accr.z += y.z; accr.w += y.w;
+            }
+            f |= of;
+        }
+    }
+    acc = up(acc, LPG);
+    accr = up(accr, LPG);
+    if (head_at >= 0) {
+        if (g > 0) {
+            head.x += acc.x; head.y += acc.y; head.z += acc.z; head.w += acc.w;
+            headr.x += accr.x; headr.y += accr.y; headr.z += accr.z; headr.w += accr.w;
+        }
+        write_row(rows[head_at], head, headr);
+    }
+}
+
 // dTheta[j, :] += ds_l[j] a_l + ds_r[j] a_r (ds_l counts only for j < n_l)
 __global__ void k_rank1_add(float *__restrict__ D, long long ldd, long long n, int f, const float *__restrict__ ds_l, long long n_l,
                             const float *__restrict__ ds_r, const float *__restrict__ a_l, const float *__restrict__ a_r) {
@@ -2556,8 +2695,8 @@ __global__ __launch_bounds__(256) void k_theta_t_vec(const float *__restrict__ t
                                                      double *__restrict__ part, long long head_stride) {
     __shared__ double red[2][4][32];   // per wavefront
     const int tile = blockIdx.x, slab = blockIdx.y;
-    v_l += tile * head_stride;   // heads of one slice: a pair of vectors per tile
-    v_r += tile * head_stride;
+    if (v_l) v_l += tile * head_stride;   // heads of one slice: a pair of vectors per tile
+    if (v_r) v_r += tile * head_stride;
     const int q = threadIdx.x & 7, rr = threadIdx.x >> 3;
     const long long j_lo = (long long)slab * rows_per_slab;
     const long long j_hi = (j_lo + rows_per_slab < n) ? j_lo + rows_per_slab : n;
@@ -2566,7 +2705,7 @@ __global__ __launch_bounds__(256) void k_theta_t_vec(const float *__restrict__ t
 #pragma unroll 4
     for (long long j = j_lo + rr; j < j_hi; j += 32) {
         const float4 x = *reinterpret_cast<const float4 *>(th + j * 32);
-        const double l = j < n_l ? (double)v_l[j] : 0.0, r = (double)v_r[j];
+        const double l = j >= n_l ? 0.0 : v_l ? (double)v_l[j] : 1.0, r = v_r ? (double)v_r[j] : 0.0;   // null: column sums; nothing
         sl[0] += (double)x.x * l; sl[1] += (double)x.y * l; sl[2] += (double)x.z * l; sl[3] += (double)x.w * l;
         sr[0] += (double)x.x * r; sr[1] += (double)x.y * r; sr[2] += (double)x.z * r; sr[3] += (double)x.w * r;
     }
@@ -2612,7 +2751,8 @@ __global__ __launch_bounds__(256) void k_sum_slabs(const double *__restrict__ pa
     double t = 0.0;
 #pragma unroll
     for (int u = 0; u < 16; ++u) t += red[y][u][c];
-    (y == 0 ? out_l : out_r)[out] = (float)t;
+    float *dst = y == 0 ? out_l : out_r;
+    if (dst) dst[out] = (float)t;
 }
 
 // pos[k] = index in the transposed pattern of the entry (i, j) stored at k: the place of i among the ascending
@@ -2760,7 +2900,7 @@ size_t spmm_carry_bytes(int64_t nnz, int f) {
 hipError_t launch_spmm(const sensei_csr &A, int mode, const float *r, const float *c, const float *B, int64_t ldb,
                        int f, float *C, int64_t ldc, int f_store, int act, const ChunkPlan &p, float *carry,
                        hipStream_t s, KernelTimer *timer, bool accumulate, bool finalize, const float2 *mz, bool b_sliced, int val_stride,
-                       bool c_sliced, bool defer_fixup, const AttnFusedArgs *fused, const SelfSumArgs *self) {
+                       bool c_sliced, bool defer_fixup, const AttnFusedArgs *fused) {
     SpmmShape sh = spmm_shape(B, ldb, f);
     if (b_sliced) {  // slices of 32 floats per row: one 128-byte line per neighbour and tile
         sh.vec = 4; sh.lpg = 8; sh.n_tiles = (f + 31) / 32; sh.f_carry = sh.n_tiles * 32;
@@ -2790,12 +2930,6 @@ hipError_t launch_spmm(const sensei_csr &A, int mode, const float *r, const floa
             if (!b_sliced || f != fused->heads * 32 || f_store != f) return hipErrorInvalidValue;
             a.head_vec = A.n_cols; a.head_mz = A.n_rows + 1;
         }
-    }
-    a.self = nullptr; a.self_tile = 0;
-    if (mode == kSpmmSignSum || mode == kSpmmLreluSum) {
-        if (!self || !self->self_sliced || !b_sliced || !A.val) return hipErrorInvalidValue;
-        a.self = self->self_sliced; a.slope = self->slope;
-        a.self_tile = (long long)(A.n_rows > 0 ? A.n_rows : 1) * 32;
     }
     const unsigned groups = blocks_for(p.n_chunks, kWavesPerBlock);
     // Feature tiles worked on at the same time (consecutive XCDs take consecutive tiles of the live set): all eight
@@ -2924,7 +3058,7 @@ hipError_t launch_softmax(const sensei_csr &A, const float *e, float *alpha, con
     return with_per(p.chunk_nnz, [&](auto per) {
         hipLaunchKernelGGL((k_softmax_stats<true, per()>), g1, dim3(kBlock), 0, s, a);
         if (p.n_chunks > 1) hipLaunchKernelGGL(k_softmax_fixup, dim3(blocks_for(p.n_chunks - 1, kBlock)), dim3(kBlock), 0, s, a);
-        if (A.nnz > 0) hipLaunchKernelGGL(k_softmax_alpha<per()>, g1, dim3(kBlock), 0, s, a);
+        if (A.nnz > 0 && alpha) hipLaunchKernelGGL(k_softmax_alpha<per()>, g1, dim3(kBlock), 0, s, a);
     });
 }
 
@@ -3045,6 +3179,37 @@ hipError_t launch_rank1_add(float *D, int64_t ldd, int64_t n, int f, const float
     if (n <= 0 || f <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_rank1_add, dim3(blocks_for(n * f, kBlock)), dim3(kBlock), 0, s, D, (long long)ldd, (long long)n, f, ds_l, (long long)n_l,
                        ds_r, a_l, a_r);
+    return hipGetLastError();
+}
+
+// the two walks of the GATv2 backward (see k_v2_walk); carry, carry_r: spmm_carry_bytes of the pattern at pad32(f) columns
+hipError_t launch_v2_walk(const sensei_csr &A, const ChunkPlan &p, bool cols, const float *own, const float *other, const float *dP, const float *w,
+                          const float *att_padded, float slope, int f, float *C, int64_t ldc, float *R, float *carry, float *carry_r, hipStream_t s) {
+    V2WalkArgs a;
+    a.n = nnz_args(A, p);
+    a.own = own; a.other = other; a.dP = dP; a.w = w; a.att = att_padded; a.C = C; a.R = R; a.carry = carry; a.carry_r = carry_r;
+    a.own_tile = (long long)(A.n_rows > 0 ? A.n_rows : 1) * 32;
+    a.other_tile = (long long)(A.n_cols > 0 ? A.n_cols : 1) * 32;
+    a.ldc = ldc; a.f = f; a.n_tiles = (f + 31) / 32; a.f_carry = a.n_tiles * 32; a.slope = slope;
+    a.store_vec_ok = ldc % 4 == 0 && reinterpret_cast<uintptr_t>(C) % 16 == 0;
+    a.tiles_live = a.other_tile * 4 > 8000000 ? 4 : 8;   // as in launch_spmm
+    if (a.tiles_live > a.n_tiles) a.tiles_live = a.n_tiles;
+    a.n_groups = (int)blocks_for(p.n_chunks, kWavesPerBlock);
+    const dim3 grid((unsigned)(a.n_groups * a.tiles_live * ((a.n_tiles + a.tiles_live - 1) / a.tiles_live)));
+    const hipError_t e = with_per(p.chunk_nnz, [&](auto per) {
+        if (cols) hipLaunchKernelGGL((k_v2_walk<true, per()>), grid, dim3(kBlock), 0, s, a);
+        else hipLaunchKernelGGL((k_v2_walk<false, per()>), grid, dim3(kBlock), 0, s, a);
+    });
+    if (e != hipSuccess || p.n_chunks <= 1) return e;
+    SpmmArgs x = {};   // the carry slots of rows that span chunks: raw sums
+    x.row_ptr = A.row_ptr; x.chunk_row = p.chunk_row; x.n_rows = A.n_rows; x.nnz = (int)A.nnz; x.chunk_nnz = p.chunk_nnz; x.n_chunks = p.n_chunks;
+    x.f_carry = a.f_carry; x.c_tf = 32; x.c_shift = 5; x.act = SENSEI_ACT_NONE; x.fix_quads = p.n_chunks < 8192 ? 8 : 32;
+    for (int out = 0; out < (cols ? 1 : 2); ++out) {
+        x.C = out ? R : C; x.carry = out ? carry_r : carry;
+        x.ldc = out ? 32 : ldc; x.c_tile = out ? a.own_tile : 32; x.f_store = out ? a.f_carry : f;
+        x.store_vec_ok = out ? 1 : a.store_vec_ok;
+        hipLaunchKernelGGL(k_spmm_fixup, dim3(blocks_for(p.n_chunks - 1, kWavesPerBlock * kFixupChunks), blocks_for(x.f_store, 4 * x.fix_quads)), dim3(kBlock), 0, s, x);
+    }
     return hipGetLastError();
 }
 
