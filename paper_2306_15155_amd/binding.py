@@ -183,11 +183,12 @@ def _check(status: int, where: str):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()   # the argument types turn the number into a pointer
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the handle of the current device's current stream, without a Stream object around it
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def csr_struct(n_rows, n_cols, row_ptr, col_idx, val=None, panels=None, tiles=None) -> CsrStruct:
@@ -295,8 +296,17 @@ class Tiles:
 
 
 def mat_struct(t: torch.Tensor) -> MatStruct:
-    assert t.dtype == torch.float32 and t.dim() == 2 and (t.stride(1) == 1 or t.size(1) <= 1)
-    return MatStruct(t.data_ptr(), t.size(0), t.size(1), t.stride(0) if t.size(0) > 1 else max(t.stride(0), t.size(1)))
+    assert t.dtype == torch.float32 and t.dim() == 2
+    (rows, cols), (ld, step) = t.shape, t.stride()
+    assert step == 1 or cols <= 1
+    return MatStruct(t.data_ptr(), rows, cols, ld if rows > 1 else max(ld, cols))
+
+
+def _ld(t: torch.Tensor) -> int:
+    assert t.dtype == torch.float32 and t.dim() == 2
+    (rows, cols), (ld, step) = t.shape, t.stride()
+    assert step == 1 or cols <= 1
+    return ld if rows > 1 else max(ld, cols)
 
 
 class Workspace:
@@ -313,13 +323,11 @@ class Workspace:
 
     @property
     def ptr(self):
-        p = self.buf.data_ptr()
-        return ctypes.c_void_p((p + 255) // 256 * 256)
+        return (self.buf.data_ptr() + 255) & ~255
 
     @property
     def nbytes(self):
-        p = self.buf.data_ptr()
-        return max(0, self.buf.numel() - ((p + 255) // 256 * 256 - p))
+        return max(0, self.buf.numel() - (-self.buf.data_ptr() & 255))
 
 
 class Context:
@@ -366,25 +374,25 @@ class Context:
 
     def row_broadcast(self, s, X, out=None):
         Y = torch.empty_like(X) if out is None else out
-        _check(lib().sensei_row_broadcast(self._h, _ptr(s), mat_struct(X), _ptr(Y), mat_struct(Y).ld, _stream()), "sensei_row_broadcast")
+        _check(lib().sensei_row_broadcast(self._h, _ptr(s), mat_struct(X), _ptr(Y), _ld(Y), _stream()), "sensei_row_broadcast")
         return Y
 
     def spmm(self, A: CsrStruct, mode, B, r=None, c=None, activation=ACT_NONE, out=None):
         C = torch.empty((A.n_rows, B.size(1)), dtype=torch.float32, device=self.device) if out is None else out
         self.ws.ensure(self.sparse_workspace(A, B.size(1)))
-        _check(lib().sensei_spmm(self._h, ctypes.byref(A), mode, _ptr(r), _ptr(c), mat_struct(B), _ptr(C), mat_struct(C).ld,
+        _check(lib().sensei_spmm(self._h, ctypes.byref(A), mode, _ptr(r), _ptr(c), mat_struct(B), _ptr(C), _ld(C),
                                  activation, self.ws.ptr, self.ws.nbytes, _stream()), "sensei_spmm")
         return C
 
     def spmm_static(self, A: CsrStruct, mode, B, out, r=None, c=None, activation=ACT_NONE):
         """sensei_spmm_static: the caller passes the output; nothing is allocated on either side of the boundary."""
-        _check(lib().sensei_spmm_static(self._h, ctypes.byref(A), mode, _ptr(r), _ptr(c), mat_struct(B), _ptr(out), mat_struct(out).ld,
+        _check(lib().sensei_spmm_static(self._h, ctypes.byref(A), mode, _ptr(r), _ptr(c), mat_struct(B), _ptr(out), _ld(out),
                                         activation, _stream()), "sensei_spmm_static")
         return out
 
     def gemm(self, A, W, activation=ACT_NONE, out=None):
         Y = torch.empty((A.size(0), W.size(1)), dtype=torch.float32, device=self.device) if out is None else out
-        _check(lib().sensei_gemm(self._h, mat_struct(A), mat_struct(W), _ptr(Y), mat_struct(Y).ld, activation, _stream()), "sensei_gemm")
+        _check(lib().sensei_gemm(self._h, mat_struct(A), mat_struct(W), _ptr(Y), _ld(Y), activation, _stream()), "sensei_gemm")
         return Y
 
     def gemv2(self, A, v1, v2):
@@ -417,7 +425,7 @@ class Context:
         Y = torch.empty((A.n_rows, W.size(1)), dtype=torch.float32, device=self.device) if out is None else out
         self.ws.ensure(self.gcn_workspace(A, X.size(1), W.size(1), comp_id))
         _check(lib().sensei_gcn_layer(self._h, ctypes.byref(A), _ptr(r), _ptr(c), mat_struct(X), mat_struct(W), _ptr(Y),
-                                      mat_struct(Y).ld, activation, comp_id, self.ws.ptr, self.ws.nbytes, _stream()), "sensei_gcn_layer")
+                                      _ld(Y), activation, comp_id, self.ws.ptr, self.ws.nbytes, _stream()), "sensei_gcn_layer")
         return Y
 
     def gat_workspace(self, A: CsrStruct, f_in, f_out, comp_id) -> int:
@@ -434,9 +442,9 @@ class Context:
         _check(lib().sensei_gcn_backward_workspace(ctypes.byref(A), f_in, f_out, bwd_id, ctypes.byref(need)), "sensei_gcn_backward_workspace")
         self.ws.ensure(need.value)
         _check(lib().sensei_gcn_backward(self._h, ctypes.byref(A), ctypes.byref(At), _ptr(r), _ptr(c), mat_struct(X), mat_struct(W), _ptr(Y),
-                                         mat_struct(Y).ld if Y is not None else 0, mat_struct(dY), activation, _ptr(U_saved),
-                                         mat_struct(U_saved).ld if U_saved is not None else 0, _ptr(dX),
-                                         mat_struct(dX).ld if dX is not None else 0, _ptr(dW), mat_struct(dW).ld, bwd_id, self.ws.ptr,
+                                         _ld(Y) if Y is not None else 0, mat_struct(dY), activation, _ptr(U_saved),
+                                         _ld(U_saved) if U_saved is not None else 0, _ptr(dX),
+                                         _ld(dX) if dX is not None else 0, _ptr(dW), _ld(dW), bwd_id, self.ws.ptr,
                                          self.ws.nbytes, _stream()), "sensei_gcn_backward")
         return dX, dW
 
@@ -459,8 +467,8 @@ class Context:
         _check(lib().sensei_gat_backward_workspace(ctypes.byref(A), ctypes.byref(At), f_in, f_out, ctypes.byref(need)), "sensei_gat_backward_workspace")
         self.ws.ensure(need.value)
         _check(lib().sensei_gat_backward(self._h, ctypes.byref(A), ctypes.byref(At), _ptr(t_pos), mat_struct(X), mat_struct(W), _ptr(a_l),
-                                         _ptr(a_r), neg_slope, _ptr(Y), mat_struct(Y).ld if Y is not None else 0, mat_struct(dY), activation,
-                                         _ptr(dX), mat_struct(dX).ld if dX is not None else 0, _ptr(dW), mat_struct(dW).ld, _ptr(dal),
+                                         _ptr(a_r), neg_slope, _ptr(Y), _ld(Y) if Y is not None else 0, mat_struct(dY), activation,
+                                         _ptr(dX), _ld(dX) if dX is not None else 0, _ptr(dW), _ld(dW), _ptr(dal),
                                          _ptr(dar), self.ws.ptr, self.ws.nbytes, _stream()), "sensei_gat_backward")
         return dX, dW, dal, dar
 
@@ -477,8 +485,8 @@ class Context:
                "sensei_gat_backward_heads_workspace")
         self.ws.ensure(need.value)
         _check(lib().sensei_gat_backward_heads(self._h, ctypes.byref(A), ctypes.byref(At), _ptr(t_pos), mat_struct(X), mat_struct(W), _ptr(a_l),
-                                               _ptr(a_r), n_heads, neg_slope, _ptr(Y), mat_struct(Y).ld if Y is not None else 0, mat_struct(dY),
-                                               activation, _ptr(dX), mat_struct(dX).ld if dX is not None else 0, _ptr(dW), mat_struct(dW).ld,
+                                               _ptr(a_r), n_heads, neg_slope, _ptr(Y), _ld(Y) if Y is not None else 0, mat_struct(dY),
+                                               activation, _ptr(dX), _ld(dX) if dX is not None else 0, _ptr(dW), _ld(dW),
                                                _ptr(dal), _ptr(dar), self.ws.ptr, self.ws.nbytes, _stream()), "sensei_gat_backward_heads")
         return dX, dW, dal, dar
 
@@ -493,9 +501,9 @@ class Context:
         _check(lib().sensei_gatv2_backward_workspace(ctypes.byref(A), f_in, f_out, ctypes.byref(need)), "sensei_gatv2_backward_workspace")
         self.ws.ensure(need.value)
         _check(lib().sensei_gatv2_backward(self._h, ctypes.byref(A), ctypes.byref(At), _ptr(t_pos), mat_struct(X), mat_struct(W_l), mat_struct(W_r),
-                                           _ptr(att), neg_slope, _ptr(Y), mat_struct(Y).ld if Y is not None else 0, mat_struct(dY), activation,
-                                           _ptr(dX), mat_struct(dX).ld if dX is not None else 0, _ptr(dWl), mat_struct(dWl).ld, _ptr(dWr),
-                                           mat_struct(dWr).ld, _ptr(da), self.ws.ptr, self.ws.nbytes, _stream()), "sensei_gatv2_backward")
+                                           _ptr(att), neg_slope, _ptr(Y), _ld(Y) if Y is not None else 0, mat_struct(dY), activation,
+                                           _ptr(dX), _ld(dX) if dX is not None else 0, _ptr(dWl), _ld(dWl), _ptr(dWr),
+                                           _ld(dWr), _ptr(da), self.ws.ptr, self.ws.nbytes, _stream()), "sensei_gatv2_backward")
         return dX, dWl, dWr, da
 
     def dotgat_backward(self, A: CsrStruct, At: CsrStruct, t_pos, X, W_q, W_k, W_v, scale, dY, Y=None, activation=ACT_NONE, want_dx=True):
@@ -509,9 +517,9 @@ class Context:
         _check(lib().sensei_dotgat_backward_workspace(ctypes.byref(A), f_in, d_k, f_out, ctypes.byref(need)), "sensei_dotgat_backward_workspace")
         self.ws.ensure(need.value)
         _check(lib().sensei_dotgat_backward(self._h, ctypes.byref(A), ctypes.byref(At), _ptr(t_pos), mat_struct(X), mat_struct(W_q), mat_struct(W_k),
-                                            mat_struct(W_v), scale, _ptr(Y), mat_struct(Y).ld if Y is not None else 0, mat_struct(dY), activation,
-                                            _ptr(dX), mat_struct(dX).ld if dX is not None else 0, _ptr(dWq), mat_struct(dWq).ld, _ptr(dWk),
-                                            mat_struct(dWk).ld, _ptr(dWv), mat_struct(dWv).ld, self.ws.ptr, self.ws.nbytes, _stream()),
+                                            mat_struct(W_v), scale, _ptr(Y), _ld(Y) if Y is not None else 0, mat_struct(dY), activation,
+                                            _ptr(dX), _ld(dX) if dX is not None else 0, _ptr(dWq), _ld(dWq), _ptr(dWk),
+                                            _ld(dWk), _ptr(dWv), _ld(dWv), self.ws.ptr, self.ws.nbytes, _stream()),
                "sensei_dotgat_backward")
         return dX, dWq, dWk, dWv
 
@@ -534,7 +542,7 @@ class Context:
         Y = torch.empty((A.n_rows, W.size(1)), dtype=torch.float32, device=self.device) if out is None else out
         self.ws.ensure(self.gat_workspace(A, X.size(1), W.size(1), comp_id))
         _check(lib().sensei_gat_layer(self._h, ctypes.byref(A), mat_struct(X), mat_struct(W), _ptr(a_l), _ptr(a_r), neg_slope,
-                                      _ptr(Y), mat_struct(Y).ld, activation, comp_id, self.ws.ptr, self.ws.nbytes, _stream()),
+                                      _ptr(Y), _ld(Y), activation, comp_id, self.ws.ptr, self.ws.nbytes, _stream()),
                "sensei_gat_layer")
         return Y
 
@@ -544,7 +552,7 @@ class Context:
         need = ctypes.c_size_t()
         _check(lib().sensei_sgc_workspace(ctypes.byref(A), X.size(1), W.size(1), comp_id, ctypes.byref(need)), "sensei_sgc_workspace")
         self.ws.ensure(need.value)
-        _check(lib().sensei_sgc_layer(self._h, ctypes.byref(A), _ptr(r), _ptr(c), mat_struct(X), mat_struct(W), k_hops, _ptr(Y), mat_struct(Y).ld,
+        _check(lib().sensei_sgc_layer(self._h, ctypes.byref(A), _ptr(r), _ptr(c), mat_struct(X), mat_struct(W), k_hops, _ptr(Y), _ld(Y),
                                       activation, comp_id, self.ws.ptr, self.ws.nbytes, _stream()), "sensei_sgc_layer")
         return Y
 
@@ -557,8 +565,8 @@ class Context:
         _check(lib().sensei_sgc_backward_workspace(ctypes.byref(A), f_in, f_out, k_hops, bwd_id, ctypes.byref(need)), "sensei_sgc_backward_workspace")
         self.ws.ensure(need.value)
         _check(lib().sensei_sgc_backward(self._h, ctypes.byref(A), ctypes.byref(At), _ptr(r), _ptr(c), mat_struct(X), mat_struct(W), k_hops, _ptr(Y),
-                                         mat_struct(Y).ld if Y is not None else 0, mat_struct(dY), activation, _ptr(dX),
-                                         mat_struct(dX).ld if dX is not None else 0, _ptr(dW), mat_struct(dW).ld, bwd_id, self.ws.ptr,
+                                         _ld(Y) if Y is not None else 0, mat_struct(dY), activation, _ptr(dX),
+                                         _ld(dX) if dX is not None else 0, _ptr(dW), _ld(dW), bwd_id, self.ws.ptr,
                                          self.ws.nbytes, _stream()), "sensei_sgc_backward")
         return dX, dW
 
@@ -572,8 +580,8 @@ class Context:
                "sensei_tagcn_backward_workspace")
         self.ws.ensure(need.value)
         _check(lib().sensei_tagcn_backward(self._h, ctypes.byref(A), ctypes.byref(At), _ptr(r), _ptr(c), mat_struct(X), mat_struct(W), k_hops, _ptr(Y),
-                                           mat_struct(Y).ld if Y is not None else 0, mat_struct(dY), activation, _ptr(dX),
-                                           mat_struct(dX).ld if dX is not None else 0, _ptr(dW), mat_struct(dW).ld, bwd_id, self.ws.ptr,
+                                           _ld(Y) if Y is not None else 0, mat_struct(dY), activation, _ptr(dX),
+                                           _ld(dX) if dX is not None else 0, _ptr(dW), _ld(dW), bwd_id, self.ws.ptr,
                                            self.ws.nbytes, _stream()), "sensei_tagcn_backward")
         return dX, dW
 
@@ -583,7 +591,7 @@ class Context:
         need = ctypes.c_size_t()
         _check(lib().sensei_tagcn_workspace(ctypes.byref(A), X.size(1), W.size(1), k_hops, comp_id, ctypes.byref(need)), "sensei_tagcn_workspace")
         self.ws.ensure(need.value)
-        _check(lib().sensei_tagcn_layer(self._h, ctypes.byref(A), _ptr(r), _ptr(c), mat_struct(X), mat_struct(W), k_hops, _ptr(Y), mat_struct(Y).ld,
+        _check(lib().sensei_tagcn_layer(self._h, ctypes.byref(A), _ptr(r), _ptr(c), mat_struct(X), mat_struct(W), k_hops, _ptr(Y), _ld(Y),
                                         activation, comp_id, self.ws.ptr, self.ws.nbytes, _stream()), "sensei_tagcn_layer")
         return Y
 
@@ -594,7 +602,7 @@ class Context:
         _check(lib().sensei_gatv2_workspace(ctypes.byref(A), X.size(1), W_r.size(1), comp_id, ctypes.byref(need)), "sensei_gatv2_workspace")
         self.ws.ensure(need.value)
         _check(lib().sensei_gatv2_layer(self._h, ctypes.byref(A), mat_struct(X), mat_struct(W_l), mat_struct(W_r), _ptr(att), neg_slope, _ptr(Y),
-                                        mat_struct(Y).ld, activation, comp_id, self.ws.ptr, self.ws.nbytes, _stream()), "sensei_gatv2_layer")
+                                        _ld(Y), activation, comp_id, self.ws.ptr, self.ws.nbytes, _stream()), "sensei_gatv2_layer")
         return Y
 
     def dotgat_layer(self, A: CsrStruct, X, W_q, W_k, W_v, scale, comp_id, activation=ACT_NONE, out=None):
@@ -604,7 +612,7 @@ class Context:
         _check(lib().sensei_dotgat_workspace(ctypes.byref(A), X.size(1), W_q.size(1), W_v.size(1), comp_id, ctypes.byref(need)), "sensei_dotgat_workspace")
         self.ws.ensure(need.value)
         _check(lib().sensei_dotgat_layer(self._h, ctypes.byref(A), mat_struct(X), mat_struct(W_q), mat_struct(W_k), mat_struct(W_v), scale, _ptr(Y),
-                                         mat_struct(Y).ld, activation, comp_id, self.ws.ptr, self.ws.nbytes, _stream()), "sensei_dotgat_layer")
+                                         _ld(Y), activation, comp_id, self.ws.ptr, self.ws.nbytes, _stream()), "sensei_dotgat_layer")
         return Y
 
     def gat_layer_heads(self, A: CsrStruct, X, W, a_l, a_r, n_heads, comp_id, neg_slope=0.2, activation=ACT_NONE, out=None):
@@ -612,7 +620,7 @@ class Context:
         Y = torch.empty((A.n_rows, W.size(1)), dtype=torch.float32, device=self.device) if out is None else out
         self.ws.ensure(self.gat_workspace(A, X.size(1), W.size(1), comp_id))
         _check(lib().sensei_gat_layer_heads(self._h, ctypes.byref(A), mat_struct(X), mat_struct(W), _ptr(a_l), _ptr(a_r), n_heads, neg_slope,
-                                            _ptr(Y), mat_struct(Y).ld, activation, comp_id, self.ws.ptr, self.ws.nbytes, _stream()),
+                                            _ptr(Y), _ld(Y), activation, comp_id, self.ws.ptr, self.ws.nbytes, _stream()),
                "sensei_gat_layer_heads")
         return Y
 
