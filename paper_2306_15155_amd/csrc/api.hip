@@ -248,6 +248,9 @@ hipError_t spmm_any(const sensei_csr &A, int mode, const float *r, const float *
                     bool val_in_panel_order = false, const float2 *mz = nullptr, bool b_sliced = false, bool c_sliced = false,
                     const AttnVectors *attn = nullptr) {
     // attn: softmax mode on a pattern with a dense-tile split; A.val then holds the logits of the remainder, in its order
+    // A slice-major operand is gathered in whole slices, its pad columns are zeros: what decides is the padded width, whichever width the caller
+    // names (transposed aggregation of 41 columns over 115 M entries: 1,560 us unsplit, 790 on the split that 64 columns take).
+    if (b_sliced) f = pad32(f);
     const bool has_val = (mode == SENSEI_SPMM_WEIGHTED || mode == kSpmmSoftmax);
     if (tiles_usable(A, mode, f, b_sliced, attn != nullptr)) {
         // The hub tiles go to the matrix cores, the sparse remainder runs as an SpMM; a last pass joins the two raw sums and
