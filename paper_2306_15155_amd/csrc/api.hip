@@ -133,6 +133,8 @@ ChunkPlan make_plan(const sensei_csr &A, Carver &cv) {
     return p;
 }
 
+constexpr int kFindRowsChunks = 8192;
+
 bool gcn_is_agg(int id) { return id == SENSEI_GCN_DYN_AGG || id == SENSEI_GCN_DYNF_AGG || id == SENSEI_GCN_PRE_AGG; }
 
 // A slice-major copy of a user matrix the SpMM gathers from costs one pass over it (8 bytes per element); it pays
@@ -357,6 +359,12 @@ int run_gcn(const sensei_csr &A, const float *r, const float *c, const sensei_ma
             else SENSEI_TRY(launch_row_broadcast(scale, X.ptr, X.ld, A.n_cols, f_in, T, fs, SENSEI_ACT_NONE, s, nullptr, 0, &side));
             src = T;
             if (!sliced) ld_src = fs;
+        }
+        // a walk over X itself is the call's first launch: on few chunks its wavefronts find their own rows (about 2 us) instead of waiting for a
+        // launch that does (5 us, and as much again on the host)
+        if (side.blocks > 0 && plan.n_chunks <= kFindRowsChunks) {
+            plan.pending = true;
+            side = SideWork();
         }
         SENSEI_TRY(launch_side(&side, s));
         const bool scaled = (mode == SENSEI_SPMM_SCALED);

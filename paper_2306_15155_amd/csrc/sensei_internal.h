@@ -19,6 +19,7 @@ struct ChunkPlan {
     int chunk_nnz;        // T: non-zeros per chunk, multiple of 64
     int n_chunks;         // max(1, ceil(nnz / T))
     int32_t *chunk_row;   // device, n_chunks + 1: first row starting at or after c*T; [n_chunks] = n_rows
+    bool pending = false; // chunk_row is not filled in yet: launch_spmm sees to it (its wavefronts find their rows where that is cheaper than a launch)
 };
 
 // Small work that nothing before it on the stream produces and the next kernels need: the chunk boundaries of up to two patterns (a

@@ -63,6 +63,7 @@ struct SpmmArgs {
     int tiles_live, n_groups;  // feature tiles worked on at the same time; chunk groups (blocks per tile)
     int accumulate, finalize;  // column panels: add to what C holds; apply row scale and activation (last panel only)
     int fix_quads;      // k_spmm_fixup: groups of four columns per workgroup
+    int32_t *find_rows; // k_spmm_flat: chunk_row is still to be filled in (null: it is there)
     int scale_weights;  // k_spmm_flat: the row factor (or 1 / z) is applied to the weights of the entries, by every panel pass
     // fused attention mode: the two score vectors, the LeakyReLU slope, and where the (max, sum) pairs of row pieces go
     const float *s_l, *s_r;
@@ -128,12 +129,11 @@ template <int PER> struct ChunkSpan {
 
 // empty(r0, none) is called for every 64 rows of the chunk, by all lanes: `none` says that row r0 + lane is owned and has no entries
 template <int PER, int PAD = 0, int PARTS = 8, class Empty>
-__device__ __forceinline__ FlatChunk<PER> flat_rows(const NnzArgs &a, int chunk, int lane, int *rows, Empty empty) {
+__device__ __forceinline__ FlatChunk<PER> flat_rows_from(const NnzArgs &a, int chunk, int i0, int i1, int lane, int *rows, Empty empty) {
     FlatChunk<PER> c;
     c.lo = chunk * (64 * PER);
     c.hi = (a.nnz - c.lo > 64 * PER) ? c.lo + 64 * PER : a.nnz;
-    const int i0 = __builtin_amdgcn_readfirstlane(a.chunk_row[chunk]);
-    c.i1 = __builtin_amdgcn_readfirstlane(a.chunk_row[chunk + 1]);
+    c.i1 = i1;
     // rows from i0 - 1 on, the one that may go on from the chunk before: whether it does is in the first lane's own row pointers
     const int r_first = i0 > 0 ? i0 - 1 : 0;
     int s = 0, e = 0;
@@ -181,6 +181,36 @@ __device__ __forceinline__ FlatChunk<PER> flat_rows(const NnzArgs &a, int chunk,
     }
     lds_exchange();
     return c;
+}
+
+template <int PER, int PAD = 0, int PARTS = 8, class Empty>
+__device__ __forceinline__ FlatChunk<PER> flat_rows(const NnzArgs &a, int chunk, int lane, int *rows, Empty empty) {
+    return flat_rows_from<PER, PAD, PARTS>(a, chunk, __builtin_amdgcn_readfirstlane(a.chunk_row[chunk]), __builtin_amdgcn_readfirstlane(a.chunk_row[chunk + 1]), lane,
+                                           rows, empty);
+}
+
+// The first rows starting at or after the two ends of a chunk, found by the wavefront itself: both row pointers' places narrowed 64-fold a round.
+__device__ __forceinline__ int2 find_chunk_rows(const NnzArgs &a, int chunk, int lane) {
+    const long long t0 = (long long)chunk * a.chunk_nnz, t1 = t0 + a.chunk_nnz;
+    // invariant: row_ptr[lo - 1] < target (or lo = 0), row_ptr[hi] >= target (or hi = n_rows)
+    int lo0 = 0, hi0 = a.n_rows, lo1 = 0, hi1 = a.n_rows;
+    while (lo0 < hi0 || lo1 < hi1) {
+        const int s0 = (hi0 - lo0 + 64) / 65, s1 = (hi1 - lo1 + 64) / 65;   // lane l looks s (l + 1) - 1 places behind lo
+        const int p0 = lo0 + s0 * (lane + 1) - 1, p1 = lo1 + s1 * (lane + 1) - 1;
+        const int n0 = __popcll(__ballot(p0 < hi0 && (long long)a.row_ptr[p0 < hi0 ? p0 : hi0] < t0));
+        const int n1 = __popcll(__ballot(p1 < hi1 && (long long)a.row_ptr[p1 < hi1 ? p1 : hi1] < t1));
+        if (lo0 < hi0) {   // the probe after the last smaller one bounds the place from above, if there is one
+            lo0 += s0 * n0;
+            if (n0 < 64 && lo0 + s0 - 1 < hi0) hi0 = lo0 + s0 - 1;
+            if (lo0 > hi0) lo0 = hi0;
+        }
+        if (lo1 < hi1) {
+            lo1 += s1 * n1;
+            if (n1 < 64 && lo1 + s1 - 1 < hi1) hi1 = lo1 + s1 - 1;
+            if (lo1 > hi1) lo1 = hi1;
+        }
+    }
+    return make_int2(lo0, chunk + 1 < a.n_chunks ? lo1 : a.n_rows);
 }
 
 // Segmented sum of v (blocked order; entries past the end of the chunk hold 0): write(row, sum, place of the piece's last entry) once per
@@ -730,7 +760,20 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
             if (MODE == SENSEI_SPMM_WEIGHTED || MODE == kSpmmSoftmax) es[u] = a.val[k * a.val_stride];
         }
     }
-    const FlatChunk<PER> c = flat_rows<PER, PAD, G>(nz, chunk, lane, rows, [&](int r0, bool none) {
+    int i0, i1;
+    if (a.find_rows) {   // nobody has: for the fix-up to read, too
+        const int2 ends = find_chunk_rows(nz, chunk, lane);
+        i0 = ends.x;
+        i1 = ends.y;
+        if (tile == 0 && lane == 0) {
+            a.find_rows[chunk] = i0;
+            if (chunk + 1 == a.n_chunks) a.find_rows[chunk + 1] = i1;
+        }
+    } else {
+        i0 = __builtin_amdgcn_readfirstlane(a.chunk_row[chunk]);
+        i1 = __builtin_amdgcn_readfirstlane(a.chunk_row[chunk + 1]);
+    }
+    const FlatChunk<PER> c = flat_rows_from<PER, PAD, G>(nz, chunk, i0, i1, lane, rows, [&](int r0, bool none) {
         unsigned long long m = __ballot(none);
         for (int b = 0; m; ++b, m >>= G) {   // rows without entries: one per group at a time
             if (!((m >> g) & 1ull)) continue;
@@ -2946,9 +2989,11 @@ hipError_t launch_spmm(const sensei_csr &A, int mode, const float *r, const floa
     const bool off32 = (unsigned long long)(A.n_cols > 0 ? A.n_cols : 1) * (unsigned long long)ldb * 4ull + 4ull * (unsigned long long)f <= 0xffffffffull &&
                        A.n_cols < (1 << 24) && ldb * 4 < (1 << 24);
     hipError_t err;
+    const bool by_rows = sh.vec == 4 && spmm_by_rows(A, mode, f, b_sliced, sh.n_tiles), flat = sh.vec == 4 && !by_rows;
+    a.find_rows = p.pending && flat && A.nnz > 0 ? p.chunk_row : nullptr;
+    if (p.pending && !a.find_rows && (err = launch_chunk_rows(A, p, s)) != hipSuccess) return err;
     hipEvent_t t0 = timer ? timer->next() : nullptr, t1 = t0 ? timer->next() : nullptr;
     if (t1 && hipEventRecord(t0, s) != hipSuccess) return hipErrorUnknown;
-    const bool by_rows = sh.vec == 4 && spmm_by_rows(A, mode, f, b_sliced, sh.n_tiles), flat = sh.vec == 4 && !by_rows;
     if (by_rows) err = off32 ? spmm_rows_pattern<true>(a, sh.lpg, grid, s) : spmm_rows_pattern<false>(a, sh.lpg, grid, s);
     else if (flat && sh.lpg == 8) err = off32 ? spmm_flat_mode<8, true>(a, mode, grid, s) : spmm_flat_mode<8, false>(a, mode, grid, s);
     else if (flat) err = sh.lpg == 16 ? spmm_flat_mode<16, false>(a, mode, grid, s) : sh.lpg == 32 ? spmm_flat_mode<32, false>(a, mode, grid, s)
