@@ -1,0 +1,77 @@
+"""The two-walk backward of narrow heads and of the GATv2 score where they can go wrong, against the oracle: rows that span many chunks beside
+empty rows, fewer destinations than sources, widths inside a 32-column slice and across slices, more heads than one launch takes, a pattern
+without entries.  Bound: the parity tolerance per element (fp32 sums of at most a few thousand terms of order one)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from paper_2306_15155_amd import ACT_NONE, ACT_RELU, Context
+
+from gpu_util import DeviceCSR, assert_close, dev, hub_and_empty_graph, rect_block
+
+pytestmark = pytest.mark.gpu
+
+PATTERNS = {"hub": lambda: hub_and_empty_graph(3, 900, 5_000, 700, 40), "wide": lambda: rect_block(4, 260, 900, 9), "one": lambda: rect_block(5, 1, 6, 3)}
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = Context(0)
+    yield c
+    c.close()
+
+
+def _patterns(ctx, name):
+    g = PATTERNS[name]()
+    rows = np.repeat(np.arange(g.n_rows), np.diff(g.row_ptr))
+    gt = synth.build_csr(g.n_cols, g.n_rows, g.col_idx.astype(np.int32), rows.astype(np.int32), False, False)
+    A, At = DeviceCSR(g), DeviceCSR(gt)
+    return g, A, At, ctx.transpose_positions(A.s, At.s)
+
+
+@pytest.mark.parametrize("name", PATTERNS)
+@pytest.mark.parametrize("heads,d", [(1, 8), (3, 20), (2, 32), (17, 8), (4, 31)])
+def test_narrow_heads(ctx, name, heads, d):
+    g, A, At, pos = _patterns(ctx, name)
+    f_in, f_out = 36, heads * d
+    X, W = synth.uniform(7, 1, (g.n_cols, f_in), -0.5, 0.5), synth.glorot(7, 2, f_in, f_out)
+    a_l, a_r = synth.normal(7, 3, (f_out,), 0.0, 0.3), synth.normal(7, 4, (f_out,), 0.0, 0.3)
+    dY = synth.normal(7, 5, (g.n_rows, f_out), 0.0, 1.0)
+    for act in (ACT_NONE, ACT_RELU):
+        Y = oracle.gat_layer_heads(g.n_rows, g.n_cols, g.row_ptr, g.col_idx, X, W, a_l, a_r, heads, 0.2, act)
+        for comp in (0, 1):
+            assert_close(ctx.gat_layer_heads(A.s, dev(X), dev(W), dev(a_l), dev(a_r), heads, comp, 0.2, act), Y, what=f"Y {comp}")
+        Y = Y.astype(np.float32)
+        want = oracle.gat_backward_heads(g.n_rows, g.n_cols, g.row_ptr, g.col_idx, X, W, a_l, a_r, heads, dY, Y=Y, slope=0.2, act=act)
+        got = ctx.gat_backward_heads(A.s, At.s, pos, dev(X), dev(W), dev(a_l), dev(a_r), heads, dev(dY), Y=dev(Y), neg_slope=0.2, activation=act)
+        for what, a, b in zip(("dX", "dW", "da_l", "da_r"), got, want):
+            assert_close(a, b, what=f"{what} act {act}")
+
+
+@pytest.mark.parametrize("name", PATTERNS)
+@pytest.mark.parametrize("f_out", [1, 31, 64, 97])
+def test_gatv2_score(ctx, name, f_out):
+    g, A, At, pos = _patterns(ctx, name)
+    f_in = 21
+    X = synth.uniform(8, 1, (g.n_cols, f_in), -0.5, 0.5)
+    W_l, W_r, att = synth.glorot(8, 2, f_in, f_out), synth.glorot(8, 3, f_in, f_out), synth.normal(8, 4, (f_out,), 0.0, 0.3)
+    dY = synth.normal(8, 5, (g.n_rows, f_out), 0.0, 1.0)
+    Y = oracle.gatv2_layer(g.n_rows, g.n_cols, g.row_ptr, g.col_idx, X, W_l, W_r, att, 0.2, ACT_RELU).astype(np.float32)
+    for act in (ACT_NONE, ACT_RELU):
+        want = oracle.gatv2_backward(g.n_rows, g.n_cols, g.row_ptr, g.col_idx, X, W_l, W_r, att, dY, Y=Y, slope=0.2, act=act)
+        got = ctx.gatv2_backward(A.s, At.s, pos, dev(X), dev(W_l), dev(W_r), dev(att), dev(dY), Y=dev(Y), neg_slope=0.2, activation=act)
+        for what, a, b in zip(("dX", "dW_l", "dW_r", "datt"), got, want):
+            assert_close(a, b, what=f"{what} act {act}")
+
+
+def test_no_entries(ctx):
+    ptr, col = np.zeros(6, dtype=np.int32), np.zeros(0, dtype=np.int32)
+    g = synth.CSR(n_rows=5, n_cols=5, row_ptr=ptr, col_idx=col)
+    A = DeviceCSR(g)
+    pos = ctx.transpose_positions(A.s, A.s)
+    X, W, a, dY = torch.ones(5, 8, device="cuda"), torch.ones(8, 32, device="cuda"), torch.ones(32, device="cuda"), torch.ones(5, 32, device="cuda")
+    for got in (ctx.gat_backward_heads(A.s, A.s, pos, X, W, a, a, 4, dY, neg_slope=0.2), ctx.gatv2_backward(A.s, A.s, pos, X, W, W, a, dY, neg_slope=0.2)):
+        assert all(bool((t == 0).all()) for t in got)
+    torch.cuda.synchronize()
