@@ -1410,14 +1410,13 @@ int run_gat_backward(const sensei_csr &A, const sensei_csr &At, const int32_t *t
         SENSEI_TRY(launch_gat_dalpha(A, theta, T, f_out, logits, stats, dt, rowdot, plan, sum_carry, s));
     }
     SENSEI_TRY(launch_gat_dt(A, logits, dt, rowdot, stats, t_pos, slope, nullptr, adt_t, plan, s, ds_l, sum_carry));
-    SENSEI_TRY(launch_row_sum(At, reinterpret_cast<const float *>(adt_t) + 1, 2, ds_r, plan_t, sum_carry, s));
     // dTheta = alpha^T.dP + ds_l a_l^T + ds_r a_r^T
     if (split_t) {
-        // the remainder of the transposed pattern with its coefficients copied into its own order; the tiles' share was started above
+        // the remainder of the transposed pattern, its coefficients copied into its own order on the way; the tiles' share was started above
         const sensei_tiles &D = *At.tiles;
         float *alpha_rem = cv.take<float>((size_t)(D.nnz_rem > 0 ? D.nnz_rem : 1));
         const bool pm = remainder_panels_usable(D, f_out);   // the panel-major copy of the remainder, as in the forward aggregation
-        SENSEI_TRY(launch_compact_values(At.nnz, D.dst_rem, reinterpret_cast<const float *>(adt_t), 2, alpha_rem, s, pm ? D.pos_pm : nullptr));
+        SENSEI_TRY(launch_row_sum(At, reinterpret_cast<const float *>(adt_t), 2, ds_r, plan_t, sum_carry, s, D.dst_rem, pm ? D.pos_pm : nullptr, alpha_rem));
         sensei_csr Ar = At;
         Ar.nnz = D.nnz_rem; Ar.row_ptr = D.row_ptr_rem; Ar.col_idx = D.col_rem; Ar.val = alpha_rem; Ar.panels = nullptr; Ar.tiles = nullptr;
         if (pm) {
@@ -1435,6 +1434,7 @@ int run_gat_backward(const sensei_csr &A, const sensei_csr &At, const int32_t *t
                                             D.plan_rem.chunk_nnz, carry, fo32));
         }
     } else {
+        SENSEI_TRY(launch_row_sum(At, reinterpret_cast<const float *>(adt_t) + 1, 2, ds_r, plan_t, sum_carry, s));
         sensei_csr Aw = At;
         Aw.val = reinterpret_cast<const float *>(adt_t);
         Aw.panels = nullptr;  // the values follow the order of At itself

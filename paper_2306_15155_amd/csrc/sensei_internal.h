@@ -192,8 +192,11 @@ hipError_t launch_panel_stats(const PanelWalk *panels, int n_panels, int width, 
                               float2 *seg_stats, float2 *seg_carry, float2 *stats, hipStream_t s);
 
 // ---- backward of the attention layer
-// out[i] = sum of val[k * stride] over the entries k of row i; carry: n_chunks floats
-hipError_t launch_row_sum(const sensei_csr &A, const float *val, int stride, float *out, const ChunkPlan &p, float *carry, hipStream_t s);
+// out[i] = sum of val[k * stride] over the entries k of row i; carry: n_chunks floats.  With dst_rem, val holds pairs (8-byte aligned) of which the
+// second is summed and the first of the entries that stay in the sparse remainder (dst_rem[k] >= 0) goes to first_rem[dst_rem[k]], or to
+// first_rem[place[dst_rem[k]]] where the remainder has another order
+hipError_t launch_row_sum(const sensei_csr &A, const float *val, int stride, float *out, const ChunkPlan &p, float *carry, hipStream_t s,
+                          const int32_t *dst_rem = nullptr, const int32_t *place = nullptr, float *first_rem = nullptr);
 // dalpha[k] = <dP[i,:], Theta[j,:]> per stored entry, rowdot[i] = sum_j alpha_ij dalpha_ij (skipped when rowdot is null); theta, dP slice-major
 hipError_t launch_gat_dalpha(const sensei_csr &A, const float *theta, const float *dP, int f, const float *logits, const float2 *mz,
                              float *dalpha, float *rowdot, const ChunkPlan &p, float *carry, hipStream_t s, float scale = 1.f, int dp_rows = 0);
@@ -284,9 +287,6 @@ hipError_t launch_tile_split(const sensei_csr &A, const ChunkPlan &p, const int3
                              const int32_t *slot_of, int n_slots, unsigned *bits, int32_t *pos, int32_t *scan_temp, int32_t *col_rem,
                              int32_t *dst_rem, int32_t *row_ptr_rem, hipStream_t s);
 hipError_t launch_zero_matrix(float *C, int64_t n, int f, int64_t ldc, bool sliced, hipStream_t s);
-// out[dst_rem[k]] = src[k * stride] for the entries k of the pattern that stay in the sparse remainder (dst_rem[k] >= 0)
-hipError_t launch_compact_values(int64_t nnz, const int32_t *dst_rem, const float *src, int stride, float *out, hipStream_t s,
-                                 const int32_t *place = nullptr);
 // T.dh[rank, 0:f) = (kept tiles of the rank's row of tiles) . B, raw sums; B slice-major with f (a multiple of 32) columns;
 // Bh: nt_c * 128 * f floats.  With s_l, s_r, mz (attention mode) entry (i, j) of a tile weighs
 // exp(LeakyReLU(s_l[i] + s_r[j]) - mz[i].x) instead of 1.  `transposed` (attention mode only): T holds the tiles of the transposed

@@ -1829,16 +1829,6 @@ __global__ __launch_bounds__(kBlock) void k_rem_scatter(NnzArgs a, const int32_t
     }
 }
 
-// values of the entries that stay sparse, moved from the order of the pattern to the order of the remainder (place: to the place of
-// every remainder entry in another order of the remainder, its panel-major copy)
-__global__ __launch_bounds__(kBlock) void k_compact_values(long long nnz, const int32_t *__restrict__ dst_rem, const float *__restrict__ src, int stride,
-                                                            float *__restrict__ out, const int32_t *__restrict__ place) {
-    const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nnz) return;
-    const int d = dst_rem[k];
-    if (d >= 0) out[place ? place[d] : d] = src[k * stride];
-}
-
 __global__ void k_rem_rowptr(const int32_t *__restrict__ row_ptr, int n_rows, const int32_t *__restrict__ pos, int32_t *__restrict__ row_ptr_rem) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i <= n_rows) row_ptr_rem[i] = pos[row_ptr[i]];
@@ -1877,18 +1867,49 @@ __global__ __launch_bounds__(kBlock) void k_sum_fixup(NnzArgs a, float *__restri
                });
 }
 
-// out[i] = sum of val over the stored entries of row i.  2.1 M values at stride 2, 100,000 rows: 173 -> 7 us.
-template <int PER>
+// where an entry's weight goes: to its place among the entries outside kept tiles (dst_rem < 0: inside one), itself looked up in `place` where
+// those have an order of their own
+struct RemWeights {
+    const int32_t *dst_rem;
+    const int32_t *place;
+    float *out;
+};
+
+// out[i] = sum of val over the stored entries of row i.  2.1 M values at stride 2, 100,000 rows: 173 -> 7 us.  COMPACT: val is the second of
+// the pairs (alpha, ds), and the first is copied into the remainder's order in the same pass; the kernel is bound by the pairs' bytes, which a
+// pass for the copy read again (GAT training on 115 M entries, where it runs beside the tiles' products: 17.44 -> 17.37 ms).
+template <int PER, bool COMPACT>
 __global__ __launch_bounds__(kBlock) void k_row_sum(NnzArgs a, const float *__restrict__ val, int stride, float *__restrict__ out,
-                                                     float *__restrict__ carry) {
+                                                     float *__restrict__ carry, RemWeights rem) {
     __shared__ FlatLds<PER> lds;
     const int chunk = wave_chunk(), lane = threadIdx.x & 63;
     if (chunk >= a.n_chunks) return;
-    float vs[PER], v[PER];
+    float vs[PER], v[PER], w[COMPACT ? PER : 1];
+    int to[COMPACT ? PER : 1];
     if (a.nnz > 0) {
         const ChunkSpan<PER> span(a, chunk);
 #pragma unroll
-        for (int u = 0; u < PER; ++u) vs[u] = val[(size_t)span.at(u, lane) * stride];
+        for (int u = 0; u < PER; ++u) {
+            const size_t k = span.at(u, lane);
+            if constexpr (COMPACT) {
+                const float2 p = reinterpret_cast<const float2 *>(val)[k];
+                w[u] = p.x;
+                vs[u] = p.y;
+                to[u] = span.lo + u * 64 + lane < span.hi ? rem.dst_rem[k] : -1;
+            } else {
+                vs[u] = val[k * stride];
+            }
+        }
+        if constexpr (COMPACT) {
+            if (rem.place) {
+#pragma unroll
+                for (int u = 0; u < PER; ++u)
+                    if (to[u] >= 0) to[u] = rem.place[to[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < PER; ++u)
+                if (to[u] >= 0) rem.out[to[u]] = w[u];
+        }
     }
     const FlatChunk<PER> c = flat_rows<PER>(a, chunk, lane, lds.row[threadIdx.x >> 6], [&](int r0, bool none) { if (none) out[r0 + lane] = 0.f; });
     if (c.lo >= c.hi) return;
@@ -3147,10 +3168,14 @@ hipError_t launch_panel_stats(const PanelWalk *panels, int n_panels, int width, 
 
 // ------------------------------------------------------------ backward of the attention layer (host side)
 
-hipError_t launch_row_sum(const sensei_csr &A, const float *val, int stride, float *out, const ChunkPlan &p, float *carry, hipStream_t s) {
+hipError_t launch_row_sum(const sensei_csr &A, const float *val, int stride, float *out, const ChunkPlan &p, float *carry, hipStream_t s,
+                          const int32_t *dst_rem, const int32_t *place, float *first_rem) {
     const NnzArgs n = nnz_args(A, p);
+    const RemWeights rem = {dst_rem, place, first_rem};
     return with_per(p.chunk_nnz, [&](auto per) {
-        hipLaunchKernelGGL(k_row_sum<per()>, dim3(blocks_for(p.n_chunks, kWavesPerBlock)), dim3(kBlock), 0, s, n, val, stride, out, carry);
+        const dim3 grid(blocks_for(p.n_chunks, kWavesPerBlock));
+        if (dst_rem) hipLaunchKernelGGL((k_row_sum<per(), true>), grid, dim3(kBlock), 0, s, n, val, 2, out, carry, rem);
+        else hipLaunchKernelGGL((k_row_sum<per(), false>), grid, dim3(kBlock), 0, s, n, val, stride, out, carry, rem);
         if (p.n_chunks > 1) hipLaunchKernelGGL(k_sum_fixup, dim3(blocks_for(p.n_chunks - 1, kBlock)), dim3(kBlock), 0, s, n, out, carry);
     });
 }
@@ -3428,12 +3453,6 @@ hipError_t launch_tile_split(const sensei_csr &A, const ChunkPlan &p, const int3
     if (A.nnz > 0) hipLaunchKernelGGL(k_rem_scatter, dim3(blocks_for(A.nnz, kBlock)), dim3(kBlock), 0, s, nnz_args(A, p), (const int32_t *)pos, col_rem, dst_rem);
     hipLaunchKernelGGL(k_rem_rowptr, dim3(blocks_for((long long)A.n_rows + 1, kBlock)), dim3(kBlock), 0, s, A.row_ptr, A.n_rows, (const int32_t *)pos,
                        row_ptr_rem);
-    return hipGetLastError();
-}
-
-hipError_t launch_compact_values(int64_t nnz, const int32_t *dst_rem, const float *src, int stride, float *out, hipStream_t s, const int32_t *place) {
-    if (nnz <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_compact_values, dim3(blocks_for(nnz, kBlock)), dim3(kBlock), 0, s, (long long)nnz, dst_rem, src, stride, out, place);
     return hipGetLastError();
 }
 
