@@ -229,7 +229,7 @@ int sensei_chunk_nnz(int64_t nnz);
 
 /* Which matrix-core kernel sensei_gemm (and the GEMM inside the layers) takes for an n x k by k x m product: the fp32 instruction,
  * or, for large products, the bf16 instruction on three exact bf16 pieces per fp32 operand element with six piece products per
- * term (what is left out is below 2^-21 of a term, 2^-24.7 on average: over many terms the result is as accurate as the fp32
+ * term (what is left out is below 2^-26 of a term: over many terms the result is as accurate as the fp32
  * instruction's, at several times its rate).  Host arithmetic; for reports that price the kernel against the right matrix-core peak. */
 enum { SENSEI_GEMM_FP32 = 0, SENSEI_GEMM_BF16_PIECES = 1 };
 int sensei_gemm_kernel(int64_t n, int k, int m);
