@@ -13,6 +13,7 @@
 #include <cfloat>
 #include <type_traits>
 
+#include "row_search.h"
 #include "sensei_internal.h"
 
 namespace sensei {
@@ -189,28 +190,17 @@ __device__ __forceinline__ FlatChunk<PER> flat_rows(const NnzArgs &a, int chunk,
                                            rows, empty);
 }
 
-// The first rows starting at or after the two ends of a chunk, found by the wavefront itself: both row pointers' places narrowed 64-fold a round.
+// The first rows starting at or after the two ends of a chunk, found by the wavefront itself: both row pointers' places narrowed together.
 __device__ __forceinline__ int2 find_chunk_rows(const NnzArgs &a, int chunk, int lane) {
     const long long t0 = (long long)chunk * a.chunk_nnz, t1 = t0 + a.chunk_nnz;
-    // invariant: row_ptr[lo - 1] < target (or lo = 0), row_ptr[hi] >= target (or hi = n_rows)
-    int lo0 = 0, hi0 = a.n_rows, lo1 = 0, hi1 = a.n_rows;
-    while (lo0 < hi0 || lo1 < hi1) {
-        const int s0 = (hi0 - lo0 + 64) / 65, s1 = (hi1 - lo1 + 64) / 65;   // lane l looks s (l + 1) - 1 places behind lo
-        const int p0 = lo0 + s0 * (lane + 1) - 1, p1 = lo1 + s1 * (lane + 1) - 1;
-        const int n0 = __popcll(__ballot(p0 < hi0 && (long long)a.row_ptr[p0 < hi0 ? p0 : hi0] < t0));
-        const int n1 = __popcll(__ballot(p1 < hi1 && (long long)a.row_ptr[p1 < hi1 ? p1 : hi1] < t1));
-        if (lo0 < hi0) {   // the probe after the last smaller one bounds the place from above, if there is one
-            lo0 += s0 * n0;
-            if (n0 < 64 && lo0 + s0 - 1 < hi0) hi0 = lo0 + s0 - 1;
-            if (lo0 > hi0) lo0 = hi0;
-        }
-        if (lo1 < hi1) {
-            lo1 += s1 * n1;
-            if (n1 < 64 && lo1 + s1 - 1 < hi1) hi1 = lo1 + s1 - 1;
-            if (lo1 > hi1) lo1 = hi1;
-        }
+    RowSearch first = {0, a.n_rows}, last = first;
+    while (first.open() || last.open()) {
+        const int p0 = first.place(lane), p1 = last.place(lane);
+        const long long v0 = a.row_ptr[p0], v1 = a.row_ptr[p1];   // row_ptr[n_rows] exists: both are read whether they count or not
+        first.narrow(__popcll(__ballot(p0 < first.hi && v0 < t0)));
+        last.narrow(__popcll(__ballot(p1 < last.hi && v1 < t1)));
     }
-    return make_int2(lo0, chunk + 1 < a.n_chunks ? lo1 : a.n_rows);
+    return make_int2(first.lo, chunk + 1 < a.n_chunks ? last.lo : a.n_rows);
 }
 
 // Segmented sum of v (blocked order; entries past the end of the chunk hold 0): write(row, sum, place of the piece's last entry) once per
