@@ -272,17 +272,40 @@ typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));   // 16-byte load at any word: the vector memory unit needs no more alignment
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
-// Two elements -> their three pieces, packed as pairs (first in the low half).  The largest finite values round up to infinity, so the first
-// piece is cut from the value clamped to the largest finite bf16; what is left over still fits the other two.  The second is clamped for the sake
-// of infinities, which then end up in the third piece alone (inf - inf nowhere): a product with one is infinite or NaN as in fp32.
+// Two elements -> their three pieces, packed as pairs (first in the low half).  An element that is infinite, NaN or rounds up to infinity makes
+// every sum it enters infinite or NaN; those sums are formed again on the fp32 instruction (product_fp32).
 __device__ __forceinline__ void cut_pair(float x, float y, unsigned &hi, unsigned &mid, unsigned &lo) {
-    constexpr float kMaxBf = 3.3895313892515355e38f;
     auto pack = [](float a, float b) { const floatx2 v = {a, b}; return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2)); };
-    hi = pack(__builtin_amdgcn_fmed3f(x, -kMaxBf, kMaxBf), __builtin_amdgcn_fmed3f(y, -kMaxBf, kMaxBf));
+    hi = pack(x, y);
     x -= __uint_as_float(hi << 16);
     y -= __uint_as_float(hi & 0xFFFF0000u);
-    mid = pack(__builtin_amdgcn_fmed3f(x, -kMaxBf, kMaxBf), __builtin_amdgcn_fmed3f(y, -kMaxBf, kMaxBf));
+    mid = pack(x, y);
     lo = pack(x - __uint_as_float(mid << 16), y - __uint_as_float(mid & 0xFFFF0000u));
+}
+
+// whether any of a lane's sums is infinite or NaN
+template <int N>
+__device__ __forceinline__ bool not_finite(const floatx16 (&acc)[N]) {
+    float t = 0.f;
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) t = fmaf(acc[j][r], 0.f, t);
+    return t != 0.f;   // 0 from finite sums, NaN otherwise
+}
+
+// 32 x 32 sums over k on the fp32 instruction, operands straight from memory: a(q), b(q) are this lane's elements of its row and its column at q
+template <class A, class B>
+__device__ __forceinline__ floatx16 product_fp32(int k, int kh, A a, B b) {
+    floatx16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll 4
+    for (int k0 = 0; k0 < k; k0 += 2) {
+        const int q = k0 + kh;
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(q < k ? a(q) : 0.f, q < k ? b(q) : 0.f, acc, 0, 0, 0);
+    }
+    return acc;
 }
 
 __device__ __forceinline__ void split_bf16x3(float v, unsigned &hi, unsigned &mid, unsigned &lo) {
@@ -345,25 +368,24 @@ __global__ __launch_bounds__(kGemmThreads, 2 * gemm_held(TN)) void k_gemm_bf(Gem
         row0 = rest * 8;
         at = (unsigned)((rest >> 1) * STEP_BYTES + (c >> 5) * 1024 + (rest & 1) * 512 + (c & 31) * 16);
     };
-    auto fetch_w = [&](int k0, int c, int row0, float (&w)[8]) {
+    auto fetch_w = [&](int k0, int c, int row0, float (&w)[8]) {   // uniform base, lane offset; rows past k read a row that exists
         const unsigned col_off = (unsigned)((n0 + c < g.m ? n0 + c : g.m - 1) * 4);
         const unsigned off = (unsigned)(row0 * (unsigned)g.ldw * 4u) + col_off;
-        const bool col_ok = n0 + c < g.m;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {   // uniform base, lane offset; rows past k read a row that exists and are cleared (masks, not branches)
+        for (int e = 0; e < 8; ++e) {
             const int kb = k0 + e < g.k ? k0 + e : g.k - 1;
-            const bool ok = k0 + row0 + e < g.k;
             const char *base = reinterpret_cast<const char *>(g.W + (long long)kb * g.ldw);
-            const float v = *reinterpret_cast<const float *>(base + (ok ? off : col_off));
-            w[e] = __uint_as_float(__float_as_uint(v) & (ok && col_ok ? ~0u : 0u));
+            w[e] = *reinterpret_cast<const float *>(base + (k0 + row0 + e < g.k ? off : col_off));
         }
     };
-    auto stash_w = [&](unsigned char *dst, const float (&w)[8]) {
+    // what lies past k or m is cleared here and not where it is fetched: there the compiler waits for every load by itself
+    auto stash_w = [&](unsigned char *dst, int k0, int c, int row0, float (&w)[8]) {
+        const int live = n0 + c < g.m ? g.k - k0 - row0 : 0;
         uintx4 p[3];
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
             unsigned a, b, c;
-            cut_pair(w[2 * d], w[2 * d + 1], a, b, c);
+            cut_pair(2 * d < live ? w[2 * d] : 0.f, 2 * d + 1 < live ? w[2 * d + 1] : 0.f, a, b, c);
             p[0][d] = a; p[1][d] = b; p[2][d] = c;
         }
 #pragma unroll
@@ -497,6 +519,12 @@ __global__ __launch_bounds__(kGemmThreads, 2 * gemm_held(TN)) void k_gemm_bf(Gem
         else store_rows(tile, std::false_type());
     };
 
+    // Tiles with a sum that is infinite or NaN (every one of this wavefront's up to 64, runs of them beyond).  They are formed again at the end: inside
+    // the loop the loads of it made the compiler wait for each of the others (233,000 x 602 x 256: 477 us without, 652 so, 467 now).
+    const int most = (int)((t1 - t0 + kGemmWaves - 1) / kGemmWaves), again_shift = most > 64 ? 26 - __clz(most - 1) : 0;
+    unsigned long long again = 0;
+    int done = 0;
+
     // DEPTH groups of this wavefront's tile from group g0 on, out of the fragments at w; every group's registers are refilled with the group
     // DEPTH later (of the next tile where the row ends)
     long long tile = t0 + wave;
@@ -516,6 +544,8 @@ __global__ __launch_bounds__(kGemmThreads, 2 * gemm_held(TN)) void k_gemm_bf(Gem
             }
         }
         if (ends) {
+            if (__any(not_finite<TN>(acc))) again |= 1ull << (done >> again_shift);
+            ++done;
             store(tile);
             clear();
             tile += kGemmWaves;
@@ -535,7 +565,7 @@ __global__ __launch_bounds__(kGemmThreads, 2 * gemm_held(TN)) void k_gemm_bf(Gem
             float w[8];
             item_of(item, c, row0, at);
             fetch_w(0, c, row0, w);
-            stash_w(lds + at, w);
+            stash_w(lds + at, 0, c, row0, w);
         }
         __syncthreads();
         while (tile < t1)
@@ -551,26 +581,46 @@ __global__ __launch_bounds__(kGemmThreads, 2 * gemm_held(TN)) void k_gemm_bf(Gem
 #pragma unroll
             for (int i = 0; i < WI; ++i) fetch_w(k0, wc[i], wrow[i], w[i]);
         };
-        auto stash_chunk = [&](unsigned char *dst) {
+        auto stash_chunk = [&](unsigned char *dst, int k0) {
 #pragma unroll
             for (int i = 0; i < WI; ++i)
-                if (t + i * kGemmThreads < KC / 16 * 2 * BN) stash_w(dst + wat[i], w[i]);
+                if (t + i * kGemmThreads < KC / 16 * 2 * BN) stash_w(dst + wat[i], k0, wc[i], wrow[i], w[i]);
         };
         fetch_chunk(0);
-        stash_chunk(lds);
+        stash_chunk(lds, 0);
         int which = 0;
         for (int round = 0; round < rounds; ++round)
             for (int ch = 0; ch < chunks; ++ch) {
                 __syncthreads();   // this chunk's pieces are in its buffer; nobody reads the other one any more
                 const bool more = ch + 1 < chunks || round + 1 < rounds;
-                if (more) fetch_chunk(ch + 1 < chunks ? (ch + 1) * KC : 0);
+                const int k_next = ch + 1 < chunks ? (ch + 1) * KC : 0;
+                if (more) fetch_chunk(k_next);
                 if (tile < t1)
                     for (int g0 = ch * (KC / 32), g1 = g0 + KC / 32; g0 < g1 && g0 < groups; g0 += DEPTH)
                         run(g0, lds + which * (KC / 16 * STEP_BYTES) + (g0 - ch * (KC / 32)) * 2 * STEP_BYTES);
                 __builtin_amdgcn_sched_barrier(0);
                 which ^= 1;
-                if (more) stash_chunk(lds + which * (KC / 16 * STEP_BYTES));
+                if (more) stash_chunk(lds + which * (KC / 16 * STEP_BYTES), k_next);
             }
+    }
+    if (!again) return;
+    done = 0;
+    for (tile = t0 + wave; tile < t1; tile += kGemmWaves, ++done) {
+        if (!((again >> (done >> again_shift)) & 1ull)) continue;
+        const long long row = tile * 32 + ll;
+        const float *a = g.A + (row < g.n ? row : g.n - 1) * g.lda;
+#pragma unroll 1
+        for (int j = 0; j < TN; ++j) {
+            const int col = n0 + j * 32 + ll;
+            const float *w = g.W + (col < g.m ? col : g.m - 1);
+            const bool live = col < g.m;
+            const floatx16 sums = product_fp32(g.k, kh, [&](int q) { return a[(long long)(q >> 5) * g.a_slice + (q & 31)]; },
+                                               [&](int q) { const float v = w[(long long)q * g.ldw]; return live ? v : 0.f; });
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+                if (i == j) acc[i] = sums;
+        }
+        store_rows(tile, std::false_type());
     }
 }
 
@@ -1099,6 +1149,19 @@ __global__ __launch_bounds__(kThreads, 2) void k_tiles_sddmm(const float *__rest
         }
         __builtin_amdgcn_sched_barrier(0);
         stash((st + 1) & 1);
+    }
+    if (__any(not_finite<TN>(acc[0]) || not_finite<TN>(acc[1]))) {
+#pragma unroll 1
+        for (int u = 0; u < TM * TN; ++u) {
+            const float *l = Lh + ((size_t)slot_rt[slot] * 128 + (wm * TM + u / TN) * 32 + ll) * f;
+            const float *r = Rh + ((size_t)slot_ct[slot] * 128 + (wn * TN + u % TN) * 32 + ll) * f;
+            const floatx16 sums = product_fp32(f, kh, [&](int q) { return l[q]; }, [&](int q) { return r[q]; });
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    if (i * TN + j == u) acc[i][j] = sums;
+        }
     }
     float *out = Dt + (size_t)slot * 128 * 128;
 #pragma unroll

@@ -60,6 +60,53 @@ def test_infinities_and_the_largest_values(ctx):
     assert np.all(np.isfinite(Y[rest]))
 
 
+# resident and chunked W, one to four blocks of columns, more than 64 tiles of rows a wavefront
+@pytest.mark.parametrize("shape", [(66_000, 70, 20), (66_000, 720, 17), (66_000, 100, 64), (66_000, 301, 50), (66_000, 90, 96), (66_001, 259, 88), (66_031, 66, 128),
+                                   (66_000, 200, 256), (4_300_000, 16, 32)])
+def test_overflow_and_infinities_are_those_of_fp32(ctx, shape):
+    """Pieces of mixed signs must not turn a product that overflows, or one with an infinity, into NaN or the other infinity: one element per row,
+    weights of both signs that are cut with rounding up and down, products from 2^100 to 2^200."""
+    n, k, m = shape
+    assert binding.gemm_kernel(n, k, m) == binding.GEMM_BF16_PIECES
+    g = torch.Generator(device="cuda:0").manual_seed(n + k)
+    W = torch.randn(k, m, device="cuda:0", generator=g) * 700.0
+    W[:, 0], W[:, 1] = 602.5, -602.5          # second piece against the first
+    W[:, 2:4] *= 1e30
+    A = torch.randn(n, k, device="cuda:0", generator=g)
+    plain = ctx.gemm(A, W, ACT_NONE)
+    rows = torch.randperm(n, device="cuda:0", generator=g)[: 64 * 12].reshape(64, 12)
+    rows[0, 0], rows[0, 1] = n - 1, 31
+    rows = rows.flatten()
+    rows = torch.unique(rows)
+    special = torch.zeros(rows.numel(), k, device="cuda:0")
+    at = torch.arange(rows.numel(), device="cuda:0")
+    x = torch.randn(rows.numel(), device="cuda:0", generator=g) * 2.0 ** (100 + (at % 28).float())
+    x[at % 7 == 0], x[at % 7 == 1], x[at % 7 == 2] = float("inf"), float("-inf"), float(np.finfo(np.float32).max)
+    q = torch.randint(0, k, (rows.numel(),), device="cuda:0", generator=g)
+    special[at, q] = x
+    A[rows] = special
+    finite = torch.isfinite(x)
+    for act in (ACT_NONE, ACT_RELU):
+        Y = ctx.gemm(A, W, act)
+        # a finite element: its product, infinite where fp32 has no value for it; an infinite one: 0 * w of the others does not matter, w = 0 would be NaN
+        ref = (x[:, None].double() * W[q].double()).float()
+        ref = ref.clamp(min=0) if act == ACT_RELU else ref
+        got = Y[rows]
+        assert torch.equal(torch.isinf(got), torch.isinf(ref)) and not torch.isnan(got).any()
+        assert torch.equal(got[torch.isinf(ref)], ref[torch.isinf(ref)])
+        ok = torch.isfinite(ref) & (ref.abs() > 1e-30)
+        assert ((got[ok].double() - ref[ok].double()).abs() <= 2.0 ** -22 * ref[ok].double().abs()).all()
+        assert finite.any()
+    # a row with a NaN is NaN, the rows around it are not
+    A[rows] = 0.0
+    A[17, k // 2] = float("nan")
+    Y = ctx.gemm(A, W, ACT_NONE)
+    assert torch.isnan(Y[17]).all() and torch.isfinite(Y[:17]).all() and torch.isfinite(Y[18:]).all()
+    rest = torch.ones(n, dtype=torch.bool, device="cuda:0")
+    rest[rows], rest[:32] = False, False
+    assert torch.equal(Y[rest], plain[rest])   # tiles without such a row keep their bits
+
+
 @pytest.mark.parametrize("f_in,f_out", [(64, 41), (101, 96)])
 def test_epilogue_adds_a_sliced_matrix(ctx, f_in, f_out):
     """TAGCN, update first: every product but the first adds the running sum of the hops."""
