@@ -341,6 +341,9 @@ constexpr int gemm_depth(int tn) { return tn == 1 ? 1 : 4; }
 constexpr int gemm_held(int tn) { return tn == 1 ? 2 : 1; }      // workgroups a compute unit holds at a time, by registers
 constexpr int gemm_a_bufs(int tn) { return tn == 1 ? 1 : 2; }
 
+enum { kWholeTile, kAnyTile, kMarks, kAgain };
+constexpr unsigned kAgainBits = 0x7FCA6A1Bu;   // a NaN; one that is an operand's own is formed again too, to the same end
+
 template <int TN, bool CHUNKED>
 __global__ __launch_bounds__(kGemmThreads, 2 * gemm_held(TN)) void k_gemm_bf(GemmArgs g) {
     if ((int)blockIdx.x < g.side.blocks) {
@@ -477,8 +480,9 @@ __global__ __launch_bounds__(kGemmThreads, 2 * gemm_held(TN)) void k_gemm_bf(Gem
     };
     // register r of lane l holds row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32; in a tile whose rows all exist the loads of `add` and
     // `row_scale` are not behind branches and are in flight together
-    auto store_rows = [&](long long tile, auto whole) {
-        constexpr bool kWhole = decltype(whole)::value;
+    auto store_rows = [&](long long tile, auto form) {
+        constexpr int kForm = decltype(form)::value;   // whole tile; any tile; the same, marks for what is to be formed again; in place of marks only
+        constexpr bool kWhole = kForm == kWholeTile;
         const long long row0 = tile * 32 + 4 * kh;
         {
             float sc[16];
@@ -509,18 +513,21 @@ __global__ __launch_bounds__(kGemmThreads, 2 * gemm_held(TN)) void k_gemm_bf(Gem
                     const long long row = row0 + 8 * (r / 4) + (r % 4);
                     float v = y[r] * sc[r];
                     if (g.act == SENSEI_ACT_RELU) v = v > 0.f ? v : 0.f;
-                    if (kWhole || row < g.n) g.Y[row * y_ld + y_col] = v;
+                    if (kForm == kMarks && !__builtin_isfinite(acc[j][r])) v = __uint_as_float(kAgainBits);
+                    float *dst = g.Y + row * y_ld + y_col;
+                    if ((kWhole || row < g.n) && (kForm != kAgain || __float_as_uint(*dst) == kAgainBits)) *dst = v;
                 }
             }
         }
     };
     auto store = [&](long long tile) {
-        if ((tile + 1) * 32 <= g.n) store_rows(tile, std::true_type());
-        else store_rows(tile, std::false_type());
+        if ((tile + 1) * 32 <= g.n) store_rows(tile, std::integral_constant<int, kWholeTile>());
+        else store_rows(tile, std::integral_constant<int, kAnyTile>());
     };
 
-    // Tiles with a sum that is infinite or NaN (every one of this wavefront's up to 64, runs of them beyond).  They are formed again at the end: inside
-    // the loop the loads of it made the compiler wait for each of the others (233,000 x 602 x 256: 477 us without, 652 so, 467 now).
+    // Tiles with a sum that is infinite or NaN (every one of this wavefront's up to 64, runs of them beyond).  Those sums are stored as marks and formed
+    // again at the end: inside the loop the loads of it made the compiler wait for each of the others (233,000 x 602 x 256: 477 us without, 652
+    // so, 467 now).
     const int most = (int)((t1 - t0 + kGemmWaves - 1) / kGemmWaves), again_shift = most > 64 ? 26 - __clz(most - 1) : 0;
     unsigned long long again = 0;
     int done = 0;
@@ -544,9 +551,13 @@ __global__ __launch_bounds__(kGemmThreads, 2 * gemm_held(TN)) void k_gemm_bf(Gem
             }
         }
         if (ends) {
-            if (__any(not_finite<TN>(acc))) again |= 1ull << (done >> again_shift);
+            if (__any(not_finite<TN>(acc))) {
+                again |= 1ull << (done >> again_shift);
+                store_rows(tile, std::integral_constant<int, kMarks>());
+            } else {
+                store(tile);
+            }
             ++done;
-            store(tile);
             clear();
             tile += kGemmWaves;
         }
@@ -620,7 +631,7 @@ __global__ __launch_bounds__(kGemmThreads, 2 * gemm_held(TN)) void k_gemm_bf(Gem
             for (int i = 0; i < TN; ++i)
                 if (i == j) acc[i] = sums;
         }
-        store_rows(tile, std::false_type());
+        store_rows(tile, std::integral_constant<int, kAgain>());
     }
 }
 
@@ -1160,7 +1171,10 @@ __global__ __launch_bounds__(kThreads, 2) void k_tiles_sddmm(const float *__rest
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
-                    if (i * TN + j == u) acc[i][j] = sums;
+                    if (i * TN + j == u)
+#pragma unroll
+                        for (int q = 0; q < 16; ++q)
+                            if (!__builtin_isfinite(acc[i][j][q])) acc[i][j][q] = sums[q];
         }
     }
     float *out = Dt + (size_t)slot * 128 * 128;

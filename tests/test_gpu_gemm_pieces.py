@@ -86,12 +86,15 @@ def test_overflow_and_infinities_are_those_of_fp32(ctx, shape):
     special[at, q] = x
     A[rows] = special
     finite = torch.isfinite(x)
+    rest = torch.ones(n, dtype=torch.bool, device="cuda:0")
+    rest[rows] = False
     for act in (ACT_NONE, ACT_RELU):
         Y = ctx.gemm(A, W, act)
         # a finite element: its product, infinite where fp32 has no value for it; an infinite one: 0 * w of the others does not matter, w = 0 would be NaN
         ref = (x[:, None].double() * W[q].double()).float()
         ref = ref.clamp(min=0) if act == ACT_RELU else ref
         got = Y[rows]
+        assert torch.equal(Y[rest], plain[rest] if act == ACT_NONE else plain[rest].clamp(min=0))   # the rows beside keep their bits
         assert torch.equal(torch.isinf(got), torch.isinf(ref)) and not torch.isnan(got).any()
         assert torch.equal(got[torch.isinf(ref)], ref[torch.isinf(ref)])
         ok = torch.isfinite(ref) & (ref.abs() > 1e-30)
@@ -102,9 +105,8 @@ def test_overflow_and_infinities_are_those_of_fp32(ctx, shape):
     A[17, k // 2] = float("nan")
     Y = ctx.gemm(A, W, ACT_NONE)
     assert torch.isnan(Y[17]).all() and torch.isfinite(Y[:17]).all() and torch.isfinite(Y[18:]).all()
-    rest = torch.ones(n, dtype=torch.bool, device="cuda:0")
-    rest[rows], rest[:32] = False, False
-    assert torch.equal(Y[rest], plain[rest])   # tiles without such a row keep their bits
+    rest[17] = False
+    assert torch.equal(Y[rest], plain[rest])   # the rows beside such a row keep their bits
 
 
 @pytest.mark.parametrize("f_in,f_out", [(64, 41), (101, 96)])
