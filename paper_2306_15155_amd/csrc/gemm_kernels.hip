@@ -263,9 +263,14 @@ __global__ __launch_bounds__(kThreads) void k_gemm_small(GemmArgs g) {
 
 // ---- the same GEMM on the bf16 matrix cores, which run 16 times the fp32 rate, at fp32 accuracy.  Every fp32 operand element
 // is cut into three bf16 pieces (round to nearest, subtract, round, subtract: both subtractions are exact and the pieces add up to the
-// element exactly); of the nine piece products of a term the six largest are formed (a1 b1, a1 b2, a2 b1, a1 b3, a2 b2, a3 b1), each exact,
-// and accumulated in fp32 by the matrix core.  A rounded piece is at most 2^-9 of what it was cut from, so what is left out (a2 b3, a3 b2,
-// a3 b3) is below 2^-26 of the term, either sign: less than the rounding of the product itself.
+// element exactly).  bf16 has eight significand bits, so a second piece is at most 2^-8 of the element and a third 2^-17 of it.  Of the nine piece
+// products of a term, each exact and accumulated in fp32 by the matrix core, are formed
+//   six (a1 b1, a1 b2, a2 b1, a1 b3, a2 b2, a3 b1): what is left out is below 2^-23.9 of the term (a2 b3 + a3 b2 + a3 b3, reached by operands like
+//     1 + 2^-8 - 2^-17), 2^-26.4 rms, either sign, and the instruction's own sums lose up to another unit of 2^-23: a sum of many terms is closer to
+//     the exact one than fp32's (rms over 32 to 602 mixed terms 0.27-0.34 units of 2^-24 of their magnitudes, fp32 0.40-0.41), a sum that one
+//     term makes up is not (largest error 2.7 units, fp32 1.0); or
+//   eight, a3 b3 alone left out (2^-34 of the term), a1 b1 and the seven others in accumulators of their own that are added at the end: many terms
+//     0.11-0.14 units, a single term the one rounding of fp32 (1.0).
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
@@ -1082,13 +1087,14 @@ __global__ void k_tiles_combine_pm(float *__restrict__ C, long long n_rows, int 
 
 // Dt[slot] = Lh[rows of the slot's row tile] . Rh[rows of its column tile]^T, 128 x 128 per kept tile: the per-entry dot product
 // <dP_i, Theta_j> of the attention backward for all entries of a tile at once, on the matrix cores (the cells outside the tile's
-// bit mask are computed too and never read).  bf16 instruction on three exact pieces per operand, cut with rounding (six products a term, what
-// is left out is below 2^-26 of it): with the fp32 instruction the kernel was bound by it (16 k of a tile: 2,048 matrix cycles per wavefront,
-// here 768).  Both operands are rows with k contiguous: two neighbouring threads take the 16 k of a row and step, cut eight each and leave them
-// in LDS in lane order, so that an element is cut once per workgroup; two buffers, one barrier per step (8 rows of padding between the halves
-// of k: the two threads' 16-byte writes fall on different banks).  22,334 tiles at 256 columns, beside the remainder's dot products: GAT
-// training on 115 M entries 17.99 -> 17.44 ms.  Against fp64, in 2^-24 of the terms' magnitudes: rms of sums over 128 to 256 columns
-// 0.39-0.40 -> 0.32, with terms of one sign 2.6-3.6 -> 2.1-3.0; of single products 0.42 -> 0.37.
+// bit mask are computed too and never read).  bf16 instruction on three exact pieces per operand, eight products a term in two accumulators: these
+// are single dot products, used one by one.  With the fp32 instruction the kernel was bound by it (16 k of a tile: 2,048 matrix cycles per
+// wavefront, here 1,024).  Both operands are rows with k contiguous: two neighbouring threads take the 16 k of a row and step, cut eight each and leave
+// them in LDS in lane order, so that an element is cut once per workgroup; two buffers, one barrier per step (8 rows of padding between the
+// halves of k: the two threads' 16-byte writes fall on different banks).  22,334 tiles at 256 columns, beside the remainder's dot products: GAT
+// training on 115 M entries 17.99 ms with the fp32 instruction, 17.43 so (six products: 17.19).  Against fp64, in 2^-24 of the terms' magnitudes, fp32
+// instruction / so: rms of sums over 128 to 256 columns 0.39-0.40 / 0.11-0.12, with terms of one sign 2.6-3.6 / 1.0-1.4; single products 0.43 / 0.43,
+// the largest 1.00 / 1.00 (six products: 1.4 measured, 2.0 where a second piece is as large as it gets).
 __global__ __launch_bounds__(kThreads, 2) void k_tiles_sddmm(const float *__restrict__ Lh, const float *__restrict__ Rh, int f,
                                                               const int32_t *__restrict__ slot_rt, const int32_t *__restrict__ slot_ct,
                                                               float *__restrict__ Dt) {
@@ -1101,13 +1107,13 @@ __global__ __launch_bounds__(kThreads, 2) void k_tiles_sddmm(const float *__rest
     const int row = t >> 1, half = t & 1;
     const float *src[2] = {Lh + ((size_t)slot_rt[slot] * 128 + row) * f + half * 8, Rh + ((size_t)slot_ct[slot] * 128 + row) * f + half * 8};
 
-    floatx16 acc[TM][TN];
+    floatx16 acc[TM][TN], low[TM][TN];   // the products of the first pieces; all others
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = low[i][j][r] = 0.f;
 
     float4 raw[2][2];
     auto fetch = [&](int k0) {
@@ -1152,15 +1158,20 @@ __global__ __launch_bounds__(kThreads, 2) void k_tiles_sddmm(const float *__rest
 #pragma unroll
             for (int pa = 2; pa >= 0; --pa)
 #pragma unroll
-                for (int pb = 2 - pa; pb >= 0; --pb)   // smallest products first
+                for (int pb = pa == 2 ? 1 : 2; pb >= 0; --pb)   // smallest products first
 #pragma unroll
-                    for (int i = 0; i < TM; ++i)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[i][pa]), __builtin_bit_cast(bf16x8, bf[pb]),
-                                                                             acc[i][j], 0, 0, 0);
+                    for (int i = 0; i < TM; ++i) {
+                        floatx16 &sum = pa + pb > 0 ? low[i][j] : acc[i][j];
+                        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[i][pa]), __builtin_bit_cast(bf16x8, bf[pb]), sum, 0, 0, 0);
+                    }
         }
         __builtin_amdgcn_sched_barrier(0);
         stash((st + 1) & 1);
     }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] += low[i][j];
     if (__any(not_finite<TN>(acc[0]) || not_finite<TN>(acc[1]))) {
 #pragma unroll 1
         for (int u = 0; u < TM * TN; ++u) {

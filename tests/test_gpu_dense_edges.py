@@ -134,3 +134,41 @@ def test_tile_products_keep_all_bits(f):
     assert worst <= 3.0, worst
     T.close()
     ctx.close()
+
+
+# The same over many operands, and held to what the kernel claims: a product is rounded once (one unit of 2^-24 of it at most) and its small piece
+# products lose seven times 2^-23 of at most 2^-7 of it (0.11 units).  Neighbours cancel exactly, so m is 0 and nothing else rounds.  Every eighth
+# pair has 1 +- 2^-8 -+ 2^-17, whose second and third pieces are as large as rounding leaves them.
+@pytest.mark.parametrize("f", [128, 256])
+def test_tile_products_are_rounded_once(f):
+    from paper_2306_15155_amd import Context, Tiles, csr_struct
+    ctx, n = Context(0), 256
+    g = torch.Generator(device="cuda").manual_seed(f)
+    row_ptr = (torch.arange(n + 1, device="cuda") * n).to(torch.int32)
+    col_idx = torch.arange(n, device="cuda", dtype=torch.int32).repeat(n)
+    A = csr_struct(n, n, row_ptr, col_idx)
+    T = Tiles(ctx, A, 0.05, 256, min_width=32)
+    assert T.n_tiles == 4
+    Ah, pos = csr_struct(n, n, row_ptr, col_idx, tiles=T), ctx.transpose_positions(A, A)
+    half = torch.rand(n // 2, f, generator=g, device="cuda") - 0.5
+    half[::8], half[1::8] = 1.0 + 2.0 ** -8 - 2.0 ** -17, 1.0 - 2.0 ** -8 + 2.0 ** -17
+    theta = torch.stack([half, -half], 1).reshape(n, f).contiguous()
+    theta[:, 1:3] = 1.0
+    a_l, a_r = torch.zeros(f, device="cuda"), torch.zeros(f, device="cuda")
+    a_l[2] = a_r[1] = 0.5
+    X, worst = torch.eye(n, device="cuda"), 0.0
+    for i in range(0, 256, 7):
+        q = int(torch.randint(3, f, (1,), generator=g, device="cuda"))
+        d = float(torch.rand(1, generator=g, device="cuda")) - 0.5
+        for d in (d, 1.0 + 2.0 ** -8 - 2.0 ** -17, -1.0 + 2.0 ** -8 - 2.0 ** -17):
+            dY = torch.zeros(n, f, device="cuda")
+            dY[i, q] = d
+            dW = ctx.gat_backward(Ah, Ah, pos, X, theta, a_l, a_r, dY, neg_slope=0.2)[1]
+            ds_r = 2.0 * dW[:, 1].double()
+            term = theta[:, q].double() * float(dY[i, q]) * 2.0 ** -8
+            got, want = ds_r[0::2] - ds_r[1::2], term[0::2] - term[1::2]
+            worst = max(worst, float(((got - want).abs() / want.abs()).nan_to_num().max()) * 2.0 ** 24)
+    print(f"{f} columns: {worst:.3f} units of 2^-24")
+    assert worst <= 1.11, worst
+    T.close()
+    ctx.close()
