@@ -228,9 +228,10 @@ int sensei_norm_vectors(sensei_ctx *ctx, const int32_t *deg, int64_t n, float *o
 int sensei_chunk_nnz(int64_t nnz);
 
 /* Which matrix-core kernel sensei_gemm (and the GEMM inside the layers) takes for an n x k by k x m product: the fp32 instruction,
- * or, for large products, the bf16 instruction on three exact bf16 pieces per fp32 operand element with six piece products per
- * term (what is left out is below 2^-26 of a term: over many terms the result is as accurate as the fp32
- * instruction's, at several times its rate).  Host arithmetic; for reports that price the kernel against the right matrix-core peak. */
+ * or, for larger products, the bf16 instruction on three exact bf16 pieces per fp32 operand element.  Eight piece products per term where there are fewer
+ * than 256 blocks of 256 rows x up to 128 columns (what is left out is below 2^-34 of a term: nowhere less accurate than the fp32 instruction), six above
+ * (below 2^-23.9 of a term, 2^-27.5 rms: over many terms more accurate than the fp32 instruction, a sum of one term up to 2.7 units of 2^-24
+ * off instead of 1).  Host arithmetic; for reports that price the kernel against the right matrix-core peak. */
 enum { SENSEI_GEMM_FP32 = 0, SENSEI_GEMM_BF16_PIECES = 1 };
 int sensei_gemm_kernel(int64_t n, int k, int m);
 

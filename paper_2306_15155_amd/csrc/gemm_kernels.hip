@@ -265,8 +265,8 @@ __global__ __launch_bounds__(kThreads) void k_gemm_small(GemmArgs g) {
 // is cut into three bf16 pieces (round to nearest, subtract, round, subtract: both subtractions are exact and the pieces add up to the
 // element exactly).  bf16 has eight significand bits, so a second piece is at most 2^-8 of the element and a third 2^-17 of it.  Of the nine piece
 // products of a term, each exact and accumulated in fp32 by the matrix core, are formed
-//   six (a1 b1, a1 b2, a2 b1, a1 b3, a2 b2, a3 b1): what is left out is below 2^-23.9 of the term (a2 b3 + a3 b2 + a3 b3, reached by operands like
-//     1 + 2^-8 - 2^-17), 2^-26.4 rms, either sign, and the instruction's own sums lose up to another unit of 2^-23: a sum of many terms is closer to
+//   six (a1 b1, a1 b2, a2 b1, a1 b3, a2 b2, a3 b1): what is left out is below 2^-23.9 of the term (a2 b3 + a3 b2 + a3 b3; 2^-24.0 for operands like
+//     1 + 2^-8 - 2^-17), 2^-27.5 rms, either sign, and the instruction's own sums lose up to another unit of 2^-23: a sum of many terms is closer to
 //     the exact one than fp32's (rms over 32 to 602 mixed terms 0.27-0.34 units of 2^-24 of their magnitudes, fp32 0.40-0.41), a sum that one
 //     term makes up is not (largest error 2.7 units, fp32 1.0); or
 //   eight, a3 b3 alone left out (2^-34 of the term), a1 b1 and the seven others in accumulators of their own that are added at the end: many terms
@@ -349,7 +349,8 @@ constexpr int gemm_a_bufs(int tn) { return tn == 1 ? 1 : 2; }
 enum { kWholeTile, kAnyTile, kMarks, kAgain };
 constexpr unsigned kAgainBits = 0x7FCA6A1Bu;   // a NaN; one that is an operand's own is formed again too, to the same end
 
-template <int TN, bool CHUNKED>
+// FULL: eight piece products a term in two accumulators, else six in one
+template <int TN, bool CHUNKED, bool FULL>
 __global__ __launch_bounds__(kGemmThreads, 2 * gemm_held(TN)) void k_gemm_bf(GemmArgs g) {
     if ((int)blockIdx.x < g.side.blocks) {
         if (threadIdx.x < kSideThreads) side_block(g.side, (int)blockIdx.x);
@@ -443,12 +444,15 @@ __global__ __launch_bounds__(kGemmThreads, 2 * gemm_held(TN)) void k_gemm_bf(Gem
         __builtin_amdgcn_wave_barrier();
     };
 
-    floatx16 acc[TN];
+    floatx16 acc[TN], low[FULL ? TN : 1];   // FULL: the products of the first pieces; all others
     auto clear = [&]() {
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+            for (int r = 0; r < 16; ++r) {
+                acc[j][r] = 0.f;
+                if (FULL) low[FULL ? j : 0][r] = 0.f;
+            }
     };
     auto multiply = [&](int buf, const unsigned char *w) {   // the group in `buf` (two steps), fragments of W at w
         uintx4 af[2][3];
@@ -476,11 +480,12 @@ __global__ __launch_bounds__(kGemmThreads, 2 * gemm_held(TN)) void k_gemm_bf(Gem
 #pragma unroll
                 for (int pa = 2; pa >= 0; --pa)
 #pragma unroll
-                    for (int pb = 2 - pa; pb >= 0; --pb)   // smallest products first
+                    for (int pb = !FULL ? 2 - pa : pa == 2 ? 1 : 2; pb >= 0; --pb)   // smallest products first
 #pragma unroll
-                        for (int i = 0; i < J; ++i)
-                            acc[j + i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[step][pa]), __builtin_bit_cast(bf16x8, bf[i][pb]),
-                                                                                 acc[j + i], 0, 0, 0);
+                        for (int i = 0; i < J; ++i) {
+                            floatx16 &sum = FULL && pa + pb > 0 ? low[FULL ? j + i : 0] : acc[j + i];
+                            sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[step][pa]), __builtin_bit_cast(bf16x8, bf[i][pb]), sum, 0, 0, 0);
+                        }
             }
     };
     // register r of lane l holds row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32; in a tile whose rows all exist the loads of `add` and
@@ -556,6 +561,9 @@ __global__ __launch_bounds__(kGemmThreads, 2 * gemm_held(TN)) void k_gemm_bf(Gem
             }
         }
         if (ends) {
+            if (FULL)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc[j] += low[FULL ? j : 0];
             if (__any(not_finite<TN>(acc))) {
                 again |= 1ull << (done >> again_shift);
                 store_rows(tile, std::integral_constant<int, kMarks>());
@@ -640,7 +648,7 @@ __global__ __launch_bounds__(kGemmThreads, 2 * gemm_held(TN)) void k_gemm_bf(Gem
     }
 }
 
-template <int TN>
+template <int TN, bool FULL>
 hipError_t gemm_bf_launch(GemmArgs g, hipStream_t s) {
     const int steps = (g.k + 31) / 32 * 2;
     const size_t a_bytes = (size_t)kGemmWaves * 4096 * gemm_a_bufs(TN);
@@ -654,8 +662,8 @@ hipError_t gemm_bf_launch(GemmArgs g, hipStream_t s) {
     const long long parts = g.by_xcd ? 8 * (held / g.n_bn) : 8 * held > g.n_bn ? 8 * held / g.n_bn : 1;
     g.n_parts = (int)(parts < tiles ? parts : tiles);
     const dim3 grid((unsigned)(g.n_parts * g.n_bn + g.side.blocks));
-    if (chunked) hipLaunchKernelGGL((k_gemm_bf<TN, true>), grid, dim3(kGemmThreads), g.a_lds + a_bytes, s, g);
-    else hipLaunchKernelGGL((k_gemm_bf<TN, false>), grid, dim3(kGemmThreads), g.a_lds + a_bytes, s, g);
+    if (chunked) hipLaunchKernelGGL((k_gemm_bf<TN, true, FULL>), grid, dim3(kGemmThreads), g.a_lds + a_bytes, s, g);
+    else hipLaunchKernelGGL((k_gemm_bf<TN, false, FULL>), grid, dim3(kGemmThreads), g.a_lds + a_bytes, s, g);
     return hipGetLastError();
 }
 
@@ -1767,15 +1775,32 @@ static int gemm_bf_blocks(int64_t n, int m_store) {
     return tn;
 }
 
-// Where the fixed costs of k_gemm_bf (about 6 us: W is fetched and cut before the first multiply) are earned back, by k and rows; outputs wider
-// than 192 columns count more.  fp32 kernels / k_gemm_bf, us: k = 602, 256 columns, 6,000 rows 34 / 25, 18,000 94 / 57; k = 300, 96 columns, 6,000
-// rows 13.3 / 12.3; k = 256, 41 columns, 10,000 rows 10.8 / 12.9, 18,000 18.5 / 13.4; k = 100, 47 columns, 14,000 rows 8.8 / 9.9, 18,000 10.7 /
-// 10.0, 256 columns, 10,000 rows 12.8 / 13.8, 14,000 16.3 / 14.4; k = 32, 128 columns, 22,000 rows 7.7 / 8.9, 28,000 9.2 / 8.4; k = 16, 32 columns,
-// 50,000 rows 6.2 / 7.2, 100,000 8.7 / 8.3.
+// Products of at least a block of 256 rows x 128 columns (the columns there are, up to 64) per compute unit take six piece products, smaller ones
+// eight: there the matrix pipe is seldom the bound and the two cost little (30,000 x 602 x 256 61 -> 72 us, 16,000 x 100 x 64 9.9 -> 10.1), and what a single
+// term makes up stays as exact as on the fp32 instruction, which these sizes would take otherwise (96 us, 8.1).  Above, eight cost 13 % on
+// average and more where four blocks of columns need two sets of accumulators (233,000 x 602 x 256 467 -> 560).
+static bool gemm_is_large(int64_t n, int m_store) {
+    const int64_t blocks = (m_store + 31) / 32;
+    return (n + 255) / 256 * (blocks <= 2 ? 1 : (blocks + 3) / 4) >= 256;
+}
+
+// Where the fixed costs of k_gemm_bf (about 6 us: W is fetched and cut before the first multiply, and a wavefront walks all of k) are earned
+// back.  Large products, by k and rows, outputs wider than 192 columns counting more (fp32 kernels / here, us): k = 16, 32 columns, 50,000 rows 6.2 / 7.2, 100,000
+// 8.7 / 8.3.  Below that size, with eight piece products, outputs of at most 64 columns need more rows, whole blocks of 64 the most, for which the fp32 kernel has its widest loads: k = 100, 64 columns, 30,000 rows 9.7 / 11.0; k = 100, 47 columns, 16,000 rows 8.7 / 10.0, 20,000
+// 10.7 / 10.1; k = 128, 32 columns, 16,000 rows 7.6 / 8.6, 20,000 9.7 / 9.4; k = 256, 64 columns, 16,000 rows 12.4 / 14.1, 20,000 15.7 / 14.5; k = 512, 32
+// columns, 6,000 rows 10.6 / 15.8, 12,000 18.8 / 15.7; k = 1024, 64 columns, 16,000 rows 36.5 / 42.7, 20,000 48.6 / 43.2.  Wider ones: k = 32, 192
+// columns, 30,000 rows 15.9 / 12.6; k = 64, 192 columns, 16,000 rows 10.2 / 10.7, 20,000 19.5 / 12.8; k = 128, 96 columns, 16,000 rows 10.5 / 10.4, 256
+// columns, 12,000 rows 14.7 / 14.5; k = 300, 96 columns, 6,000 rows 13.2 / 12.7; k = 1024, 96 columns, 6,000 rows 35.6 / 41.6, 9,000 48.6 / 43.0, 192
+// columns, 6,000 rows 48.3 / 44.1.
 bool gemm_uses_pieces(int64_t n, int k, int m_store) {
     if (k < 16 || m_store <= 0) return false;
-    const int64_t blocks = (m_store + 31) / 32;
-    return n * (blocks > 6 ? blocks : 6) / 6 >= (k >= 300 ? 6000 : k >= 64 ? 16000 : k >= 32 ? 28000 : 65536);
+    const int64_t blocks = (m_store + 31) / 32, rows = n * (blocks > 6 ? blocks : 6) / 6;
+    if (gemm_is_large(n, m_store)) return rows >= (k >= 64 ? 16000 : k >= 32 ? 28000 : 65536);
+    if (k < 32) return false;
+    if (blocks > 2) return rows >= (k >= 700 && blocks < 6 ? 8000 : k >= 300 ? 6000 : k >= 64 ? 16000 : 28000);
+    if (k >= 300) return n >= (k >= 700 ? 20000 : 12000);
+    if (k >= 128) return n >= (m_store > 48 ? 20000 : 16000);
+    return k >= 64 && n >= (m_store > 48 ? 65536 : m_store > 32 ? 16000 : 40000);
 }
 
 hipError_t launch_gemm(const float *A, int64_t lda, const float *W, int64_t ldw, float *Y, int64_t ldy, int64_t n,
@@ -1805,12 +1830,16 @@ hipError_t launch_gemm(const float *A, int64_t lda, const float *W, int64_t ldw,
         const int tn = gemm_bf_blocks(n, m_store), blocks = (m_store + 31) / 32;
         g.n_bn = (blocks + tn - 1) / tn;
         if (gemm_uses_pieces(n, k, m_store) && lda < (1 << 20) && ldw < (1 << 20)) {   // leading dimensions: 32-bit byte offsets within a block
-            switch (tn) {
-                case 1: return done(gemm_bf_launch<1>(g, s));
-                case 2: return done(gemm_bf_launch<2>(g, s));
-                case 3: return done(gemm_bf_launch<3>(g, s));
-                default: return done(gemm_bf_launch<4>(g, s));
-            }
+            auto launch = [&](auto full) {
+                constexpr bool kFull = decltype(full)::value;
+                switch (tn) {
+                    case 1: return gemm_bf_launch<1, kFull>(g, s);
+                    case 2: return gemm_bf_launch<2, kFull>(g, s);
+                    case 3: return gemm_bf_launch<3, kFull>(g, s);
+                    default: return gemm_bf_launch<4, kFull>(g, s);
+                }
+            };
+            return done(gemm_is_large(n, m_store) ? launch(std::false_type()) : launch(std::true_type()));
         }
     }
     // Few enough 64 x 64 blocks to leave compute units idle: 32 x 32 blocks with k split over the wavefronts.  A small block reads its operands

@@ -109,6 +109,28 @@ def test_overflow_and_infinities_are_those_of_fp32(ctx, shape):
     assert torch.equal(Y[rest], plain[rest])   # the rows beside such a row keep their bits
 
 
+# fewer than 256 blocks of 256 rows: one to four blocks of columns, resident and chunked W
+@pytest.mark.parametrize("shape", [(40_000, 100, 32), (20_033, 720, 17), (40_000, 200, 64), (33_000, 301, 50), (40_001, 100, 96), (40_001, 259, 88), (40_000, 66, 128),
+                                   (30_000, 602, 256)])
+def test_a_single_term_is_rounded_once(ctx, shape):
+    """Products of sizes that the fp32 instruction would take otherwise: one element a row, so that every sum is one product.  It is rounded once (one
+    unit of 2^-24 of it at most), and its small piece products, at most 2^-7 of it, lose up to 2^-23 of that each time one of seven is
+    added (0.11 units).  A third of the operands is 1 +- 2^-8 -+ 2^-17, whose second and third pieces are as large as rounding leaves them."""
+    n, k, m = shape
+    assert binding.gemm_kernel(n, k, m) == binding.GEMM_BF16_PIECES
+    g = torch.Generator(device="cuda:0").manual_seed(n + k + m)
+    wide = torch.tensor([1.0 + 2.0 ** -8 - 2.0 ** -17, 1.0 - 2.0 ** -8 + 2.0 ** -17], device="cuda:0")
+    def operand(*size):
+        x, pick = torch.randn(*size, device="cuda:0", generator=g), torch.randint(0, 6, size, device="cuda:0", generator=g)
+        return torch.where(pick < 2, wide[pick.clamp(max=1)] * x.sign(), x)
+    W, x = operand(k, m), operand(n)
+    A, q = torch.zeros(n, k, device="cuda:0"), torch.randint(0, k, (n,), device="cuda:0", generator=g)
+    A[torch.arange(n, device="cuda:0"), q] = x
+    ref = x.double()[:, None] * W.double()[q]
+    worst = ((ctx.gemm(A, W, ACT_NONE).double() - ref).abs() / ref.abs()).max().item() * 2.0 ** 24
+    assert worst <= 1.11, worst
+
+
 @pytest.mark.parametrize("f_in,f_out", [(64, 41), (101, 96)])
 def test_epilogue_adds_a_sliced_matrix(ctx, f_in, f_out):
     """TAGCN, update first: every product but the first adds the running sum of the hops."""

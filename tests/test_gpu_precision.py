@@ -1,5 +1,7 @@
 """The kernels that run on the bf16 matrix instruction claim fp32 accuracy: every fp32 operand element is cut exactly into three
-bf16 pieces (8 + 8 + 8 significand bits) and only the three smallest of the nine piece products are left out, below 2^-21 of a term.  These tests hold them to
+bf16 pieces (8 + 8 + 8 significand bits), and of the nine piece products of a term the six or eight largest are formed.  What is left out is below 2^-23.9 of
+a term where the pieces are rounded (2^-34 with eight products) and below 2^-21 where they are truncated (value-less tiles and those of the
+attention, weight gradients).  These tests hold them to
 that claim on operands whose low significand bits matter (full 24-bit significands, exponents spread over many binades): the
 error against the fp64 oracle must be a small multiple of fp32 rounding, and several times smaller than the error that dropping
 the third piece (a 16-bit significand) would cause on the same operands, which the test works out on the CPU."""
