@@ -2284,7 +2284,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_head_rows(GatHeadArgs a) {
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             mx[q] = fmaxf(mx[q], -FLT_MAX);   // entries of -inf weigh 0 also where a piece holds no others
-            p[q] = q < n_mine ? __expf(e[q] - mx[q]) : 0.f;
+            p[q] = q < n_mine ? expf(e[q] - mx[q]) : 0.f;
             neg |= (e[q] > 0.f ? 0u : 1u) << q;
             top[lane * PER + q] = mx[q];
         }
@@ -2439,7 +2439,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_head_cols(GatHeadArgs a) {
             const int at = flat_at<PER, PAD, G>(u * 64 + lane), rw = rows[at];
             cols[at] = (int)((unsigned)col[u] | ((unsigned)rw & 0x80000000u));
             const float t = st[u].x + row_val(sr, rw & 0x7fffffff);
-            float w = __expf(leaky(t, a.slope) - st[u].y) * st[u].z;
+            float w = expf(leaky(t, a.slope) - st[u].y) * st[u].z;
             if (c.lo + u * 64 + lane >= c.hi) w = 0.f;
             alpha[at] = t > 0.f ? w : __uint_as_float(__float_as_uint(w) | 0x80000000u);
             rdot[at] = st[u].w;

@@ -50,6 +50,33 @@ def test_narrow_heads(ctx, name, heads, d):
             assert_close(a, b, what=f"{what} act {act}")
 
 
+# Coefficients far below their row's largest, whose exponential must be as exact there as near 0.  X is the identity, so dW is dTheta.  Row i has a source i
+# of logit 100 and a source n + i of 100 - x, x up to 80 (positive and exact: neither the slope nor the subtraction rounds).  Source n + i gets alpha dP_i in the
+# columns that no attention vector reads.  Column 0, which a_r reads, gets alpha (dalpha - rowdot) of source i, where dalpha is 0 and rowdot the product of the
+# small coefficient and a power of two that makes it about one.  Bound: two units of 2^-23 for the exponential, one each for 1 / z and the products.
+@pytest.mark.parametrize("d", [8, 32])
+def test_small_coefficients_are_exact(ctx, d):
+    n = 300
+    x = np.round(np.linspace(0.0, 80.0, n) * 1024) / 1024
+    g = synth.CSR(n, 2 * n, (2 * np.arange(n + 1)).astype(np.int32), np.stack([np.arange(n), n + np.arange(n)], 1).reshape(-1).astype(np.int32))
+    A, At = DeviceCSR(g), DeviceCSR(synth.transpose(g))
+    theta, dY = synth.uniform(9, 1, (2 * n, d), 0.5, 1.0), synth.uniform(9, 2, (n, d), 0.5, 1.0)
+    theta[:, 0] = 100.0 - np.concatenate([np.zeros(n), x])
+    theta[:, 1] = np.concatenate([np.zeros(n), np.exp2(np.round(x / np.log(2.0)))])
+    dY[:, 0], dY[:, 1] = 0.0, 1.0
+    theta[:, 2:] = 0.0
+    a_l, a_r = np.zeros(d, np.float32), np.zeros(d, np.float32)
+    a_r[0] = 1.0
+    pos = ctx.transpose_positions(A.s, At.s)
+    dW = ctx.gat_backward(A.s, At.s, pos, torch.eye(2 * n, device="cuda"), dev(theta), dev(a_l), dev(a_r), dev(dY), neg_slope=0.2)[1].double().cpu().numpy()
+    small = 1.0 / (1.0 + np.exp(x))
+    rel = np.abs(dW[n:, 2:] / (small[:, None] * dY[:, 2:].astype(np.float64)) - 1.0)
+    assert rel.max() <= 5 * 2.0 ** -23, rel.max()
+    rowdot = small * theta[n:, 1].astype(np.float64)
+    rel = np.abs(dW[:n, 0] / (-(1.0 - small) * rowdot) - 1.0)
+    assert rel.max() <= 8 * 2.0 ** -23, rel.max()
+
+
 @pytest.mark.parametrize("name", PATTERNS)
 @pytest.mark.parametrize("f_out", [1, 31, 64, 97])
 def test_gatv2_score(ctx, name, f_out):
