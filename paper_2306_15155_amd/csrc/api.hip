@@ -1567,12 +1567,14 @@ double t_spmm_unsplit(const sensei_ctx &c, const Features &g, double f, int flav
 // What the call costs on the path it will take: a pattern that carries a usable dense-tile split runs its value-less and
 // attention aggregations as tiles + remainder, which removes the tiles' share of the gathers but leaves the cold entries
 // (measured on the 233,000-node power-law graph, 64 % of the entries in tiles: 0.57 of the unsplit call at 256 columns,
-// 3.26 against 5.74 ms).  Weighted and scaled SpMMs do not take the split.
+// 3.26 against 5.74 ms).  Weighted and scaled SpMMs do not take the split.  The operand is slice-major where the split is taken, so that the padded
+// width decides, as in spmm_any and attention_path.
 double t_spmm(const sensei_ctx &c, const Features &g, double f, int flavour) {
     const double t = t_spmm_unsplit(c, g, f, flavour);
     const bool takes_split = (flavour == kSpmmPattern || flavour == kSpmmSoftmaxCost) && g.tile_share > 0.0;
     const double need = flavour == kSpmmSoftmaxCost ? g.tile_min_width / 2.0 : g.tile_min_width;
-    if (!takes_split || f < need || std::ceil(f / 32.0) * 32.0 > g.tile_max_width) return t;
+    const double padded = std::ceil(f / 32.0) * 32.0;
+    if (!takes_split || padded < need || padded > g.tile_max_width) return t;
     return t * (1.0 - 0.65 * g.tile_share);
 }
 
@@ -1632,7 +1634,7 @@ double gat_cost(const sensei_ctx &c, const Features &g, int f_in, int f_out, int
         t += t_spmm(c, g, f_out, kSpmmSoftmaxCost);
     } else {
         Features gs = g;
-        if (g.nnz < 16.0 * g.n_cols) gs.tile_share = 0.0;  // X is gathered row-major: no split
+        if (g.nnz < 16.0 * g.n_cols || f_in < g.tile_min_width / 2.0) gs.tile_share = 0.0;  // X is gathered row-major, or judged by its own width: no split
         t += t_spmm(c, gs, f_in, kSpmmSoftmaxCost) + t_gemm(c, g.n_rows, f_in, f_out, g.learned);
         if (g.nnz >= 16.0 * g.n_cols) t += t_stream(c, 8.0 * g.n_cols * f_in);  // slice-major copy of X
     }
