@@ -186,9 +186,12 @@ def _ptr(t):
     return None if t is None else t.data_ptr()   # the argument types turn the number into a pointer
 
 
+# The handle of a device's current stream without a Stream object around it (1.5 us of a small call's host time).  Not part of torch's public interface.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    # the handle of the current device's current stream, without a Stream object around it
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return _raw_stream(torch.cuda.current_device()) if _raw_stream else torch.cuda.current_stream().cuda_stream
 
 
 def csr_struct(n_rows, n_cols, row_ptr, col_idx, val=None, panels=None, tiles=None) -> CsrStruct:

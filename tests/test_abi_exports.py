@@ -128,3 +128,20 @@ def test_bench_refuses_more_than_one_gpu_before_touching_one():
     import sys
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert r.returncode == 2 and "one GPU only" in r.stderr and r.stdout.strip() == ""
+
+
+def test_pointers_are_declared_and_the_stream_has_a_public_source(monkeypatch):
+    """Pointers and streams are passed as numbers, so every entry point that takes any has its argument types declared; without torch's private
+    query of the stream the public one gives the same handle."""
+    from paper_2306_15155_amd import binding
+    L = binding.lib()
+    bare = [n for n in binding.EXPORTS if getattr(L, n).argtypes is None]
+    assert bare == []
+    class Stream:
+        cuda_stream = 0x7F0000001230
+    monkeypatch.setattr(binding, "_raw_stream", lambda device: 0x7F0000001230 if device == 3 else 0)
+    monkeypatch.setattr(binding.torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(binding.torch.cuda, "current_stream", lambda: Stream)
+    with_private = binding._stream()
+    monkeypatch.setattr(binding, "_raw_stream", None)
+    assert binding._stream() == with_private == 0x7F0000001230
