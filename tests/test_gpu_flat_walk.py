@@ -8,7 +8,7 @@ import torch
 import oracle
 import synth
 from paper_2306_15155_amd import ACT_NONE, ACT_RELU, SPMM_PATTERN, SPMM_SCALED, SPMM_WEIGHTED, Context
-from paper_2306_15155_amd.binding import chunk_nnz
+from paper_2306_15155_amd.binding import GAT_PATH_ONE_WALK, chunk_nnz, gat_attention_path
 
 from gpu_util import DeviceCSR, assert_close, dev
 
@@ -103,6 +103,48 @@ def test_flat_spmm_at_chunk_boundaries(ctx, t, least):
     got = ctx.gatv2_backward(A.s, At.s, ctx.transpose_positions(A.s, At.s), dev(X), dev(Wl), dev(W), dev(a_l), dev(dY), neg_slope=1.0)
     for gpu, ref, what in zip(got, want, ("dX", "dW_l", "dW_r", "datt")):
         assert_close(gpu, ref, what=what)
+
+
+def head_inputs(g, t, f_in, heads, d):
+    """X, W, a_l, a_r whose logits stay away from zero with both signs in every longer row: the derivative of LeakyReLU jumps there.  Column 0 of
+    every head is +-1 by the source and only a_r sees it (2.5), the rest of the score stays below 2."""
+    X, W = synth.uniform(t, 21, (g.n_cols, f_in)), synth.glorot(t, 22, f_in, heads * d)
+    a_l, a_r = synth.normal(t, 23, (heads * d,), 0.0, 0.1), synth.normal(t, 24, (heads * d,), 0.0, 0.1)
+    X[:, 0] = np.where(np.random.default_rng(t).random(g.n_cols) < 0.5, 1.0, -1.0)
+    W[0, :], W[:, ::d] = 0.0, 0.0
+    W[0, ::d], a_l[::d], a_r[::d] = 1.0, 0.0, 2.5
+    theta = (X.astype(np.float64) @ W).reshape(g.n_cols, heads, d)
+    s_l, s_r = ((theta * a.reshape(heads, d)).sum(-1) for a in (a_l, a_r))
+    assert (np.abs(s_r).min(0) - np.abs(s_l).max(0)).min() > 0.1
+    return X, W, a_l, a_r
+
+
+# heads of at most one slice: the two walks of the backward at every chunk length, heads that fill their slice and heads that do not
+@pytest.mark.parametrize("t,least", [(64, 3_000), (128, 140_000), (256, 270_000), (512, 530_000)])
+@pytest.mark.parametrize("heads,d", [(1, 32), (3, 20), (4, 32)])
+def test_narrow_heads_at_chunk_boundaries(ctx, t, least, heads, d):
+    g = pattern(t, least)
+    assert chunk_nnz(g.nnz) == t
+    f_in = 24
+    X, W, a_l, a_r = head_inputs(g, t, f_in, heads, d)
+    dY = synth.normal(t, 25, (g.n_rows, heads * d))
+    A, At = DeviceCSR(g), DeviceCSR(synth.transpose(g))
+    want = oracle.gat_backward_heads(g.n_rows, g.n_cols, g.row_ptr, g.col_idx, X, W, a_l, a_r, heads, dY, slope=0.2)
+    got = ctx.gat_backward_heads(A.s, At.s, ctx.transpose_positions(A.s, At.s), dev(X), dev(W), dev(a_l), dev(a_r), heads, dev(dY), neg_slope=0.2)
+    for gpu, ref, what in zip(got, want, ("dX", "dW", "da_l", "da_r")):
+        assert_close(gpu, ref, what=what)
+
+
+# the forward walk of heads of one slice: more of them than slices are worked on at a time (8), and than one launch takes (16)
+@pytest.mark.parametrize("t,least", [(256, 270_000), (512, 530_000)])
+@pytest.mark.parametrize("heads", [2, 9, 17])
+def test_heads_of_one_walk(ctx, t, least, heads):
+    g = pattern(t, least)
+    f_in, A = 24, DeviceCSR(g)
+    assert chunk_nnz(g.nnz) == t and gat_attention_path(A.s, f_in, heads * 32, 0, heads) == GAT_PATH_ONE_WALK
+    X, W, a_l, a_r = head_inputs(g, t, f_in, heads, 32)
+    want = oracle.gat_layer_heads(g.n_rows, g.n_cols, g.row_ptr, g.col_idx, X, W, a_l, a_r, heads, 0.2, ACT_RELU)
+    assert_close(ctx.gat_layer_heads(A.s, dev(X), dev(W), dev(a_l), dev(a_r), heads, 0, 0.2, ACT_RELU), want, what=f"{heads} heads")
 
 
 # logits of -inf (masked entries) weigh 0 wherever they stand in their row; a row of nothing else is NaN, as 0 / 0 is; the lowest finite
