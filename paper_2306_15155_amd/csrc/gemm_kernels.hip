@@ -508,16 +508,17 @@ __global__ __launch_bounds__(kGemmThreads, 2 * gemm_held(TN)) void k_gemm_bf(Gem
                 const long long y_col = g.y_sliced ? (long long)(col >> 5) * g.n * 32 + (col & 31) : (long long)col;
                 const long long y_ld = g.y_sliced ? 32 : g.ldy;
                 float y[16];
-#pragma unroll
-                for (int r = 0; r < 16; ++r) y[r] = acc[j][r];
                 if (g.add) {
                     const float *add = g.add + (long long)(col >> 5) * g.n * 32 + (col & 31);
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
                         const long long row = row0 + 8 * (r / 4) + (r % 4);
-                        y[r] += add[(kWhole || row < g.n ? row : g.n - 1) * 32];
+                        y[r] = add[(kWhole || row < g.n ? row : g.n - 1) * 32];
                     }
+                    __builtin_amdgcn_sched_barrier(0);   // all sixteen under way before the first is added: short of registers, the scheduler would wait for each
                 }
+#pragma unroll
+                for (int r = 0; r < 16; ++r) y[r] = g.add ? acc[j][r] + y[r] : acc[j][r];
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const long long row = row0 + 8 * (r / 4) + (r % 4);
@@ -564,11 +565,10 @@ __global__ __launch_bounds__(kGemmThreads, 2 * gemm_held(TN)) void k_gemm_bf(Gem
             if (FULL)
 #pragma unroll
                 for (int j = 0; j < TN; ++j) acc[j] += low[FULL ? j : 0];
-            if (__any(not_finite<TN>(acc))) {
+            store(tile);
+            if (__any(not_finite<TN>(acc))) {   // behind the store, whose loads do not wait for it
                 again |= 1ull << (done >> again_shift);
                 store_rows(tile, std::integral_constant<int, kMarks>());
-            } else {
-                store(tile);
             }
             ++done;
             clear();
