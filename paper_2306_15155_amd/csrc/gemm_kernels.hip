@@ -1785,13 +1785,16 @@ static bool gemm_is_large(int64_t n, int m_store) {
 }
 
 // Where the fixed costs of k_gemm_bf (about 6 us: W is fetched and cut before the first multiply, and a wavefront walks all of k) are earned
-// back.  Large products, by k and rows, outputs wider than 192 columns counting more (fp32 kernels / here, us): k = 16, 32 columns, 50,000 rows 6.2 / 7.2, 100,000
-// 8.7 / 8.3.  Below that size, with eight piece products, outputs of at most 64 columns need more rows, whole blocks of 64 the most, for which the fp32 kernel has its widest loads: k = 100, 64 columns, 30,000 rows 9.7 / 11.0; k = 100, 47 columns, 16,000 rows 8.7 / 10.0, 20,000
-// 10.7 / 10.1; k = 128, 32 columns, 16,000 rows 7.6 / 8.6, 20,000 9.7 / 9.4; k = 256, 64 columns, 16,000 rows 12.4 / 14.1, 20,000 15.7 / 14.5; k = 512, 32
-// columns, 6,000 rows 10.6 / 15.8, 12,000 18.8 / 15.7; k = 1024, 64 columns, 16,000 rows 36.5 / 42.7, 20,000 48.6 / 43.2.  Wider ones: k = 32, 192
-// columns, 30,000 rows 15.9 / 12.6; k = 64, 192 columns, 16,000 rows 10.2 / 10.7, 20,000 19.5 / 12.8; k = 128, 96 columns, 16,000 rows 10.5 / 10.4, 256
-// columns, 12,000 rows 14.7 / 14.5; k = 300, 96 columns, 6,000 rows 13.2 / 12.7; k = 1024, 96 columns, 6,000 rows 35.6 / 41.6, 9,000 48.6 / 43.0, 192
-// columns, 6,000 rows 48.3 / 44.1.
+// back, in us on the fp32 kernels / here.  Large products by k and rows, outputs wider than 192 columns counting more: k = 16, 32 columns,
+// 50,000 rows 6.2 / 7.2, 100,000 8.7 / 8.3.  Below that size, with eight piece products:
+//   at most 32 columns: k = 48, 40,000 rows 7.6 / 7.9; k = 64, 20,000 rows 7.1 / 7.1; k = 128, 16,000 rows 7.6 / 8.6, 20,000 9.7 / 9.4; k = 512, 6,000
+//     rows 10.6 / 15.8, 12,000 18.8 / 15.7;
+//   at most 48: k = 100, 16,000 rows 8.7 / 10.0, 20,000 10.7 / 10.1;
+//   64, for which the fp32 kernel has whole blocks: k = 100, 30,000 rows 9.7 / 11.0; k = 256, 16,000 rows 12.4 / 14.1, 20,000 15.7 / 14.5; k = 1024, 16,000
+//     rows 36.5 / 42.7, 20,000 48.6 / 43.2;
+//   more: k = 32, 192 columns, 30,000 rows 15.9 / 12.6; k = 64, 192 columns, 16,000 rows 10.2 / 10.7, 20,000 19.5 / 12.8; k = 128, 256 columns, 12,000 rows
+//     14.7 / 14.5; k = 300, 96 columns, 6,000 rows 13.2 / 12.7; k = 1024, 96 columns, 6,000 rows 35.6 / 41.6, 9,000 48.6 / 43.0, 192 columns,
+//     6,000 rows 48.3 / 44.1.
 bool gemm_uses_pieces(int64_t n, int k, int m_store) {
     if (k < 16 || m_store <= 0) return false;
     const int64_t blocks = (m_store + 31) / 32, rows = n * (blocks > 6 ? blocks : 6) / 6;
@@ -1800,7 +1803,8 @@ bool gemm_uses_pieces(int64_t n, int k, int m_store) {
     if (blocks > 2) return rows >= (k >= 700 && blocks < 6 ? 8000 : k >= 300 ? 6000 : k >= 64 ? 16000 : 28000);
     if (k >= 300) return n >= (k >= 700 ? 20000 : 12000);
     if (k >= 128) return n >= (m_store > 48 ? 20000 : 16000);
-    return k >= 64 && n >= (m_store > 48 ? 65536 : m_store > 32 ? 16000 : 40000);
+    if (m_store > 32) return k >= 64 && n >= (m_store > 48 ? 65536 : 16000);
+    return n >= (k >= 64 ? 20000 : 40000);
 }
 
 hipError_t launch_gemm(const float *A, int64_t lda, const float *W, int64_t ldw, float *Y, int64_t ldy, int64_t n,
@@ -1829,7 +1833,9 @@ hipError_t launch_gemm(const float *A, int64_t lda, const float *W, int64_t ldw,
     {
         const int tn = gemm_bf_blocks(n, m_store), blocks = (m_store + 31) / 32;
         g.n_bn = (blocks + tn - 1) / tn;
-        if (gemm_uses_pieces(n, k, m_store) && lda < (1 << 20) && ldw < (1 << 20)) {   // leading dimensions: 32-bit byte offsets within a block
+        // (a matrix to add costs the fp32 kernels more: TAGCN, update first, 100 -> 64 columns twice on 20,000 rows 80.6 / 72.3 us)
+        const bool pieces = gemm_uses_pieces(n, k, m_store) || (add_sliced && k >= 64 && n >= 16000);
+        if (pieces && lda < (1 << 20) && ldw < (1 << 20)) {   // leading dimensions: 32-bit byte offsets within a block
             auto launch = [&](auto full) {
                 constexpr bool kFull = decltype(full)::value;
                 switch (tn) {

@@ -2519,8 +2519,8 @@ __global__ __launch_bounds__(kBlock) void k_gat_head_cols(GatHeadArgs a) {
     }
 }
 
-// the rows of dTheta and ds_r that span several chunks, in chunk order or (long rows) eight pieces at a time: a wavefront takes 8 chunks' rows,
-// lanes over the columns (lane 32: ds_r)
+// the rows of dTheta and ds_r that span several chunks, their pieces added one after the other in chunk order (eight loads under way): a wavefront
+// takes 8 chunks' rows, lanes over the columns (lane 32: ds_r)
 __global__ __launch_bounds__(kBlock) void k_gat_head_cols_fixup(GatHeadArgs a) {
     const int head = blockIdx.y, lane = threadIdx.x & 63;
     const int c0 = 1 + (blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6)) * 8;
