@@ -339,18 +339,19 @@ __device__ __forceinline__ unsigned pack_bf16(unsigned first, unsigned second) {
 // round trip and the next tile's is under way); a group changes places through 4 KB of LDS that no other wavefront touches (16-byte pieces,
 // exchanged within a row by the row's number so that neither side meets bank conflicts) into the order the instruction reads, lane (row, k
 // half) eight consecutive k, and is cut there.  A is thus read once and cut once per block of columns, and never waits for a barrier.  W is cut
-// once per workgroup (512 threads) and left in LDS in lane order, every fragment one contiguous kilobyte:
+// by the workgroup (512 threads) and left in LDS in lane order, every fragment one contiguous kilobyte:
 //   CHUNKED = false: all of W's k fits beside the rows of A in 160 KB; it is cut once, after which the wavefronts walk their rows
 //     independently of each other;
-//   CHUNKED = true: chunks of gemm_kc k in two buffers, the next chunk fetched and cut while this one is multiplied, one barrier per chunk.
+//   CHUNKED = true: chunks of gemm_kc k in two buffers, the next chunk fetched and cut while this one is multiplied, one barrier per chunk; all of W
+//     is cut again for every eight tiles of rows, half as much cutting again as A's.
 // The grid is what the chip holds at a time; every workgroup takes an equal share of the 32-row tiles, and the blocks of columns of one
 // share run on one XCD, so that A comes from its L2 for all but the first of them.
 // Rows past the end read the last row and are not stored; k past the end are cleared in both operands.
-// Up to about 128 k and 128 columns it is bound by memory (1 M rows, 64 -> 32 columns 82 us, 4.7 TB/s); beyond, by the matrix pipe and the vector
+// Up to about 128 k and 128 columns it is bound by memory (1 M rows, 64 -> 32 columns 79 us, 4.8 TB/s); beyond, by the matrix pipe and the vector
 // instructions of the cuts, which hardly overlap on a SIMD, at a clock that the matrix load brings down to about 1.9 GHz.  Before (a block of 256
-// rows a workgroup, A through LDS uncut behind a barrier per 16 k) / now, us: 100,000 x 64 x 256 50 / 33, 233,000 x 41 x 256 89 / 63, 233,000 x 602
-// x 64 204 / 169, 2.45 M x 100 x 512 2,660 / 2,150, 12 M x 32 x 128 1,800 / 1,600, 150,000 x 333 x 160 180 / 153, 233,000 x 602 x 256 493 / 467, 2.45 M
-// x 512 x 512 7,560 / 7,640; and against the fp32 kernel 30,000 x 602 x 256 97 / 63, 50,000 x 128 x 128 30 / 23.
+// rows a workgroup, A through LDS uncut behind a barrier per 16 k) / now, us: 100,000 x 64 x 256 52 / 35, 233,000 x 41 x 256 95 / 70, 233,000 x 602
+// x 64 206 / 177, 2.45 M x 100 x 512 2,670 / 2,110, 12 M x 32 x 128 1,800 / 1,610, 150,000 x 333 x 160 184 / 153, 233,000 x 602 x 256 502 / 470, 2.45 M
+// x 512 x 512 7,430 / 7,560; and with eight products against the fp32 kernel 30,000 x 602 x 256 98 / 78, 50,000 x 128 x 128 29 / 28.
 constexpr int kGemmThreads = 512, kGemmWaves = kGemmThreads / 64, kGemmCusPerXcd = 32;
 constexpr size_t kGemmLds = 160 * 1024;
 constexpr int gemm_kc(int tn) { return tn <= 2 ? 128 : 64; }     // k per chunk: 24 to 48 KB of pieces a buffer
@@ -1790,7 +1791,7 @@ static int gemm_bf_blocks(int64_t n, int m_store) {
 // Products of at least a block of 256 rows x 128 columns (the columns there are, up to 64) per compute unit take six piece products, smaller ones
 // eight: there the matrix pipe is seldom the bound and the two cost little (30,000 x 602 x 256 61 -> 72 us, 16,000 x 100 x 64 9.9 -> 10.1), and what a single
 // term makes up stays as exact as on the fp32 instruction, which these sizes would take otherwise (96 us, 8.1).  Above, eight cost 13 % on
-// average and more where four blocks of columns need two sets of accumulators (233,000 x 602 x 256 467 -> 560).
+// average (64,000 x 602 x 256 119 -> 139).
 static bool gemm_is_large(int64_t n, int m_store) {
     const int64_t blocks = (m_store + 31) / 32;
     return (n + 255) / 256 * (blocks <= 2 ? 1 : (blocks + 3) / 4) >= 256;
