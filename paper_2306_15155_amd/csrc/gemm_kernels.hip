@@ -1113,7 +1113,7 @@ __global__ void k_tiles_combine_pm(float *__restrict__ C, long long n_rows, int 
 // wavefront, here 1,024).  Both operands are rows with k contiguous: two neighbouring threads take the 16 k of a row and step, cut eight each and leave
 // them in LDS in lane order, so that an element is cut once per workgroup; two buffers, one barrier per step (8 rows of padding between the
 // halves of k: the two threads' 16-byte writes fall on different banks).  22,334 tiles at 256 columns, beside the remainder's dot products: GAT
-// training on 115 M entries 17.99 ms with the fp32 instruction, 17.43 so (six products: 17.19).  Against fp64, in 2^-24 of the terms' magnitudes, fp32
+// training on 115 M entries 17.9 ms with the fp32 instruction, 17.3 so (six products: 17.2).  Against fp64, in 2^-24 of the terms' magnitudes, fp32
 // instruction / so: rms of sums over 128 to 256 columns 0.39-0.40 / 0.11-0.12, with terms of one sign 2.6-3.6 / 1.0-1.4; single products 0.43 / 0.43,
 // the largest 1.00 / 1.00 (six products: 1.4 measured, 2.0 where a second piece is as large as it gets).
 __global__ __launch_bounds__(kThreads, 2) void k_tiles_sddmm(const float *__restrict__ Lh, const float *__restrict__ Rh, int f,
@@ -1788,10 +1788,10 @@ static int gemm_bf_blocks(int64_t n, int m_store) {
     return tn;
 }
 
-// Products of at least a block of 256 rows x 128 columns (the columns there are, up to 64) per compute unit take six piece products, smaller ones
-// eight: there the matrix pipe is seldom the bound and the two cost little (30,000 x 602 x 256 61 -> 72 us, 16,000 x 100 x 64 9.9 -> 10.1), and what a single
-// term makes up stays as exact as on the fp32 instruction, which these sizes would take otherwise (96 us, 8.1).  Above, eight cost 13 % on
-// average (64,000 x 602 x 256 119 -> 139).
+// Products of 256 blocks of 256 rows by up to 128 columns and more (a block per compute unit) take six piece products, smaller ones eight: there the
+// matrix pipe is seldom the bound and the two cost little (30,000 x 602 x 256 61 -> 72 us, 16,000 x 100 x 64 9.9 -> 10.1), and what a single term makes
+// up stays as exact as on the fp32 instruction, which these sizes would take otherwise (96 us, 8.1).  Above, eight cost 13 % on average (64,000 x
+// 602 x 256 119 -> 139).
 static bool gemm_is_large(int64_t n, int m_store) {
     const int64_t blocks = (m_store + 31) / 32;
     return (n + 255) / 256 * (blocks <= 2 ? 1 : (blocks + 3) / 4) >= 256;
