@@ -111,6 +111,33 @@ __device__ __forceinline__ void lds_exchange() {
     __builtin_amdgcn_wave_barrier();
 }
 
+// value of x in another lane by a data-parallel-primitive move (no LDS traffic), `none` where the move has no source; every lane is active where
+// these are used
+template <int CTRL> __device__ __forceinline__ int dpp_i32(int x, int none = 0) { return __builtin_amdgcn_update_dpp(none, x, CTRL, 0xF, 0xF, false); }
+template <int CTRL> __device__ __forceinline__ float dpp_f32(float x, float none = 0.f) { return __int_as_float(dpp_i32<CTRL>(__float_as_int(x), __float_as_int(none))); }
+
+// One step of a scan over the wavefront's lanes by data-parallel-primitive moves: what the lane gets from the one a step below, `none` where there is
+// no such lane.  Steps 0 to 3 reach 1, 2, 4 and 8 lanes down within a row of 16 lanes, step 4 hands the last lane of rows 0 and 2 to all of
+// rows 1 and 3, step 5 lane 31 to the upper half: after six steps of v = op(from, v) every lane holds the sum up to itself.  A move by the LDS
+// crossbar (__shfl) waits a hundred cycles a step, these a few.  All lanes must be active.
+template <int STEP> __device__ __forceinline__ int scan_from(int x, int none) {
+    constexpr int kCtrl[6] = {0x111, 0x112, 0x114, 0x118, 0x142, 0x143}, kRows[6] = {0xF, 0xF, 0xF, 0xF, 0xA, 0xC};
+    return __builtin_amdgcn_update_dpp(none, x, kCtrl[STEP], kRows[STEP], 0xF, false);
+}
+template <int STEP> __device__ __forceinline__ float scan_from(float x, float none) {
+    return __int_as_float(scan_from<STEP>(__float_as_int(x), __float_as_int(none)));
+}
+// calls step(std::integral_constant<int, s>) for s = 0 .. 5
+template <class Step> __device__ __forceinline__ void scan_steps(Step step) {
+    step(std::integral_constant<int, 0>()); step(std::integral_constant<int, 1>()); step(std::integral_constant<int, 2>());
+    step(std::integral_constant<int, 3>()); step(std::integral_constant<int, 4>()); step(std::integral_constant<int, 5>());
+}
+// the value of the lane before / behind, `none` in the first / last lane
+__device__ __forceinline__ int lane_before(int x, int none) { return dpp_i32<0x138>(x, none); }
+__device__ __forceinline__ float lane_before(float x, float none) { return dpp_f32<0x138>(x, none); }
+__device__ __forceinline__ int lane_behind(int x, int none) { return dpp_i32<0x130>(x, none); }
+__device__ __forceinline__ float lane_behind(float x, float none) { return dpp_f32<0x130>(x, none); }
+
 template <int PER> struct FlatChunk {
     int lo, hi, i_first, i1;
     bool cont;              // the first row began in an earlier chunk: its sum goes to the chunk's carry slot
@@ -173,13 +200,11 @@ __device__ __forceinline__ FlatChunk<PER> flat_rows_from(const NnzArgs &a, int c
         c.rid[e] = top;
     }
     int run = top;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int o = __shfl_up(run, off, 64);
-        if (lane >= off) run = o > run ? o : run;
-    }
-    c.prev_row = __shfl_up(run, 1, 64);
-    if (lane == 0) c.prev_row = -1;
+    scan_steps([&](auto st) {
+        const int o = scan_from<decltype(st)::value>(run, -1);
+        run = o > run ? o : run;
+    });
+    c.prev_row = lane_before(run, -1);
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
         c.rid[e] = c.rid[e] > c.prev_row ? c.rid[e] : c.prev_row;
@@ -234,20 +259,17 @@ __device__ __forceinline__ void flat_sums(const FlatChunk<PER> &c, int lane, con
         for (int n = 0; n < N; ++n) run[n] += v[n][e];
     }
     int f = started;   // run: the tail from here on
+    scan_steps([&](auto st) {
+        const int of = scan_from<decltype(st)::value>(f, 0);
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        float o[N];
-#pragma unroll
-        for (int n = 0; n < N; ++n) o[n] = __shfl_up(run[n], off, 64);
-        const int of = __shfl_up(f, off, 64);
-        if (lane >= off) {
-#pragma unroll
-            for (int n = 0; n < N; ++n) if (!f) run[n] += o[n];
-            f |= of;
+        for (int n = 0; n < N; ++n) {
+            const float o = scan_from<decltype(st)::value>(run[n], 0.f);
+            run[n] += f ? 0.f : o;
         }
-    }
+        f |= of;
+    });
 #pragma unroll
-    for (int n = 0; n < N; ++n) before[n] = __shfl_up(run[n], 1, 64);   // the open row piece of the lanes before this one
+    for (int n = 0; n < N; ++n) before[n] = lane_before(run[n], 0.f);   // the open row piece of the lanes before this one
     const int head_row = (c.starts & 1u) ? c.prev_row : c.rid[0];
     if (started && head_row >= 0 && lane > 0) {
 #pragma unroll
@@ -275,22 +297,27 @@ __device__ __forceinline__ void flat_piece_max(const FlatChunk<PER> &c, int lane
         if (!((c.starts >> (q + 1)) & 1u)) mx[q] = mx[q + 1];
     float fwd = mx[PER - 1], bwd = (c.starts & 1u) ? -INFINITY : mx[0];
     int ff = c.starts != 0u, fb = ff;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const float of = __shfl_up(fwd, off, 64), ob = __shfl_down(bwd, off, 64);
-        const int gf = __shfl_up(ff, off, 64), gb = __shfl_down(fb, off, 64);
-        if (lane >= off) {
-            if (!ff) fwd = fmaxf(fwd, of);
-            ff |= gf;
-        }
-        if (lane + off < 64) {
-            if (!fb) bwd = fmaxf(bwd, ob);
-            fb |= gb;
-        }
-    }
-    float before = __shfl_up(fwd, 1, 64), behind = __shfl_down(bwd, 1, 64);
-    if (lane == 0) before = -INFINITY;
-    if (lane == 63) behind = -INFINITY;
+    scan_steps([&](auto st) {
+        const float o = scan_from<decltype(st)::value>(fwd, -INFINITY);
+        const int g = scan_from<decltype(st)::value>(ff, 0);
+        fwd = ff ? fwd : fmaxf(fwd, o);
+        ff |= g;
+    });
+    // backwards: within the rows of 16 lanes, then what lies behind the row (its first lanes' values, at most three)
+    auto back = [&](float o, int g) {
+        bwd = fb ? bwd : fmaxf(bwd, o);
+        fb |= g;
+    };
+    back(dpp_f32<0x101>(bwd, -INFINITY), dpp_i32<0x101>(fb, 0));
+    back(dpp_f32<0x102>(bwd, -INFINITY), dpp_i32<0x102>(fb, 0));
+    back(dpp_f32<0x104>(bwd, -INFINITY), dpp_i32<0x104>(fb, 0));
+    back(dpp_f32<0x108>(bwd, -INFINITY), dpp_i32<0x108>(fb, 0));
+    auto first_of = [&](int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bwd), l)); };
+    const float b3 = first_of(48);
+    const float b2 = __builtin_amdgcn_readlane(fb, 32) ? first_of(32) : fmaxf(first_of(32), b3);
+    const float b1 = __builtin_amdgcn_readlane(fb, 16) ? first_of(16) : fmaxf(first_of(16), b2);
+    if (!fb && lane < 48) bwd = fmaxf(bwd, lane < 16 ? b1 : lane < 32 ? b2 : b3);
+    const float before = lane_before(fwd, -INFINITY), behind = lane_behind(bwd, -INFINITY);
     bool open = true;   // entries up to the lane's first row start belong to a piece that began before the lane
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
@@ -669,25 +696,32 @@ __global__ __launch_bounds__(kBlock) void k_spmm(SpmmArgs a) {
 // SpMM as a flat walk.  k_spmm walks the rows of its chunk one after the other, two or three dependent memory round trips each: with 20
 // entries per row a chunk of 512 entries is a chain of 75 round trips (2.1 M entries x 32 columns: 67 us).  Here the chunk's entries are cut
 // into eight equal parts, one per group of eight lanes, whatever rows they belong to; a group gathers its entries in order, eight in
-// flight, and closes a row where the entry's flag (the sign bit of its column in LDS) says that it is the row's last one in the chunk.
+// flight, and closes a row where the entry holds one in LDS (the row's last entry in the chunk; -1 elsewhere).
 // The first row a group closes and what it has left at the end are joined over the groups by a scan; rows in between are written
-// directly.  Rows (by the marks of flat_rows), columns, weights and row factors are in LDS before the loop, so that the loop waits for
-// gathers only.  Tiles, chunk ownership, carry slots and fix-up are those of k_spmm.
+// directly.  The row that goes on in the next chunk is closed nowhere: it is what the last group is left with.  Columns, weights and row factors are in LDS
+// before the loop, and what an iteration needs of them and of the rows' ends is read ahead of it, so that a close waits for nothing.  Tiles, chunk ownership, carry slots and fix-up are those of k_spmm.
+// Where no entry needs its row (no weights, or weights without a row factor) the lane that holds a row's pointers marks its end, and the first eight gathers
+// leave as soon as the columns are there, before the row pointers are; elsewhere the rows are spread over the entries by flat_rows first.
+// PLAIN: rows are written in whole 16-byte pieces and not added to; the code for the rest, unrolled into every close, costs 1 to 3 %.
+// Bound by the gathers: of lines, 4 ps each from the L2s and up to 18 from far, whatever part of a line a row fills.  With the ends as flags and the rows
+// looked up at a close (which the chunks of the shortest rows, the slowest, did for every entry) and the gathers behind the row pointers, before / now:
+// 2.1 M entries on 100,000 rows x 64 columns 56 / 39 us (gathers alone 30), 105,000 entries x 100 columns 16.1 / 13.1 us, 42 M entries of a panel-major
+// remainder x 256 columns 2.10 / 2.03 ms, 127 M entries on 2.45 M rows x 512 columns 24.7 / 23.7 ms.
 // kSpmmAttnFused: the logits of the chunk are formed before the loop, and with them the maximum and the sum of every row piece
 // (segmented scans), so that the loop is a plain weighted sum.
 // B is row-major (a row holds all its 32-column tiles) or slice-major (all rows of tile 0, then all rows of tile 1, ...: what an XCD
 // gathers from is then one contiguous range, which spreads evenly over the memory channels whatever the row pitch).
-template <int MODE, int PER, int LPG, bool OFF32>
+template <int MODE, int PER, int LPG, bool OFF32, bool PLAIN>
 __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
-    constexpr int G = 64 / LPG, T = 64 * PER, PART = T / G, PAD = 4, U = 8;
+    constexpr int G = 64 / LPG, T = 64 * PER, PART = T / G, PAD = 4, U = 8, WORDS = T + G * PAD;
     constexpr bool kWeights = MODE != SENSEI_SPMM_PATTERN;
     // where entries have weights the row factor goes into them (launch_spmm tells the fix-up so); a third array in LDS would cost a
     // third of the wavefronts
     constexpr bool kScaleRows = MODE == SENSEI_SPMM_PATTERN || MODE == kSpmmAttnFused;
-    __shared__ __attribute__((aligned(16))) int s_col[kWavesPerBlock][T + G * PAD];
-    __shared__ __attribute__((aligned(16))) int s_row[kWavesPerBlock][T + G * PAD];
-    __shared__ __attribute__((aligned(16))) float s_scale[kScaleRows ? kWavesPerBlock : 1][kScaleRows ? T + G * PAD : 4];
-    __shared__ __attribute__((aligned(16))) float s_w[kWeights ? kWavesPerBlock : 1][kWeights ? T + G * PAD : 4];
+    __shared__ __attribute__((aligned(16))) int s_col[kWavesPerBlock][WORDS];
+    __shared__ __attribute__((aligned(16))) int s_row[kWavesPerBlock][WORDS];
+    __shared__ __attribute__((aligned(16))) float s_scale[kScaleRows ? kWavesPerBlock : 1][kScaleRows ? WORDS : 4];
+    __shared__ __attribute__((aligned(16))) float s_w[kWeights ? kWavesPerBlock : 1][kWeights ? WORDS : 4];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane / LPG, li = lane % LPG;
     const int per_set = a.n_groups * a.tiles_live;
     const int set = blockIdx.x / per_set, in_set = blockIdx.x % per_set;
@@ -708,16 +742,11 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
     };
     int *rows = s_row[wave], *cols = s_col[wave];
     float *scale = s_scale[kScaleRows ? wave : 0], *wgt = s_w[kWeights ? wave : 0];
-
-    int cont_row = -1, open_row = -1;   // the row continued from the chunk before; the row that goes on in the next chunk
-    auto write_row = [&](int row, float sc, float4 v) {
-        if (row == cont_row) {
-            if (fok) *reinterpret_cast<float4 *>(a.carry + (size_t)chunk * a.f_carry + f0) = v;
-            return;
-        }
+    const bool vec = PLAIN ? f0 < a.f_store : a.store_vec_ok && f0 + 4 <= a.f_store;
+    // a finished row, or (finish = false) a piece of one that goes on in the next chunk
+    auto write_row = [&](int row, float sc, float4 v, bool finish) {
         float *dst = c_lane + (size_t)row * a.ldc;
-        const bool vec = a.store_vec_ok && f0 + 4 <= a.f_store;
-        if (a.accumulate) {   // later column panel: add to what the earlier panels left in C
+        if (!PLAIN && a.accumulate) {   // later column panel: add to what the earlier panels left in C
             if (vec) {
                 const float4 o = *reinterpret_cast<const float4 *>(dst);
                 v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
@@ -728,7 +757,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
                 if (f0 + 3 < a.f_store) v.w += dst[3];
             }
         }
-        if (a.finalize && row != open_row) {
+        if (a.finalize && finish) {
             v.x *= sc; v.y *= sc; v.z *= sc; v.w *= sc;
             if (a.act == SENSEI_ACT_RELU) {
                 v.x = v.x > 0.f ? v.x : 0.f; v.y = v.y > 0.f ? v.y : 0.f; v.z = v.z > 0.f ? v.z : 0.f; v.w = v.w > 0.f ? v.w : 0.f;
@@ -736,7 +765,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
         }
         if (vec) {
             *reinterpret_cast<float4 *>(dst) = v;
-        } else {
+        } else if (!PLAIN) {
             if (f0 < a.f_store) dst[0] = v.x;
             if (f0 + 1 < a.f_store) dst[1] = v.y;
             if (f0 + 2 < a.f_store) dst[2] = v.z;
@@ -744,6 +773,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
         }
     };
     const NnzArgs nz = {a.row_ptr, a.col_idx, a.chunk_row, a.n_rows, a.nnz, a.chunk_nnz, a.n_chunks};
+    const int lo = chunk * T, hi = a.nnz - lo > T ? lo + T : a.nnz, n = hi - lo;
     float es[PER];
     int col[PER];
     if (a.nnz > 0) {
@@ -768,40 +798,92 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
         i0 = __builtin_amdgcn_readfirstlane(a.chunk_row[chunk]);
         i1 = __builtin_amdgcn_readfirstlane(a.chunk_row[chunk + 1]);
     }
-    const FlatChunk<PER> c = flat_rows_from<PER, PAD, G>(nz, chunk, i0, i1, lane, rows, [&](int r0, bool none) {
+    auto empty_rows = [&](int r0, bool none) {   // rows without entries: one per group at a time
         unsigned long long m = __ballot(none);
-        for (int b = 0; m; ++b, m >>= G) {   // rows without entries: one per group at a time
+        for (int b = 0; m; ++b, m >>= G) {
             if (!((m >> g) & 1ull)) continue;
             const int row = r0 + b * G + g;
-            write_row(row, MODE == SENSEI_SPMM_PATTERN && a.r ? a.r[row] : 1.f, make_float4(0.f, 0.f, 0.f, 0.f));
+            write_row(row, MODE == SENSEI_SPMM_PATTERN && a.r ? a.r[row] : 1.f, make_float4(0.f, 0.f, 0.f, 0.f), true);
         }
-    });
-    if (c.lo >= c.hi) return;
-    const int n = c.hi - c.lo;
-    if (c.cont) cont_row = c.i_first;
-    {   // the last entry of every row piece is flagged (sign bit of its row for now)
-        const int next_start = __shfl_down((int)(c.starts & 1u), 1, 64);
-        unsigned ends = (c.starts >> 1) | ((lane < 63 ? (unsigned)next_start : 0u) << (PER - 1));
-        const int e_last = n - 1 - lane * PER;
-        if (e_last >= 0 && e_last < PER) ends |= 1u << e_last;
-#pragma unroll
-        for (int e = 0; e < PER; ++e) rows[flat_at<PER, PAD, G>(lane * PER + e)] = (int)((unsigned)c.rid[e] | (((ends >> e) & 1u) << 31));
-        const int last_row = __shfl(c.rid[PER - 1], 63, 64);
-        if (__builtin_amdgcn_readfirstlane(a.row_ptr[last_row + 1]) > c.hi) open_row = __builtin_amdgcn_readfirstlane(last_row);
-    }
-    lds_exchange();
+    };
     const bool use_scale = MODE == kSpmmSoftmax ? a.scale_weights != 0 : MODE != kSpmmAttnFused && a.r && (kWeights ? a.scale_weights != 0 : a.finalize != 0);
-    {
-        int rw[PER];
+    int cont_row = -1, open_row = -1;   // the row continued from the chunk before; the row that goes on in the next chunk
+    const int part0 = g * (PART + PAD);
+    float4 b[U];
+    auto fetch = [&](int s) {   // the gathers of a group's entries s .. s + U - 1
+#pragma unroll
+        for (int q = 0; q < U; q += 4) {
+            const int4 t = *reinterpret_cast<const int4 *>(&cols[part0 + s + q]);
+            b[q] = gather(t.x); b[q + 1] = gather(t.y); b[q + 2] = gather(t.z); b[q + 3] = gather(t.w);
+        }
+    };
+    if (MODE == SENSEI_SPMM_PATTERN || ((MODE == SENSEI_SPMM_WEIGHTED || MODE == SENSEI_SPMM_SCALED) && !use_scale)) {
+        // No entry needs to know its row: the last entry of every row is marked with it (and its factor) by the lane that has its pointers, and
+        // the first gathers are under way before those arrive.
+        const int r_first = i0 > 0 ? i0 - 1 : 0;
+        int rs = 0, re = 0;
+        float sc = 1.f;
+        auto pointers = [&](int r, int &s, int &e, float &x) {
+            if (r < a.n_rows) {
+                s = a.row_ptr[r];
+                e = a.row_ptr[r + 1];
+                if (kScaleRows && use_scale) x = a.r[r];
+            }
+        };
+        if (r_first + lane < i1 || lane == 0) pointers(r_first + lane, rs, re, sc);
+        for (int i = lane; i < WORDS / 4; i += 64) reinterpret_cast<int4 *>(rows)[i] = make_int4(-1, -1, -1, -1);
+        if (n > 0) {
+#pragma unroll
+            for (int u = 0; u < PER; ++u) cols[flat_at<PER, PAD, G>(u * 64 + lane)] = col[u];
+            if (MODE == SENSEI_SPMM_SCALED) {
+#pragma unroll
+                for (int u = 0; u < PER; ++u) es[u] = a.c[col[u]];
+            }
+        }
+        lds_exchange();
+        if (n > 0) fetch(0);
+        const bool cont = i0 > 0 && __builtin_amdgcn_readfirstlane(re) > lo && a.nnz > 0;
+        const int i_first = cont ? i0 - 1 : i0;
+        if (cont) cont_row = i_first;
+        for (int r0 = r_first; r0 < i1; r0 += 64) {
+            const int r = r0 + lane, ahead = r + 64;
+            int s_ahead = 0, e_ahead = 0;
+            float sc_ahead = 1.f;
+            if (ahead < i1) pointers(ahead, s_ahead, e_ahead, sc_ahead);
+            const bool mine = r < i1 && r >= i_first, none = mine && re <= rs;
+            if (mine && !none && re <= hi) {
+                const int at = flat_at<PER, PAD, G>(re - 1 - lo);
+                rows[at] = r;
+                if (kScaleRows) scale[at] = sc;
+            }
+            const unsigned long long open = __ballot(mine && !none && re > hi);
+            if (open) open_row = r0 + __ffsll((long long)open) - 1;
+            empty_rows(r0, none);
+            rs = s_ahead;
+            re = e_ahead;
+            sc = sc_ahead;
+        }
+        if (n <= 0) return;
+        if (kWeights) {
+#pragma unroll
+            for (int u = 0; u < PER; ++u) wgt[flat_at<PER, PAD, G>(u * 64 + lane)] = es[u];
+        }
+        lds_exchange();
+    } else {
+        const FlatChunk<PER> c = flat_rows_from<PER, PAD, G>(nz, chunk, i0, i1, lane, rows, empty_rows);
+        if (n <= 0) return;
+        if (c.cont) cont_row = c.i_first;
+        const int last_row = __builtin_amdgcn_readfirstlane(__shfl(c.rid[PER - 1], 63, 64));
+        if (__builtin_amdgcn_readfirstlane(a.row_ptr[last_row + 1]) > hi) open_row = last_row;
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
-            const int at = flat_at<PER, PAD, G>(u * 64 + lane);
-            rw[u] = rows[at];
-            cols[at] = (int)((unsigned)col[u] | ((unsigned)rw[u] & 0x80000000u));
-            rw[u] &= 0x7fffffff;
+            cols[flat_at<PER, PAD, G>(u * 64 + lane)] = col[u];
             if (MODE == SENSEI_SPMM_SCALED) es[u] = a.c[col[u]];
             if (MODE == kSpmmAttnFused) es[u] = a.s_r[tile * a.head_vec + col[u]];
         }
+        int rw[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) rw[u] = rows[flat_at<PER, PAD, G>(u * 64 + lane)];
         if (MODE == kSpmmSoftmax) {
             // (max, sum) pairs of the rows; gathered per entry where the chunk has more rows than lanes
             const bool in_lanes = c.i1 - c.i_first <= 64;
@@ -815,16 +897,11 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
                 es[u] = __expf(es[u] - p.x);
                 if (use_scale) es[u] *= inv_z(p.y);
             }
-        } else if (use_scale) {
+        } else if (MODE != kSpmmAttnFused) {
             const RowVals rv = row_vals<PER>(c, lane, a.r);
 #pragma unroll
-            for (int u = 0; u < PER; ++u) {
-                const float x = row_val(rv, rw[u]);
-                if (kWeights) es[u] *= x;
-                else scale[flat_at<PER, PAD, G>(u * 64 + lane)] = x;
-            }
-        }
-        if (MODE == kSpmmAttnFused) {
+            for (int u = 0; u < PER; ++u) es[u] *= row_val(rv, rw[u]);
+        } else {
             const RowVals rv = row_vals<PER>(c, lane, a.s_l + tile * a.head_vec);
 #pragma unroll
             for (int u = 0; u < PER; ++u) {
@@ -832,54 +909,59 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
                 es[u] = t > 0.f ? t : a.slope * t;
             }
         }
-        if (kWeights) {
 #pragma unroll
-            for (int u = 0; u < PER; ++u) wgt[flat_at<PER, PAD, G>(u * 64 + lane)] = es[u];
-        }
-    }
-    lds_exchange();
-    if (MODE == kSpmmAttnFused) {
-        float e[PER], mx[PER], p[PER];
-        const int n_mine = n - lane * PER;
-#pragma unroll
-        for (int q = 0; q < PER; ++q) e[q] = q < n_mine ? wgt[flat_at<PER, PAD, G>(lane * PER + q)] : -INFINITY;
-        flat_piece_max<PER>(c, lane, e, mx);
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            p[q] = q < n_mine ? __expf(e[q] - mx[q]) : 0.f;
-            wgt[flat_at<PER, PAD, G>(lane * PER + q)] = p[q];
-            scale[flat_at<PER, PAD, G>(lane * PER + q)] = mx[q];
-        }
+        for (int u = 0; u < PER; ++u) wgt[flat_at<PER, PAD, G>(u * 64 + lane)] = es[u];
         lds_exchange();
-        flat_sum<PER>(c, lane, p, [&](int i, float z, int end) {
-            const int at = flat_at<PER, PAD, G>(end);
-            if (tile == 0 || a.head_vec) {   // every feature tile of the chunk forms the same pairs: one writes them (a tile is a head: each its own)
-                if (i == cont_row) a.carry_mz[(a.head_vec ? (size_t)tile * a.n_chunks : 0) + chunk] = make_float2(scale[at], z);
-                else if (i == open_row) a.mz_out[tile * a.head_mz + i] = make_float2(scale[at], z);
+        fetch(0);
+        {   // the last entry of a row in the chunk keeps its row, the others and the row that goes on are no place to close one
+            unsigned ends = (c.starts >> 1) | ((unsigned)lane_behind((int)(c.starts & 1u), 0) << (PER - 1));
+            const int e_last = n - 1 - lane * PER;
+            if (e_last >= 0 && e_last < PER && open_row < 0) ends |= 1u << e_last;
+#pragma unroll
+            for (int e = 0; e < PER; ++e) rows[flat_at<PER, PAD, G>(lane * PER + e)] = (ends >> e) & 1u ? c.rid[e] : -1;
+        }
+        if (MODE == kSpmmAttnFused) {
+            float e[PER], mx[PER], p[PER];
+            const int n_mine = n - lane * PER;
+#pragma unroll
+            for (int q = 0; q < PER; ++q) e[q] = q < n_mine ? wgt[flat_at<PER, PAD, G>(lane * PER + q)] : -INFINITY;
+            flat_piece_max<PER>(c, lane, e, mx);
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+                p[q] = q < n_mine ? __expf(e[q] - mx[q]) : 0.f;
+                wgt[flat_at<PER, PAD, G>(lane * PER + q)] = p[q];
+                scale[flat_at<PER, PAD, G>(lane * PER + q)] = mx[q];
             }
-            scale[at] = inv_z(z);
-        });
+            lds_exchange();
+            flat_sum<PER>(c, lane, p, [&](int i, float z, int end) {
+                const int at = flat_at<PER, PAD, G>(end);
+                if (tile == 0 || a.head_vec) {   // every feature tile of the chunk forms the same pairs: one writes them (a tile is a head: each its own)
+                    if (i == cont_row) a.carry_mz[(a.head_vec ? (size_t)tile * a.n_chunks : 0) + chunk] = make_float2(scale[at], z);
+                    else if (i == open_row) a.mz_out[tile * a.head_mz + i] = make_float2(scale[at], z);
+                }
+                scale[at] = inv_z(z);
+            });
+        }
         lds_exchange();
     }
 
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), head = acc;
-    int head_at = -1;
-    const int part0 = g * (PART + PAD);
+    int head_row = -1;
+    float head_sc = 1.f;
+    const bool scaled = MODE == kSpmmAttnFused || (MODE == SENSEI_SPMM_PATTERN && use_scale);
     for (int s = 0; s < PART && s < n; s += U) {
-        int cf[U];
-        float w[U];
-        float4 b[U];
+        int end[U];
+        float w[U], sc[U];
 #pragma unroll
         for (int q = 0; q < U; q += 4) {
-            const int4 t = *reinterpret_cast<const int4 *>(&cols[part0 + s + q]);
-            cf[q] = t.x; cf[q + 1] = t.y; cf[q + 2] = t.z; cf[q + 3] = t.w;
-            if (kWeights) {
-                const float4 v = *reinterpret_cast<const float4 *>(&wgt[part0 + s + q]);
-                w[q] = v.x; w[q + 1] = v.y; w[q + 2] = v.z; w[q + 3] = v.w;
-            }
+            const int4 r4 = *reinterpret_cast<const int4 *>(&rows[part0 + s + q]);
+            float4 w4 = make_float4(1.f, 1.f, 1.f, 1.f), s4 = w4;
+            if (kWeights) w4 = *reinterpret_cast<const float4 *>(&wgt[part0 + s + q]);
+            if (kScaleRows && scaled) s4 = *reinterpret_cast<const float4 *>(&scale[part0 + s + q]);
+            end[q] = r4.x; end[q + 1] = r4.y; end[q + 2] = r4.z; end[q + 3] = r4.w;
+            w[q] = w4.x; w[q + 1] = w4.y; w[q + 2] = w4.z; w[q + 3] = w4.w;
+            sc[q] = s4.x; sc[q + 1] = s4.y; sc[q + 2] = s4.z; sc[q + 3] = s4.w;
         }
-#pragma unroll
-        for (int q = 0; q < U; ++q) b[q] = gather(cf[q] & 0x7fffffff);
 #pragma unroll
         for (int q = 0; q < U; ++q) {
             if (kWeights) {
@@ -887,33 +969,42 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
             } else {
                 acc.x += b[q].x; acc.y += b[q].y; acc.z += b[q].z; acc.w += b[q].w;
             }
-            if (cf[q] < 0) {
-                const int at = part0 + s + q;
-                if (head_at < 0) {
+            if (end[q] >= 0) {
+                if (head_row < 0) {
                     head = acc;
-                    head_at = at;
+                    head_row = end[q];
+                    head_sc = sc[q];
                 } else {
-                    write_row(rows[at] & 0x7fffffff, kScaleRows && (use_scale || MODE == kSpmmAttnFused) ? scale[at] : 1.f, acc);
+                    write_row(end[q], sc[q], acc, true);
                 }
                 acc = make_float4(0.f, 0.f, 0.f, 0.f);
             }
         }
+        if (s + U < PART) fetch(s + U);
     }
-    int f = head_at >= 0;
-    float4 in = acc;
+    // a group's first row joins what the groups before it have left; the row that goes on in the next chunk is what the last group is left with
+    int f = head_row >= 0;
 #pragma unroll
     for (int off = LPG; off < 64; off <<= 1) {
-        const float x = __shfl_up(in.x, off, 64), y = __shfl_up(in.y, off, 64), z = __shfl_up(in.z, off, 64), w = __shfl_up(in.w, off, 64);
+        const float x = __shfl_up(acc.x, off, 64), y = __shfl_up(acc.y, off, 64), z = __shfl_up(acc.z, off, 64), w = __shfl_up(acc.w, off, 64);
         const int of = __shfl_up(f, off, 64);
         if (lane >= off) {
-            if (!f) { in.x += x; in.y += y; in.z += z; in.w += w; }
+            if (!f) { acc.x += x; acc.y += y; acc.z += z; acc.w += w; }
             f |= of;
         }
     }
-    in = make_float4(__shfl_up(in.x, LPG, 64), __shfl_up(in.y, LPG, 64), __shfl_up(in.z, LPG, 64), __shfl_up(in.w, LPG, 64));
-    if (head_at >= 0) {
+    auto write_carry = [&](const float4 &v) {
+        if (fok) *reinterpret_cast<float4 *>(a.carry + (size_t)chunk * a.f_carry + f0) = v;
+    };
+    if (open_row >= 0 && g == G - 1) {
+        if (open_row == cont_row) write_carry(acc);
+        else write_row(open_row, 1.f, acc, false);
+    }
+    const float4 in = make_float4(__shfl_up(acc.x, LPG, 64), __shfl_up(acc.y, LPG, 64), __shfl_up(acc.z, LPG, 64), __shfl_up(acc.w, LPG, 64));
+    if (head_row >= 0) {
         if (g > 0) { head.x += in.x; head.y += in.y; head.z += in.z; head.w += in.w; }
-        write_row(rows[head_at] & 0x7fffffff, kScaleRows && (use_scale || MODE == kSpmmAttnFused) ? scale[head_at] : 1.f, head);
+        if (head_row == cont_row) write_carry(head);
+        else write_row(head_row, head_sc, head, true);
     }
 }
 
@@ -1131,30 +1222,39 @@ hipError_t spmm_rows_pattern(const SpmmArgs &a, int lpg, dim3 grid, hipStream_t 
     return hipGetLastError();
 }
 
-template <int MODE, int LPG, bool OFF32>
+template <int MODE, int LPG, bool OFF32, bool PLAIN>
 hipError_t spmm_flat_per(const SpmmArgs &a, dim3 grid, hipStream_t s) {
     switch (a.chunk_nnz) {
-        case 64: hipLaunchKernelGGL((k_spmm_flat<MODE, 1, LPG, OFF32>), grid, dim3(kBlock), 0, s, a); break;
-        case 128: hipLaunchKernelGGL((k_spmm_flat<MODE, 2, LPG, OFF32>), grid, dim3(kBlock), 0, s, a); break;
-        case 256: hipLaunchKernelGGL((k_spmm_flat<MODE, 4, LPG, OFF32>), grid, dim3(kBlock), 0, s, a); break;
-        case 512: hipLaunchKernelGGL((k_spmm_flat<MODE, 8, LPG, OFF32>), grid, dim3(kBlock), 0, s, a); break;
+        case 64: hipLaunchKernelGGL((k_spmm_flat<MODE, 1, LPG, OFF32, PLAIN>), grid, dim3(kBlock), 0, s, a); break;
+        case 128: hipLaunchKernelGGL((k_spmm_flat<MODE, 2, LPG, OFF32, PLAIN>), grid, dim3(kBlock), 0, s, a); break;
+        case 256: hipLaunchKernelGGL((k_spmm_flat<MODE, 4, LPG, OFF32, PLAIN>), grid, dim3(kBlock), 0, s, a); break;
+        case 512: hipLaunchKernelGGL((k_spmm_flat<MODE, 8, LPG, OFF32, PLAIN>), grid, dim3(kBlock), 0, s, a); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
 // operands with 16-byte loads: 32-column tiles, or wider ones on a row-major operand (spmm_shape)
-template <int LPG, bool OFF32>
+template <int LPG, bool OFF32, bool PLAIN>
 hipError_t spmm_flat_mode(const SpmmArgs &a, int mode, dim3 grid, hipStream_t s) {
     switch (mode) {
-        case SENSEI_SPMM_PATTERN: return spmm_flat_per<SENSEI_SPMM_PATTERN, LPG, OFF32>(a, grid, s);
-        case SENSEI_SPMM_WEIGHTED: return spmm_flat_per<SENSEI_SPMM_WEIGHTED, LPG, OFF32>(a, grid, s);
-        case SENSEI_SPMM_SCALED: return spmm_flat_per<SENSEI_SPMM_SCALED, LPG, OFF32>(a, grid, s);
-        case kSpmmSoftmax: return spmm_flat_per<kSpmmSoftmax, LPG, OFF32>(a, grid, s);
-        case kSpmmAttnFused: return spmm_flat_per<kSpmmAttnFused, LPG, OFF32>(a, grid, s);
+        case SENSEI_SPMM_PATTERN: return spmm_flat_per<SENSEI_SPMM_PATTERN, LPG, OFF32, PLAIN>(a, grid, s);
+        case SENSEI_SPMM_WEIGHTED: return spmm_flat_per<SENSEI_SPMM_WEIGHTED, LPG, OFF32, PLAIN>(a, grid, s);
+        case SENSEI_SPMM_SCALED: return spmm_flat_per<SENSEI_SPMM_SCALED, LPG, OFF32, PLAIN>(a, grid, s);
+        case kSpmmSoftmax: return spmm_flat_per<kSpmmSoftmax, LPG, OFF32, PLAIN>(a, grid, s);
+        case kSpmmAttnFused: return spmm_flat_per<kSpmmAttnFused, LPG, OFF32, PLAIN>(a, grid, s);
         default: break;
     }
     return hipErrorInvalidValue;
+}
+template <bool PLAIN>
+hipError_t spmm_flat_dispatch(const SpmmArgs &a, int mode, int lpg, bool off32, dim3 grid, hipStream_t s) {
+    switch (lpg) {
+        case 8: return off32 ? spmm_flat_mode<8, true, PLAIN>(a, mode, grid, s) : spmm_flat_mode<8, false, PLAIN>(a, mode, grid, s);
+        case 16: return spmm_flat_mode<16, false, PLAIN>(a, mode, grid, s);
+        case 32: return spmm_flat_mode<32, false, PLAIN>(a, mode, grid, s);
+        default: return spmm_flat_mode<64, false, PLAIN>(a, mode, grid, s);
+    }
 }
 
 template <int VEC>
@@ -1453,54 +1553,29 @@ __device__ __forceinline__ void softmax_stats_chunk(const SoftmaxArgs &a, int ch
         }
     }
     to_blocked<PER>(val, lane, es, e);
-    // head, whole rows and tail of this lane as in flat_sum, with (max, sum of exp) pairs: the maximum over the part of a row that
-    // lies in this lane first (forwards, then handed back), then one exp per entry
     const int n_mine = c.hi - c.lo - lane * PER;   // entries of this lane inside the chunk (may be more than PER, or negative)
-    float mx[PER];   // never below the lowest finite value: entries of -inf (masked out) then weigh exp(-inf) = 0, also where the lane holds no others
+    float mx[PER], p[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) if (q >= n_mine) e[q] = -INFINITY;
+    flat_piece_max<PER>(c, lane, e, mx);
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-        if (q >= n_mine) e[q] = -INFINITY;
-        mx[q] = fmaxf((q > 0 && !((c.starts >> q) & 1u)) ? mx[q > 0 ? q - 1 : 0] : -FLT_MAX, e[q]);
+        mx[q] = fmaxf(mx[q], -FLT_MAX);   // entries of -inf (masked out) weigh exp(-inf) = 0 also where a piece holds no others
+        p[q] = q < n_mine ? __expf(e[q] - mx[q]) : 0.f;
     }
-#pragma unroll
-    for (int q = PER - 2; q >= 0; --q)
-        if (!((c.starts >> (q + 1)) & 1u)) mx[q] = mx[q + 1];
     auto write = [&](int i, float m, float z) {
         if (z == 0.f) m = -INFINITY;
         if (c.cont && i == c.i_first) a.carry[chunk] = make_float2(m, z);
         else a.stats[i] = make_float2(m, z);
     };
-    float hm = -INFINITY, hz = 0.f, rz = 0.f;
-    bool started = false;
+    // every entry of a piece has its maximum: it is taken from the last one, this lane's or the lane's before
+    const float m_before = lane_before(mx[PER - 1], 0.f);
+    flat_sum<PER>(c, lane, p, [&](int i, float z, int end) {
+        float m = m_before;
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        if ((c.starts >> q) & 1u) {
-            const float pm = q > 0 ? mx[q > 0 ? q - 1 : 0] : -INFINITY;
-            if (started) write(c.rid[q > 0 ? q - 1 : 0], pm, rz);
-            else { hm = pm; hz = rz; }
-            started = true;
-            rz = 0.f;
-        }
-        if (q < n_mine) rz += __expf(e[q] - mx[q]);
-    }
-    float m = mx[PER - 1], z = rz;
-    int f = started;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const float m2 = __shfl_up(m, off, 64), z2 = __shfl_up(z, off, 64);
-        const int of = __shfl_up(f, off, 64);
-        if (lane >= off) {
-            if (!f) mz_merge(m, z, m2, z2);
-            f |= of;
-        }
-    }
-    const float bm = __shfl_up(m, 1, 64), bz = __shfl_up(z, 1, 64);
-    const int head_row = (c.starts & 1u) ? c.prev_row : c.rid[0];
-    if (started && head_row >= 0 && lane > 0) {
-        mz_merge(hm, hz, bm, bz);
-        write(head_row, hm, hz);
-    }
-    if (lane == 63) write(c.rid[PER - 1], m, z);
+        for (int q = 0; q < PER; ++q) m = end >= lane * PER + q ? mx[q] : m;
+        write(i, m, z);
+    });
 }
 
 template <bool FROM_E, int PER>
@@ -1916,13 +1991,6 @@ __global__ __launch_bounds__(kBlock) void k_row_sum(NnzArgs a, const float *__re
         if (c.cont && i == c.i_first) carry[chunk] = t;
         else out[i] = t;
     });
-}
-
-// value of x in another lane by a data-parallel-primitive move (no LDS traffic): quad permutations and the mirror of a
-// half row of eight lanes; every lane is active where this is used
-template <int CTRL>
-__device__ __forceinline__ float dpp_f32(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
 }
 
 // ---- per-entry reductions over one 32-column slice (the general g-SDDMM of Eq. 2: a vector per stored entry)
@@ -2429,8 +2497,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_head_cols(GatHeadArgs a) {
     const int n = c.hi - c.lo;
     if (c.cont) cont_row = c.i_first;
     {   // the last entry of every row piece is flagged (sign bit of its row for now)
-        const int next_start = __shfl_down((int)(c.starts & 1u), 1, 64);
-        unsigned ends = (c.starts >> 1) | ((lane < 63 ? (unsigned)next_start : 0u) << (PER - 1));
+        unsigned ends = (c.starts >> 1) | ((unsigned)lane_behind((int)(c.starts & 1u), 0) << (PER - 1));
         const int e_last = n - 1 - lane * PER;
         if (e_last >= 0 && e_last < PER) ends |= 1u << e_last;
 #pragma unroll
@@ -2626,8 +2693,7 @@ __global__ __launch_bounds__(kBlock) void k_v2_walk(V2WalkArgs a) {
     const int n = c.hi - c.lo;
     if (c.cont) cont_row = c.i_first;
     {   // the last entry of every row piece is flagged (sign bit of its column)
-        const int next_start = __shfl_down((int)(c.starts & 1u), 1, 64);
-        unsigned ends = (c.starts >> 1) | ((lane < 63 ? (unsigned)next_start : 0u) << (PER - 1));
+        unsigned ends = (c.starts >> 1) | ((unsigned)lane_behind((int)(c.starts & 1u), 0) << (PER - 1));
         const int e_last = n - 1 - lane * PER;
         if (e_last >= 0 && e_last < PER) ends |= 1u << e_last;
 #pragma unroll
@@ -3011,9 +3077,9 @@ hipError_t launch_spmm(const sensei_csr &A, int mode, const float *r, const floa
     hipEvent_t t0 = timer ? timer->next() : nullptr, t1 = t0 ? timer->next() : nullptr;
     if (t1 && hipEventRecord(t0, s) != hipSuccess) return hipErrorUnknown;
     if (by_rows) err = off32 ? spmm_rows_pattern<true>(a, sh.lpg, grid, s) : spmm_rows_pattern<false>(a, sh.lpg, grid, s);
-    else if (flat && sh.lpg == 8) err = off32 ? spmm_flat_mode<8, true>(a, mode, grid, s) : spmm_flat_mode<8, false>(a, mode, grid, s);
-    else if (flat) err = sh.lpg == 16 ? spmm_flat_mode<16, false>(a, mode, grid, s) : sh.lpg == 32 ? spmm_flat_mode<32, false>(a, mode, grid, s)
-                                                                                         : spmm_flat_mode<64, false>(a, mode, grid, s);
+    // plain: whole 16-byte pieces of a row, written and not added to.  Without the code for the others in its loop the kernel is 1 to 3 % faster.
+    else if (flat) err = a.store_vec_ok && f_store % 4 == 0 && !accumulate ? spmm_flat_dispatch<true>(a, mode, sh.lpg, off32, grid, s)
+                                                                           : spmm_flat_dispatch<false>(a, mode, sh.lpg, off32, grid, s);
     else switch (sh.vec) {
         case 2: err = spmm_dispatch_lpg<2>(a, mode, sh.lpg, off32, grid, s); break;
         default: err = spmm_dispatch_lpg<1>(a, mode, sh.lpg, off32, grid, s); break;
