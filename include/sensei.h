@@ -224,7 +224,8 @@ int sensei_degrees(sensei_ctx *ctx, const sensei_csr *A, int32_t *deg_row, int32
 int sensei_norm_vectors(sensei_ctx *ctx, const int32_t *deg, int64_t n, float *out, void *stream);
 
 /* Stored entries per chunk (= per 64-lane wavefront) that every sparse kernel uses on a pattern of `nnz` entries: 64, 128, 256
- * or 512, growing with nnz (small graphs are latency bound and get more, shorter wavefronts).  Host arithmetic; 0 if nnz < 0. */
+ * or 512, growing with nnz (small graphs are latency bound and get more, shorter wavefronts).  Host arithmetic; 0 if nnz < 0.
+ * (The two backward walks of attention heads of at most 32 columns have shorter ones, at most 256.) */
 int sensei_chunk_nnz(int64_t nnz);
 
 /* Which matrix-core kernel sensei_gemm (and the GEMM inside the layers) takes for an n x k by k x m product: the fp32 instruction,

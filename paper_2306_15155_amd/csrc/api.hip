@@ -125,9 +125,9 @@ size_t sparse_ws(const sensei_csr &A, int f) {
     return plan_bytes(A.nnz) + spmm_carry_bytes(A.nnz, f) + softmax_ws_bytes(A) + spmm_copy_bytes(A, f) + 256;
 }
 
-ChunkPlan make_plan(const sensei_csr &A, Carver &cv) {
+ChunkPlan make_plan(const sensei_csr &A, Carver &cv, int chunk_nnz = 0) {
     ChunkPlan p;
-    p.chunk_nnz = choose_chunk_nnz(A.nnz);
+    p.chunk_nnz = chunk_nnz ? chunk_nnz : choose_chunk_nnz(A.nnz);
     p.n_chunks = A.nnz <= 0 ? 1 : (int)((A.nnz + p.chunk_nnz - 1) / p.chunk_nnz);
     p.chunk_row = cv.take<int32_t>((size_t)p.n_chunks + 1);
     return p;
@@ -1264,9 +1264,9 @@ bool heads_narrow(const sensei_csr &A, const sensei_csr &At, int d) { return d <
 
 size_t narrow_bwd_ws(const sensei_csr &A, int f_in, int n_heads) {
     const size_t h = n_heads < kHeadsPerLaunch ? n_heads : kHeadsPerLaunch;
-    const int t = choose_chunk_nnz(A.nnz);
+    const int t = choose_head_chunk_nnz(A.nnz);
     const size_t n_chunks = A.nnz <= 0 ? 1 : (size_t)((A.nnz + t - 1) / t);
-    size_t b = 2 * plan_bytes(A.nnz) + 512;
+    size_t b = 2 * align_up((n_chunks + 1) * sizeof(int32_t), 256) + 512;
     b += 4 * align_up(h * A.n_cols * sizeof(float), 256);                                            // s_l, s_r, ds_l, ds_r
     b += align_up(h * A.n_cols * 32 * sizeof(float), 256) + align_up(h * A.n_rows * 32 * sizeof(float), 256);   // Theta, dP
     b += align_up(h * ((size_t)A.n_rows + 1) * sizeof(float4), 256);                                 // rows
@@ -1281,7 +1281,8 @@ int run_narrow_backward(const sensei_csr &A, const sensei_csr &At, const sensei_
                         float *Wt, int64_t ldwt, Carver cv, hipStream_t s) {
     const int f_in = (int)X.cols, d = (int)W.cols / n_heads, most = n_heads < kHeadsPerLaunch ? n_heads : kHeadsPerLaunch;
     const size_t nc = A.n_cols, nr = A.n_rows;
-    ChunkPlan plan = make_plan(A, cv), plan_t = make_plan(At, cv);
+    const int t = choose_head_chunk_nnz(A.nnz);
+    ChunkPlan plan = make_plan(A, cv, t), plan_t = make_plan(At, cv, t);
     SideWork side;
     side.add_plan(A, plan);
     side.add_plan(At, plan_t);

@@ -73,6 +73,7 @@ __device__ __forceinline__ void side_block(const SideWork &w, int block) {
 #endif
 
 int choose_chunk_nnz(int64_t nnz);
+int choose_head_chunk_nnz(int64_t nnz);   // of launch_gat_heads_backward
 size_t plan_bytes(int64_t nnz);  // upper bound over all chunk sizes
 hipError_t launch_chunk_rows(const sensei_csr &A, const ChunkPlan &p, hipStream_t s);
 hipError_t launch_side(SideWork *side, hipStream_t s);   // nothing if it is empty

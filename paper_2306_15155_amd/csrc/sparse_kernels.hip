@@ -330,22 +330,17 @@ __device__ __forceinline__ void flat_piece_max(const FlatChunk<PER> &c, int lane
 // A value per row for entries in striped order.  Chunks of at most 64 rows keep the values of their rows in the lanes' registers and hand
 // them out by cross-lane reads; the others gather them (a gather costs the vector cache path what the entry's own gather costs:
 // statistics pass on 98,000 rows of 1,021 entries 0.73 ms with it, 0.48 without).
-struct RowVals {
-    bool in_lanes;
-    int i_first;
-    float x;
-    const float *src;
-};
 template <int PER>
-__device__ __forceinline__ RowVals row_vals(const FlatChunk<PER> &c, int lane, const float *__restrict__ src) {
-    RowVals v;
-    v.in_lanes = c.i1 - c.i_first <= 64;
-    v.i_first = c.i_first;
-    v.src = src;
-    v.x = (v.in_lanes && c.i_first + lane < c.i1) ? src[c.i_first + lane] : 0.f;
-    return v;
+__device__ __forceinline__ void row_values(const FlatChunk<PER> &c, int lane, const float *__restrict__ src, const int (&row)[PER], float (&x)[PER]) {
+    if (c.i1 - c.i_first <= 64) {
+        const float mine = c.i_first + lane < c.i1 ? src[c.i_first + lane] : 0.f;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) x[u] = lane_read((row[u] - c.i_first) * 4, mine);
+    } else {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) x[u] = src[row[u]];
+    }
 }
-__device__ __forceinline__ float row_val(const RowVals &v, int row) { return v.in_lanes ? lane_read((row - v.i_first) * 4, v.x) : v.src[row]; }
 
 // values from striped to blocked order (val[] of the wavefront)
 template <int PER>
@@ -898,14 +893,16 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
                 if (use_scale) es[u] *= inv_z(p.y);
             }
         } else if (MODE != kSpmmAttnFused) {
-            const RowVals rv = row_vals<PER>(c, lane, a.r);
+            float x[PER];
+            row_values<PER>(c, lane, a.r, rw, x);
 #pragma unroll
-            for (int u = 0; u < PER; ++u) es[u] *= row_val(rv, rw[u]);
+            for (int u = 0; u < PER; ++u) es[u] *= x[u];
         } else {
-            const RowVals rv = row_vals<PER>(c, lane, a.s_l + tile * a.head_vec);
+            float x[PER];
+            row_values<PER>(c, lane, a.s_l + tile * a.head_vec, rw, x);
 #pragma unroll
             for (int u = 0; u < PER; ++u) {
-                const float t = row_val(rv, rw[u]) + es[u];
+                const float t = x[u] + es[u];
                 es[u] = t > 0.f ? t : a.slope * t;
             }
         }
@@ -1400,9 +1397,10 @@ __device__ __forceinline__ void flat_edge_op(const NnzArgs &a, const float *__re
     for (int u = 0; u < PER; ++u) y[u] = col_vec[a.col_idx[span.at(u, lane)]];
     const FlatChunk<PER> c = flat_rows<PER>(a, chunk, lane, rows, [](int, bool) {});
     if (c.lo >= c.hi) return;
-    const RowVals rv = row_vals<PER>(c, lane, row_vec);
+    int rw[PER];
 #pragma unroll
-    for (int u = 0; u < PER; ++u) x[u] = row_val(rv, rows[u * 64 + lane]);
+    for (int u = 0; u < PER; ++u) rw[u] = rows[u * 64 + lane];
+    row_values<PER>(c, lane, row_vec, rw, x);
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
         const int k = c.lo + u * 64 + lane;
@@ -1543,9 +1541,10 @@ __device__ __forceinline__ void softmax_stats_chunk(const SoftmaxArgs &a, int ch
     const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [&](int r0, bool none) { if (none) a.stats[r0 + lane] = make_float2(-INFINITY, 0.f); });
     if (c.lo >= c.hi) return;
     if (!FROM_E) {
-        const RowVals sl = row_vals<PER>(c, lane, a.s_l);
+        int rw[PER];
 #pragma unroll
-        for (int u = 0; u < PER; ++u) es[u] = row_val(sl, rows[u * 64 + lane]);
+        for (int u = 0; u < PER; ++u) rw[u] = rows[u * 64 + lane];
+        row_values<PER>(c, lane, a.s_l, rw, es);
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
             es[u] = leaky(es[u] + sr[u], a.slope);
@@ -1993,67 +1992,157 @@ __global__ __launch_bounds__(kBlock) void k_row_sum(NnzArgs a, const float *__re
     });
 }
 
-// ---- per-entry reductions over one 32-column slice (the general g-SDDMM of Eq. 2: a vector per stored entry)
+// ---- per-entry sums over 32-column slices of a vector of the entry's row and one of its column (the general g-SDDMM of Eq. 2)
 //
-// total(k) = sum over the slice's 32 columns of inner(left[i, col], right[j, col]) for the entries k = (i, j) of a chunk, both matrices
-// slice-major and already offset by this lane's first column (4 * (lane % 4)).  Four lanes take one entry: lane `sub` of the four reads
-// columns 4 sub .. 4 sub + 3 and 16 + 4 sub .. 16 + 4 sub + 3, so each of the two loads of a step covers 64 contiguous bytes of 16
-// neighbours' lines; four steps make a batch of 64 entries.  The four partial sums a lane holds after a batch (one per step) are reduced
-// across the four lanes and scattered at the same time (two exchanges: keep the half this lane will own, hand the other half to the
-// partner), after which lane (g = lane / 4, sub) owns entry 64 b + 16 sub + g of the chunk: what is read or written per entry is one
-// coalesced 256-byte access.  The walk is flat: an entry's row comes from LDS and the row of `left` is gathered like that of `right`
-// (neighbouring entries share it, so it hits the vector cache), except in batches that lie in one row, where it stays in registers -
-// on long rows the gathers, which bound the kernel, are then those of `right` alone.  before(k) is called with the owned entry
-// while the gathers are in flight and its result is handed to own(k_local, k, total, got).
-template <int PER, class LoadLeft, class Inner, class Before, class Own>
-__device__ __forceinline__ void flat_dots(const FlatChunk<PER> &c, const int *rows, int lane, const int32_t *__restrict__ col_idx, const float *right,
-                                          LoadLeft load_left, Inner inner, Before before, Own own) {
-    const int g = lane >> 2, sub = lane & 3;
+// Four lanes take one entry: lane `sub` of the four reads columns 4 sub .. 4 sub + 3 and 16 + 4 sub .. 16 + 4 sub + 3 of a slice, so each of the two
+// loads of an entry covers 64 contiguous bytes.  A group of four lanes owns a sixteenth of the chunk, consecutive entries (those of its own lanes in
+// blocked order), and keeps the vectors of the row it is in in registers, those of the row after it already under way: what is
+// gathered per entry is the column's vector alone.  Before, consecutive entries went to neighbouring groups and the row's vector was gathered like the
+// column's; it hit the vector cache, but the path from there, 64 bytes a clock and compute unit, is what bounds these kernels once the
+// slice sits in the L2s: scores of 3 M entries x 64 columns
+// 63 -> 48 us, dot products with the row sums behind them 64 -> 54 (both slices in one launch now).
+// LDS words of a chunk lie in flat_at<PER, 4, 16> order (four words free after each group's part).
+struct Lane8 { float4 lo, hi; };   // a lane's eight columns of a slice
+__device__ __forceinline__ Lane8 load8(const float *slice, int row) {   // slice: offset by 4 sub columns
+    const float *p = reinterpret_cast<const float *>(reinterpret_cast<const char *>(slice) + ((size_t)(unsigned)row << 7));
+    return {*reinterpret_cast<const float4 *>(p), *reinterpret_cast<const float4 *>(p + 16)};
+}
+__device__ __forceinline__ float dot8(const Lane8 &a, const Lane8 &b) {
+    return fmaf(b.lo.x, a.lo.x, fmaf(b.lo.y, a.lo.y, fmaf(b.lo.z, a.lo.z, fmaf(b.lo.w, a.lo.w, fmaf(b.hi.x, a.hi.x, fmaf(b.hi.y, a.hi.y, fmaf(b.hi.z, a.hi.z, b.hi.w * a.hi.w)))))));
+}
+template <int PER> constexpr int kPairWords = 64 * PER + 64;
+template <int PER> __device__ __forceinline__ int pair_at(int p) { return flat_at<PER, 4, 16>(p); }
+
+// words[pair_at(p)] = the row of entry p, sign bit: it is the first of its row in the chunk
+template <int PER>
+__device__ __forceinline__ void pair_words(const FlatChunk<PER> &c, int lane, int *words) {
+#pragma unroll
+    for (int e = 0; e < PER; ++e) words[pair_at<PER>(lane * PER + e)] = (int)((unsigned)c.rid[e] | (((c.starts >> e) & 1u) << 31));
+}
+
+// total(at, sums) once per entry of the chunk, by the one of its four lanes that owns it (at: its place in LDS): N sums over the slice's 32 columns, of
+// what inner(own, column's vector, parts) leaves in each lane.  load_own(row, own) fetches the OWN vectors of a row.
+template <int PER, int OWN, int N, class LoadOwn, class Inner, class Total>
+__device__ __forceinline__ void pair_dots(const FlatChunk<PER> &c, const int *cols, const int *words, int lane, const float *other, LoadOwn load_own, Inner inner, Total total) {
+    constexpr int PART = 4 * PER;
+    const int sub = lane & 3, part0 = (lane >> 2) * (PART + 4);
     const bool up = (sub & 2) != 0, odd = (sub & 1) != 0;
-    int cur = -1;
-    float4 p, q;
-    p = q = make_float4(0.f, 0.f, 0.f, 0.f);
-    int col = col_idx[c.lo + lane < c.hi ? c.lo + lane : c.lo];
+    Lane8 own[OWN];
 #pragma unroll 1
-    for (int b = 0; b < PER && c.lo + b * 64 < c.hi; ++b) {
-        float4 r0[4], r1[4];
+    for (int s = 0; s < PART; s += 4) {
+        const int4 c4 = *reinterpret_cast<const int4 *>(&cols[part0 + s]), w4 = *reinterpret_cast<const int4 *>(&words[part0 + s]);
+        const int col[4] = {c4.x, c4.y, c4.z, c4.w};
+        const int word[4] = {s > 0 ? w4.x : (int)((unsigned)w4.x | 0x80000000u), w4.y, w4.z, w4.w};   // a part begins with a row to load
+        Lane8 b[4], fresh[4][OWN];   // fresh: read where the row changes, and nowhere else written
+        float d[N][4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float *src = right + (size_t)lane_read((u * 16 + g) * 4, col) * 32;
-            r0[u] = *reinterpret_cast<const float4 *>(src);
-            r1[u] = *reinterpret_cast<const float4 *>(src + 16);
-        }
-        const int own_local = b * 64 + sub * 16 + g, k_own = c.lo + own_local;
-        const auto got = before(k_own < c.hi ? k_own : c.lo, rows[own_local]);
-        {   // columns of the next batch
-            const int kn = c.lo + (b + 1) * 64 + lane;
-            col = col_idx[kn < c.hi ? kn : c.lo];
-        }
-        float d[4];
-        const int first = __builtin_amdgcn_readfirstlane(rows[b * 64]), last = __builtin_amdgcn_readfirstlane(rows[b * 64 + 63]);
-        if (first == last) {
-            if (first != cur) {
-                load_left(first, p, q);
-                cur = first;
+        for (int q = 0; q < 4; ++q) if (word[q] < 0) load_own(word[q] & 0x7fffffff, fresh[q]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) b[q] = load8(other, col[q]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (word[q] < 0) {
+#pragma unroll
+                for (int o = 0; o < OWN; ++o) own[o] = fresh[q][o];
             }
+            float parts[N];
+            inner(own, b[q], parts);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) d[u] = inner(p, q, r0[u], r1[u]);
-        } else {
-            float4 lp[4], lq[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) load_left(rows[b * 64 + u * 16 + g], lp[u], lq[u]);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) d[u] = inner(lp[u], lq[u], r0[u], r1[u]);
+            for (int n = 0; n < N; ++n) d[n][q] = parts[n];
         }
-        // lanes 2, 3 of the four will own steps 2, 3: they keep d[2], d[3] and receive the partner's, and hand over d[0], d[1]
-        const float keep_a = up ? d[2] : d[0], keep_b = up ? d[3] : d[1];
-        const float send_a = up ? d[0] : d[2], send_b = up ? d[1] : d[3];
-        const float a2 = keep_a + dpp_f32<0x4E>(send_a);   // from lane ^ 2
-        const float b2 = keep_b + dpp_f32<0x4E>(send_b);
-        const float keep = odd ? b2 : a2, send = odd ? a2 : b2;
-        const float total = keep + dpp_f32<0xB1>(send);    // from lane ^ 1: the sum over the four lanes for step `sub`
-        if (k_own < c.hi) own(own_local, k_own, total, got);
+        // lanes 2, 3 of the four will own entries 2, 3: they keep d[2], d[3] and receive the partner's, and hand over d[0], d[1]
+        float sums[N];
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+            const float keep_a = up ? d[n][2] : d[n][0], keep_b = up ? d[n][3] : d[n][1];
+            const float send_a = up ? d[n][0] : d[n][2], send_b = up ? d[n][1] : d[n][3];
+            const float a2 = keep_a + dpp_f32<0x4E>(send_a);   // from lane ^ 2
+            const float b2 = keep_b + dpp_f32<0x4E>(send_b);
+            const float keep = odd ? b2 : a2, send = odd ? a2 : b2;
+            sums[n] = keep + dpp_f32<0xB1>(send);              // from lane ^ 1: the sum over the four lanes for entry s + sub
+        }
+        total(part0 + s + sub, sums);
     }
+}
+
+// Sums over the rows of the chunk of what add(weights, q, own, column's vector, acc) adds per entry to NA accumulators a lane: a group of four lanes walks its
+// part as in pair_dots and closes a row (close(row, extra, acc)) where the next one starts; the first row a group closes waits for what the
+// groups before it are left with (a scan over the groups), as does its last one where it ends with the part.  weights(at) fetches what two entries weigh from
+// LDS, load_own(row, own, extra) a row's vector and one more number.  Two entries at a time: with four the registers leave three wavefronts a SIMD
+// (a training pass of four heads on 2.1 M entries 614 us, with two 589; this walk 155 us with eight lanes an entry and the own row gathered per entry, now 124).
+template <int PER, int NA, class Weights, class LoadOwn, class Add, class Close>
+__device__ __forceinline__ void pair_sums(const int *cols, const int *words, int lane, const float *other, Weights weights, LoadOwn load_own, Add add, Close close) {
+    constexpr int PART = 4 * PER, U = 2;
+    const int g = lane >> 2, part0 = g * (PART + 4);
+    float acc[NA], head[NA], extra = 0.f, head_extra = 0.f;
+    int row = 0, head_row = -1;
+    Lane8 own;
+#pragma unroll
+    for (int n = 0; n < NA; ++n) acc[n] = head[n] = 0.f;
+    auto finish = [&] {
+        if (head_row < 0) {
+#pragma unroll
+            for (int n = 0; n < NA; ++n) head[n] = acc[n];
+            head_extra = extra;
+            head_row = row;
+        } else {
+            close(row, extra, acc);
+        }
+#pragma unroll
+        for (int n = 0; n < NA; ++n) acc[n] = 0.f;
+    };
+#pragma unroll 1
+    for (int s = 0; s < PART; s += U) {
+        int col[U], word[U];
+        const auto w = weights(part0 + s);
+        const int2 c2 = *reinterpret_cast<const int2 *>(&cols[part0 + s]), w2 = *reinterpret_cast<const int2 *>(&words[part0 + s]);
+        col[0] = c2.x; col[1] = c2.y;
+        word[0] = w2.x; word[1] = w2.y;
+        if (s == 0) word[0] = (int)((unsigned)word[0] | 0x80000000u);   // a part begins with a row to load
+        Lane8 fresh[U], b[U];   // fresh: read where the row changes, and nowhere else written
+        float fresh_extra[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) if (word[q] < 0) load_own(word[q] & 0x7fffffff, fresh[q], fresh_extra[q]);
+#pragma unroll
+        for (int q = 0; q < U; ++q) b[q] = load8(other, col[q]);
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            if (word[q] < 0) {
+                if (q > 0 || s > 0) finish();
+                own = fresh[q];
+                extra = fresh_extra[q];
+                row = word[q] & 0x7fffffff;
+            }
+            add(w, q, own, b[q], acc);
+        }
+    }
+    if (g == 15 || words[part0 + PART + 4] < 0) finish();
+    int f = head_row >= 0;
+    auto step = [&](float (&x)[NA], int of) {
+#pragma unroll
+        for (int n = 0; n < NA; ++n) acc[n] += f ? 0.f : x[n];
+        f |= of;
+    };
+    float x[NA];
+#pragma unroll
+    for (int n = 0; n < NA; ++n) x[n] = dpp_f32<0x114>(acc[n]);
+    step(x, dpp_i32<0x114>(f));
+#pragma unroll
+    for (int n = 0; n < NA; ++n) x[n] = dpp_f32<0x118>(acc[n]);
+    step(x, dpp_i32<0x118>(f));
+    // the last group of the first and third sixteen lanes to the second and fourth, then that of the second to both behind it
+#pragma unroll
+    for (int half = 16; half < 64; half <<= 1) {
+        const int from = ((half == 16 ? (lane & 48) - 4 : 28) + (lane & 3)) * 4;
+        const bool takes = (lane & half) != 0;
+#pragma unroll
+        for (int n = 0; n < NA; ++n) { const float y = lane_read(from, acc[n]); x[n] = takes ? y : 0.f; }
+        const int of = lane_read(from, f);
+        step(x, takes ? of : 0);
+    }
+#pragma unroll
+    for (int n = 0; n < NA; ++n) { const float y = __shfl_up(acc[n], 4, 64); if (g > 0) head[n] += y; }
+    if (head_row >= 0) close(head_row, head_extra, head);
 }
 
 struct GatBwdArgs {
@@ -2070,57 +2159,68 @@ struct GatBwdArgs {
 };
 
 // dalpha_ij = <dP[i,:], Theta[j,:]> for every stored entry (Eq. 2 with a dot product as the inner operator) together
-// with the row sums sum_j alpha_ij dalpha_ij that the softmax backward needs.  One launch per 32-column slice: every
-// wavefront of the GPU then gathers from the same contiguous slice of Theta (as the SpMM keeps one slice per L2), and
-// the lane that owns an entry adds the slice's share to dalpha[k] - launches follow each other on the stream, so no
-// atomics.  The last launch sees the complete dot products and forms the row sums.
+// with the row sums sum_j alpha_ij dalpha_ij that the softmax backward needs.  A launch takes the 32-column slices t0 .. t1 - 1 (launch_gat_dalpha:
+// one, so that every wavefront of the GPU gathers from the same contiguous slice of Theta, or all of a small Theta) and adds to what the launches before
+// it left in dalpha: they follow each other on the stream, so no atomics.  The last launch sees the complete dot products and forms the row sums.
 template <bool LAST, int PER>
-__global__ __launch_bounds__(kBlock) void k_gat_dalpha(GatBwdArgs a, int tile, int first) {
-    __shared__ FlatLds<PER> lds;
-    const int chunk = wave_chunk();
+__global__ __launch_bounds__(kBlock) void k_gat_dalpha(GatBwdArgs a, int t0, int t1) {
+    __shared__ __attribute__((aligned(16))) int s_col[kWavesPerBlock][kPairWords<PER>], s_word[kWavesPerBlock][kPairWords<PER>];
+    __shared__ __attribute__((aligned(16))) float s_val[kWavesPerBlock][kPairWords<PER>];
+    const int chunk = wave_chunk(), wave = threadIdx.x >> 6;
     if (chunk >= a.n.n_chunks) return;
-    const int lane = threadIdx.x & 63;
-    const int sub = lane & 3;
-    int *rows = lds.row[threadIdx.x >> 6];
-    float *val = lds.val[threadIdx.x >> 6];
-    const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [&](int r0, bool none) { if (LAST && none) a.rowdot[r0 + lane] = 0.f; });
-    if (c.lo >= c.hi) return;
-    const float *theta = a.theta + (size_t)tile * a.theta_tile + sub * 4;
-    const float *dP = a.dP + (size_t)tile * a.dp_tile + sub * 4;
-    if (LAST) {
+    const int lane = threadIdx.x & 63, sub = lane & 3;
+    int *cols = s_col[wave], *words = s_word[wave];
+    float *val = s_val[wave];
+    float es[LAST ? PER : 1], sum[PER];
+    int col[PER];
+    if (a.n.nnz > 0) {
+        const ChunkSpan<PER> span(a.n, chunk);
 #pragma unroll
-        for (int u = 0; u < PER; ++u) val[u * 64 + lane] = 0.f;
-        lds_exchange();
+        for (int u = 0; u < PER; ++u) {
+            const int k = span.at(u, lane);
+            col[u] = a.n.col_idx[k];
+            sum[u] = t0 > 0 ? a.dalpha[k] : 0.f;
+            if (LAST) es[LAST ? u : 0] = a.logits[k];
+        }
     }
-    struct Got { float sum, e; float2 st; };
+    const FlatChunk<PER> c = flat_rows<PER, 4, 16>(a.n, chunk, lane, words, [&](int r0, bool none) { if (LAST && none) a.rowdot[r0 + lane] = 0.f; });
+    if (c.lo >= c.hi) return;
+    pair_words<PER>(c, lane, words);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        cols[pair_at<PER>(u * 64 + lane)] = col[u];
+        val[pair_at<PER>(u * 64 + lane)] = sum[u];
+    }
+    lds_exchange();
     const int panel_row = c.i_first / a.dp_rows * a.dp_rows;   // first row of the panel the chunk begins in
-    flat_dots<PER>(c, rows, lane, a.n.col_idx, theta,
-                   [&](int i, float4 &p, float4 &q) {
-                       i -= panel_row;
-                       while (i >= a.dp_rows) i -= a.dp_rows;   // only where a chunk runs over the end of its panel
-                       p = *reinterpret_cast<const float4 *>(dP + (size_t)i * 32);
-                       q = *reinterpret_cast<const float4 *>(dP + (size_t)i * 32 + 16);
-                   },
-                   [&](const float4 &p, const float4 &q, const float4 &b, const float4 &d) {
-                       const float t = fmaf(b.x, p.x, fmaf(b.y, p.y, fmaf(b.z, p.z, fmaf(b.w, p.w, fmaf(d.x, q.x, fmaf(d.y, q.y, fmaf(d.z, q.z, d.w * q.w)))))));
-                       return t * a.scale;   // exact when the factor is 1
-                   },
-                   [&](int k, int i) {
-                       Got got = {0.f, 0.f, make_float2(0.f, 0.f)};
-                       if (!first) got.sum = a.dalpha[k];
-                       if (LAST) { got.e = a.logits[k]; got.st = a.mz[i]; }
-                       return got;
-                   },
-                   [&](int local, int k, float total, const Got &got) {
-                       const float v = got.sum + total;
-                       a.dalpha[k] = v;
-                       if (LAST) val[local] = expf(got.e - got.st.x) * inv_z(got.st.y) * v;
-                   });
+    for (int tile = t0; tile < t1; ++tile) {
+        const float *dP = a.dP + (size_t)tile * a.dp_tile + sub * 4;
+        pair_dots<PER, 1, 1>(c, cols, words, lane, a.theta + (size_t)tile * a.theta_tile + sub * 4,
+                             [&](int i, Lane8 (&own)[1]) {
+                                 i -= panel_row;
+                                 while (i >= a.dp_rows) i -= a.dp_rows;   // only where a chunk runs over the end of its panel
+                                 own[0] = load8(dP, i);
+                             },
+                             [&](const Lane8 (&own)[1], const Lane8 &b, float (&parts)[1]) { parts[0] = dot8(own[0], b) * a.scale; },   // exact when the factor is 1
+                             [&](int at, const float (&sums)[1]) { val[at] += sums[0]; });
+    }
+    lds_exchange();
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int at = pair_at<PER>(u * 64 + lane), k = c.lo + u * 64 + lane;
+        if (k < c.hi) a.dalpha[k] = val[at];
+        if (LAST) cols[at] = __float_as_int(es[LAST ? u : 0]);
+    }
     if (LAST) {
         float v[PER];
         lds_exchange();
+        const int n_mine = c.hi - c.lo - lane * PER;
 #pragma unroll
-        for (int e = 0; e < PER; ++e) v[e] = val[lane * PER + e];
+        for (int e = 0; e < PER; ++e) {
+            const int at = pair_at<PER>(lane * PER + e);
+            const float2 st = a.mz[c.rid[e]];
+            v[e] = e < n_mine ? expf(__int_as_float(cols[at]) - st.x) * inv_z(st.y) * val[at] : 0.f;
+        }
         flat_sum<PER>(c, lane, v, [&](int i, float t, int) {
             if (c.cont && i == c.i_first) a.carry[chunk] = t;
             else a.rowdot[i] = t;
@@ -2187,37 +2287,56 @@ struct ScoreV2Args {
 };
 
 // Logits of the GATv2 score, e_ij = sum_m a[m] LeakyReLU(Theta_l[i, m] + Theta_r[j, m]): Eq. 2 with an inner operator
-// that is neither a product nor a sum alone.  Same walk as k_gat_dalpha, one launch per 32-column slice.
+// that is neither a product nor a sum alone.  Slices as in k_gat_dalpha.
 template <int PER>
-__global__ __launch_bounds__(kBlock) void k_score_v2(ScoreV2Args a, int tile, int first) {
-    __shared__ FlatLds<PER> lds;
-    const int chunk = wave_chunk();
+__global__ __launch_bounds__(kBlock) void k_score_v2(ScoreV2Args a, int t0, int t1) {
+    __shared__ __attribute__((aligned(16))) int s_col[kWavesPerBlock][kPairWords<PER>], s_word[kWavesPerBlock][kPairWords<PER>];
+    __shared__ __attribute__((aligned(16))) float s_val[kWavesPerBlock][kPairWords<PER>];
+    const int chunk = wave_chunk(), wave = threadIdx.x >> 6;
     if (chunk >= a.n.n_chunks) return;
-    const int lane = threadIdx.x & 63;
-    const int sub = lane & 3;
-    int *rows = lds.row[threadIdx.x >> 6];
-    const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [](int, bool) {});
+    const int lane = threadIdx.x & 63, sub = lane & 3;
+    int *cols = s_col[wave], *words = s_word[wave];
+    float *val = s_val[wave];
+    float sum[PER];
+    int col[PER];
+    const ChunkSpan<PER> span(a.n, chunk);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int k = span.at(u, lane);
+        col[u] = a.n.col_idx[k];
+        sum[u] = t0 > 0 ? a.logits[k] : 0.f;
+    }
+    const FlatChunk<PER> c = flat_rows<PER, 4, 16>(a.n, chunk, lane, words, [](int, bool) {});
     if (c.lo >= c.hi) return;
-    const float *theta_r = a.theta_r + (size_t)tile * a.tr_tile + sub * 4;
-    const float *theta_l = a.theta_l + (size_t)tile * a.tl_tile + sub * 4;
-    const float4 w = *reinterpret_cast<const float4 *>(a.att + tile * 32 + sub * 4);
-    const float4 w2 = *reinterpret_cast<const float4 *>(a.att + tile * 32 + 16 + sub * 4);
+    pair_words<PER>(c, lane, words);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        cols[pair_at<PER>(u * 64 + lane)] = col[u];
+        val[pair_at<PER>(u * 64 + lane)] = sum[u];
+    }
+    lds_exchange();
     const float slope = a.slope;
     auto term = [&](float wt, float x, float y) {
         const float t = x + y;
         return wt * (t > 0.f ? t : slope * t);
     };
-    flat_dots<PER>(c, rows, lane, a.n.col_idx, theta_r,
-                   [&](int i, float4 &p, float4 &q) {
-                       p = *reinterpret_cast<const float4 *>(theta_l + (size_t)i * 32);
-                       q = *reinterpret_cast<const float4 *>(theta_l + (size_t)i * 32 + 16);
-                   },
-                   [&](const float4 &p, const float4 &q, const float4 &b, const float4 &d) {
-                       return ((term(w.x, p.x, b.x) + term(w.y, p.y, b.y)) + (term(w.z, p.z, b.z) + term(w.w, p.w, b.w))) +
-                              ((term(w2.x, q.x, d.x) + term(w2.y, q.y, d.y)) + (term(w2.z, q.z, d.z) + term(w2.w, q.w, d.w)));
-                   },
-                   [&](int k, int) { return first ? 0.f : a.logits[k]; },
-                   [&](int, int k, float total, float sum) { a.logits[k] = sum + total; });
+    for (int tile = t0; tile < t1; ++tile) {
+        const float *theta_l = a.theta_l + (size_t)tile * a.tl_tile + sub * 4;
+        const Lane8 w = load8(a.att + tile * 32 + sub * 4, 0);
+        pair_dots<PER, 1, 1>(c, cols, words, lane, a.theta_r + (size_t)tile * a.tr_tile + sub * 4, [&](int i, Lane8 (&own)[1]) { own[0] = load8(theta_l, i); },
+                             [&](const Lane8 (&own)[1], const Lane8 &b, float (&parts)[1]) {
+                                 const Lane8 &p = own[0];
+                                 parts[0] = ((term(w.lo.x, p.lo.x, b.lo.x) + term(w.lo.y, p.lo.y, b.lo.y)) + (term(w.lo.z, p.lo.z, b.lo.z) + term(w.lo.w, p.lo.w, b.lo.w))) +
+                                            ((term(w.hi.x, p.hi.x, b.hi.x) + term(w.hi.y, p.hi.y, b.hi.y)) + (term(w.hi.z, p.hi.z, b.hi.z) + term(w.hi.w, p.hi.w, b.hi.w)));
+                             },
+                             [&](int at, const float (&sums)[1]) { val[at] += sums[0]; });
+    }
+    lds_exchange();
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int k = c.lo + u * 64 + lane;
+        if (k < c.hi) a.logits[k] = val[pair_at<PER>(u * 64 + lane)];
+    }
 }
 
 struct GatDtArgs {
@@ -2328,68 +2447,74 @@ __device__ __forceinline__ void finish_head_row(const GatHeadArgs &a, int head, 
 
 template <int PER>
 __global__ __launch_bounds__(kBlock) void k_gat_head_rows(GatHeadArgs a) {
-    __shared__ FlatLds<PER> lds;
-    __shared__ float s_max[kWavesPerBlock][64 * PER];
+    __shared__ __attribute__((aligned(16))) int s_col[kWavesPerBlock][kPairWords<PER>], s_word[kWavesPerBlock][kPairWords<PER>];
+    __shared__ __attribute__((aligned(16))) float s_val[kWavesPerBlock][kPairWords<PER>];
     const int chunk = wave_chunk(), head = blockIdx.y, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, sub = lane & 3;
     if (chunk >= a.n.n_chunks) return;
-    int *rows = lds.row[wave];
-    float *val = lds.val[wave], *top = s_max[wave];
+    int *cols = s_col[wave], *words = s_word[wave];
+    float *val = s_val[wave];
     const float *s_l = a.s_l + head * a.n_src, *s_r = a.s_r + head * a.n_src;
-    float es[PER], p[PER];
+    float es[PER], p[PER], mx[PER];
+    int col[PER];
     if (a.n.nnz > 0) {
         const ChunkSpan<PER> span(a.n, chunk);
 #pragma unroll
-        for (int u = 0; u < PER; ++u) es[u] = s_r[a.n.col_idx[span.at(u, lane)]];
+        for (int u = 0; u < PER; ++u) col[u] = a.n.col_idx[span.at(u, lane)];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) es[u] = s_r[col[u]];
     }
-    const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [&](int r0, bool none) { if (none) a.ds_l[head * a.n_src + r0 + lane] = 0.f; });
+    const FlatChunk<PER> c = flat_rows<PER, 4, 16>(a.n, chunk, lane, words, [&](int r0, bool none) { if (none) a.ds_l[head * a.n_src + r0 + lane] = 0.f; });
     if (c.lo >= c.hi) return;
     unsigned neg = 0u;   // bit q: entry q of this lane (blocked order) has a logit of 0 or below
     {
-        const RowVals sl = row_vals<PER>(c, lane, s_l);
-        float mx[PER], e[PER];
+        float e[PER];
+        int rw[PER];
 #pragma unroll
-        for (int u = 0; u < PER; ++u) es[u] = leaky(row_val(sl, rows[u * 64 + lane]) + es[u], a.slope);
-        to_blocked<PER>(val, lane, es, e);
+        for (int u = 0; u < PER; ++u) rw[u] = words[pair_at<PER>(u * 64 + lane)];
+        row_values<PER>(c, lane, s_l, rw, e);
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int at = pair_at<PER>(u * 64 + lane);
+            val[at] = leaky(e[u] + es[u], a.slope);
+            cols[at] = col[u];
+        }
+        lds_exchange();
+        pair_words<PER>(c, lane, words);
         const int n_mine = c.hi - c.lo - lane * PER;
 #pragma unroll
-        for (int q = 0; q < PER; ++q) if (q >= n_mine) e[q] = -INFINITY;
+        for (int q = 0; q < PER; ++q) e[q] = q < n_mine ? val[pair_at<PER>(lane * PER + q)] : -INFINITY;
         flat_piece_max<PER>(c, lane, e, mx);
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             mx[q] = fmaxf(mx[q], -FLT_MAX);   // entries of -inf weigh 0 also where a piece holds no others
             p[q] = q < n_mine ? expf(e[q] - mx[q]) : 0.f;
             neg |= (e[q] > 0.f ? 0u : 1u) << q;
-            top[lane * PER + q] = mx[q];
         }
     }
     lds_exchange();
-#pragma unroll
-    for (int u = 0; u < PER; ++u) val[u * 64 + lane] = 0.f;
     const float *theta = a.theta + (size_t)head * a.n_src * 32 + sub * 4, *dP = a.dP + (size_t)head * a.n_dst * 32 + sub * 4;
-    flat_dots<PER>(c, rows, lane, a.n.col_idx, theta,
-                   [&](int i, float4 &x, float4 &y) {
-                       x = *reinterpret_cast<const float4 *>(dP + (size_t)i * 32);
-                       y = *reinterpret_cast<const float4 *>(dP + (size_t)i * 32 + 16);
-                   },
-                   [&](const float4 &x, const float4 &y, const float4 &b, const float4 &d) {
-                       return fmaf(b.x, x.x, fmaf(b.y, x.y, fmaf(b.z, x.z, fmaf(b.w, x.w, fmaf(d.x, y.x, fmaf(d.y, y.y, fmaf(d.z, y.z, d.w * y.w)))))));
-                   },
-                   [](int, int) { return 0; }, [&](int local, int, float total, int) { val[local] = total; });
+    pair_dots<PER, 1, 1>(c, cols, words, lane, theta, [&](int i, Lane8 (&own)[1]) { own[0] = load8(dP, i); },
+                         [](const Lane8 (&own)[1], const Lane8 &b, float (&parts)[1]) { parts[0] = dot8(own[0], b); },
+                         [&](int at, const float (&sums)[1]) { val[at] = sums[0]; });
     lds_exchange();
     float v[4][PER];
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-        const float t = p[q] * val[lane * PER + q];
+        const float t = q < c.hi - c.lo - lane * PER ? p[q] * val[pair_at<PER>(lane * PER + q)] : 0.f;
         const bool n = (neg >> q) & 1u;
         v[0][q] = n ? 0.f : p[q];
         v[1][q] = n ? p[q] : 0.f;
         v[2][q] = n ? 0.f : t;
         v[3][q] = n ? t : 0.f;
     }
+    const float m_before = lane_before(mx[PER - 1], 0.f);   // every entry of a piece has its maximum: it is taken from the last one
     const int last_row = __builtin_amdgcn_readfirstlane(__shfl(c.rid[PER - 1], 63, 64));
     const bool open = __builtin_amdgcn_readfirstlane(a.n.row_ptr[last_row + 1]) > c.hi;
     flat_sums<PER, 4>(c, lane, v, [&](int i, const float (&sum)[4], int end) {
-        const HeadPiece piece = {top[end], sum[0], sum[1], sum[2], sum[3]};
+        float m = m_before;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) m = end >= lane * PER + q ? mx[q] : m;
+        const HeadPiece piece = {m, sum[0], sum[1], sum[2], sum[3]};
         const bool cont = c.cont && i == c.i_first;
         if (cont || (open && i == last_row)) {
             float *dst = a.piece + (((size_t)head * a.n.n_chunks + chunk) * 2 + (cont ? 0 : 1)) * 8;
@@ -2430,52 +2555,52 @@ __global__ __launch_bounds__(kBlock) void k_gat_head_fixup(GatHeadArgs a) {
                });
 }
 
-// The walk over the transposed pattern: k_spmm_flat's, with the own row's Theta gathered per entry while rows change and
-// the dot product reduced over the eight lanes of a group by DPP moves.
+// The walk over the transposed pattern (pair_sums): the dot product of the gathered row of dP with the row's own Theta_j is reduced over the four
+// lanes of a group by DPP moves.
 template <int PER>
 __global__ __launch_bounds__(kBlock) void k_gat_head_cols(GatHeadArgs a) {
-    constexpr int LPG = 8, G = 64 / LPG, T = 64 * PER, PART = T / G, PAD = 4, U = 4;
-    __shared__ __attribute__((aligned(16))) int s_col[kWavesPerBlock][T + G * PAD];
-    __shared__ __attribute__((aligned(16))) int s_row[kWavesPerBlock][T + G * PAD];
-    __shared__ __attribute__((aligned(16))) float s_alpha[kWavesPerBlock][T + G * PAD];   // negative: the logit is 0 or below
-    __shared__ __attribute__((aligned(16))) float s_dot[kWavesPerBlock][T + G * PAD];     // rowdot of the entry's destination
-    const int chunk = wave_chunk(), head = blockIdx.y, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane / LPG, li = lane % LPG;
+    __shared__ __attribute__((aligned(16))) int s_col[kWavesPerBlock][kPairWords<PER>], s_word[kWavesPerBlock][kPairWords<PER>];
+    __shared__ __attribute__((aligned(16))) float s_alpha[kWavesPerBlock][kPairWords<PER>];   // negative: the logit is 0 or below
+    __shared__ __attribute__((aligned(16))) float s_dot[kWavesPerBlock][kPairWords<PER>];     // rowdot of the entry's destination
+    __shared__ __attribute__((aligned(16))) float s_att[kWavesPerBlock][64];
+    const int chunk = wave_chunk(), head = blockIdx.y, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, sub = lane & 3;
     if (chunk >= a.n.n_chunks) return;
-    int *rows = s_row[wave], *cols = s_col[wave];
+    int *words = s_word[wave], *cols = s_col[wave];
     float *alpha = s_alpha[wave], *rdot = s_dot[wave];
-    const float *theta = a.theta + (size_t)head * a.n_src * 32 + li * 4, *dP = a.dP + (size_t)head * a.n_dst * 32 + li * 4;
-    float *out = a.dtheta + (size_t)head * a.d + li * 4, *ds_out = a.ds_r + head * a.n_src;
-    float4 al = make_float4(0.f, 0.f, 0.f, 0.f), ar = al;   // this lane's columns of the attention vectors
-    {
-        const float *pl = a.a_l + head * a.d, *pr = a.a_r + head * a.d;
-        const int q = li * 4;
-        if (q < a.d) { al.x = pl[q]; ar.x = pr[q]; }
-        if (q + 1 < a.d) { al.y = pl[q + 1]; ar.y = pr[q + 1]; }
-        if (q + 2 < a.d) { al.z = pl[q + 2]; ar.z = pr[q + 2]; }
-        if (q + 3 < a.d) { al.w = pl[q + 3]; ar.w = pr[q + 3]; }
-    }
+    const float *theta = a.theta + (size_t)head * a.n_src * 32 + sub * 4, *dP = a.dP + (size_t)head * a.n_dst * 32 + sub * 4;
+    float *out = a.dtheta + (size_t)head * a.d, *ds_out = a.ds_r + head * a.n_src;
+    float *a_l = s_att[wave], *a_r = a_l + 32;   // the head's attention vectors, zeros behind them
+    if ((lane & 31) < a.d) a_l[lane] = (lane < 32 ? a.a_l : a.a_r)[head * a.d + (lane & 31)];
+    else a_l[lane] = 0.f;
     const float *ds_l = a.ds_l + head * a.n_src;
     auto own_ds = [&](int row) { return row < a.n_dst ? ds_l[row] : 0.f; };   // sources that are no destination have none
     int cont_row = -1;
+    constexpr int NA = 9;   // eight columns of dTheta, ds_r
     // the rank-1 terms ds_l a_l + ds_r a_r: every piece of a row adds its share of ds_r, the first one ds_l
-    auto write_row = [&](int row, float4 v, float ds, float dl) {
-        v.x = fmaf(ds, ar.x, v.x); v.y = fmaf(ds, ar.y, v.y); v.z = fmaf(ds, ar.z, v.z); v.w = fmaf(ds, ar.w, v.w);
-        if (row != cont_row) { v.x = fmaf(dl, al.x, v.x); v.y = fmaf(dl, al.y, v.y); v.z = fmaf(dl, al.z, v.z); v.w = fmaf(dl, al.w, v.w); }
-        if (row == cont_row) {
-            *reinterpret_cast<float4 *>(a.carry + ((size_t)head * a.n.n_chunks + chunk) * 32 + li * 4) = v;
-            if (li == 0) a.ds_carry[(size_t)head * a.n.n_chunks + chunk] = ds;
-            return;
+    auto close = [&](int row, float dl, const float (&v)[NA]) {
+        const bool cont = row == cont_row;
+        const float ds = v[8];
+        float *dst = cont ? a.carry + ((size_t)head * a.n.n_chunks + chunk) * 32 : out + (size_t)row * a.ldd;
+        if (cont) dl = 0.f;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int q = h * 16 + sub * 4;
+            const float4 l4 = *reinterpret_cast<const float4 *>(a_l + q), r4 = *reinterpret_cast<const float4 *>(a_r + q);
+            const float l[4] = {l4.x, l4.y, l4.z, l4.w}, r[4] = {r4.x, r4.y, r4.z, r4.w};
+            float y[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) y[i] = fmaf(dl, l[i], fmaf(ds, r[i], v[h * 4 + i]));
+            if (cont || (a.store_vec_ok && q + 4 <= a.d)) {
+                *reinterpret_cast<float4 *>(dst + q) = make_float4(y[0], y[1], y[2], y[3]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) if (q + i < a.d) dst[q + i] = y[i];
+            }
         }
-        float *dst = out + (size_t)row * a.ldd;
-        if (a.store_vec_ok && li * 4 + 4 <= a.d) {
-            *reinterpret_cast<float4 *>(dst) = v;
-        } else {
-            if (li * 4 < a.d) dst[0] = v.x;
-            if (li * 4 + 1 < a.d) dst[1] = v.y;
-            if (li * 4 + 2 < a.d) dst[2] = v.z;
-            if (li * 4 + 3 < a.d) dst[3] = v.w;
+        if (sub == 0) {
+            if (cont) a.ds_carry[(size_t)head * a.n.n_chunks + chunk] = ds;
+            else ds_out[row] = ds;
         }
-        if (li == 0) ds_out[row] = ds;
     };
     int col[PER];
     float4 st[PER];
@@ -2486,104 +2611,61 @@ __global__ __launch_bounds__(kBlock) void k_gat_head_cols(GatHeadArgs a) {
 #pragma unroll
         for (int u = 0; u < PER; ++u) st[u] = a.row[head * a.n_dst + col[u]];
     }
-    const FlatChunk<PER> c = flat_rows<PER, PAD, G>(a.n, chunk, lane, rows, [&](int r0, bool none) {
+    const float none_of[NA] = {};
+    const FlatChunk<PER> c = flat_rows<PER, 4, 16>(a.n, chunk, lane, words, [&](int r0, bool none) {
         unsigned long long m = __ballot(none);
-        for (int b = 0; m; ++b, m >>= G) {   // rows without entries: one per group at a time
-            if (!((m >> g) & 1ull)) continue;
-            write_row(r0 + b * G + g, make_float4(0.f, 0.f, 0.f, 0.f), 0.f, own_ds(r0 + b * G + g));
+        for (int b = 0; m; ++b, m >>= 16) {   // rows without entries: one per group at a time
+            if (!((m >> (lane >> 2)) & 1ull)) continue;
+            const int row = r0 + b * 16 + (lane >> 2);
+            close(row, own_ds(row), none_of);
         }
     });
     if (c.lo >= c.hi) return;
-    const int n = c.hi - c.lo;
     if (c.cont) cont_row = c.i_first;
-    {   // the last entry of every row piece is flagged (sign bit of its row for now)
-        unsigned ends = (c.starts >> 1) | ((unsigned)lane_behind((int)(c.starts & 1u), 0) << (PER - 1));
-        const int e_last = n - 1 - lane * PER;
-        if (e_last >= 0 && e_last < PER) ends |= 1u << e_last;
-#pragma unroll
-        for (int e = 0; e < PER; ++e) rows[flat_at<PER, PAD, G>(lane * PER + e)] = (int)((unsigned)c.rid[e] | (((ends >> e) & 1u) << 31));
-    }
-    lds_exchange();
     {
-        const RowVals sr = row_vals<PER>(c, lane, a.s_r + head * a.n_src);
+        int rw[PER];
+        float x[PER];
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
-            const int at = flat_at<PER, PAD, G>(u * 64 + lane), rw = rows[at];
-            cols[at] = (int)((unsigned)col[u] | ((unsigned)rw & 0x80000000u));
-            const float t = st[u].x + row_val(sr, rw & 0x7fffffff);
+            const int at = pair_at<PER>(u * 64 + lane);
+            rw[u] = words[at];
+            cols[at] = col[u];
+        }
+        row_values<PER>(c, lane, a.s_r + head * a.n_src, rw, x);
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int at = pair_at<PER>(u * 64 + lane);
+            const float t = st[u].x + x[u];
             float w = expf(leaky(t, a.slope) - st[u].y) * st[u].z;
             if (c.lo + u * 64 + lane >= c.hi) w = 0.f;
             alpha[at] = t > 0.f ? w : __uint_as_float(__float_as_uint(w) | 0x80000000u);
             rdot[at] = st[u].w;
         }
+        lds_exchange();
+        pair_words<PER>(c, lane, words);
     }
     lds_exchange();
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), head_acc = acc, own = acc;
-    float ds = 0.f, head_ds = 0.f, head_dl = 0.f, own_dl = 0.f;
-    int head_at = -1, own_row = -1;
-    const int part0 = g * (PART + PAD);
-    for (int s = 0; s < PART && s < n; s += U) {
-        const int4 c4 = *reinterpret_cast<const int4 *>(&cols[part0 + s]), r4 = *reinterpret_cast<const int4 *>(&rows[part0 + s]);
-        const float4 w4 = *reinterpret_cast<const float4 *>(&alpha[part0 + s]), d4 = *reinterpret_cast<const float4 *>(&rdot[part0 + s]);
-        const int cf[U] = {c4.x, c4.y, c4.z, c4.w}, rf[U] = {r4.x, r4.y, r4.z, r4.w};
-        const float w[U] = {w4.x, w4.y, w4.z, w4.w}, rd[U] = {d4.x, d4.y, d4.z, d4.w};
-        float4 b[U], o[U];
-        float dl[U];
-#pragma unroll
-        for (int q = 0; q < U; ++q) b[q] = *reinterpret_cast<const float4 *>(dP + (size_t)(cf[q] & 0x7fffffff) * 32);
-        if (__all((rf[U - 1] & 0x7fffffff) == own_row)) {   // (rows ascend) every group stays in its row
-#pragma unroll
-            for (int q = 0; q < U; ++q) { o[q] = own; dl[q] = own_dl; }
-        } else {
-#pragma unroll
-            for (int q = 0; q < U; ++q) {
-                o[q] = *reinterpret_cast<const float4 *>(theta + (size_t)(rf[q] & 0x7fffffff) * 32);
-                dl[q] = own_ds(rf[q] & 0x7fffffff);
-            }
-            own_row = rf[U - 1] & 0x7fffffff;
-            own = o[U - 1];
-            own_dl = dl[U - 1];
-        }
-#pragma unroll
-        for (int q = 0; q < U; ++q) {
-            float x = fmaf(b[q].x, o[q].x, fmaf(b[q].y, o[q].y, fmaf(b[q].z, o[q].z, b[q].w * o[q].w)));
+    struct W { float w[2], rd[2]; };
+    pair_sums<PER, NA>(
+        cols, words, lane, dP,
+        [&](int at) {
+            const float2 w4 = *reinterpret_cast<const float2 *>(&alpha[at]), d4 = *reinterpret_cast<const float2 *>(&rdot[at]);
+            return W{{w4.x, w4.y}, {d4.x, d4.y}};
+        },
+        [&](int row, Lane8 &own, float &dl) {
+            own = load8(theta, row);
+            dl = own_ds(row);
+        },
+        [&](const W &w, int q, const Lane8 &own, const Lane8 &b, float (&acc)[NA]) {
+            float x = dot8(own, b);
             x += dpp_f32<0xB1>(x);    // lane ^ 1
             x += dpp_f32<0x4E>(x);    // lane ^ 2
-            x += dpp_f32<0x141>(x);   // the other four of the eight (mirrored)
-            const float al = fabsf(w[q]);
-            ds = fmaf(__float_as_uint(w[q]) >> 31 ? a.slope * al : al, x - rd[q], ds);
-            acc.x = fmaf(al, b[q].x, acc.x); acc.y = fmaf(al, b[q].y, acc.y); acc.z = fmaf(al, b[q].z, acc.z); acc.w = fmaf(al, b[q].w, acc.w);
-            if (cf[q] < 0) {
-                if (head_at < 0) {
-                    head_acc = acc;
-                    head_ds = ds;
-                    head_dl = dl[q];
-                    head_at = part0 + s + q;
-                } else {
-                    write_row(rf[q] & 0x7fffffff, acc, ds, dl[q]);
-                }
-                acc = make_float4(0.f, 0.f, 0.f, 0.f);
-                ds = 0.f;
-            }
-        }
-    }
-    int f = head_at >= 0;
-#pragma unroll
-    for (int off = LPG; off < 64; off <<= 1) {
-        const float x = __shfl_up(acc.x, off, 64), y = __shfl_up(acc.y, off, 64), z = __shfl_up(acc.z, off, 64), w = __shfl_up(acc.w, off, 64);
-        const float t = __shfl_up(ds, off, 64);
-        const int of = __shfl_up(f, off, 64);
-        if (lane >= off) {
-            if (!f) { acc.x += x; acc.y += y; acc.z += z; acc.w += w; ds += t; }
-            f |= of;
-        }
-    }
-    acc = make_float4(__shfl_up(acc.x, LPG, 64), __shfl_up(acc.y, LPG, 64), __shfl_up(acc.z, LPG, 64), __shfl_up(acc.w, LPG, 64));
-    ds = __shfl_up(ds, LPG, 64);
-    if (head_at >= 0) {
-        if (g > 0) { head_acc.x += acc.x; head_acc.y += acc.y; head_acc.z += acc.z; head_acc.w += acc.w; head_ds += ds; }
-        write_row(rows[head_at] & 0x7fffffff, head_acc, head_ds, head_dl);
-    }
+            const float al = fabsf(w.w[q]);
+            acc[8] = fmaf(__float_as_uint(w.w[q]) >> 31 ? a.slope * al : al, x - w.rd[q], acc[8]);
+            acc[0] = fmaf(al, b.lo.x, acc[0]); acc[1] = fmaf(al, b.lo.y, acc[1]); acc[2] = fmaf(al, b.lo.z, acc[2]); acc[3] = fmaf(al, b.lo.w, acc[3]);
+            acc[4] = fmaf(al, b.hi.x, acc[4]); acc[5] = fmaf(al, b.hi.y, acc[5]); acc[6] = fmaf(al, b.hi.z, acc[6]); acc[7] = fmaf(al, b.hi.w, acc[7]);
+        },
+        close);
 }
 
 // the rows of dTheta and ds_r that span several chunks, their pieces added one after the other in chunk order (eight loads under way): a wavefront
@@ -2737,10 +2819,11 @@ __global__ __launch_bounds__(kBlock) void k_v2_walk(V2WalkArgs a) {
         }
 #pragma unroll
         for (int q = 0; q < U; ++q) {
+            const float e_neg = a.slope * e[q];
             auto add = [&](float &s1, float &s2, float x, float y, float p) {
-                const float t = x + y, dt = t > 0.f ? 1.f : a.slope;
-                s1 = fmaf(e[q], dt, s1);
-                s2 = COLS ? fmaf(w[q], p, s2) : fmaf(e[q], dt * t, s2);
+                const float t = x + y, g = t > 0.f ? e[q] : e_neg;   // de LeakyReLU'(t)
+                s1 += g;
+                s2 = COLS ? fmaf(w[q], p, s2) : fmaf(g, t, s2);
             };
             const float4 p = d[COLS ? q : 0];
             add(acc.x, accr.x, o[q].x, b[q].x, p.x);
@@ -2938,6 +3021,18 @@ hipError_t with_per(int chunk_nnz, F f) {
     return hipGetLastError();
 }
 
+// for chunks of choose_head_chunk_nnz
+template <class F>
+hipError_t with_head_per(int chunk_nnz, F f) {
+    switch (chunk_nnz) {
+        case 64: f(std::integral_constant<int, 1>()); break;
+        case 128: f(std::integral_constant<int, 2>()); break;
+        case 256: f(std::integral_constant<int, 4>()); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 NnzArgs nnz_args(const sensei_csr &A, const ChunkPlan &p) {
     NnzArgs n;
     n.row_ptr = A.row_ptr; n.col_idx = A.col_idx; n.chunk_row = p.chunk_row;
@@ -2959,6 +3054,11 @@ int choose_chunk_nnz(int64_t nnz) {
     if (nnz >= (1LL << 17)) return 128;
     return 64;  // small graphs are latency bound: more, shorter wavefronts
 }
+
+// The two walks of the narrow heads' backward hold more per entry: chunks of 512 leave them three wavefronts a SIMD.  Training passes with chunks of 64 / 128 /
+// 256 / 512 there, us: 4 heads, 2.1 M entries 670 / 612 / 589 / 604, 2.4 M on a grid, 2 heads 1,437 / 1,413 / 1,433 / 1,463, 8 heads, 20 M 10,935 / 9,710 / 8,993 /
+// 8,986, 2 heads, 99 M 26,575 / 26,213 / 26,081 / 25,959, one head, 292,000 103 / 106 / 106 / 117, 2 heads, 170,000 146 / 139 / 144 / 157.
+int choose_head_chunk_nnz(int64_t nnz) { return choose_chunk_nnz(nnz) < 256 ? choose_chunk_nnz(nnz) : 256; }
 
 static int n_chunks_for(int64_t nnz, int t) { return nnz <= 0 ? 1 : (int)((nnz + t - 1) / t); }
 
@@ -3241,6 +3341,14 @@ hipError_t launch_row_sum(const sensei_csr &A, const float *val, int stride, flo
     });
 }
 
+// 32-column slices of the gathered matrix that one launch of the per-entry sums takes: all of a small matrix, which saves finding the rows again and the sums
+// written and read in between (3 M entries on 50,000 columns, 64 wide, 54 us in one launch of two slices, 61 in two), one of a larger one, so that what the L2s hold
+// is one slice (a gathered line, in launches of one slice / of four: 50,000 columns 7.3 / 6.9 ps, 100,000 8.4 / 10.1, 233,000 7.6 / 13.3).
+static int slices_a_walk(int64_t n_cols, int n_tiles) {
+    const int64_t most = (32LL << 20) / (128 * (n_cols > 0 ? n_cols : 1));
+    return most >= n_tiles ? n_tiles : 1;
+}
+
 hipError_t launch_gat_dalpha(const sensei_csr &A, const float *theta, const float *dP, int f, const float *logits, const float2 *mz,
                              float *dalpha, float *rowdot, const ChunkPlan &p, float *carry, hipStream_t s, float scale, int dp_rows) {
     GatBwdArgs a;
@@ -3254,9 +3362,11 @@ hipError_t launch_gat_dalpha(const sensei_csr &A, const float *theta, const floa
     const dim3 grid(blocks_for(p.n_chunks, kWavesPerBlock));
     if (A.nnz <= 0 && !rowdot) return hipSuccess;
     return with_per(p.chunk_nnz, [&](auto per) {
-        for (int t = 0; t < a.n_tiles; ++t) {
-            if (t == a.n_tiles - 1 && rowdot) hipLaunchKernelGGL((k_gat_dalpha<true, per()>), grid, dim3(kBlock), 0, s, a, t, t == 0 ? 1 : 0);
-            else hipLaunchKernelGGL((k_gat_dalpha<false, per()>), grid, dim3(kBlock), 0, s, a, t, t == 0 ? 1 : 0);
+        const int step = slices_a_walk(A.n_cols, a.n_tiles);
+        for (int t = 0; t < a.n_tiles; t += step) {
+            const int t1 = t + step < a.n_tiles ? t + step : a.n_tiles;
+            if (t1 == a.n_tiles && rowdot) hipLaunchKernelGGL((k_gat_dalpha<true, per()>), grid, dim3(kBlock), 0, s, a, t, t1);
+            else hipLaunchKernelGGL((k_gat_dalpha<false, per()>), grid, dim3(kBlock), 0, s, a, t, t1);
         }
         if (rowdot && p.n_chunks > 1)
             hipLaunchKernelGGL(k_sum_fixup, dim3(blocks_for(p.n_chunks - 1, kBlock)), dim3(kBlock), 0, s, a.n, rowdot, carry);
@@ -3284,7 +3394,8 @@ hipError_t launch_score_v2(const sensei_csr &A, const float *theta_l, const floa
     const dim3 grid(blocks_for(p.n_chunks, kWavesPerBlock));
     const int n_tiles = (f + 31) / 32;
     return with_per(p.chunk_nnz, [&](auto per) {
-        for (int t = 0; t < n_tiles; ++t) hipLaunchKernelGGL(k_score_v2<per()>, grid, dim3(kBlock), 0, s, a, t, t == 0 ? 1 : 0);
+        const int step = slices_a_walk(A.n_cols, n_tiles);
+        for (int t = 0; t < n_tiles; t += step) hipLaunchKernelGGL(k_score_v2<per()>, grid, dim3(kBlock), 0, s, a, t, t + step < n_tiles ? t + step : n_tiles);
     });
 }
 
@@ -3387,13 +3498,13 @@ hipError_t launch_gat_heads_backward(const sensei_csr &A, const ChunkPlan &p, co
     a.n_src = A.n_cols; a.n_dst = A.n_rows; a.ldd = b.ldd; a.d = b.d; a.slope = b.slope;
     a.store_vec_ok = b.ldd % 4 == 0 && b.d % 4 == 0 && reinterpret_cast<uintptr_t>(b.dtheta) % 16 == 0;
     const unsigned heads = (unsigned)b.heads;
-    hipError_t e = with_per(p.chunk_nnz, [&](auto per) {
+    hipError_t e = with_head_per(p.chunk_nnz, [&](auto per) {
         hipLaunchKernelGGL(k_gat_head_rows<per()>, dim3(blocks_for(p.n_chunks, kWavesPerBlock), heads), dim3(kBlock), 0, s, a);
         if (p.n_chunks > 1) hipLaunchKernelGGL(k_gat_head_fixup, dim3(blocks_for(p.n_chunks - 1, kBlock), heads), dim3(kBlock), 0, s, a);
     });
     if (e != hipSuccess) return e;
     a.n = nnz_args(At, pt);
-    return with_per(pt.chunk_nnz, [&](auto per) {
+    return with_head_per(pt.chunk_nnz, [&](auto per) {
         hipLaunchKernelGGL(k_gat_head_cols<per()>, dim3(blocks_for(pt.n_chunks, kWavesPerBlock), heads), dim3(kBlock), 0, s, a);
         if (pt.n_chunks > 1)
             hipLaunchKernelGGL(k_gat_head_cols_fixup, dim3(blocks_for(pt.n_chunks - 1, kWavesPerBlock * 8), heads), dim3(kBlock), 0, s, a);
