@@ -1552,17 +1552,19 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tn(GemmTnArgs g) {
 // of 16 k, fetches one step ahead.  The fp32 accumulators are emptied into fp64 registers after every second step.
 constexpr int kFlushStepsBf = 2;
 
+// A wavefront takes 64 x 32 outputs; a block of 128 columns has eight.  As four wavefronts of 64 x 64 they held 312 registers (fp32 and fp64 accumulators), one wavefront a SIMD
+// and nothing beside its cuts, flushes and waits: 602 x 233,000 x 256 833 us, now 560; 128 x 100,000 x 128 with its slab sums 80 -> 43.
 // TN = 1 (blocks of 128 x 64) where the product has at most 64 columns: half of the matrix work, of the pieces of B and of the fp64
 // accumulators of a 128-column block would be for columns that are not there (100,000 rows, 100 x 47: 45 -> 26.5 us; 233,000 rows,
 // 256 x 41: 150 -> 97; 50,000 rows, 100 x 64: 33 -> 19.6).
 template <int TN>
-__global__ __launch_bounds__(kThreads) void k_gemm_tn_bf(GemmTnArgs g) {
+__global__ __launch_bounds__(kThreads * TN, 2) void k_gemm_tn_bf(GemmTnArgs g) {
     constexpr int BM = 128, BN = 64 * TN, TM = 2;
     // [buffer][piece][32-column block: four of A, then 2 TN of B][k half][column][8 k]
     __shared__ __attribute__((aligned(16))) unsigned short Ps[2][3][4 + 2 * TN][2][32][8];
     const int t = threadIdx.x;
     const int wave = t >> 6, lane = t & 63;
-    const int wm = wave >> 1, wn = wave & 1;
+    const int wm = wave / (2 * TN), wn = wave % (2 * TN);   // a wavefront takes 64 x 32
     const int kh = lane >> 5, ll = lane & 31;
     const int tile = (int)(blockIdx.x % g.n_tiles), split = (int)(blockIdx.x / g.n_tiles);
     const int jn = tile % (g.n_bn * g.segs), seg = jn / g.n_bn;
@@ -1571,14 +1573,12 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tn_bf(GemmTnArgs g) {
     const long long k_lo = (long long)split * g.k_per_split;
     const long long k_hi = (k_lo + g.k_per_split < g.k) ? k_lo + g.k_per_split : g.k;
 
-    floatx16 acc[TM][TN];
-    double dacc[TM][TN][16];
+    floatx16 acc[TM];
+    double dacc[TM][16];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) { acc[i][j][r] = 0.f; dacc[i][j][r] = 0.0; }
+        for (int r = 0; r < 16; ++r) { acc[i][r] = 0.f; dacc[i][r] = 0.0; }
     // Every other group of steps multiplies -A and is subtracted: the instruction's sum of 16 products and the accumulator loses
     // low bits of the smaller addends downwards whatever their sign (measured: about -2^-29 of the sum of the terms' magnitudes),
     // which over 10^5 rows would add up to several units of fp32 rounding of the root-sum-square; in alternating groups it cancels.
@@ -1588,56 +1588,66 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tn_bf(GemmTnArgs g) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) { dacc[i][j][r] = fma(sg, (double)acc[i][j][r], dacc[i][j][r]); acc[i][j][r] = 0.f; }
+            for (int r = 0; r < 16; ++r) { dacc[i][r] = fma(sg, (double)acc[i][r], dacc[i][r]); acc[i][r] = 0.f; }
     };
 
-    // staging: thread -> (column of the 128, k half); columns past the edge read the last column and are cleared, rows past the slab
-    // read its last row and are cleared (masks, not branches around the fetches)
-    const int col = t & 127, skh = t >> 7;
-    const int b_col = t % BN, b_skh = (t / BN) & 1;   // TN = 1: the second 128 threads fetch the same words again and leave them
-    const bool b_on = t < 2 * BN;
-    const bool a_ok = m0 + col < g.m, b_ok = n0 + b_col < g.n;
-    const unsigned a_mask = a_ok ? ~0u : 0u, b_mask = b_ok ? ~0u : 0u;
-    // addresses: a uniform row pointer per k plus one 32-bit byte offset per lane (its k half and column), fixed before the loop
-    const unsigned a_off = (unsigned)(((long long)skh * 8 * g.lda + (a_ok ? m0 + col : g.m - 1)) * 4);
-    const unsigned b_off = (unsigned)(((long long)b_skh * 8 * g.ldb + (b_ok ? n0 + b_col : g.n - 1)) * 4);
-    float ra[8], rb[8];
-    auto fetch = [&](long long k0, auto whole) {
+    // staging: thread -> (operand, column, k half): with 512 threads one column of one operand each, with 256 a column of A and, half of them, one of
+    // B; columns past the edge read the last column and are cleared, rows past the slab read its last row and are cleared (masks, not branches
+    // around the fetches).  Addresses: a uniform row pointer per k plus one 32-bit byte offset per lane (its k half and column), fixed before the loop
+    struct Column { const float *base; long long ld; unsigned mask, off; int block, half, at; bool on; float v[8]; };
+    auto column = [&](bool of_a, int task) {
+        Column c;
+        const int cols = of_a ? BM : BN, col = task % cols, first = of_a ? m0 : n0, n_cols = of_a ? g.m : g.n;
+        c.on = task < 2 * cols;
+        c.half = (task / cols) & 1;
+        c.base = of_a ? g.A : B;
+        c.ld = of_a ? g.lda : g.ldb;
+        const bool ok = first + col < n_cols;
+        c.mask = ok ? ~0u : 0u;
+        c.off = (unsigned)(((long long)c.half * 8 * c.ld + (ok ? first + col : n_cols - 1)) * 4);
+        c.block = (of_a ? 0 : 4) + (col >> 5);
+        c.at = col & 31;
+        return c;
+    };
+    const bool mine_a = TN == 1 || __builtin_amdgcn_readfirstlane(wave) < 4;
+    Column own = column(mine_a, t & 255), second = TN == 1 ? column(false, t) : own;
+    auto fetch_one = [&](Column &c, bool of_a, long long k0, auto whole) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             if constexpr (decltype(whole)::value) {   // all 16 rows of the step lie inside the slab
-                const char *ar = reinterpret_cast<const char *>(g.A + (k0 + e) * g.lda), *br = reinterpret_cast<const char *>(B + (k0 + e) * g.ldb);
-                ra[e] = __uint_as_float(__float_as_uint(*reinterpret_cast<const float *>(ar + a_off)) & a_mask);
-                rb[e] = __uint_as_float(__float_as_uint(*reinterpret_cast<const float *>(br + b_off)) & b_mask);
+                const char *r = reinterpret_cast<const char *>(c.base + (k0 + e) * c.ld);
+                c.v[e] = __uint_as_float(__float_as_uint(*reinterpret_cast<const float *>(r + c.off)) & c.mask);
             } else {
-                const long long k = k0 + skh * 8 + e, kb = k0 + b_skh * 8 + e;
-                const long long kc = (k < k_hi ? k : k_hi - 1) - skh * 8, kbc = (kb < k_hi ? kb : k_hi - 1) - b_skh * 8;
-                const unsigned live = k < k_hi ? ~0u : 0u;
-                const char *ar = reinterpret_cast<const char *>(g.A + kc * g.lda), *br = reinterpret_cast<const char *>(B + kbc * g.ldb);
-                ra[e] = __uint_as_float(__float_as_uint(*reinterpret_cast<const float *>(ar + a_off)) & a_mask & live);
-                rb[e] = __uint_as_float(__float_as_uint(*reinterpret_cast<const float *>(br + b_off)) & b_mask);
+                const long long k = k0 + c.half * 8 + e, kc = (k < k_hi ? k : k_hi - 1) - c.half * 8;
+                const unsigned live = k < k_hi || !of_a ? ~0u : 0u;   // a row past the slab is cleared in A
+                const char *r = reinterpret_cast<const char *>(c.base + kc * c.ld);
+                c.v[e] = __uint_as_float(__float_as_uint(*reinterpret_cast<const float *>(r + c.off)) & c.mask & live);
             }
         }
     };
-    auto stash_one = [&](const float (&src)[8], int buf, int operand, int c, int half) {
+    auto fetch = [&](long long k0, auto whole) {
+        fetch_one(own, mine_a, k0, whole);
+        if constexpr (TN == 1) fetch_one(second, false, k0, whole);
+    };
+    auto stash_one = [&](const Column &c, bool of_a, int buf) {
         unsigned pc[8][3];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) split_bf16x3(src[e], pc[e][0], pc[e][1], pc[e][2]);
-        const unsigned flip = (operand == 0 && neg) ? 0x80008000u : 0u;   // the sign bits of a pair of bf16
+        for (int e = 0; e < 8; ++e) split_bf16x3(c.v[e], pc[e][0], pc[e][1], pc[e][2]);
+        const unsigned flip = (of_a && neg) ? 0x80008000u : 0u;   // the sign bits of a pair of bf16
 #pragma unroll
         for (int p = 0; p < 3; ++p) {
             uintx4 w;
 #pragma unroll
             for (int d = 0; d < 4; ++d) w[d] = pack_bf16(pc[2 * d][p], pc[2 * d + 1][p]) ^ flip;
-            if (operand == 0 || b_on) *reinterpret_cast<uintx4 *>(&Ps[buf][p][operand * 4 + (c >> 5)][half][c & 31][0]) = w;
+            if (c.on) *reinterpret_cast<uintx4 *>(&Ps[buf][p][c.block][c.half][c.at][0]) = w;
         }
     };
     auto stash = [&](int buf) {
-        stash_one(ra, buf, 0, col, skh);
-        __builtin_amdgcn_sched_barrier(0);   // one operand's pieces at a time in registers
-        stash_one(rb, buf, 1, b_col, b_skh);
+        stash_one(own, mine_a, buf);
+        if constexpr (TN == 1) {
+            __builtin_amdgcn_sched_barrier(0);   // one operand's pieces at a time in registers
+            stash_one(second, false, buf);
+        }
     };
 
     if (k_lo < k_hi) {
@@ -1654,14 +1664,12 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tn_bf(GemmTnArgs g) {
 #pragma unroll
                 for (int i = 0; i < TM; ++i) af[i] = *reinterpret_cast<const uintx4 *>(&Ps[buf][pa][wm * TM + i][kh][ll][0]);
 #pragma unroll
-                for (int pb = 2 - pa; pb >= 0; --pb)   // smallest products first
+                for (int pb = 2 - pa; pb >= 0; --pb) {   // smallest products first
+                    const uintx4 bf = *reinterpret_cast<const uintx4 *>(&Ps[buf][pb][4 + wn][kh][ll][0]);
 #pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        const uintx4 bf = *reinterpret_cast<const uintx4 *>(&Ps[buf][pb][4 + wn * TN + j][kh][ll][0]);
-#pragma unroll
-                        for (int i = 0; i < TM; ++i)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[i]), __builtin_bit_cast(bf16x8, bf), acc[i][j], 0, 0, 0);
-                    }
+                    for (int i = 0; i < TM; ++i)
+                        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[i]), __builtin_bit_cast(bf16x8, bf), acc[i], 0, 0, 0);
+                }
             }
             if (++since_flush == kFlushStepsBf) { flush(); since_flush = 0; neg ^= 1; }   // the pieces stashed below belong to the next group
             __builtin_amdgcn_sched_barrier(0);
@@ -1678,17 +1686,14 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tn_bf(GemmTnArgs g) {
 
     const size_t width = (size_t)g.n * g.segs;
     double *out = g.part + (size_t)split * (size_t)g.m * width + (size_t)seg * g.n;
+    const int c = n0 + wn * 32 + ll;
+    if (c >= g.n) return;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int c = n0 + (wn * TN + j) * 32 + ll;
-            if (c >= g.n) continue;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = m0 + (wm * TM + i) * 32 + 8 * (r / 4) + 4 * kh + (r % 4);
-                if (row < g.m) out[(size_t)row * width + c] = dacc[i][j][r];
-            }
+        for (int r = 0; r < 16; ++r) {
+            const int row = m0 + (wm * TM + i) * 32 + 8 * (r / 4) + 4 * kh + (r % 4);
+            if (row < g.m) out[(size_t)row * width + c] = dacc[i][r];
         }
 }
 
@@ -2046,9 +2051,14 @@ hipError_t launch_gemv2(const float *A, int64_t lda, int64_t n, int k, const flo
     return hipGetLastError();
 }
 
+// Slabs: as many workgroups as the chip holds at once, one a compute unit (two of the 64-column kernel's), and not one more: the slab sums are 128 KB a block
+// in fp64, written and read again, and the workgroups that did not fit ran in a round of their own.  With 256 / 512 / 768 workgroups (twice as many
+// of the 64-column kernel), training passes, us: four heads on 100,000 nodes 570 / 575 / 592, GATv2 on 50,000 601 / 619 / 631, K-hop on 100,000 390 / 402 / 421, two layers on
+// 233,000 8,580 / 8,549 / 8,584.
 int gemm_tn_splits(int64_t k, int m, int n, int segs) {
     const long long tiles = (long long)((m + 127) / 128) * ((n + 127) / 128) * segs;
-    long long s = (768 + tiles - 1) / tiles;              // about three workgroups per compute unit
+    // below 4,096 rows the fp32 kernel runs, three workgroups a compute unit
+    long long s = k < 4096 ? (768 + tiles - 1) / tiles : (n <= 64 ? 512 : 256) / tiles;
     const long long max_s = (k + 4 * KT - 1) / (4 * KT);  // at least four k-tiles per slab
     if (s > max_s) s = max_s;
     return (int)(s < 1 ? 1 : s);
@@ -2075,7 +2085,7 @@ hipError_t launch_gemm_tn(const float *A, int64_t lda, const float *B, int64_t l
     // long reductions (the weight gradients of a layer) take the bf16-piece kernel
     if (g.k >= 4096 && g.k_per_split >= 64) {
         if (n <= 64) hipLaunchKernelGGL(k_gemm_tn_bf<1>, grid, dim3(kThreads), 0, s, g);   // one block of columns either way
-        else hipLaunchKernelGGL(k_gemm_tn_bf<2>, grid, dim3(kThreads), 0, s, g);
+        else hipLaunchKernelGGL(k_gemm_tn_bf<2>, grid, dim3(2 * kThreads), 0, s, g);
     }
     else if (va && vb) hipLaunchKernelGGL((k_gemm_tn<4, 4>), grid, dim3(kThreads), 0, s, g);
     else if (va) hipLaunchKernelGGL((k_gemm_tn<4, 1>), grid, dim3(kThreads), 0, s, g);
