@@ -158,11 +158,19 @@ size_t gcn_ws(const sensei_csr &A, int f_in, int f_out, int id) {
 
 bool gat_is_reuse(int id) { return id == SENSEI_GAT_REUSE || id == SENSEI_GAT_REUSE_FOLD; }
 
-// Heads of 32 columns whose Theta is slice-major are aggregated in one launch where the one-walk form is taken; at most kHeadsPerLaunch (the
-// workspace query does not know the number of heads: it makes room for as many as f_out allows).
+// Heads whose columns do not begin at a multiple of four: side by side in Theta they would be gathered four or eight bytes a lane, so each gets slices of its
+// own (zero columns behind it), as many heads at a time as Theta has room for.  Passes before / now, us: inference, 8 heads of 15 columns on 1.5 M entries 928 (heads one after
+// the other) / 300, 2 of 37 on 1.1 M 451 / 255; training, 4 of 23 on 9.4 M 5,000 / 3,720, on 164,000 336 / 257.  Where Theta holds one head at a time every head costs
+// a launch more: on a small pattern they stay side by side (2 heads of 14 on 13,500 entries, training, 106 / 112).
+bool heads_padded(const sensei_csr &A, int d, int n_heads, int id) {
+    return gat_is_reuse(id) && n_heads > 1 && d % 4 != 0 && (pad32(d * n_heads) > pad32(d) || A.nnz >= (1 << 17));
+}
+
+// Heads of at most 32 columns whose Theta is slice-major are aggregated in one launch where the one-walk form is taken; at most kHeadsPerLaunch (the
+// workspace query does not know the number of heads: it makes room for as many slices as f_out fills).
 constexpr int kHeadsPerLaunch = 16;
 int fused_heads_max(int f_out, int id) {
-    const int heads = f_out % 32 == 0 && id == SENSEI_GAT_REUSE ? f_out / 32 : 1;
+    const int heads = id == SENSEI_GAT_REUSE ? pad32(f_out) / 32 : 1;
     return heads < kHeadsPerLaunch ? heads : kHeadsPerLaunch;
 }
 
@@ -186,6 +194,7 @@ size_t gat_ws(const sensei_csr &A, int f_in, int f_out, int id) {
     b += align_up((size_t)(A.nnz > 0 ? A.nnz : 1) * sizeof(float), 256);       // attention logits
     b += 2 * align_up((size_t)fi * sizeof(float), 256);                        // W.a_l, W.a_r
     if (id != SENSEI_GAT_RECOMP_FOLD) b += align_up((size_t)A.n_cols * fo * sizeof(float), 256);  // Theta
+    if (gat_is_reuse(id)) b += align_up((size_t)f_in * fo * sizeof(float), 256);                  // W with padded heads
     if (A.panels) b += align_up(panel_stats_pairs(*A.panels) * sizeof(float2), 256);
     if (gat_is_reuse(id)) {
         b += spmm_carry_bytes(A.nnz, fo);
@@ -762,6 +771,10 @@ int run_gat(const sensei_csr &A, const sensei_mat &X, const sensei_mat &W, const
     float *v_r = cv.take<float>((size_t)fi);
     float *theta = nullptr;
     if (id != SENSEI_GAT_RECOMP_FOLD) theta = cv.take<float>((size_t)A.n_cols * fo);
+    const bool padded = heads_padded(A, d, n_heads, id);
+    const int dp = padded ? pad32(d) : d;               // columns of a head in Theta
+    const int per_theta = padded ? fo / dp : n_heads;   // heads that are in Theta at a time
+    float *Wp = padded ? cv.take<float>((size_t)f_in * fo) : nullptr;
 
     SideWork side;
     side.add_plan(A, plan);
@@ -769,10 +782,17 @@ int run_gat(const sensei_csr &A, const sensei_mat &X, const sensei_mat &W, const
     const bool reuse = gat_is_reuse(id);
     // Theta is slice-major when the SpMM gathers from it (reuse) and a head's columns are whole 32-column slices; the
     // recompute id only projects it
-    const bool theta_sliced = reuse && (n_heads == 1 || d % 32 == 0);
-    if (theta)
-        SENSEI_TRY(launch_gemm(X.ptr, X.ld, W.ptr, W.ld, theta, fo, A.n_cols, f_in, f_out, fo, SENSEI_ACT_NONE, s, nullptr, gt, theta_sliced, false, nullptr,
-                               &side));
+    const bool theta_sliced = reuse && (n_heads == 1 || dp % 32 == 0);
+    auto project = [&](int h) -> hipError_t {   // Theta, or its columns of the heads from h on
+        if (!padded)
+            return launch_gemm(X.ptr, X.ld, W.ptr, W.ld, theta, fo, A.n_cols, f_in, f_out, fo, SENSEI_ACT_NONE, s, nullptr, gt, theta_sliced, false, nullptr,
+                               &side);
+        const int hb = n_heads - h < per_theta ? n_heads - h : per_theta;
+        const hipError_t e = launch_pad_heads(W.ptr + (size_t)h * d, W.ld, f_in, hb, d, Wp, hb * dp, s);
+        if (e != hipSuccess) return e;
+        return launch_gemm(X.ptr, X.ld, Wp, hb * dp, theta, hb * dp, A.n_cols, f_in, hb * dp, hb * dp, SENSEI_ACT_NONE, s, nullptr, gt, true, false, nullptr, &side);
+    };
+    if (theta) SENSEI_TRY(project(0));
     // recompute ids gather from X: slice-major copy once for all heads when its rows are gathered often enough
     float *carry = cv.take<float>(spmm_carry_bytes(A.nnz, reuse ? fo : fi) / sizeof(float));
     float *U = nullptr;
@@ -788,24 +808,26 @@ int run_gat(const sensei_csr &A, const sensei_mat &X, const sensei_mat &W, const
         }
     }
     SENSEI_TRY(launch_side(&side, s));
-    const int f_gather = reuse ? (n_heads == 1 ? fo : d) : f_in;  // width of the aggregation of one head
+    const int f_gather = reuse ? (n_heads == 1 ? fo : dp) : f_in;  // width of the aggregation of one head
     // dense-tile split (the gathered operand, Theta or X, must be slice-major): the tiles form their weights from s_l, s_r
     // themselves, only the remainder's logits are stored
     const int path = attention_path(A, f_gather, reuse ? theta_sliced : x_sliced);
     const bool by_tiles = path == kAttnTiles, by_panel = path == kAttnPanels, fused = path == kAttnOneWalk;
-    if (fused && theta_sliced && n_heads > 1 && d == 32 && id == SENSEI_GAT_REUSE) {
+    const int most = std::min(fused_heads_max(f_out, id), per_theta);
+    if (fused && theta_sliced && n_heads > 1 && dp == 32 && id == SENSEI_GAT_REUSE && most > 1) {
         // every head is a slice of Theta: projections, walk and fix-up of up to kHeadsPerLaunch heads in a launch each
-        const int most = fused_heads_max(f_out, id);
         float *hs_l = cv.take<float>((size_t)most * A.n_cols), *hs_r = cv.take<float>((size_t)most * A.n_cols);
         float2 *h_mz = cv.take<float2>((size_t)most * (A.n_rows + 1)), *h_carry = cv.take<float2>((size_t)most * plan.n_chunks);
-        for (int h = 0; h < n_heads; h += most) {
-            const int hb = n_heads - h < most ? n_heads - h : most;
-            const float *theta_h = theta + (size_t)h * (size_t)A.n_cols * 32;
+        for (int h = 0, hb = 0; h < n_heads; h += hb) {
+            const int in_theta = h % per_theta;
+            hb = std::min(std::min(n_heads - h, most), per_theta - in_theta);
+            if (h > 0 && in_theta == 0) SENSEI_TRY(project(h));
+            const float *theta_h = theta + (size_t)in_theta * (size_t)A.n_cols * 32;
             SENSEI_TRY(launch_head_scores(theta_h, A.n_cols, hb, d, a_l + (size_t)h * d, a_r + (size_t)h * d, hs_l, hs_r, s));
-            const AttnFusedArgs fa = {hs_l, hs_r, slope, h_mz, h_carry, hb};
+            const AttnFusedArgs fa = {hs_l, hs_r, slope, h_mz, h_carry, hb, d};
             hipEvent_t t0 = kt ? kt->next() : nullptr, t1 = t0 ? kt->next() : nullptr;
             if (t1) SENSEI_TRY(hipEventRecord(t0, s));
-            SENSEI_TRY(launch_spmm(A, kSpmmAttnFused, nullptr, nullptr, theta_h, fo, hb * d, Y + (size_t)h * d, ldy, hb * d, act, plan, carry, s, nullptr, false,
+            SENSEI_TRY(launch_spmm(A, kSpmmAttnFused, nullptr, nullptr, theta_h, fo, hb * 32, Y + (size_t)h * d, ldy, hb * d, act, plan, carry, s, nullptr, false,
                                    true, nullptr, true, 1, false, false, &fa));
             if (t1) SENSEI_TRY(hipEventRecord(t1, s));
         }
@@ -814,7 +836,8 @@ int run_gat(const sensei_csr &A, const sensei_mat &X, const sensei_mat &W, const
     float2 *panel_pairs = by_panel ? cv.take<float2>(panel_stats_pairs(*A.panels)) : nullptr;
     for (int h = 0; h < n_heads; ++h) {
         const float *al = a_l + (size_t)h * d, *ar = a_r + (size_t)h * d;
-        const float *theta_h = !theta ? nullptr : theta_sliced ? theta + (size_t)h * (d / 32) * (size_t)A.n_cols * 32 : theta + (size_t)h * d;
+        if (padded && h > 0 && h % per_theta == 0) SENSEI_TRY(project(h));
+        const float *theta_h = !theta ? nullptr : theta_sliced ? theta + (size_t)(h % per_theta) * (dp / 32) * (size_t)A.n_cols * 32 : theta + (size_t)h * d;
         if (!fold) {  // the two projections of the head's columns of Theta
             SENSEI_TRY(launch_gemv2(theta_h, fo, A.n_cols, d, al, ar, s_l, s_r, s, theta_sliced));
         } else {      // (X.W).a = X.(W.a)
@@ -2749,8 +2772,9 @@ int sensei_gat_attention_path(const sensei_csr *A, int f_in, int f_out, int n_he
     if (!csr_ok(A, false) || f_in <= 0 || f_out <= 0 || n_heads < 1 || f_out % n_heads != 0 || comp_id < 0 || comp_id >= kNumGat) return -1;
     const bool reuse = gat_is_reuse(comp_id);
     const int d = f_out / n_heads;
-    const bool sliced = reuse ? (n_heads == 1 || d % 32 == 0) : relayout_pays(*A);
-    return attention_path(*A, reuse ? (n_heads == 1 ? pad32(f_out) : d) : f_in, sliced);
+    const int dp = heads_padded(*A, d, n_heads, comp_id) ? pad32(d) : d;
+    const bool sliced = reuse ? (n_heads == 1 || dp % 32 == 0) : relayout_pays(*A);
+    return attention_path(*A, reuse ? (n_heads == 1 ? pad32(f_out) : dp) : f_in, sliced);
 }
 
 int sensei_gat_workspace(const sensei_csr *A, int f_in, int f_out, int comp_id, size_t *bytes) {

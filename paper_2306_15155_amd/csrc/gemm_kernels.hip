@@ -1253,13 +1253,13 @@ __global__ __launch_bounds__(kThreads) void k_head_scores(const float *__restric
     }
 }
 
-__global__ void k_pad_heads(const float *__restrict__ W, long long ldw, int f_in, int heads, int d, float *__restrict__ out, long long ldo) {
+__global__ void k_pad_heads(const float *__restrict__ W, long long ldw, int f_in, int heads, int d, int dp, float *__restrict__ out, long long ldo) {
     const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const int cols = heads * 32;
+    const int cols = heads * dp;
     if (t >= (long long)f_in * cols) return;
-    const int q = (int)(t % cols), c = q & 31;
+    const int q = (int)(t % cols), c = q % dp;
     const long long k = t / cols;
-    out[k * ldo + q] = c < d ? W[k * ldw + (q >> 5) * d + c] : 0.f;
+    out[k * ldo + q] = c < d ? W[k * ldw + (q / dp) * d + c] : 0.f;
 }
 
 // the attention vectors in rank order (zeros where a rank has no node)
@@ -2033,9 +2033,10 @@ hipError_t launch_head_scores(const float *theta, int64_t n, int heads, int d, c
 }
 
 hipError_t launch_pad_heads(const float *W, int64_t ldw, int f_in, int heads, int d, float *out, int64_t ldo, hipStream_t s) {
-    const long long total = (long long)f_in * heads * 32;
+    const int dp = pad32(d);
+    const long long total = (long long)f_in * heads * dp;
     if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_pad_heads, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, W, (long long)ldw, f_in, heads, d, out, (long long)ldo);
+    hipLaunchKernelGGL(k_pad_heads, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, W, (long long)ldw, f_in, heads, d, dp, out, (long long)ldo);
     return hipGetLastError();
 }
 

@@ -136,7 +136,8 @@ struct AttnFusedArgs {
     const float *s_l, *s_r;
     float slope;
     float2 *row_mz, *chunk_mz;
-    int heads = 1;   // > 1 (slice-major B of heads * 32 columns, all stored): slice h is head h's; s_l, s_r, row_mz and chunk_mz one after the other per head
+    int heads = 1;   // > 1 (slice-major B of heads * 32 columns): slice h is head h's; s_l, s_r, row_mz and chunk_mz one after the other per head
+    int cols = 32;   // heads > 1: columns of a head that are stored, side by side in C (f_store = heads * cols)
 };
 // Backward of the GATv2 score (slice-major own over the rows of A, other and dP over its columns): cols = false: C = att (x) sum_j w LeakyReLU'(own + other)
 // and R (slice-major) = sum_j w LeakyReLU(own + other); cols = true, w holding (alpha, de) pairs: C = sum_j alpha dP_j + att (x) sum_j de LeakyReLU'(own +
@@ -242,7 +243,7 @@ hipError_t launch_gat_heads_backward(const sensei_csr &A, const ChunkPlan &p, co
                                      hipStream_t s);
 // s_l[h][j] = Theta_h[j, :] . a_l[h], s_r likewise, for heads of d <= 32 columns; theta holds one slice a head (n rows)
 hipError_t launch_head_scores(const float *theta, int64_t n, int heads, int d, const float *a_l, const float *a_r, float *s_l, float *s_r, hipStream_t s);
-// out (f_in x heads * 32, ldo): head h's d columns of W followed by zero columns up to 32
+// out (f_in x heads * pad32(d), ldo): head h's d columns of W followed by zero columns up to a multiple of 32
 hipError_t launch_pad_heads(const float *W, int64_t ldw, int f_in, int heads, int d, float *out, int64_t ldo, hipStream_t s);
 // pos[k] = place of entry k of A in At (binary search in the ascending columns of At); *miss (cleared first) counts entries not found
 hipError_t launch_transpose_pos(const sensei_csr &A, const sensei_csr &At, const ChunkPlan &p, int32_t *pos, int32_t *miss, hipStream_t s);

@@ -70,6 +70,7 @@ struct SpmmArgs {
     const float *s_l, *s_r;
     float slope;
     long long head_vec, head_mz;  // several heads of one tile each: floats from one head's score vectors to the next, pairs from one head's mz_out to the next (0: one head)
+    int head_cols;   // several heads: columns of a head that are stored (c_tile apart)
     float2 *mz_out, *carry_mz;  // per row: pair of a first piece whose row goes on in the next chunk; per chunk: pair of its continued row
 };
 
@@ -726,6 +727,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
     if (chunk >= a.n_chunks) return;
     const int f0 = tile * (4 * LPG) + li * 4;
     const bool fok = f0 < a.f;
+    const int f_end = MODE == kSpmmAttnFused && a.head_vec ? tile * 32 + a.head_cols : a.f_store;   // columns from here on are not stored
     const char *Bb = reinterpret_cast<const char *>(a.B) + (long long)tile * a.tile_stride_b;
     const unsigned f0_b = fok ? (unsigned)li * 16u : 0u;
     float *c_lane = a.C + (size_t)tile * a.c_tile + li * 4;   // this lane's columns of row 0 of C
@@ -737,7 +739,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
     };
     int *rows = s_row[wave], *cols = s_col[wave];
     float *scale = s_scale[kScaleRows ? wave : 0], *wgt = s_w[kWeights ? wave : 0];
-    const bool vec = PLAIN ? f0 < a.f_store : a.store_vec_ok && f0 + 4 <= a.f_store;
+    const bool vec = PLAIN ? f0 < f_end : a.store_vec_ok && f0 + 4 <= f_end;
     // a finished row, or (finish = false) a piece of one that goes on in the next chunk
     auto write_row = [&](int row, float sc, float4 v, bool finish) {
         float *dst = c_lane + (size_t)row * a.ldc;
@@ -746,10 +748,10 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
                 const float4 o = *reinterpret_cast<const float4 *>(dst);
                 v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
             } else {
-                if (f0 < a.f_store) v.x += dst[0];
-                if (f0 + 1 < a.f_store) v.y += dst[1];
-                if (f0 + 2 < a.f_store) v.z += dst[2];
-                if (f0 + 3 < a.f_store) v.w += dst[3];
+                if (f0 < f_end) v.x += dst[0];
+                if (f0 + 1 < f_end) v.y += dst[1];
+                if (f0 + 2 < f_end) v.z += dst[2];
+                if (f0 + 3 < f_end) v.w += dst[3];
             }
         }
         if (a.finalize && finish) {
@@ -761,10 +763,10 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
         if (vec) {
             *reinterpret_cast<float4 *>(dst) = v;
         } else if (!PLAIN) {
-            if (f0 < a.f_store) dst[0] = v.x;
-            if (f0 + 1 < a.f_store) dst[1] = v.y;
-            if (f0 + 2 < a.f_store) dst[2] = v.z;
-            if (f0 + 3 < a.f_store) dst[3] = v.w;
+            if (f0 < f_end) dst[0] = v.x;
+            if (f0 + 1 < f_end) dst[1] = v.y;
+            if (f0 + 2 < f_end) dst[2] = v.z;
+            if (f0 + 3 < f_end) dst[3] = v.w;
         }
     };
     const NnzArgs nz = {a.row_ptr, a.col_idx, a.chunk_row, a.n_rows, a.nnz, a.chunk_nnz, a.n_chunks};
@@ -1143,7 +1145,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_fixup_attn(SpmmArgs a) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     if (a.head_vec) {   // one head (32 columns) per blockIdx.y
         const int head = blockIdx.y;
-        a.f_store = min(a.f_store - head * 32, 32);
+        a.f_store = a.head_cols;
         a.C += (size_t)head * a.c_tile;
         a.carry += (size_t)head * 32;
         a.mz_out += head * a.head_mz;
@@ -3147,13 +3149,15 @@ hipError_t launch_spmm(const sensei_csr &A, int mode, const float *r, const floa
     a.store_vec_ok = (ldc % sh.vec == 0) && (reinterpret_cast<uintptr_t>(C) % (4 * sh.vec) == 0);
     a.accumulate = accumulate ? 1 : 0; a.finalize = finalize ? 1 : 0;
     a.scale_weights = defer_fixup ? 0 : 1;   // deferred fix-up: the caller wants raw sums
-    a.s_l = nullptr; a.s_r = nullptr; a.slope = 0.f; a.mz_out = nullptr; a.carry_mz = nullptr; a.head_vec = 0; a.head_mz = 0;
+    a.s_l = nullptr; a.s_r = nullptr; a.slope = 0.f; a.mz_out = nullptr; a.carry_mz = nullptr; a.head_vec = 0; a.head_mz = 0; a.head_cols = 0;
     if (mode == kSpmmAttnFused) {
         if (!fused || accumulate || !finalize || defer_fixup) return hipErrorInvalidValue;
         a.s_l = fused->s_l; a.s_r = fused->s_r; a.slope = fused->slope; a.mz_out = fused->row_mz; a.carry_mz = fused->chunk_mz;
         if (fused->heads > 1) {
-            if (!b_sliced || f != fused->heads * 32 || f_store != f) return hipErrorInvalidValue;
-            a.head_vec = A.n_cols; a.head_mz = A.n_rows + 1;
+            if (!b_sliced || c_sliced || f != fused->heads * 32 || fused->cols > 32 || f_store != fused->heads * fused->cols) return hipErrorInvalidValue;
+            a.head_vec = A.n_cols; a.head_mz = A.n_rows + 1; a.head_cols = fused->cols;
+            a.c_tile = fused->cols;
+            if (fused->cols % 4 != 0) a.store_vec_ok = 0;   // a head's columns begin anywhere
         }
     }
     const unsigned groups = blocks_for(p.n_chunks, kWavesPerBlock);

@@ -1,0 +1,52 @@
+"""Forward attention of heads whose columns do not begin at a multiple of four: they get slices of their own in Theta, as many at a time as it has room for.  One head at a
+time (patterns of 131,072 entries on; the others of 2 x 14 stay side by side), batches with one left over, heads of one slice and of two, rows long enough for the one-walk form and not, with a dense-tile split, against
+the oracle at the parity tolerance per element (fp32 sums of at most a few thousand terms of order one)."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from paper_2306_15155_amd import ACT_NONE, ACT_RELU, Context, Tiles, binding, csr_struct
+
+from gpu_util import DeviceCSR, assert_close, dev, hub_and_empty_graph, rect_block
+
+pytestmark = pytest.mark.gpu
+
+PATTERNS = {"long": lambda: synth.rmat(5, 2_000, 60_000), "short": lambda: synth.rmat(6, 4_000, 16_000), "hub": lambda: hub_and_empty_graph(3, 900, 5_000, 700, 40),
+            "rect": lambda: rect_block(4, 260, 900, 20), "large": lambda: synth.rmat(9, 8_000, 110_000)}
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = Context(0)
+    yield c
+    c.close()
+
+
+def _inputs(g, heads, d):
+    X, W = synth.uniform(7, 1, (g.n_cols, 36), -0.5, 0.5), synth.glorot(7, 2, 36, heads * d)
+    return X, W, synth.normal(7, 3, (heads * d,), 0.0, 0.3), synth.normal(7, 4, (heads * d,), 0.0, 0.3)
+
+
+# 2 x 14: Theta holds one head; 4 x 23: three and one; 17 x 3: two and a last one; 3 x 37: two slices a head, two heads and one; 20 x 31: more than one launch takes
+@pytest.mark.parametrize("name", PATTERNS)
+@pytest.mark.parametrize("heads,d", [(2, 1), (2, 14), (4, 23), (17, 3), (3, 37), (20, 31)])
+def test_heads(ctx, name, heads, d):
+    g = PATTERNS[name]()
+    A, (X, W, a_l, a_r) = DeviceCSR(g), _inputs(g, heads, d)
+    for act, comp in ((ACT_RELU, 0), (ACT_NONE, 3)):
+        want = oracle.gat_layer_heads(g.n_rows, g.n_cols, g.row_ptr, g.col_idx, X, W, a_l, a_r, heads, 0.2, act)
+        assert_close(ctx.gat_layer_heads(A.s, dev(X), dev(W), dev(a_l), dev(a_r), heads, comp, 0.2, act), want, what=f"comp {comp}")
+
+
+def test_with_tiles(ctx):
+    g = synth.rmat(8, 3_000, 300_000)
+    heads, d = 2, 37
+    row_ptr, col_idx = dev(g.row_ptr), dev(g.col_idx)
+    tiles = Tiles(ctx, csr_struct(g.n_rows, g.n_cols, row_ptr, col_idx), 0.05, 128)
+    At = csr_struct(g.n_rows, g.n_cols, row_ptr, col_idx, tiles=tiles)
+    assert tiles.n_tiles > 0 and binding.gat_attention_path(At, 36, heads * d, 0, heads) == binding.GAT_PATH_TILES
+    X, W, a_l, a_r = _inputs(g, heads, d)
+    want = oracle.gat_layer_heads(g.n_rows, g.n_cols, g.row_ptr, g.col_idx, X, W, a_l, a_r, heads, 0.2, ACT_RELU)
+    for comp in (0, 3):
+        assert_close(ctx.gat_layer_heads(At, dev(X), dev(W), dev(a_l), dev(a_r), heads, comp, 0.2, ACT_RELU), want, what=f"comp {comp}")
