@@ -1039,15 +1039,13 @@ int run_gatv2_backward(const sensei_csr &A_in, const sensei_csr &At_in, const in
     SideWork side;
     side.add_plan(A, plan);
     side.add_plan(At, plan_t);
-    // forward quantities: both projections (slice-major), the logits and the row statistics
+    // forward quantities: both projections (slice-major)
     SENSEI_TRY(launch_to_slices(nullptr, att, f_out, 1, f_out, att_pad, s, nullptr, 0, &side));
     SENSEI_TRY(launch_gemm(X.ptr, X.ld, Wr.ptr, Wr.ld, theta_r, fo, A.n_cols, f_in, f_out, fo, SENSEI_ACT_NONE, s, nullptr, nullptr, true));
     SENSEI_TRY(launch_gemm(X.ptr, X.ld, Wl.ptr, Wl.ld, theta_l, fo, A.n_rows, f_in, f_out, fo, SENSEI_ACT_NONE, s, nullptr, nullptr, true));
-    SENSEI_TRY(launch_score_v2(A, theta_l, theta_r, f_out, att_pad, slope, logits, plan, s));
-    SENSEI_TRY(launch_softmax(A, logits, nullptr, plan, stats, carry_stats, s));
     SENSEI_TRY(launch_to_slices(nullptr, dY.ptr, dY.ld, A.n_rows, f_out, dPs, s, act == SENSEI_ACT_RELU ? Y : nullptr, ldy));
-    // per stored entry: dalpha and its weighted row sums, then the softmax backward; alpha and de also in transposed order
-    SENSEI_TRY(launch_gat_dalpha(A, theta_r, dPs, f_out, logits, stats, de, rowdot, plan, sum_carry, s));
+    // per stored entry: logit and dalpha, over the rows the statistics and the weighted sums; then the softmax backward; alpha and de also in transposed order
+    SENSEI_TRY(launch_v2_scores(A, theta_l, theta_r, dPs, f_out, att_pad, slope, logits, de, stats, carry_stats, rowdot, sum_carry, plan, s));
     SENSEI_TRY(launch_gat_dt(A, logits, de, rowdot, stats, t_pos, 1.f, de, ade_t, plan, s));
     // [dTheta_r | dTheta_l], zero where nothing is written (pad columns; the rows of dTheta_l past the destinations)
     const bool padded = fo4 != f_out;

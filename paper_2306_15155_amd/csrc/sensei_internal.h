@@ -217,6 +217,9 @@ hipError_t launch_gat_dt(const sensei_csr &A, const float *logits, const float *
 // (n_rows x pad32(f), n_cols x pad32(f)), att padded with zeros to pad32(f)
 hipError_t launch_score_v2(const sensei_csr &A, const float *theta_l, const float *theta_r, int f, const float *att_padded, float slope,
                            float *logits, const ChunkPlan &p, hipStream_t s);
+// the same, dalpha[k] = <dP[i,:], theta_r[j,:]>, the row statistics of the logits and rowdot[i] = sum_j alpha_ij dalpha_ij, in one walk (backward of the GATv2 layer)
+hipError_t launch_v2_scores(const sensei_csr &A, const float *theta_l, const float *theta_r, const float *dP, int f, const float *att_padded, float slope,
+                            float *logits, float *dalpha, float2 *stats, float2 *carry_stats, float *rowdot, float *carry, const ChunkPlan &p, hipStream_t s);
 hipError_t launch_rank1_add(float *D, int64_t ldd, int64_t n, int f, const float *ds_l, int64_t n_l, const float *ds_r, const float *a_l,
                             const float *a_r, hipStream_t s);
 // out_l = Theta^T v_l (v_l counted for the first n_l rows), out_r = Theta^T v_r; Theta slice-major n x pad32(f); sums in fp64

@@ -234,21 +234,22 @@ __device__ __forceinline__ int2 find_chunk_rows(const NnzArgs &a, int chunk, int
     return make_int2(first.lo, chunk + 1 < a.n_chunks ? last.lo : a.n_rows);
 }
 
-// Segmented sum of v (blocked order; entries past the end of the chunk hold 0): write(row, sum, place of the piece's last entry) once per
-// row piece of the chunk.
+// Segmented sum of v (blocked order; entries past the end of the chunk hold 0): write(row, sum, end, last) once per
+// row piece of the chunk: end is the place of its last entry in the chunk, last that entry's number in this lane (-1: the lane before's last; past the end of the
+// chunk entries count as the last piece's).
 // A lane's entries fall into a head (up to its first row start), whole rows, and a tail; the heads are completed by the scan.
 template <int PER, int N, class Write>
 __device__ __forceinline__ void flat_sums(const FlatChunk<PER> &c, int lane, const float (&v)[N][PER], Write write) {
     float head[N], run[N], before[N];
 #pragma unroll
     for (int n = 0; n < N; ++n) head[n] = run[n] = 0.f;
-    int head_end = 0;
+    int head_last = 0;
     bool started = false;
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
         if ((c.starts >> e) & 1u) {
-            if (started) write(c.rid[e > 0 ? e - 1 : 0], run, lane * PER + e - 1);
-            else head_end = lane * PER + e - 1;
+            if (started) write(c.rid[e > 0 ? e - 1 : 0], run, lane * PER + e - 1, e - 1);
+            else head_last = e - 1;
 #pragma unroll
             for (int n = 0; n < N; ++n) {
                 if (!started) head[n] = run[n];
@@ -275,16 +276,25 @@ __device__ __forceinline__ void flat_sums(const FlatChunk<PER> &c, int lane, con
     if (started && head_row >= 0 && lane > 0) {
 #pragma unroll
         for (int n = 0; n < N; ++n) head[n] = before[n] + head[n];
-        write(head_row, head, head_end);
+        write(head_row, head, lane * PER + head_last, head_last);
     }
-    if (lane == 63) write(c.rid[PER - 1], run, c.hi - c.lo - 1);
+    if (lane == 63) write(c.rid[PER - 1], run, c.hi - c.lo - 1, PER - 1);
 }
 template <int PER, class Write>
 __device__ __forceinline__ void flat_sum(const FlatChunk<PER> &c, int lane, const float (&v)[PER], Write write) {
     float one[1][PER];
 #pragma unroll
     for (int e = 0; e < PER; ++e) one[0][e] = v[e];
-    flat_sums<PER, 1>(c, lane, one, [&](int row, const float (&sum)[1], int end) { write(row, sum[0], end); });
+    flat_sums<PER, 1>(c, lane, one, [&](int row, const float (&sum)[1], int end, int) { write(row, sum[0], end); });
+}
+
+// x[last], before for last = -1 (flat_sums' `last`: a constant but for a lane's first piece)
+template <int PER>
+__device__ __forceinline__ float last_value(const float (&x)[PER], float before, int last) {
+    float v = before;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) v = last >= q ? x[q] : v;
+    return v;
 }
 
 // The maximum over every row piece, for each of its entries (blocked order; entries past the end of the chunk hold -inf): inside the lane,
@@ -740,20 +750,23 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
     int *rows = s_row[wave], *cols = s_col[wave];
     float *scale = s_scale[kScaleRows ? wave : 0], *wgt = s_w[kWeights ? wave : 0];
     const bool vec = PLAIN ? f0 < f_end : a.store_vec_ok && f0 + 4 <= f_end;
-    // a finished row, or (finish = false) a piece of one that goes on in the next chunk
-    auto write_row = [&](int row, float sc, float4 v, bool finish) {
-        float *dst = c_lane + (size_t)row * a.ldc;
-        if (!PLAIN && a.accumulate) {   // later column panel: add to what the earlier panels left in C
-            if (vec) {
-                const float4 o = *reinterpret_cast<const float4 *>(dst);
-                v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
-            } else {
-                if (f0 < f_end) v.x += dst[0];
-                if (f0 + 1 < f_end) v.y += dst[1];
-                if (f0 + 2 < f_end) v.z += dst[2];
-                if (f0 + 3 < f_end) v.w += dst[3];
-            }
+    auto old_row = [&](int row) {   // later column panel: what the earlier panels left in C
+        float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+        const float *src = c_lane + (size_t)row * a.ldc;
+        if (vec) {
+            o = *reinterpret_cast<const float4 *>(src);
+        } else {
+            if (f0 < f_end) o.x = src[0];
+            if (f0 + 1 < f_end) o.y = src[1];
+            if (f0 + 2 < f_end) o.z = src[2];
+            if (f0 + 3 < f_end) o.w = src[3];
         }
+        return o;
+    };
+    auto plus = [](float4 v, const float4 &o) { v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w; return v; };
+    // a finished row, or (finish = false) a piece of one that goes on in the next chunk
+    auto store_row = [&](int row, float sc, float4 v, bool finish) {
+        float *dst = c_lane + (size_t)row * a.ldc;
         if (a.finalize && finish) {
             v.x *= sc; v.y *= sc; v.z *= sc; v.w *= sc;
             if (a.act == SENSEI_ACT_RELU) {
@@ -768,6 +781,10 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
             if (f0 + 2 < f_end) dst[2] = v.z;
             if (f0 + 3 < f_end) dst[3] = v.w;
         }
+    };
+    auto write_row = [&](int row, float sc, float4 v) {
+        if (!PLAIN && a.accumulate) v = plus(v, old_row(row));
+        store_row(row, sc, v, true);
     };
     const NnzArgs nz = {a.row_ptr, a.col_idx, a.chunk_row, a.n_rows, a.nnz, a.chunk_nnz, a.n_chunks};
     const int lo = chunk * T, hi = a.nnz - lo > T ? lo + T : a.nnz, n = hi - lo;
@@ -800,7 +817,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
         for (int b = 0; m; ++b, m >>= G) {
             if (!((m >> g) & 1ull)) continue;
             const int row = r0 + b * G + g;
-            write_row(row, MODE == SENSEI_SPMM_PATTERN && a.r ? a.r[row] : 1.f, make_float4(0.f, 0.f, 0.f, 0.f), true);
+            write_row(row, MODE == SENSEI_SPMM_PATTERN && a.r ? a.r[row] : 1.f, make_float4(0.f, 0.f, 0.f, 0.f));
         }
     };
     const bool use_scale = MODE == kSpmmSoftmax ? a.scale_weights != 0 : MODE != kSpmmAttnFused && a.r && (kWeights ? a.scale_weights != 0 : a.finalize != 0);
@@ -974,7 +991,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
                     head_row = end[q];
                     head_sc = sc[q];
                 } else {
-                    write_row(end[q], sc[q], acc, true);
+                    write_row(end[q], sc[q], acc);
                 }
                 acc = make_float4(0.f, 0.f, 0.f, 0.f);
             }
@@ -982,6 +999,12 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
         if (s + U < PART) fetch(s + U);
     }
     // a group's first row joins what the groups before it have left; the row that goes on in the next chunk is what the last group is left with
+    const bool writes_head = head_row >= 0 && head_row != cont_row, writes_open = open_row >= 0 && open_row != cont_row && g == G - 1;
+    float4 old_head = make_float4(0.f, 0.f, 0.f, 0.f), old_open = old_head;   // under way while the groups join
+    if (!PLAIN && a.accumulate) {
+        if (writes_head) old_head = old_row(head_row);
+        if (writes_open) old_open = old_row(open_row);
+    }
     int f = head_row >= 0;
 #pragma unroll
     for (int off = LPG; off < 64; off <<= 1) {
@@ -995,15 +1018,13 @@ __global__ __launch_bounds__(kBlock) void k_spmm_flat(SpmmArgs a) {
     auto write_carry = [&](const float4 &v) {
         if (fok) *reinterpret_cast<float4 *>(a.carry + (size_t)chunk * a.f_carry + f0) = v;
     };
-    if (open_row >= 0 && g == G - 1) {
-        if (open_row == cont_row) write_carry(acc);
-        else write_row(open_row, 1.f, acc, false);
-    }
+    if (writes_open) store_row(open_row, 1.f, plus(acc, old_open), false);
+    else if (open_row >= 0 && g == G - 1) write_carry(acc);
     const float4 in = make_float4(__shfl_up(acc.x, LPG, 64), __shfl_up(acc.y, LPG, 64), __shfl_up(acc.z, LPG, 64), __shfl_up(acc.w, LPG, 64));
     if (head_row >= 0) {
         if (g > 0) { head.x += in.x; head.y += in.y; head.z += in.z; head.w += in.w; }
-        if (head_row == cont_row) write_carry(head);
-        else write_row(head_row, head_sc, head, true);
+        if (writes_head) store_row(head_row, head_sc, plus(head, old_head), true);
+        else write_carry(head);
     }
 }
 
@@ -1543,10 +1564,11 @@ __device__ __forceinline__ void softmax_stats_chunk(const SoftmaxArgs &a, int ch
     const FlatChunk<PER> c = flat_rows<PER>(a.n, chunk, lane, rows, [&](int r0, bool none) { if (none) a.stats[r0 + lane] = make_float2(-INFINITY, 0.f); });
     if (c.lo >= c.hi) return;
     if (!FROM_E) {
-        int rw[PER];
+        // (row_values for all eight at once costs the pass over column panels 5 %: 335 -> 352 us on 100 M entries)
+        const bool in_lanes = c.i1 - c.i_first <= 64;
+        const float mine = in_lanes && c.i_first + lane < c.i1 ? a.s_l[c.i_first + lane] : 0.f;
 #pragma unroll
-        for (int u = 0; u < PER; ++u) rw[u] = rows[u * 64 + lane];
-        row_values<PER>(c, lane, a.s_l, rw, es);
+        for (int u = 0; u < PER; ++u) es[u] = in_lanes ? lane_read((rows[u * 64 + lane] - c.i_first) * 4, mine) : a.s_l[rows[u * 64 + lane]];
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
             es[u] = leaky(es[u] + sr[u], a.slope);
@@ -1554,29 +1576,55 @@ __device__ __forceinline__ void softmax_stats_chunk(const SoftmaxArgs &a, int ch
         }
     }
     to_blocked<PER>(val, lane, es, e);
+    // head, whole rows and tail of this lane as in flat_sum, with (max, sum of exp) pairs: the maximum over the part of a row that
+    // lies in this lane first (forwards, then handed back), then one exp per entry
     const int n_mine = c.hi - c.lo - lane * PER;   // entries of this lane inside the chunk (may be more than PER, or negative)
-    float mx[PER], p[PER];
-#pragma unroll
-    for (int q = 0; q < PER; ++q) if (q >= n_mine) e[q] = -INFINITY;
-    flat_piece_max<PER>(c, lane, e, mx);
+    float mx[PER];   // never below the lowest finite value: entries of -inf (masked out) then weigh exp(-inf) = 0, also where the lane holds no others
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-        mx[q] = fmaxf(mx[q], -FLT_MAX);   // entries of -inf (masked out) weigh exp(-inf) = 0 also where a piece holds no others
-        p[q] = q < n_mine ? __expf(e[q] - mx[q]) : 0.f;
+        if (q >= n_mine) e[q] = -INFINITY;
+        mx[q] = fmaxf((q > 0 && !((c.starts >> q) & 1u)) ? mx[q > 0 ? q - 1 : 0] : -FLT_MAX, e[q]);
     }
+#pragma unroll
+    for (int q = PER - 2; q >= 0; --q)
+        if (!((c.starts >> (q + 1)) & 1u)) mx[q] = mx[q + 1];
     auto write = [&](int i, float m, float z) {
         if (z == 0.f) m = -INFINITY;
         if (c.cont && i == c.i_first) a.carry[chunk] = make_float2(m, z);
         else a.stats[i] = make_float2(m, z);
     };
-    // every entry of a piece has its maximum: it is taken from the last one, this lane's or the lane's before
-    const float m_before = lane_before(mx[PER - 1], 0.f);
-    flat_sum<PER>(c, lane, p, [&](int i, float z, int end) {
-        float m = m_before;
+    float hm = -INFINITY, hz = 0.f, rz = 0.f;
+    bool started = false;
 #pragma unroll
-        for (int q = 0; q < PER; ++q) m = end >= lane * PER + q ? mx[q] : m;
-        write(i, m, z);
-    });
+    for (int q = 0; q < PER; ++q) {
+        if ((c.starts >> q) & 1u) {
+            const float pm = q > 0 ? mx[q > 0 ? q - 1 : 0] : -INFINITY;
+            if (started) write(c.rid[q > 0 ? q - 1 : 0], pm, rz);
+            else { hm = pm; hz = rz; }
+            started = true;
+            rz = 0.f;
+        }
+        if (q < n_mine) rz += __expf(e[q] - mx[q]);
+    }
+    float m = mx[PER - 1], z = rz;
+    int f = started;
+    // by the LDS crossbar: the pass is bound by vector instructions, which moves of three values a step would add to
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const float m2 = __shfl_up(m, off, 64), z2 = __shfl_up(z, off, 64);
+        const int of = __shfl_up(f, off, 64);
+        if (lane >= off) {
+            if (!f) mz_merge(m, z, m2, z2);
+            f |= of;
+        }
+    }
+    const float bm = __shfl_up(m, 1, 64), bz = __shfl_up(z, 1, 64);
+    const int head_row = (c.starts & 1u) ? c.prev_row : c.rid[0];
+    if (started && head_row >= 0 && lane > 0) {
+        mz_merge(hm, hz, bm, bz);
+        write(head_row, hm, hz);
+    }
+    if (lane == 63) write(c.rid[PER - 1], m, z);
 }
 
 template <bool FROM_E, int PER>
@@ -2026,7 +2074,7 @@ __device__ __forceinline__ void pair_words(const FlatChunk<PER> &c, int lane, in
 // what inner(own, column's vector, parts) leaves in each lane.  load_own(row, own) fetches the OWN vectors of a row.
 template <int PER, int OWN, int N, class LoadOwn, class Inner, class Total>
 __device__ __forceinline__ void pair_dots(const FlatChunk<PER> &c, const int *cols, const int *words, int lane, const float *other, LoadOwn load_own, Inner inner, Total total) {
-    constexpr int PART = 4 * PER;
+    constexpr int PART = 4 * PER, H = OWN == 1 ? 4 : 2;   // entries whose vectors are under way: with two of the row's, registers for two
     const int sub = lane & 3, part0 = (lane >> 2) * (PART + 4);
     const bool up = (sub & 2) != 0, odd = (sub & 1) != 0;
     Lane8 own[OWN];
@@ -2035,22 +2083,26 @@ __device__ __forceinline__ void pair_dots(const FlatChunk<PER> &c, const int *co
         const int4 c4 = *reinterpret_cast<const int4 *>(&cols[part0 + s]), w4 = *reinterpret_cast<const int4 *>(&words[part0 + s]);
         const int col[4] = {c4.x, c4.y, c4.z, c4.w};
         const int word[4] = {s > 0 ? w4.x : (int)((unsigned)w4.x | 0x80000000u), w4.y, w4.z, w4.w};   // a part begins with a row to load
-        Lane8 b[4], fresh[4][OWN];   // fresh: read where the row changes, and nowhere else written
         float d[N][4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) if (word[q] < 0) load_own(word[q] & 0x7fffffff, fresh[q]);
+        for (int h = 0; h < 4; h += H) {
+            Lane8 b[H], fresh[H][OWN];   // fresh: read where the row changes, and nowhere else written
 #pragma unroll
-        for (int q = 0; q < 4; ++q) b[q] = load8(other, col[q]);
+            for (int q = 0; q < H; ++q) if (word[h + q] < 0) load_own(word[h + q] & 0x7fffffff, fresh[q]);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (word[q] < 0) {
+            for (int q = 0; q < H; ++q) b[q] = load8(other, col[h + q]);
 #pragma unroll
-                for (int o = 0; o < OWN; ++o) own[o] = fresh[q][o];
+            for (int q = 0; q < H; ++q) {
+                if (word[h + q] < 0) {
+#pragma unroll
+                    for (int o = 0; o < OWN; ++o) own[o] = fresh[q][o];
+                }
+                float parts[N];
+                inner(own, b[q], parts);
+#pragma unroll
+                for (int n = 0; n < N; ++n) d[n][h + q] = parts[n];
             }
-            float parts[N];
-            inner(own, b[q], parts);
-#pragma unroll
-            for (int n = 0; n < N; ++n) d[n][q] = parts[n];
+            if (H < 4) __builtin_amdgcn_sched_barrier(0);
         }
         // lanes 2, 3 of the four will own entries 2, 3: they keep d[2], d[3] and receive the partner's, and hand over d[0], d[1]
         float sums[N];
@@ -2341,6 +2393,146 @@ __global__ __launch_bounds__(kBlock) void k_score_v2(ScoreV2Args a, int t0, int 
     }
 }
 
+struct V2ScoresArgs {
+    NnzArgs n;
+    const float *theta_l, *theta_r, *dP, *att;   // dP over the destinations like theta_l
+    float *logits, *dalpha;                      // out, per stored entry
+    float2 *stats, *carry_stats;                 // out, per row: (max logit, sum of exp(logit - max)) (+ per-chunk carry slots)
+    float *rowdot, *carry;                       // out, per row: sum_j alpha_ij dalpha_ij (+ per-chunk carry slots)
+    long long tl_tile, tr_tile;
+    float slope;
+};
+
+// What the backward of the GATv2 layer needs per entry, logit and <dP_i, Theta_r[j]>, from one gather of Theta_r[j], and the row's statistics and weighted sum
+// behind them.  As k_score_v2, k_softmax_stats and k_gat_dalpha these were 123 us on 3 M entries x 64 columns, with their
+// fix-ups, so 103.
+template <bool LAST, int PER>
+__global__ __launch_bounds__(kBlock) void k_v2_scores(V2ScoresArgs a, int t0, int t1) {
+    __shared__ __attribute__((aligned(16))) int s_col[kWavesPerBlock][kPairWords<PER>], s_word[kWavesPerBlock][kPairWords<PER>];
+    __shared__ __attribute__((aligned(16))) float s_e[kWavesPerBlock][kPairWords<PER>], s_d[kWavesPerBlock][kPairWords<PER>];
+    const int chunk = wave_chunk(), wave = threadIdx.x >> 6;
+    if (chunk >= a.n.n_chunks) return;
+    const int lane = threadIdx.x & 63, sub = lane & 3;
+    int *cols = s_col[wave], *words = s_word[wave];
+    float *es = s_e[wave], *ds = s_d[wave];
+    float e0[PER], d0[PER];
+    int col[PER];
+    if (a.n.nnz > 0) {
+        const ChunkSpan<PER> span(a.n, chunk);
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int k = span.at(u, lane);
+            col[u] = a.n.col_idx[k];
+            e0[u] = t0 > 0 ? a.logits[k] : 0.f;
+            d0[u] = t0 > 0 ? a.dalpha[k] : 0.f;
+        }
+    }
+    const FlatChunk<PER> c = flat_rows<PER, 4, 16>(a.n, chunk, lane, words, [&](int r0, bool none) {
+        if (LAST && none) {
+            a.stats[r0 + lane] = make_float2(-INFINITY, 0.f);
+            a.rowdot[r0 + lane] = 0.f;
+        }
+    });
+    if (c.lo >= c.hi) return;
+    pair_words<PER>(c, lane, words);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int at = pair_at<PER>(u * 64 + lane);
+        cols[at] = col[u];
+        es[at] = e0[u];
+        ds[at] = d0[u];
+    }
+    lds_exchange();
+    const float slope = a.slope;
+    auto term = [&](float wt, float x, float y) {
+        const float t = x + y;
+        return wt * (t > 0.f ? t : slope * t);
+    };
+    for (int tile = t0; tile < t1; ++tile) {
+        const float *theta_l = a.theta_l + (size_t)tile * a.tl_tile + sub * 4, *dP = a.dP + (size_t)tile * a.tl_tile + sub * 4;
+        const Lane8 w = load8(a.att + tile * 32 + sub * 4, 0);
+        pair_dots<PER, 2, 2>(c, cols, words, lane, a.theta_r + (size_t)tile * a.tr_tile + sub * 4,
+                             [&](int i, Lane8 (&own)[2]) { own[0] = load8(theta_l, i); own[1] = load8(dP, i); },
+                             [&](const Lane8 (&own)[2], const Lane8 &b, float (&parts)[2]) {
+                                 const Lane8 &p = own[0];
+                                 parts[0] = ((term(w.lo.x, p.lo.x, b.lo.x) + term(w.lo.y, p.lo.y, b.lo.y)) + (term(w.lo.z, p.lo.z, b.lo.z) + term(w.lo.w, p.lo.w, b.lo.w))) +
+                                            ((term(w.hi.x, p.hi.x, b.hi.x) + term(w.hi.y, p.hi.y, b.hi.y)) + (term(w.hi.z, p.hi.z, b.hi.z) + term(w.hi.w, p.hi.w, b.hi.w)));
+                                 parts[1] = dot8(own[1], b);
+                             },
+                             [&](int at, const float (&sums)[2]) { es[at] += sums[0]; ds[at] += sums[1]; });
+    }
+    lds_exchange();
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int at = pair_at<PER>(u * 64 + lane), k = c.lo + u * 64 + lane;
+        if (k < c.hi) {
+            a.logits[k] = es[at];
+            a.dalpha[k] = ds[at];
+        }
+    }
+    if (!LAST) return;
+    float e[PER], mx[PER], v[2][PER];
+    const int n_mine = c.hi - c.lo - lane * PER;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) e[q] = q < n_mine ? es[pair_at<PER>(lane * PER + q)] : -INFINITY;
+    flat_piece_max<PER>(c, lane, e, mx);
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        mx[q] = fmaxf(mx[q], -FLT_MAX);   // entries of -inf weigh 0 also where a piece holds no others
+        v[0][q] = q < n_mine ? expf(e[q] - mx[q]) : 0.f;
+        v[1][q] = q < n_mine ? v[0][q] * ds[pair_at<PER>(lane * PER + q)] : 0.f;
+    }
+    const float m_before = lane_before(mx[PER - 1], 0.f);   // every entry of a piece has its maximum: it is taken from the last one
+    const int last_row = __builtin_amdgcn_readfirstlane(__shfl(c.rid[PER - 1], 63, 64));
+    const bool open = __builtin_amdgcn_readfirstlane(a.n.row_ptr[last_row + 1]) > c.hi;
+    flat_sums<PER, 2>(c, lane, v, [&](int i, const float (&sum)[2], int, int last) {
+        float m = last_value<PER>(mx, m_before, last);
+        if (sum[0] == 0.f) m = -INFINITY;
+        if (c.cont && i == c.i_first) {
+            a.carry_stats[chunk] = make_float2(m, sum[0]);
+            a.carry[chunk] = sum[1];
+        } else {   // a row that goes on in the next chunk: its sum waits for the fix-up to be divided
+            a.stats[i] = make_float2(m, sum[0]);
+            a.rowdot[i] = open && i == last_row ? sum[1] : sum[1] * inv_z(sum[0]);
+        }
+    });
+}
+
+struct V2Piece { float m, z, a; };
+__device__ __forceinline__ void merge_v2(V2Piece &p, const V2Piece &q) {
+    const float m = p.m > q.m ? p.m : q.m;
+    if (m == -INFINITY) { p.m = m; return; }   // neither has entries that weigh anything
+    const float kp = expf(p.m - m), kq = expf(q.m - m);
+    p.z = p.z * kp + q.z * kq;
+    p.a = p.a * kp + q.a * kq;
+    p.m = m;
+}
+// the rows that span several chunks, their pieces in chunk order or (long rows) lane by lane and then over the lanes
+__global__ __launch_bounds__(kBlock) void k_v2_scores_fixup(V2ScoresArgs a) {
+    const int lane = threadIdx.x & 63;
+    auto load = [&](int c) { const float2 p = a.carry_stats[c]; return V2Piece{p.x, p.y, a.carry[c]}; };
+    auto finish = [&](int i, const V2Piece &rest) {
+        const float2 st = a.stats[i];
+        V2Piece p = {st.x, st.y, a.rowdot[i]};
+        merge_v2(p, rest);
+        a.stats[i] = make_float2(p.z == 0.f ? -INFINITY : p.m, p.z);
+        a.rowdot[i] = p.a * inv_z(p.z);
+    };
+    fixup_rows(a.n,
+               [&](int i, int c, int c_last) {
+                   V2Piece p = load(c);
+                   for (int cc = c + 1; cc <= c_last; ++cc) merge_v2(p, load(cc));
+                   finish(i, p);
+               },
+               [&](int i, int c, int c_last) {
+                   V2Piece p = {-INFINITY, 0.f, 0.f};
+                   for (int cc = c + lane; cc <= c_last; cc += 64) merge_v2(p, load(cc));
+#pragma unroll
+                   for (int off = 1; off < 64; off <<= 1) merge_v2(p, V2Piece{__shfl_xor(p.m, off, 64), __shfl_xor(p.z, off, 64), __shfl_xor(p.a, off, 64)});
+                   if (lane == 0) finish(i, p);
+               });
+}
+
 struct GatDtArgs {
     NnzArgs n;
     const float *logits, *dalpha, *rowdot;
@@ -2512,10 +2704,8 @@ __global__ __launch_bounds__(kBlock) void k_gat_head_rows(GatHeadArgs a) {
     const float m_before = lane_before(mx[PER - 1], 0.f);   // every entry of a piece has its maximum: it is taken from the last one
     const int last_row = __builtin_amdgcn_readfirstlane(__shfl(c.rid[PER - 1], 63, 64));
     const bool open = __builtin_amdgcn_readfirstlane(a.n.row_ptr[last_row + 1]) > c.hi;
-    flat_sums<PER, 4>(c, lane, v, [&](int i, const float (&sum)[4], int end) {
-        float m = m_before;
-#pragma unroll
-        for (int q = 0; q < PER; ++q) m = end >= lane * PER + q ? mx[q] : m;
+    flat_sums<PER, 4>(c, lane, v, [&](int i, const float (&sum)[4], int, int last) {
+        const float m = last_value<PER>(mx, m_before, last);
         const HeadPiece piece = {m, sum[0], sum[1], sum[2], sum[3]};
         const bool cont = c.cont && i == c.i_first;
         if (cont || (open && i == last_row)) {
@@ -3400,6 +3590,26 @@ hipError_t launch_score_v2(const sensei_csr &A, const float *theta_l, const floa
     return with_per(p.chunk_nnz, [&](auto per) {
         const int step = slices_a_walk(A.n_cols, n_tiles);
         for (int t = 0; t < n_tiles; t += step) hipLaunchKernelGGL(k_score_v2<per()>, grid, dim3(kBlock), 0, s, a, t, t + step < n_tiles ? t + step : n_tiles);
+    });
+}
+
+hipError_t launch_v2_scores(const sensei_csr &A, const float *theta_l, const float *theta_r, const float *dP, int f, const float *att_padded, float slope,
+                            float *logits, float *dalpha, float2 *stats, float2 *carry_stats, float *rowdot, float *carry, const ChunkPlan &p, hipStream_t s) {
+    V2ScoresArgs a;
+    a.n = nnz_args(A, p);
+    a.theta_l = theta_l; a.theta_r = theta_r; a.dP = dP; a.att = att_padded; a.logits = logits; a.dalpha = dalpha; a.slope = slope;
+    a.stats = stats; a.carry_stats = carry_stats; a.rowdot = rowdot; a.carry = carry;
+    a.tl_tile = (long long)(A.n_rows > 0 ? A.n_rows : 1) * 32;
+    a.tr_tile = (long long)(A.n_cols > 0 ? A.n_cols : 1) * 32;
+    const dim3 grid(blocks_for(p.n_chunks, kWavesPerBlock));
+    const int n_tiles = (f + 31) / 32, step = slices_a_walk(A.n_cols, n_tiles);
+    return with_per(p.chunk_nnz, [&](auto per) {
+        for (int t = 0; t < n_tiles; t += step) {
+            const int t1 = t + step < n_tiles ? t + step : n_tiles;
+            if (t1 == n_tiles) hipLaunchKernelGGL((k_v2_scores<true, per()>), grid, dim3(kBlock), 0, s, a, t, t1);
+            else hipLaunchKernelGGL((k_v2_scores<false, per()>), grid, dim3(kBlock), 0, s, a, t, t1);
+        }
+        if (p.n_chunks > 1) hipLaunchKernelGGL(k_v2_scores_fixup, dim3(blocks_for(p.n_chunks - 1, kBlock)), dim3(kBlock), 0, s, a);
     });
 }
 
