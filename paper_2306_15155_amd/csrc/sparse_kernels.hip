@@ -2063,11 +2063,13 @@ __device__ __forceinline__ float dot8(const Lane8 &a, const Lane8 &b) {
 template <int PER> constexpr int kPairWords = 64 * PER + 64;
 template <int PER> __device__ __forceinline__ int pair_at(int p) { return flat_at<PER, 4, 16>(p); }
 
-// words[pair_at(p)] = the row of entry p, sign bit: it is the first of its row in the chunk
+// words[pair_at(p)] = the row of entry p, sign bit: it is the first of its row in the chunk.  The place behind the chunk's last entry has the bit too: what
+// is read there and after it (some other entry's column) makes up a piece of its own, which no row gets.
 template <int PER>
 __device__ __forceinline__ void pair_words(const FlatChunk<PER> &c, int lane, int *words) {
+    const int end = c.hi - c.lo - lane * PER;
 #pragma unroll
-    for (int e = 0; e < PER; ++e) words[pair_at<PER>(lane * PER + e)] = (int)((unsigned)c.rid[e] | (((c.starts >> e) & 1u) << 31));
+    for (int e = 0; e < PER; ++e) words[pair_at<PER>(lane * PER + e)] = (int)((unsigned)c.rid[e] | ((((c.starts >> e) & 1u) | (e == end ? 1u : 0u)) << 31));
 }
 
 // total(at, sums) once per entry of the chunk, by the one of its four lanes that owns it (at: its place in LDS): N sums over the slice's 32 columns, of
@@ -2122,10 +2124,11 @@ __device__ __forceinline__ void pair_dots(const FlatChunk<PER> &c, const int *co
 // Sums over the rows of the chunk of what add(weights, q, own, column's vector, acc) adds per entry to NA accumulators a lane: a group of four lanes walks its
 // part as in pair_dots and closes a row (close(row, extra, acc)) where the next one starts; the first row a group closes waits for what the
 // groups before it are left with (a scan over the groups), as does its last one where it ends with the part.  weights(at) fetches what two entries weigh from
-// LDS, load_own(row, own, extra) a row's vector and one more number.  Two entries at a time: with four the registers leave three wavefronts a SIMD
+// LDS, load_own(row, own, extra) a row's vector and one more number.  The places behind the chunk's n_entries are walked like entries and left out (0 times an infinite
+// or undefined vector is no 0).  Two entries at a time: with four the registers leave three wavefronts a SIMD
 // (a training pass of four heads on 2.1 M entries 614 us, with two 589; this walk 155 us with eight lanes an entry and the own row gathered per entry, now 124).
 template <int PER, int NA, class Weights, class LoadOwn, class Add, class Close>
-__device__ __forceinline__ void pair_sums(const int *cols, const int *words, int lane, const float *other, Weights weights, LoadOwn load_own, Add add, Close close) {
+__device__ __forceinline__ void pair_sums(int n_entries, const int *cols, const int *words, int lane, const float *other, Weights weights, LoadOwn load_own, Add add, Close close) {
     constexpr int PART = 4 * PER, U = 2;
     const int g = lane >> 2, part0 = g * (PART + 4);
     float acc[NA], head[NA], extra = 0.f, head_extra = 0.f;
@@ -2170,7 +2173,7 @@ __device__ __forceinline__ void pair_sums(const int *cols, const int *words, int
             add(w, q, own, b[q], acc);
         }
     }
-    if (g == 15 || words[part0 + PART + 4] < 0) finish();
+    if (g == 15 ? n_entries == 64 * PER : words[part0 + PART + 4] < 0) finish();
     int f = head_row >= 0;
     auto step = [&](float (&x)[NA], int of) {
 #pragma unroll
@@ -2839,7 +2842,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_head_cols(GatHeadArgs a) {
     lds_exchange();
     struct W { float w[2], rd[2]; };
     pair_sums<PER, NA>(
-        cols, words, lane, dP,
+        c.hi - c.lo, cols, words, lane, dP,
         [&](int at) {
             const float2 w4 = *reinterpret_cast<const float2 *>(&alpha[at]), d4 = *reinterpret_cast<const float2 *>(&rdot[at]);
             return W{{w4.x, w4.y}, {d4.x, d4.y}};

@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 import synth
-from paper_2306_15155_amd import ACT_NONE, Context
+from paper_2306_15155_amd import ACT_NONE, Context, binding
 
 from gpu_util import DeviceCSR, assert_close, dev
 
@@ -80,3 +80,33 @@ def test_dots_and_scores(ctx, t, least, n_cols, f_out):
     want = oracle.gatv2_backward(*args, Wl, Wv, att, dY, slope=0.25)
     for gpu, ref, what in zip(ctx.gatv2_backward(A.s, At.s, pos, dev(X), dev(Wl), dev(Wv), dev(att), dev(dY), neg_slope=0.25), want, ("dX", "dW_l", "dW_r", "datt")):
         assert_close(gpu, ref, what="GATv2 " + what)
+
+
+# Places behind the last entry of the pattern are walked with the last chunk: what is read there belongs to the chunk's first entry, and must reach no result
+# also where it is no number.  Both the oracle and the call with zeros in its place say what the sources without a link to that destination get.
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+@pytest.mark.parametrize("n,per_row,heads,d", [(300, 9, 1, 32), (3_000, 50, 2, 20), (4_000, 75, 2, 32)])
+def test_no_number_behind_the_last_entry(ctx, n, per_row, heads, d, bad):
+    rng = np.random.default_rng(n)
+    last = 40   # the last sources have three links each, so that the last chunk holds several
+    dst = np.concatenate([np.repeat(np.arange(n), per_row), rng.integers(0, n, last * 3)])
+    src = np.concatenate([rng.integers(0, n - last, n * per_row), np.repeat(np.arange(n - last, n), 3)])
+    g = synth.build_csr(n, n, dst, src, False, False)
+    gt = synth.transpose(g)
+    t = min(binding.chunk_nnz(g.nnz), 256)
+    assert g.nnz % t, "the last chunk is to be a short one"
+    first = int(gt.col_idx[g.nnz // t * t])   # the destination of the last chunk's first entry
+    linked = np.zeros(n, bool)
+    linked[g.col_idx[g.row_ptr[first]:g.row_ptr[first + 1]]] = True
+    linked[first] = True
+    assert not linked[n - 1] and gt.row_ptr[n] > gt.row_ptr[n - 1]
+    X, W = synth.uniform(n, 1, (n, 20), -0.5, 0.5), synth.glorot(n, 2, 20, heads * d)
+    a_l, a_r = synth.normal(n, 3, (heads * d,), 0.0, 0.3), synth.normal(n, 4, (heads * d,), 0.0, 0.3)
+    dY = synth.normal(n, 5, (n, heads * d))
+    dY[first] = 0.0
+    want = oracle.gat_backward_heads(n, n, g.row_ptr, g.col_idx, X, W, a_l, a_r, heads, dY, slope=0.2)[0]
+    dY[first] = bad
+    A, At = DeviceCSR(g), DeviceCSR(gt)
+    dX = ctx.gat_backward_heads(A.s, At.s, ctx.transpose_positions(A.s, At.s), dev(X), dev(W), dev(a_l), dev(a_r), heads, dev(dY), neg_slope=0.2)[0].cpu().numpy()
+    assert_close(dX[~linked], want[~linked], what="dX")
+    assert not np.isfinite(dX[linked]).all()
