@@ -162,16 +162,28 @@ bool gat_is_reuse(int id) { return id == SENSEI_GAT_REUSE || id == SENSEI_GAT_RE
 // own (zero columns behind it), as many heads at a time as Theta has room for.  Passes before / now, us: inference, 8 heads of 15 columns on 1.5 M entries 928 (heads one after
 // the other) / 300, 2 of 37 on 1.1 M 451 / 255; training, 4 of 23 on 9.4 M 5,000 / 3,720, on 164,000 336 / 257.  Where Theta holds one head at a time every head costs
 // a launch more: on a small pattern they stay side by side (2 heads of 14 on 13,500 entries, training, 106 / 112).
-bool heads_padded(const sensei_csr &A, int d, int n_heads, int id) {
-    return gat_is_reuse(id) && n_heads > 1 && d % 4 != 0 && (pad32(d * n_heads) > pad32(d) || A.nnz >= (1 << 17));
+// W with the padding columns is laid out in the room of the aggregation's carry sums, which nothing else uses while Theta is formed; where it does not
+// fit (fewer chunks than input columns: the smallest patterns) the heads stay side by side too.
+bool heads_padded(const sensei_csr &A, int f_in, int d, int n_heads, int id) {
+    if (!gat_is_reuse(id) || n_heads == 1 || d % 4 == 0) return false;
+    const int fo = pad32(d * n_heads);
+    if ((size_t)f_in * fo * sizeof(float) > spmm_carry_bytes(A.nnz, fo)) return false;
+    return fo > pad32(d) || A.nnz >= (1 << 17);
 }
 
-// Heads of at most 32 columns whose Theta is slice-major are aggregated in one launch where the one-walk form is taken; at most kHeadsPerLaunch (the
-// workspace query does not know the number of heads: it makes room for as many slices as f_out fills).
+// Heads of at most 32 columns whose Theta is slice-major are aggregated in one launch where the one-walk form is taken; at most kHeadsPerLaunch.  The workspace
+// query does not know the number of heads: it makes room where f_out is a multiple of 32, for as many heads of 32 columns; padded heads of other
+// widths take what that form leaves unused (logits, statistics and scores of a single head), for as many of them as fit.
 constexpr int kHeadsPerLaunch = 16;
 int fused_heads_max(int f_out, int id) {
-    const int heads = id == SENSEI_GAT_REUSE ? pad32(f_out) / 32 : 1;
+    const int heads = f_out % 32 == 0 && id == SENSEI_GAT_REUSE ? f_out / 32 : 1;
     return heads < kHeadsPerLaunch ? heads : kHeadsPerLaunch;
+}
+// score vectors and (max, sum) pairs of h heads
+size_t fused_heads_ws(const sensei_csr &A, size_t h) {
+    const int t = choose_chunk_nnz(A.nnz);
+    return 2 * align_up(h * A.n_cols * sizeof(float), 256) + align_up(h * ((size_t)A.n_rows + 1) * sizeof(float2), 256) +
+           align_up(h * (size_t)(A.nnz > 0 ? (A.nnz + t - 1) / t : 1) * sizeof(float2), 256);
 }
 
 // scratch of the statistics pass over a column-panel copy (launch_panel_stats)
@@ -185,16 +197,10 @@ size_t gat_ws(const sensei_csr &A, int f_in, int f_out, int id) {
     const int fo = pad32(f_out), fi = pad4(f_in);
     size_t b = plan_bytes(A.nnz) + softmax_ws_bytes(A);
     b += 2 * align_up((size_t)A.n_cols * sizeof(float), 256);                  // s_l, s_r
-    if (fused_heads_max(f_out, id) > 1) {                                      // the same for every head of one slice, and (max, sum) pairs
-        const size_t h = fused_heads_max(f_out, id);
-        const int t = choose_chunk_nnz(A.nnz);
-        b += 2 * align_up(h * A.n_cols * sizeof(float), 256) + align_up(h * ((size_t)A.n_rows + 1) * sizeof(float2), 256) +
-             align_up(h * (size_t)(A.nnz > 0 ? (A.nnz + t - 1) / t : 1) * sizeof(float2), 256);
-    }
+    if (fused_heads_max(f_out, id) > 1) b += fused_heads_ws(A, fused_heads_max(f_out, id));   // the same for every head of one slice, and (max, sum) pairs
     b += align_up((size_t)(A.nnz > 0 ? A.nnz : 1) * sizeof(float), 256);       // attention logits
     b += 2 * align_up((size_t)fi * sizeof(float), 256);                        // W.a_l, W.a_r
     if (id != SENSEI_GAT_RECOMP_FOLD) b += align_up((size_t)A.n_cols * fo * sizeof(float), 256);  // Theta
-    if (gat_is_reuse(id)) b += align_up((size_t)f_in * fo * sizeof(float), 256);                  // W with padded heads
     if (A.panels) b += align_up(panel_stats_pairs(*A.panels) * sizeof(float2), 256);
     if (gat_is_reuse(id)) {
         b += spmm_carry_bytes(A.nnz, fo);
@@ -771,15 +777,16 @@ int run_gat(const sensei_csr &A, const sensei_mat &X, const sensei_mat &W, const
     float *v_r = cv.take<float>((size_t)fi);
     float *theta = nullptr;
     if (id != SENSEI_GAT_RECOMP_FOLD) theta = cv.take<float>((size_t)A.n_cols * fo);
-    const bool padded = heads_padded(A, d, n_heads, id);
+    const bool padded = heads_padded(A, f_in, d, n_heads, id);
     const int dp = padded ? pad32(d) : d;               // columns of a head in Theta
     const int per_theta = padded ? fo / dp : n_heads;   // heads that are in Theta at a time
-    float *Wp = padded ? cv.take<float>((size_t)f_in * fo) : nullptr;
+    const bool reuse = gat_is_reuse(id);
+    float *carry = cv.take<float>(spmm_carry_bytes(A.nnz, reuse ? fo : fi) / sizeof(float));
+    float *Wp = carry;   // W with padded heads: read by the product alone, before the aggregation writes its carry sums
 
     SideWork side;
     side.add_plan(A, plan);
     const bool fold = (id == SENSEI_GAT_RECOMP_FOLD || id == SENSEI_GAT_REUSE_FOLD);
-    const bool reuse = gat_is_reuse(id);
     // Theta is slice-major when the SpMM gathers from it (reuse) and a head's columns are whole 32-column slices; the
     // recompute id only projects it
     const bool theta_sliced = reuse && (n_heads == 1 || dp % 32 == 0);
@@ -794,7 +801,6 @@ int run_gat(const sensei_csr &A, const sensei_mat &X, const sensei_mat &W, const
     };
     if (theta) SENSEI_TRY(project(0));
     // recompute ids gather from X: slice-major copy once for all heads when its rows are gathered often enough
-    float *carry = cv.take<float>(spmm_carry_bytes(A.nnz, reuse ? fo : fi) / sizeof(float));
     float *U = nullptr;
     const float *x_src = X.ptr;
     bool x_sliced = false;
@@ -813,11 +819,18 @@ int run_gat(const sensei_csr &A, const sensei_mat &X, const sensei_mat &W, const
     // themselves, only the remainder's logits are stored
     const int path = attention_path(A, f_gather, reuse ? theta_sliced : x_sliced);
     const bool by_tiles = path == kAttnTiles, by_panel = path == kAttnPanels, fused = path == kAttnOneWalk;
-    const int most = std::min(fused_heads_max(f_out, id), per_theta);
+    int most = std::min(kHeadsPerLaunch, per_theta);
+    Carver hv = cv;   // where the vectors of several heads lie
+    if (padded && fused_heads_max(f_out, id) == 1) {
+        hv = Carver(stats, (size_t)(reinterpret_cast<char *>(v_l) - reinterpret_cast<char *>(stats)));
+        while (most > 1 && fused_heads_ws(A, most) > hv.cap) --most;
+    } else {
+        most = std::min(most, fused_heads_max(f_out, id));
+    }
     if (fused && theta_sliced && n_heads > 1 && dp == 32 && id == SENSEI_GAT_REUSE && most > 1) {
         // every head is a slice of Theta: projections, walk and fix-up of up to kHeadsPerLaunch heads in a launch each
-        float *hs_l = cv.take<float>((size_t)most * A.n_cols), *hs_r = cv.take<float>((size_t)most * A.n_cols);
-        float2 *h_mz = cv.take<float2>((size_t)most * (A.n_rows + 1)), *h_carry = cv.take<float2>((size_t)most * plan.n_chunks);
+        float *hs_l = hv.take<float>((size_t)most * A.n_cols), *hs_r = hv.take<float>((size_t)most * A.n_cols);
+        float2 *h_mz = hv.take<float2>((size_t)most * (A.n_rows + 1)), *h_carry = hv.take<float2>((size_t)most * plan.n_chunks);
         for (int h = 0, hb = 0; h < n_heads; h += hb) {
             const int in_theta = h % per_theta;
             hb = std::min(std::min(n_heads - h, most), per_theta - in_theta);
@@ -2770,7 +2783,7 @@ int sensei_gat_attention_path(const sensei_csr *A, int f_in, int f_out, int n_he
     if (!csr_ok(A, false) || f_in <= 0 || f_out <= 0 || n_heads < 1 || f_out % n_heads != 0 || comp_id < 0 || comp_id >= kNumGat) return -1;
     const bool reuse = gat_is_reuse(comp_id);
     const int d = f_out / n_heads;
-    const int dp = heads_padded(*A, d, n_heads, comp_id) ? pad32(d) : d;
+    const int dp = heads_padded(*A, f_in, d, n_heads, comp_id) ? pad32(d) : d;
     const bool sliced = reuse ? (n_heads == 1 || dp % 32 == 0) : relayout_pays(*A);
     return attention_path(*A, reuse ? (n_heads == 1 ? pad32(f_out) : dp) : f_in, sliced);
 }

@@ -1,14 +1,16 @@
 """Forward attention of heads whose columns do not begin at a multiple of four: they get slices of their own in Theta, as many at a time as it has room for.  One head at a
 time (patterns of 131,072 entries on; the others of 2 x 14 stay side by side), batches with one left over, heads of one slice and of two, rows long enough for the one-walk form and not, with a dense-tile split, against
 the oracle at the parity tolerance per element (fp32 sums of at most a few thousand terms of order one)."""
-import numpy as np
+import ctypes
+
 import pytest
+import torch
 
 import oracle
 import synth
 from paper_2306_15155_amd import ACT_NONE, ACT_RELU, Context, Tiles, binding, csr_struct
 
-from gpu_util import DeviceCSR, assert_close, dev, hub_and_empty_graph, rect_block
+from gpu_util import DEV, DeviceCSR, assert_close, dev, hub_and_empty_graph, rect_block
 
 pytestmark = pytest.mark.gpu
 
@@ -50,3 +52,25 @@ def test_with_tiles(ctx):
     want = oracle.gat_layer_heads(g.n_rows, g.n_cols, g.row_ptr, g.col_idx, X, W, a_l, a_r, heads, 0.2, ACT_RELU)
     for comp in (0, 3):
         assert_close(ctx.gat_layer_heads(At, dev(X), dev(W), dev(a_l), dev(a_r), heads, comp, 0.2, ACT_RELU), want, what=f"comp {comp}")
+
+
+# scratch of exactly the size that the query asks for, full of NaN before: W with its padding and the vectors of several heads lie in pieces of it that
+# other forms use
+@pytest.mark.parametrize("name", ["long", "short", "rect", "large"])
+@pytest.mark.parametrize("heads,d,f_in", [(2, 1, 36), (8, 15, 36), (4, 23, 36), (20, 31, 36), (3, 37, 36), (32, 3, 36), (5, 7, 900)])
+def test_scratch(ctx, name, heads, d, f_in):
+    g = PATTERNS[name]()
+    A = DeviceCSR(g)
+    X, W = dev(synth.uniform(7, 1, (g.n_cols, f_in), -0.5, 0.5)), dev(synth.glorot(7, 2, f_in, heads * d))
+    a_l, a_r = dev(synth.normal(7, 3, (heads * d,), 0.0, 0.3)), dev(synth.normal(7, 4, (heads * d,), 0.0, 0.3))
+    want = oracle.gat_layer_heads(g.n_rows, g.n_cols, g.row_ptr, g.col_idx, X.cpu().numpy(), W.cpu().numpy(), a_l.cpu().numpy(), a_r.cpu().numpy(), heads, 0.2,
+                                  ACT_NONE)
+    for comp in (0, 3):
+        need = ctx.gat_workspace(A.s, f_in, heads * d, comp)
+        room = torch.full((need + 1024,), 0xFF, dtype=torch.uint8, device=DEV)
+        at = -room.data_ptr() % 256
+        Y = torch.empty(g.n_rows, heads * d, device=DEV)
+        binding._check(binding.lib().sensei_gat_layer_heads(ctx._h, ctypes.byref(A.s), binding.mat_struct(X), binding.mat_struct(W), a_l.data_ptr(), a_r.data_ptr(), heads, 0.2,
+                                                            Y.data_ptr(), heads * d, ACT_NONE, comp, room.data_ptr() + at, need, binding._stream()), "sensei_gat_layer_heads")
+        assert_close(Y, want, what=f"comp {comp}")
+        assert bool((room[:at] == 0xFF).all()) and bool((room[at + need:] == 0xFF).all())

@@ -1,0 +1,25 @@
+"""Scratch that the queries ask for, on sizes alone: buffers that callers sized by these figures stay large enough."""
+import ctypes
+
+import pytest
+
+from paper_2306_15155_amd import binding
+from paper_2306_15155_amd.binding import CsrStruct
+
+
+def _csr(n_rows, n_cols, nnz):
+    A = CsrStruct()
+    A.n_rows, A.n_cols, A.nnz, A.row_ptr, A.col_idx = n_rows, n_cols, nnz, 256, 256   # the queries read no entry
+    return A
+
+
+# single heads and several (the query does not know how many), widths that are no multiple of a slice, wide inputs on small patterns
+@pytest.mark.parametrize("n_rows,n_cols,nnz,f_in,f_out,comp,most", [
+    (2_400_000, 2_400_000, 9_600_000, 128, 250, 0, 2_573_026_560), (100_000, 100_000, 2_100_000, 128, 100, 0, 67_552_256),
+    (100_000, 100_000, 2_100_000, 128, 100, 3, 67_552_256), (233_000, 233_000, 115_000_000, 602, 41, 0, 813_578_240),
+    (1_000, 5_000, 20_000, 1433, 120, 0, 3_185_408), (1_000, 5_000, 20_000, 1433, 120, 3, 3_185_408),
+    (100_000, 100_000, 2_100_000, 128, 128, 0, 74_083_840), (0, 0, 0, 16, 33, 0, 3_072)])
+def test_gat_layer(n_rows, n_cols, nnz, f_in, f_out, comp, most):
+    need = ctypes.c_size_t()
+    assert binding.lib().sensei_gat_workspace(ctypes.byref(_csr(n_rows, n_cols, nnz)), f_in, f_out, comp, ctypes.byref(need)) == 0
+    assert need.value <= most
