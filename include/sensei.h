@@ -225,7 +225,7 @@ int sensei_norm_vectors(sensei_ctx *ctx, const int32_t *deg, int64_t n, float *o
 
 /* Stored entries per chunk (= per 64-lane wavefront) that every sparse kernel uses on a pattern of `nnz` entries: 64, 128, 256
  * or 512, growing with nnz (small graphs are latency bound and get more, shorter wavefronts).  Host arithmetic; 0 if nnz < 0.
- * (The two backward walks of attention heads of at most 32 columns have shorter ones, at most 256.) */
+ * (The two backward walks of attention heads of at most 32 columns have shorter ones, at most 256, where the workspace has room for as many.) */
 int sensei_chunk_nnz(int64_t nnz);
 
 /* Which matrix-core kernel sensei_gemm (and the GEMM inside the layers) takes for an n x k by k x m product: the fp32 instruction,

@@ -1296,26 +1296,44 @@ size_t gat_bwd_ws(const sensei_csr &A, const sensei_csr *At, int f_in, int f_out
 // Heads of one slice (at most 32 columns) without tile splits: both walks of all heads in one launch each, nothing stored per entry.
 bool heads_narrow(const sensei_csr &A, const sensei_csr &At, int d) { return d <= 32 && !tiles_serve_dalpha(A, d) && !tiles_serve_transposed(At, d); }
 
-size_t narrow_bwd_ws(const sensei_csr &A, int f_in, int n_heads) {
+// The walk over the rows leaves pieces (16 floats a chunk and head) that are merged before the walk over the transposed pattern writes its carry sums.
+size_t narrow_pieces_bytes(const sensei_csr &A, int n_heads, int t) {
     const size_t h = n_heads < kHeadsPerLaunch ? n_heads : kHeadsPerLaunch;
-    const int t = choose_head_chunk_nnz(A.nnz);
+    return align_up(h * (A.nnz <= 0 ? 1 : (size_t)((A.nnz + t - 1) / t)) * 16 * sizeof(float), 256);
+}
+size_t narrow_carry_bytes(const sensei_csr &A, int n_heads, int t) {
+    const size_t h = n_heads < kHeadsPerLaunch ? n_heads : kHeadsPerLaunch, n_chunks = A.nnz <= 0 ? 1 : (size_t)((A.nnz + t - 1) / t);
+    return align_up(h * n_chunks * 32 * sizeof(float), 256) + align_up(h * n_chunks * sizeof(float), 256);
+}
+// what the walks take with chunks of t entries beside these
+size_t narrow_rest_bytes(const sensei_csr &A, int f_in, int n_heads, int t) {
+    const size_t h = n_heads < kHeadsPerLaunch ? n_heads : kHeadsPerLaunch;
     const size_t n_chunks = A.nnz <= 0 ? 1 : (size_t)((A.nnz + t - 1) / t);
     size_t b = 2 * align_up((n_chunks + 1) * sizeof(int32_t), 256) + 512;
     b += 4 * align_up(h * A.n_cols * sizeof(float), 256);                                            // s_l, s_r, ds_l, ds_r
     b += align_up(h * A.n_cols * 32 * sizeof(float), 256) + align_up(h * A.n_rows * 32 * sizeof(float), 256);   // Theta, dP
     b += align_up(h * ((size_t)A.n_rows + 1) * sizeof(float4), 256);                                 // rows
-    b += align_up(h * n_chunks * 16 * sizeof(float), 256) + align_up(h * n_chunks * 32 * sizeof(float), 256) + align_up(h * n_chunks * sizeof(float), 256);
     b += align_up((size_t)f_in * h * 32 * sizeof(float), 256);                                       // W with a slice per head
     return b + theta_t_vec_bytes(A.n_cols, (int)(h * 32));
 }
+// What the query asks for: the pattern's ordinary chunks, pieces and carry sums apart.
+size_t narrow_bwd_ws(const sensei_csr &A, int f_in, int n_heads) {
+    const int t = choose_chunk_nnz(A.nnz);
+    return narrow_rest_bytes(A, f_in, n_heads, t) + narrow_pieces_bytes(A, n_heads, t) + narrow_carry_bytes(A, n_heads, t);
+}
 
-// dTheta (row-major, ldt, head h's columns from h * d on), da_l and da_r of all heads; Wt (optional, leading dimension ldwt): W transposed
+// dTheta (row-major, ldt, head h's columns from h * d on), da_l and da_r of all heads; Wt (optional, leading dimension ldwt): W transposed.
+// The walks' own chunks are half as long as those that the query makes room for (`room` bytes of cv).  Pieces and carry sums of as many chunks lie in the slabs of dW,
+// which are written afterwards, where they fit, otherwise in one place; where that does not fit either (narrow heads on long rows: chunks are what
+// takes the room) the chunks are the ordinary ones (training passes with chunks of 256 / 512, us: 8 heads of 16 columns on 20 M entries 9,896 / 9,945, 17 of 2 on 12 M 6,721 / 6,750).
 int run_narrow_backward(const sensei_csr &A, const sensei_csr &At, const sensei_mat &X, const sensei_mat &W, const float *a_l, const float *a_r, int n_heads,
                         float slope, const float *Y, int64_t ldy, const sensei_mat &dY, int act, float *dTheta, int64_t ldt, float *da_l, float *da_r,
-                        float *Wt, int64_t ldwt, Carver cv, hipStream_t s) {
+                        float *Wt, int64_t ldwt, Carver cv, size_t room, double *slabs, size_t slab_bytes, hipStream_t s) {
     const int f_in = (int)X.cols, d = (int)W.cols / n_heads, most = n_heads < kHeadsPerLaunch ? n_heads : kHeadsPerLaunch;
     const size_t nc = A.n_cols, nr = A.n_rows;
-    const int t = choose_head_chunk_nnz(A.nnz);
+    int t = choose_head_chunk_nnz(A.nnz);
+    const bool in_slabs = std::max(narrow_pieces_bytes(A, n_heads, t), narrow_carry_bytes(A, n_heads, t)) <= slab_bytes;
+    if (narrow_rest_bytes(A, f_in, n_heads, t) + (in_slabs ? 0 : narrow_carry_bytes(A, n_heads, t)) > room) t = choose_chunk_nnz(A.nnz);
     ChunkPlan plan = make_plan(A, cv, t), plan_t = make_plan(At, cv, t);
     SideWork side;
     side.add_plan(A, plan);
@@ -1324,8 +1342,10 @@ int run_narrow_backward(const sensei_csr &A, const sensei_csr &At, const sensei_
     float *s_l = cv.take<float>(most * nc), *s_r = cv.take<float>(most * nc), *ds_l = cv.take<float>(most * nc), *ds_r = cv.take<float>(most * nc);
     float *theta = cv.take<float>(most * nc * 32), *T = cv.take<float>(most * nr * 32);
     float4 *row = cv.take<float4>(most * (nr + 1));
-    float *piece = cv.take<float>((size_t)most * plan.n_chunks * 16);
-    float *carry = cv.take<float>((size_t)most * plan_t.n_chunks * 32), *ds_carry = cv.take<float>((size_t)most * plan_t.n_chunks);
+    Carver in = in_slabs ? Carver(slabs, slab_bytes) : cv;
+    float *carry = in.take<float>((size_t)most * plan_t.n_chunks * 32), *ds_carry = in.take<float>((size_t)most * plan_t.n_chunks);
+    float *piece = carry;
+    if (!in_slabs) cv = in;
     float *Wp = cv.take<float>((size_t)f_in * most * 32);
     double *part_a = cv.take<double>(theta_t_vec_bytes(A.n_cols, most * 32) / sizeof(double));
     for (int h = 0; h < n_heads; h += most) {
@@ -1367,7 +1387,7 @@ int run_gat_backward(const sensei_csr &A, const sensei_csr &At, const int32_t *t
         float *dTheta = cv.take<float>((size_t)A.n_cols * fo4), *Wt = cv.take<float>((size_t)fo4 * fi4);
         double *part = cv.take<double>(gemm_tn_bytes(A.n_cols, f_in, f_out) / sizeof(double));
         const int rc = run_narrow_backward(A, At, X, W, a_l, a_r, 1, slope, Y, ldy, dY, act, dTheta, fo4, da_l, da_r, dX ? Wt : nullptr, fi4,
-                                           cv, s);
+                                           cv, gat_bwd_ws(A, &At, f_in, f_out) - cv.used, part, gemm_tn_bytes(A.n_cols, f_in, f_out), s);
         if (rc != SENSEI_OK) return rc;
         SENSEI_TRY(launch_gemm_tn(X.ptr, X.ld, dTheta, fo4, A.n_cols, f_in, f_out, dW, lddw, part, s));
         if (dX) SENSEI_TRY(launch_gemm(dTheta, fo4, Wt, fi4, dX, lddx, A.n_cols, f_out, f_in, f_in, SENSEI_ACT_NONE, s));
@@ -1506,7 +1526,8 @@ int run_gat_backward_heads(const sensei_csr &A, const sensei_csr &At, const int3
     double *part = cv.take<double>(gemm_tn_bytes(A.n_cols, f_in, f_out) / sizeof(double));
     if (heads_narrow(A, At, d)) {
         const int rc = run_narrow_backward(A, At, X, W, a_l, a_r, n_heads, slope, Y, ldy, dY, act, dTh, fo4, da_l, da_r, dX ? Wt : nullptr,
-                                           fi4, cv, s);
+                                           fi4, cv, std::max(gat_bwd_ws(A, &At, f_in, d), narrow_bwd_ws(A, f_in, n_heads)), part,
+                                           gemm_tn_bytes(A.n_cols, f_in, f_out), s);
         if (rc != SENSEI_OK) return rc;
         SENSEI_TRY(launch_gemm_tn(X.ptr, X.ld, dTh, fo4, A.n_cols, f_in, f_out, dW, lddw, part, s));
         if (dX) SENSEI_TRY(launch_gemm(dTh, fo4, Wt, fi4, dX, lddx, A.n_cols, f_out, f_in, f_in, SENSEI_ACT_NONE, s));

@@ -3216,18 +3216,6 @@ hipError_t with_per(int chunk_nnz, F f) {
     return hipGetLastError();
 }
 
-// for chunks of choose_head_chunk_nnz
-template <class F>
-hipError_t with_head_per(int chunk_nnz, F f) {
-    switch (chunk_nnz) {
-        case 64: f(std::integral_constant<int, 1>()); break;
-        case 128: f(std::integral_constant<int, 2>()); break;
-        case 256: f(std::integral_constant<int, 4>()); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
 NnzArgs nnz_args(const sensei_csr &A, const ChunkPlan &p) {
     NnzArgs n;
     n.row_ptr = A.row_ptr; n.col_idx = A.col_idx; n.chunk_row = p.chunk_row;
@@ -3715,13 +3703,13 @@ hipError_t launch_gat_heads_backward(const sensei_csr &A, const ChunkPlan &p, co
     a.n_src = A.n_cols; a.n_dst = A.n_rows; a.ldd = b.ldd; a.d = b.d; a.slope = b.slope;
     a.store_vec_ok = b.ldd % 4 == 0 && b.d % 4 == 0 && reinterpret_cast<uintptr_t>(b.dtheta) % 16 == 0;
     const unsigned heads = (unsigned)b.heads;
-    hipError_t e = with_head_per(p.chunk_nnz, [&](auto per) {
+    hipError_t e = with_per(p.chunk_nnz, [&](auto per) {
         hipLaunchKernelGGL(k_gat_head_rows<per()>, dim3(blocks_for(p.n_chunks, kWavesPerBlock), heads), dim3(kBlock), 0, s, a);
         if (p.n_chunks > 1) hipLaunchKernelGGL(k_gat_head_fixup, dim3(blocks_for(p.n_chunks - 1, kBlock), heads), dim3(kBlock), 0, s, a);
     });
     if (e != hipSuccess) return e;
     a.n = nnz_args(At, pt);
-    return with_head_per(pt.chunk_nnz, [&](auto per) {
+    return with_per(pt.chunk_nnz, [&](auto per) {
         hipLaunchKernelGGL(k_gat_head_cols<per()>, dim3(blocks_for(pt.n_chunks, kWavesPerBlock), heads), dim3(kBlock), 0, s, a);
         if (pt.n_chunks > 1)
             hipLaunchKernelGGL(k_gat_head_cols_fixup, dim3(blocks_for(pt.n_chunks - 1, kWavesPerBlock * 8), heads), dim3(kBlock), 0, s, a);

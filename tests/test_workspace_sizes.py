@@ -23,3 +23,14 @@ def test_gat_layer(n_rows, n_cols, nnz, f_in, f_out, comp, most):
     need = ctypes.c_size_t()
     assert binding.lib().sensei_gat_workspace(ctypes.byref(_csr(n_rows, n_cols, nnz)), f_in, f_out, comp, ctypes.byref(need)) == 0
     assert need.value <= most
+
+
+# many narrow heads on long rows, where the walks' own chunks would take more than there was room for; 4 heads of a slice on ordinary rows
+@pytest.mark.parametrize("n_rows,n_cols,nnz,f_in,f_out,heads,most", [
+    (40_571, 40_571, 14_892_209, 8, 34, 17, 292_005_632), (20_000, 60_000, 9_000_000, 36, 384, 16, 364_032_256),
+    (50_000, 50_000, 30_000_000, 64, 512, 16, 734_928_640), (100_000, 100_000, 2_100_000, 128, 128, 4, 271_493_376)])
+def test_gat_backward_heads(n_rows, n_cols, nnz, f_in, f_out, heads, most):
+    need = ctypes.c_size_t()
+    A, At = _csr(n_rows, n_cols, nnz), _csr(n_cols, n_rows, nnz)
+    assert binding.lib().sensei_gat_backward_heads_workspace(ctypes.byref(A), ctypes.byref(At), f_in, f_out, heads, ctypes.byref(need)) == 0
+    assert need.value <= most
