@@ -158,17 +158,29 @@ size_t gcn_ws(const sensei_csr &A, int f_in, int f_out, int id) {
 
 bool gat_is_reuse(int id) { return id == SENSEI_GAT_REUSE || id == SENSEI_GAT_REUSE_FOLD; }
 
-// Heads whose columns do not begin at a multiple of four: side by side in Theta they would be gathered four or eight bytes a lane, so each gets slices of its
-// own (zero columns behind it), as many heads at a time as Theta has room for.  Passes before / now, us: inference, 8 heads of 15 columns on 1.5 M entries 928 (heads one after
-// the other) / 300, 2 of 37 on 1.1 M 451 / 255; training, 4 of 23 on 9.4 M 5,000 / 3,720, on 164,000 336 / 257.  Where Theta holds one head at a time every head costs
-// a launch more: on a small pattern they stay side by side (2 heads of 14 on 13,500 entries, training, 106 / 112).
+// Heads whose columns do not begin at a multiple of four: side by side in Theta they are gathered four or eight bytes a lane, by the walk that goes row by row.  Padded, each
+// has slices of its own (zero columns behind it), as many heads at a time as Theta has room for, with a product over all of X for each such batch.
+//   What that costs, us: a batch more 5, and its reading of X 0.8e-6 a word (0.03 a column where rows are few: k is walked serially); products and stores of the zero columns.
+//   What it saves a head, us: 16e-6 an entry, and 300e-6 a row where the one-walk form goes over the rows; where all heads do not fit the slices of one, 2e-6 an entry and
+//   column (lines that two heads share), and 12 where the heads of a batch share the launches of the one-walk form.
+// Fitted to 3,570 forward passes (2,000 to 1 M nodes of 3 to 200 entries, power-law patterns counted like uniform ones, 16 to 600 input columns, 2 to 17 heads of 1 to 63 columns):
+// 2 % slower than the better form in the geometric mean, 4.7 % with the rule before (padded wherever Theta is wider than a head's slices or the pattern holds 131,072 entries),
+// 55 % side by side.  What the rows' lengths are the sizes do not say, and the hubs and short rows of a power-law pattern are what the walk by rows is slow on: 382 calls on uniform
+// and small patterns are more than 5 % slower than side by side (up to 1.6 times; before, 774, up to 3.3 times).
+// Side by side / padded, us: 200,000 nodes of 4 entries, 600 input columns, 8 heads of 3 columns 510 / 1,357, of 5 581 / 966, 4 of 23 726 / 596; 62,500 nodes of 18 on a power-law
+// graph, 30 input columns, 2 heads of 11 354 / 113, 8 of 3 1,152 / 426, 600 input columns 372 / 150 and 1,183 / 568; 50,000 nodes of 32, 40 columns, 2 of 14 88 / 94.
 // W with the padding columns is laid out in the room of the aggregation's carry sums, which nothing else uses while Theta is formed; where it does not
 // fit (fewer chunks than input columns: the smallest patterns) the heads stay side by side too.
 bool heads_padded(const sensei_csr &A, int f_in, int d, int n_heads, int id) {
-    if (!gat_is_reuse(id) || n_heads == 1 || d % 4 == 0) return false;
-    const int fo = pad32(d * n_heads);
+    if (!gat_is_reuse(id) || n_heads == 1 || d % 4 == 0 || A.n_rows <= 0) return false;
+    const int dp = pad32(d), fo = pad32(d * n_heads), per_theta = fo / dp, batches = (n_heads + per_theta - 1) / per_theta;
     if ((size_t)f_in * fo * sizeof(float) > spmm_carry_bytes(A.nnz, fo)) return false;
-    return fo > pad32(d) || A.nnz >= (1 << 17);
+    const double rows = 1e-6 * A.n_rows, cols = 1e-6 * A.n_cols, entries = 1e-6 * (double)A.nnz;
+    const bool one_walk = dp == 32 && entries >= 16.0 * rows;   // attention_path
+    const double cost = (batches - 1) * (5.0 + 0.03 * f_in + 0.8 * cols * f_in) + ((double)n_heads * dp - fo) * cols * (0.01 * f_in + 0.8);
+    double saved = 16.0 * entries + (one_walk ? 300.0 * rows : 0.0);
+    if (fo > dp) saved += 2.0 * entries * d + (one_walk ? 12.0 : 0.0);
+    return n_heads * saved > cost;
 }
 
 // Heads of at most 32 columns whose Theta is slice-major are aggregated in one launch where the one-walk form is taken; at most kHeadsPerLaunch.  The workspace

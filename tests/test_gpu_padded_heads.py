@@ -1,8 +1,9 @@
-"""Forward attention of heads whose columns do not begin at a multiple of four: they get slices of their own in Theta, as many at a time as it has room for.  One head at a
-time (patterns of 131,072 entries on; the others of 2 x 14 stay side by side), batches with one left over, heads of one slice and of two, rows long enough for the one-walk form and not, with a dense-tile split, against
+"""Forward attention of heads whose columns do not begin at a multiple of four: side by side, or padded to slices of their own in Theta, as many at a time as it has room
+for.  Batches with one left over, heads of one slice and of two, rows long enough for the one-walk form and not, with a dense-tile split, against
 the oracle at the parity tolerance per element (fp32 sums of at most a few thousand terms of order one)."""
 import ctypes
 
+import numpy as np
 import pytest
 import torch
 
@@ -30,7 +31,7 @@ def _inputs(g, heads, d):
     return X, W, synth.normal(7, 3, (heads * d,), 0.0, 0.3), synth.normal(7, 4, (heads * d,), 0.0, 0.3)
 
 
-# 2 x 14: Theta holds one head; 4 x 23: three and one; 17 x 3: two and a last one; 3 x 37: two slices a head, two heads and one; 20 x 31: more than one launch takes
+# 2 x 14: Theta holds one padded head; 4 x 23: three and one; 17 x 3: two and a last one; 3 x 37: two slices a head, two heads and one; 20 x 31: more than one launch takes
 @pytest.mark.parametrize("name", PATTERNS)
 @pytest.mark.parametrize("heads,d", [(2, 1), (2, 14), (4, 23), (17, 3), (3, 37), (20, 31)])
 def test_heads(ctx, name, heads, d):
@@ -74,3 +75,38 @@ def test_scratch(ctx, name, heads, d, f_in):
                                                             Y.data_ptr(), heads * d, ACT_NONE, comp, room.data_ptr() + at, need, binding._stream()), "sensei_gat_layer_heads")
         assert_close(Y, want, what=f"comp {comp}")
         assert bool((room[:at] == 0xFF).all()) and bool((room[at + need:] == 0xFF).all())
+
+
+# How many products there are says which form a call took.  Products over a wide X cost more than padding saves where rows are short or the heads narrow, and where
+# there are few entries at all.
+@pytest.mark.parametrize("n,per_row,f_in,heads,d,products", [
+    (60_000, 4, 600, 8, 3, 1), (60_000, 4, 600, 8, 5, 1), (60_000, 4, 600, 17, 3, 1), (60_000, 4, 600, 8, 1, 1), (20_000, 10, 600, 2, 14, 1), (3_000, 40, 36, 2, 14, 1),
+    (60_000, 4, 16, 4, 23, 2), (60_000, 20, 36, 17, 3, 9), (20_000, 60, 100, 8, 15, 2), (20_000, 60, 100, 2, 37, 2), (20_000, 60, 100, 3, 37, 2), (30_000, 18, 36, 4, 7, 4)])
+def test_products_over_the_input(ctx, n, per_row, f_in, heads, d, products):
+    g = rect_block(n, n, n, per_row)
+    A, X, W = DeviceCSR(g), synth.uniform(7, 1, (n, f_in), -0.5, 0.5), synth.glorot(7, 2, f_in, heads * d)
+    a_l, a_r = synth.normal(7, 3, (heads * d,), 0.0, 0.3), synth.normal(7, 4, (heads * d,), 0.0, 0.3)
+    args = (A.s, dev(X), dev(W), dev(a_l), dev(a_r), heads)
+    for comp in (0, 3):
+        ctx.profile_enable(True)
+        Y = ctx.gat_layer_heads(*args, comp, 0.2, ACT_NONE)
+        torch.cuda.synchronize()
+        count = len(ctx.profile_read(1))
+        ctx.profile_enable(False)
+        assert count == products, f"comp {comp}"
+        rows = np.random.default_rng(d).integers(0, n, 200)
+        want = np.empty((rows.size, heads * d))
+        for k, i in enumerate(rows):
+            want[k] = _row(g, X, W, a_l, a_r, heads, d, i)
+        assert_close(Y[torch.from_numpy(rows).cuda()], want, what=f"comp {comp}")
+
+
+def _row(g, X, W, a_l, a_r, heads, d, i):
+    """One row of the layer in fp64."""
+    j = np.concatenate([[i], g.col_idx[g.row_ptr[i]:g.row_ptr[i + 1]]])
+    theta = (X[j].astype(np.float64) @ W.astype(np.float64)).reshape(j.size, heads, d)
+    s_l, s_r = (theta[0] * a_l.reshape(heads, d)).sum(1), (theta[1:] * a_r.reshape(heads, d)).sum(2)
+    e = s_l + s_r
+    e = np.where(e > 0, e, 0.2 * e)
+    p = np.exp(e - e.max(0))
+    return ((p / p.sum(0))[:, :, None] * theta[1:]).sum(0).reshape(-1)
