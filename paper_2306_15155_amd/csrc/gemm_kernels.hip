@@ -2052,14 +2052,29 @@ hipError_t launch_gemv2(const float *A, int64_t lda, int64_t n, int k, const flo
     return hipGetLastError();
 }
 
-// Slabs: as many workgroups as the chip holds at once, one a compute unit (two of the 64-column kernel's), and not one more: the slab sums are 128 KB a block
-// in fp64, written and read again, and the workgroups that did not fit ran in a round of their own.  With 256 / 512 / 768 workgroups (twice as many
+// Slabs: as many workgroups as the chip holds at once, one a compute unit (two of the 64-column kernel's): the slab sums are 128 KB a block in fp64,
+// written and read again, and the workgroups that did not fit ran in a round of their own.  With 256 / 512 / 768 workgroups (twice as many
 // of the 64-column kernel), training passes, us: four heads on 100,000 nodes 570 / 575 / 592, GATv2 on 50,000 601 / 619 / 631, K-hop on 100,000 390 / 402 / 421, two layers on
 // 233,000 8,580 / 8,549 / 8,584.
+// Where that leaves an eighth of the chip idle (from 86 blocks on a whole number of slabs seldom fills it) as many slabs, up to three rounds of them, as make the rounds
+// shortest: a round is a slab's rows at 59 ns (a block of 128 x 128), a slab more its sums at 5 TB/s.  dW of 1,433 x 1,433 over 50,000 rows (144 blocks) with 1 / 2 / 3 / 5 / 6
+// slabs 2,957 / 3,188 / 2,277 / 2,146 / 2,305 us, of 1,433 x 1,000 (96) with 2 / 3 / 5 / 8 1,547 / 1,984 / 1,358 / 1,325, of 1,280 x 1,100 over 20,000 (90) with 2 / 5 / 8 / 9 634 / 557 /
+// 553 / 623; 3,703 x 500 (116 blocks, nine tenths of the chip) with 2 / 4 / 6 661 / 660 / 674.
 int gemm_tn_splits(int64_t k, int m, int n, int segs) {
     const long long tiles = (long long)((m + 127) / 128) * ((n + 127) / 128) * segs;
-    // below 4,096 rows the fp32 kernel runs, three workgroups a compute unit
-    long long s = k < 4096 ? (768 + tiles - 1) / tiles : (n <= 64 ? 512 : 256) / tiles;
+    const long long most = (768 + tiles - 1) / tiles;   // below 4,096 rows the fp32 kernel runs, three workgroups a compute unit
+    long long s = most;
+    if (k >= 4096) {
+        const long long slots = n <= 64 ? 512 : 256;
+        auto rounds = [&](long long c) { return (c * tiles + slots - 1) / slots; };
+        s = slots / tiles > 1 ? slots / tiles : 1;
+        if (8 * s * tiles < 7 * rounds(s) * slots) {
+            const double sums = 16.0 * m * n * segs / 5e12, rows = 59e-9 * (double)k;
+            auto time = [&](long long c) { return rows * (double)rounds(c) / (double)c + sums * (double)c; };
+            for (long long c = s + 1; c <= most; ++c)
+                if (time(c) < time(s)) s = c;
+        }
+    }
     const long long max_s = (k + 4 * KT - 1) / (4 * KT);  // at least four k-tiles per slab
     if (s > max_s) s = max_s;
     return (int)(s < 1 ? 1 : s);

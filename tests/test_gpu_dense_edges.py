@@ -54,7 +54,9 @@ def test_gemm_beside_the_small_kernel(n, k, m, pad):
 # the weight gradient of a layer on the identity pattern is X^T dY: around the 64 columns that choose the narrow block, the 128 x 64 block's
 # edges, odd leading dimensions and row counts that leave a ragged last slab.  Slabs of 32 rows are summed in fp32 (six products a term),
 # everything after that in fp64.
-@pytest.mark.parametrize("n,f_in,f_out", [(4096, 1, 1), (4097, 100, 47), (5003, 128, 64), (4999, 129, 63), (6000, 130, 65), (20_001, 33, 32)])
+# The last three: 90 and 144 blocks of 128 x 128, for which the slabs of one round leave a part of the chip idle, and more blocks than compute units.
+@pytest.mark.parametrize("n,f_in,f_out", [(4096, 1, 1), (4097, 100, 47), (5003, 128, 64), (4999, 129, 63), (6000, 130, 65), (20_001, 33, 32), (4099, 1280, 1100),
+                                          (4097, 1433, 1433), (4096, 2200, 2200)])
 def test_weight_gradient_columns(n, f_in, f_out):
     from paper_2306_15155_amd import Context, csr_struct
     ctx = Context(0)

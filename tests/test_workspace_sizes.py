@@ -34,3 +34,12 @@ def test_gat_backward_heads(n_rows, n_cols, nnz, f_in, f_out, heads, most):
     A, At = _csr(n_rows, n_cols, nnz), _csr(n_cols, n_rows, nnz)
     assert binding.lib().sensei_gat_backward_heads_workspace(ctypes.byref(A), ctypes.byref(At), f_in, f_out, heads, ctypes.byref(need)) == 0
     assert need.value <= most
+
+
+# the slabs of a weight gradient of 144, 96 and 324 blocks: at least as many as fill three quarters of the rounds that they take, no more than there was room for
+@pytest.mark.parametrize("n,f_in,f_out,least,most", [(50_000, 1433, 1433, 643_000_000, 692_632_832), (20_000, 1433, 1000, 231_000_000, 265_786_624),
+                                                     (20_000, 2300, 2300, 529_000_000, 529_250_816), (233_000, 602, 256, 0, 512_369_408)])
+def test_gcn_backward(n, f_in, f_out, least, most):
+    need = ctypes.c_size_t()
+    assert binding.lib().sensei_gcn_backward_workspace(ctypes.byref(_csr(n, n, 4 * n)), f_in, f_out, 0, ctypes.byref(need)) == 0
+    assert least <= need.value <= most
