@@ -134,3 +134,20 @@ def test_scratch_of_narrow_heads(ctx, n, per_row, heads, d):
     for got, ref, what in zip(outs, want, ("dX", "dW", "da_l", "da_r")):
         assert_close(got, ref, what=what)
     assert bool((room[:at] == 0xFF).all()) and bool((room[at + need:] == 0xFF).all())
+
+
+# Products with the slope are not rounded before they are added.  Row i has the sources i and m + i; Theta_l is 0, Theta_r (X is the identity) is (1, -1) and (-1, 1) in
+# the two columns that `att` reads with ones, so that both logits are 1 - slope, both coefficients 1/2, dalpha u and -u, and dTheta_l[i, 0] the sum of u / 2 and
+# -u / 2 times the slope: one rounding.  dW_l is dTheta_l.
+@pytest.mark.parametrize("m,f_out", [(300, 8), (1_000, 40)])
+def test_products_with_the_slope_are_not_rounded(ctx, m, f_out):
+    g = synth.CSR(m, 2 * m, (2 * np.arange(m + 1)).astype(np.int32), np.stack([np.arange(m), m + np.arange(m)], 1).reshape(-1).astype(np.int32))
+    A, At = DeviceCSR(g), DeviceCSR(synth.transpose(g))
+    W_l, W_r = np.zeros((2 * m, f_out), np.float32), np.zeros((2 * m, f_out), np.float32)
+    W_r[:m, :2], W_r[m:, :2] = (1.0, -1.0), (-1.0, 1.0)
+    att, dY = np.zeros(f_out, np.float32), np.zeros((m, f_out), np.float32)
+    att[:2] = 1.0
+    dY[:, 0] = synth.uniform(11, 1, (m,), 0.5, 1.0)
+    dW_l = ctx.gatv2_backward(A.s, At.s, ctx.transpose_positions(A.s, At.s), torch.eye(2 * m, device="cuda"), dev(W_l), dev(W_r), dev(att), dev(dY), neg_slope=0.7)[1]
+    u, slope = dY[:, 0].astype(np.float64), np.float64(np.float32(0.7))
+    assert np.array_equal(dW_l[:m, 0].cpu().numpy(), (u / 2 - u / 2 * slope).astype(np.float32))
