@@ -25,7 +25,7 @@ def pattern(t, least, n_cols):
     part = t // 16
     head = [part] * 16 + [1] * (part - 1) + [part + 1] + [part - 1 or 1, 1] * 7 + [t, t + part, 1, 0, t - part, 3 * t + 1, 0] + [1] * t + [5 * part] * 5
     rng = np.random.default_rng(t)
-    tail = rng.integers(0, 40, max(least - sum(head), 0) // 20 + 2)
+    tail = rng.integers(0, 40, max(least - sum(head), 0) // 19 + 50)   # 19.5 on average
     lens = np.minimum(np.concatenate([head, tail]), n_cols).astype(np.int64)
     row_ptr = np.concatenate([[0], np.cumsum(lens)])
     row = np.repeat(np.arange(lens.size), lens)
@@ -35,13 +35,12 @@ def pattern(t, least, n_cols):
     return synth.CSR(lens.size, max(n_cols, lens.size), row_ptr.astype(np.int32), col.astype(np.int32))
 
 
-CHUNKS = [(64, 3_000), (128, 140_000), (256, 270_000), (512, 530_000)]
-
-
-@pytest.mark.parametrize("t,least", CHUNKS)
+# (the walks of narrow heads have chunks of at most 256 entries)
+@pytest.mark.parametrize("t,least", [(64, 3_000), (128, 140_000), (256, 270_000), (256, 530_000)])
 @pytest.mark.parametrize("heads,d", [(2, 12), (1, 32)])
 def test_narrow_heads(ctx, t, least, heads, d):
     g = pattern(t, least, 4_000)
+    assert min(binding.chunk_nnz(g.nnz), 256) == t and g.nnz >= least
     X, W = synth.uniform(t, 1, (g.n_cols, 20), -0.5, 0.5), synth.glorot(t, 2, 20, heads * d)
     a_l, a_r = synth.normal(t, 3, (heads * d,), 0.0, 0.3), synth.normal(t, 4, (heads * d,), 0.0, 0.3)
     # every score well away from zero, where the derivative jumps: feature 0 is +-1 and only a_r sees it
@@ -57,9 +56,11 @@ def test_narrow_heads(ctx, t, least, heads, d):
 
 
 # the dot products (keys of 40 columns, values of 33 to 96) and the scores behind them; 100,000 sources of 96 columns are past the size that one launch takes whole
-@pytest.mark.parametrize("t,least,n_cols,f_out", [(64, 3_000, 4_000, 33), (128, 140_000, 4_000, 96), (256, 270_000, 100_000, 96), (512, 530_000, 4_000, 70)])
+@pytest.mark.parametrize("t,least,n_cols,f_out", [(64, 3_000, 4_000, 33), (128, 140_000, 4_000, 96), (256, 270_000, 100_000, 96), (512, 530_000, 4_000, 70),
+                                                  (512, 530_000, 100_000, 96)])
 def test_dots_and_scores(ctx, t, least, n_cols, f_out):
     g = pattern(t, least, n_cols)
+    assert binding.chunk_nnz(g.nnz) == t
     f_in, d_k = 12, 40
     X = np.round(synth.uniform(t, 1, (g.n_cols, f_in), -1.0, 1.0) * 8) / 8   # on a grid: the projections are exact, the score's derivative jumps on both sides alike
     Wq, Wk, Wv = (np.round(synth.uniform(t, 2 + i, (f_in, w), -0.5, 0.5) * 16) / 16 for i, w in enumerate((d_k, d_k, f_out)))
