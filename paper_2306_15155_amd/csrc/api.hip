@@ -750,8 +750,8 @@ int run_tagcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r
 }
 
 // n_heads > 1: W holds the heads side by side (head h = columns [h d, (h + 1) d), d = f_out / n_heads), a_l / a_r likewise,
-// Y is their concatenation; Theta = X.W is formed by one GEMM for all heads, everything after it runs head by head on the
-// head's columns (its own logits, statistics and aggregation), reusing the same buffers.
+// Y is their concatenation; Theta = X.W is formed by one GEMM for all heads (for a batch of heads where they are padded: heads_padded), everything after
+// it runs head by head on the head's columns (its own logits, statistics and aggregation), reusing the same buffers; heads of one slice share launches.
 // How the attention part of a GAT layer call runs (sensei_gat_attention_path reports it):
 //   tiles: statistics and aggregation split into dense tiles and remainder; panels: two passes, the logits stored in panel order;
 //   one walk: score, running-maximum softmax and weighted sum fused in the aggregation kernel (no stored logits, no statistics

@@ -232,7 +232,7 @@ hipError_t launch_theta_t_vec(const float *theta_sliced, int64_t n, int f, const
 // null v_l: column sums; null v_r: out_r is not written.  n_heads > 1: heads of f / n_heads columns, a pair of vectors each, n floats apart; Theta holds one slice a head
 // Backward of attention heads of d <= 32 columns, slice h of theta (n_cols rows) and dP (n_rows rows) being head h's: ds_l, ds_r (n_cols floats a head)
 // and dtheta (row-major, head h's columns from h * d on).  Scratch: row n_rows float4 a head, piece 16 floats a head and chunk
-// of A, carry 32 floats and ds_carry one a head and chunk of At.
+// of A, carry 32 floats and ds_carry one a head and chunk of At (piece is not read any more when these are written: they may share a place).
 struct GatHeadsBackward {
     const float *theta, *dP, *s_l, *s_r;   // s_l, s_r: n_cols floats a head
     const float *a_l, *a_r;                // d floats a head
