@@ -114,6 +114,8 @@ struct Carver {
     }
 };
 
+Slabs take_slabs(Carver &cv, size_t bytes) { return {cv.take<double>(bytes / sizeof(double)), bytes}; }
+
 bool relayout_pays(const sensei_csr &A);
 
 // room for a slice-major copy of the gathered matrix of the stand-alone SpMM, where it pays
@@ -568,7 +570,7 @@ int run_gcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r, 
         float *carry = cv.take<float>(spmm_carry_bytes(At.nnz, pad32(f_out)) / sizeof(float));
         float *T = cv.take<float>((size_t)A.n_rows * pad32(f_out));
         float *G = cv.take<float>((size_t)A.n_cols * fo4);
-        double *part = cv.take<double>(gemm_tn_bytes(A.n_cols, f_in, f_out) / sizeof(double));
+        const Slabs part = take_slabs(cv, gemm_tn_bytes(A.n_cols, f_in, f_out));
         float *Wt = dX ? cv.take<float>((size_t)f_out * pad4(f_in)) : nullptr;
         if (dX) side.add_transpose(W.ptr, W.ld, f_in, f_out, Wt, pad4(f_in));
         // T = r (x) (dY (.) mask), slice-major: what the transposed SpMM gathers from
@@ -593,7 +595,7 @@ int run_gcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r, 
         const int fo4 = pad4(f_out), fi4 = pad4(f_in), fi32 = pad32(f_in);
         float *carry = cv.take<float>(spmm_carry_bytes(A.nnz, fi32) / sizeof(float));
         float *dP = cv.take<float>((size_t)A.n_rows * fo4);
-        double *part = cv.take<double>(gemm_tn_bytes(A.n_rows, f_in, f_out) / sizeof(double));
+        const Slabs part = take_slabs(cv, gemm_tn_bytes(A.n_rows, f_in, f_out));
         ChunkPlan plan;
         if (!U_saved) {
             plan = make_plan(A, cv);
@@ -695,7 +697,7 @@ int run_tagcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r
         float *Q = cv.take<float>((size_t)n * ldq);
         float *S = cv.take<float>((size_t)n * fo32);
         float *Wst = cv.take<float>((size_t)ldq * fi4);
-        double *part = cv.take<double>(gemm_tn_bytes(n, f_in, f_out, k_hops + 1) / sizeof(double));
+        const Slabs part = take_slabs(cv, gemm_tn_bytes(n, f_in, f_out, k_hops + 1));
         // the pad columns enter the GEMM below: those of Q_0 are cleared here, the propagations write the others (S has zeros there)
         if (fo4 != f_out) SENSEI_TRY(launch_zero_matrix(Q + f_out, n, fo4 - f_out, ldq, false, s));
         SENSEI_TRY(launch_row_broadcast(nullptr, dY.ptr, dY.ld, n, f_out, Q, ldq, SENSEI_ACT_NONE, s, mask, ldy, &side));
@@ -720,7 +722,7 @@ int run_tagcn_backward(const sensei_csr &A, const sensei_csr &At, const float *r
     float *H = cv.take<float>((size_t)n * fi4);
     float *T = cv.take<float>((size_t)n * fi32), *P = cv.take<float>((size_t)n * fi32);
     float *Wt = cv.take<float>((size_t)(k_hops + 1) * fo4 * fi4);
-    double *part = cv.take<double>(gemm_tn_bytes(n, f_in, f_out) / sizeof(double));
+    const Slabs part = take_slabs(cv, gemm_tn_bytes(n, f_in, f_out));
     SENSEI_TRY(launch_row_broadcast(nullptr, dY.ptr, dY.ld, n, f_out, dP, fo4, SENSEI_ACT_NONE, s, mask, ldy, &side));
     // weight gradients, hop after hop: H_k = r (x) (A~ (c (x) H_(k-1)))
     SENSEI_TRY(launch_gemm_tn(X.ptr, X.ld, dP, fo4, n, f_in, f_out, dw_block(0), lddw, part, s));
@@ -1008,10 +1010,9 @@ int run_gatv2(const sensei_csr &A, const sensei_mat &X, const sensei_mat &Wl, co
 //   datt        = sum_i sum_j de_ij LeakyReLU(U_ij)
 //   dW_l = X_dst^T dTheta_l,  dW_r = X^T dTheta_r,  dX = dTheta_r W_r^T + [dTheta_l W_l^T on the first n_rows rows]
 // The three sums with a vector per entry are SpMM walks whose gathered row meets a vector of the output row (launch_v2_walk).
-// both weight gradients are one launch where both are sums over the same rows
+// both weight gradients are one launch where both are sums over the same rows; a product over fewer rows, or of fewer columns, may take more slabs
 size_t v2_tn_bytes(const sensei_csr &A, int f_in, int f_out) {
-    const size_t one = gemm_tn_bytes(A.n_cols, f_in, f_out), both = gemm_tn_bytes(A.n_cols, f_in, f_out, 2);
-    return one > both ? one : both;
+    return std::max({gemm_tn_bytes(A.n_cols, f_in, f_out), gemm_tn_bytes(A.n_cols, f_in, f_out, 2), gemm_tn_bytes(A.n_rows, f_in, f_out)});
 }
 
 size_t gatv2_bwd_ws(const sensei_csr &A, int f_in, int f_out) {
@@ -1057,7 +1058,7 @@ int run_gatv2_backward(const sensei_csr &A_in, const sensei_csr &At_in, const in
     float *Dcat = cv.take<float>((size_t)A.n_cols * ldd);
     float *carry = cv.take<float>(spmm_carry_bytes(A.nnz, fo) / sizeof(float)), *carry_r = cv.take<float>(spmm_carry_bytes(A.nnz, fo) / sizeof(float));
     float *Wcat = cv.take<float>((size_t)ldd * fi4);
-    double *part = cv.take<double>(v2_tn_bytes(A, f_in, f_out) / sizeof(double));
+    const Slabs part = take_slabs(cv, v2_tn_bytes(A, f_in, f_out));
     double *part_a = cv.take<double>(theta_t_vec_bytes(A.n_rows, f_out) / sizeof(double));
     float *dThR = Dcat, *dThL = Dcat + fo4;
 
@@ -1163,6 +1164,10 @@ int run_dotgat(const sensei_csr &A, const sensei_mat &X, const sensei_mat &Wq, c
 //   dW_q = X_dst^T dQ,  dW_k = X^T dK,  dW_v = X^T dV,  dX = dK W_k^T + dV W_v^T + [dQ W_q^T on the first n_rows rows].
 // Every step is a kernel the other layers already use: the per-entry dot products and the softmax backward of the GAT backward, weighted
 // SpMMs over the pattern (dQ) and its transpose (dK, dV).
+size_t dotgat_tn_bytes(const sensei_csr &A, int f_in, int d_k, int f_out) {   // dW_k, dW_v, dW_q one after the other
+    return std::max({gemm_tn_bytes(A.n_cols, f_in, d_k), gemm_tn_bytes(A.n_cols, f_in, f_out), gemm_tn_bytes(A.n_rows, f_in, d_k)});
+}
+
 size_t dotgat_bwd_ws(const sensei_csr &A, int f_in, int d_k, int f_out) {
     const size_t nz = (size_t)(A.nnz > 0 ? A.nnz : 1), dk = pad32(d_k), fo = pad32(f_out), dk4 = pad4(d_k), fo4 = pad4(f_out), fi4 = pad4(f_in);
     const int t = choose_chunk_nnz(A.nnz);
@@ -1177,7 +1182,7 @@ size_t dotgat_bwd_ws(const sensei_csr &A, int f_in, int d_k, int f_out) {
     b += align_up(dk * sizeof(float), 256);                                            // the scale, once per column
     b += spmm_carry_bytes(A.nnz, (int)(fo > dk ? fo : dk));
     b += align_up(ldd * fi4 * sizeof(float), 256);                                     // [W_k^T; W_v^T; W_q^T]
-    b += gemm_tn_bytes(A.n_cols, f_in, f_out > d_k ? f_out : d_k);
+    b += dotgat_tn_bytes(A, f_in, d_k, f_out);
     return b;
 }
 
@@ -1208,7 +1213,7 @@ int run_dotgat_backward(const sensei_csr &A_in, const sensei_csr &At_in, const i
     float *scale_vec = cv.take<float>((size_t)dk);
     float *carry = cv.take<float>(spmm_carry_bytes(A.nnz, fo > dk ? fo : dk) / sizeof(float));
     float *Wcat = cv.take<float>((size_t)ldd * fi4);
-    double *part = cv.take<double>(gemm_tn_bytes(A.n_cols, f_in, f_out > d_k ? f_out : d_k) / sizeof(double));
+    const Slabs part = take_slabs(cv, dotgat_tn_bytes(A, f_in, d_k, f_out));
     float *dK = Dcat, *dV = Dcat + dk4, *dQ = Dcat + dk4 + fo4;
 
     SideWork side;
@@ -1340,11 +1345,11 @@ size_t narrow_bwd_ws(const sensei_csr &A, int f_in, int n_heads) {
 // takes the room) the chunks are the ordinary ones (training passes with chunks of 256 / 512, us: 8 heads of 16 columns on 20 M entries 9,896 / 9,945, 17 of 2 on 12 M 6,721 / 6,750).
 int run_narrow_backward(const sensei_csr &A, const sensei_csr &At, const sensei_mat &X, const sensei_mat &W, const float *a_l, const float *a_r, int n_heads,
                         float slope, const float *Y, int64_t ldy, const sensei_mat &dY, int act, float *dTheta, int64_t ldt, float *da_l, float *da_r,
-                        float *Wt, int64_t ldwt, Carver cv, size_t room, double *slabs, size_t slab_bytes, hipStream_t s) {
+                        float *Wt, int64_t ldwt, Carver cv, size_t room, const Slabs &slabs, hipStream_t s) {
     const int f_in = (int)X.cols, d = (int)W.cols / n_heads, most = n_heads < kHeadsPerLaunch ? n_heads : kHeadsPerLaunch;
     const size_t nc = A.n_cols, nr = A.n_rows;
     int t = choose_head_chunk_nnz(A.nnz);
-    const bool in_slabs = std::max(narrow_pieces_bytes(A, n_heads, t), narrow_carry_bytes(A, n_heads, t)) <= slab_bytes;
+    const bool in_slabs = std::max(narrow_pieces_bytes(A, n_heads, t), narrow_carry_bytes(A, n_heads, t)) <= slabs.bytes;
     if (narrow_rest_bytes(A, f_in, n_heads, t) + (in_slabs ? 0 : narrow_carry_bytes(A, n_heads, t)) > room) t = choose_chunk_nnz(A.nnz);
     ChunkPlan plan = make_plan(A, cv, t), plan_t = make_plan(At, cv, t);
     SideWork side;
@@ -1354,7 +1359,7 @@ int run_narrow_backward(const sensei_csr &A, const sensei_csr &At, const sensei_
     float *s_l = cv.take<float>(most * nc), *s_r = cv.take<float>(most * nc), *ds_l = cv.take<float>(most * nc), *ds_r = cv.take<float>(most * nc);
     float *theta = cv.take<float>(most * nc * 32), *T = cv.take<float>(most * nr * 32);
     float4 *row = cv.take<float4>(most * (nr + 1));
-    Carver in = in_slabs ? Carver(slabs, slab_bytes) : cv;
+    Carver in = in_slabs ? Carver(slabs.p, slabs.bytes) : cv;
     float *carry = in.take<float>((size_t)most * plan_t.n_chunks * 32), *ds_carry = in.take<float>((size_t)most * plan_t.n_chunks);
     float *piece = carry;
     if (!in_slabs) cv = in;
@@ -1397,9 +1402,9 @@ int run_gat_backward(const sensei_csr &A, const sensei_csr &At, const int32_t *t
     Carver cv(ws, ws_bytes);
     if (!dtheta_out && heads_narrow(A, At, f_out)) {
         float *dTheta = cv.take<float>((size_t)A.n_cols * fo4), *Wt = cv.take<float>((size_t)fo4 * fi4);
-        double *part = cv.take<double>(gemm_tn_bytes(A.n_cols, f_in, f_out) / sizeof(double));
+        const Slabs part = take_slabs(cv, gemm_tn_bytes(A.n_cols, f_in, f_out));
         const int rc = run_narrow_backward(A, At, X, W, a_l, a_r, 1, slope, Y, ldy, dY, act, dTheta, fo4, da_l, da_r, dX ? Wt : nullptr, fi4,
-                                           cv, gat_bwd_ws(A, &At, f_in, f_out) - cv.used, part, gemm_tn_bytes(A.n_cols, f_in, f_out), s);
+                                           cv, gat_bwd_ws(A, &At, f_in, f_out) - cv.used, part, s);
         if (rc != SENSEI_OK) return rc;
         SENSEI_TRY(launch_gemm_tn(X.ptr, X.ld, dTheta, fo4, A.n_cols, f_in, f_out, dW, lddw, part, s));
         if (dX) SENSEI_TRY(launch_gemm(dTheta, fo4, Wt, fi4, dX, lddx, A.n_cols, f_out, f_in, f_in, SENSEI_ACT_NONE, s));
@@ -1424,7 +1429,7 @@ int run_gat_backward(const sensei_csr &A, const sensei_csr &At, const int32_t *t
     const int64_t ldt = dtheta_out ? ld_dtheta : fo4;
     float *carry = cv.take<float>(spmm_carry_bytes(A.nnz, fo32) / sizeof(float));
     float *Wt = cv.take<float>((size_t)fo4 * fi4);
-    double *part = cv.take<double>(gemm_tn_bytes(A.n_cols, f_in, f_out) / sizeof(double));
+    const Slabs part = take_slabs(cv, gemm_tn_bytes(A.n_cols, f_in, f_out));
     double *part_a = cv.take<double>(theta_t_vec_bytes(A.n_cols, f_out) / sizeof(double));
 
     SideWork side;
@@ -1535,11 +1540,10 @@ int run_gat_backward_heads(const sensei_csr &A, const sensei_csr &At, const int3
     Carver cv(ws, ws_bytes);
     float *dTh = cv.take<float>((size_t)A.n_cols * fo4);
     float *Wt = cv.take<float>((size_t)fo4 * fi4);
-    double *part = cv.take<double>(gemm_tn_bytes(A.n_cols, f_in, f_out) / sizeof(double));
+    const Slabs part = take_slabs(cv, gemm_tn_bytes(A.n_cols, f_in, f_out));
     if (heads_narrow(A, At, d)) {
         const int rc = run_narrow_backward(A, At, X, W, a_l, a_r, n_heads, slope, Y, ldy, dY, act, dTh, fo4, da_l, da_r, dX ? Wt : nullptr,
-                                           fi4, cv, std::max(gat_bwd_ws(A, &At, f_in, d), narrow_bwd_ws(A, f_in, n_heads)), part,
-                                           gemm_tn_bytes(A.n_cols, f_in, f_out), s);
+                                           fi4, cv, std::max(gat_bwd_ws(A, &At, f_in, d), narrow_bwd_ws(A, f_in, n_heads)), part, s);
         if (rc != SENSEI_OK) return rc;
         SENSEI_TRY(launch_gemm_tn(X.ptr, X.ld, dTh, fo4, A.n_cols, f_in, f_out, dW, lddw, part, s));
         if (dX) SENSEI_TRY(launch_gemm(dTh, fo4, Wt, fi4, dX, lddx, A.n_cols, f_out, f_in, f_in, SENSEI_ACT_NONE, s));

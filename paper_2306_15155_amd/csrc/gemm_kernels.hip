@@ -2085,10 +2085,11 @@ size_t gemm_tn_bytes(int64_t k, int m, int n, int segs) {
 }
 
 hipError_t launch_gemm_tn(const float *A, int64_t lda, const float *B, int64_t ldb, int64_t k, int m, int n, float *C, int64_t ldc,
-                          double *part, hipStream_t s, int segs, int64_t b_seg, int64_t c_seg) {
+                          const Slabs &part, hipStream_t s, int segs, int64_t b_seg, int64_t c_seg) {
     if (m <= 0 || n <= 0) return hipSuccess;
+    if (gemm_tn_bytes(k, m, n, segs) > part.bytes) return hipErrorInvalidValue;
     GemmTnArgs g;
-    g.A = A; g.B = B; g.part = part; g.lda = lda; g.ldb = ldb; g.k = k > 0 ? k : 0; g.m = m; g.n = n;
+    g.A = A; g.B = B; g.part = part.p; g.lda = lda; g.ldb = ldb; g.k = k > 0 ? k : 0; g.m = m; g.n = n;
     g.segs = segs; g.b_seg = b_seg;
     g.n_bn = (n + 127) / 128;
     g.n_tiles = ((m + 127) / 128) * g.n_bn * segs;
@@ -2108,7 +2109,7 @@ hipError_t launch_gemm_tn(const float *A, int64_t lda, const float *B, int64_t l
     else if (vb) hipLaunchKernelGGL((k_gemm_tn<1, 4>), grid, dim3(kThreads), 0, s, g);
     else hipLaunchKernelGGL((k_gemm_tn<1, 1>), grid, dim3(kThreads), 0, s, g);
     const long long mn = (long long)m * n * segs;
-    hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((mn + kSumElems - 1) / kSumElems)), dim3(kSumElems * kSumLanes), 0, s, part, splits, mn, n,
+    hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((mn + kSumElems - 1) / kSumElems)), dim3(kSumElems * kSumLanes), 0, s, part.p, splits, mn, n,
                        segs, C, (long long)ldc, (long long)c_seg);
     return hipGetLastError();
 }

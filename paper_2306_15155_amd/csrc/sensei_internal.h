@@ -342,12 +342,14 @@ hipError_t launch_gemm(const float *A, int64_t lda, const float *W, int64_t ldw,
 hipError_t launch_gemv2(const float *A, int64_t lda, int64_t n, int k, const float *v1, const float *v2, float *y1,
                         float *y2, hipStream_t s, bool a_sliced = false);
 
-// C[m x n] (row-major, ldc) = A^T . B with A stored k x m and B stored k x n; `part` holds gemm_tn_bytes(k, m, n) bytes.
+// C[m x n] (row-major, ldc) = A^T . B with A stored k x m and B stored k x n; `part` holds gemm_tn_bytes(k, m, n, segs) bytes or more (fewer: an error).
+// gemm_tn_bytes grows with none of k, m and n alone: scratch that several products use one after the other is as large as the largest of theirs.
 // The k range is cut into slabs whose partial products are kept and added in fp64, in slab order (deterministic).
 // segs > 1: as many products with the same A in one launch, B's columns h * b_seg .. + n to C + h * c_seg.
+struct Slabs { double *p; size_t bytes; };
 size_t gemm_tn_bytes(int64_t k, int m, int n, int segs = 1);
 hipError_t launch_gemm_tn(const float *A, int64_t lda, const float *B, int64_t ldb, int64_t k, int m, int n, float *C, int64_t ldc,
-                          double *part, hipStream_t s, int segs = 1, int64_t b_seg = 0, int64_t c_seg = 0);
+                          const Slabs &part, hipStream_t s, int segs = 1, int64_t b_seg = 0, int64_t c_seg = 0);
 hipError_t launch_transpose(const float *W, int64_t ldw, int rows, int cols, float *Wt, int64_t ldt, hipStream_t s, int count = 1, int64_t w_step = 0,
                             int64_t wt_step = 0);
 

@@ -151,3 +151,37 @@ def test_products_with_the_slope_are_not_rounded(ctx, m, f_out):
     dW_l = ctx.gatv2_backward(A.s, At.s, ctx.transpose_positions(A.s, At.s), torch.eye(2 * m, device="cuda"), dev(W_l), dev(W_r), dev(att), dev(dY), neg_slope=0.7)[1]
     u, slope = dY[:, 0].astype(np.float64), np.float64(np.float32(0.7))
     assert np.array_equal(dW_l[:m, 0].cpu().numpy(), (u / 2 - u / 2 * slope).astype(np.float32))
+
+
+# Scratch of exactly the size that the query asks for.  The weight gradients share their slabs: keys of 64 columns take more of them than values of 114, keys of 128 more than
+# values of 129, and destinations below 4,096 more than the sources above.
+@pytest.mark.parametrize("n_rows,n_cols,f_in,d_k,f_out", [(7_000, 7_000, 576, 64, 114), (6_000, 6_000, 300, 128, 129), (3_000, 6_000, 700, 128, 300), (500, 700, 20, 64, 33)])
+def test_slabs_of_several_weight_gradients(ctx, n_rows, n_cols, f_in, d_k, f_out):
+    g = rect_block(n_rows, n_rows, n_cols, 3)
+    A, At = DeviceCSR(g), DeviceCSR(synth.transpose(g))
+    pos = ctx.transpose_positions(A.s, At.s)
+    X = np.round(synth.uniform(7, 1, (n_cols, f_in), -1.0, 1.0) * 8) / 8   # on grids: the projections are exact, the derivatives of the score jump alike
+    Wq, Wk, Wv, Wl = (np.round(synth.uniform(7, 2 + i, (f_in, w), -0.5, 0.5) * 16) / 64 for i, w in enumerate((d_k, d_k, f_out, f_out)))
+    att, dY = np.round(synth.normal(7, 6, (f_out,), 0.0, 0.2) * 64) / 64, synth.normal(7, 7, (n_rows, f_out))
+    X, Wq, Wk, Wv, Wl, att = (a.astype(np.float32) for a in (X, Wq, Wk, Wv, Wl, att))
+    L, m, need = binding.lib(), binding.mat_struct, ctypes.c_size_t()
+    x, q, k, v, l, a, dy = (dev(t) for t in (X, Wq, Wk, Wv, Wl, att, dY))
+    args = (n_rows, n_cols, g.row_ptr, g.col_idx, X)
+
+    def checked(call, want, names):
+        room = torch.full((need.value + (1 << 22),), 0xFF, dtype=torch.uint8, device="cuda")
+        at = -room.data_ptr() % 256
+        outs = [torch.empty(w.shape, device="cuda") for w in want]
+        binding._check(call([t.data_ptr() for t in outs], room.data_ptr() + at), "backward")
+        for got, ref, what in zip(outs, want, names):
+            assert_close(got, ref, what=what)
+        assert bool((room[at + need.value:] == 0xFF).all())
+
+    binding._check(L.sensei_dotgat_backward_workspace(ctypes.byref(A.s), f_in, d_k, f_out, ctypes.byref(need)), "workspace")
+    checked(lambda o, w: L.sensei_dotgat_backward(ctx._h, ctypes.byref(A.s), ctypes.byref(At.s), pos.data_ptr(), m(x), m(q), m(k), m(v), 0.01, None, f_out, m(dy), ACT_NONE,
+                                                  o[0], f_in, o[1], d_k, o[2], d_k, o[3], f_out, w, need.value, binding._stream()),
+            oracle.dotgat_backward(*args, Wq, Wk, Wv, 0.01, dY), ("dX", "dW_q", "dW_k", "dW_v"))
+    binding._check(L.sensei_gatv2_backward_workspace(ctypes.byref(A.s), f_in, f_out, ctypes.byref(need)), "workspace")
+    checked(lambda o, w: L.sensei_gatv2_backward(ctx._h, ctypes.byref(A.s), ctypes.byref(At.s), pos.data_ptr(), m(x), m(l), m(v), a.data_ptr(), 0.25, None, f_out, m(dy), ACT_NONE,
+                                                 o[0], f_in, o[1], f_out, o[2], f_out, o[3], w, need.value, binding._stream()),
+            oracle.gatv2_backward(*args, Wl, Wv, att, dY, slope=0.25), ("dX", "dW_l", "dW_r", "datt"))

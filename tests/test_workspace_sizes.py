@@ -43,3 +43,22 @@ def test_gcn_backward(n, f_in, f_out, least, most):
     need = ctypes.c_size_t()
     assert binding.lib().sensei_gcn_backward_workspace(ctypes.byref(_csr(n, n, 4 * n)), f_in, f_out, 0, ctypes.byref(need)) == 0
     assert least <= need.value <= most
+
+
+# The weight gradients of a layer are formed one after the other in the same slabs.  The one of fewer columns (keys of 64, values of 114), or over fewer rows (sampled
+# blocks), may take the larger ones.
+@pytest.mark.parametrize("n_rows,n_cols,nnz,f_in,d_k,f_out,least,most", [
+    (207_936, 207_936, 770_000, 576, 64, 114, 570_136_576, 620_953_600), (3_000, 100_000, 60_000, 700, 128, 130, 311_209_984, 324_112_384),
+    (6_000, 6_000, 40_000, 300, 128, 129, 51_480_320, 54_470_912)])
+def test_dotgat_backward(n_rows, n_cols, nnz, f_in, d_k, f_out, least, most):
+    need = ctypes.c_size_t()
+    assert binding.lib().sensei_dotgat_backward_workspace(ctypes.byref(_csr(n_rows, n_cols, nnz)), f_in, d_k, f_out, ctypes.byref(need)) == 0
+    assert least <= need.value <= most
+
+
+@pytest.mark.parametrize("n_rows,n_cols,nnz,f_in,f_out,least,most", [(4_000, 100_000, 60_000, 700, 400, 586_574_336, 586_574_336),
+                                                                     (3_000, 6_000, 40_000, 700, 300, 111_214_336, 112_894_208)])
+def test_gatv2_backward(n_rows, n_cols, nnz, f_in, f_out, least, most):
+    need = ctypes.c_size_t()
+    assert binding.lib().sensei_gatv2_backward_workspace(ctypes.byref(_csr(n_rows, n_cols, nnz)), f_in, f_out, ctypes.byref(need)) == 0
+    assert least <= need.value <= most
