@@ -1415,15 +1415,18 @@ __device__ __forceinline__ void flat_edge_op(const NnzArgs &a, const float *__re
     if (chunk >= a.n_chunks) return;
     int *rows = lds.row[threadIdx.x >> 6];
     const ChunkSpan<PER> span(a, chunk);
-    float x[PER], y[PER];
+    float y[PER];
 #pragma unroll
     for (int u = 0; u < PER; ++u) y[u] = col_vec[a.col_idx[span.at(u, lane)]];
     const FlatChunk<PER> c = flat_rows<PER>(a, chunk, lane, rows, [](int, bool) {});
     if (c.lo >= c.hi) return;
-    int rw[PER];
+    // one value at a time: with all eight read in one branch (row_values) 115 M entries of 494 a row take 365 us instead of 327, 100 M of 1,021 421 instead of
+    // 394, and patterns of short rows 3 to 5 % less (2.1 M entries of 21 12.8 instead of 13.4 us)
+    const bool in_lanes = c.i1 - c.i_first <= 64;
+    const float mine = in_lanes && c.i_first + lane < c.i1 ? row_vec[c.i_first + lane] : 0.f;
+    float x[PER];
 #pragma unroll
-    for (int u = 0; u < PER; ++u) rw[u] = rows[u * 64 + lane];
-    row_values<PER>(c, lane, row_vec, rw, x);
+    for (int u = 0; u < PER; ++u) x[u] = in_lanes ? lane_read((rows[u * 64 + lane] - c.i_first) * 4, mine) : row_vec[rows[u * 64 + lane]];
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
         const int k = c.lo + u * 64 + lane;
